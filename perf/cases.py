@@ -214,3 +214,88 @@ def tolerance(case):
     if case["kind"] == "train":
         return {"rel": 1.5e-2, "max": 0.25}
     return {"rel": 1e-2, "max": 5e-2}
+
+
+# Token pairs of all heads up to which `exact` is computed (a few seconds; a training step costs three times more).
+_EXACT_PAIRS = 5.0e10
+
+
+def _half_widths(c):
+    """Largest |k - l| that frames at distance 0 .. f-1 see of each other, -1: nothing."""
+    s, num, den = c["tokens_per_frame"], c["width_num"], c["width_den"]
+    hw = []
+    for d in range(c["frames"]):
+        b = 1 << max(d.bit_length() - 1, 0)
+        w = s if d < 2 else min(s, s * num // (den * b))
+        hw.append(w - 1 if w >= 1 else (0 if d % -(-b * den // (s * num)) == 0 else -1))
+    return hw
+
+
+def _seen(c, r0, r1, hw):
+    """[r1 - r0, N] bool: which keys the tokens r0 .. r1-1 attend (r0 is the first token of a block)."""
+    n, s, blk = _n_tokens(c), c["tokens_per_frame"], c["block"]
+    if c["dense"]:
+        return torch.ones((r1 - r0, n), dtype=torch.bool, device=DEVICE)
+    pos = torch.arange(n, dtype=torch.int32, device=DEVICE)
+    frame, text = pos // s, pos >= c["frames"] * s
+    at = pos - frame * s
+    distance = (frame[r0:r1, None] - frame[None]).abs().clamp(max=c["frames"] - 1)
+    vis = (at[r0:r1, None] - at[None]).abs() <= hw[distance]
+    vis |= (frame < c["sink_frames"])[None] | text[None] | text[r0:r1, None]
+    if c["token_rule"]:
+        return vis
+    nq, nk = -(-(r1 - r0) // blk), -(-n // blk)  # a block pair is listed if any token pair in it is visible
+    padded = torch.zeros((nq * blk, nk * blk), dtype=torch.bool, device=DEVICE)
+    padded[:r1 - r0, :n] = vis
+    listed = padded.view(nq, blk, nk, blk).any(dim=3).any(dim=1)
+    return listed.repeat_interleave(blk, 0).repeat_interleave(blk, 1)[:r1 - r0, :n]
+
+
+def exact(case, seed):
+    """The outputs of `run` in float64: the masks from their definition over token pairs, plain softmax attention."""
+    c = case
+    B, H, N, D = c["B"], c["H"], _n_tokens(c), c["D"]
+    train, fp8 = c["kind"] == "train", c["kind"] == "fp8"
+    if float(N) * N * B * H * (3.0 if train else 1.0) > _EXACT_PAIRS:
+        return None
+    gen = torch.Generator(device=DEVICE).manual_seed(seed)
+    x = {}
+    for name in ("q", "k", "v") + (("dout",) if train else ()):
+        x[name] = _empty(c).normal_(0.0, c["gain"] if name == "q" else 1.0, generator=gen)
+    res = {"out": torch.empty((B, H, N, D), dtype=torch.float64, device=DEVICE),
+           "lse": torch.empty((B, H, N), dtype=torch.float64, device=DEVICE)}
+    if train:
+        res.update({n: torch.zeros((B, H, N, D), dtype=torch.float64, device=DEVICE) for n in ("dq", "dk", "dv")})
+    if fp8:  # codes: x / scale in 8 bits (4 exponent, 3 mantissa bits), one scale per block; the scores are those of the codes
+        blk = c["block"]
+        nb = -(-N // blk)
+        for t in ("q", "k"):
+            wide = torch.zeros((B, H, nb * blk, D), dtype=torch.float32, device=DEVICE)
+            wide[:, :, :N] = x[t].float()
+            amax = wide.abs().view(B, H, nb, blk * D).amax(dim=3)
+            scales = torch.where(amax > 0, amax / 448.0, torch.ones_like(amax))
+            per_token = scales.repeat_interleave(blk, 2)[:, :, :N, None]
+            codes = (wide[:, :, :N] / per_token).clamp(-448.0, 448.0).to(torch.float8_e4m3fn)
+            res[t + "8"], res[t + "s"] = codes.view(torch.uint8), scales
+            x[t] = codes.double() * per_token.double()
+    scale = 1.0 / math.sqrt(D)
+    hw = torch.tensor(_half_widths(c), dtype=torch.int32, device=DEVICE)
+    step = 8 * c["block"]
+    for b in range(B):
+        for r0 in range(0, N, step):
+            r1 = min(N, r0 + step)
+            hidden = ~_seen(c, r0, r1, hw)
+            for h in range(H):
+                q, k, v = x["q"][b, h, r0:r1].double(), x["k"][b, h].double(), x["v"][b, h].double()
+                p = (scale * (q @ k.T)).masked_fill_(hidden, -math.inf)
+                lse = torch.logsumexp(p, dim=1)
+                p = p.sub_(lse[:, None]).exp_()
+                out = p @ v
+                res["out"][b, h, r0:r1], res["lse"][b, h, r0:r1] = out, lse
+                if train:
+                    g = x["dout"][b, h, r0:r1].double()
+                    ds = p * (g @ v.T - (g * out).sum(dim=1, keepdim=True))
+                    res["dv"][b, h] += p.T @ g
+                    res["dq"][b, h, r0:r1] = scale * (ds @ k)
+                    res["dk"][b, h] += scale * (ds.T @ q)
+    return res
