@@ -107,14 +107,8 @@ __global__ void __launch_bounds__(2 * BLK, 1) radial_bwd_dkdv_kernel(const BwdAr
   const int i16 = lane & 15;
   const int half16 = (lane >> 4) & 1;
 
-  // work item: XCD x owns the key blocks [slice_t[x], slice_t[x+1]) of every (batch, head)
-  const int32_t xcd = blockIdx.x & 7;
-  const int32_t s0 = a.slice_t[xcd];
-  const int32_t slice_len = a.slice_t[xcd + 1] - s0;
-  const int64_t idx = blockIdx.x >> 3;
-  if (slice_len <= 0 || idx >= (int64_t)slice_len * a.B * a.H) return;
-  const int32_t bh = (int32_t)(idx / slice_len);
-  const int32_t kb = s0 + (int32_t)(idx % slice_len);
+  int32_t bh, kb;
+  if (!work_item(a.work_t, bh, kb)) return;
   const int32_t b = bh / a.H, h = bh % a.H;
 
   const __bf16* qp = (const __bf16*)a.q.ptr + (int64_t)b * a.q.sb + (int64_t)h * a.q.sh;
@@ -419,14 +413,8 @@ __global__ void __launch_bounds__(2 * BLK, 2) radial_bwd_dq_kernel(const BwdArgs
   const int i16 = lane & 15;
   const int half16 = (lane >> 4) & 1;
 
-  // work item: XCD x owns the query blocks [slice[x], slice[x+1]) of every (batch, head)
-  const int32_t xcd = blockIdx.x & 7;
-  const int32_t s0 = a.slice[xcd];
-  const int32_t slice_len = a.slice[xcd + 1] - s0;
-  const int64_t idx = blockIdx.x >> 3;
-  if (slice_len <= 0 || idx >= (int64_t)slice_len * a.B * a.H) return;
-  const int32_t bh = (int32_t)(idx / slice_len);
-  const int32_t qb = s0 + (int32_t)(idx % slice_len);
+  int32_t bh, qb;
+  if (!work_item(a.work, bh, qb)) return;
   const int32_t b = bh / a.H, h = bh % a.H;
 
   const __bf16* qp = (const __bf16*)a.q.ptr + (int64_t)b * a.q.sb + (int64_t)h * a.q.sh;
@@ -631,9 +619,9 @@ int launch(const BwdArgs& a, hipStream_t stream) {
   const int64_t rows = (int64_t)a.B * a.H * a.N;
   const int rows_per_block = 256 / (D / 8);
   const int64_t prep_grid = (rows + rows_per_block - 1) / rows_per_block;
-  const int64_t grid_kv = 8LL * a.B * a.H * a.max_slice_t;
-  const int64_t grid_q = 8LL * a.B * a.H * a.max_slice;
-  if (prep_grid > 0x7fffffffLL || grid_kv > 0x7fffffffLL || grid_q > 0x7fffffffLL)
+  const int64_t grid_kv = work_grid(a.work_t, a.n_blocks);
+  const int64_t grid_q = work_grid(a.work, a.n_blocks);
+  if (prep_grid > 0x7fffffffLL || work_grid_bound(a.work_t) > 0x7fffffffLL || work_grid_bound(a.work) > 0x7fffffffLL)
     return fail(RADIAL_ESHAPE, "problem too large for one launch");
   // The dK/dV kernel needs more dynamic LDS than the default limit.  The attribute belongs to the
   // (device, kernel) pair; it is set once per device and template instance.  Setting it twice is

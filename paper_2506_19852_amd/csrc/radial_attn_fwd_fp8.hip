@@ -100,16 +100,8 @@ __global__ void __launch_bounds__(kThreads, 3) radial_fwd_fp8_kernel(const Fp8Fw
   const int lq = lane & 31;
   const int g = lane >> 5;
 
-  // Workgroup -> (batch*head, query block): as in the bf16 kernel (8 slices of equal list weight,
-  // XCD x takes slice (x + head) mod 8, the XCDs move from head to head together).
-  const int32_t xcd = blockIdx.x & 7;
-  const int64_t idx = blockIdx.x >> 3;
-  const int32_t bh = (int32_t)(idx / a.max_slice);
-  const int32_t pos = (int32_t)(idx % a.max_slice);
-  const int32_t sl = (xcd + bh) & 7;
-  const int32_t s0 = a.slice[sl];
-  if (pos >= a.slice[sl + 1] - s0) return;
-  const int32_t qb = s0 + pos;
+  int32_t bh, qb;
+  if (!work_item(a.work, bh, qb)) return;
   const int32_t b = bh / a.H, h = bh % a.H;
 
   const uint8_t* qp = a.q8 + (int64_t)bh * a.N * D;
@@ -354,8 +346,8 @@ int launch_quantize_fp8(int32_t B, int32_t H, int32_t N, int32_t Dh, const Tenso
 }
 
 int launch_fwd_fp8(const Fp8FwdArgs& a, hipStream_t stream) {
-  const int64_t grid = 8LL * a.B * a.H * a.max_slice;
-  if (grid > 0x7fffffffLL) return fail(RADIAL_ESHAPE, "B*H*n_blocks is too large for one launch");
+  const int64_t grid = work_grid(a.work, a.n_blocks);
+  if (work_grid_bound(a.work) > 0x7fffffffLL) return fail(RADIAL_ESHAPE, "B*H*n_blocks is too large for one launch");
   if (grid == 0) return RADIAL_OK;
   radial_fwd_fp8_kernel<<<dim3((unsigned)grid), dim3(kThreads), 0, stream>>>(a);
   RADIAL_HIP_TRY(hipGetLastError());

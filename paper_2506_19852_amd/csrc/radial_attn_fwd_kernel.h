@@ -80,21 +80,9 @@ __global__ void __launch_bounds__(2 * BLK, 2) radial_fwd_kernel(const FwdArgs a)
   const int lq = lane & 31;   // query column / K row inside a 32-tile
   const int g = lane >> 5;    // which half of the 16-wide MFMA k-slice this lane feeds
 
-  // Workgroup -> work item.  Consecutive workgroup ids go to different XCDs.  The query blocks are
-  // cut into 8 slices of equal list weight; for head bh, XCD x takes slice (x + bh) mod 8 and the
-  // XCDs move from head to head together, so all of them work on the same head at the same time
-  // (its K/V stay in the shared last-level cache), neighbouring workgroups of an XCD share K/V
-  // tiles in that XCD's L2, and every XCD gets every slice equally often (slices of equal weight
-  // do not take exactly equal time).
   const uint64_t t_begin = kTrace ? __builtin_amdgcn_s_memrealtime() : 0;
-  const int32_t xcd = blockIdx.x & 7;
-  const int64_t idx = blockIdx.x >> 3;
-  const int32_t bh = (int32_t)(idx / a.max_slice);
-  const int32_t pos = (int32_t)(idx % a.max_slice);
-  const int32_t sl = (xcd + bh) & 7;
-  const int32_t s0 = a.slice[sl];
-  if (pos >= a.slice[sl + 1] - s0) return;
-  const int32_t qb = s0 + pos;
+  int32_t bh, qb;
+  if (!work_item(a.work, bh, qb)) return;
   const int32_t b = bh / a.H, h = bh % a.H;
 
   const __bf16* qp = (const __bf16*)a.q.ptr + (int64_t)b * a.q.sb + (int64_t)h * a.q.sh;
@@ -374,8 +362,8 @@ __global__ void __launch_bounds__(2 * BLK, 2) radial_fwd_kernel(const FwdArgs a)
 // Launches the kernel instance for (D, block, token rule); kTrace selects the diagnostics build.
 template <int D, int BLK, bool kTrace>
 int launch(const FwdArgs& a, hipStream_t stream) {
-  const int64_t grid = 8LL * a.B * a.H * a.max_slice;
-  if (grid > 0x7fffffffLL) return fail(RADIAL_ESHAPE, "B*H*n_blocks is too large for one launch");
+  const int64_t grid = work_grid(a.work, a.n_blocks);
+  if (work_grid_bound(a.work) > 0x7fffffffLL) return fail(RADIAL_ESHAPE, "B*H*n_blocks is too large for one launch");
   if (grid == 0) return RADIAL_OK;
   if (a.rule.exact)
     radial_fwd_kernel<D, BLK, true, kTrace><<<dim3((unsigned)grid), dim3(Tile<D, BLK>::kThreads), 0, stream>>>(a);

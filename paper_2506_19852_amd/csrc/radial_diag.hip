@@ -56,7 +56,7 @@ using namespace radial;
 
 extern "C" int64_t radial_attn_fwd_trace_records(int32_t B, int32_t H, const radial_mask* mask) {
   if (!mask || B < 1 || H < 1) return 0;
-  return 8LL * B * H * mask->max_slice;
+  return work_grid_bound(make_work_map(mask, false, B * H, 64));
 }
 
 extern "C" int radial_attn_fwd_trace(int32_t B, int32_t H, int32_t N, int32_t D, radial_tensor q, radial_tensor k,
@@ -65,8 +65,9 @@ extern "C" int radial_attn_fwd_trace(int32_t B, int32_t H, int32_t N, int32_t D,
   if (!trace) return fail(RADIAL_EINVAL, "trace is NULL");
   FwdArgs a;
   if (int rc = make_fwd_args(B, H, N, D, q, k, v, out, lse, mask, scale, &a)) return rc;
-  if (trace_records < fwd_grid(a))
-    return fail(RADIAL_ESHAPE, "trace holds %lld records, %lld needed", (long long)trace_records, (long long)fwd_grid(a));
+  const int64_t need = radial_attn_fwd_trace_records(B, H, mask);
+  if (trace_records < need)
+    return fail(RADIAL_ESHAPE, "trace holds %lld records, %lld needed", (long long)trace_records, (long long)need);
   a.wg_trace = trace;
   return fwd::launch_any<true>(D, mask->block, a, (hipStream_t)hip_stream);
 }

@@ -27,6 +27,9 @@ struct radial_mask {
   // in the shared last-level cache) and carry equal weight.  Same for key blocks (backward).
   int32_t* d_slice = nullptr;    // [9]
   int32_t* d_slice_t = nullptr;  // [9]
+  // Blocks by falling list length (null above kMaxOrdered blocks): the work order of short launches.
+  int32_t* d_order = nullptr;    // [n_blocks]
+  int32_t* d_order_t = nullptr;  // [n_blocks]
   int32_t max_slice = 0;         // longest slice, in blocks (host copy, sizes the grid)
   int32_t max_slice_t = 0;
   int32_t tokens_per_frame = 0;  // geometry of a radial mask (0 for dense / caller-supplied lists)
@@ -77,6 +80,45 @@ inline TokenRule make_token_rule(const radial_mask* m) {
   return r;
 }
 
+// Which (batch*head, block) a workgroup works on: the first `sliced` heads by slices, the others by
+// falling list length.
+struct WorkMap {
+  const int32_t* slice;  // [9]
+  const int32_t* order;  // [n_blocks]; null only if ordered == 0
+  int32_t max_slice;
+  int32_t sliced, ordered;  // heads; sum B * H
+};
+
+constexpr int32_t kMaxOrdered = 16384;  // blocks up to which a mask carries the order
+
+// Slices keep an XCD's workgroups on neighbouring blocks of one head, but the launch ends on whatever
+// lists come last in the last heads: with few heads, or rows that list everything (text tokens), compute
+// units idle there.  Longest lists first, dealt over the XCDs with all heads of a block side by side,
+// ends on short lists and gives every XCD the same mix; it costs locality, since the K and V of all those
+// heads are walked at once.  So it takes the whole launch while K and V fit the 256 MB last-level cache
+// (3 heads x 119 026 tokens with text: forward 9.79 -> 8.52 ms; 5 heads x 14 040: 0.638 -> 0.567 ms;
+// forward+backward of 5 x 14 040: 2.41 -> 2.23 ms; ties at 10 x 32 760 = 160 MB), and beyond that only the
+// last heads of the launch, up to 128 MB (40 x 32 760: forward 13.7 -> 13.45 ms, 20 x 32 760 forward+backward
+// 31.2 -> 30.5 ms; a tail of 256 MB gains nothing).  All heads by length at 24 x 118 800 (1.4 GB): 77.5 -> 89.7 ms.
+constexpr int64_t kOrderedWholeBytes = 256 << 20, kOrderedTailBytes = 128 << 20;
+
+inline WorkMap make_work_map(const radial_mask* m, bool transposed, int32_t heads, int32_t D) {
+  WorkMap w;
+  w.slice = transposed ? m->d_slice_t : m->d_slice;
+  w.order = transposed ? m->d_order_t : m->d_order;
+  w.max_slice = transposed ? m->max_slice_t : m->max_slice;
+  const int64_t per_head = 4LL * D * m->n_tokens;  // K and V of one head
+  const int64_t tail = kOrderedTailBytes / per_head;
+  w.ordered = !w.order ? 0 : (per_head * heads <= kOrderedWholeBytes || tail > heads ? heads : (int32_t)tail);
+  w.sliced = heads - w.ordered;
+  return w;
+}
+// Workgroups of a launch, and the most that any division of the heads could start.
+inline int64_t work_grid_bound(const WorkMap& w) { return 8LL * (w.sliced + w.ordered) * w.max_slice; }
+inline int64_t work_grid(const WorkMap& w, int32_t n_blocks) {
+  return 8LL * w.sliced * w.max_slice + (int64_t)w.ordered * n_blocks;
+}
+
 struct TensorArg {
   const void* ptr;
   int64_t sb, sh, sn;  // element strides
@@ -87,8 +129,7 @@ struct FwdArgs {
   float* lse;  // may be null
   const int32_t* row_ptr;
   const int32_t* col_idx;
-  const int32_t* slice;  // [9] query-block partition over the XCDs
-  int32_t max_slice;
+  WorkMap work;
   int32_t B, H, N, n_blocks;
   float scale;
   TokenRule rule;
@@ -99,8 +140,6 @@ int launch_fwd(int D, int block, const FwdArgs& a, hipStream_t stream);
 // Argument checks of a forward call (as radial_attn_fwd documents them); fills *a, wg_trace = null.
 int make_fwd_args(int32_t B, int32_t H, int32_t N, int32_t D, radial_tensor q, radial_tensor k, radial_tensor v,
                   radial_tensor out, float* lse, const radial_mask* mask, float scale, FwdArgs* a);
-// Workgroups one forward launch of this shape starts (the number of trace records).
-int64_t fwd_grid(const FwdArgs& a);
 // Launches a kernel that only issues dependent bf16 MFMAs from registers; *flops_out (host)
 // receives the floating-point operations it performs.
 int launch_mfma_probe(int64_t iters, hipStream_t stream, double* flops_out);
@@ -116,8 +155,7 @@ struct Fp8FwdArgs {
   float* lse;  // may be null
   const int32_t* row_ptr;
   const int32_t* col_idx;
-  const int32_t* slice;
-  int32_t max_slice;
+  WorkMap work;
   int32_t B, H, N, n_blocks;
   float scale;
 };
@@ -133,9 +171,8 @@ struct BwdArgs {
   const int32_t* col_idx;
   const int32_t* col_ptr;
   const int32_t* row_idx;
-  const int32_t* slice;    // [9] query-block partition over the XCDs
-  const int32_t* slice_t;  // [9] key-block partition over the XCDs
-  int32_t max_slice, max_slice_t;
+  WorkMap work;    // query blocks
+  WorkMap work_t;  // key blocks
   int32_t B, H, N, n_blocks;
   float scale;
   TokenRule rule;

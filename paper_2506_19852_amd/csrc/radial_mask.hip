@@ -240,7 +240,22 @@ __global__ void __launch_bounds__(kThreads) transpose_fill_kernel(const int32_t*
 // equal work, one per XCD.  kItemCost stands for the fixed cost of a work item (loading Q,
 // storing O) in units of one listed block.
 constexpr int kItemCost = 4;
-__global__ void slice_kernel(const int32_t* ptr, int32_t nb, int32_t* slice) {
+// Workgroup 0 cuts the slices; the others, a wave per block, place the block at its rank by falling
+// list length (equal lengths: by index) if there is an order to fill.
+__global__ void __launch_bounds__(kThreads) partition_kernel(const int32_t* ptr, int32_t nb, int32_t* slice, int32_t* order) {
+  if (blockIdx.x > 0) {
+    const int32_t b = (blockIdx.x - 1) * (kThreads / 64) + (threadIdx.x >> 6);
+    if (b >= nb) return;
+    const int32_t len = ptr[b + 1] - ptr[b];
+    int32_t ahead = 0;
+    for (int32_t j = threadIdx.x & 63; j < nb; j += 64) {
+      const int32_t other = ptr[j + 1] - ptr[j];
+      ahead += (other > len || (other == len && j < b)) ? 1 : 0;
+    }
+    for (int off = 32; off > 0; off >>= 1) ahead += __shfl_xor(ahead, off);
+    if ((threadIdx.x & 63) == 0) order[ahead] = b;
+    return;
+  }
   const int k = threadIdx.x;
   if (k > 8) return;
   const long long total = (long long)ptr[nb] + (long long)kItemCost * nb;
@@ -264,19 +279,27 @@ int check_common(int64_t n_tokens, int32_t block, uint32_t flags) {
 }
 
 // Device storage of a mask is three allocations: `meta` (two 64-bit totals and the two launch
-// partitions), `ptrs` (row_ptr and, with the transposed lists, col_ptr) and `idx` (col_idx and
+// partitions), `ptrs` (row_ptr and its order and, with the transposed lists, col_ptr and its order) and `idx` (col_idx and
 // row_idx).  The views d_row_ptr, d_col_ptr, ... point into them at 256-byte aligned offsets.
 constexpr int kMetaInts = 32;  // [0..1] total of rows, [2..3] total of columns, [8..16] slice, [20..28] slice_t
+void launch_partition(const int32_t* ptr, int32_t nb, int32_t* slice, int32_t* order, hipStream_t st) {
+  const int32_t per = kThreads / 64;
+  partition_kernel<<<1 + (order ? (nb + per - 1) / per : 0), kThreads, 0, st>>>(ptr, nb, slice, order);
+}
+
 inline int64_t aligned_ints(int64_t n) { return (n + 63) & ~(int64_t)63; }
 
 int alloc_meta_and_ptrs(radial_mask* m) {
   const int64_t np = aligned_ints((int64_t)m->n_blocks + 1);
   RADIAL_HIP_TRY(hipMalloc(&m->d_meta, sizeof(int32_t) * kMetaInts));
-  RADIAL_HIP_TRY(hipMalloc(&m->d_ptrs, sizeof(int32_t) * np * ((m->flags & RADIAL_MASK_TRANSPOSE) ? 2 : 1)));
+  const int64_t no = m->n_blocks <= kMaxOrdered ? aligned_ints(m->n_blocks) : 0;
+  RADIAL_HIP_TRY(hipMalloc(&m->d_ptrs, sizeof(int32_t) * (np + no) * ((m->flags & RADIAL_MASK_TRANSPOSE) ? 2 : 1)));
   m->d_row_ptr = m->d_ptrs;
+  if (no) m->d_order = m->d_ptrs + np;
   m->d_slice = m->d_meta + 8;
   if (m->flags & RADIAL_MASK_TRANSPOSE) {
-    m->d_col_ptr = m->d_ptrs + np;
+    m->d_col_ptr = m->d_ptrs + np + no;
+    if (no) m->d_order_t = m->d_col_ptr + np;
     m->d_slice_t = m->d_meta + 20;
   }
   return RADIAL_OK;
@@ -296,12 +319,12 @@ int alloc_idx(radial_mask* m) {
 int finish_mask(radial_mask* m, hipStream_t st) {
   const int32_t nb = m->n_blocks;
   int32_t h_meta[kMetaInts];
-  slice_kernel<<<1, 64, 0, st>>>(m->d_row_ptr, nb, m->d_slice);
+  launch_partition(m->d_row_ptr, nb, m->d_slice, m->d_order, st);
   if (m->flags & RADIAL_MASK_TRANSPOSE) {
     transpose_count_kernel<<<nb, kThreads, 0, st>>>(m->d_row_ptr, m->d_col_idx, nb, m->d_col_ptr);
     scan_kernel<<<1, kThreads, 0, st>>>(m->d_col_ptr, nb, (long long*)(m->d_meta + 2));
     transpose_fill_kernel<<<nb, kThreads, 0, st>>>(m->d_row_ptr, m->d_col_idx, nb, m->d_col_ptr, m->d_row_idx);
-    slice_kernel<<<1, 64, 0, st>>>(m->d_col_ptr, nb, m->d_slice_t);
+    launch_partition(m->d_col_ptr, nb, m->d_slice_t, m->d_order_t, st);
   }
   hipError_t e = hipGetLastError();
   if (e == hipSuccess) e = hipMemcpyAsync(h_meta, m->d_meta, sizeof h_meta, hipMemcpyDeviceToHost, st);

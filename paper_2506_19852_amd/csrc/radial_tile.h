@@ -126,6 +126,29 @@ __device__ __forceinline__ float max_with_other_half(float x) {
   return fmaxf(__builtin_bit_cast(float, first), __builtin_bit_cast(float, second));
 }
 
+// Work item of this workgroup; false: none.  Consecutive workgroup ids go to different XCDs.
+// By slices: the blocks are cut into 8 slices of equal list weight; for head bh, XCD x takes slice
+// (x + bh) mod 8 and the XCDs move from head to head together, so all of them work on the same head
+// at the same time (its K/V stay in the shared last-level cache), neighbouring workgroups of an XCD
+// share K/V tiles in that XCD's L2, and every XCD gets every slice equally often (slices of equal
+// weight do not take exactly equal time).
+__device__ __forceinline__ bool work_item(const WorkMap& w, int32_t& bh, int32_t& block) {
+  const uint32_t n_sliced = 8u * (uint32_t)w.sliced * (uint32_t)w.max_slice;
+  if (blockIdx.x >= n_sliced) {  // by falling list length, the heads of a block next to each other
+    const uint32_t idx = blockIdx.x - n_sliced, rank = idx / (uint32_t)w.ordered;
+    bh = w.sliced + (int32_t)(idx - rank * (uint32_t)w.ordered);
+    block = w.order[rank];
+    return true;
+  }
+  const uint32_t idx = blockIdx.x >> 3;
+  bh = (int32_t)(idx / (uint32_t)w.max_slice);
+  const int32_t pos = (int32_t)(idx - (uint32_t)bh * (uint32_t)w.max_slice);
+  const int32_t sl = ((int32_t)(blockIdx.x & 7) + bh) & 7;
+  const int32_t s0 = w.slice[sl];
+  block = s0 + pos;
+  return pos < w.slice[sl + 1] - s0;
+}
+
 // ---- token-level rule of the radial mask inside listed blocks ---------------------------------
 // (Sec. 4.2 of the paper, formal definition, plus the attention sink of App. A.1.)
 
