@@ -87,20 +87,21 @@ struct WorkMap {
   const int32_t* order;  // [n_blocks]; null only if ordered == 0
   int32_t max_slice;
   int32_t sliced, ordered;  // heads; sum B * H
+  int32_t n_blocks;
 };
 
 constexpr int32_t kMaxOrdered = 16384;  // blocks up to which a mask carries the order
 
-// Slices keep an XCD's workgroups on neighbouring blocks of one head, but the launch ends on whatever
-// lists come last in the last heads: with few heads, or rows that list everything (text tokens), compute
-// units idle there.  Longest lists first, dealt over the XCDs with all heads of a block side by side,
-// ends on short lists and gives every XCD the same mix; it costs locality, since the K and V of all those
-// heads are walked at once.  So it takes the whole launch while K and V fit the 256 MB last-level cache
-// (3 heads x 119 026 tokens with text: forward 9.79 -> 8.52 ms; 5 heads x 14 040: 0.638 -> 0.567 ms;
-// forward+backward of 5 x 14 040: 2.41 -> 2.23 ms; ties at 10 x 32 760 = 160 MB), and beyond that only the
-// last heads of the launch, up to 128 MB (40 x 32 760: forward 13.7 -> 13.45 ms, 20 x 32 760 forward+backward
-// 31.2 -> 30.5 ms; a tail of 256 MB gains nothing).  All heads by length at 24 x 118 800 (1.4 GB): 77.5 -> 89.7 ms.
-constexpr int64_t kOrderedWholeBytes = 256 << 20, kOrderedTailBytes = 128 << 20;
+// Slices keep the whole chip on one head, but the launch ends on whatever lists come last in the last
+// heads: with few heads, or rows that list everything (text tokens), compute units idle there.  Longest
+// lists first, each XCD on its own head of the last 8, ends on short lists; it walks the K and V of those
+// heads at once, so they have to fit the 256 MB last-level cache (and leave room for Q and O).  Whole
+// launches of up to 8 heads within it (forward, 3 heads x 119 026 tokens with text: 9.28 -> 8.35 ms; 5 x 14 040:
+// 0.639 -> 0.563 ms; forward+backward under the token rule, 5 x 32 760: 8.91 -> 8.36 ms), and the last heads of
+// larger ones, at most 8 and 160 MB (forward, 10 x 14 040: 0.910 -> 0.858 ms, 40 x 32 760: 13.44 -> 13.24 ms,
+// 24 x 118 800, 2 heads: 74.1 -> 73.4 ms; with 8 = 490 MB it takes 77.0 ms, with all 24 88.2 ms).  More than 8
+// heads by length put several heads on each XCD: 30 x 27 000 tokens in 64-token blocks 6.97 -> 9.35 ms.
+constexpr int64_t kOrderedWholeBytes = 256 << 20, kOrderedTailBytes = 160 << 20;
 
 inline WorkMap make_work_map(const radial_mask* m, bool transposed, int32_t heads, int32_t D) {
   WorkMap w;
@@ -108,9 +109,11 @@ inline WorkMap make_work_map(const radial_mask* m, bool transposed, int32_t head
   w.order = transposed ? m->d_order_t : m->d_order;
   w.max_slice = transposed ? m->max_slice_t : m->max_slice;
   const int64_t per_head = 4LL * D * m->n_tokens;  // K and V of one head
-  const int64_t tail = kOrderedTailBytes / per_head;
-  w.ordered = !w.order ? 0 : (per_head * heads <= kOrderedWholeBytes || tail > heads ? heads : (int32_t)tail);
+  const int64_t fit = (heads <= 8 && per_head * heads <= kOrderedWholeBytes ? kOrderedWholeBytes : kOrderedTailBytes) / per_head;
+  const int32_t most = heads < 8 ? heads : 8;
+  w.ordered = !w.order ? 0 : (fit < most ? (int32_t)fit : most);
   w.sliced = heads - w.ordered;
+  w.n_blocks = m->n_blocks;
   return w;
 }
 // Workgroups of a launch, and the most that any division of the heads could start.

@@ -134,9 +134,23 @@ __device__ __forceinline__ float max_with_other_half(float x) {
 // weight do not take exactly equal time).
 __device__ __forceinline__ bool work_item(const WorkMap& w, int32_t& bh, int32_t& block) {
   const uint32_t n_sliced = 8u * (uint32_t)w.sliced * (uint32_t)w.max_slice;
-  if (blockIdx.x >= n_sliced) {  // by falling list length, the heads of a block next to each other
-    const uint32_t idx = blockIdx.x - n_sliced, rank = idx / (uint32_t)w.ordered;
-    bh = w.sliced + (int32_t)(idx - rank * (uint32_t)w.ordered);
+  if (blockIdx.x >= n_sliced) {
+    // By falling list length.  A window of 8 ranks of every head goes to the 8 XCDs at once; inside it an
+    // XCD takes neighbouring (head, rank) pairs, head by head, so that it stays with the same
+    // heads / 8 heads from window to window (their K/V are what its L2 sees).
+    const uint32_t idx = blockIdx.x - n_sliced, heads = (uint32_t)w.ordered;
+    const uint32_t window = idx / (8u * heads), j = idx - window * 8u * heads;
+    uint32_t head, rank;
+    if (8u * window + 8u <= (uint32_t)w.n_blocks) {
+      const uint32_t pair = (j & 7u) * heads + (j >> 3);
+      head = pair >> 3;
+      rank = 8u * window + (pair & 7u);
+    } else {  // the last n_blocks % 8 ranks
+      rank = j / heads;
+      head = j - rank * heads;
+      rank += 8u * window;
+    }
+    bh = w.sliced + (int32_t)head;
     block = w.order[rank];
     return true;
   }

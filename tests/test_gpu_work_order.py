@@ -6,8 +6,8 @@ import pytest
 pytestmark = pytest.mark.gpu
 
 
-# K and V of all heads below 256 MB: all by length; above: the last 128 MB by length, the rest by slices.
-@pytest.mark.parametrize("B, H, N, extra", [(1, 3, 2085, 70), (1, 130, 4113, 0), (2, 66, 4096, 33), (1, 1, 1, 0)])
+# Up to 8 heads: all by length; above: the last 8 by length, the rest by slices.
+@pytest.mark.parametrize("B, H, N, extra", [(1, 3, 2085, 70), (1, 8, 1000, 0), (1, 19, 1313, 0), (2, 11, 2048, 33), (1, 1, 1, 0)])
 def test_every_head_gets_its_own_result(B, H, N, extra):
     import torch
     from paper_2506_19852_amd import binding as rb
