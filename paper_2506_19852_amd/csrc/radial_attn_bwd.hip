@@ -20,8 +20,6 @@
 //             here (7 products in total instead of 5), which is cheaper than pushing every
 //             listed pair's 64 KiB of dQ partial sums through memory atomics.
 // Stage tiles are copied HBM -> LDS by global_load_lds, double buffered, one stage ahead.
-#include <atomic>
-
 #include "radial_internal.h"
 #include "radial_tile.h"
 
@@ -31,18 +29,24 @@ namespace {
 constexpr int kStageQ = 64;  // query rows per pipeline stage
 constexpr float kLog2e = 1.4426950408889634f;
 
-template <int D, int BLK>
+// S: groups of waves that share the keys (dq kernel: the query rows); group i walks the list entries
+// i, i + S, ... on its own stage buffers and the groups' sums are added at the end.
+// R: workgroups per block, of kRows keys (rows) each.
+template <int D, int BLK, int S, int R>
 struct BwdTile {
-  static constexpr int kWaves = BLK / 32;  // one wave per 32 keys
-  static constexpr int kThreads = 64 * kWaves;
+  static constexpr int kRows = BLK / R;
+  static constexpr int kWaves = kRows / 32;  // one wave per 32 keys
+  static constexpr int kThreads = 64 * kWaves * S;
   static constexpr int kSubs = BLK / kStageQ;  // stages per listed query block
   static constexpr int kSteps = D / 16;
   static constexpr int kDTiles = D / 32;
   static constexpr int kQBytes = kStageQ * D * 2;        // Q or dO stage tile
   static constexpr int kStatBytes = 2 * kStageQ * 4;     // LSE and delta of a stage
   static constexpr int kStageBytes = 2 * kQBytes + kStatBytes;
-  static constexpr int kLdsBytes = 2 * kStageBytes;
+  static constexpr int kGroupBytes = 2 * kStageBytes;
+  static constexpr int kLdsBytes = S * kGroupBytes;
   static constexpr int kQLoadsPerWave = kQBytes / 1024 / kWaves;
+  static_assert((S - 1) * kWaves * 2 * kDTiles * 4096 <= kLdsBytes || S == 1, "the sums reuse the stage buffers");
 };
 
 template <int D>
@@ -92,16 +96,48 @@ __device__ __forceinline__ void mfma_results_settle(f32x16& acc0, f32x16& acc1) 
   asm volatile("s_nop 15" : "+v"(acc0), "+v"(acc1));
 }
 
+// Adds the accumulators of the groups 1 .. S-1 to those of group 0 through LDS (the stage buffers, once
+// every wave is done with them); returns whether this wave holds the sums (group 0).
+template <int S, int kWaves, int kTiles>
+__device__ __forceinline__ bool add_groups(f32x16 (&acc)[kTiles], char* lds_all, int group, int wave, int lane) {
+  if (group > 0) {
+    char* dst = lds_all + ((group - 1) * kWaves + wave) * kTiles * 4096 + lane * 16;
+#pragma unroll
+    for (int i = 0; i < kTiles; ++i)
+#pragma unroll
+      for (int e4 = 0; e4 < 4; ++e4)
+        *lds_cast<f32x4>(dst + (i * 4 + e4) * 1024) = f32x4{acc[i][4 * e4], acc[i][4 * e4 + 1], acc[i][4 * e4 + 2], acc[i][4 * e4 + 3]};
+  }
+  __syncthreads();
+  if (group > 0) return false;
+#pragma unroll 1
+  for (int other = 1; other < S; ++other) {
+    const char* src = lds_all + ((other - 1) * kWaves + wave) * kTiles * 4096 + lane * 16;
+#pragma unroll
+    for (int i = 0; i < kTiles; ++i)
+#pragma unroll
+      for (int e4 = 0; e4 < 4; ++e4) {
+        const f32x4 v = *lds_cast<const f32x4>(src + (i * 4 + e4) * 1024);
+#pragma unroll
+        for (int x = 0; x < 4; ++x) acc[i][4 * e4 + x] += v[x];
+      }
+  }
+  return true;
+}
+
 // kExact (all three kernels' callers): apply the token-level rule inside the listed blocks.
-template <int D, int BLK, bool kExact>
-__global__ void __launch_bounds__(2 * BLK, 1) radial_bwd_dkdv_kernel(const BwdArgs a) {
-  using T = BwdTile<D, BLK>;
+template <int D, int BLK, bool kExact, int S, int R>
+__device__ __forceinline__ void dkdv_body(const BwdArgs& a) {
+  using T = BwdTile<D, BLK, S, R>;
   using QT = SwzTile<D>;  // Q, dO tiles: rows of D elements
-  extern __shared__ __attribute__((aligned(1024))) char lds[];
-  const uint32_t lds_base = lds_address(lds);
+  extern __shared__ __attribute__((aligned(1024))) char lds_all[];
 
   const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wave_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int group = S == 1 ? 0 : wave_all / T::kWaves;
+  const int wave = S == 1 ? wave_all : wave_all % T::kWaves;
+  char* lds = lds_all + group * T::kGroupBytes;
+  const uint32_t lds_base = lds_address(lds);
   const int lq = lane & 31;
   const int g = lane >> 5;
   const int i16 = lane & 15;
@@ -109,6 +145,8 @@ __global__ void __launch_bounds__(2 * BLK, 1) radial_bwd_dkdv_kernel(const BwdAr
 
   int32_t bh, kb;
   if (!work_item(a.work_t, bh, kb)) return;
+  const int32_t part = R == 1 ? 0 : bh % R;  // with R > 1 the work map counts R heads for each
+  if (R > 1) bh /= R;
   const int32_t b = bh / a.H, h = bh % a.H;
 
   const __bf16* qp = (const __bf16*)a.q.ptr + (int64_t)b * a.q.sb + (int64_t)h * a.q.sh;
@@ -119,9 +157,10 @@ __global__ void __launch_bounds__(2 * BLK, 1) radial_bwd_dkdv_kernel(const BwdAr
   const float* deltap = a.delta + (int64_t)bh * a.N;
 
   const int32_t list_lo = __builtin_amdgcn_readfirstlane(a.col_ptr[kb]);
-  const int32_t n_list = __builtin_amdgcn_readfirstlane(a.col_ptr[kb + 1]) - list_lo;
+  const int32_t n_col = __builtin_amdgcn_readfirstlane(a.col_ptr[kb + 1]) - list_lo;
+  const int32_t n_list = S == 1 ? n_col : (n_col - group + S - 1) / S;  // entries of this group
   const int32_t n_stage = n_list * T::kSubs;
-  const int32_t key_row = kb * BLK + wave * 32 + lq;
+  const int32_t key_row = kb * BLK + part * T::kRows + wave * 32 + lq;
   const bool key_ok = key_row < a.N;
 
   // K and V rows of this lane's key: B operands of S = Q K^T and dP = dO V^T.
@@ -139,9 +178,9 @@ __global__ void __launch_bounds__(2 * BLK, 1) radial_bwd_dkdv_kernel(const BwdAr
     }
   }
 
-  const int32_t* rows_list = a.row_idx + list_lo;
-  int32_t cvec = lane < n_list ? rows_list[lane] : 0;
-  int32_t nvec = 64 + lane < n_list ? rows_list[64 + lane] : 0;
+  const int32_t* rows_list = a.row_idx + list_lo + group;
+  int32_t cvec = lane < n_list ? rows_list[S * lane] : 0;
+  int32_t nvec = 64 + lane < n_list ? rows_list[S * (64 + lane)] : 0;
   // token rule: (frame, position) of this lane's key and of every listed query block's first row
   StagePos key_at = {0, 0}, cvec_at = {0, 0};
   if (kExact) {
@@ -202,7 +241,7 @@ __global__ void __launch_bounds__(2 * BLK, 1) radial_bwd_dkdv_kernel(const BwdAr
       const int32_t e1 = (u + 1) / T::kSubs;
       if ((u + 1) % T::kSubs == 0 && (e1 & 63) == 0) {
         cvec = nvec;
-        nvec = e1 + 64 + lane < n_list ? rows_list[e1 + 64 + lane] : 0;
+        nvec = e1 + 64 + lane < n_list ? rows_list[S * (e1 + 64 + lane)] : 0;
         if (kExact) cvec_at = block_pos(cvec * BLK, a.rule.s);
       }
       q0_next = __builtin_amdgcn_readlane(cvec, e1 & 63) * BLK + ((u + 1) % T::kSubs) * kStageQ;
@@ -367,6 +406,15 @@ __global__ void __launch_bounds__(2 * BLK, 1) radial_bwd_dkdv_kernel(const BwdAr
     q_at = q_at_next;
   }
 
+  if (S > 1) {
+    // a stage is a barrier: as many as group 0, which has most stages
+    for (int32_t u = n_stage; u < (n_col + S - 1) / S * T::kSubs; ++u) __syncthreads();
+    __syncthreads();
+    add_groups<S, T::kWaves>(dk, lds_all, group, wave, lane);
+    __syncthreads();
+    if (!add_groups<S, T::kWaves>(dv, lds_all, group, wave, lane)) return;
+  }
+
   // ---- epilogue: dK = scale * dK^T, dV -----------------------------------------------------
   if (key_ok) {
     __bf16* dkd = (__bf16*)a.dk.ptr + (int64_t)b * a.dk.sb + (int64_t)h * a.dk.sh + (int64_t)key_row * a.dk.sn;
@@ -384,30 +432,45 @@ __global__ void __launch_bounds__(2 * BLK, 1) radial_bwd_dkdv_kernel(const BwdAr
   }
 }
 
-template <int D, int BLK>
+template <int D, int BLK, bool kExact>
+__global__ void __launch_bounds__(2 * BLK, 1) radial_bwd_dkdv_kernel(const BwdArgs a) {
+  dkdv_body<D, BLK, kExact, 1, 1>(a);
+}
+template <int D, int BLK, bool kExact, int S, int R>
+__global__ void __launch_bounds__(2 * BLK / R * S, 1) radial_bwd_dkdv_split_kernel(const BwdArgs a) {
+  dkdv_body<D, BLK, kExact, S, R>(a);
+}
+
+template <int D, int BLK, int S, int R>
 struct DqTile {
-  // Keys per stage of the dQ kernel.  Head dimension 128 with 64-token blocks walks half-size stages:
-  // two 64-key stage buffers (64 KiB) per 2-wave workgroup would leave a compute unit with 4 waves.
-  static constexpr int kStageKeys = (D == 128 && BLK == 64) ? 32 : 64;
-  static constexpr int kWaves = BLK / 32;  // one wave per 32 query rows
-  static constexpr int kThreads = 64 * kWaves;
+  static constexpr int kRows = BLK / R;
+  // Keys per stage of the dQ kernel.  Head dimension 128 with 64 rows walks half-size stages:
+  // two 64-key stage buffers (64 KiB) per 2 waves would leave a compute unit with 4 waves.
+  static constexpr int kStageKeys = (D == 128 && kRows == 64) ? 32 : 64;
+  static constexpr int kWaves = kRows / 32;  // one wave per 32 query rows
+  static constexpr int kThreads = 64 * kWaves * S;
   static constexpr int kSubs = BLK / kStageKeys;
   static constexpr int kSteps = D / 16;
   static constexpr int kDTiles = D / 32;
   static constexpr int kTileBytes = kStageKeys * D * 2;  // one K (or V) stage tile
   static constexpr int kLoadsPerWave = kTileBytes / 1024 / kWaves;
+  static constexpr int kGroupBytes = 4 * kTileBytes;     // [stage buffer][K, V]
+  static constexpr int kLdsBytes = S * kGroupBytes;
+  static_assert((S - 1) * kWaves * kDTiles * 4096 <= kLdsBytes || S == 1, "the sums reuse the stage buffers");
 };
 
-template <int D, int BLK, bool kExact>
-__global__ void __launch_bounds__(2 * BLK, 2) radial_bwd_dq_kernel(const BwdArgs a) {
-  using T = DqTile<D, BLK>;
+template <int D, int BLK, bool kExact, int S, int R>
+__global__ void __launch_bounds__(2 * BLK / R * S, 2) radial_bwd_dq_kernel(const BwdArgs a) {
+  using T = DqTile<D, BLK, S, R>;
   using SW = SwzTile<D>;
-  // [stage buffer][K, V][kStageKeys x D bf16]
-  __shared__ __attribute__((aligned(1024))) char lds[4 * T::kTileBytes];
-  const uint32_t lds_base = lds_address(lds);
+  extern __shared__ __attribute__((aligned(1024))) char lds_all[];  // [group][stage buffer][K, V][kStageKeys x D bf16]
 
   const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wave_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int group = S == 1 ? 0 : wave_all / T::kWaves;
+  const int wave = S == 1 ? wave_all : wave_all % T::kWaves;
+  char* lds = lds_all + group * T::kGroupBytes;
+  const uint32_t lds_base = lds_address(lds);
   const int lq = lane & 31;
   const int g = lane >> 5;
   const int i16 = lane & 15;
@@ -415,6 +478,8 @@ __global__ void __launch_bounds__(2 * BLK, 2) radial_bwd_dq_kernel(const BwdArgs
 
   int32_t bh, qb;
   if (!work_item(a.work, bh, qb)) return;
+  const int32_t part = R == 1 ? 0 : bh % R;
+  if (R > 1) bh /= R;
   const int32_t b = bh / a.H, h = bh % a.H;
 
   const __bf16* qp = (const __bf16*)a.q.ptr + (int64_t)b * a.q.sb + (int64_t)h * a.q.sh;
@@ -423,9 +488,10 @@ __global__ void __launch_bounds__(2 * BLK, 2) radial_bwd_dq_kernel(const BwdArgs
   const __bf16* gp = (const __bf16*)a.dout.ptr + (int64_t)b * a.dout.sb + (int64_t)h * a.dout.sh;
 
   const int32_t list_lo = __builtin_amdgcn_readfirstlane(a.row_ptr[qb]);
-  const int32_t n_list = __builtin_amdgcn_readfirstlane(a.row_ptr[qb + 1]) - list_lo;
+  const int32_t n_row = __builtin_amdgcn_readfirstlane(a.row_ptr[qb + 1]) - list_lo;
+  const int32_t n_list = S == 1 ? n_row : (n_row - group + S - 1) / S;  // entries of this group
   const int32_t n_stage = n_list * T::kSubs;
-  const int32_t q_row = qb * BLK + wave * 32 + lq;
+  const int32_t q_row = qb * BLK + part * T::kRows + wave * 32 + lq;
   const bool q_ok = q_row < a.N;
   const int64_t q_clamped = q_ok ? q_row : a.N - 1;
 
@@ -443,9 +509,9 @@ __global__ void __launch_bounds__(2 * BLK, 2) radial_bwd_dq_kernel(const BwdArgs
   const float lse2 = a.lse[(int64_t)bh * a.N + q_clamped] * kLog2e;  // rows past N: values unused
   const float dlt = a.delta[(int64_t)bh * a.N + q_clamped];
 
-  const int32_t* cols = a.col_idx + list_lo;
-  int32_t cvec = lane < n_list ? cols[lane] : 0;
-  int32_t nvec = 64 + lane < n_list ? cols[64 + lane] : 0;
+  const int32_t* cols = a.col_idx + list_lo + group;
+  int32_t cvec = lane < n_list ? cols[S * lane] : 0;
+  int32_t nvec = 64 + lane < n_list ? cols[S * (64 + lane)] : 0;
   // token rule: (frame, position) of this lane's query and of every listed key block's first key
   StagePos q_at = {0, 0}, cvec_at = {0, 0};
   if (kExact) {
@@ -508,7 +574,7 @@ __global__ void __launch_bounds__(2 * BLK, 2) radial_bwd_dq_kernel(const BwdArgs
       const int32_t e1 = (u + 1) / T::kSubs;
       if ((u + 1) % T::kSubs == 0 && (e1 & 63) == 0) {
         cvec = nvec;
-        nvec = e1 + 64 + lane < n_list ? cols[e1 + 64 + lane] : 0;
+        nvec = e1 + 64 + lane < n_list ? cols[S * (e1 + 64 + lane)] : 0;
         if (kExact) cvec_at = block_pos(cvec * BLK, a.rule.s);
       }
       key0_next = __builtin_amdgcn_readlane(cvec, e1 & 63) * BLK + ((u + 1) % T::kSubs) * T::kStageKeys;
@@ -601,6 +667,12 @@ __global__ void __launch_bounds__(2 * BLK, 2) radial_bwd_dq_kernel(const BwdArgs
     k_at = k_at_next;
   }
 
+  if (S > 1) {
+    // a stage is a barrier: as many as group 0, which has most stages
+    for (int32_t u = n_stage; u < (n_row + S - 1) / S * T::kSubs; ++u) __syncthreads();
+    __syncthreads();
+    if (!add_groups<S, T::kWaves>(dq, lds_all, group, wave, lane)) return;
+  }
   if (q_ok) {
     __bf16* dst = (__bf16*)a.dq.ptr + (int64_t)b * a.dq.sb + (int64_t)h * a.dq.sh + (int64_t)q_row * a.dq.sn;
 #pragma unroll
@@ -613,32 +685,62 @@ __global__ void __launch_bounds__(2 * BLK, 2) radial_bwd_dq_kernel(const BwdArgs
   }
 }
 
+template <int D, int BLK, bool kExact, int S, int R>
+int launch_dkdv(BwdArgs a, hipStream_t stream) {
+  using T = BwdTile<D, BLK, S, R>;
+  void (*kernel)(BwdArgs);
+  if constexpr (S == 1) kernel = radial_bwd_dkdv_kernel<D, BLK, kExact>;
+  else kernel = radial_bwd_dkdv_split_kernel<D, BLK, kExact, S, R>;
+  static DeviceOnce configured;
+  if (int rc = allow_dynamic_lds(configured, (const void*)kernel, T::kLdsBytes)) return rc;
+  a.work_t.ordered *= R;  // R > 1 only where all heads are taken by list length
+  kernel<<<dim3((unsigned)work_grid(a.work_t, a.n_blocks)), dim3(T::kThreads), T::kLdsBytes, stream>>>(a);
+  return RADIAL_OK;
+}
+
+template <int D, int BLK, bool kExact, int S, int R>
+int launch_dq(BwdArgs a, hipStream_t stream) {
+  using T = DqTile<D, BLK, S, R>;
+  const auto kernel = radial_bwd_dq_kernel<D, BLK, kExact, S, R>;
+  if (T::kLdsBytes > 65536) {
+    static DeviceOnce configured;
+    if (int rc = allow_dynamic_lds(configured, (const void*)kernel, T::kLdsBytes)) return rc;
+  }
+  a.work.ordered *= R;
+  kernel<<<dim3((unsigned)work_grid(a.work, a.n_blocks)), dim3(T::kThreads), T::kLdsBytes, stream>>>(a);
+  return RADIAL_OK;
+}
+
+// How many groups of waves share a list: as in the forward, more while the launch is too small to fill the
+// chip.  The dK/dV kernel holds one wave per SIMD, so a group of 4 waves already fills a compute unit: it
+// takes half blocks of 64 keys (block 128) or 64-token blocks in two groups.  Forward and backward
+// together, S = 1 / chosen, microseconds: block 128, D 128: 84 items 208 / 122, 235 items 445 / 413;
+// block 64: 168 items D 64 148 / 79, D 128 229 / 118; 1128 items D 64 670 / 590.  dK/dV alone in two groups:
+// 1128 items -15, 1400 items +30 (D 64, block 64); dQ alone: 1400 items -51, 2820 items +6; block 128, 564
+// items D 64: +20.
 template <int D, int BLK, bool kExact>
 int launch(const BwdArgs& a, hipStream_t stream) {
-  using T = BwdTile<D, BLK>;
   const int64_t rows = (int64_t)a.B * a.H * a.N;
   const int rows_per_block = 256 / (D / 8);
   const int64_t prep_grid = (rows + rows_per_block - 1) / rows_per_block;
-  const int64_t grid_kv = work_grid(a.work_t, a.n_blocks);
-  const int64_t grid_q = work_grid(a.work, a.n_blocks);
   if (prep_grid > 0x7fffffffLL || work_grid_bound(a.work_t) > 0x7fffffffLL || work_grid_bound(a.work) > 0x7fffffffLL)
     return fail(RADIAL_ESHAPE, "problem too large for one launch");
-  // The dK/dV kernel needs more dynamic LDS than the default limit.  The attribute belongs to the
-  // (device, kernel) pair; it is set once per device and template instance.  Setting it twice is
-  // harmless, so two host threads racing through here only repeat the call.
-  static std::atomic<bool> configured[kMaxDevices];
-  int dev = 0;
-  RADIAL_HIP_TRY(hipGetDevice(&dev));
-  if (dev < 0 || dev >= kMaxDevices || !configured[dev].load(std::memory_order_acquire)) {
-    RADIAL_HIP_TRY(hipFuncSetAttribute((const void*)radial_bwd_dkdv_kernel<D, BLK, kExact>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, T::kLdsBytes));
-    if (dev >= 0 && dev < kMaxDevices) configured[dev].store(true, std::memory_order_release);
-  }
   bwd_prepare_kernel<D><<<dim3((unsigned)prep_grid), dim3(256), 0, stream>>>(a);
-  if (grid_kv > 0)
-    radial_bwd_dkdv_kernel<D, BLK, kExact><<<dim3((unsigned)grid_kv), dim3(T::kThreads), T::kLdsBytes, stream>>>(a);
-  if (grid_q > 0)
-    radial_bwd_dq_kernel<D, BLK, kExact><<<dim3((unsigned)grid_q), dim3(DqTile<D, BLK>::kThreads), 0, stream>>>(a);
+  const int64_t items = work_items(a.work, a.n_blocks);
+  int rc = RADIAL_OK;
+  if constexpr (BLK == 128) {
+    const bool halves = items <= 128 && a.work.sliced == 0;
+    rc = halves ? launch_dkdv<D, BLK, kExact, 2, 2>(a, stream) : launch_dkdv<D, BLK, kExact, 1, 1>(a, stream);
+    if (rc) return rc;
+    rc = halves ? launch_dq<D, BLK, kExact, 4, 2>(a, stream)
+                : items <= 256 ? launch_dq<D, BLK, kExact, 2, 1>(a, stream) : launch_dq<D, BLK, kExact, 1, 1>(a, stream);
+  } else {
+    rc = items <= 1200 ? launch_dkdv<D, BLK, kExact, 2, 1>(a, stream) : launch_dkdv<D, BLK, kExact, 1, 1>(a, stream);
+    if (rc) return rc;
+    rc = items <= 256 ? launch_dq<D, BLK, kExact, 4, 1>(a, stream)
+                      : items <= 1536 ? launch_dq<D, BLK, kExact, 2, 1>(a, stream) : launch_dq<D, BLK, kExact, 1, 1>(a, stream);
+  }
+  if (rc) return rc;
   RADIAL_HIP_TRY(hipGetLastError());
   return RADIAL_OK;
 }

@@ -2,7 +2,8 @@
 // with per-workgroup trace records, by radial_diag.hip): Eq. 2 of the paper evaluated only on the key
 // blocks that the block list names (Eq. 1 when the list names all of them).
 //
-// One workgroup = one (batch, head, query block).  Wave w owns 32 query rows.  Everything
+// One workgroup = one (batch, head, query block), or half of one.  Wave w of a group of waves owns 32
+// query rows; where a launch is small, several groups share the rows and take the list's entries in turn.  Everything
 // that belongs to query row r lives in lanes r and r+32 of that wave, because both products
 // are computed transposed on v_mfma_f32_32x32x16_bf16:
 //     S^T[key, q] = K[key, :] . Q[q, :]      A = K tile (LDS),     B = Q^T (registers)
@@ -30,13 +31,17 @@
 namespace radial {
 namespace fwd {
 
-template <int D, int BLK>
+// S: groups of waves that share the query rows; group i walks the list entries i, i + S, ... on its
+// own stage buffers and the groups' results are merged at the end.
+// R: workgroups per query block, of kRows rows each.
+template <int D, int BLK, int S, int R>
 struct Tile {
-  // Keys per pipeline stage.  Head dimension 128 with 64-token blocks walks half-size stages: two
-  // 64-key stage buffers (64 KiB) per 2-wave workgroup would leave a compute unit with 4 waves.
-  static constexpr int kStageKeys = (D == 128 && BLK == 64) ? 32 : 64;
-  static constexpr int kWaves = BLK / 32;          // one wave per 32 query rows
-  static constexpr int kThreads = 64 * kWaves;
+  static constexpr int kRows = BLK / R;
+  // Keys per pipeline stage.  Head dimension 128 with 64 rows walks half-size stages: two
+  // 64-key stage buffers (64 KiB) per 2 waves would leave a compute unit with 4 waves.
+  static constexpr int kStageKeys = (D == 128 && kRows == 64) ? 32 : 64;
+  static constexpr int kWaves = kRows / 32;        // one wave per 32 query rows
+  static constexpr int kThreads = 64 * kWaves * S;
   static constexpr int kPiecesPerRow = D / 8;      // 16-byte pieces per K/V row
   static constexpr int kSubs = BLK / kStageKeys;   // stages per listed key block
   static constexpr int kStageBytes = kStageKeys * D * 2;            // one K (or V) stage tile
@@ -47,6 +52,11 @@ struct Tile {
   // MFMAs of the first product per copy of the next stage (copies are spread over that product)
   static constexpr int kCopyEvery = (kKeyTiles * kSteps) / (2 * kLoadsPerWave);
   static_assert(kCopyEvery >= 1, "more copies than MFMAs in the first product");
+  static constexpr int kGroupBytes = 4 * kStageBytes;               // [stage buffer][K, V]
+  static constexpr int kLdsBytes = S * kGroupBytes;
+  // one wave's share of a merge: O in 16-byte pieces, then m and l, all in lane order
+  static constexpr int kMergeBytes = kDTiles * 4096 + 512;
+  static_assert((S - 1) * kWaves * kMergeBytes <= kLdsBytes || S == 1, "the merge reuses the stage buffers");
 };
 
 // Swizzle key of a 256-byte LDS line (16 pieces of 16 bytes); pieces move inside their line only.
@@ -67,22 +77,27 @@ __device__ __forceinline__ int piece_offset(int r, int p) {
 // kExact: apply the token-level rule of the radial mask inside the listed blocks.
 // kTrace: also record begin, end and hardware ids of the workgroup (diagnostics build of the kernel;
 // the library's radial_attn_fwd launches kTrace = false, which carries none of it).
-template <int D, int BLK, bool kExact, bool kTrace>
-// Two waves per SIMD: two 4-wave workgroups per compute unit (BLK = 128) or four 2-wave ones (BLK = 64).
-__global__ void __launch_bounds__(2 * BLK, 2) radial_fwd_kernel(const FwdArgs a) {
-  using T = Tile<D, BLK>;
-  // [stage buffer][K, V][T::kStageKeys x D bf16]
-  __shared__ __attribute__((aligned(1024))) char lds[2 * 2 * T::kStageBytes];
-  const uint32_t lds_base = lds_address(lds);
+template <int D, int BLK, bool kExact, bool kTrace, int S, int R>
+// Two waves per SIMD: two 4-wave workgroups per compute unit (BLK = 128) or four 2-wave ones (BLK = 64)
+// with S = R = 1.
+__global__ void __launch_bounds__(2 * BLK / R * S, 2) radial_fwd_kernel(const FwdArgs a) {
+  using T = Tile<D, BLK, S, R>;
+  extern __shared__ __attribute__((aligned(1024))) char lds_all[];  // [group][stage buffer][K, V][T::kStageKeys x D bf16]
 
   const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wave_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int group = S == 1 ? 0 : wave_all / T::kWaves;
+  const int wave = S == 1 ? wave_all : wave_all % T::kWaves;
+  char* lds = lds_all + group * T::kGroupBytes;
+  const uint32_t lds_base = lds_address(lds);
   const int lq = lane & 31;   // query column / K row inside a 32-tile
   const int g = lane >> 5;    // which half of the 16-wide MFMA k-slice this lane feeds
 
   const uint64_t t_begin = kTrace ? __builtin_amdgcn_s_memrealtime() : 0;
   int32_t bh, qb;
   if (!work_item(a.work, bh, qb)) return;
+  const int32_t part = R == 1 ? 0 : bh % R;  // with R > 1 the work map counts R heads for each
+  if (R > 1) bh /= R;
   const int32_t b = bh / a.H, h = bh % a.H;
 
   const __bf16* qp = (const __bf16*)a.q.ptr + (int64_t)b * a.q.sb + (int64_t)h * a.q.sh;
@@ -91,9 +106,10 @@ __global__ void __launch_bounds__(2 * BLK, 2) radial_fwd_kernel(const FwdArgs a)
   __bf16* op = (__bf16*)a.o.ptr + (int64_t)b * a.o.sb + (int64_t)h * a.o.sh;
 
   const int32_t list_lo = __builtin_amdgcn_readfirstlane(a.row_ptr[qb]);
-  const int32_t n_list = __builtin_amdgcn_readfirstlane(a.row_ptr[qb + 1]) - list_lo;
+  const int32_t n_row = __builtin_amdgcn_readfirstlane(a.row_ptr[qb + 1]) - list_lo;
+  const int32_t n_list = S == 1 ? n_row : (n_row - group + S - 1) / S;  // entries of this group
   const int32_t n_stage = n_list * T::kSubs;
-  const int32_t q_row = qb * BLK + wave * 32 + lq;
+  const int32_t q_row = qb * BLK + part * T::kRows + wave * 32 + lq;
   const bool q_ok = q_row < a.N;
 
   // Q^T fragments: for k-step t this lane holds Q[q_row, 16t + 8g .. +7].
@@ -110,9 +126,9 @@ __global__ void __launch_bounds__(2 * BLK, 2) radial_fwd_kernel(const FwdArgs a)
 
   // The list entries of this row, 64 at a time in one register per lane; cvec is the chunk
   // being walked, nvec the one after it.
-  const int32_t* cols = a.col_idx + list_lo;
-  int32_t cvec = lane < n_list ? cols[lane] : 0;
-  int32_t nvec = 64 + lane < n_list ? cols[64 + lane] : 0;
+  const int32_t* cols = a.col_idx + list_lo + group;
+  int32_t cvec = lane < n_list ? cols[S * lane] : 0;
+  int32_t nvec = 64 + lane < n_list ? cols[S * (64 + lane)] : 0;
   // token rule: this lane's query as (frame, position), and the same for the first token of
   // every listed key block (one division per lane per 64 entries)
   StagePos q_at = {0, 0}, cvec_at = {0, 0};
@@ -295,7 +311,7 @@ __global__ void __launch_bounds__(2 * BLK, 2) radial_fwd_kernel(const FwdArgs a)
       const int32_t e1 = (u + 1) / T::kSubs;
       if ((u + 1) % T::kSubs == 0 && (e1 & 63) == 0) {  // entering the next chunk of the list
         cvec = nvec;
-        nvec = e1 + 64 + lane < n_list ? cols[e1 + 64 + lane] : 0;
+        nvec = e1 + 64 + lane < n_list ? cols[S * (e1 + 64 + lane)] : 0;
         if (kExact) cvec_at = block_pos(cvec * BLK, a.rule.s);
       }
       key0_next = __builtin_amdgcn_readlane(cvec, e1 & 63) * BLK + ((u + 1) % T::kSubs) * T::kStageKeys;
@@ -328,6 +344,47 @@ __global__ void __launch_bounds__(2 * BLK, 2) radial_fwd_kernel(const FwdArgs a)
     if (u + 1 < n_stage) one_stage(u + 1, std::integral_constant<int, 1>{});
   }
 
+  // ---- merge of the groups: group 0 gathers (m, l, O) of the others through LDS ---------------
+  // (float32 throughout; at most 3 x 34 KiB per workgroup, about a microsecond)
+  if (S > 1) {
+    // a stage is a barrier: as many as group 0, which has most stages
+    for (int32_t u = n_stage; u < (n_row + S - 1) / S * T::kSubs; ++u) __syncthreads();
+    __syncthreads();  // the last stages are consumed; their buffers are reused
+    if (group > 0) {
+      char* dst = lds_all + ((group - 1) * T::kWaves + wave) * T::kMergeBytes + lane * 16;
+#pragma unroll
+      for (int i = 0; i < T::kDTiles; ++i)
+#pragma unroll
+        for (int e4 = 0; e4 < 4; ++e4)
+          *lds_cast<f32x4>(dst + (i * 4 + e4) * 1024) = f32x4{o[i][4 * e4], o[i][4 * e4 + 1], o[i][4 * e4 + 2], o[i][4 * e4 + 3]};
+      char* ml = lds_all + ((group - 1) * T::kWaves + wave) * T::kMergeBytes + T::kDTiles * 4096 + lane * 4;
+      *lds_cast<float>(ml) = m_run;
+      *lds_cast<float>(ml + 256) = l_run;
+    }
+    __syncthreads();
+    if (group > 0) return;
+#pragma unroll 1
+    for (int other = 1; other < S; ++other) {
+      const char* src = lds_all + ((other - 1) * T::kWaves + wave) * T::kMergeBytes;
+      const float m_o = *lds_cast<const float>(src + T::kDTiles * 4096 + lane * 4);
+      const float l_o = *lds_cast<const float>(src + T::kDTiles * 4096 + 256 + lane * 4);
+      const float m_new = fmaxf(m_run, m_o);
+      // a group without a visible key has m = -inf, l = 0, O = 0
+      const float alpha = m_new > m_run ? __builtin_amdgcn_exp2f((m_run - m_new) * c) : 1.f;
+      const float beta = m_new > m_o ? __builtin_amdgcn_exp2f((m_o - m_new) * c) : 1.f;
+      l_run = l_run * alpha + l_o * beta;
+#pragma unroll
+      for (int i = 0; i < T::kDTiles; ++i)
+#pragma unroll
+        for (int e4 = 0; e4 < 4; ++e4) {
+          const f32x4 v = *lds_cast<const f32x4>(src + (i * 4 + e4) * 1024 + lane * 16);
+#pragma unroll
+          for (int x = 0; x < 4; ++x) o[i][4 * e4 + x] = o[i][4 * e4 + x] * alpha + v[x] * beta;
+        }
+      m_run = m_new;
+    }
+  }
+
   // ---- epilogue: O / l, LSE ----------------------------------------------------------------
   const float l_tot = l_run + __shfl_xor(l_run, 32);
   const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
@@ -348,37 +405,71 @@ __global__ void __launch_bounds__(2 * BLK, 2) radial_fwd_kernel(const FwdArgs a)
       a.lse[idx] = l_tot > 0.f ? m_run * a.scale + __logf(l_tot) : -INFINITY;
     }
   }
-  if (kTrace && a.wg_trace != nullptr && threadIdx.x == 0) {
+  if (kTrace && a.wg_trace != nullptr && threadIdx.x == 0 && part == 0) {  // one record per (head, query block)
     // hardware id registers: which XCD, shader engine and compute unit this workgroup ran on
     constexpr int kHwId = 4, kXccId = 20, kAllBits = 31 << 11;
     const uint64_t where = ((uint64_t)__builtin_amdgcn_s_getreg(kXccId | kAllBits) << 32) | (uint32_t)__builtin_amdgcn_s_getreg(kHwId | kAllBits);
-    uint64_t* rec = a.wg_trace + 3 * (int64_t)blockIdx.x;
+    uint64_t* rec = a.wg_trace + 3 * (R == 1 ? (int64_t)blockIdx.x : (int64_t)bh * a.n_blocks + qb);
     rec[0] = t_begin;
     rec[1] = __builtin_amdgcn_s_memrealtime();
     rec[2] = where;
   }
 }
 
-// Launches the kernel instance for (D, block, token rule); kTrace selects the diagnostics build.
-template <int D, int BLK, bool kTrace>
-int launch(const FwdArgs& a, hipStream_t stream) {
-  const int64_t grid = work_grid(a.work, a.n_blocks);
-  if (work_grid_bound(a.work) > 0x7fffffffLL) return fail(RADIAL_ESHAPE, "B*H*n_blocks is too large for one launch");
-  if (grid == 0) return RADIAL_OK;
-  if (a.rule.exact)
-    radial_fwd_kernel<D, BLK, true, kTrace><<<dim3((unsigned)grid), dim3(Tile<D, BLK>::kThreads), 0, stream>>>(a);
-  else
-    radial_fwd_kernel<D, BLK, false, kTrace><<<dim3((unsigned)grid), dim3(Tile<D, BLK>::kThreads), 0, stream>>>(a);
+template <int D, int BLK, bool kExact, bool kTrace, int S, int R>
+int launch_split(FwdArgs a, hipStream_t stream) {
+  using T = Tile<D, BLK, S, R>;
+  const auto kernel = radial_fwd_kernel<D, BLK, kExact, kTrace, S, R>;
+  if (T::kLdsBytes > 65536) {
+    static DeviceOnce configured;
+    if (int rc = allow_dynamic_lds(configured, (const void*)kernel, T::kLdsBytes)) return rc;
+  }
+  a.work.ordered *= R;  // R > 1 only where all heads are taken by list length
+  kernel<<<dim3((unsigned)work_grid(a.work, a.n_blocks)), dim3(T::kThreads), T::kLdsBytes, stream>>>(a);
   RADIAL_HIP_TRY(hipGetLastError());
   return RADIAL_OK;
 }
 
+// How many groups of waves share a list, by the number of (head, block) items.  A workgroup walks its list
+// stage by stage, so while there are fewer items than the 256 compute units can hold the launch lasts as
+// long as its longest walk; S groups cut that by S.  Once the chip is full the groups of a workgroup only
+// wait for each other at the same barriers.  Measured S = 1 / chosen, microseconds:
+//   block 128: up to 128 items half blocks with S = 4 (84 items: D 128 51.0 / 32.4, D 64 37.9 / 20.1), up to
+//              256 S = 2 (235 items, D 128: 110 / 96); at 288 items S = 2 loses (D 128: 101 / 111).
+//   block 64:  up to 256 items S = 4 (168 items: D 64 37.8 / 19.3, D 128 67.2 / 31.1); above, S = 2 while it
+//              pays: D 128 up to 1536 items (1400: 488 / 438; 1880: 359 / 373), D 64 always (20 480 items:
+//              8.82 / 8.14 ms; 15 800 longer ones: 16.3 / 13.1 ms): two workgroups of 4 waves per compute unit
+//              walk fewer lists at once than five of 2 waves.
+template <int D, int BLK, bool kExact, bool kTrace>
+int launch(const FwdArgs& a, hipStream_t stream) {
+  if (work_grid_bound(a.work) > 0x7fffffffLL) return fail(RADIAL_ESHAPE, "B*H*n_blocks is too large for one launch");
+  const int64_t items = work_items(a.work, a.n_blocks);
+  if (items == 0) return RADIAL_OK;
+  if constexpr (BLK == 128) {
+    if (items <= 128 && a.work.sliced == 0) return launch_split<D, BLK, kExact, kTrace, 4, 2>(a, stream);
+    if (items <= 256) return launch_split<D, BLK, kExact, kTrace, 2, 1>(a, stream);
+    return launch_split<D, BLK, kExact, kTrace, 1, 1>(a, stream);
+  } else {
+    if (items <= 256) return launch_split<D, BLK, kExact, kTrace, 4, 1>(a, stream);
+    if constexpr (D == 128) {
+      if (items > 1536) return launch_split<D, BLK, kExact, kTrace, 1, 1>(a, stream);
+    }
+    return launch_split<D, BLK, kExact, kTrace, 2, 1>(a, stream);
+  }
+}
+
+// Launches the kernel instance for (D, block, token rule); kTrace selects the diagnostics build.
+template <int D, int BLK, bool kTrace>
+int launch_tile(const FwdArgs& a, hipStream_t stream) {
+  return a.rule.exact ? launch<D, BLK, true, kTrace>(a, stream) : launch<D, BLK, false, kTrace>(a, stream);
+}
+
 template <bool kTrace>
 int launch_any(int D, int block, const FwdArgs& a, hipStream_t stream) {
-  if (D == 128 && block == 128) return launch<128, 128, kTrace>(a, stream);
-  if (D == 64 && block == 128) return launch<64, 128, kTrace>(a, stream);
-  if (D == 128 && block == 64) return launch<128, 64, kTrace>(a, stream);
-  if (D == 64 && block == 64) return launch<64, 64, kTrace>(a, stream);
+  if (D == 128 && block == 128) return launch_tile<128, 128, kTrace>(a, stream);
+  if (D == 64 && block == 128) return launch_tile<64, 128, kTrace>(a, stream);
+  if (D == 128 && block == 64) return launch_tile<128, 64, kTrace>(a, stream);
+  if (D == 64 && block == 64) return launch_tile<64, 64, kTrace>(a, stream);
   return fail(RADIAL_EUNSUPPORTED, "head dimension %d with block %d is not supported", D, block);
 }
 

@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <atomic>
+
 #include "radial.h"
 
 // Device-side description of a block list; owned by radial_mask.
@@ -52,6 +54,22 @@ int fail(int code, const char* fmt, ...);
     if (e_ != hipSuccess)                                                                 \
       return ::radial::fail(RADIAL_EHIP, "%s failed: %s", #expr, hipGetErrorString(e_));  \
   } while (0)
+
+// Lets `kernel` use `bytes` of dynamic LDS (the default limit is 64 KiB).  The attribute belongs to the
+// (device, kernel) pair; `done` belongs to the kernel and remembers the devices where it is set.  Setting
+// it twice is harmless, so two host threads racing through here only repeat the call.
+struct DeviceOnce {
+  std::atomic<bool> done[kMaxDevices];
+};
+inline int allow_dynamic_lds(DeviceOnce& once, const void* kernel, int bytes) {
+  int dev = 0;
+  RADIAL_HIP_TRY(hipGetDevice(&dev));
+  const bool tracked = dev >= 0 && dev < kMaxDevices;
+  if (tracked && once.done[dev].load(std::memory_order_acquire)) return RADIAL_OK;
+  RADIAL_HIP_TRY(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes));
+  if (tracked) once.done[dev].store(true, std::memory_order_release);
+  return RADIAL_OK;
+}
 
 // Token-level rule of the radial mask, for kernels that apply it inside listed blocks.
 struct TokenRule {
@@ -116,8 +134,9 @@ inline WorkMap make_work_map(const radial_mask* m, bool transposed, int32_t head
   w.n_blocks = m->n_blocks;
   return w;
 }
-// Workgroups of a launch, and the most that any division of the heads could start.
+// (head, block) pairs of a launch, its workgroups, and the most workgroups that any division of the heads could start.
 inline int64_t work_grid_bound(const WorkMap& w) { return 8LL * (w.sliced + w.ordered) * w.max_slice; }
+inline int64_t work_items(const WorkMap& w, int32_t n_blocks) { return (int64_t)(w.sliced + w.ordered) * n_blocks; }
 inline int64_t work_grid(const WorkMap& w, int32_t n_blocks) {
   return 8LL * w.sliced * w.max_slice + (int64_t)w.ordered * n_blocks;
 }

@@ -122,3 +122,11 @@ def test_the_checker_sees_planted_violations(edit, what):
     assert check_kernel("good", GOOD) == 3
     with pytest.raises(AssertionError, match=what):
         check_kernel("planted", edit(list(GOOD)))
+
+
+def test_hand_issued_mfmas_of_the_split_kernels_keep_their_promises(bwd_asm):
+    found = 0
+    for name, body in kernels(bwd_asm, "radial_bwd_dkdv_split_kernel"):
+        found += 1
+        assert check_kernel(name, list(instructions(body))) > 0, name
+    assert found == 8, found   # D in {64, 128} x (block 64, half blocks of 128) x token rule on / off
