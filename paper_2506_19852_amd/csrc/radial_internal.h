@@ -18,8 +18,9 @@ struct radial_mask {
   int device = 0;
   // owners of the device storage; the pointers below are views into them
   int32_t* d_meta = nullptr;     // totals and launch partitions
-  int32_t* d_ptrs = nullptr;     // row_ptr (+ col_ptr)
+  int32_t* d_ptrs = nullptr;     // row_ptr, order (+ col_ptr, order), counts
   int32_t* d_idx = nullptr;      // col_idx (+ row_idx)
+  int32_t* d_counts = nullptr;   // [n_blocks] scratch of the build; null above kMaxOrdered blocks
   int32_t* d_row_ptr = nullptr;  // [n_blocks + 1]
   int32_t* d_col_idx = nullptr;  // [nnz]
   int32_t* d_col_ptr = nullptr;  // [n_blocks + 1]  (transpose; only with RADIAL_MASK_TRANSPOSE)

@@ -13,6 +13,7 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <memory>
 #include <new>
 #include <vector>
 
@@ -33,6 +34,12 @@ int fail(int code, const char* fmt, ...) {
 namespace {
 
 constexpr int kThreads = 256;
+// Blocks up to which a radial mask's lists get room for every pair, so that nothing has to be known before
+// they are written (2 MiB per list; hipMalloc becomes slow above that, and counting first is then cheaper).
+// radial_mask_build and free, four kernels and two waits / two kernels and one wait: 110 blocks 61 / 36 us,
+// with the transposed lists 77 / 46; 929 blocks 65 / 73.
+constexpr int32_t kMaxUncounted = 720;
+static_assert(kMaxUncounted <= kMaxOrdered, "place_list writes the order");
 constexpr int kMaxWords = 15 * 1024;  // 60 KiB of LDS bitmap: up to 491 520 key blocks
 
 struct MaskGeom {
@@ -142,24 +149,29 @@ __global__ void __launch_bounds__(kThreads) mask_count_kernel(MaskGeom g, int32_
   if (threadIdx.x == 0) counts[blockIdx.x] = total;
 }
 
-__global__ void __launch_bounds__(kThreads) mask_fill_kernel(MaskGeom g, int32_t nwords, const int32_t* row_ptr,
-                                                            int32_t* col_idx) {
-  extern __shared__ uint32_t words[];
-  row_bitmap(g, blockIdx.x, words, nwords);
+// Writes the entries of words[] (a row's bitmap in LDS) to out, ascending.
+__device__ void write_row(const uint32_t* words, int32_t nwords, int32_t* out) {
   const int32_t per = (nwords + kThreads - 1) / kThreads;
   const int32_t w0 = threadIdx.x * per;
   const int32_t w1 = w0 + per < nwords ? w0 + per : nwords;
   int32_t c = 0;
   for (int32_t w = w0; w < w1; ++w) c += __popc(words[w]);
-  int32_t pos = row_ptr[blockIdx.x] + block_exclusive_scan(c, nullptr);
+  int32_t pos = block_exclusive_scan(c, nullptr);
   for (int32_t w = w0; w < w1; ++w) {
     uint32_t m = words[w];
     while (m) {
       const int32_t bit = __ffs(m) - 1;
       m &= m - 1;
-      col_idx[pos++] = w * 32 + bit;
+      out[pos++] = w * 32 + bit;
     }
   }
+}
+
+__global__ void __launch_bounds__(kThreads) mask_fill_kernel(MaskGeom g, int32_t nwords, const int32_t* row_ptr,
+                                                            int32_t* col_idx) {
+  extern __shared__ uint32_t words[];
+  row_bitmap(g, blockIdx.x, words, nwords);
+  write_row(words, nwords, col_idx + row_ptr[blockIdx.x]);
 }
 
 // In place: counts[0..n) -> exclusive prefix, counts[n] = total (as int32), *total64 = exact total.
@@ -209,6 +221,85 @@ __device__ inline bool row_contains(const int32_t* col_idx, int32_t lo, int32_t 
   return false;
 }
 
+// Sum of (a, b, c) over the workgroup, to every thread.
+__device__ void block_sum3(long long& a, long long& b, int32_t& c) {
+  __shared__ long long part_a[kThreads / 64], part_b[kThreads / 64];
+  __shared__ int32_t part_c[kThreads / 64];
+  for (int off = 32; off > 0; off >>= 1) {
+    a += __shfl_xor(a, off);
+    b += __shfl_xor(b, off);
+    c += __shfl_xor(c, off);
+  }
+  if ((threadIdx.x & 63) == 0) {
+    part_a[threadIdx.x >> 6] = a;
+    part_b[threadIdx.x >> 6] = b;
+    part_c[threadIdx.x >> 6] = c;
+  }
+  __syncthreads();
+  a = b = 0;
+  c = 0;
+  for (int w = 0; w < kThreads / 64; ++w) {
+    a += part_a[w];
+    b += part_b[w];
+    c += part_c[w];
+  }
+  __syncthreads();
+}
+
+// Launch partition: slice[k] = first block r whose weight prefix W(r) = ptr[r] + kItemCost*r
+// reaches k/8 of the total (slice[0] = 0, slice[8] = nb): 8 runs of consecutive blocks with
+// equal work, one per XCD.  kItemCost stands for the fixed cost of a work item (loading Q,
+// storing O) in units of one listed block.
+constexpr int kItemCost = 4;
+__device__ inline long long slice_target(long long total, int32_t nb, int k) {
+  return ((total + (long long)kItemCost * nb) * k + 7) / 8;
+}
+
+// What workgroup r needs to know of all lists to write its own: where it starts.  On the way it writes
+// ptr[r], the launch partitions and the totals, so that neither a scan nor a partition pass is needed: every
+// workgroup reads all counts (nb / 256 rounds), which up to kMaxOrdered blocks costs less than the launches.
+__device__ int32_t place_list(const int32_t* counts, int32_t nb, int32_t r, int32_t* ptr, int32_t* slice, int32_t* order,
+                              long long* total64) {
+  const int32_t len = counts[r];
+  long long before = 0, total = 0;
+  int32_t ahead = 0;
+  for (int32_t j = threadIdx.x; j < nb; j += kThreads) {
+    const int32_t other = counts[j];
+    total += other;
+    before += j < r ? other : 0;
+    ahead += (other > len || (other == len && j < r)) ? 1 : 0;
+  }
+  block_sum3(before, total, ahead);
+  if (threadIdx.x == 0) {
+    ptr[r] = (int32_t)before;
+    order[ahead] = r;
+    if (r == nb - 1) {
+      ptr[nb] = (int32_t)total;
+      *total64 = total;
+    }
+  }
+  if (threadIdx.x <= 8) {
+    const int k = threadIdx.x;
+    const long long w = before + (long long)kItemCost * r, target = slice_target(total, nb, k);
+    if (k == 0 || k == 8) {
+      if (r == 0) slice[k] = k == 0 ? 0 : nb;
+    } else if (w >= target && (r == 0 || w - counts[r - 1] - kItemCost < target)) {
+      slice[k] = r;
+    } else if (r == nb - 1 && w < target) {
+      slice[k] = nb;
+    }
+  }
+  return (int32_t)before;
+}
+
+__global__ void __launch_bounds__(kThreads) mask_lists_kernel(MaskGeom g, int32_t nwords, const int32_t* counts, int32_t* row_ptr,
+                                                             int32_t* slice, int32_t* order, long long* total64, int32_t* col_idx) {
+  extern __shared__ uint32_t words[];
+  row_bitmap(g, blockIdx.x, words, nwords);
+  const int32_t start = place_list(counts, g.nb, blockIdx.x, row_ptr, slice, order, total64);
+  write_row(words, nwords, col_idx + start);
+}
+
 // Transposed lists: workgroup kb looks kb up in every (ascending) row.
 __global__ void __launch_bounds__(kThreads) transpose_count_kernel(const int32_t* row_ptr, const int32_t* col_idx,
                                                                   int32_t nb, int32_t* tcounts) {
@@ -221,10 +312,7 @@ __global__ void __launch_bounds__(kThreads) transpose_count_kernel(const int32_t
   if (threadIdx.x == 0) tcounts[kb] = total;
 }
 
-__global__ void __launch_bounds__(kThreads) transpose_fill_kernel(const int32_t* row_ptr, const int32_t* col_idx,
-                                                                 int32_t nb, const int32_t* col_ptr, int32_t* row_idx) {
-  const int32_t kb = blockIdx.x;
-  int32_t pos = col_ptr[kb];
+__device__ void write_column(const int32_t* row_ptr, const int32_t* col_idx, int32_t nb, int32_t kb, int32_t pos, int32_t* row_idx) {
   for (int32_t base = 0; base < nb; base += kThreads) {
     const int32_t qb = base + threadIdx.x;
     const int32_t hit = (qb < nb && row_contains(col_idx, row_ptr[qb], row_ptr[qb + 1], kb)) ? 1 : 0;
@@ -235,11 +323,18 @@ __global__ void __launch_bounds__(kThreads) transpose_fill_kernel(const int32_t*
   }
 }
 
-// Launch partition: slice[k] = first block r whose weight prefix W(r) = ptr[r] + kItemCost*r
-// reaches k/8 of the total (slice[0] = 0, slice[8] = nb): 8 runs of consecutive blocks with
-// equal work, one per XCD.  kItemCost stands for the fixed cost of a work item (loading Q,
-// storing O) in units of one listed block.
-constexpr int kItemCost = 4;
+__global__ void __launch_bounds__(kThreads) transpose_fill_kernel(const int32_t* row_ptr, const int32_t* col_idx,
+                                                                 int32_t nb, const int32_t* col_ptr, int32_t* row_idx) {
+  write_column(row_ptr, col_idx, nb, blockIdx.x, col_ptr[blockIdx.x], row_idx);
+}
+
+__global__ void __launch_bounds__(kThreads) transpose_lists_kernel(const int32_t* row_ptr, const int32_t* col_idx, int32_t nb,
+                                                                  const int32_t* counts, int32_t* col_ptr, int32_t* slice,
+                                                                  int32_t* order, long long* total64, int32_t* row_idx) {
+  const int32_t start = place_list(counts, nb, blockIdx.x, col_ptr, slice, order, total64);
+  write_column(row_ptr, col_idx, nb, blockIdx.x, start, row_idx);
+}
+
 // Workgroup 0 cuts the slices; the others, a wave per block, place the block at its rank by falling
 // list length (equal lengths: by index) if there is an order to fill.
 __global__ void __launch_bounds__(kThreads) partition_kernel(const int32_t* ptr, int32_t nb, int32_t* slice, int32_t* order) {
@@ -258,8 +353,7 @@ __global__ void __launch_bounds__(kThreads) partition_kernel(const int32_t* ptr,
   }
   const int k = threadIdx.x;
   if (k > 8) return;
-  const long long total = (long long)ptr[nb] + (long long)kItemCost * nb;
-  const long long target = (total * k + 7) / 8;
+  const long long target = slice_target(ptr[nb], nb, k);
   int32_t lo = 0, hi = nb;  // smallest r in [0, nb] with W(r) >= target
   while (lo < hi) {
     const int32_t mid = lo + ((hi - lo) >> 1);
@@ -293,7 +387,9 @@ int alloc_meta_and_ptrs(radial_mask* m) {
   const int64_t np = aligned_ints((int64_t)m->n_blocks + 1);
   RADIAL_HIP_TRY(hipMalloc(&m->d_meta, sizeof(int32_t) * kMetaInts));
   const int64_t no = m->n_blocks <= kMaxOrdered ? aligned_ints(m->n_blocks) : 0;
-  RADIAL_HIP_TRY(hipMalloc(&m->d_ptrs, sizeof(int32_t) * (np + no) * ((m->flags & RADIAL_MASK_TRANSPOSE) ? 2 : 1)));
+  const int64_t lists = (m->flags & RADIAL_MASK_TRANSPOSE) ? 2 : 1;
+  RADIAL_HIP_TRY(hipMalloc(&m->d_ptrs, sizeof(int32_t) * ((np + no) * lists + no)));
+  if (no) m->d_counts = m->d_ptrs + (np + no) * lists;
   m->d_row_ptr = m->d_ptrs;
   if (no) m->d_order = m->d_ptrs + np;
   m->d_slice = m->d_meta + 8;
@@ -305,7 +401,7 @@ int alloc_meta_and_ptrs(radial_mask* m) {
   return RADIAL_OK;
 }
 
-// Needs m->nnz.
+// Needs m->nnz (or a bound of it).
 int alloc_idx(radial_mask* m) {
   const int64_t ni = aligned_ints(m->nnz > 0 ? m->nnz : 1);
   RADIAL_HIP_TRY(hipMalloc(&m->d_idx, sizeof(int32_t) * ni * ((m->flags & RADIAL_MASK_TRANSPOSE) ? 2 : 1)));
@@ -316,11 +412,16 @@ int alloc_idx(radial_mask* m) {
 
 // Shared tail of the constructors: transposed lists (optional) and launch partitions, then the one
 // wait of the call for everything queued on the stream (the partitions come back to the host).
-int finish_mask(radial_mask* m, hipStream_t st) {
+// rows_placed: the rows' launch partitions and their total are on the device already.
+int finish_mask(radial_mask* m, bool rows_placed, hipStream_t st) {
   const int32_t nb = m->n_blocks;
-  int32_t h_meta[kMetaInts];
-  launch_partition(m->d_row_ptr, nb, m->d_slice, m->d_order, st);
-  if (m->flags & RADIAL_MASK_TRANSPOSE) {
+  alignas(8) int32_t h_meta[kMetaInts];
+  if (!rows_placed) launch_partition(m->d_row_ptr, nb, m->d_slice, m->d_order, st);
+  if ((m->flags & RADIAL_MASK_TRANSPOSE) && m->d_counts) {
+    transpose_count_kernel<<<nb, kThreads, 0, st>>>(m->d_row_ptr, m->d_col_idx, nb, m->d_counts);
+    transpose_lists_kernel<<<nb, kThreads, 0, st>>>(m->d_row_ptr, m->d_col_idx, nb, m->d_counts, m->d_col_ptr, m->d_slice_t, m->d_order_t,
+                                                    (long long*)(m->d_meta + 2), m->d_row_idx);
+  } else if (m->flags & RADIAL_MASK_TRANSPOSE) {
     transpose_count_kernel<<<nb, kThreads, 0, st>>>(m->d_row_ptr, m->d_col_idx, nb, m->d_col_ptr);
     scan_kernel<<<1, kThreads, 0, st>>>(m->d_col_ptr, nb, (long long*)(m->d_meta + 2));
     transpose_fill_kernel<<<nb, kThreads, 0, st>>>(m->d_row_ptr, m->d_col_idx, nb, m->d_col_ptr, m->d_row_idx);
@@ -330,6 +431,7 @@ int finish_mask(radial_mask* m, hipStream_t st) {
   if (e == hipSuccess) e = hipMemcpyAsync(h_meta, m->d_meta, sizeof h_meta, hipMemcpyDeviceToHost, st);
   if (e == hipSuccess) e = hipStreamSynchronize(st);
   if (e != hipSuccess) return fail(RADIAL_EHIP, "mask kernels failed: %s", hipGetErrorString(e));
+  if (rows_placed) m->nnz = *(const long long*)h_meta;
   for (int k = 0; k < 8; ++k) {
     const int32_t len = h_meta[8 + k + 1] - h_meta[8 + k];
     m->max_slice = len > m->max_slice ? len : m->max_slice;
@@ -385,6 +487,25 @@ static int build_radial(radial_mask* m, const radial_mask_params* p, hipStream_t
                    (int32_t)((int64_t)p->frames * p->tokens_per_frame)};
   long long total = 0;
   if (int rc = alloc_meta_and_ptrs(m)) return rc;
+  if (m->d_counts) {
+    mask_count_kernel<<<nb, kThreads, nwords * sizeof(uint32_t), st>>>(g, nwords, m->d_counts);
+    RADIAL_HIP_TRY(hipGetLastError());
+    if (nb <= kMaxUncounted) {
+      m->nnz = (int64_t)nb * nb;
+    } else {
+      const std::unique_ptr<int32_t[]> counts(new (std::nothrow) int32_t[nb]);
+      if (!counts) return fail(RADIAL_ENOMEM, "host allocation failed");
+      hipError_t e = hipMemcpyAsync(counts.get(), m->d_counts, sizeof(int32_t) * nb, hipMemcpyDeviceToHost, st);
+      if (e == hipSuccess) e = hipStreamSynchronize(st);   // the list storage is sized by the count
+      if (e != hipSuccess) return fail(RADIAL_EHIP, "mask count failed: %s", hipGetErrorString(e));
+      for (int32_t r = 0; r < nb; ++r) m->nnz += counts[r];  // at most kMaxOrdered^2 = 2^28
+    }
+    if (int rc = alloc_idx(m)) return rc;
+    mask_lists_kernel<<<nb, kThreads, nwords * sizeof(uint32_t), st>>>(g, nwords, m->d_counts, m->d_row_ptr, m->d_slice, m->d_order,
+                                                                       (long long*)m->d_meta, m->d_col_idx);
+    RADIAL_HIP_TRY(hipGetLastError());
+    return finish_mask(m, true, st);
+  }
   mask_count_kernel<<<nb, kThreads, nwords * sizeof(uint32_t), st>>>(g, nwords, m->d_row_ptr);
   scan_kernel<<<1, kThreads, 0, st>>>(m->d_row_ptr, nb, (long long*)m->d_meta);
   hipError_t e = hipGetLastError();
@@ -396,7 +517,7 @@ static int build_radial(radial_mask* m, const radial_mask_params* p, hipStream_t
   if (int rc = alloc_idx(m)) return rc;
   mask_fill_kernel<<<nb, kThreads, nwords * sizeof(uint32_t), st>>>(g, nwords, m->d_row_ptr, m->d_col_idx);
   RADIAL_HIP_TRY(hipGetLastError());
-  return finish_mask(m, st);
+  return finish_mask(m, false, st);
 }
 
 extern "C" int radial_mask_build(const radial_mask_params* p, void* hip_stream, radial_mask** out) {
@@ -467,7 +588,7 @@ static int build_dense(radial_mask* m, hipStream_t st) {
   if (int rc = alloc_idx(m)) return rc;
   dense_fill_kernel<<<1024, kThreads, 0, st>>>((int32_t)nb, m->d_row_ptr, m->d_col_idx);
   RADIAL_HIP_TRY(hipGetLastError());
-  return finish_mask(m, st);
+  return finish_mask(m, false, st);
 }
 
 extern "C" int radial_mask_build_dense(int32_t n_tokens, int32_t block, uint32_t flags, void* hip_stream,
@@ -501,7 +622,7 @@ static int build_from_csr(radial_mask* m, const int32_t* row_ptr, const int32_t*
   RADIAL_HIP_TRY(hipMemcpyAsync(m->d_row_ptr, row_ptr, sizeof(int32_t) * (nb + 1), hipMemcpyHostToDevice, st));
   if (m->nnz > 0)
     RADIAL_HIP_TRY(hipMemcpyAsync(m->d_col_idx, col_idx, sizeof(int32_t) * m->nnz, hipMemcpyHostToDevice, st));
-  return finish_mask(m, st);
+  return finish_mask(m, false, st);
 }
 
 extern "C" int radial_mask_from_csr(int32_t n_tokens, int32_t block, uint32_t flags, const int32_t* row_ptr,
