@@ -103,9 +103,9 @@ def _check(rc: int):
 
 
 def _stream_ptr(stream):
-    if stream is None:
+    if stream is None:  # the current stream of the current device, without a Stream object around it
         import torch
-        stream = torch.cuda.current_stream()
+        return c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
     return c_void_p(int(getattr(stream, "cuda_stream", stream)))
 
 
@@ -192,21 +192,23 @@ def radial_mask_copy_transpose_to_host(mask: RadialMask):
 
 def _tensor(t, name) -> radial_tensor:
     import torch
-    if t.dtype != torch.bfloat16 or not t.is_cuda or t.dim() != 4 or t.stride(3) != 1:
+    stride = t.stride()
+    if t.dtype is not torch.bfloat16 or not t.is_cuda or len(stride) != 4 or stride[3] != 1:
         raise ValueError(f"{name} must be a CUDA bf16 tensor [B, H, N, D] with unit stride in D")
-    return radial_tensor(t.data_ptr(), t.stride(0), t.stride(1), t.stride(2))
+    return radial_tensor(t.data_ptr(), stride[0], stride[1], stride[2])
 
 
 def radial_attn_fwd(q, k, v, out, lse, mask: RadialMask, scale: float, stream=None):
     """out[B,H,N,D] (bf16) and lse[B,H,N] (fp32, or None) <- block-sparse attention of q, k, v."""
     import torch
-    B, H, N, D = q.shape
+    shape = q.shape
+    B, H, N, D = shape
     for t, nm in ((k, "k"), (v, "v"), (out, "out")):
-        if tuple(t.shape) != (B, H, N, D):
+        if t.shape != shape:
             raise ValueError(f"{nm} has shape {tuple(t.shape)}, expected {(B, H, N, D)}")
     lse_ptr = None
     if lse is not None:
-        if lse.dtype != torch.float32 or not lse.is_cuda or not lse.is_contiguous() or tuple(lse.shape) != (B, H, N):
+        if lse.dtype is not torch.float32 or not lse.is_cuda or not lse.is_contiguous() or lse.shape != shape[:3]:
             raise ValueError("lse must be a contiguous CUDA float32 tensor [B, H, N]")
         lse_ptr = c_void_p(lse.data_ptr())
     _check(load().radial_attn_fwd(B, H, N, D, _tensor(q, "q"), _tensor(k, "k"), _tensor(v, "v"), _tensor(out, "out"),
