@@ -8,7 +8,8 @@
 //     b > s and |i-j| mod ceil(b/s) == 0:   l in [klo, khi]  (single diagonal k == l),
 // so the key blocks touched by a query block are a union of contiguous block ranges, one per
 // (query frame in the block, key frame).  Each workgroup ORs those ranges into a bitmap in
-// LDS; a count pass, an exclusive scan and a fill pass turn the bitmaps into compressed lists.
+// LDS; a count pass and a pass in which every row finds its place among the counts turn the bitmaps into
+// compressed lists (above kMaxOrdered blocks: count, exclusive scan, fill).
 #include <stdarg.h>
 #include <stdio.h>
 #include <string.h>
