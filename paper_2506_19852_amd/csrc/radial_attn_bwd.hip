@@ -38,6 +38,7 @@ struct BwdTile {
   static constexpr int kWaves = kRows / 32;  // one wave per 32 keys
   static constexpr int kThreads = 64 * kWaves * S;
   static constexpr int kSubs = BLK / kStageQ;  // stages per listed query block
+  static constexpr int kLastOffset = BLK - kStageQ;
   static constexpr int kSteps = D / 16;
   static constexpr int kDTiles = D / 32;
   static constexpr int kQBytes = kStageQ * D * 2;        // Q or dO stage tile
@@ -229,7 +230,7 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a) {
   StagePos q_at = {0, 0}, q_at_next = {0, 0};
   if (n_stage > 0) {
     q0 = __builtin_amdgcn_readlane(cvec, 0) * BLK;
-    if (kExact) q_at = stage_pos(cvec_at, 0, 0, a.rule.s);
+    if (kExact) q_at = stage_pos<0>(cvec_at, 0, 0, a.rule.s);
     issue_stage(q0, 0);
   }
 
@@ -245,7 +246,7 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a) {
         if (kExact) cvec_at = block_pos(cvec * BLK, a.rule.s);
       }
       q0_next = __builtin_amdgcn_readlane(cvec, e1 & 63) * BLK + ((u + 1) % T::kSubs) * kStageQ;
-      if (kExact) q_at_next = stage_pos(cvec_at, e1 & 63, ((u + 1) % T::kSubs) * kStageQ, a.rule.s);
+      if (kExact) q_at_next = stage_pos<T::kLastOffset>(cvec_at, e1 & 63, ((u + 1) % T::kSubs) * kStageQ, a.rule.s);
     }
 
     wait_all_copies();  // stage u has landed
@@ -450,6 +451,7 @@ struct DqTile {
   static constexpr int kWaves = kRows / 32;  // one wave per 32 query rows
   static constexpr int kThreads = 64 * kWaves * S;
   static constexpr int kSubs = BLK / kStageKeys;
+  static constexpr int kLastOffset = BLK - kStageKeys;
   static constexpr int kSteps = D / 16;
   static constexpr int kDTiles = D / 32;
   static constexpr int kTileBytes = kStageKeys * D * 2;  // one K (or V) stage tile
@@ -563,7 +565,7 @@ __global__ void __launch_bounds__(2 * BLK / R * S, 2) radial_bwd_dq_kernel(const
   StagePos k_at = {0, 0}, k_at_next = {0, 0};
   if (n_stage > 0) {
     key0 = __builtin_amdgcn_readlane(cvec, 0) * BLK;
-    if (kExact) k_at = stage_pos(cvec_at, 0, 0, a.rule.s);
+    if (kExact) k_at = stage_pos<0>(cvec_at, 0, 0, a.rule.s);
     issue_stage(key0, 0);
   }
   for (int32_t u = 0; u < n_stage; ++u) {
@@ -578,7 +580,7 @@ __global__ void __launch_bounds__(2 * BLK / R * S, 2) radial_bwd_dq_kernel(const
         if (kExact) cvec_at = block_pos(cvec * BLK, a.rule.s);
       }
       key0_next = __builtin_amdgcn_readlane(cvec, e1 & 63) * BLK + ((u + 1) % T::kSubs) * T::kStageKeys;
-      if (kExact) k_at_next = stage_pos(cvec_at, e1 & 63, ((u + 1) % T::kSubs) * T::kStageKeys, a.rule.s);
+      if (kExact) k_at_next = stage_pos<T::kLastOffset>(cvec_at, e1 & 63, ((u + 1) % T::kSubs) * T::kStageKeys, a.rule.s);
     }
     wait_all_copies();
     __syncthreads();

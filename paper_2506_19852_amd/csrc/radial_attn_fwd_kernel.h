@@ -44,6 +44,7 @@ struct Tile {
   static constexpr int kThreads = 64 * kWaves * S;
   static constexpr int kPiecesPerRow = D / 8;      // 16-byte pieces per K/V row
   static constexpr int kSubs = BLK / kStageKeys;   // stages per listed key block
+  static constexpr int kLastOffset = BLK - kStageKeys;
   static constexpr int kStageBytes = kStageKeys * D * 2;            // one K (or V) stage tile
   static constexpr int kLoadsPerWave = kStageBytes / 1024 / kWaves; // 1 KiB copies per wave per tile
   static constexpr int kSteps = D / 16;            // MFMA k-steps of the S product
@@ -194,7 +195,7 @@ __global__ void __launch_bounds__(2 * BLK / R * S, 2) radial_fwd_kernel(const Fw
   StagePos k_at = {0, 0}, k_at_next = {0, 0};  // its (frame, position), and the next stage's
   if (n_stage > 0) {
     key0 = __builtin_amdgcn_readlane(cvec, 0) * BLK;
-    if (kExact) k_at = stage_pos(cvec_at, 0, 0, a.rule.s);
+    if (kExact) k_at = stage_pos<0>(cvec_at, 0, 0, a.rule.s);
     issue_stage(key0, 0);
   }
 
@@ -315,7 +316,7 @@ __global__ void __launch_bounds__(2 * BLK / R * S, 2) radial_fwd_kernel(const Fw
         if (kExact) cvec_at = block_pos(cvec * BLK, a.rule.s);
       }
       key0_next = __builtin_amdgcn_readlane(cvec, e1 & 63) * BLK + ((u + 1) % T::kSubs) * T::kStageKeys;
-      if (kExact) k_at_next = stage_pos(cvec_at, e1 & 63, ((u + 1) % T::kSubs) * T::kStageKeys, a.rule.s);
+      if (kExact) k_at_next = stage_pos<T::kLastOffset>(cvec_at, e1 & 63, ((u + 1) % T::kSubs) * T::kStageKeys, a.rule.s);
     }
 
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's copies of stage u have landed

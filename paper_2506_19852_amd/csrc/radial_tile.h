@@ -168,12 +168,12 @@ __device__ __forceinline__ bool work_item(const WorkMap& w, int32_t& bh, int32_t
 
 // For one (query frame i, key frame j) pair: the largest |k - l| a query position k may
 // attend; -1 = nothing, >= s - 1 = the whole frame.
-__device__ __forceinline__ int32_t radial_half_width(const TokenRule& rule, int32_t i, int32_t j) {
+__host__ __device__ __forceinline__ int32_t radial_half_width(const TokenRule& rule, int32_t i, int32_t j) {
   if (j < rule.sink || i >= rule.frames || j >= rule.frames) return rule.s;  // sink, text tokens
   const int32_t d = i > j ? i - j : j - i;
   if (rule.half_width) return rule.half_width[d];  // banded pattern: table lookup (d <= frames)
   if (d < 2) return rule.s - 1;            // band 0: the whole frame, never scaled
-  const int32_t r = 31 - __clz(d);         // floor(log2 d)
+  const int32_t r = 31 - __builtin_clz(d);       // floor(log2 d)
   const int32_t w = rule.w0 >> r;          // diagonal width floor(c*s / 2^r)
   if (w >= 1) return (w < rule.s ? w : rule.s) - 1;
   const int64_t b_den = (int64_t)rule.den << r;
@@ -189,23 +189,33 @@ struct StagePos {
 };
 
 // (frame, position) of token index `block_start` for every lane's list entry.
-__device__ __forceinline__ StagePos block_pos(int32_t block_start, int32_t s) {
+__host__ __device__ __forceinline__ StagePos block_pos(int32_t block_start, int32_t s) {
   StagePos r;
   r.frame = block_start / s;
   r.pos = block_start - r.frame * s;
   return r;
 }
 
-// Entry `idx` of the per-lane positions, advanced by `offset` (< 128) tokens; wave-uniform.
+// The position `offset` tokens further on, 0 <= offset <= kMaxOffset (the last stage's place in a block).
+// pos < s and s >= 64: up to 64 tokens cross at most one frame boundary, up to 128 at most two.
+template <int kMaxOffset>
+__host__ __device__ __forceinline__ StagePos advance(StagePos at, int32_t offset, int32_t s) {
+  static_assert(kMaxOffset <= 128, "more tokens than two frames");
+  at.pos += offset;
+#pragma unroll
+  for (int crossed = 0; crossed < (kMaxOffset > 64 ? 2 : 1); ++crossed)
+    if (at.pos >= s) {
+      at.pos -= s;
+      at.frame += 1;
+    }
+  return at;
+}
+
+// Entry `idx` of the per-lane positions, advanced by `offset` tokens; wave-uniform.
+template <int kMaxOffset>
 __device__ __forceinline__ StagePos stage_pos(StagePos per_lane, int idx, int32_t offset, int32_t s) {
-  StagePos r;
-  r.frame = __builtin_amdgcn_readlane(per_lane.frame, idx);
-  r.pos = __builtin_amdgcn_readlane(per_lane.pos, idx) + offset;
-  if (r.pos >= s) {
-    r.pos -= s;
-    r.frame += 1;
-  }
-  return r;
+  const StagePos at = {__builtin_amdgcn_readlane(per_lane.frame, idx), __builtin_amdgcn_readlane(per_lane.pos, idx)};
+  return advance<kMaxOffset>(at, offset, s);
 }
 
 // What one lane's token (its own frame/position, a query or a key) sees of a stage: tokens
@@ -218,13 +228,13 @@ struct StageRule {
   bool none;     // wave-uniform: no lane of the wave has a visible pair in this stage
 
   // token `x` (0..63) of the stage
-  __device__ __forceinline__ bool visible(int x) const {
+  __host__ __device__ __forceinline__ bool visible(int x) const {
     return ((uint32_t)(x - lo0) < n0) | ((uint32_t)(x - lo1) < n1);  // n1 = 0 without a second frame
   }
   // bit x set iff token x of the stage is visible
-  __device__ __forceinline__ uint64_t visible_mask() const { return stage_interval(lo0, n0) | stage_interval(lo1, n1); }
+  __host__ __device__ __forceinline__ uint64_t visible_mask() const { return stage_interval(lo0, n0) | stage_interval(lo1, n1); }
   // bits [lo, lo + n) of a 64-token stage (n = 0: none; lo + n <= 64 otherwise)
-  __device__ static __forceinline__ uint64_t stage_interval(int32_t lo, uint32_t n) {
+  __host__ __device__ static __forceinline__ uint64_t stage_interval(int32_t lo, uint32_t n) {
     if (n == 0u) return 0ull;
     const uint64_t ones = n >= 64u ? ~0ull : ((1ull << n) - 1ull);
     return ones << lo;
@@ -248,10 +258,11 @@ __device__ __forceinline__ uint32_t lane_element_bits(uint64_t token_mask, int g
   return (uint32_t)v;
 }
 
+// The lane's own part of a StageRule (lo0, n0, lo1, n1).
 // own_is_query: the lane holds a query and the stage holds keys; otherwise the reverse.
 // kWidth: tokens in the stage (64, or 32 for the kernels that walk half-size stages).
-template <int kWidth = 64>
-__device__ __forceinline__ StageRule stage_rule(const TokenRule& rule, StagePos own, StagePos stage, bool own_is_query) {
+template <int kWidth>
+__host__ __device__ __forceinline__ StageRule stage_intervals(const TokenRule& rule, StagePos own, StagePos stage, bool own_is_query) {
   const int32_t s = rule.s;
   const int32_t hw0 = own_is_query ? radial_half_width(rule, own.frame, stage.frame)
                                    : radial_half_width(rule, stage.frame, own.frame);
@@ -267,6 +278,12 @@ __device__ __forceinline__ StageRule stage_rule(const TokenRule& rule, StagePos 
   const int32_t a1 = max(own.pos - hw1 + split, split), b1 = min(own.pos + hw1 + split, kWidth - 1);
   r.lo1 = a1;
   r.n1 = b1 >= a1 ? (uint32_t)(b1 - a1 + 1) : 0u;
+  return r;
+}
+
+template <int kWidth = 64>
+__device__ __forceinline__ StageRule stage_rule(const TokenRule& rule, StagePos own, StagePos stage, bool own_is_query) {
+  StageRule r = stage_intervals<kWidth>(rule, own, stage, own_is_query);
   const bool all_visible = r.n0 + r.n1 == (uint32_t)kWidth;
   r.partial = __builtin_amdgcn_ballot_w64(!all_visible) != 0;
   r.none = __builtin_amdgcn_ballot_w64(r.n0 + r.n1 != 0u) == 0;

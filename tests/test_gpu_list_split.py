@@ -73,6 +73,38 @@ def test_forward_and_backward_match_float64(D, block, H, N, rule):
     m.free()
 
 
+# Frames whose boundaries fall anywhere in a block; heads so that 8 blocks of 128 (16 of 64) take each form: half
+# blocks, two groups, one; four groups, two, and from 1600 items one in every kernel that has that form.
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("block, H", [(128, 4), (128, 20), (128, 40), (64, 4), (64, 20), (64, 100)])
+@pytest.mark.parametrize("s", [65, 70, 79, 90, 93, 100, 333])
+def test_token_rule_with_any_frame_length(D, block, H, s):
+    import torch
+    from oracle import build as obuild
+    from paper_2506_19852_amd import binding as rb
+    print(f"token rule s={s} block={block} H={H} D={D}", flush=True)
+    frames = 1000 // s
+    N = frames * s
+    g = torch.Generator(device="cuda").manual_seed(s + H)
+    q, k, v, do = (torch.randn((1, H, N, D), device="cuda", generator=g).bfloat16() for _ in range(4))
+    scale = D ** -0.5
+    m = rb.radial_mask_build(frames, s, block, 1, rb.RADIAL_MASK_TRANSPOSE | rb.RADIAL_MASK_TOKEN_EXACT)
+    vis = torch.from_numpy(obuild.token_mask(frames, s, 1, 0, N, np.arange(N))).cuda()
+    out, dq, dk, dv = (torch.full_like(q, float("nan")) for _ in range(4))
+    lse = torch.full((1, H, N), float("nan"), dtype=torch.float32, device="cuda")
+    ws = torch.empty(rb.radial_attn_bwd_workspace(1, H, N, D, m), dtype=torch.uint8, device="cuda")
+    rb.radial_attn_fwd(q, k, v, out, lse, m, scale)
+    rb.radial_attn_bwd(q, k, v, out, do, lse, dq, dk, dv, m, scale, ws)
+    for h in (0, H // 2, H - 1):
+        ref = reference(q[0, h], k[0, h], v[0, h], do[0, h], vis, scale)
+        # bounds as above
+        assert (lse[0, h].double() - ref[1]).abs().max() <= 1e-4, h
+        for name, x, r in zip(("out", "dq", "dk", "dv"), (out[0, h], dq[0, h], dk[0, h], dv[0, h]), (ref[0], *ref[2:])):
+            assert torch.isfinite(x).all(), (name, h)
+            assert (x.double() - r).norm() <= 8e-3 * r.norm(), (name, h, (x.double() - r).norm() / r.norm())
+    m.free()
+
+
 @pytest.mark.parametrize("H, N", [(1, 1), (2, 777), (4, 64 * 128 - 7), (5, 52 * 128)])
 def test_8bit_scores_match_float64_on_the_codes(H, N):
     import torch
