@@ -465,14 +465,19 @@ template <int D, int BLK, bool kExact, int S, int R>
 __global__ void __launch_bounds__(2 * BLK / R * S, 2) radial_bwd_dq_kernel(const BwdArgs a) {
   using T = DqTile<D, BLK, S, R>;
   using SW = SwzTile<D>;
-  extern __shared__ __attribute__((aligned(1024))) char lds_all[];  // [group][stage buffer][K, V][kStageKeys x D bf16]
+  // [group][stage buffer][K, V][kStageKeys x D bf16]; one group's are a static array, as in the forward
+  __shared__ __attribute__((aligned(1024))) char lds_one[S == 1 ? T::kLdsBytes : 16];
+  extern __shared__ __attribute__((aligned(1024))) char lds_all[];
 
   const int lane = threadIdx.x & 63;
   const int wave_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int group = S == 1 ? 0 : wave_all / T::kWaves;
   const int wave = S == 1 ? wave_all : wave_all % T::kWaves;
-  char* lds = lds_all + group * T::kGroupBytes;
-  const uint32_t lds_base = lds_address(lds);
+  const auto lds_at = [&](int32_t offset) __attribute__((always_inline)) -> const char* {
+    if constexpr (S == 1) return lds_one + offset;
+    else return lds_all + group * T::kGroupBytes + offset;
+  };
+  const uint32_t lds_base = lds_address(lds_at(0));
   const int lq = lane & 31;
   const int g = lane >> 5;
   const int i16 = lane & 15;
@@ -585,7 +590,7 @@ __global__ void __launch_bounds__(2 * BLK / R * S, 2) radial_bwd_dq_kernel(const
     wait_all_copies();
     __syncthreads();
 
-    const char* lds_k = lds + buf * 2 * T::kTileBytes;
+    const char* lds_k = lds_at(buf * 2 * T::kTileBytes);
     const char* lds_v = lds_k + T::kTileBytes;
     const bool ragged = key0 + T::kStageKeys > a.N;
     StageRule vis = {};
@@ -704,12 +709,12 @@ template <int D, int BLK, bool kExact, int S, int R>
 int launch_dq(BwdArgs a, hipStream_t stream) {
   using T = DqTile<D, BLK, S, R>;
   const auto kernel = radial_bwd_dq_kernel<D, BLK, kExact, S, R>;
-  if (T::kLdsBytes > 65536) {
+  if (S > 1 && T::kLdsBytes > 65536) {
     static DeviceOnce configured;
     if (int rc = allow_dynamic_lds(configured, (const void*)kernel, T::kLdsBytes)) return rc;
   }
   a.work.ordered *= R;
-  kernel<<<dim3((unsigned)work_grid(a.work, a.n_blocks)), dim3(T::kThreads), T::kLdsBytes, stream>>>(a);
+  kernel<<<dim3((unsigned)work_grid(a.work, a.n_blocks)), dim3(T::kThreads), S == 1 ? 0 : T::kLdsBytes, stream>>>(a);
   return RADIAL_OK;
 }
 

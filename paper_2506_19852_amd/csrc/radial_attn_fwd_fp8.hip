@@ -95,14 +95,19 @@ __global__ void __launch_bounds__(256) quantize_fp8_kernel(TensorArg x, uint8_t*
 template <int S>
 __global__ void __launch_bounds__(64 * kWaves * S, 3) radial_fwd_fp8_kernel(const Fp8FwdArgs a) {
   static_assert((S - 1) * kWaves * kMergeBytes <= S * 2 * kBufBytes || S == 1, "the merge reuses the stage buffers");
-  extern __shared__ __attribute__((aligned(1024))) char lds_all[];  // [group][stage buffer][K8 tile, V tile]
+  // [group][stage buffer][K8 tile, V tile]; one group's are a static array, as in the bf16 kernel
+  __shared__ __attribute__((aligned(1024))) char lds_one[S == 1 ? 2 * kBufBytes : 16];
+  extern __shared__ __attribute__((aligned(1024))) char lds_all[];
 
   const int lane = threadIdx.x & 63;
   const int wave_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int group = S == 1 ? 0 : wave_all / kWaves;
   const int wave = S == 1 ? wave_all : wave_all % kWaves;
-  char* lds = lds_all + group * 2 * kBufBytes;
-  const uint32_t lds_base = lds_address(lds);
+  const auto lds_at = [&](int32_t offset) __attribute__((always_inline)) -> const char* {
+    if constexpr (S == 1) return lds_one + offset;
+    else return lds_all + group * 2 * kBufBytes + offset;
+  };
+  const uint32_t lds_base = lds_address(lds_at(0));
   const int lq = lane & 31;
   const int g = lane >> 5;
 
@@ -237,7 +242,7 @@ __global__ void __launch_bounds__(64 * kWaves * S, 3) radial_fwd_fp8_kernel(cons
     const __bf16* vbase_next = vp + (int64_t)key_src * a.v.sn;
     const uint32_t kdst_next = lds_base + (buf ^ 1) * kBufBytes + wave * kKLoads * 1024;
     const uint32_t vdst_next = lds_base + (buf ^ 1) * kBufBytes + kK8Bytes + wave * kVLoads * 1024;
-    const char* lds_k = lds + buf * kBufBytes;
+    const char* lds_k = lds_at(buf * kBufBytes);
     const char* lds_v = lds_k + kK8Bytes;
 
     // ---- S^T = K8 Q8^T (unscaled code products) ---------------------------------------------
@@ -396,11 +401,11 @@ int launch_quantize_fp8(int32_t B, int32_t H, int32_t N, int32_t Dh, const Tenso
 template <int S>
 static int launch_split(const Fp8FwdArgs& a, hipStream_t stream) {
   constexpr int kLdsBytes = S * 2 * kBufBytes;
-  if (kLdsBytes > 65536) {
+  if (S > 1 && kLdsBytes > 65536) {
     static DeviceOnce configured;
     if (int rc = allow_dynamic_lds(configured, (const void*)radial_fwd_fp8_kernel<S>, kLdsBytes)) return rc;
   }
-  radial_fwd_fp8_kernel<S><<<dim3((unsigned)work_grid(a.work, a.n_blocks)), dim3(64 * kWaves * S), kLdsBytes, stream>>>(a);
+  radial_fwd_fp8_kernel<S><<<dim3((unsigned)work_grid(a.work, a.n_blocks)), dim3(64 * kWaves * S), S == 1 ? 0 : kLdsBytes, stream>>>(a);
   RADIAL_HIP_TRY(hipGetLastError());
   return RADIAL_OK;
 }

@@ -130,3 +130,23 @@ def test_hand_issued_mfmas_of_the_split_kernels_keep_their_promises(bwd_asm):
         found += 1
         assert check_kernel(name, list(instructions(body))) > 0, name
     assert found == 8, found   # D in {64, 128} x (block 64, half blocks of 128) x token rule on / off
+
+
+@pytest.mark.parametrize("source, kernel, unsplit", [
+    ("radial_attn_fwd.hip", "radial_fwd_kernel", "ELi1ELi1EEE"), ("radial_attn_bwd.hip", "radial_bwd_dq_kernel", "ELi1ELi1EEE"),
+    ("radial_attn_fwd_fp8.hip", "radial_fwd_fp8_kernel", "ILi1EEE")])
+def test_stage_buffers_of_unsplit_kernels_have_a_constant_address(source, kernel, unsplit, tmp_path):
+    """A static array: as dynamic LDS its address costs the stage loop vector adds, waits and read-ahead."""
+    if not os.path.exists(HIPCC) and shutil.which(HIPCC) is None:
+        pytest.skip("hipcc not available")
+    import sys
+    sys.path.insert(0, ROOT)
+    from paper_2506_19852_amd import build as hip_build
+    out = tmp_path / "kernels.s"
+    cmd = [HIPCC, *hip_build.FLAGS, "--cuda-device-only", "-S", os.path.join(hip_build.CSRC, source), "-o", str(out)]
+    r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    assert r.returncode == 0, r.stdout[-3000:]
+    sizes = re.findall(r"\.amdhsa_kernel (\S*" + kernel + r"\S*" + unsplit + r"\S*)\s+\.amdhsa_group_segment_fixed_size (\d+)", out.read_text())
+    assert sizes
+    for name, size in sizes:
+        assert int(size) >= 32768, name
