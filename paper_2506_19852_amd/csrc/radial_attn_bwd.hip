@@ -700,7 +700,7 @@ int launch_dkdv(BwdArgs a, hipStream_t stream) {
   else kernel = radial_bwd_dkdv_split_kernel<D, BLK, kExact, S, R>;
   static DeviceOnce configured;
   if (int rc = allow_dynamic_lds(configured, (const void*)kernel, T::kLdsBytes)) return rc;
-  a.work_t.ordered *= R;  // R > 1 only where all heads are taken by list length
+  a.work_t.ordered *= R;  // R > 1 only up to kOneRound items, where all heads are taken by list length
   kernel<<<dim3((unsigned)work_grid(a.work_t, a.n_blocks)), dim3(T::kThreads), T::kLdsBytes, stream>>>(a);
   return RADIAL_OK;
 }
@@ -736,7 +736,7 @@ int launch(const BwdArgs& a, hipStream_t stream) {
   const int64_t items = work_items(a.work, a.n_blocks);
   int rc = RADIAL_OK;
   if constexpr (BLK == 128) {
-    const bool halves = items <= 128 && a.work.sliced == 0;
+    const bool halves = items <= 128;
     rc = halves ? launch_dkdv<D, BLK, kExact, 2, 2>(a, stream) : launch_dkdv<D, BLK, kExact, 1, 1>(a, stream);
     if (rc) return rc;
     rc = halves ? launch_dq<D, BLK, kExact, 4, 2>(a, stream)

@@ -434,7 +434,7 @@ int launch_split(FwdArgs a, hipStream_t stream) {
     static DeviceOnce configured;
     if (int rc = allow_dynamic_lds(configured, (const void*)kernel, T::kLdsBytes)) return rc;
   }
-  a.work.ordered *= R;  // R > 1 only where all heads are taken by list length
+  a.work.ordered *= R;  // R > 1 only up to kOneRound items, where all heads are taken by list length
   kernel<<<dim3((unsigned)work_grid(a.work, a.n_blocks)), dim3(T::kThreads), S == 1 ? 0 : T::kLdsBytes, stream>>>(a);
   RADIAL_HIP_TRY(hipGetLastError());
   return RADIAL_OK;
@@ -456,7 +456,7 @@ int launch(const FwdArgs& a, hipStream_t stream) {
   const int64_t items = work_items(a.work, a.n_blocks);
   if (items == 0) return RADIAL_OK;
   if constexpr (BLK == 128) {
-    if (items <= 128 && a.work.sliced == 0) return launch_split<D, BLK, kExact, kTrace, 4, 2>(a, stream);
+    if (items <= 128) return launch_split<D, BLK, kExact, kTrace, 4, 2>(a, stream);
     if (items <= 256) return launch_split<D, BLK, kExact, kTrace, 2, 1>(a, stream);
     return launch_split<D, BLK, kExact, kTrace, 1, 1>(a, stream);
   } else {

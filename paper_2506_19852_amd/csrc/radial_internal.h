@@ -120,7 +120,12 @@ constexpr int32_t kMaxOrdered = 16384;  // blocks up to which a mask carries the
 // larger ones, at most 8 and 160 MB (forward, 10 x 14 040: 0.910 -> 0.858 ms, 40 x 32 760: 13.44 -> 13.24 ms,
 // 24 x 118 800, 2 heads: 74.1 -> 73.4 ms; with 8 = 490 MB it takes 77.0 ms, with all 24 88.2 ms).  More than 8
 // heads by length put several heads on each XCD: 30 x 27 000 tokens in 64-token blocks 6.97 -> 9.35 ms.
+// A launch of at most kOneRound items, a workgroup for each compute unit, runs all at once: there is no tail and no
+// locality to keep, but slices of unequal length start workgroups without work, which hold up to 128 KiB of LDS as long as they
+// wait for their turn.  Such a launch goes by length whatever its number of heads (20 heads x 12 blocks: 288
+// workgroups for 240 items; forward, D 128, block 128, two groups: lists of 4 29.4 -> 17.4 us, of 12 55.8 -> 33.0).
 constexpr int64_t kOrderedWholeBytes = 256 << 20, kOrderedTailBytes = 160 << 20;
+constexpr int64_t kOneRound = 256;
 
 inline WorkMap make_work_map(const radial_mask* m, bool transposed, int32_t heads, int32_t D) {
   WorkMap w;
@@ -130,7 +135,7 @@ inline WorkMap make_work_map(const radial_mask* m, bool transposed, int32_t head
   const int64_t per_head = 4LL * D * m->n_tokens;  // K and V of one head
   const int64_t fit = (heads <= 8 && per_head * heads <= kOrderedWholeBytes ? kOrderedWholeBytes : kOrderedTailBytes) / per_head;
   const int32_t most = heads < 8 ? heads : 8;
-  w.ordered = !w.order ? 0 : (fit < most ? (int32_t)fit : most);
+  w.ordered = !w.order ? 0 : (int64_t)heads * m->n_blocks <= kOneRound ? heads : (fit < most ? (int32_t)fit : most);
   w.sliced = heads - w.ordered;
   w.n_blocks = m->n_blocks;
   return w;

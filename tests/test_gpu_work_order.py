@@ -63,3 +63,24 @@ def test_order_covers_all_blocks_of_caller_lists():
             ref = p @ v[0, h, keys].double()
             assert ((out[0, h, rs].double() - ref).abs() <= 1e-2 + 1e-2 * ref.abs()).all(), r
     m.free()
+
+
+@pytest.mark.parametrize("block, H, N", [(128, 20, 12 * 128), (64, 20, 12 * 64 - 5), (64, 85, 3 * 64)])
+def test_small_launches_of_many_heads_start_no_idle_workgroups(block, H, N):
+    """Up to 256 (head, block) items the records of the traced forward are those of the first `items` workgroups."""
+    import torch
+    from paper_2506_19852_amd import binding as rb
+    D, nb = 128, -(-N // block)
+    g = torch.Generator(device="cuda").manual_seed(5)
+    q, k, v = (torch.randn((1, H, N, D), device="cuda", generator=g).bfloat16() for _ in range(3))
+    m = rb.radial_mask_build_dense(N, block)
+    out = torch.full_like(q, float("nan"))
+    lse = torch.empty((1, H, N), dtype=torch.float32, device="cuda")
+    trace = torch.zeros((rb.radial_attn_fwd_trace_records(1, H, m), 3), dtype=torch.int64, device="cuda")
+    rb.radial_attn_fwd_trace(q, k, v, out, lse, m, D ** -0.5, trace)
+    used = torch.nonzero(trace[:, 1]).flatten()
+    assert used.numel() == H * nb and int(used.max()) == H * nb - 1
+    for h in (0, H // 2, H - 1):
+        ref = torch.softmax(q[0, h].double() @ k[0, h].double().T * D ** -0.5, dim=1) @ v[0, h].double()
+        assert (out[0, h].double() - ref).norm() <= 8e-3 * ref.norm(), h   # P and out rounded to bf16
+    m.free()
