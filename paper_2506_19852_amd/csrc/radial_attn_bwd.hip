@@ -718,13 +718,6 @@ int launch_dq(BwdArgs a, hipStream_t stream) {
   return RADIAL_OK;
 }
 
-// How many groups of waves share a list: as in the forward, more while the launch is too small to fill the
-// chip.  The dK/dV kernel holds one wave per SIMD, so a group of 4 waves already fills a compute unit: it
-// takes half blocks of 64 keys (block 128) or 64-token blocks in two groups.  Forward and backward
-// together, S = 1 / chosen, microseconds: block 128, D 128: 84 items 208 / 122, 235 items 445 / 413;
-// block 64: 168 items D 64 148 / 79, D 128 229 / 118; 1128 items D 64 670 / 590.  dK/dV alone in two groups:
-// 1128 items -15, 1400 items +30 (D 64, block 64); dQ alone: 1400 items -51, 2820 items +6; block 128, 564
-// items D 64: +20.
 template <int D, int BLK, bool kExact>
 int launch(const BwdArgs& a, hipStream_t stream) {
   const int64_t rows = (int64_t)a.B * a.H * a.N;
@@ -734,19 +727,11 @@ int launch(const BwdArgs& a, hipStream_t stream) {
     return fail(RADIAL_ESHAPE, "problem too large for one launch");
   bwd_prepare_kernel<D><<<dim3((unsigned)prep_grid), dim3(256), 0, stream>>>(a);
   const int64_t items = work_items(a.work, a.n_blocks);
-  int rc = RADIAL_OK;
-  if constexpr (BLK == 128) {
-    const bool halves = items <= 128;
-    rc = halves ? launch_dkdv<D, BLK, kExact, 2, 2>(a, stream) : launch_dkdv<D, BLK, kExact, 1, 1>(a, stream);
-    if (rc) return rc;
-    rc = halves ? launch_dq<D, BLK, kExact, 4, 2>(a, stream)
-                : items <= 256 ? launch_dq<D, BLK, kExact, 2, 1>(a, stream) : launch_dq<D, BLK, kExact, 1, 1>(a, stream);
-  } else {
-    rc = items <= 1200 ? launch_dkdv<D, BLK, kExact, 2, 1>(a, stream) : launch_dkdv<D, BLK, kExact, 1, 1>(a, stream);
-    if (rc) return rc;
-    rc = items <= 256 ? launch_dq<D, BLK, kExact, 4, 1>(a, stream)
-                      : items <= 1536 ? launch_dq<D, BLK, kExact, 2, 1>(a, stream) : launch_dq<D, BLK, kExact, 1, 1>(a, stream);
-  }
+  const int kv = key_groups(BLK, a.work_t, items), q = query_groups(D, BLK, a.work, items, false);
+  int rc = kv == 2 ? launch_dkdv<D, BLK, kExact, 2, BLK / 64>(a, stream) : launch_dkdv<D, BLK, kExact, 1, 1>(a, stream);
+  if (rc) return rc;
+  rc = q == 4 ? launch_dq<D, BLK, kExact, 4, BLK / 64>(a, stream)
+              : q == 2 ? launch_dq<D, BLK, kExact, 2, 1>(a, stream) : launch_dq<D, BLK, kExact, 1, 1>(a, stream);
   if (rc) return rc;
   RADIAL_HIP_TRY(hipGetLastError());
   return RADIAL_OK;

@@ -414,10 +414,7 @@ int launch_fwd_fp8(const Fp8FwdArgs& a, hipStream_t stream) {
   if (work_grid_bound(a.work) > 0x7fffffffLL) return fail(RADIAL_ESHAPE, "B*H*n_blocks is too large for one launch");
   const int64_t items = work_items(a.work, a.n_blocks);
   if (items == 0) return RADIAL_OK;
-  // Three groups of 4 waves (12 waves: what a compute unit holds of this kernel) while every item can have a
-  // compute unit of its own: quantising and forward, one / three groups, 84 items 79.8 / 59.8 us, 235 items
-  // 153 / 111 us; at 288 items 127 / 133.
-  return items <= 256 ? launch_split<3>(a, stream) : launch_split<1>(a, stream);
+  return fp8_groups(a.work, items) == 3 ? launch_split<3>(a, stream) : launch_split<1>(a, stream);
 }
 
 }  // namespace radial

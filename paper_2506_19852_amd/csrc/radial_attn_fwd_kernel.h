@@ -444,32 +444,15 @@ int launch_split(FwdArgs a, hipStream_t stream) {
   return RADIAL_OK;
 }
 
-// How many groups of waves share a list, by the number of (head, block) items.  A workgroup walks its list
-// stage by stage, so while there are fewer items than the 256 compute units can hold the launch lasts as
-// long as its longest walk; S groups cut that by S.  Once the chip is full the groups of a workgroup only
-// wait for each other at the same barriers.  Measured S = 1 / chosen, microseconds:
-//   block 128: up to 128 items half blocks with S = 4 (84 items: D 128 51.0 / 32.4, D 64 37.9 / 20.1), up to
-//              256 S = 2 (235 items, D 128: 110 / 96); at 288 items S = 2 loses (D 128: 101 / 111).
-//   block 64:  up to 256 items S = 4 (168 items: D 64 37.8 / 19.3, D 128 67.2 / 31.1); above, S = 2 while it
-//              pays: D 128 up to 1536 items (1400: 488 / 438; 1880: 359 / 373), D 64 always (20 480 items:
-//              8.82 / 8.14 ms; 15 800 longer ones: 16.3 / 13.1 ms): two workgroups of 4 waves per compute unit
-//              walk fewer lists at once than five of 2 waves.
 template <int D, int BLK, bool kExact, bool kTrace>
 int launch(const FwdArgs& a, hipStream_t stream) {
   if (work_grid_bound(a.work) > 0x7fffffffLL) return fail(RADIAL_ESHAPE, "B*H*n_blocks is too large for one launch");
   const int64_t items = work_items(a.work, a.n_blocks);
   if (items == 0) return RADIAL_OK;
-  if constexpr (BLK == 128) {
-    if (items <= 128) return launch_split<D, BLK, kExact, kTrace, 4, 2>(a, stream);
-    if (items <= 256) return launch_split<D, BLK, kExact, kTrace, 2, 1>(a, stream);
-    return launch_split<D, BLK, kExact, kTrace, 1, 1>(a, stream);
-  } else {
-    if (items <= 256) return launch_split<D, BLK, kExact, kTrace, 4, 1>(a, stream);
-    if constexpr (D == 128) {
-      if (items > 1536) return launch_split<D, BLK, kExact, kTrace, 1, 1>(a, stream);
-    }
-    return launch_split<D, BLK, kExact, kTrace, 2, 1>(a, stream);
-  }
+  const int groups = query_groups(D, BLK, a.work, items, true);
+  if (groups == 4) return launch_split<D, BLK, kExact, kTrace, 4, BLK / 64>(a, stream);
+  if (groups == 2) return launch_split<D, BLK, kExact, kTrace, 2, 1>(a, stream);
+  return launch_split<D, BLK, kExact, kTrace, 1, 1>(a, stream);
 }
 
 // Launches the kernel instance for (D, block, token rule); kTrace selects the diagnostics build.

@@ -35,6 +35,7 @@ struct radial_mask {
   int32_t* d_order_t = nullptr;  // [n_blocks]
   int32_t max_slice = 0;         // longest slice, in blocks (host copy, sizes the grid)
   int32_t max_slice_t = 0;
+  int32_t longest = 0, longest_t = 0;  // entries of the longest list (n_blocks, a bound, where there is no order)
   int32_t tokens_per_frame = 0;  // geometry of a radial mask (0 for dense / caller-supplied lists)
   int32_t sink_frames = 0;
   int32_t width_num = 1, width_den = 1;  // sparsity knob of a radial mask
@@ -107,6 +108,7 @@ struct WorkMap {
   int32_t max_slice;
   int32_t sliced, ordered;  // heads; sum B * H
   int32_t n_blocks;
+  int32_t longest, mean;    // entries of the longest and of an average list
 };
 
 constexpr int32_t kMaxOrdered = 16384;  // blocks up to which a mask carries the order
@@ -138,6 +140,8 @@ inline WorkMap make_work_map(const radial_mask* m, bool transposed, int32_t head
   w.ordered = !w.order ? 0 : (int64_t)heads * m->n_blocks <= kOneRound ? heads : (fit < most ? (int32_t)fit : most);
   w.sliced = heads - w.ordered;
   w.n_blocks = m->n_blocks;
+  w.longest = transposed ? m->longest_t : m->longest;
+  w.mean = (int32_t)(m->nnz / m->n_blocks);
   return w;
 }
 // (head, block) pairs of a launch, its workgroups, and the most workgroups that any division of the heads could start.
@@ -146,6 +150,64 @@ inline int64_t work_items(const WorkMap& w, int32_t n_blocks) { return (int64_t)
 inline int64_t work_grid(const WorkMap& w, int32_t n_blocks) {
   return 8LL * w.sliced * w.max_slice + (int64_t)w.ordered * n_blocks;
 }
+
+// ---- How many groups of waves share a list ------------------------------------------------------
+// A workgroup walks its list stage by stage, so a launch that runs in one round lasts as long as its longest
+// walk, and S groups cut that by S.  They cost a merge (1 to 4 us) and, once the chip is full, wait for each
+// other at the same barriers.  All figures are kernel times in microseconds, one group / the form named,
+// on lists of equal length L unless said otherwise.
+// `groups` = 4 at block 128 and 2 in the dK/dV kernel at block 128 mean half blocks: two workgroups per block, of 64 rows each.
+
+// Two groups for 64-token blocks above kOneRound items: four workgroups of one group fit a compute unit, or two of two, so that
+// two groups take ceil(items / 512) / 2 walks where one takes ceil(items / 1024).
+//   up to 512 items:  a round either way.  Forward, D 128, 300 items: L 8 22.2 / 17.0, L 48 91.9 / 58.9; dQ -5, -48.
+//   up to 1024:  one round or two of half the length, which pays only for what long lists leave over.  Forward, D 128,
+//     600 items: L 16 40.5 / 44.8, L 48 97.8 / 107.1; radial lists (mean 86, longest 106, 742 items) 176.7 / 173.6, with
+//     text rows (188, 299; 897 items) 492 / 413.  D 64, mean 86, longest 106: 112 / 97; mean 61, longest 66: 81.4 / 81.8.
+//   up to 1536:  two rounds or three of half the length.  Forward, D 128, 1200 items: L 8 46.1 / 44.6, L 12 62.0 / 56.7,
+//     L 48 195 / 172; dQ, L 8 0, L 12 -4, L 48 -36.  L 4, forward: 30.3 / 32.2.
+//   above:  D 128 loses (1800 items, L 48 224 / 233; 1880 items on radial lists 359 / 373).
+inline bool two_groups_pay_64(const WorkMap& w, int64_t items) {
+  if (items <= 512) return w.longest >= 4;
+  if (items <= 1024) return w.mean >= 16 && 8LL * w.longest > 9LL * w.mean;
+  return items <= 1536 && w.mean >= 12;
+}
+
+// Block 128, up to 256 items.  Forward, D 128: half blocks at 64 items L 2 10.5 / 11.0, L 3 12.6 / 12.2, L 16 41.3 / 25.8, at
+// 256 items L 16 48.0 / 54.0; two groups at 256 items L 3 15.0 / 15.9, L 4 17.4 / 17.4, L 16 48.0 / 41.6, at 288 items
+// (longer lists) 101 / 111.  dQ at 64 items: L 2 -0.6, L 3 -2.3, L 16 -28; 564 items, D 64: +20.
+// Block 64, up to 256 items.  Forward, D 128, one / two / four groups: L 3 9.6 / 9.5 / 10.6, L 4 11.1 / 9.4 / 10.7,
+// L 8 17.2 / 12.5 / 13.0, L 12 23.1 / 15.8 / 15.6, L 32 52.1 / 31.0 / 27.9; dQ alike (L 32 0 / -26 / -29).
+// D 64, block 64, above 1536 items: two workgroups of 4 waves per compute unit walk fewer lists at once than five of 2 waves,
+// which pays on long lists: 19 200 items L 16 499 / 526, L 32 912 / 918, L 64 1722 / 1690, L 100 2637 / 2557; 4000 items L 12
+// 87.8 / 87.2, L 48 290 / 279; on radial lists (15 800 items) 16.3 / 13.1 ms.
+inline int query_groups(int D, int block, const WorkMap& w, int64_t items, bool forward) {
+  if (block == 128) {
+    if (items <= 128) return w.longest >= (forward ? 3 : 2) ? 4 : 1;
+    return items <= kOneRound && w.longest >= 4 ? 2 : 1;
+  }
+  if (items <= kOneRound && w.longest >= 12) return 4;
+  if (two_groups_pay_64(w, items)) return 2;
+  return forward && D == 64 && items > 1536 && w.mean >= 32 ? 2 : 1;
+}
+
+// dK/dV holds one wave per SIMD: a compute unit takes one workgroup of 128 keys, one of two groups of 64, or two of
+// one group of 64, so that at block 64 two groups take ceil(items / 256) / 2 walks where one takes ceil(items / 512).
+//   block 128, half blocks, 64 items: L 1 0, L 2 -3, L 16 -27; 256 items, L 32: +13.
+//   block 64, D 128: 256 items L 2 +1, L 3 0, L 8 -7, L 32 -22; 300 items L 8 +2, L 16 -6, L 48 -40; 500 items L 48 +7;
+//   600 items L 8 +2, L 16 -1, L 48 -34; 700 items L 16 +9, L 48 -33; 1000 items L 48 +18; 1200 items L 16 +23, L 48 -25,
+//   radial lists (mean 51, 1140 items) -9; 1300 items, L 48: +5.
+inline int key_groups(int block, const WorkMap& w, int64_t items) {
+  if (block == 128) return items <= 128 && w.longest >= 2 ? 2 : 1;
+  if (items <= kOneRound) return w.longest >= 3 ? 2 : 1;
+  if (items <= 384) return w.longest >= 16 ? 2 : 1;
+  return items <= 1200 && (items - 1) / 256 % 2 == 0 && w.mean >= 32 ? 2 : 1;
+}
+
+// 8-bit scores: three groups of 4 waves (12 waves are what a compute unit holds of this kernel) while every item can
+// have a compute unit of its own.  64 items: L 4 16.9 / 17.7, L 6 22.3 / 19.8; 256 items: L 6 24.0 / 22.7, L 32 93.5 / 69.0;
+// 288 items (with the quantisation) 127 / 133.
+inline int fp8_groups(const WorkMap& w, int64_t items) { return items <= kOneRound && w.longest >= 6 ? 3 : 1; }
 
 struct TensorArg {
   const void* ptr;

@@ -257,10 +257,10 @@ __device__ inline long long slice_target(long long total, int32_t nb, int k) {
 }
 
 // What workgroup r needs to know of all lists to write its own: where it starts.  On the way it writes
-// ptr[r], the launch partitions and the totals, so that neither a scan nor a partition pass is needed: every
+// ptr[r], the launch partitions, the longest list and the totals, so that neither a scan nor a partition pass is needed: every
 // workgroup reads all counts (nb / 256 rounds), which up to kMaxOrdered blocks costs less than the launches.
 __device__ int32_t place_list(const int32_t* counts, int32_t nb, int32_t r, int32_t* ptr, int32_t* slice, int32_t* order,
-                              long long* total64) {
+                              int32_t* longest, long long* total64) {
   const int32_t len = counts[r];
   long long before = 0, total = 0;
   int32_t ahead = 0;
@@ -274,6 +274,7 @@ __device__ int32_t place_list(const int32_t* counts, int32_t nb, int32_t r, int3
   if (threadIdx.x == 0) {
     ptr[r] = (int32_t)before;
     order[ahead] = r;
+    if (ahead == 0) *longest = len;
     if (r == nb - 1) {
       ptr[nb] = (int32_t)total;
       *total64 = total;
@@ -294,10 +295,11 @@ __device__ int32_t place_list(const int32_t* counts, int32_t nb, int32_t r, int3
 }
 
 __global__ void __launch_bounds__(kThreads) mask_lists_kernel(MaskGeom g, int32_t nwords, const int32_t* counts, int32_t* row_ptr,
-                                                             int32_t* slice, int32_t* order, long long* total64, int32_t* col_idx) {
+                                                             int32_t* slice, int32_t* order, int32_t* longest, long long* total64,
+                                                             int32_t* col_idx) {
   extern __shared__ uint32_t words[];
   row_bitmap(g, blockIdx.x, words, nwords);
-  const int32_t start = place_list(counts, g.nb, blockIdx.x, row_ptr, slice, order, total64);
+  const int32_t start = place_list(counts, g.nb, blockIdx.x, row_ptr, slice, order, longest, total64);
   write_row(words, nwords, col_idx + start);
 }
 
@@ -331,14 +333,15 @@ __global__ void __launch_bounds__(kThreads) transpose_fill_kernel(const int32_t*
 
 __global__ void __launch_bounds__(kThreads) transpose_lists_kernel(const int32_t* row_ptr, const int32_t* col_idx, int32_t nb,
                                                                   const int32_t* counts, int32_t* col_ptr, int32_t* slice,
-                                                                  int32_t* order, long long* total64, int32_t* row_idx) {
-  const int32_t start = place_list(counts, nb, blockIdx.x, col_ptr, slice, order, total64);
+                                                                  int32_t* order, int32_t* longest, long long* total64, int32_t* row_idx) {
+  const int32_t start = place_list(counts, nb, blockIdx.x, col_ptr, slice, order, longest, total64);
   write_column(row_ptr, col_idx, nb, blockIdx.x, start, row_idx);
 }
 
 // Workgroup 0 cuts the slices; the others, a wave per block, place the block at its rank by falling
-// list length (equal lengths: by index) if there is an order to fill.
-__global__ void __launch_bounds__(kThreads) partition_kernel(const int32_t* ptr, int32_t nb, int32_t* slice, int32_t* order) {
+// list length (equal lengths: by index) if there is an order to fill, and the first writes its length.
+__global__ void __launch_bounds__(kThreads) partition_kernel(const int32_t* ptr, int32_t nb, int32_t* slice, int32_t* order,
+                                                            int32_t* longest) {
   if (blockIdx.x > 0) {
     const int32_t b = (blockIdx.x - 1) * (kThreads / 64) + (threadIdx.x >> 6);
     if (b >= nb) return;
@@ -349,7 +352,10 @@ __global__ void __launch_bounds__(kThreads) partition_kernel(const int32_t* ptr,
       ahead += (other > len || (other == len && j < b)) ? 1 : 0;
     }
     for (int off = 32; off > 0; off >>= 1) ahead += __shfl_xor(ahead, off);
-    if ((threadIdx.x & 63) == 0) order[ahead] = b;
+    if ((threadIdx.x & 63) == 0) {
+      order[ahead] = b;
+      if (ahead == 0) *longest = len;
+    }
     return;
   }
   const int k = threadIdx.x;
@@ -376,10 +382,11 @@ int check_common(int64_t n_tokens, int32_t block, uint32_t flags) {
 // Device storage of a mask is three allocations: `meta` (two 64-bit totals and the two launch
 // partitions), `ptrs` (row_ptr and its order and, with the transposed lists, col_ptr and its order) and `idx` (col_idx and
 // row_idx).  The views d_row_ptr, d_col_ptr, ... point into them at 256-byte aligned offsets.
-constexpr int kMetaInts = 32;  // [0..1] total of rows, [2..3] total of columns, [8..16] slice, [20..28] slice_t
-void launch_partition(const int32_t* ptr, int32_t nb, int32_t* slice, int32_t* order, hipStream_t st) {
+// [0..1] total of rows, [2..3] total of columns, [4] longest row, [5] longest column, [8..16] slice, [20..28] slice_t
+constexpr int kMetaInts = 32, kLongest = 4, kLongestT = 5;
+void launch_partition(const int32_t* ptr, int32_t nb, int32_t* slice, int32_t* order, int32_t* longest, hipStream_t st) {
   const int32_t per = kThreads / 64;
-  partition_kernel<<<1 + (order ? (nb + per - 1) / per : 0), kThreads, 0, st>>>(ptr, nb, slice, order);
+  partition_kernel<<<1 + (order ? (nb + per - 1) / per : 0), kThreads, 0, st>>>(ptr, nb, slice, order, longest);
 }
 
 inline int64_t aligned_ints(int64_t n) { return (n + 63) & ~(int64_t)63; }
@@ -417,22 +424,24 @@ int alloc_idx(radial_mask* m) {
 int finish_mask(radial_mask* m, bool rows_placed, hipStream_t st) {
   const int32_t nb = m->n_blocks;
   alignas(8) int32_t h_meta[kMetaInts];
-  if (!rows_placed) launch_partition(m->d_row_ptr, nb, m->d_slice, m->d_order, st);
+  if (!rows_placed) launch_partition(m->d_row_ptr, nb, m->d_slice, m->d_order, m->d_meta + kLongest, st);
   if ((m->flags & RADIAL_MASK_TRANSPOSE) && m->d_counts) {
     transpose_count_kernel<<<nb, kThreads, 0, st>>>(m->d_row_ptr, m->d_col_idx, nb, m->d_counts);
     transpose_lists_kernel<<<nb, kThreads, 0, st>>>(m->d_row_ptr, m->d_col_idx, nb, m->d_counts, m->d_col_ptr, m->d_slice_t, m->d_order_t,
-                                                    (long long*)(m->d_meta + 2), m->d_row_idx);
+                                                    m->d_meta + kLongestT, (long long*)(m->d_meta + 2), m->d_row_idx);
   } else if (m->flags & RADIAL_MASK_TRANSPOSE) {
     transpose_count_kernel<<<nb, kThreads, 0, st>>>(m->d_row_ptr, m->d_col_idx, nb, m->d_col_ptr);
     scan_kernel<<<1, kThreads, 0, st>>>(m->d_col_ptr, nb, (long long*)(m->d_meta + 2));
     transpose_fill_kernel<<<nb, kThreads, 0, st>>>(m->d_row_ptr, m->d_col_idx, nb, m->d_col_ptr, m->d_row_idx);
-    launch_partition(m->d_col_ptr, nb, m->d_slice_t, m->d_order_t, st);
+    launch_partition(m->d_col_ptr, nb, m->d_slice_t, m->d_order_t, m->d_meta + kLongestT, st);
   }
   hipError_t e = hipGetLastError();
   if (e == hipSuccess) e = hipMemcpyAsync(h_meta, m->d_meta, sizeof h_meta, hipMemcpyDeviceToHost, st);
   if (e == hipSuccess) e = hipStreamSynchronize(st);
   if (e != hipSuccess) return fail(RADIAL_EHIP, "mask kernels failed: %s", hipGetErrorString(e));
   if (rows_placed) m->nnz = *(const long long*)h_meta;
+  m->longest = m->d_order ? h_meta[kLongest] : nb;
+  if (m->flags & RADIAL_MASK_TRANSPOSE) m->longest_t = m->d_order_t ? h_meta[kLongestT] : nb;
   for (int k = 0; k < 8; ++k) {
     const int32_t len = h_meta[8 + k + 1] - h_meta[8 + k];
     m->max_slice = len > m->max_slice ? len : m->max_slice;
@@ -503,7 +512,7 @@ static int build_radial(radial_mask* m, const radial_mask_params* p, hipStream_t
     }
     if (int rc = alloc_idx(m)) return rc;
     mask_lists_kernel<<<nb, kThreads, nwords * sizeof(uint32_t), st>>>(g, nwords, m->d_counts, m->d_row_ptr, m->d_slice, m->d_order,
-                                                                       (long long*)m->d_meta, m->d_col_idx);
+                                                                       m->d_meta + kLongest, (long long*)m->d_meta, m->d_col_idx);
     RADIAL_HIP_TRY(hipGetLastError());
     return finish_mask(m, true, st);
   }

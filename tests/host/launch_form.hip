@@ -1,0 +1,30 @@
+// The launch rules (radial_internal.h) on the host: for each input line
+//   head_dim block heads n_blocks nnz longest longest_t
+// one line "forward dq dkdv fp8 ordered": groups of waves per list in each kernel, and the heads that go by list length.
+#include <stdio.h>
+
+#include "radial_internal.h"
+
+using namespace radial;
+
+int main() {
+  int D, block, heads, nb, longest, longest_t;
+  long long nnz;
+  int32_t order = 0;  // only looked at for being there
+  while (scanf("%d %d %d %d %lld %d %d", &D, &block, &heads, &nb, &nnz, &longest, &longest_t) == 7) {
+    radial_mask m;
+    m.block = block;
+    m.n_blocks = nb;
+    m.n_tokens = nb * block;
+    m.nnz = nnz;
+    m.longest = longest;
+    m.longest_t = longest_t;
+    m.max_slice = m.max_slice_t = (nb + 7) / 8;
+    if (nb <= kMaxOrdered) m.d_order = m.d_order_t = &order;
+    const WorkMap w = make_work_map(&m, false, heads, D), wt = make_work_map(&m, true, heads, D);
+    const int64_t items = work_items(w, nb);
+    printf("%d %d %d %d %d\n", query_groups(D, block, w, items, true), query_groups(D, block, w, items, false), key_groups(block, wt, items),
+           fp8_groups(w, items), w.ordered);
+  }
+  return 0;
+}

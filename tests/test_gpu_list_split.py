@@ -73,6 +73,40 @@ def test_forward_and_backward_match_float64(D, block, H, N, rule):
     m.free()
 
 
+# Lists of at most two entries are walked by one group whatever the size of the launch.
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("block, H, N", [(128, 2, 777), (128, 20, 11 * 128 + 1), (128, 9, 29 * 128 - 90), (64, 3, 333), (64, 24, 50 * 64 + 3), (64, 28, 80 * 64 - 5)])
+def test_short_lists_match_float64(D, block, H, N):
+    import torch
+    from paper_2506_19852_amd import binding as rb
+    nb = -(-N // block)
+    g = torch.Generator(device="cuda").manual_seed(N)
+    q, k, v, do = (torch.randn((1, H, N, D), device="cuda", generator=g).bfloat16() for _ in range(4))
+    rng = np.random.default_rng(N)
+    rows = [np.sort(rng.choice(nb, size=r % 3, replace=False)) for r in range(nb)]
+    row_ptr = np.concatenate([[0], np.cumsum([len(r) for r in rows])]).astype(np.int32)
+    m = rb.radial_mask_from_csr(N, block, row_ptr, np.concatenate(rows).astype(np.int32), rb.RADIAL_MASK_TRANSPOSE)
+    bm = torch.zeros((nb, nb), dtype=torch.bool)
+    for r, c in enumerate(rows):
+        bm[r, c.astype(np.int64)] = True
+    vis = bm.cuda().repeat_interleave(block, 0).repeat_interleave(block, 1)[:N, :N]
+    out, dq, dk, dv = (torch.full_like(q, float("nan")) for _ in range(4))
+    lse = torch.full((1, H, N), float("nan"), dtype=torch.float32, device="cuda")
+    ws = torch.empty(rb.radial_attn_bwd_workspace(1, H, N, D, m), dtype=torch.uint8, device="cuda")
+    rb.radial_attn_fwd(q, k, v, out, lse, m, D ** -0.5)
+    rb.radial_attn_bwd(q, k, v, out, do, lse, dq, dk, dv, m, D ** -0.5, ws)
+    some = vis.any(1)
+    for h in (0, H - 1):
+        ref = reference(q[0, h], k[0, h], v[0, h], do[0, h], vis, D ** -0.5)
+        assert (lse[0, h][~some] == float("-inf")).all() and (out[0, h][~some] == 0).all()
+        # bounds as above
+        assert (lse[0, h][some].double() - ref[1][some]).abs().max() <= 1e-4
+        for name, x, r in zip(("out", "dq", "dk", "dv"), (out[0, h], dq[0, h], dk[0, h], dv[0, h]), (ref[0], *ref[2:])):
+            assert torch.isfinite(x).all(), (name, h)
+            assert (x.double() - r).norm() <= 8e-3 * r.norm() + 1e-6, (name, h, (x.double() - r).norm() / r.norm())
+    m.free()
+
+
 # Frames whose boundaries fall anywhere in a block; heads so that 8 blocks of 128 (16 of 64) take each form: half
 # blocks, two groups, one; four groups, two, and from 1600 items one in every kernel that has that form.
 @pytest.mark.parametrize("D", [64, 128])

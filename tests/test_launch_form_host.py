@@ -1,0 +1,68 @@
+"""The rules that choose a launch's form, evaluated on the host as the library compiles them: lists too short to
+share are not split, whatever the number of items, and the forms change where the rules' comments say."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+from paper_2506_19852_amd import build as hip_build
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+SOURCE = os.path.join(ROOT, "tests", "host", "launch_form.hip")
+
+
+@pytest.fixture(scope="module")
+def forms(tmp_path_factory):
+    if not os.path.exists(hip_build.HIPCC) and shutil.which(hip_build.HIPCC) is None:
+        pytest.skip("hipcc not available")
+    exe = tmp_path_factory.mktemp("host") / "launch_form"
+    r = subprocess.run([hip_build.HIPCC, *hip_build.FLAGS, "--cuda-host-only", SOURCE, "-o", str(exe)],
+                       stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    assert r.returncode == 0, r.stdout[-3000:]
+
+    def run(cases):
+        """(D, block, heads, n_blocks, entries per list or (total, longest)) -> (forward, dq, dkdv, fp8, ordered heads)"""
+        lines = []
+        for D, block, heads, nb, per in cases:
+            nnz, longest = (nb * per, per) if isinstance(per, int) else per
+            lines.append(f"{D} {block} {heads} {nb} {nnz} {longest} {longest}")
+        r = subprocess.run([str(exe)], input="\n".join(lines), stdout=subprocess.PIPE, text=True, timeout=60)
+        assert r.returncode == 0
+        out = [tuple(map(int, line.split())) for line in r.stdout.split("\n") if line]
+        assert len(out) == len(cases)
+        return out
+    return run
+
+
+def test_short_lists_are_not_split(forms):
+    cases = [(D, block, heads, nb, per) for D in (64, 128) for block in (64, 128) for per in (0, 1)
+             for heads, nb in ((1, 1), (4, 16), (8, 32), (20, 12), (5, 60), (16, 60), (24, 50), (24, 200), (24, 800))]
+    for case, form in zip(cases, forms(cases)):
+        assert form[:4] == (1, 1, 1, 1), case
+    # two entries pay for half blocks in the backward only; three entries for nothing above one round
+    assert [f[:4] for f in forms([(128, 128, 4, 16, 2), (128, 128, 4, 16, 3), (128, 128, 8, 32, 3), (64, 64, 16, 60, 3), (64, 64, 24, 200, 6)])] == [
+        (1, 4, 2, 1), (4, 4, 2, 1), (1, 1, 1, 1), (1, 1, 1, 1), (1, 1, 1, 1)]
+
+
+def test_forms_change_at_the_measured_sizes(forms):
+    wide = lambda nb: (60 * nb, 120)   # lists of very unequal length
+    assert [f[:3] for f in forms([
+        # block 128: half blocks to 128 items, two groups to 256
+        (128, 128, 8, 16, 16), (128, 128, 3, 43, 16), (128, 128, 8, 32, 16), (128, 128, 1, 257, 16),
+        # block 64: four groups to 256 items, two to 512
+        (128, 64, 8, 32, 16), (128, 64, 8, 32, 11), (128, 64, 1, 257, 16), (128, 64, 8, 64, 48),
+        # to 1024 items: equal lists alone, unequal ones in two groups (dK/dV: 513 to 768 items)
+        (128, 64, 12, 50, 48), (64, 64, 12, 50, wide(50)), (128, 64, 9, 100, wide(100)),
+        # to 1536: two groups (dK/dV: to 1200); above: D 64 forward, long lists only
+        (128, 64, 11, 100, 48), (128, 64, 15, 100, 48), (128, 64, 16, 100, 48), (64, 64, 40, 100, 48), (64, 64, 40, 100, 24)])] == [
+        (4, 4, 2), (2, 2, 1), (2, 2, 1), (1, 1, 1),
+        (4, 4, 2), (2, 2, 2), (2, 2, 2), (2, 2, 1),
+        (1, 1, 2), (2, 2, 2), (2, 2, 1),
+        (2, 2, 2), (2, 2, 1), (1, 1, 1), (2, 1, 1), (1, 1, 1)]
+
+
+def test_heads_by_list_length(forms):
+    """All heads up to one round of workgroups (256 items) and up to 8 heads; else the last ones that fit the cache."""
+    assert [f[4] for f in forms([(128, 128, 20, 12, 4), (64, 64, 256, 1, 1), (128, 128, 257, 1, 1), (128, 128, 8, 300, 50), (128, 128, 9, 300, 50),
+                                 (128, 128, 24, 929, 100), (128, 128, 1, 16385, 100)])] == [20, 256, 8, 8, 8, 2, 0]
