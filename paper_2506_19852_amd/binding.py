@@ -102,10 +102,25 @@ def _check(rc: int):
         raise RadialError(rc, radial_last_error())
 
 
+_current_stream = None
+
+
+def _find_current_stream():
+    """A function that gives the current stream of the current device as an integer: without a Stream object
+    around it where this torch build can say it so."""
+    import torch
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None:
+        return lambda: torch.cuda.current_stream().cuda_stream
+    return lambda: raw(torch.cuda.current_device())
+
+
 def _stream_ptr(stream):
-    if stream is None:  # the current stream of the current device, without a Stream object around it
-        import torch
-        return c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
+    if stream is None:
+        global _current_stream
+        if _current_stream is None:
+            _current_stream = _find_current_stream()
+        return c_void_p(_current_stream())
     return c_void_p(int(getattr(stream, "cuda_stream", stream)))
 
 
