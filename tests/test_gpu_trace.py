@@ -40,6 +40,15 @@ def test_traced_forward_matches_the_plain_call_and_fills_one_record_per_workgrou
     m.free()
 
 
+def test_number_of_records_does_not_wrap():
+    m = rb.radial_mask_build(6, 200, 128, 1, 0)
+    one = rb.radial_attn_fwd_trace_records(1, 1, m)
+    assert one > 0
+    assert rb.radial_attn_fwd_trace_records(1 << 16, 1 << 16, m) == one << 32
+    assert rb.radial_attn_fwd_trace_records(2, (1 << 31) - 1, m) == one * 2 * ((1 << 31) - 1)
+    m.free()
+
+
 def test_mfma_probe_runs_and_counts_its_operations():
     flops = rb.radial_probe_mfma_bf16(100)
     torch.cuda.synchronize()
