@@ -85,7 +85,9 @@ typedef struct {
 #define RADIAL_MASK_TOKEN_EXACT 2u
 
 /* Opaque.  Owns device copies of row_ptr[nqb+1], col_idx[nnz] (and the transposed lists when
- * requested) plus a launch order for the attention kernels.  Immutable after construction;
+ * requested) plus a launch order for the attention kernels.  Masks that radial_mask_build and
+ * radial_mask_build_banded make of up to 720 blocks keep room for every block pair (at most 2 MiB per
+ * list), whatever they list.  Immutable after construction;
  * may be shared by any number of attention calls and streams on the device it was built on.
  * The mask does not depend on B, H or D. */
 typedef struct radial_mask radial_mask;

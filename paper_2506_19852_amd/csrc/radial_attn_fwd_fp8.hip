@@ -328,7 +328,7 @@ __global__ void __launch_bounds__(64 * kWaves * S, 3) radial_fwd_fp8_kernel(cons
   }
 
   // ---- merge of the groups: group 0 gathers (m, l, O) of the others through LDS ---------------
-  // (float32 throughout; at most 3 x 34 KiB per workgroup, about a microsecond)
+  // (float32 throughout; 132 KiB per workgroup, two groups of four waves)
   if (S > 1) {
     // a stage is a barrier: as many as group 0, which has most stages
     for (int32_t u = n_stage; u < (n_row + S - 1) / S * kSubs; ++u) __syncthreads();

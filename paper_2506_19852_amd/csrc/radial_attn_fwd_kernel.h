@@ -359,7 +359,7 @@ __global__ void __launch_bounds__(2 * BLK / R * S, 2) radial_fwd_kernel(const Fw
   }
 
   // ---- merge of the groups: group 0 gathers (m, l, O) of the others through LDS ---------------
-  // (float32 throughout; at most 3 x 34 KiB per workgroup, about a microsecond)
+  // (float32 throughout; at most 99 KiB per workgroup, three groups of two waves, in about a microsecond)
   if (S > 1) {
     // a stage is a barrier: as many as group 0, which has most stages
     for (int32_t u = n_stage; u < (n_row + S - 1) / S * T::kSubs; ++u) __syncthreads();

@@ -36,9 +36,10 @@ namespace {
 
 constexpr int kThreads = 256;
 // Blocks up to which a radial mask's lists get room for every pair, so that nothing has to be known before
-// they are written (2 MiB per list; hipMalloc becomes slow above that, and counting first is then cheaper).
-// radial_mask_build and free, four kernels and two waits / two kernels and one wait: 110 blocks 61 / 36 us,
-// with the transposed lists 77 / 46; 929 blocks 65 / 73.
+// they are written (up to 2 MiB per list; hipMalloc becomes slow from there on, and counting first is then cheaper).
+// radial_mask_build and free, four kernels and two waits / two kernels and one wait: 110 blocks 61 / 34 us, 720 blocks
+// 62 / 35; 929 blocks 65 / 73.  With the transposed lists both come from one hipMalloc, of 2 MiB and more from 512 blocks
+// on, which takes most of the gain: 244 blocks 77 / 45, 512 blocks 94 / 90, 720 blocks 149 / 107.
 constexpr int32_t kMaxUncounted = 720;
 static_assert(kMaxUncounted <= kMaxOrdered, "place_list writes the order");
 constexpr int kMaxWords = 15 * 1024;  // 60 KiB of LDS bitmap: up to 491 520 key blocks
