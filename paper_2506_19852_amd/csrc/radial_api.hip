@@ -47,7 +47,7 @@ int radial::make_fwd_args(int32_t B, int32_t H, int32_t N, int32_t D, radial_ten
   a->lse = lse;
   a->row_ptr = mask->d_row_ptr;
   a->col_idx = mask->d_col_idx;
-  a->work = make_work_map(mask, false, B * H, D);
+  a->work = make_work_map(mask, Walk::kForward, B * H, D);
   a->B = B; a->H = H; a->N = N; a->n_blocks = mask->n_blocks;
   a->scale = scale;
   a->rule = make_token_rule(mask);
@@ -86,8 +86,8 @@ static int bwd_call(int32_t B, int32_t H, int32_t N, int32_t D, radial_tensor q,
   a.delta = delta;
   a.row_ptr = mask->d_row_ptr; a.col_idx = mask->d_col_idx;
   a.col_ptr = mask->d_col_ptr; a.row_idx = mask->d_row_idx;
-  a.work = make_work_map(mask, false, B * H, D);
-  a.work_t = make_work_map(mask, true, B * H, D);
+  a.work = make_work_map(mask, Walk::kQueryGrad, B * H, D);
+  a.work_t = make_work_map(mask, Walk::kKeyGrad, B * H, D);
   a.B = B; a.H = H; a.N = N; a.n_blocks = mask->n_blocks;
   a.scale = scale;
   a.rule = make_token_rule(mask);
@@ -191,7 +191,7 @@ extern "C" int radial_attn_fwd_fp8(int32_t B, int32_t H, int32_t N, int32_t D, i
   a.lse = lse;
   a.row_ptr = mask->d_row_ptr;
   a.col_idx = mask->d_col_idx;
-  a.work = make_work_map(mask, false, B * H, D);
+  a.work = make_work_map(mask, Walk::kForward, B * H, D);
   a.B = B; a.H = H; a.N = N; a.n_blocks = mask->n_blocks;
   a.scale = scale;
   return launch_fwd_fp8(a, (hipStream_t)hip_stream);

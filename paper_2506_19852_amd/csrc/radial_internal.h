@@ -128,20 +128,43 @@ constexpr int32_t kMaxOrdered = 16384;  // blocks up to which a mask carries the
 // workgroups for 240 items; forward, D 128, block 128, two groups: lists of 4 29.4 -> 17.4 us, of 12 55.8 -> 33.0).
 constexpr int64_t kOrderedWholeBytes = 256 << 20, kOrderedTailBytes = 160 << 20;
 constexpr int64_t kOneRound = 256;
+// Blocks of 64 tokens move twice the K and V per product, and by length the blocks that an XCD works on at one time
+// are no neighbours: beyond some multiple of its 4 MB L2 the walk over the K and V of its heads is slower than the
+// tail is worth, unless single lists are far longer than the others (text tokens) and half as long as the whole
+// launch.  An XCD sees one head where their number divides 8 (else some XCDs are on two): (heads + 8 - gcd(heads, 8)) / 8
+// on average.
+// By slices / by length, ms, D 128 unless said, MB of K and V per XCD in brackets.  Forward, whole launches: 1 / 4 / 8 heads [16]
+// 0.497 / 0.388, 1.71 / 1.39, 3.13 / 2.89; 7 heads [29] 2.91 / 2.66; 2 / 8 heads [20] 0.966 / 0.897, 3.74 / 3.41; 1 / 4 / 8 heads
+// [27] 0.686 / 0.703, 2.76 / 2.67, 5.37 / 5.30; 5 / 7 heads [31, 36] 2.40 / 2.48, 3.31 / 3.43; 1 / 4 / 8 heads [59]
+// 3.18 / 3.73, 12.6 / 14.0, 26.7 / 28.3; D 64, 8 heads [30] 12.8 / 13.1, 2 heads [66] 10.2 / 12.0.  The last 8 of more heads: 12 and 20
+// heads [16] 4.86 / 4.69, 8.00 / 8.02, 16 heads [20] 7.34 / 7.77.  The dQ kernel: 4 heads [27] -0.25 of 8.5, 4 heads [61] +0.36
+// of 45, 1 head [132] +0.96 of 30.  With text rows (longest / mean): 3 heads of 854 blocks (854 / 301) forward and backward 11.4 / 10.1,
+// 6 heads of 1631 blocks 20.9 / 24.1.  dK/dV, and everything in blocks of 128, gain or tie throughout.
+constexpr int64_t kForwardXcdBytes64 = 28 << 20, kForwardTailBytes64 = 16 << 20, kQueryGradXcdBytes64 = 64 << 20;
+inline int64_t xcd_bytes(int64_t per_head, int32_t heads) {
+  const int32_t gcd = heads & 1 ? 1 : heads & 2 ? 2 : heads & 4 ? 4 : 8;
+  return heads > 8 ? per_head : per_head * (heads + 8 - gcd) / 8;  // above 8 heads the last 8 go by length
+}
 
-inline WorkMap make_work_map(const radial_mask* m, bool transposed, int32_t heads, int32_t D) {
+enum class Walk { kForward, kQueryGrad, kKeyGrad };
+
+inline WorkMap make_work_map(const radial_mask* m, Walk walk, int32_t heads, int32_t D) {
   WorkMap w;
+  const bool transposed = walk == Walk::kKeyGrad;
   w.slice = transposed ? m->d_slice_t : m->d_slice;
   w.order = transposed ? m->d_order_t : m->d_order;
   w.max_slice = transposed ? m->max_slice_t : m->max_slice;
+  w.longest = transposed ? m->longest_t : m->longest;
+  w.mean = (int32_t)(m->nnz / m->n_blocks);
   const int64_t per_head = 4LL * D * m->n_tokens;  // K and V of one head
   const int64_t fit = (heads <= 8 && per_head * heads <= kOrderedWholeBytes ? kOrderedWholeBytes : kOrderedTailBytes) / per_head;
   const int32_t most = heads < 8 ? heads : 8;
-  w.ordered = !w.order ? 0 : (int64_t)heads * m->n_blocks <= kOneRound ? heads : (fit < most ? (int32_t)fit : most);
+  const int64_t most_bytes = walk == Walk::kQueryGrad ? kQueryGradXcdBytes64 : heads > 8 ? kForwardTailBytes64 : kForwardXcdBytes64;
+  const bool long_tail = w.longest >= 2LL * w.mean && 2048LL * w.longest >= (int64_t)w.mean * heads * m->n_blocks;
+  const bool scattered = m->block == 64 && !transposed && xcd_bytes(per_head, heads) > most_bytes && !long_tail;
+  w.ordered = !w.order ? 0 : (int64_t)heads * m->n_blocks <= kOneRound ? heads : scattered ? 0 : (fit < most ? (int32_t)fit : most);
   w.sliced = heads - w.ordered;
   w.n_blocks = m->n_blocks;
-  w.longest = transposed ? m->longest_t : m->longest;
-  w.mean = (int32_t)(m->nnz / m->n_blocks);
   return w;
 }
 // (head, block) pairs of a launch, its workgroups, and the most workgroups that any division of the heads could start.

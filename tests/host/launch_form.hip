@@ -1,6 +1,7 @@
 // The launch rules (radial_internal.h) on the host: for each input line
 //   head_dim block heads n_blocks nnz longest longest_t
-// one line "forward dq dkdv fp8 ordered": groups of waves per list in each kernel, and the heads that go by list length.
+// one line "forward dq dkdv fp8 ordered ordered_q ordered_k": groups of waves per list in each kernel, and the heads that
+// go by list length in the forward, dQ and dK/dV kernels.
 #include <stdio.h>
 
 #include "radial_internal.h"
@@ -21,10 +22,11 @@ int main() {
     m.longest_t = longest_t;
     m.max_slice = m.max_slice_t = (nb + 7) / 8;
     if (nb <= kMaxOrdered) m.d_order = m.d_order_t = &order;
-    const WorkMap w = make_work_map(&m, false, heads, D), wt = make_work_map(&m, true, heads, D);
+    const WorkMap w = make_work_map(&m, Walk::kForward, heads, D), wq = make_work_map(&m, Walk::kQueryGrad, heads, D),
+                  wt = make_work_map(&m, Walk::kKeyGrad, heads, D);
     const int64_t items = work_items(w, nb);
-    printf("%d %d %d %d %d\n", query_groups(D, block, w, items, true), query_groups(D, block, w, items, false), key_groups(block, wt, items),
-           fp8_groups(w, items), w.ordered);
+    printf("%d %d %d %d %d %d %d\n", query_groups(D, block, w, items, true), query_groups(D, block, wq, items, false),
+           key_groups(block, wt, items), fp8_groups(w, items), w.ordered, wq.ordered, wt.ordered);
   }
   return 0;
 }

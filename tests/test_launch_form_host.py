@@ -22,7 +22,7 @@ def forms(tmp_path_factory):
     assert r.returncode == 0, r.stdout[-3000:]
 
     def run(cases):
-        """(D, block, heads, n_blocks, entries per list or (total, longest)) -> (forward, dq, dkdv, fp8, ordered heads)"""
+        """(D, block, heads, n_blocks, entries per list or (total, longest)) -> (forward, dq, dkdv, fp8, heads by length in forward, dq, dkdv)"""
         lines = []
         for D, block, heads, nb, per in cases:
             nnz, longest = (nb * per, per) if isinstance(per, int) else per
@@ -66,3 +66,16 @@ def test_heads_by_list_length(forms):
     """All heads up to one round of workgroups (256 items) and up to 8 heads; else the last ones that fit the cache."""
     assert [f[4] for f in forms([(128, 128, 20, 12, 4), (64, 64, 256, 1, 1), (128, 128, 257, 1, 1), (128, 128, 8, 300, 50), (128, 128, 9, 300, 50),
                                  (128, 128, 24, 929, 100), (128, 128, 1, 16385, 100)])] == [20, 256, 8, 8, 8, 2, 0]
+
+
+def test_long_heads_in_blocks_of_64_stay_with_slices(forms):
+    """On either side of the most K and V per XCD: 28 MiB (forward), 16 MiB (its last 8 of more heads), 64 MiB (dQ).  Blocks
+    of 128, dK/dV and launches that last as long as one of their lists have no such limit."""
+    skewed = lambda nb: (100 * nb, 200)
+    cases = [(128, 64, 4, 896, 100), (128, 64, 4, 897, 100), (64, 64, 4, 1792, 100), (64, 64, 4, 1793, 100), (128, 64, 1, 897, skewed(897)), (128, 64, 4, 1100, skewed(1100)),
+             (128, 64, 5, 597, 100), (128, 64, 5, 598, 100), (128, 64, 6, 598, 100), (128, 64, 3, 716, 100), (128, 64, 3, 717, 100),
+             (128, 64, 7, 512, 100), (128, 64, 7, 513, 100), (128, 64, 16, 512, 100), (128, 64, 16, 513, 100),
+             (128, 64, 2, 2048, 100), (128, 64, 2, 2049, 100), (128, 128, 4, 513, 100), (128, 128, 1, 2056, 100)]
+    assert [f[4:] for f in forms(cases)] == [
+        (4, 4, 4), (0, 4, 4), (4, 4, 4), (0, 4, 4), (1, 1, 1), (0, 4, 4), (5, 5, 5), (0, 5, 5), (0, 6, 6), (3, 3, 3), (0, 3, 3),
+        (7, 7, 7), (0, 7, 7), (8, 8, 8), (0, 8, 8), (0, 2, 2), (0, 0, 2), (4, 4, 4), (1, 1, 1)]
