@@ -184,15 +184,20 @@ inline int64_t work_grid(const WorkMap& w, int32_t n_blocks) {
 // Two groups for 64-token blocks above kOneRound items: four workgroups of one group fit a compute unit, or two of two, so that
 // two groups take ceil(items / 512) / 2 walks where one takes ceil(items / 1024).
 //   up to 512 items:  a round either way.  Forward, D 128, 300 items: L 8 22.2 / 17.0, L 48 91.9 / 58.9; dQ -5, -48.
-//   up to 1024:  one round or two of half the length, which pays only for what long lists leave over.  Forward, D 128,
-//     600 items: L 16 40.5 / 44.8, L 48 97.8 / 107.1; radial lists (mean 86, longest 106, 742 items) 176.7 / 173.6, with
-//     text rows (188, 299; 897 items) 492 / 413.  D 64, mean 86, longest 106: 112 / 97; mean 61, longest 66: 81.4 / 81.8.
+//   up to 1024:  one round or two of half the length, which pays for what long lists of unequal length leave over, more so
+//     at D 64.  Forward, (items; mean, longest), D 128 / D 64: (568; 103, 115) 194 / 194, 129 / 106; (568; 62, 65) 119 / 125,
+//     76.1 / 69.5; (882; 84, 98) 192 / 200, 120 / 115; (879; 236, 293) 513 / 508, 323 / 299; (891; 418, 505) 1113 / 988,
+//     576 / 529; with text rows (897; 188, 299) 492 / 413, 271 / 244.  Equal lists: D 128 (835; 167, 167) 356 / 377,
+//     (640; 16, 16) 40.6 / 42.5; D 64 (830; 166, 166) 211 / 218.  dQ 0 to -5 % from 90 entries on.
 //   up to 1536:  two rounds or three of half the length.  Forward, D 128, 1200 items: L 8 46.1 / 44.6, L 12 62.0 / 56.7,
 //     L 48 195 / 172; dQ, L 8 0, L 12 -4, L 48 -36.  L 4, forward: 30.3 / 32.2.
 //   above:  D 128 loses (1800 items, L 48 224 / 233; 1880 items on radial lists 359 / 373).
-inline bool two_groups_pay_64(const WorkMap& w, int64_t items) {
+inline bool two_groups_pay_64(int D, const WorkMap& w, int64_t items) {
   if (items <= 512) return w.longest >= 4;
-  if (items <= 1024) return w.mean >= 16 && 8LL * w.longest > 9LL * w.mean;
+  if (items <= 1024) {
+    if (2LL * w.longest >= 3LL * w.mean) return w.mean >= 16;
+    return D == 64 ? w.mean >= 24 && 32LL * w.longest > 33LL * w.mean : w.mean >= 96 && 8LL * w.longest > 9LL * w.mean;
+  }
   return items <= 1536 && w.mean >= 12;
 }
 
@@ -210,7 +215,7 @@ inline int query_groups(int D, int block, const WorkMap& w, int64_t items, bool 
     return items <= kOneRound && w.longest >= 4 ? 2 : 1;
   }
   if (items <= kOneRound && w.longest >= 12) return 4;
-  if (two_groups_pay_64(w, items)) return 2;
+  if (two_groups_pay_64(D, w, items)) return 2;
   return forward && D == 64 && items > 1536 && w.mean >= 32 ? 2 : 1;
 }
 
@@ -218,19 +223,20 @@ inline int query_groups(int D, int block, const WorkMap& w, int64_t items, bool 
 // one group of 64, so that at block 64 two groups take ceil(items / 256) / 2 walks where one takes ceil(items / 512).
 //   block 128, half blocks, 64 items: L 1 0, L 2 -3, L 16 -27; 256 items, L 32: +13.
 //   block 64, D 128: 256 items L 2 +1, L 3 0, L 8 -7, L 32 -22; 300 items L 8 +2, L 16 -6, L 48 -40; 500 items L 48 +7;
-//   600 items L 8 +2, L 16 -1, L 48 -34; 700 items L 16 +9, L 48 -33; 1000 items L 48 +18; 1200 items L 16 +23, L 48 -25,
-//   radial lists (mean 51, 1140 items) -9; 1300 items, L 48: +5.
+//   572 items L 26 -26 (with dQ); 600 items L 8 +2, L 16 -1, L 48 -34; 700 items L 16 +9, L 48 -33; 1000 items L 48 +18; 1200 items L 16 +23, L 48 -25,
+//   radial lists (mean 51, 1140 items) -9; 1300 items, L 48: +5.  One list far longer than the others (text, the sink's
+//   columns) makes up for a round: 891 items (mean 418, longest 891) -153 of 3219.
 inline int key_groups(int block, const WorkMap& w, int64_t items) {
   if (block == 128) return items <= 128 && w.longest >= 2 ? 2 : 1;
   if (items <= kOneRound) return w.longest >= 3 ? 2 : 1;
   if (items <= 384) return w.longest >= 16 ? 2 : 1;
-  return items <= 1200 && (items - 1) / 256 % 2 == 0 && w.mean >= 32 ? 2 : 1;
+  return items <= 1200 && w.mean >= (items <= 768 ? 24 : 32) && ((items - 1) / 256 % 2 == 0 || w.longest >= 2LL * w.mean) ? 2 : 1;
 }
 
 // 8-bit scores: three groups of 4 waves (12 waves are what a compute unit holds of this kernel) while every item can
-// have a compute unit of its own.  64 items: L 4 16.9 / 17.7, L 6 22.3 / 19.8; 256 items: L 6 24.0 / 22.7, L 32 93.5 / 69.0;
+// have a compute unit of its own.  64 items: L 4 16.9 / 17.7, L 6 22.3 / 19.8; 105 items L 5 (with the quantisation) 40.4 / 37.5; 256 items: L 6 24.0 / 22.7, L 32 93.5 / 69.0;
 // 288 items (with the quantisation) 127 / 133.
-inline int fp8_groups(const WorkMap& w, int64_t items) { return items <= kOneRound && w.longest >= 6 ? 3 : 1; }
+inline int fp8_groups(const WorkMap& w, int64_t items) { return items <= kOneRound && w.longest >= 5 ? 3 : 1; }
 
 struct TensorArg {
   const void* ptr;

@@ -52,13 +52,15 @@ def test_forms_change_at_the_measured_sizes(forms):
         (128, 128, 8, 16, 16), (128, 128, 3, 43, 16), (128, 128, 8, 32, 16), (128, 128, 1, 257, 16),
         # block 64: four groups to 256 items, two to 512
         (128, 64, 8, 32, 16), (128, 64, 8, 32, 11), (128, 64, 1, 257, 16), (128, 64, 8, 64, 48),
-        # to 1024 items: equal lists alone, unequal ones in two groups (dK/dV: 513 to 768 items)
-        (128, 64, 12, 50, 48), (64, 64, 12, 50, wide(50)), (128, 64, 9, 100, wide(100)),
+        # to 1024 items: long unequal lists in two groups (dK/dV: 513 to 768 items), or very unequal ones
+        (128, 64, 12, 50, 48), (64, 64, 12, 50, (48 * 50, 50)), (64, 64, 12, 50, (23 * 50, 30)), (128, 64, 9, 100, (9600, 109)), (128, 64, 9, 100, 100),
+        (128, 64, 9, 100, wide(100)),
         # to 1536: two groups (dK/dV: to 1200); above: D 64 forward, long lists only
         (128, 64, 11, 100, 48), (128, 64, 15, 100, 48), (128, 64, 16, 100, 48), (64, 64, 40, 100, 48), (64, 64, 40, 100, 24)])] == [
         (4, 4, 2), (2, 2, 1), (2, 2, 1), (1, 1, 1),
         (4, 4, 2), (2, 2, 2), (2, 2, 2), (2, 2, 1),
-        (1, 1, 2), (2, 2, 2), (2, 2, 1),
+        (1, 1, 2), (2, 2, 2), (1, 1, 1), (2, 2, 1), (1, 1, 1),
+        (2, 2, 2),
         (2, 2, 2), (2, 2, 1), (1, 1, 1), (2, 1, 1), (1, 1, 1)]
 
 
