@@ -126,6 +126,8 @@ constexpr int32_t kMaxOrdered = 16384;  // blocks up to which a mask carries the
 // locality to keep, but slices of unequal length start workgroups without work, which hold up to 128 KiB of LDS as long as they
 // wait for their turn.  Such a launch goes by length whatever its number of heads (20 heads x 12 blocks: 288
 // workgroups for 240 items; forward, D 128, block 128, two groups: lists of 4 29.4 -> 17.4 us, of 12 55.8 -> 33.0).
+// In blocks of 64, where two groups take half a compute unit, that holds up to twice as many (40 heads x 12 blocks: 608
+// workgroups for 480 items; D 128, lists of 12, forward 37.3 -> 23.4 us, forward and backward 140 -> 91).
 constexpr int64_t kOrderedWholeBytes = 256 << 20, kOrderedTailBytes = 160 << 20;
 constexpr int64_t kOneRound = 256;
 // Blocks of 64 tokens move twice the K and V per product, and by length the blocks that an XCD works on at one time
@@ -162,7 +164,7 @@ inline WorkMap make_work_map(const radial_mask* m, Walk walk, int32_t heads, int
   const int64_t most_bytes = walk == Walk::kQueryGrad ? kQueryGradXcdBytes64 : heads > 8 ? kForwardTailBytes64 : kForwardXcdBytes64;
   const bool long_tail = w.longest >= 2LL * w.mean && 2048LL * w.longest >= (int64_t)w.mean * heads * m->n_blocks;
   const bool scattered = m->block == 64 && !transposed && xcd_bytes(per_head, heads) > most_bytes && !long_tail;
-  w.ordered = !w.order ? 0 : (int64_t)heads * m->n_blocks <= kOneRound ? heads : scattered ? 0 : (fit < most ? (int32_t)fit : most);
+  w.ordered = !w.order ? 0 : (int64_t)heads * m->n_blocks <= (m->block == 64 ? 2 * kOneRound : kOneRound) ? heads : scattered ? 0 : (fit < most ? (int32_t)fit : most);
   w.sliced = heads - w.ordered;
   w.n_blocks = m->n_blocks;
   return w;

@@ -65,9 +65,9 @@ def test_order_covers_all_blocks_of_caller_lists():
     m.free()
 
 
-@pytest.mark.parametrize("block, H, N", [(128, 20, 12 * 128), (64, 20, 12 * 64 - 5), (64, 85, 3 * 64)])
+@pytest.mark.parametrize("block, H, N", [(128, 20, 12 * 128), (64, 20, 12 * 64 - 5), (64, 85, 3 * 64), (64, 40, 12 * 64)])
 def test_small_launches_of_many_heads_start_no_idle_workgroups(block, H, N):
-    """Up to 256 (head, block) items the records of the traced forward are those of the first `items` workgroups."""
+    """Up to 256 (head, block) items, 512 in blocks of 64, the records of the traced forward are those of the first `items` workgroups."""
     import torch
     from paper_2506_19852_amd import binding as rb
     D, nb = 128, -(-N // block)

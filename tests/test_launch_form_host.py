@@ -65,9 +65,11 @@ def test_forms_change_at_the_measured_sizes(forms):
 
 
 def test_heads_by_list_length(forms):
-    """All heads up to one round of workgroups (256 items) and up to 8 heads; else the last ones that fit the cache."""
-    assert [f[4] for f in forms([(128, 128, 20, 12, 4), (64, 64, 256, 1, 1), (128, 128, 257, 1, 1), (128, 128, 8, 300, 50), (128, 128, 9, 300, 50),
-                                 (128, 128, 24, 929, 100), (128, 128, 1, 16385, 100)])] == [20, 256, 8, 8, 8, 2, 0]
+    """All heads up to one round of workgroups (256 items; 512 in blocks of 64) and up to 8 heads; else the last ones that
+    fit the cache."""
+    assert [f[4] for f in forms([(128, 128, 20, 12, 4), (128, 128, 256, 1, 1), (128, 128, 257, 1, 1), (128, 64, 40, 12, 12), (64, 64, 512, 1, 1),
+                                 (64, 64, 513, 1, 1), (128, 128, 8, 300, 50), (128, 128, 9, 300, 50), (128, 128, 24, 929, 100),
+                                 (128, 128, 1, 16385, 100)])] == [20, 256, 8, 40, 512, 8, 8, 8, 2, 0]
 
 
 def test_long_heads_in_blocks_of_64_stay_with_slices(forms):
