@@ -45,9 +45,10 @@ struct BwdTile {
   static constexpr int kStatBytes = 2 * kStageQ * 4;     // LSE and delta of a stage
   static constexpr int kStageBytes = 2 * kQBytes + kStatBytes;
   static constexpr int kGroupBytes = 2 * kStageBytes;
-  static constexpr int kLdsBytes = S * kGroupBytes;
+  using Join = Merge<S, kWaves, kDTiles>;
+  static constexpr int kLdsBytes = S * kGroupBytes > Join::kLdsBytes ? S * kGroupBytes : Join::kLdsBytes;
   static constexpr int kQLoadsPerWave = kQBytes / 1024 / kWaves;
-  static_assert((S - 1) * kWaves * 2 * kDTiles * 4096 <= kLdsBytes || S == 1, "the sums reuse the stage buffers");
+  static constexpr int kStatLoads = kWaves == 1 ? 2 : 1;  // copies of LSE and delta: waves 0 and 1 take one each
 };
 
 template <int D>
@@ -95,35 +96,6 @@ __device__ __forceinline__ void mfma32_vgpr(f32x16& acc, bf16x8 a, bf16x8 b) {
 // The accumulators are operands so that every later use of them stays behind the wait.
 __device__ __forceinline__ void mfma_results_settle(f32x16& acc0, f32x16& acc1) {
   asm volatile("s_nop 15" : "+v"(acc0), "+v"(acc1));
-}
-
-// Adds the accumulators of the groups 1 .. S-1 to those of group 0 through LDS (the stage buffers, once
-// every wave is done with them); returns whether this wave holds the sums (group 0).
-template <int S, int kWaves, int kTiles>
-__device__ __forceinline__ bool add_groups(f32x16 (&acc)[kTiles], char* lds_all, int group, int wave, int lane) {
-  if (group > 0) {
-    char* dst = lds_all + ((group - 1) * kWaves + wave) * kTiles * 4096 + lane * 16;
-#pragma unroll
-    for (int i = 0; i < kTiles; ++i)
-#pragma unroll
-      for (int e4 = 0; e4 < 4; ++e4)
-        *lds_cast<f32x4>(dst + (i * 4 + e4) * 1024) = f32x4{acc[i][4 * e4], acc[i][4 * e4 + 1], acc[i][4 * e4 + 2], acc[i][4 * e4 + 3]};
-  }
-  __syncthreads();
-  if (group > 0) return false;
-#pragma unroll 1
-  for (int other = 1; other < S; ++other) {
-    const char* src = lds_all + ((other - 1) * kWaves + wave) * kTiles * 4096 + lane * 16;
-#pragma unroll
-    for (int i = 0; i < kTiles; ++i)
-#pragma unroll
-      for (int e4 = 0; e4 < 4; ++e4) {
-        const f32x4 v = *lds_cast<const f32x4>(src + (i * 4 + e4) * 1024);
-#pragma unroll
-        for (int x = 0; x < 4; ++x) acc[i][4 * e4 + x] += v[x];
-      }
-  }
-  return true;
 }
 
 // kExact (all three kernels' callers): apply the token-level rule inside the listed blocks.
@@ -216,6 +188,7 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a) {
       r = r < a.N ? r : a.N - 1;
       const uint32_t sdst = lds_base + buf * T::kStageBytes + 2 * T::kQBytes + wave * kStageQ * 4;
       copy4_to_lds((wave == 0 ? lsep : deltap) + r, sdst);
+      if (T::kStatLoads == 2) copy4_to_lds(deltap + r, sdst + kStageQ * 4);
     }
   };
 
@@ -249,8 +222,12 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a) {
       if (kExact) q_at_next = stage_pos<T::kLastOffset>(cvec_at, e1 & 63, ((u + 1) % T::kSubs) * kStageQ, a.rule.s);
     }
 
-    wait_all_copies();  // stage u has landed
-    __syncthreads();    // for every wave; stage u-1 is finished
+    if (T::kWaves == 1) {  // nobody else reads or writes this group's stage buffers
+      asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    } else {
+      wait_all_copies();  // stage u has landed
+      __syncthreads();    // for every wave; stage u-1 is finished
+    }
     // The copies of a full next stage are spread over the first MFMAs of this one (see below);
     // a ragged one is issued at once.
     const bool spread_next = has_next && q0_next + kStageQ <= a.N;
@@ -277,14 +254,15 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a) {
     const __bf16* gbase_next = gp + (int64_t)q_src * a.dout.sn;
     const uint32_t qdst_next = lds_base + (buf ^ 1) * T::kStageBytes + wave * T::kQLoadsPerWave * 1024;
     const uint32_t gdst_next = qdst_next + T::kQBytes;
-    auto spread_copy = [&](int j) {  // j = 0 .. 2 * kQLoadsPerWave: Q pieces, dO pieces, LSE/delta
+    auto spread_copy = [&](int j) {  // Q pieces, dO pieces, LSE and delta
       if (j < T::kQLoadsPerWave) {
         copy16_to_lds_sv_masked(qbase_next, qoff[j], qdst_next + j * 1024, copy_lanes);
       } else if (j < 2 * T::kQLoadsPerWave) {
         copy16_to_lds_sv_masked(gbase_next, goff[j - T::kQLoadsPerWave], gdst_next + (j - T::kQLoadsPerWave) * 1024, copy_lanes);
-      } else if (j == 2 * T::kQLoadsPerWave) {
-        const uint32_t sdst = lds_base + (buf ^ 1) * T::kStageBytes + 2 * T::kQBytes + (wave & 1) * kStageQ * 4;
-        copy4_to_lds_sv_masked((wave == 0 ? lsep : deltap) + q_src, (uint32_t)lane * 4u, sdst, wave < 2 ? copy_lanes : 0ull);
+      } else {
+        const int which = T::kStatLoads == 2 ? j - 2 * T::kQLoadsPerWave : wave & 1;
+        const uint32_t sdst = lds_base + (buf ^ 1) * T::kStageBytes + 2 * T::kQBytes + which * kStageQ * 4;
+        copy4_to_lds_sv_masked((which == 0 ? lsep : deltap) + q_src, (uint32_t)lane * 4u, sdst, wave < 2 ? copy_lanes : 0ull);
       }
     };
 
@@ -346,7 +324,7 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a) {
         mfma32_vgpr(s[0], qfr[t], kf[t]);
         mfma32_vgpr(dp[0], gfr[t], vf[t]);
       }
-      constexpr int kCopies = 2 * T::kQLoadsPerWave + 1;
+      constexpr int kCopies = 2 * T::kQLoadsPerWave + T::kStatLoads;
 #pragma unroll
       for (int j = t * kCopies / T::kSteps; j < (t + 1) * kCopies / T::kSteps; ++j) spread_copy(j);
       __builtin_amdgcn_sched_barrier(0);
@@ -407,19 +385,19 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a) {
     q_at = q_at_next;
   }
 
-  if (S > 1) {
-    // a stage is a barrier: as many as group 0, which has most stages
-    for (int32_t u = n_stage; u < (n_col + S - 1) / S * T::kSubs; ++u) __syncthreads();
-    __syncthreads();
-    add_groups<S, T::kWaves>(dk, lds_all, group, wave, lane);
-    __syncthreads();
-    if (!add_groups<S, T::kWaves>(dv, lds_all, group, wave, lane)) return;
-  }
-
   // ---- epilogue: dK = scale * dK^T, dV -----------------------------------------------------
-  if (key_ok) {
-    __bf16* dkd = (__bf16*)a.dk.ptr + (int64_t)b * a.dk.sb + (int64_t)h * a.dk.sh + (int64_t)key_row * a.dk.sn;
-    __bf16* dvd = (__bf16*)a.dv.ptr + (int64_t)b * a.dv.sb + (int64_t)h * a.dv.sh + (int64_t)key_row * a.dv.sn;
+  __bf16* dkd = (__bf16*)a.dk.ptr + (int64_t)b * a.dk.sb + (int64_t)h * a.dk.sh + (int64_t)key_row * a.dk.sn;
+  __bf16* dvd = (__bf16*)a.dv.ptr + (int64_t)b * a.dv.sb + (int64_t)h * a.dv.sh + (int64_t)key_row * a.dv.sn;
+  if (S > 1) {
+    if (T::kWaves > 1)  // a stage is a barrier: as many as group 0, which has most stages
+      for (int32_t u = n_stage; u < (n_col + S - 1) / S * T::kSubs; ++u) __syncthreads();
+    T::Join::add(dk, lds_all, group, wave, lane, [&](int p, f32x4 v) __attribute__((always_inline)) {
+      if (key_ok) *(u32x2*)(dkd + 8 * p + 4 * g) = u32x2{pack_bf16(v[0] * a.scale, v[1] * a.scale), pack_bf16(v[2] * a.scale, v[3] * a.scale)};
+    });
+    T::Join::add(dv, lds_all, group, wave, lane, [&](int p, f32x4 v) __attribute__((always_inline)) {
+      if (key_ok) *(u32x2*)(dvd + 8 * p + 4 * g) = u32x2{pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
+    });
+  } else if (key_ok) {
 #pragma unroll
     for (int dt = 0; dt < T::kDTiles; ++dt)
 #pragma unroll
@@ -441,13 +419,17 @@ template <int D, int BLK, bool kExact, int S, int R>
 __global__ void __launch_bounds__(2 * BLK / R * S, 1) radial_bwd_dkdv_split_kernel(const BwdArgs a) {
   dkdv_body<D, BLK, kExact, S, R>(a);
 }
+template <int D, int BLK, bool kExact, int S, int R>
+__global__ void __launch_bounds__(2 * BLK / R * S, 1) radial_bwd_dkdv_single_kernel(const BwdArgs a) {  // one wave per group
+  dkdv_body<D, BLK, kExact, S, R>(a);
+}
 
 template <int D, int BLK, int S, int R>
 struct DqTile {
   static constexpr int kRows = BLK / R;
   // Keys per stage of the dQ kernel.  Head dimension 128 with 64 rows walks half-size stages:
   // two 64-key stage buffers (64 KiB) per 2 waves would leave a compute unit with 4 waves.
-  static constexpr int kStageKeys = (D == 128 && kRows == 64) ? 32 : 64;
+  static constexpr int kStageKeys = (D == 128 && kRows == 64) || kRows == 32 ? 32 : 64;
   static constexpr int kWaves = kRows / 32;  // one wave per 32 query rows
   static constexpr int kThreads = 64 * kWaves * S;
   static constexpr int kSubs = BLK / kStageKeys;
@@ -457,8 +439,8 @@ struct DqTile {
   static constexpr int kTileBytes = kStageKeys * D * 2;  // one K (or V) stage tile
   static constexpr int kLoadsPerWave = kTileBytes / 1024 / kWaves;
   static constexpr int kGroupBytes = 4 * kTileBytes;     // [stage buffer][K, V]
-  static constexpr int kLdsBytes = S * kGroupBytes;
-  static_assert((S - 1) * kWaves * kDTiles * 4096 <= kLdsBytes || S == 1, "the sums reuse the stage buffers");
+  using Join = Merge<S, kWaves, kDTiles>;
+  static constexpr int kLdsBytes = S * kGroupBytes > Join::kLdsBytes ? S * kGroupBytes : Join::kLdsBytes;
 };
 
 template <int D, int BLK, bool kExact, int S, int R>
@@ -587,8 +569,12 @@ __global__ void __launch_bounds__(2 * BLK / R * S, 2) radial_bwd_dq_kernel(const
       key0_next = __builtin_amdgcn_readlane(cvec, e1 & 63) * BLK + ((u + 1) % T::kSubs) * T::kStageKeys;
       if (kExact) k_at_next = stage_pos<T::kLastOffset>(cvec_at, e1 & 63, ((u + 1) % T::kSubs) * T::kStageKeys, a.rule.s);
     }
-    wait_all_copies();
-    __syncthreads();
+    if (T::kWaves == 1) {  // nobody else reads or writes this group's stage buffers
+      asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    } else {
+      wait_all_copies();
+      __syncthreads();
+    }
 
     const char* lds_k = lds_at(buf * 2 * T::kTileBytes);
     const char* lds_v = lds_k + T::kTileBytes;
@@ -674,14 +660,14 @@ __global__ void __launch_bounds__(2 * BLK / R * S, 2) radial_bwd_dq_kernel(const
     k_at = k_at_next;
   }
 
+  __bf16* dst = (__bf16*)a.dq.ptr + (int64_t)b * a.dq.sb + (int64_t)h * a.dq.sh + (int64_t)q_row * a.dq.sn;
   if (S > 1) {
-    // a stage is a barrier: as many as group 0, which has most stages
-    for (int32_t u = n_stage; u < (n_row + S - 1) / S * T::kSubs; ++u) __syncthreads();
-    __syncthreads();
-    if (!add_groups<S, T::kWaves>(dq, lds_all, group, wave, lane)) return;
-  }
-  if (q_ok) {
-    __bf16* dst = (__bf16*)a.dq.ptr + (int64_t)b * a.dq.sb + (int64_t)h * a.dq.sh + (int64_t)q_row * a.dq.sn;
+    if (T::kWaves > 1)  // a stage is a barrier: as many as group 0, which has most stages
+      for (int32_t u = n_stage; u < (n_row + S - 1) / S * T::kSubs; ++u) __syncthreads();
+    T::Join::add(dq, lds_all, group, wave, lane, [&](int p, f32x4 v) __attribute__((always_inline)) {
+      if (q_ok) *(u32x2*)(dst + 8 * p + 4 * g) = u32x2{pack_bf16(v[0] * a.scale, v[1] * a.scale), pack_bf16(v[2] * a.scale, v[3] * a.scale)};
+    });
+  } else if (q_ok) {
 #pragma unroll
     for (int dt = 0; dt < T::kDTiles; ++dt)
 #pragma unroll
@@ -697,7 +683,8 @@ int launch_dkdv(BwdArgs a, hipStream_t stream) {
   using T = BwdTile<D, BLK, S, R>;
   void (*kernel)(BwdArgs);
   if constexpr (S == 1) kernel = radial_bwd_dkdv_kernel<D, BLK, kExact>;
-  else kernel = radial_bwd_dkdv_split_kernel<D, BLK, kExact, S, R>;
+  else if constexpr (T::kWaves > 1) kernel = radial_bwd_dkdv_split_kernel<D, BLK, kExact, S, R>;
+  else kernel = radial_bwd_dkdv_single_kernel<D, BLK, kExact, S, R>;
   static DeviceOnce configured;
   if (int rc = allow_dynamic_lds(configured, (const void*)kernel, T::kLdsBytes)) return rc;
   a.work_t.ordered *= R;  // R > 1 only up to kOneRound items, where all heads are taken by list length
@@ -728,10 +715,13 @@ int launch(const BwdArgs& a, hipStream_t stream) {
   bwd_prepare_kernel<D><<<dim3((unsigned)prep_grid), dim3(256), 0, stream>>>(a);
   const int64_t items = work_items(a.work, a.n_blocks);
   const int kv = key_groups(BLK, a.work_t, items), q = query_groups(D, BLK, a.work, items, false);
-  int rc = kv == 2 ? launch_dkdv<D, BLK, kExact, 2, BLK / 64>(a, stream) : launch_dkdv<D, BLK, kExact, 1, 1>(a, stream);
+  int rc;
+  if (D == 64 && single_waves(BLK, a.work_t, items)) rc = launch_dkdv<64, BLK, kExact, 4, BLK / 32>(a, stream);
+  else rc = kv == 2 ? launch_dkdv<D, BLK, kExact, 2, BLK / 64>(a, stream) : launch_dkdv<D, BLK, kExact, 1, 1>(a, stream);
   if (rc) return rc;
-  rc = q == 4 ? launch_dq<D, BLK, kExact, 4, BLK / 64>(a, stream)
-              : q == 2 ? launch_dq<D, BLK, kExact, 2, 1>(a, stream) : launch_dq<D, BLK, kExact, 1, 1>(a, stream);
+  if (single_waves(BLK, a.work, items)) rc = launch_dq<D, BLK, kExact, D == 64 ? 8 : 4, BLK / 32>(a, stream);
+  else if (q == 4) rc = launch_dq<D, BLK, kExact, 4, BLK / 64>(a, stream);
+  else rc = q == 2 ? launch_dq<D, BLK, kExact, 2, 1>(a, stream) : launch_dq<D, BLK, kExact, 1, 1>(a, stream);
   if (rc) return rc;
   RADIAL_HIP_TRY(hipGetLastError());
   return RADIAL_OK;

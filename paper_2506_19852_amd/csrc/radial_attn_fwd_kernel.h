@@ -39,7 +39,7 @@ struct Tile {
   static constexpr int kRows = BLK / R;
   // Keys per pipeline stage.  Head dimension 128 with 64 rows walks half-size stages: two
   // 64-key stage buffers (64 KiB) per 2 waves would leave a compute unit with 4 waves.
-  static constexpr int kStageKeys = (D == 128 && kRows == 64) ? 32 : 64;
+  static constexpr int kStageKeys = (D == 128 && kRows == 64) || kRows == 32 ? 32 : 64;
   static constexpr int kWaves = kRows / 32;        // one wave per 32 query rows
   static constexpr int kThreads = 64 * kWaves * S;
   static constexpr int kPiecesPerRow = D / 8;      // 16-byte pieces per K/V row
@@ -50,14 +50,11 @@ struct Tile {
   static constexpr int kSteps = D / 16;            // MFMA k-steps of the S product
   static constexpr int kKeyTiles = kStageKeys / 32;
   static constexpr int kDTiles = D / 32;           // 32-wide d tiles of O
-  // MFMAs of the first product per copy of the next stage (copies are spread over that product)
-  static constexpr int kCopyEvery = (kKeyTiles * kSteps) / (2 * kLoadsPerWave);
-  static_assert(kCopyEvery >= 1, "more copies than MFMAs in the first product");
+  // a wave's copies of the next stage, and the MFMAs of the first product that they are spread over
+  static constexpr int kCopies = 2 * kLoadsPerWave, kCopyOver = kKeyTiles * kSteps;
   static constexpr int kGroupBytes = 4 * kStageBytes;               // [stage buffer][K, V]
-  static constexpr int kLdsBytes = S * kGroupBytes;
-  // one wave's share of a merge: O in 16-byte pieces, then m and l, all in lane order
-  static constexpr int kMergeBytes = kDTiles * 4096 + 512;
-  static_assert((S - 1) * kWaves * kMergeBytes <= kLdsBytes || S == 1, "the merge reuses the stage buffers");
+  using Join = Merge<S, kWaves, kDTiles>;
+  static constexpr int kLdsBytes = S * kGroupBytes > Join::kLdsBytes ? S * kGroupBytes : Join::kLdsBytes;
 };
 
 // Swizzle key of a 256-byte LDS line (16 pieces of 16 bytes); pieces move inside their line only.
@@ -232,13 +229,11 @@ __global__ void __launch_bounds__(2 * BLK / R * S, 2) radial_fwd_kernel(const Fw
       for (int t = 0; t < T::kSteps; ++t) {
         const bf16x8 kf = *lds_cast<const bf16x8>(lds_k + piece_offset<D, false>(kt * 32 + lq, 2 * t + g));
         s[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[t], s[kt], 0, 0, 0);
-        {  // one copy of stage u+1 every kCopyEvery MFMAs
-          const int m = kt * T::kSteps + t + 1;
-          const int j = m / T::kCopyEvery - 1;
-          if (m % T::kCopyEvery == 0 && j < T::kLoadsPerWave)
-            copy16_to_lds_sv_masked(kbase_next, koff[j], kdst_next + j * 1024, spread_lanes);
-          else if (m % T::kCopyEvery == 0 && j < 2 * T::kLoadsPerWave)
-            copy16_to_lds_sv_masked(vbase_next, voff[j - T::kLoadsPerWave], vdst_next + (j - T::kLoadsPerWave) * 1024, spread_lanes);
+        const int i = kt * T::kSteps + t;  // copies of stage u+1 after this MFMA
+#pragma unroll
+        for (int j = i * T::kCopies / T::kCopyOver; j < (i + 1) * T::kCopies / T::kCopyOver; ++j) {
+          if (j < T::kLoadsPerWave) copy16_to_lds_sv_masked(kbase_next, koff[j], kdst_next + j * 1024, spread_lanes);
+          else copy16_to_lds_sv_masked(vbase_next, voff[j - T::kLoadsPerWave], vdst_next + (j - T::kLoadsPerWave) * 1024, spread_lanes);
         }
       }
     }
@@ -332,8 +327,12 @@ __global__ void __launch_bounds__(2 * BLK / R * S, 2) radial_fwd_kernel(const Fw
       if (kExact) k_at_next = stage_pos<T::kLastOffset>(cvec_at, e1 & 63, ((u + 1) % T::kSubs) * T::kStageKeys, a.rule.s);
     }
 
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's copies of stage u have landed
-    __syncthreads();                                  // ... and everyone's; stage u-1 is fully consumed
+    if (T::kWaves == 1) {  // nobody else reads or writes this group's stage buffers
+      asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    } else {
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's copies of stage u have landed
+      __syncthreads();                                  // ... and everyone's; stage u-1 is fully consumed
+    }
 
     StageRule vis = {};
     bool skip = false;
@@ -358,65 +357,37 @@ __global__ void __launch_bounds__(2 * BLK / R * S, 2) radial_fwd_kernel(const Fw
     if (u + 1 < n_stage) one_stage(u + 1, std::integral_constant<int, 1>{});
   }
 
-  // ---- merge of the groups: group 0 gathers (m, l, O) of the others through LDS ---------------
-  // (float32 throughout; at most 99 KiB per workgroup, three groups of two waves, in about a microsecond)
+  __bf16* const dst = op + (int64_t)q_row * a.o.sn;
+  const auto store_lse = [&](float m, float l) __attribute__((always_inline)) {
+    const int64_t idx = ((int64_t)b * a.H + h) * a.N + q_row;
+    a.lse[idx] = l > 0.f ? m * a.scale + __logf(l) : -INFINITY;
+  };
+
+  // ---- several groups: merge and store ------------------------------------------------------
   if (S > 1) {
-    // a stage is a barrier: as many as group 0, which has most stages
-    for (int32_t u = n_stage; u < (n_row + S - 1) / S * T::kSubs; ++u) __syncthreads();
-    __syncthreads();  // the last stages are consumed; their buffers are reused
-    if (group > 0) {
-      char* dst = lds_all + ((group - 1) * T::kWaves + wave) * T::kMergeBytes + lane * 16;
+    if (T::kWaves > 1)  // a stage is a barrier: as many as group 0, which has most stages
+      for (int32_t u = n_stage; u < (n_row + S - 1) / S * T::kSubs; ++u) __syncthreads();
+    float m = m_run, l = l_run;
+    T::Join::softmax(o, m, l, c, lds_all, group, wave, lane, [&](int p, f32x4 v) __attribute__((always_inline)) {
+      if (q_ok) *(u32x2*)(dst + 8 * p + 4 * g) = u32x2{pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
+    });
+    if (q_ok && a.lse && g == 0 && group == 0) store_lse(m, l);
+  } else {
+    // ---- epilogue: O / l, LSE --------------------------------------------------------------
+    const float l_tot = l_run + __shfl_xor(l_run, 32);
+    const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
+    if (q_ok) {
 #pragma unroll
-      for (int i = 0; i < T::kDTiles; ++i)
-#pragma unroll
-        for (int e4 = 0; e4 < 4; ++e4)
-          *lds_cast<f32x4>(dst + (i * 4 + e4) * 1024) = f32x4{o[i][4 * e4], o[i][4 * e4 + 1], o[i][4 * e4 + 2], o[i][4 * e4 + 3]};
-      char* ml = lds_all + ((group - 1) * T::kWaves + wave) * T::kMergeBytes + T::kDTiles * 4096 + lane * 4;
-      *lds_cast<float>(ml) = m_run;
-      *lds_cast<float>(ml + 256) = l_run;
-    }
-    __syncthreads();
-    if (group > 0) return;
-#pragma unroll 1
-    for (int other = 1; other < S; ++other) {
-      const char* src = lds_all + ((other - 1) * T::kWaves + wave) * T::kMergeBytes;
-      const float m_o = *lds_cast<const float>(src + T::kDTiles * 4096 + lane * 4);
-      const float l_o = *lds_cast<const float>(src + T::kDTiles * 4096 + 256 + lane * 4);
-      const float m_new = fmaxf(m_run, m_o);
-      // a group without a visible key has m = -inf, l = 0, O = 0
-      const float alpha = m_new > m_run ? __builtin_amdgcn_exp2f((m_run - m_new) * c) : 1.f;
-      const float beta = m_new > m_o ? __builtin_amdgcn_exp2f((m_o - m_new) * c) : 1.f;
-      l_run = l_run * alpha + l_o * beta;
-#pragma unroll
-      for (int i = 0; i < T::kDTiles; ++i)
+      for (int dt = 0; dt < T::kDTiles; ++dt)
 #pragma unroll
         for (int e4 = 0; e4 < 4; ++e4) {
-          const f32x4 v = *lds_cast<const f32x4>(src + (i * 4 + e4) * 1024 + lane * 16);
-#pragma unroll
-          for (int x = 0; x < 4; ++x) o[i][4 * e4 + x] = o[i][4 * e4 + x] * alpha + v[x] * beta;
+          // o[dt][4*e4 + x] is d = 32dt + 8*e4 + 4g + x
+          u32x2 w;
+          w[0] = pack_bf16(o[dt][4 * e4] * inv, o[dt][4 * e4 + 1] * inv);
+          w[1] = pack_bf16(o[dt][4 * e4 + 2] * inv, o[dt][4 * e4 + 3] * inv);
+          *(u32x2*)(dst + 32 * dt + 8 * e4 + 4 * g) = w;
         }
-      m_run = m_new;
-    }
-  }
-
-  // ---- epilogue: O / l, LSE ----------------------------------------------------------------
-  const float l_tot = l_run + __shfl_xor(l_run, 32);
-  const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
-  if (q_ok) {
-    __bf16* dst = op + (int64_t)q_row * a.o.sn;
-#pragma unroll
-    for (int dt = 0; dt < T::kDTiles; ++dt)
-#pragma unroll
-      for (int e4 = 0; e4 < 4; ++e4) {
-        // o[dt][4*e4 + x] is d = 32dt + 8*e4 + 4g + x
-        u32x2 w;
-        w[0] = pack_bf16(o[dt][4 * e4] * inv, o[dt][4 * e4 + 1] * inv);
-        w[1] = pack_bf16(o[dt][4 * e4 + 2] * inv, o[dt][4 * e4 + 3] * inv);
-        *(u32x2*)(dst + 32 * dt + 8 * e4 + 4 * g) = w;
-      }
-    if (a.lse && g == 0) {
-      const int64_t idx = ((int64_t)b * a.H + h) * a.N + q_row;
-      a.lse[idx] = l_tot > 0.f ? m_run * a.scale + __logf(l_tot) : -INFINITY;
+      if (a.lse && g == 0) store_lse(m_run, l_tot);
     }
   }
   if (kTrace && a.wg_trace != nullptr && threadIdx.x == 0 && part == 0) {  // one record per (head, query block)
@@ -450,6 +421,7 @@ int launch(const FwdArgs& a, hipStream_t stream) {
   const int64_t items = work_items(a.work, a.n_blocks);
   if (items == 0) return RADIAL_OK;
   const int groups = query_groups(D, BLK, a.work, items, true);
+  if (single_waves(BLK, a.work, items)) return launch_split<D, BLK, kExact, kTrace, D == 64 ? 8 : 4, BLK / 32>(a, stream);
   if (groups == 4) return launch_split<D, BLK, kExact, kTrace, 4, BLK / 64>(a, stream);
   if (groups == 2) return launch_split<D, BLK, kExact, kTrace, 2, 1>(a, stream);
   return launch_split<D, BLK, kExact, kTrace, 1, 1>(a, stream);

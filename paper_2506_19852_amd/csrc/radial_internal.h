@@ -182,6 +182,7 @@ inline int64_t work_grid(const WorkMap& w, int32_t n_blocks) {
 // other at the same barriers.  All figures are kernel times in microseconds, one group / the form named,
 // on lists of equal length L unless said otherwise.
 // `groups` = 4 at block 128 and 2 in the dK/dV kernel at block 128 mean half blocks: two workgroups per block, of 64 rows each.
+// (The figures of query_groups and key_groups up to 128 items are from before single_waves, which comes first.)
 
 // Two groups for 64-token blocks above kOneRound items: four workgroups of one group fit a compute unit, or two of two, so that
 // two groups take ceil(items / 512) / 2 walks where one takes ceil(items / 1024).
@@ -202,6 +203,16 @@ inline bool two_groups_pay_64(int D, const WorkMap& w, int64_t items) {
   }
   return items <= 1536 && w.mean >= 12;
 }
+
+// Groups of a single wave, 32 rows per workgroup (in the forward and dQ 4 groups at D 128 and 8 at D 64, in dK/dV 4 at D 64;
+// dK/dV at D 128 has LDS for two waves only and keeps the forms below): while all parts of all blocks still get a compute
+// unit of their own.  Such a launch spreads over 2 (block 64) or 4 (block 128) times the compute units of a workgroup per
+// block, and a wave that shares its stage buffers with nobody needs no barrier: in the forms above it waited there for 29 %
+// of its loop (64 items of D 64, block 64).  Best of the forms above / single waves, forward then backward, us: block 64, D 64, 64
+// items L 28 15.3 / 11.1; 99 items L 99 36.6 / 23.0; D 128, 22 items L 11 15.2 / 11.0; 128 items L 3 8.9 / 7.4 and 25.3 / 21.7,
+// L 1 7.5 / 7.7 and 17.3 / 18.4; block 128, D 128, 64 items L 1 7.8 / 8.3 and 24.7 / 24.1, L 2 10.0 / 8.6 and 26.8 / 23.5, L 8
+// 16.6 / 13.5 and 44.2 / 39.2; D 64 L 8 10.2 / 8.2 and 30.2 / 23.9.  (A forward call takes the host 7.4 us.)
+inline bool single_waves(int block, const WorkMap& w, int64_t items) { return items * (block / 32) <= kOneRound && w.longest >= 2; }
 
 // Block 128, up to 256 items.  Forward, D 128: half blocks at 64 items L 2 10.5 / 11.0, L 3 12.6 / 12.2, L 16 41.3 / 25.8, at
 // 256 items L 16 48.0 / 54.0; two groups at 256 items L 3 15.0 / 15.9, L 4 17.4 / 17.4, L 16 48.0 / 41.6, at 288 items
