@@ -99,7 +99,12 @@ __device__ __forceinline__ void mfma_results_settle(f32x16& acc0, f32x16& acc1) 
 }
 
 // kExact (all three kernels' callers): apply the token-level rule inside the listed blocks.
-template <int D, int BLK, bool kExact, int S, int R>
+// kTwoWaves: two waves per SIMD and the compiler's schedule instead of one wave and the hand-made one.  At head dimension
+// 64 a stage has 32 MFMAs (1024 cycles) to 178 plain vector instructions and 32 exponentials (1220 cycles), so the vector
+// unit is what bounds it and one wave cannot keep it busy: 2478 items of block 128 (10 x 17 000 tokens) 4.75 -> 4.1 ms, the
+// step 9.34 -> 8.21 ms.  196 to 214 registers; held to 168 for a third wave it spills 23 (block 128) to 45: 1-2 % slower, in
+// blocks of 64 25 %.  Head dimension 128 needs 422 registers and has one wave.
+template <int D, int BLK, bool kExact, int S, int R, bool kTwoWaves>
 __device__ __forceinline__ void dkdv_body(const BwdArgs& a) {
   using T = BwdTile<D, BLK, S, R>;
   using QT = SwzTile<D>;  // Q, dO tiles: rows of D elements
@@ -266,6 +271,66 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a) {
       }
     };
 
+    if constexpr (kTwoWaves) {
+#pragma unroll
+      for (int h2 = 0; h2 < 2; ++h2) {
+        f32x16 s, dp;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) s[e] = dp[e] = 0.f;
+#pragma unroll
+        for (int t = 0; t < T::kSteps; ++t) {
+          const bf16x8 qfrag = *lds_cast<const bf16x8>(sq + QT::piece(h2 * 32 + lq, 2 * t + g));
+          const bf16x8 gfrag = *lds_cast<const bf16x8>(sg + QT::piece(h2 * 32 + lq, 2 * t + g));
+          s = mfma32(qfrag, kf[t], s);
+          dp = mfma32(gfrag, vf[t], dp);
+          if (h2 == 0) {
+            constexpr int kCopies = 2 * T::kQLoadsPerWave + T::kStatLoads;
+#pragma unroll
+            for (int j = t * kCopies / T::kSteps; j < (t + 1) * kCopies / T::kSteps; ++j) spread_copy(j);
+          }
+        }
+        if (any_hidden) {
+#pragma unroll
+          for (int e = 0; e < 16; ++e)
+            if ((hidden >> (16 * h2 + e)) & 1u) s[e] = -INFINITY;
+        }
+        uint32_t pp[8], dsp[8];
+#pragma unroll
+        for (int e4 = 0; e4 < 4; ++e4) {  // element 4*e4 + x: query row 32*h2 + 8*e4 + 4g + x of the stage
+          const int ql = h2 * 32 + 8 * e4 + 4 * g;
+          const f32x4 lse4 = *lds_cast<const f32x4>(st + ql * 4) * kLog2e;
+          const f32x4 dl4 = *lds_cast<const f32x4>(st + (kStageQ + ql) * 4);
+          float pr[4], dr[4];
+#pragma unroll
+          for (int x = 0; x < 4; ++x) {
+            pr[x] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[4 * e4 + x], c, -lse4[x]));
+            dr[x] = pr[x] * (dp[4 * e4 + x] - dl4[x]);
+          }
+          pp[2 * e4] = pack_bf16(pr[0], pr[1]);
+          pp[2 * e4 + 1] = pack_bf16(pr[2], pr[3]);
+          dsp[2 * e4] = pack_bf16(dr[0], dr[1]);
+          dsp[2 * e4 + 1] = pack_bf16(dr[2], dr[3]);
+        }
+#pragma unroll
+        for (int t2 = 0; t2 < 2; ++t2) {
+          const bf16x8 pf = as_bf16x8(pp[4 * t2], pp[4 * t2 + 1], pp[4 * t2 + 2], pp[4 * t2 + 3]);
+          const bf16x8 dsf = as_bf16x8(dsp[4 * t2], dsp[4 * t2 + 1], dsp[4 * t2 + 2], dsp[4 * t2 + 3]);
+          const int r0 = h2 * 32 + 16 * t2 + 4 * g + (i16 >> 2);
+#pragma unroll
+          for (int dt = 0; dt < T::kDTiles; ++dt) {
+            const int col = 32 * dt + 16 * half16 + 4 * (i16 & 3);
+            const u32x2 g0 = lds_read_tr(sg + QT::elem(r0, col)), g1 = lds_read_tr(sg + QT::elem(r0 + 8, col));
+            const u32x2 q0v = lds_read_tr(sq + QT::elem(r0, col)), q1v = lds_read_tr(sq + QT::elem(r0 + 8, col));
+            dv[dt] = mfma32(as_bf16x8(g0[0], g0[1], g1[0], g1[1]), pf, dv[dt]);
+            dk[dt] = mfma32(as_bf16x8(q0v[0], q0v[1], q1v[0], q1v[1]), dsf, dk[dt]);
+          }
+        }
+      }
+      q0 = q0_next;
+      q_at = q_at_next;
+      continue;
+    }
+
     // The stage is two 32-row halves (h = 0, 1).  One wave per SIMD has nobody to hide its LDS
     // and VALU latencies behind, so the four products are software-pipelined by hand:
     //   A: S, dP of half 0                    B: S, dP of half 1   | P, dS of half 0
@@ -413,15 +478,20 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a) {
 
 template <int D, int BLK, bool kExact>
 __global__ void __launch_bounds__(2 * BLK, 1) radial_bwd_dkdv_kernel(const BwdArgs a) {
-  dkdv_body<D, BLK, kExact, 1, 1>(a);
+  dkdv_body<D, BLK, kExact, 1, 1, false>(a);
 }
 template <int D, int BLK, bool kExact, int S, int R>
 __global__ void __launch_bounds__(2 * BLK / R * S, 1) radial_bwd_dkdv_split_kernel(const BwdArgs a) {
-  dkdv_body<D, BLK, kExact, S, R>(a);
+  dkdv_body<D, BLK, kExact, S, R, false>(a);
 }
 template <int D, int BLK, bool kExact, int S, int R>
 __global__ void __launch_bounds__(2 * BLK / R * S, 1) radial_bwd_dkdv_single_kernel(const BwdArgs a) {  // one wave per group
-  dkdv_body<D, BLK, kExact, S, R>(a);
+  dkdv_body<D, BLK, kExact, S, R, false>(a);
+}
+
+template <int D, int BLK, bool kExact, int S, int R>
+__global__ void __launch_bounds__(2 * BLK / R * S, 2) radial_bwd_dkdv_two_kernel(const BwdArgs a) {  // two waves per SIMD
+  dkdv_body<D, BLK, kExact, S, R, true>(a);
 }
 
 template <int D, int BLK, int S, int R>
@@ -678,11 +748,12 @@ __global__ void __launch_bounds__(2 * BLK / R * S, 2) radial_bwd_dq_kernel(const
   }
 }
 
-template <int D, int BLK, bool kExact, int S, int R>
+template <int D, int BLK, bool kExact, int S, int R, bool kTwoWaves = false>
 int launch_dkdv(BwdArgs a, hipStream_t stream) {
   using T = BwdTile<D, BLK, S, R>;
   void (*kernel)(BwdArgs);
-  if constexpr (S == 1) kernel = radial_bwd_dkdv_kernel<D, BLK, kExact>;
+  if constexpr (kTwoWaves) kernel = radial_bwd_dkdv_two_kernel<D, BLK, kExact, S, R>;
+  else if constexpr (S == 1) kernel = radial_bwd_dkdv_kernel<D, BLK, kExact>;
   else if constexpr (T::kWaves > 1) kernel = radial_bwd_dkdv_split_kernel<D, BLK, kExact, S, R>;
   else kernel = radial_bwd_dkdv_single_kernel<D, BLK, kExact, S, R>;
   static DeviceOnce configured;
@@ -714,9 +785,12 @@ int launch(const BwdArgs& a, hipStream_t stream) {
     return fail(RADIAL_ESHAPE, "problem too large for one launch");
   bwd_prepare_kernel<D><<<dim3((unsigned)prep_grid), dim3(256), 0, stream>>>(a);
   const int64_t items = work_items(a.work, a.n_blocks);
-  const int kv = key_groups(BLK, a.work_t, items), q = query_groups(D, BLK, a.work, items, false);
+  const int two = key_groups_two_waves(BLK, a.work_t, items), kv = key_groups(BLK, a.work_t, items), q = query_groups(D, BLK, a.work, items, false);
   int rc;
   if (D == 64 && single_waves(BLK, a.work_t, items)) rc = launch_dkdv<64, BLK, kExact, 4, BLK / 32>(a, stream);
+  else if (D == 64 && two == 4) rc = launch_dkdv<64, BLK, kExact, 4, BLK / 64, true>(a, stream);
+  else if (D == 64 && two == 2) rc = launch_dkdv<64, BLK, kExact, 2, 1, true>(a, stream);
+  else if (D == 64 && two == 1) rc = launch_dkdv<64, BLK, kExact, 1, 1, true>(a, stream);
   else rc = kv == 2 ? launch_dkdv<D, BLK, kExact, 2, BLK / 64>(a, stream) : launch_dkdv<D, BLK, kExact, 1, 1>(a, stream);
   if (rc) return rc;
   if (single_waves(BLK, a.work, items)) rc = launch_dq<D, BLK, kExact, D == 64 ? 8 : 4, BLK / 32>(a, stream);

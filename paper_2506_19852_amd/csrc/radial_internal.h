@@ -246,6 +246,25 @@ inline int key_groups(int block, const WorkMap& w, int64_t items) {
   return items <= 1200 && w.mean >= (items <= 768 ? 24 : 32) && ((items - 1) / 256 % 2 == 0 || w.longest >= 2LL * w.mean) ? 2 : 1;
 }
 
+// dK/dV at D 64 with two waves per SIMD (see dkdv_body): groups of waves; 0: the forms of key_groups with one wave.
+// Whole backward pass, us, key_groups / one / two / four groups (four: half blocks at block 128).
+//   block 128: 128 items L 2 19.2 / 22.1 / 21.7 / 19.5, L 4 22.5 / 28.0 / 26.2 / 22.1, L 16 49.7 / 69.1 / 57.8 / 45.6; 256 items L 2
+//   24.7 / 25.1 / 24.6 / 28.5, L 4 33.5 / 33.5 / 32.1 / 35.3, L 16 83.8 / 84.2 / 76.0 / 80.0; 384 items L 1 30.3 / 26.5 / 31.8, L 32 276 /
+//   229 / 236; radial lists: 522 items (mean 57) 660 / 595 / 579, 714 (112) 1417 / 1305 / 1275, 996 (83) 1434 / 1284 / 1275, 2478 (165)
+//   6914 / 6272 / 6255, 7414 (250) 31.7 / 28.0 / 28.5 ms.
+//   block 64: 192 items L 6 19.9 / 22.9 / 20.1 / 20.4, L 16 30.4 / 40.4 / 30.7 / 29.0, L 32 47.2 / 67.7 / 47.1 / 42.7; 384 items L 2
+//   19.0 / 19.2 / 19.1 / 23.7, L 4 23.3 / 24.5 / 22.6 / 27.6, L 32 83.7 / 92.4 / 70.4 / 76.6; 768 items L 8 53.4 / 43.4 / 45.2, L 32 132 / 122 /
+//   119; 3200 items L 16 296 / 251 / 261, L 32 528 / 454 / 453; radial lists: 2136 items (172) 1800 / 1620 / 1563.
+inline int key_groups_two_waves(int block, const WorkMap& w, int64_t items) {
+  if (block == 128) {
+    if (items <= kOneRound) return w.longest < 4 ? 0 : items <= 128 ? 4 : 2;
+    return items > 512 && items <= 1024 && w.mean >= 48 ? 2 : 1;
+  }
+  if (items <= kOneRound) return w.longest >= 8 ? 4 : 0;
+  if (items <= 512) return w.longest >= 4 ? 2 : 0;
+  return w.mean >= (items <= 1536 ? 16 : 32) ? 2 : 1;
+}
+
 // 8-bit scores: three groups of 4 waves (12 waves are what a compute unit holds of this kernel) while every item can
 // have a compute unit of its own.  64 items: L 4 16.9 / 17.7, L 6 22.3 / 19.8; 105 items L 5 (with the quantisation) 40.4 / 37.5; 256 items: L 6 24.0 / 22.7, L 32 93.5 / 69.0;
 // 288 items (with the quantisation) 127 / 133.
