@@ -18,18 +18,8 @@
 namespace radial {
 namespace {
 
-constexpr int kStageKeys = 64;
 constexpr int D = 128, BLK = 128;
-constexpr int kWaves = BLK / 32;                // per group of waves (see the kernel)
-constexpr int kSubs = BLK / kStageKeys;
-constexpr int kK8Bytes = kStageKeys * D;        // one K stage tile, 1 byte per element
-constexpr int kVBytes = kStageKeys * D * 2;     // one V stage tile, bf16
-constexpr int kBufBytes = kK8Bytes + kVBytes;
-constexpr int kKLoads = kK8Bytes / 1024 / kWaves;   // 1 KiB copies per wave: 2
-constexpr int kVLoads = kVBytes / 1024 / kWaves;    // 4
-constexpr int kKeyTiles = kStageKeys / 32;
 constexpr int kDTiles = D / 32;
-constexpr int kMergeBytes = kDTiles * 4096 + 512;   // one wave's O, m and l in LDS
 using VT = SwzTile<D>;
 
 typedef int i32x8 __attribute__((ext_vector_type(8)));
@@ -50,8 +40,62 @@ __device__ __forceinline__ void k8_source_of(int lin, int& r, int& p) {
   p = src & 7;
 }
 
-// One workgroup per (batch*head, block of tokens): amax, scale, codes.
-__global__ void __launch_bounds__(256) quantize_fp8_kernel(TensorArg x, uint8_t* codes, float* scales, int32_t H, int32_t N,
+// One workgroup per (batch*head, block of tokens): amax, scale, codes.  Every thread loads its pieces of the block at once
+// and keeps them for the codes.  As a loop over pieces that read the block twice and waited for each, a launch of 16 to 82 blocks
+// took 7.1 to 8.8 us; quantising Q and K, 6 to 126 blocks, now takes 5 to 7 us less.
+template <int Dh, int kBlock>
+__global__ void __launch_bounds__(512) quantize_fp8_kernel(TensorArg x, uint8_t* codes, float* scales, int32_t H, int32_t N, int32_t nb) {
+  constexpr int kPerRow = Dh / 8;                      // 16-byte pieces per row
+  constexpr int kPieces = kBlock * kPerRow / 512;      // per thread
+  static_assert(kPieces * 512 == kBlock * kPerRow, "whole pieces per thread");
+  __shared__ float part[8];
+  const int32_t bh = blockIdx.x / nb, blk = blockIdx.x % nb;
+  const int32_t b = bh / H, h = bh % H;
+  const __bf16* src = (const __bf16*)x.ptr + (int64_t)b * x.sb + (int64_t)h * x.sh;
+  const int32_t row0 = blk * kBlock;
+  const int32_t rows = N - row0 < kBlock ? N - row0 : kBlock;
+  const int32_t r0 = threadIdx.x / kPerRow, p = threadIdx.x % kPerRow;
+  u32x4 raw[kPieces];
+#pragma unroll
+  for (int i = 0; i < kPieces; ++i) {
+    const int32_t r = r0 + i * (512 / kPerRow);
+    raw[i] = r < rows ? *(const u32x4*)(src + (int64_t)(row0 + r) * x.sn + 8 * p) : u32x4{0u, 0u, 0u, 0u};
+  }
+  float amax = 0.f;
+#pragma unroll
+  for (int i = 0; i < kPieces; ++i) {
+    const bf16x8 v = __builtin_bit_cast(bf16x8, raw[i]);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) amax = fmaxf(amax, fabsf((float)v[e]));
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) amax = fmaxf(amax, __shfl_xor(amax, off));
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = amax;
+  __syncthreads();
+  amax = part[0];
+#pragma unroll
+  for (int i = 1; i < 8; ++i) amax = fmaxf(amax, part[i]);
+  const float scale = amax > 0.f ? amax / 448.f : 1.f;
+  if (threadIdx.x == 0) scales[(int64_t)bh * nb + blk] = scale;
+  uint8_t* dst = codes + ((int64_t)bh * N + row0) * Dh;
+#pragma unroll
+  for (int i = 0; i < kPieces; ++i) {
+    const int32_t r = r0 + i * (512 / kPerRow);
+    const bf16x8 v = __builtin_bit_cast(bf16x8, raw[i]);
+    float y[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) y[e] = fminf(fmaxf((float)v[e] / scale, -448.f), 448.f);
+    int lo = 0, hi = 0;  // v_cvt_pk_fp8_f32 rounds to nearest even; beyond the clamp it would give NaN
+    lo = __builtin_amdgcn_cvt_pk_fp8_f32(y[0], y[1], lo, false);
+    lo = __builtin_amdgcn_cvt_pk_fp8_f32(y[2], y[3], lo, true);
+    hi = __builtin_amdgcn_cvt_pk_fp8_f32(y[4], y[5], hi, false);
+    hi = __builtin_amdgcn_cvt_pk_fp8_f32(y[6], y[7], hi, true);
+    if (r < rows) *(u32x2*)(dst + (int64_t)r * Dh + 8 * p) = u32x2{(uint32_t)lo, (uint32_t)hi};
+  }
+}
+
+// The same for any row length and block.
+__global__ void __launch_bounds__(256) quantize_fp8_any_kernel(TensorArg x, uint8_t* codes, float* scales, int32_t H, int32_t N,
                                                            int32_t Dh, int32_t block, int32_t nb) {
   __shared__ float part[4];
   const int32_t bh = blockIdx.x / nb, blk = blockIdx.x % nb;
@@ -91,10 +135,29 @@ __global__ void __launch_bounds__(256) quantize_fp8_kernel(TensorArg x, uint8_t*
   }
 }
 
-// S groups of 4 waves take the entries of the list in turn, as in the bf16 kernel.
-template <int S>
-__global__ void __launch_bounds__(64 * kWaves * S, 3) radial_fwd_fp8_kernel(const Fp8FwdArgs a) {
-  static_assert((S - 1) * kWaves * kMergeBytes <= S * 2 * kBufBytes || S == 1, "the merge reuses the stage buffers");
+// S groups of waves share the query rows and take the entries of the list in turn; R workgroups per query block, as in the
+// bf16 kernel.  Parts of a block walk stages of 32 keys (24 KiB per group instead of 48).
+template <int S, int R>
+struct Fp8Tile {
+  static constexpr int kRows = BLK / R;
+  static constexpr int kWaves = kRows / 32;                  // per group
+  static constexpr int kStageKeys = R == 1 ? 64 : 32;
+  static constexpr int kSubs = BLK / kStageKeys;
+  static constexpr int kK8Bytes = kStageKeys * D;            // one K stage tile, 1 byte per element
+  static constexpr int kVBytes = kStageKeys * D * 2;         // one V stage tile, bf16
+  static constexpr int kBufBytes = kK8Bytes + kVBytes;
+  static constexpr int kKLoads = kK8Bytes / 1024 / kWaves;   // 1 KiB copies per wave
+  static constexpr int kVLoads = kVBytes / 1024 / kWaves;
+  static constexpr int kKeyTiles = kStageKeys / 32;
+  using Join = Merge<S, kWaves, kDTiles>;
+  static constexpr int kLdsBytes = S * 2 * kBufBytes > Join::kLdsBytes ? S * 2 * kBufBytes : Join::kLdsBytes;
+};
+
+template <int S, int R>
+__device__ __forceinline__ void fp8_body(const Fp8FwdArgs& a) {
+  using T = Fp8Tile<S, R>;
+  constexpr int kWaves = T::kWaves, kStageKeys = T::kStageKeys, kSubs = T::kSubs, kK8Bytes = T::kK8Bytes, kBufBytes = T::kBufBytes;
+  constexpr int kKLoads = T::kKLoads, kVLoads = T::kVLoads, kKeyTiles = T::kKeyTiles;
   // [group][stage buffer][K8 tile, V tile]; one group's are a static array, as in the bf16 kernel
   __shared__ __attribute__((aligned(1024))) char lds_one[S == 1 ? 2 * kBufBytes : 16];
   extern __shared__ __attribute__((aligned(1024))) char lds_all[];
@@ -113,6 +176,8 @@ __global__ void __launch_bounds__(64 * kWaves * S, 3) radial_fwd_fp8_kernel(cons
 
   int32_t bh, qb;
   if (!work_item(a.work, bh, qb)) return;
+  const int32_t part = R == 1 ? 0 : bh % R;  // with R > 1 the work map counts R heads for each
+  if (R > 1) bh /= R;
   const int32_t b = bh / a.H, h = bh % a.H;
 
   const uint8_t* qp = a.q8 + (int64_t)bh * a.N * D;
@@ -126,7 +191,7 @@ __global__ void __launch_bounds__(64 * kWaves * S, 3) radial_fwd_fp8_kernel(cons
   const int32_t n_row = __builtin_amdgcn_readfirstlane(a.row_ptr[qb + 1]) - list_lo;
   const int32_t n_list = S == 1 ? n_row : (n_row - group + S - 1) / S;  // entries of this group
   const int32_t n_stage = n_list * kSubs;
-  const int32_t q_row = qb * BLK + wave * 32 + lq;
+  const int32_t q_row = qb * BLK + part * T::kRows + wave * 32 + lq;
   const bool q_ok = q_row < a.N;
 
   // Q8^T fragments: for the 64-byte slice t of d this lane holds bytes 64t + 32g .. +31 of its row.
@@ -228,8 +293,12 @@ __global__ void __launch_bounds__(64 * kWaves * S, 3) radial_fwd_fp8_kernel(cons
       f_next = q_scale * __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, csc), e1 & 63));
     }
 
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's copies of stage u have landed
-    __syncthreads();                                  // ... and everyone's; stage u-1 is fully consumed
+    if (kWaves == 1) {  // nobody else reads or writes this group's stage buffers
+      asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    } else {
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's copies of stage u have landed
+      __syncthreads();                                  // ... and everyone's; stage u-1 is fully consumed
+    }
 
     // Copies of stage u+1: K pieces between the MFMAs of the first product, V pieces between
     // those of the second; a ragged next stage is issued in one go.
@@ -258,7 +327,10 @@ __global__ void __launch_bounds__(64 * kWaves * S, 3) radial_fwd_fp8_kernel(cons
         const i32x8 kf = {(int)k0[0], (int)k0[1], (int)k0[2], (int)k0[3], (int)k1[0], (int)k1[1], (int)k1[2], (int)k1[3]};
         // formats 0 / 0 = E4M3 for both operands; scale exponents 127 = 2^0
         s[kt] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(kf, qf[t], s[kt], 0, 0, 0, 0x7F7F7F7F, 0, 0x7F7F7F7F);
-        if (t == 1) copy16_to_lds_sv_masked(kbase_next, koff[kt], kdst_next + kt * 1024, lanes);
+        const int i = kt * 2 + t;
+#pragma unroll
+        for (int j = i * kKLoads / (2 * kKeyTiles); j < (i + 1) * kKLoads / (2 * kKeyTiles); ++j)
+          copy16_to_lds_sv_masked(kbase_next, koff[j], kdst_next + j * 1024, lanes);
       }
     }
 
@@ -317,9 +389,11 @@ __global__ void __launch_bounds__(64 * kWaves * S, 3) radial_fwd_fp8_kernel(cons
           const u32x2 a0 = lds_read_tr(lds_v + VT::elem(vrow, dcol)), a1 = lds_read_tr(lds_v + VT::elem(vrow + 8, dcol));
           const u32x4 vraw = {a0[0], a0[1], a1[0], a1[1]};
           o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, vraw), pf, o[dt], 0, 0, 0);
-          if (dt == 0) {
-            const int j = kt * 2 + t;  // one V piece per four MFMAs
-            copy16_to_lds_sv_masked(vbase_next, voff[j], vdst_next + j * 1024, lanes);
+          if (dt % 2 == 0) {  // the V pieces: in stages of 64 keys one per four MFMAs
+            const int i = (kt * 2 + t) * 2 + dt / 2, n = 4 * kKeyTiles;
+#pragma unroll
+            for (int j = (i * kVLoads + n - 1) / n; j < ((i + 1) * kVLoads + n - 1) / n; ++j)
+              copy16_to_lds_sv_masked(vbase_next, voff[j], vdst_next + j * 1024, lanes);
           }
         }
       }
@@ -327,52 +401,25 @@ __global__ void __launch_bounds__(64 * kWaves * S, 3) radial_fwd_fp8_kernel(cons
     f_stage = f_next;
   }
 
-  // ---- merge of the groups: group 0 gathers (m, l, O) of the others through LDS ---------------
-  // (float32 throughout; 132 KiB per workgroup, two groups of four waves)
-  if (S > 1) {
-    // a stage is a barrier: as many as group 0, which has most stages
-    for (int32_t u = n_stage; u < (n_row + S - 1) / S * kSubs; ++u) __syncthreads();
-    __syncthreads();  // the last stages are consumed; their buffers are reused
-    if (group > 0) {
-      char* dst = lds_all + ((group - 1) * kWaves + wave) * kMergeBytes + lane * 16;
-#pragma unroll
-      for (int i = 0; i < kDTiles; ++i)
-#pragma unroll
-        for (int e4 = 0; e4 < 4; ++e4)
-          *lds_cast<f32x4>(dst + (i * 4 + e4) * 1024) = f32x4{o[i][4 * e4], o[i][4 * e4 + 1], o[i][4 * e4 + 2], o[i][4 * e4 + 3]};
-      char* ml = lds_all + ((group - 1) * kWaves + wave) * kMergeBytes + kDTiles * 4096 + lane * 4;
-      *lds_cast<float>(ml) = m_run;
-      *lds_cast<float>(ml + 256) = l_run;
-    }
-    __syncthreads();
-    if (group > 0) return;
-#pragma unroll 1
-    for (int other = 1; other < S; ++other) {
-      const char* src = lds_all + ((other - 1) * kWaves + wave) * kMergeBytes;
-      const float m_o = *lds_cast<const float>(src + kDTiles * 4096 + lane * 4);
-      const float l_o = *lds_cast<const float>(src + kDTiles * 4096 + 256 + lane * 4);
-      const float m_new = fmaxf(m_run, m_o);
-      // a group without a visible key has m = -inf, l = 0, O = 0
-      const float alpha = m_new > m_run ? __builtin_amdgcn_exp2f((m_run - m_new) * c) : 1.f;
-      const float beta = m_new > m_o ? __builtin_amdgcn_exp2f((m_o - m_new) * c) : 1.f;
-      l_run = l_run * alpha + l_o * beta;
-#pragma unroll
-      for (int i = 0; i < kDTiles; ++i)
-#pragma unroll
-        for (int e4 = 0; e4 < 4; ++e4) {
-          const f32x4 v = *lds_cast<const f32x4>(src + (i * 4 + e4) * 1024 + lane * 16);
-#pragma unroll
-          for (int x = 0; x < 4; ++x) o[i][4 * e4 + x] = o[i][4 * e4 + x] * alpha + v[x] * beta;
-        }
-      m_run = m_new;
-    }
+  __bf16* const dst = op + (int64_t)q_row * a.o.sn;
+  const auto store_lse = [&](float m, float l) __attribute__((always_inline)) {
+    a.lse[(int64_t)bh * a.N + q_row] = l > 0.f ? m * a.scale + __logf(l) : -INFINITY;
+  };
+  if (S > 1) {  // several groups: merge and store
+    if (kWaves > 1)  // a stage is a barrier: as many as group 0, which has most stages
+      for (int32_t u = n_stage; u < (n_row + S - 1) / S * kSubs; ++u) __syncthreads();
+    float m = m_run, l = l_run;
+    T::Join::softmax(o, m, l, c, lds_all, group, wave, lane, [&](int p, f32x4 v) __attribute__((always_inline)) {
+      if (q_ok) *(u32x2*)(dst + 8 * p + 4 * g) = u32x2{pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
+    });
+    if (q_ok && a.lse && g == 0 && group == 0) store_lse(m, l);
+    return;
   }
 
   // ---- epilogue: O / l, LSE ----------------------------------------------------------------
   const float l_tot = l_run + __shfl_xor(l_run, 32);
   const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
   if (q_ok) {
-    __bf16* dst = op + (int64_t)q_row * a.o.sn;
 #pragma unroll
     for (int dt = 0; dt < kDTiles; ++dt)
 #pragma unroll
@@ -382,8 +429,17 @@ __global__ void __launch_bounds__(64 * kWaves * S, 3) radial_fwd_fp8_kernel(cons
         w[1] = pack_bf16(o[dt][4 * e4 + 2] * inv, o[dt][4 * e4 + 3] * inv);
         *(u32x2*)(dst + 32 * dt + 8 * e4 + 4 * g) = w;
       }
-    if (a.lse && g == 0) a.lse[(int64_t)bh * a.N + q_row] = l_tot > 0.f ? m_run * a.scale + __logf(l_tot) : -INFINITY;
+    if (a.lse && g == 0) store_lse(m_run, l_tot);
   }
+}
+
+template <int S>
+__global__ void __launch_bounds__(2 * BLK * S, 3) radial_fwd_fp8_kernel(const Fp8FwdArgs a) {
+  fp8_body<S, 1>(a);
+}
+template <int S, int R>
+__global__ void __launch_bounds__(2 * BLK / R * S, (BLK / R / 32 * S + 3) / 4) radial_fwd_fp8_part_kernel(const Fp8FwdArgs a) {
+  fp8_body<S, R>(a);
 }
 
 }  // namespace
@@ -393,19 +449,26 @@ int launch_quantize_fp8(int32_t B, int32_t H, int32_t N, int32_t Dh, const Tenso
   const int32_t nb = (N + block - 1) / block;
   const int64_t grid = (int64_t)B * H * nb;
   if (grid > 0x7fffffffLL) return fail(RADIAL_ESHAPE, "B*H*n_blocks is too large for one launch");
-  quantize_fp8_kernel<<<dim3((unsigned)grid), dim3(256), 0, stream>>>(x, codes, scales, H, N, Dh, block, nb);
+  if (Dh == 128 && block == 128)  // what the forward below reads
+    quantize_fp8_kernel<128, 128><<<dim3((unsigned)grid), dim3(512), 0, stream>>>(x, codes, scales, H, N, nb);
+  else
+    quantize_fp8_any_kernel<<<dim3((unsigned)grid), dim3(256), 0, stream>>>(x, codes, scales, H, N, Dh, block, nb);
   RADIAL_HIP_TRY(hipGetLastError());
   return RADIAL_OK;
 }
 
-template <int S>
-static int launch_split(const Fp8FwdArgs& a, hipStream_t stream) {
-  constexpr int kLdsBytes = S * 2 * kBufBytes;
-  if (S > 1 && kLdsBytes > 65536) {
+template <int S, int R>
+static int launch_split(Fp8FwdArgs a, hipStream_t stream) {
+  using T = Fp8Tile<S, R>;
+  void (*kernel)(Fp8FwdArgs);
+  if constexpr (R == 1) kernel = radial_fwd_fp8_kernel<S>;
+  else kernel = radial_fwd_fp8_part_kernel<S, R>;
+  if (S > 1 && T::kLdsBytes > 65536) {
     static DeviceOnce configured;
-    if (int rc = allow_dynamic_lds(configured, (const void*)radial_fwd_fp8_kernel<S>, kLdsBytes)) return rc;
+    if (int rc = allow_dynamic_lds(configured, (const void*)kernel, T::kLdsBytes)) return rc;
   }
-  radial_fwd_fp8_kernel<S><<<dim3((unsigned)work_grid(a.work, a.n_blocks)), dim3(64 * kWaves * S), S == 1 ? 0 : kLdsBytes, stream>>>(a);
+  a.work.ordered *= R;  // R > 1 only up to kOneRound items, where all heads are taken by list length
+  kernel<<<dim3((unsigned)work_grid(a.work, a.n_blocks)), dim3(64 * T::kWaves * S), S == 1 ? 0 : T::kLdsBytes, stream>>>(a);
   RADIAL_HIP_TRY(hipGetLastError());
   return RADIAL_OK;
 }
@@ -414,7 +477,10 @@ int launch_fwd_fp8(const Fp8FwdArgs& a, hipStream_t stream) {
   if (work_grid_bound(a.work) > 0x7fffffffLL) return fail(RADIAL_ESHAPE, "B*H*n_blocks is too large for one launch");
   const int64_t items = work_items(a.work, a.n_blocks);
   if (items == 0) return RADIAL_OK;
-  return fp8_groups(a.work, items) == 3 ? launch_split<3>(a, stream) : launch_split<1>(a, stream);
+  const int parts = fp8_parts(a.work, items);
+  if (parts == 4) return launch_split<4, 4>(a, stream);
+  if (parts == 2) return launch_split<4, 2>(a, stream);
+  return fp8_groups(a.work, items) == 3 ? launch_split<3, 1>(a, stream) : launch_split<1, 1>(a, stream);
 }
 
 }  // namespace radial

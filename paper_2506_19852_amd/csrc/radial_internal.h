@@ -270,6 +270,12 @@ inline int key_groups_two_waves(int block, const WorkMap& w, int64_t items) {
 // 288 items (with the quantisation) 127 / 133.
 inline int fp8_groups(const WorkMap& w, int64_t items) { return items <= kOneRound && w.longest >= 5 ? 3 : 1; }
 
+// Workgroups per query block, of four groups each that walk stages of 32 keys: 4 (groups of one wave) or 2 (of two waves) while
+// every part has a compute unit of its own.  Best of the forms above / 4 parts / 2 parts, us, without the quantisation: 64 items L 1
+// 8.5 / 9.4 / 9.5, L 2 10.8 / 9.3 / 9.3, L 4 16.2 / 9.6 / 10.6, L 8 21.8 / 14.2 / 15.4, L 16 34.8 / 23.4 / 24.7; 128 items L 2 11.3 / 17.2 /
+// 9.8, L 4 16.7 / 17.5 / 11.4, L 16 35.8 / 45.6 / 26.0 (six groups in 2 parts: 25.1, L 8 17.6 against 16.6); 192 items L 4 16.9 / 25.0 / 20.2.
+inline int fp8_parts(const WorkMap& w, int64_t items) { return w.longest < 2 || items > 128 ? 1 : items <= 64 ? 4 : 2; }
+
 struct TensorArg {
   const void* ptr;
   int64_t sb, sh, sn;  // element strides
