@@ -122,7 +122,7 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a) {
   const int half16 = (lane >> 4) & 1;
 
   int32_t bh, kb;
-  if (!work_item(a.work_t, bh, kb)) return;
+  if (!work_item(a.work_t, blockIdx.x, bh, kb)) return;
   const int32_t part = R == 1 ? 0 : bh % R;  // with R > 1 the work map counts R heads for each
   if (R > 1) bh /= R;
   const int32_t b = bh / a.H, h = bh % a.H;
@@ -536,7 +536,7 @@ __global__ void __launch_bounds__(2 * BLK / R * S, 2) radial_bwd_dq_kernel(const
   const int half16 = (lane >> 4) & 1;
 
   int32_t bh, qb;
-  if (!work_item(a.work, bh, qb)) return;
+  if (!work_item(a.work, blockIdx.x, bh, qb)) return;
   const int32_t part = R == 1 ? 0 : bh % R;
   if (R > 1) bh /= R;
   const int32_t b = bh / a.H, h = bh % a.H;

@@ -175,7 +175,7 @@ __device__ __forceinline__ void fp8_body(const Fp8FwdArgs& a) {
   const int g = lane >> 5;
 
   int32_t bh, qb;
-  if (!work_item(a.work, bh, qb)) return;
+  if (!work_item(a.work, blockIdx.x, bh, qb)) return;
   const int32_t part = R == 1 ? 0 : bh % R;  // with R > 1 the work map counts R heads for each
   if (R > 1) bh /= R;
   const int32_t b = bh / a.H, h = bh % a.H;

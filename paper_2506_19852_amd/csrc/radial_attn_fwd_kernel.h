@@ -39,7 +39,7 @@ struct Tile {
   static constexpr int kRows = BLK / R;
   // Keys per pipeline stage.  Head dimension 128 with 64 rows walks half-size stages: two
   // 64-key stage buffers (64 KiB) per 2 waves would leave a compute unit with 4 waves.
-  static constexpr int kStageKeys = (D == 128 && kRows == 64) || kRows == 32 ? 32 : 64;
+  static constexpr int kStageKeys = (D == 128 && kRows == 64) || kRows == 32 || (S == 2 && R == 2) ? 32 : 64;
   static constexpr int kWaves = kRows / 32;        // one wave per 32 query rows
   static constexpr int kThreads = 64 * kWaves * S;
   static constexpr int kPiecesPerRow = D / 8;      // 16-byte pieces per K/V row
@@ -53,7 +53,7 @@ struct Tile {
   // a wave's copies of the next stage, and the MFMAs of the first product that they are spread over
   static constexpr int kCopies = 2 * kLoadsPerWave, kCopyOver = kKeyTiles * kSteps;
   static constexpr int kGroupBytes = 4 * kStageBytes;               // [stage buffer][K, V]
-  using Join = Merge<S, kWaves, kDTiles>;
+  using Join = Merge<S, kWaves, kDTiles, S == 2 && R == 2 ? S * kGroupBytes : 160 * 1024>;  // (2, 2): beside whole blocks in one kernel
   static constexpr int kLdsBytes = S * kGroupBytes > Join::kLdsBytes ? S * kGroupBytes : Join::kLdsBytes;
 };
 
@@ -72,20 +72,31 @@ __device__ __forceinline__ int piece_offset(int r, int p) {
   return (line << 8) + ((slot ^ swizzle_key<D, kIsV>(line)) << 4);
 }
 
+// The static stage buffers of a kernel (one array per Key, named where it is used and not through a pointer: its address is
+// then a constant that the reads of the stage loop carry in their offsets).  As dynamic LDS, D 128, block 128: 225 registers
+// instead of 205 and 6 waits more in two stages (token rule: 50 vector instructions more); 40 x 32 760 all-ones list 19.34 /
+// 19.25 ms, 24 x 118 800 74.7 / 74.3, 40 x 32 760 token rule 14.51 / 14.16.
+template <class Key, int kBytes>
+__device__ __forceinline__ char* static_lds() {
+  __shared__ __attribute__((aligned(1024))) char lds[kBytes];
+  return lds;
+}
+template <int D, int BLK, bool kExact, bool kTrace, bool kHalves>
+struct FwdKey {};
+
+// One block of query rows, or part `part` of the R of one.
 // kExact: apply the token-level rule of the radial mask inside the listed blocks.
 // kTrace: also record begin, end and hardware ids of the workgroup (diagnostics build of the kernel;
 // the library's radial_attn_fwd launches kTrace = false, which carries none of it).
-template <int D, int BLK, bool kExact, bool kTrace, int S, int R>
-// Two waves per SIMD: two 4-wave workgroups per compute unit (BLK = 128) or four 2-wave ones (BLK = 64)
-// with S = R = 1.
-__global__ void __launch_bounds__(2 * BLK / R * S, 2) radial_fwd_kernel(const FwdArgs a) {
+// kHalves: in the kernel that takes its last blocks in halves.
+template <int D, int BLK, bool kExact, bool kTrace, int S, int R, bool kHalves>
+__device__ __forceinline__ void fwd_body(const FwdArgs& a, int32_t bh, int32_t qb, int32_t part, int64_t record) {
   using T = Tile<D, BLK, S, R>;
-  // [group][stage buffer][K, V][T::kStageKeys x D bf16].  One group's are a static array, named where it is used
-  // (lds_at) and not through a pointer: its address is then a constant that the reads of the stage loop carry in their
-  // offsets.  As dynamic LDS, D 128, block 128: 225 registers instead of 205 and 6 waits more in two stages (token
-  // rule: 50 vector instructions more); 40 x 32 760 all-ones list 19.34 / 19.25 ms, 24 x 118 800 74.7 / 74.3,
-  // 40 x 32 760 token rule 14.51 / 14.16.
-  __shared__ __attribute__((aligned(1024))) char lds_one[S == 1 ? T::kLdsBytes : 16];
+  using Key = FwdKey<D, BLK, kExact, kTrace, kHalves>;
+  constexpr bool kStatic = S == 1 || kHalves;
+  constexpr int kStaticBytes = Tile<D, BLK, 1, 1>::kLdsBytes;
+  static_assert(!kHalves || T::kLdsBytes <= kStaticBytes, "halves use the stage buffers of whole blocks");
+  // [group][stage buffer][K, V][T::kStageKeys x D bf16]
   extern __shared__ __attribute__((aligned(1024))) char lds_all[];
 
   const int lane = threadIdx.x & 63;
@@ -96,7 +107,8 @@ __global__ void __launch_bounds__(2 * BLK / R * S, 2) radial_fwd_kernel(const Fw
   // against 57.9; two groups at 240 items 112.2 against 111.3).
   const char* const lds_group = lds_all + group * T::kGroupBytes;
   const auto lds_at = [&](int32_t offset) __attribute__((always_inline)) -> const char* {
-    if constexpr (S == 1) return lds_one + offset;
+    if constexpr (S == 1) return static_lds<Key, kStaticBytes>() + offset;
+    else if constexpr (kStatic) return static_lds<Key, kStaticBytes>() + group * T::kGroupBytes + offset;
     else if constexpr (R == 1) return lds_all + group * T::kGroupBytes + offset;
     else return lds_group + offset;
   };
@@ -105,10 +117,6 @@ __global__ void __launch_bounds__(2 * BLK / R * S, 2) radial_fwd_kernel(const Fw
   const int g = lane >> 5;    // which half of the 16-wide MFMA k-slice this lane feeds
 
   const uint64_t t_begin = kTrace ? __builtin_amdgcn_s_memrealtime() : 0;
-  int32_t bh, qb;
-  if (!work_item(a.work, bh, qb)) return;
-  const int32_t part = R == 1 ? 0 : bh % R;  // with R > 1 the work map counts R heads for each
-  if (R > 1) bh /= R;
   const int32_t b = bh / a.H, h = bh % a.H;
 
   const __bf16* qp = (const __bf16*)a.q.ptr + (int64_t)b * a.q.sb + (int64_t)h * a.q.sh;
@@ -368,7 +376,7 @@ __global__ void __launch_bounds__(2 * BLK / R * S, 2) radial_fwd_kernel(const Fw
     if (T::kWaves > 1)  // a stage is a barrier: as many as group 0, which has most stages
       for (int32_t u = n_stage; u < (n_row + S - 1) / S * T::kSubs; ++u) __syncthreads();
     float m = m_run, l = l_run;
-    T::Join::softmax(o, m, l, c, lds_all, group, wave, lane, [&](int p, f32x4 v) __attribute__((always_inline)) {
+    T::Join::softmax(o, m, l, c, kStatic ? static_lds<Key, kStaticBytes>() : lds_all, group, wave, lane, [&](int p, f32x4 v) __attribute__((always_inline)) {
       if (q_ok) *(u32x2*)(dst + 8 * p + 4 * g) = u32x2{pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
     });
     if (q_ok && a.lse && g == 0 && group == 0) store_lse(m, l);
@@ -394,10 +402,36 @@ __global__ void __launch_bounds__(2 * BLK / R * S, 2) radial_fwd_kernel(const Fw
     // hardware id registers: which XCD, shader engine and compute unit this workgroup ran on
     constexpr int kHwId = 4, kXccId = 20, kAllBits = 31 << 11;
     const uint64_t where = ((uint64_t)__builtin_amdgcn_s_getreg(kXccId | kAllBits) << 32) | (uint32_t)__builtin_amdgcn_s_getreg(kHwId | kAllBits);
-    uint64_t* rec = a.wg_trace + 3 * (R == 1 ? (int64_t)blockIdx.x : (int64_t)bh * a.n_blocks + qb);
+    uint64_t* rec = a.wg_trace + 3 * record;
     rec[0] = t_begin;
     rec[1] = __builtin_amdgcn_s_memrealtime();
     rec[2] = where;
+  }
+}
+
+template <int D, int BLK, bool kExact, bool kTrace, int S, int R>
+// Two waves per SIMD: two 4-wave workgroups per compute unit (BLK = 128) or four 2-wave ones (BLK = 64)
+// with S = R = 1.
+__global__ void __launch_bounds__(2 * BLK / R * S, 2) radial_fwd_kernel(const FwdArgs a) {
+  int32_t bh, qb;
+  if (!work_item(a.work, blockIdx.x, bh, qb)) return;
+  const int32_t part = R == 1 ? 0 : bh % R;  // with R > 1 the work map counts R heads for each
+  if (R > 1) bh /= R;
+  fwd_body<D, BLK, kExact, kTrace, S, R, false>(a, bh, qb, part, R == 1 ? (int64_t)blockIdx.x : (int64_t)bh * a.n_blocks + qb);
+}
+
+// Whole blocks, and the last a.work.halved of the launch in halves of two groups.
+template <int D, int BLK, bool kExact, bool kTrace>
+__global__ void __launch_bounds__(2 * BLK, 2) radial_fwd_halves_kernel(const FwdArgs a) {
+  int32_t bh, qb, part = 0;
+  const uint32_t whole = gridDim.x - 2u * (uint32_t)a.work.halved;
+  if (blockIdx.x < whole) {
+    if (!work_item(a.work, blockIdx.x, bh, qb)) return;
+    fwd_body<D, BLK, kExact, kTrace, 1, 1, true>(a, bh, qb, 0, (int64_t)blockIdx.x);
+  } else {
+    const uint32_t id = halved_item(whole, (uint32_t)a.work.halved, part);
+    if (!work_item(a.work, id, bh, qb)) return;
+    fwd_body<D, BLK, kExact, kTrace, 2, 2, true>(a, bh, qb, part, (int64_t)id);
   }
 }
 
@@ -416,6 +450,13 @@ int launch_split(FwdArgs a, hipStream_t stream) {
 }
 
 template <int D, int BLK, bool kExact, bool kTrace>
+int launch_halves(const FwdArgs& a, hipStream_t stream) {
+  radial_fwd_halves_kernel<D, BLK, kExact, kTrace><<<dim3((unsigned)(work_grid(a.work, a.n_blocks) + a.work.halved)), dim3(2 * BLK), 0, stream>>>(a);
+  RADIAL_HIP_TRY(hipGetLastError());
+  return RADIAL_OK;
+}
+
+template <int D, int BLK, bool kExact, bool kTrace>
 int launch(const FwdArgs& a, hipStream_t stream) {
   if (work_grid_bound(a.work) > 0x7fffffffLL) return fail(RADIAL_ESHAPE, "B*H*n_blocks is too large for one launch");
   const int64_t items = work_items(a.work, a.n_blocks);
@@ -424,6 +465,12 @@ int launch(const FwdArgs& a, hipStream_t stream) {
   if (single_waves(BLK, a.work, items)) return launch_split<D, BLK, kExact, kTrace, D == 64 ? 8 : 4, BLK / 32>(a, stream);
   if (groups == 4) return launch_split<D, BLK, kExact, kTrace, 4, BLK / 64>(a, stream);
   if (groups == 2) return launch_split<D, BLK, kExact, kTrace, 2, 1>(a, stream);
+  if constexpr (BLK == 128)
+    if (const int32_t halved = halved_items(a.work, items)) {
+      FwdArgs h = a;
+      h.work.halved = halved;
+      return launch_halves<D, BLK, kExact, kTrace>(h, stream);
+    }
   return launch_split<D, BLK, kExact, kTrace, 1, 1>(a, stream);
 }
 

@@ -109,6 +109,7 @@ struct WorkMap {
   int32_t sliced, ordered;  // heads; sum B * H
   int32_t n_blocks;
   int32_t longest, mean;    // entries of the longest and of an average list
+  int32_t halved = 0;       // the last items of the launch, taken in two halves each (kernels that have such a form)
 };
 
 constexpr int32_t kMaxOrdered = 16384;  // blocks up to which a mask carries the order
@@ -263,6 +264,20 @@ inline int key_groups_two_waves(int block, const WorkMap& w, int64_t items) {
   if (items <= kOneRound) return w.longest >= 8 ? 4 : 0;
   if (items <= 512) return w.longest >= 4 ? 2 : 0;
   return w.mean >= (items <= 1536 ? 16 : 32) ? 2 : 1;
+}
+
+// Blocks of 128 above one round, whole blocks by one group: the launch takes ceil(items / 256) rounds of a workgroup per compute
+// unit (two share one), so the items % 256 last ones keep most of the chip waiting for a whole list.  Up to half a
+// round of them are taken in two halves each, of 64 rows and two groups that walk half the list: the
+// same threads and stage buffers as a whole block, so that both kinds run in one launch.  They have to be the shortest
+// lists of it, so all heads go by length (among slices, 12 to 54 heads: 0.97-1.02).  Whole blocks / with halves, forward, us, equal
+// lists: 264 items L 4 23.4 / 20.1, L 64 208 / 161; 320 items L 4 22.9 / 19.5, L 32 114 / 94.5; 368 items L 32 119 / 104; 520 items L 4
+// 35.1 / 33.2, L 64 367 / 328; 624 items L 32 196 / 179; 1120 items L 4 61.2 / 59.9, L 32 321 / 303; 1600 items L 64 865 / 825; D 64 264 items L 64 147 / 108,
+// 368 items L 32 78.3 / 63.3, 1120 items L 64 373 / 345.  Radial lists: 550 items (64 to 108 entries) 514 / 469, 776 (101 to 153) 990 / 906,
+// 2254 (203 to 448; 206 left, not halved) 7327 / 7340 with 206 halved 7428; 910 (65; 142 left) 516 with 142 halved 568.
+inline int32_t halved_items(const WorkMap& w, int64_t items) {
+  const int64_t rest = items % kOneRound;
+  return items > kOneRound && rest <= kOneRound / 2 && w.sliced == 0 && w.longest >= 4 ? (int32_t)rest : 0;
 }
 
 // 8-bit scores: three groups of 4 waves (12 waves are what a compute unit holds of this kernel) while every item can

@@ -132,15 +132,15 @@ __device__ __forceinline__ float max_with_other_half(float x) {
 // sums an S-th of the pieces over the groups and stores them.  With the waves of one group doing all of it, one other group
 // after the other, the merge and the stores took 3900 cycles (four groups, D 64) to 6700 (two, D 128), a tenth of a launch of 64
 // items; 96 to 126 items of block 128, training step: 67.8 / 66.1, 48.7 / 46.3, 233 / 231 us.
-template <int S, int kWaves, int kTiles>
+template <int S, int kWaves, int kTiles, int kBudget = 160 * 1024>
 struct Merge {
   static constexpr int kPieces = 4 * kTiles;
   static constexpr int kStatBytes = S * kWaves * 512;  // m and l of every wave, 64 floats each
-  static constexpr int kRounds = S * kWaves * kPieces * 1024 + kStatBytes <= 160 * 1024 ? 1 : 2;
+  static constexpr int kRounds = S * kWaves * kPieces * 1024 + kStatBytes <= kBudget ? 1 : 2;
   static constexpr int kRoundPieces = kPieces / kRounds;
   static constexpr int kOwned = (kRoundPieces + S - 1) / S;  // pieces of a round that one group sums
   static constexpr int kLdsBytes = S == 1 ? 0 : S * kWaves * kRoundPieces * 1024 + kStatBytes;
-  static_assert(kLdsBytes <= 160 * 1024, "the partial results of a round fit the LDS");
+  static_assert(kLdsBytes <= kBudget, "the partial results of a round fit the LDS");
 
   // This wave's pieces of round r into LDS.
   __device__ static __forceinline__ void write(const f32x16 (&acc)[kTiles], int r, char* lds, int group, int wave, int lane) {
@@ -229,19 +229,19 @@ struct Merge {
   }
 };
 
-// Work item of this workgroup; false: none.  Consecutive workgroup ids go to different XCDs.
+// Work item `id`, a workgroup id where every workgroup takes one; false: none.  Consecutive workgroup ids go to different XCDs.
 // By slices: the blocks are cut into 8 slices of equal list weight; for head bh, XCD x takes slice
 // (x + bh) mod 8 and the XCDs move from head to head together, so all of them work on the same head
 // at the same time (its K/V stay in the shared last-level cache), neighbouring workgroups of an XCD
 // share K/V tiles in that XCD's L2, and every XCD gets every slice equally often (slices of equal
 // weight do not take exactly equal time).
-__device__ __forceinline__ bool work_item(const WorkMap& w, int32_t& bh, int32_t& block) {
+__device__ __forceinline__ bool work_item(const WorkMap& w, uint32_t id, int32_t& bh, int32_t& block) {
   const uint32_t n_sliced = 8u * (uint32_t)w.sliced * (uint32_t)w.max_slice;
-  if (blockIdx.x >= n_sliced) {
+  if (id >= n_sliced) {
     // By falling list length.  A window of 8 ranks of every head goes to the 8 XCDs at once; inside it an
     // XCD takes neighbouring (head, rank) pairs, head by head, so that it stays with the same
     // heads / 8 heads from window to window (their K/V are what its L2 sees).
-    const uint32_t idx = blockIdx.x - n_sliced, heads = (uint32_t)w.ordered;
+    const uint32_t idx = id - n_sliced, heads = (uint32_t)w.ordered;
     const uint32_t window = idx / (8u * heads), j = idx - window * 8u * heads;
     uint32_t head, rank;
     if (8u * window + 8u <= (uint32_t)w.n_blocks) {
@@ -257,13 +257,26 @@ __device__ __forceinline__ bool work_item(const WorkMap& w, int32_t& bh, int32_t
     block = w.order[rank];
     return true;
   }
-  const uint32_t idx = blockIdx.x >> 3;
+  const uint32_t idx = id >> 3;
   bh = (int32_t)(idx / (uint32_t)w.max_slice);
   const int32_t pos = (int32_t)(idx - (uint32_t)bh * (uint32_t)w.max_slice);
-  const int32_t sl = ((int32_t)(blockIdx.x & 7) + bh) & 7;
+  const int32_t sl = ((int32_t)(id & 7) + bh) & 7;
   const int32_t s0 = w.slice[sl];
   block = s0 + pos;
   return pos < w.slice[sl + 1] - s0;
+}
+
+// Where the last `halved` items of a launch are taken in two halves: item and half of this workgroup.  Both halves of an item
+// are on one XCD (8 workgroups apart) while 8 items are left.
+__device__ __forceinline__ uint32_t halved_item(uint32_t first, uint32_t halved, int32_t& part) {
+  const uint32_t j = blockIdx.x - first, by8 = halved >> 3;
+  if (j < 16u * by8) {
+    part = (int32_t)(j >> 3) & 1;
+    return first + (j >> 4) * 8u + (j & 7u);
+  }
+  const uint32_t rest = halved & 7u, k = j - 16u * by8;
+  part = k >= rest ? 1 : 0;
+  return first + 8u * by8 + (k >= rest ? k - rest : k);
 }
 
 // ---- token-level rule of the radial mask inside listed blocks ---------------------------------
