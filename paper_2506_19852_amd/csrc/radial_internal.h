@@ -129,6 +129,12 @@ constexpr int32_t kMaxOrdered = 16384;  // blocks up to which a mask carries the
 // workgroups for 240 items; forward, D 128, block 128, two groups: lists of 4 29.4 -> 17.4 us, of 12 55.8 -> 33.0).
 // In blocks of 64, where two groups take half a compute unit, that holds up to twice as many (40 heads x 12 blocks: 608
 // workgroups for 480 items; D 128, lists of 12, forward 37.3 -> 23.4 us, forward and backward 140 -> 91).
+// Blocks of 128 go by length with all their heads, however many, while K and V of all of them are well within the last-level
+// cache (160 MB): the grid of slices starts 8 times the longest slice per head, the more of them without work the fewer
+// blocks a head has, and ends on whole heads.  By slices but for the last 8 heads / all by length, forward, us: 74 heads x 9 blocks 90.7 /
+// 64.4, 28 x 18 (D 64) 64.7 / 51.4, 26 x 17 (D 64) 60.6 / 46.3, 15 x 49 322 / 300, 33 x 38 433 / 399, 42 x 26 278 / 259, 27 x 140 (D 64) 2569 /
+// 2413, 36 x 47 646 / 654, 10 x 146 1447 / 1447, 10 x 110 844 / 854 (the runs of one side differ by 1.5 %); forward and backward 36 x 20 (D 64) 386 / 325, 12 x 64
+// (D 64) 1016 / 936, 12 x 69 2262 / 2283.
 constexpr int64_t kOrderedWholeBytes = 256 << 20, kOrderedTailBytes = 160 << 20;
 constexpr int64_t kOneRound = 256;
 // Blocks of 64 tokens move twice the K and V per product, and by length the blocks that an XCD works on at one time
@@ -166,6 +172,7 @@ inline WorkMap make_work_map(const radial_mask* m, Walk walk, int32_t heads, int
   const bool long_tail = w.longest >= 2LL * w.mean && 2048LL * w.longest >= (int64_t)w.mean * heads * m->n_blocks;
   const bool scattered = m->block == 64 && !transposed && xcd_bytes(per_head, heads) > most_bytes && !long_tail;
   w.ordered = !w.order ? 0 : (int64_t)heads * m->n_blocks <= (m->block == 64 ? 2 * kOneRound : kOneRound) ? heads : scattered ? 0 : (fit < most ? (int32_t)fit : most);
+  if (w.order && m->block == 128 && m->n_blocks >= 8 && heads * per_head <= kOrderedTailBytes) w.ordered = heads;
   w.sliced = heads - w.ordered;
   w.n_blocks = m->n_blocks;
   return w;
