@@ -11,7 +11,8 @@
 //             (column = key = lane%32).  S and dP are computed with query rows as MFMA rows
 //             so that P and dS come out with keys across lanes: 8 accumulator rows at a time
 //             they are the B operands of dV^T += dO^T P and dK^T += Q^T dS, whose A operands
-//             are transposing LDS reads of the dO and Q stage tiles;
+//             are transposing LDS reads of the dO and Q stage tiles (head dimension 128, blocks of 128: two waves
+//             share 32 keys, see PairTile);
 //   dq      : one workgroup per (batch, head, query block) walks the row list in stages of 64
 //             keys, like the forward kernel: wave w owns 32 query rows whose Q and dO rows stay
 //             in registers; S^T = K Q^T and dP^T = V dO^T come out with queries across lanes,
@@ -494,6 +495,378 @@ __global__ void __launch_bounds__(2 * BLK / R * S, 2) radial_bwd_dkdv_two_kernel
   dkdv_body<D, BLK, kExact, S, R, true>(a);
 }
 
+// dK/dV of head dimension 128, two waves per SIMD: a pair of waves shares 32 keys.  One wave of each kind has K, S, P and dV, the
+// other V, dP, dS and dK, so that either needs half the registers of a wave that does all four products (422).  The
+// second wave needs P: the first leaves it in LDS in float32, lane by lane (both products come out in the same
+// layout), and the second takes it a stage later, when every P of that stage is behind the barrier anyway:
+//   stage u:  first wave   S(u), P(u) -> LDS, dV += P(u)^T dO(u)
+//             second wave  dS(u - 1) = P(u - 1) * (dP(u - 1) - delta), dP(u), dK += dS(u - 1)^T Q(u - 1)
+// so Q has three stage buffers and dO two, and the vector part of one wave falls on the matrix part of the other.
+// Wave w and wave w + kPairs share keys: they are on one SIMD.  212 registers (235 under the token rule), and a pair that
+// sees nothing of a stage skips it, which one wave with four products had no registers for.
+// The chip lowers its clock for the busier matrix pipes (8 x 126 360 tokens, radial lists: 46 % at 2.06 GHz -> 52 % at 1.9), so the large
+// launches gain least.  Backward pass, one wave with four products / pairs: 8 x 126 360 tokens 82.5 / 80.3 ms, 5 x 14 040 1728 / 1653 us,
+// 5 x 32 760 with the token rule 6284 / 5897, 12 x 3500 398 / 363; equal lists, 4096 blocks L 1 417 / 404, 256 L 32 254 / 242, 320 L 8
+// 129 / 119, 1680 L 12 679 / 633, 8 L 1 23.9 / 22.9.  What bounds it is LDS traffic: without the exchange of P (16 of 81 KiB per stage
+// and pair) it ran 9 % faster; LSE and delta are read once and broadcast in registers, as 16-byte reads in all lanes they took 16 KiB
+// more (256 L 32: 252 us).  Priorities of either wave, fragments read three MFMAs ahead and P read two groups ahead: ties.
+template <int D, int BLK>
+struct PairTile {
+  static constexpr int kPairs = BLK / 32;
+  static constexpr int kThreads = 128 * kPairs;
+  static constexpr int kSubs = BLK / kStageQ;
+  static constexpr int kLastOffset = BLK - kStageQ;
+  static constexpr int kSteps = D / 16;
+  static constexpr int kDTiles = D / 32;
+  static constexpr int kTileBytes = kStageQ * D * 2;  // Q or dO of a stage
+  static constexpr int kStatBytes = 2 * kStageQ * 4;  // LSE and delta of a stage
+  static constexpr int kPBytes = kStageQ * 32 * 4;    // P of a stage and a pair
+  static constexpr int kGradAt = 3 * kTileBytes;      // [Q x 3][dO x 2][LSE, delta x 3][P x 2 x pairs]
+  static constexpr int kStatAt = kGradAt + 2 * kTileBytes;
+  static constexpr int kPAt = kStatAt + 3 * kStatBytes;
+  static constexpr int kLdsBytes = kPAt + 2 * kPairs * kPBytes;
+  static constexpr int kLoadsPerWave = kTileBytes / 1024 / (2 * kPairs);
+  static constexpr int kCopies = 2 * kLoadsPerWave + 1;  // Q, dO, and LSE (wave 0) or delta (wave 1)
+};
+
+template <int D, int BLK, bool kExact>
+__global__ void __launch_bounds__(4 * BLK, 2) radial_bwd_dkdv_pairs_kernel(const BwdArgs a) {
+  using T = PairTile<D, BLK>;
+  using QT = SwzTile<D>;
+  extern __shared__ __attribute__((aligned(1024))) char lds_all[];
+
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const bool second = wave >= T::kPairs;
+  const int pair = second ? wave - T::kPairs : wave;
+  const uint32_t lds_base = lds_address(lds_all);
+  const int lq = lane & 31;
+  const int g = lane >> 5;
+  const int i16 = lane & 15;
+  const int half16 = (lane >> 4) & 1;
+
+  int32_t bh, kb;
+  if (!work_item(a.work_t, blockIdx.x, bh, kb)) return;
+  const int32_t b = bh / a.H, h = bh % a.H;
+  const __bf16* qp = (const __bf16*)a.q.ptr + (int64_t)b * a.q.sb + (int64_t)h * a.q.sh;
+  const __bf16* gp = (const __bf16*)a.dout.ptr + (int64_t)b * a.dout.sb + (int64_t)h * a.dout.sh;
+  const float* statp = (wave == 0 ? a.lse : a.delta) + (int64_t)bh * a.N;  // what this wave copies of them
+
+  const int32_t list_lo = __builtin_amdgcn_readfirstlane(a.col_ptr[kb]);
+  const int32_t n_list = __builtin_amdgcn_readfirstlane(a.col_ptr[kb + 1]) - list_lo;
+  const int32_t n_stage = n_list * T::kSubs;
+  const int32_t key_row = kb * BLK + pair * 32 + lq;
+  const bool key_ok = key_row < a.N;
+
+  bf16x8 kv[T::kSteps];  // K (first wave) or V row of this lane's key: B operands of S = Q K^T or dP = dO V^T
+  {
+    const TensorArg& src = second ? a.v : a.k;
+    const __bf16* row = (const __bf16*)src.ptr + (int64_t)b * src.sb + (int64_t)h * src.sh + (int64_t)(key_ok ? key_row : a.N - 1) * src.sn + 8 * g;
+#pragma unroll
+    for (int t = 0; t < T::kSteps; ++t) {
+      u32x4 raw = *(const u32x4*)(row + 16 * t);
+      if (!key_ok) raw = u32x4{0u, 0u, 0u, 0u};
+      kv[t] = __builtin_bit_cast(bf16x8, raw);
+    }
+  }
+
+  const int32_t* rows_list = a.row_idx + list_lo;
+  int32_t cvec = lane < n_list ? rows_list[lane] : 0;
+  int32_t nvec = 64 + lane < n_list ? rows_list[64 + lane] : 0;
+  StagePos key_at = {0, 0}, cvec_at = {0, 0};
+  if (kExact) {
+    key_at = block_pos(key_ok ? key_row : a.N - 1, a.rule.s);
+    cvec_at = block_pos(cvec * BLK, a.rule.s);
+  }
+
+  int32_t srow[T::kLoadsPerWave], scol[T::kLoadsPerWave];
+  uint32_t qoff[T::kLoadsPerWave], goff[T::kLoadsPerWave];  // byte offsets from the stage's first row
+#pragma unroll
+  for (int i = 0; i < T::kLoadsPerWave; ++i) {
+    QT::source_of((wave * T::kLoadsPerWave + i) * 64 + lane, srow[i], scol[i]);
+    qoff[i] = (uint32_t)(srow[i] * (int32_t)a.q.sn + scol[i]) * 2u;
+    goff[i] = (uint32_t)(srow[i] * (int32_t)a.dout.sn + scol[i]) * 2u;
+  }
+  // Stage buffers of stage u: Q and the row statistics go round three, dO and P round two.
+  struct Bufs {
+    int32_t q, grad, stat, p;  // byte offsets
+  };
+  const auto next_bufs = [](Bufs x) {
+    return Bufs{x.q == 2 * T::kTileBytes ? 0 : x.q + T::kTileBytes, 2 * T::kGradAt + T::kTileBytes - x.grad,
+                x.stat == T::kStatAt + 2 * T::kStatBytes ? T::kStatAt : x.stat + T::kStatBytes, 2 * T::kPAt + T::kPairs * T::kPBytes - x.p};
+  };
+  // All of this wave's copies of a stage at once (first stage, ragged stages: rows past N-1 are clamped to N-1).
+  auto issue_stage = [&](int32_t q0, const Bufs& to) {
+    const uint32_t qdst = lds_base + to.q + wave * T::kLoadsPerWave * 1024, gdst = lds_base + to.grad + wave * T::kLoadsPerWave * 1024;
+#pragma unroll
+    for (int i = 0; i < T::kLoadsPerWave; ++i) {
+      int32_t r = q0 + srow[i];
+      r = r < a.N ? r : a.N - 1;
+      copy16_to_lds(qp + (int64_t)r * a.q.sn + scol[i], qdst + i * 1024);
+      copy16_to_lds(gp + (int64_t)r * a.dout.sn + scol[i], gdst + i * 1024);
+    }
+    if (wave < 2) {
+      int32_t r = q0 + lane;
+      r = r < a.N ? r : a.N - 1;
+      copy4_to_lds(statp + r, lds_base + to.stat + wave * kStageQ * 4);
+    }
+  };
+
+  f32x16 acc[T::kDTiles];  // dV^T or dK^T: column = this lane's key, rows = d
+#pragma unroll
+  for (int i = 0; i < T::kDTiles; ++i)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[i][e] = 0.f;
+  const float c = a.scale * kLog2e;
+
+  int32_t q0 = 0, q0_next = 0;
+  StagePos q_at = {0, 0}, q_at_next = {0, 0};
+  Bufs at = {0, T::kGradAt, T::kStatAt, T::kPAt};
+  if (n_stage > 0) {
+    q0 = __builtin_amdgcn_readlane(cvec, 0) * BLK;
+    if (kExact) q_at = stage_pos<0>(cvec_at, 0, 0, a.rule.s);
+    issue_stage(q0, at);
+  }
+
+  // Where the copies of the next stage go, and whether they are spread over this one's MFMAs.
+  Bufs to = at;
+  bool spread = false;
+  uint64_t copy_lanes = 0;
+  const __bf16 *qbase = qp, *gbase = gp;
+  StageRule vis = {};
+  bool skip = false;  // token rule: no row of the stage sees a key of this pair
+  auto open_stage = [&](int32_t u) __attribute__((always_inline)) {
+    const bool has_next = u + 1 < n_stage;
+    to = next_bufs(at);
+    if (has_next) {
+      const int32_t e1 = (u + 1) / T::kSubs;
+      if ((u + 1) % T::kSubs == 0 && (e1 & 63) == 0) {
+        cvec = nvec;
+        nvec = e1 + 64 + lane < n_list ? rows_list[e1 + 64 + lane] : 0;
+        if (kExact) cvec_at = block_pos(cvec * BLK, a.rule.s);
+      }
+      q0_next = __builtin_amdgcn_readlane(cvec, e1 & 63) * BLK + ((u + 1) % T::kSubs) * kStageQ;
+      if (kExact) q_at_next = stage_pos<T::kLastOffset>(cvec_at, e1 & 63, ((u + 1) % T::kSubs) * kStageQ, a.rule.s);
+    }
+    wait_all_copies();  // stage u has landed
+    __syncthreads();    // for every wave; stage u-1 is finished and its P written
+    if (kExact) {
+      vis = stage_rule(a.rule, key_at, q_at, false);  // which of the stage's queries see this lane's key
+      skip = vis.none;
+    }
+    spread = has_next && !skip && q0_next + kStageQ <= a.N;
+    if (has_next && !spread) issue_stage(q0_next, to);
+    const uint32_t on = __builtin_amdgcn_readfirstlane(spread ? ~0u : 0u);
+    copy_lanes = ((uint64_t)on << 32) | on;
+    const int32_t q_src = spread ? q0_next : q0;  // any valid row when the copies are switched off
+    qbase = qp + (int64_t)q_src * a.q.sn;
+    gbase = gp + (int64_t)q_src * a.dout.sn;
+  };
+  auto close_stage = [&]() __attribute__((always_inline)) {
+    q0 = q0_next;
+    q_at = q_at_next;
+    at = to;
+  };
+  auto spread_copy = [&](int j) __attribute__((always_inline)) {
+    if (j < T::kLoadsPerWave) {
+      copy16_to_lds_sv_masked(qbase, qoff[j], lds_base + to.q + (wave * T::kLoadsPerWave + j) * 1024, copy_lanes);
+    } else if (j < 2 * T::kLoadsPerWave) {
+      const int i = j - T::kLoadsPerWave;
+      copy16_to_lds_sv_masked(gbase, goff[i], lds_base + to.grad + (wave * T::kLoadsPerWave + i) * 1024, copy_lanes);
+    } else {
+      copy4_to_lds_sv_masked(statp + (spread ? q0_next : q0), (uint32_t)lane * 4u, lds_base + to.stat + (wave & 1) * kStageQ * 4, wave < 2 ? copy_lanes : 0ull);
+    }
+  };
+  // LDS fragments of both products: step i = 8 * half + k-step of the first, pair j = (2 * half + 16-row step) * kDTiles + d tile of
+  // the second, whose A operand is read transposed.
+  // The swizzle exchanges pieces within a row by exclusive or, and tiles start at multiples of 1024 bytes: one address per lane
+  // and product, and the pieces by exclusive or with constants (8 offsets per product held in registers were spilled).
+  const uint32_t rows_at = lds_base + QT::piece(lq, g);
+  const uint32_t columns_at = lds_base + QT::elem(4 * g + (i16 >> 2), 16 * half16 + 4 * (i16 & 3));
+  auto read_rows = [&](int32_t tile, int i) __attribute__((always_inline)) -> bf16x8 {
+    return *lds_pointer<const bf16x8>(((rows_at + tile) ^ (i % T::kSteps * 32)) + i / T::kSteps * 32 * 2 * D);
+  };
+  auto read_columns = [&](int32_t tile, int j) __attribute__((always_inline)) -> bf16x8 {
+    const uint32_t at_row = (columns_at + tile) ^ (j % T::kDTiles * 64);
+    const uint32_t rows = j / T::kDTiles * 16 * 2 * D;
+    const s16x4 x0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16(lds_pointer<s16x4>(at_row + rows));
+    const s16x4 x1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16(lds_pointer<s16x4>((at_row ^ 32) + rows + 8 * 2 * D));
+    const u32x2 lo = __builtin_bit_cast(u32x2, x0), hi = __builtin_bit_cast(u32x2, x1);
+    return as_bf16x8(lo[0], lo[1], hi[0], hi[1]);
+  };
+  const auto p_at = [&](const Bufs& x, int w) __attribute__((always_inline)) -> char* {  // w = 4 * half + quarter
+    return lds_all + x.p + pair * T::kPBytes + w * 1024 + lane * 16;
+  };
+  // LSE (which = 0) or delta of half h2: element e of the half is this value in lane e of this lane's row of 16.
+  const uint32_t stat_at = lds_base + (8 * (i16 >> 2) + 4 * g + (i16 & 3)) * 4;
+  const auto read_stat = [&](const Bufs& x, int which, int h2) __attribute__((always_inline)) -> float {
+    return *lds_pointer<const float>(stat_at + x.stat + (which * kStageQ + h2 * 32) * 4);
+  };
+  const auto operand = [](const uint32_t (&w)[16], int j) __attribute__((always_inline)) {
+    const int k = j / T::kDTiles * 4;
+    return as_bf16x8(w[k], w[k + 1], w[k + 2], w[k + 3]);
+  };
+  constexpr int kAhead = 2;  // LDS fragments are read this many MFMAs before their use; the fences keep the written order
+  constexpr int kFirst = 2 * T::kSteps, kSecond = 4 * T::kDTiles;  // MFMAs of either product
+  static_assert(T::kSteps == 8 && T::kDTiles == 4, "the vector work is dealt over 16 + 16 MFMAs");
+  auto spread_copies = [&](int i) __attribute__((always_inline)) {
+    if (i < T::kSteps) {
+#pragma unroll
+      for (int j = i * T::kCopies / T::kSteps; j < (i + 1) * T::kCopies / T::kSteps; ++j) spread_copy(j);
+    }
+  };
+  const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+
+  if (!second) {
+    for (int32_t u = 0; u < n_stage; ++u) {
+      open_stage(u);
+      if (!skip) {
+        const int32_t tq = at.q, tg = at.grad;
+        uint32_t hidden = 0u;
+        if (q0 + kStageQ > a.N || (kExact && vis.partial)) {  // query rows past N, rows the token rule hides from this key
+          uint64_t seen = stage_prefix(a.N - q0);
+          if (kExact) seen &= vis.visible_mask();
+          hidden = ~lane_element_bits(seen, g);
+        }
+        const bool any_hidden = __builtin_amdgcn_ballot_w64(hidden != 0u) != 0;
+        f32x16 s[2];
+        float lse[2];
+        f32x4 p4;
+        uint32_t pp[16];
+        bf16x8 rows[kFirst], columns[kSecond];
+        auto hide = [&](int h2) __attribute__((always_inline)) {
+          if (any_hidden) {
+#pragma unroll
+            for (int e = 0; e < 16; ++e)
+              if ((hidden >> (16 * h2 + e)) & 1u) s[h2][e] = -INFINITY;
+          }
+        };
+        // P of elements 2 * k and 2 * k + 1 of the stage's 32
+        auto softmax_pair = [&](int k) __attribute__((always_inline)) {
+          const int h2 = k / 8, e = 2 * (k % 8);
+          const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[h2][e], c, -row_lane(lse[h2], e)));
+          const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[h2][e + 1], c, -row_lane(lse[h2], e + 1)));
+          p4[e & 3] = p0;
+          p4[(e & 3) + 1] = p1;
+          pp[k] = pack_bf16(p0, p1);
+          asm volatile("" : "+v"(pp[k]));  // stays between its MFMAs
+          if (k & 1) *lds_cast<f32x4>(p_at(at, k / 2)) = p4;
+        };
+#pragma unroll
+        for (int i = 0; i < kAhead; ++i) rows[i] = read_rows(tq, i);
+        lse[0] = read_stat(at, 0, 0) * kLog2e;
+        lse[1] = read_stat(at, 0, 1) * kLog2e;
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < kFirst; ++i) {
+          if (i + kAhead < kFirst) rows[i + kAhead] = read_rows(tq, i + kAhead);
+          else columns[i + kAhead - kFirst] = read_columns(tg, i + kAhead - kFirst);
+          const int h2 = i / T::kSteps, t = i % T::kSteps;
+          s[h2] = mfma32(rows[i], kv[t], t == 0 ? zero : s[h2]);
+          spread_copies(i);
+          if (h2 == 1) softmax_pair(t);
+          __builtin_amdgcn_sched_barrier(0);
+          if (t == T::kSteps - 1) hide(h2);
+        }
+#pragma unroll
+        for (int j = 0; j < kSecond; ++j) {
+          if (j + kAhead < kSecond) columns[j + kAhead] = read_columns(tg, j + kAhead);
+          acc[j % T::kDTiles] = mfma32(columns[j], operand(pp, j), acc[j % T::kDTiles]);
+          if (j < 8) softmax_pair(8 + j);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+      close_stage();
+    }
+    if (n_stage > 0) __syncthreads();
+  } else {
+    f32x16 dp[2] = {zero, zero};
+    Bufs last = at;     // of the stage before
+    bool owed = false;  // its dS and dK are
+    f32x4 p4[8];
+    float delta[2];
+    uint32_t ds[16];
+    auto read_p = [&](int w) __attribute__((always_inline)) {
+      if (w == 0) {
+        delta[0] = read_stat(last, 1, 0);
+        delta[1] = read_stat(last, 1, 1);
+      }
+      p4[w] = *lds_cast<const f32x4>(p_at(last, w));
+    };
+    // dS of elements 2 * k and 2 * k + 1 of the stage's 32
+    auto weight_pair = [&](int k) __attribute__((always_inline)) {
+      const int h2 = k / 8, e = 2 * (k % 8);
+      const f32x4 p = p4[k / 2];
+      ds[k] = pack_bf16(p[e & 3] * (dp[h2][e] - row_lane(delta[h2], e)), p[(e & 3) + 1] * (dp[h2][e + 1] - row_lane(delta[h2], e + 1)));
+      asm volatile("" : "+v"(ds[k]));
+    };
+    for (int32_t u = 0; u < n_stage; ++u) {
+      open_stage(u);
+      const int32_t tg = at.grad, tq = last.q;
+      bf16x8 rows[kFirst], columns[kSecond];
+      if (!kExact || !skip) {
+#pragma unroll
+        for (int i = 0; i < kAhead; ++i) rows[i] = read_rows(tg, i);
+        read_p(0);  // of the first stage: not used
+        f32x16 next[2];
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < kFirst; ++i) {
+          if (i + kAhead < kFirst) rows[i + kAhead] = read_rows(tg, i + kAhead);
+          else columns[i + kAhead - kFirst] = read_columns(tq, i + kAhead - kFirst);
+          if (i % 2 == 0 && i / 2 + 1 < 8) read_p(i / 2 + 1);
+          const int h2 = i / T::kSteps, t = i % T::kSteps;
+          next[h2] = mfma32(rows[i], kv[t], t == 0 ? zero : next[h2]);
+          spread_copies(i);
+          weight_pair(i);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        dp[0] = next[0];
+        dp[1] = next[1];
+      } else if (owed) {
+#pragma unroll
+        for (int w = 0; w < 8; ++w) read_p(w);
+#pragma unroll
+        for (int i = 0; i < kFirst; ++i) weight_pair(i);
+#pragma unroll
+        for (int j = 0; j < kAhead; ++j) columns[j] = read_columns(tq, j);
+      }
+      if (owed) {
+#pragma unroll
+        for (int j = 0; j < kSecond; ++j) {
+          if (j + kAhead < kSecond) columns[j + kAhead] = read_columns(tq, j + kAhead);
+          acc[j % T::kDTiles] = mfma32(columns[j], operand(ds, j), acc[j % T::kDTiles]);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+      owed = !skip;
+      last = at;
+      close_stage();
+    }
+    if (n_stage > 0) __syncthreads();
+    if (owed) {
+#pragma unroll
+      for (int w = 0; w < 8; ++w) read_p(w);
+#pragma unroll
+      for (int i = 0; i < kFirst; ++i) weight_pair(i);
+#pragma unroll
+      for (int j = 0; j < kSecond; ++j) acc[j % T::kDTiles] = mfma32(read_columns(last.q, j), operand(ds, j), acc[j % T::kDTiles]);
+    }
+  }
+
+  if (key_ok) {  // dK = scale * dK^T, dV
+    const TensorArg& to_tensor = second ? a.dk : a.dv;
+    const float f = second ? a.scale : 1.f;
+    __bf16* dst = (__bf16*)to_tensor.ptr + (int64_t)b * to_tensor.sb + (int64_t)h * to_tensor.sh + (int64_t)key_row * to_tensor.sn + 4 * g;
+#pragma unroll
+    for (int dt = 0; dt < T::kDTiles; ++dt)
+#pragma unroll
+      for (int e4 = 0; e4 < 4; ++e4)
+        *(u32x2*)(dst + 32 * dt + 8 * e4) = u32x2{pack_bf16(acc[dt][4 * e4] * f, acc[dt][4 * e4 + 1] * f),
+                                                  pack_bf16(acc[dt][4 * e4 + 2] * f, acc[dt][4 * e4 + 3] * f)};
+  }
+}
+
 template <int D, int BLK, int S, int R>
 struct DqTile {
   static constexpr int kRows = BLK / R;
@@ -763,6 +1136,16 @@ int launch_dkdv(BwdArgs a, hipStream_t stream) {
   return RADIAL_OK;
 }
 
+template <int BLK, bool kExact>
+int launch_dkdv_pairs(const BwdArgs& a, hipStream_t stream) {
+  using T = PairTile<128, BLK>;
+  const auto kernel = radial_bwd_dkdv_pairs_kernel<128, BLK, kExact>;
+  static DeviceOnce configured;
+  if (int rc = allow_dynamic_lds(configured, (const void*)kernel, T::kLdsBytes)) return rc;
+  kernel<<<dim3((unsigned)work_grid(a.work_t, a.n_blocks)), dim3(T::kThreads), T::kLdsBytes, stream>>>(a);
+  return RADIAL_OK;
+}
+
 template <int D, int BLK, bool kExact, int S, int R>
 int launch_dq(BwdArgs a, hipStream_t stream) {
   using T = DqTile<D, BLK, S, R>;
@@ -791,6 +1174,7 @@ int launch(const BwdArgs& a, hipStream_t stream) {
   else if (D == 64 && two == 4) rc = launch_dkdv<64, BLK, kExact, 4, BLK / 64, true>(a, stream);
   else if (D == 64 && two == 2) rc = launch_dkdv<64, BLK, kExact, 2, 1, true>(a, stream);
   else if (D == 64 && two == 1) rc = launch_dkdv<64, BLK, kExact, 1, 1, true>(a, stream);
+  else if (D == 128 && BLK == 128 && kv == 1) rc = launch_dkdv_pairs<128, kExact>(a, stream);
   else rc = kv == 2 ? launch_dkdv<D, BLK, kExact, 2, BLK / 64>(a, stream) : launch_dkdv<D, BLK, kExact, 1, 1>(a, stream);
   if (rc) return rc;
   if (single_waves(BLK, a.work, items)) rc = launch_dq<D, BLK, kExact, D == 64 ? 8 : 4, BLK / 32>(a, stream);

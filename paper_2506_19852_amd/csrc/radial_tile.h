@@ -24,6 +24,12 @@ __device__ __forceinline__ __attribute__((address_space(3))) T* lds_cast(const v
   return (__attribute__((address_space(3))) T*)(p);
 }
 
+// LDS address -> LDS pointer.
+template <class T>
+__device__ __forceinline__ __attribute__((address_space(3))) T* lds_pointer(uint32_t address) {
+  return (__attribute__((address_space(3))) T*)(uintptr_t)address;
+}
+
 __device__ __forceinline__ uint32_t lds_address(const void* p) { return (uint32_t)(uintptr_t)lds_cast<char>(p); }
 
 // v_mfma_f32_32x32x16_bf16: D[32x32] += A[32x16] * B[16x32].
@@ -113,6 +119,33 @@ struct SwzTile {
 __device__ __forceinline__ u32x2 lds_read_tr(const char* p) {
   const s16x4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16(lds_cast<s16x4>(p));
   return __builtin_bit_cast(u32x2, v);
+}
+
+// The value of x in lane e of this lane's row of 16; e is a constant once loops are unrolled.
+template <int E>
+__device__ __forceinline__ float row_lane_at(float x) {
+  constexpr int kRowNewBcast = 0x150, kAll = 0xf;
+  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), kRowNewBcast + E, kAll, kAll, true));
+}
+__device__ __forceinline__ float row_lane(float x, int e) {
+  switch (e) {
+    case 0: return row_lane_at<0>(x);
+    case 1: return row_lane_at<1>(x);
+    case 2: return row_lane_at<2>(x);
+    case 3: return row_lane_at<3>(x);
+    case 4: return row_lane_at<4>(x);
+    case 5: return row_lane_at<5>(x);
+    case 6: return row_lane_at<6>(x);
+    case 7: return row_lane_at<7>(x);
+    case 8: return row_lane_at<8>(x);
+    case 9: return row_lane_at<9>(x);
+    case 10: return row_lane_at<10>(x);
+    case 11: return row_lane_at<11>(x);
+    case 12: return row_lane_at<12>(x);
+    case 13: return row_lane_at<13>(x);
+    case 14: return row_lane_at<14>(x);
+    default: return row_lane_at<15>(x);
+  }
 }
 
 // max(x, value of x in lane^32), exchanged in registers (v_permlane32_swap: the upper 32 lanes
