@@ -236,15 +236,24 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a) {
     }
     // The copies of a full next stage are spread over the first MFMAs of this one (see below);
     // a ragged one is issued at once.
-    const bool spread_next = has_next && q0_next + kStageQ <= a.N;
+    StageRule vis = {};
+    if (kExact) vis = stage_rule(a.rule, key_at, q_at, false);  // which of the stage's queries see this lane's key
+    // A wave that sees nothing of the stage skips it.  Backward pass, us: D 64, block 128, 10 x 17 000 tokens 2150 / 2045, 4 x 30 000
+    // 2754 / 2607, blocks of 64 (fewer such stages) 910 / 911.  Not with the hand-made schedule: the second way round its
+    // loop cost 15 to 18 % (D 128, block 64, 8 x 14 040 2502 / 2953).
+    const bool skip = kExact && kTwoWaves && vis.none;
+    const bool spread_next = has_next && !skip && q0_next + kStageQ <= a.N;
     if (has_next && !spread_next) issue_stage(q0_next, buf ^ 1);
+    if (skip) {
+      q0 = q0_next;
+      q_at = q_at_next;
+      continue;
+    }
 
     const char* sq = lds + buf * T::kStageBytes;
     const char* sg = sq + T::kQBytes;
     const char* st = sg + T::kQBytes;  // 64 x LSE then 64 x delta
     const bool ragged_q = q0 + kStageQ > a.N;
-    StageRule vis = {};
-    if (kExact) vis = stage_rule(a.rule, key_at, q_at, false);  // which of the stage's queries see this lane's key
     uint32_t hidden = 0u;
     if (ragged_q || (kExact && vis.partial)) {  // query rows past N, rows the token rule hides from this key
       uint64_t seen = stage_prefix(a.N - q0);
