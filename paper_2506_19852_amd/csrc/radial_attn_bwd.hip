@@ -106,7 +106,7 @@ __device__ __forceinline__ void mfma_results_settle(f32x16& acc0, f32x16& acc1) 
 // step 9.34 -> 8.21 ms.  196 to 214 registers; held to 168 for a third wave it spills 23 (block 128) to 45: 1-2 % slower, in
 // blocks of 64 25 %.  Head dimension 128 needs 422 registers and has one wave.
 template <int D, int BLK, bool kExact, int S, int R, bool kTwoWaves>
-__device__ __forceinline__ void dkdv_body(const BwdArgs& a) {
+__device__ __forceinline__ void dkdv_body(const BwdArgs& a, uint32_t id) {
   using T = BwdTile<D, BLK, S, R>;
   using QT = SwzTile<D>;  // Q, dO tiles: rows of D elements
   extern __shared__ __attribute__((aligned(1024))) char lds_all[];
@@ -123,7 +123,7 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a) {
   const int half16 = (lane >> 4) & 1;
 
   int32_t bh, kb;
-  if (!work_item(a.work_t, blockIdx.x, bh, kb)) return;
+  if (!work_item(a.work_t, id, bh, kb)) return;
   const int32_t part = R == 1 ? 0 : bh % R;  // with R > 1 the work map counts R heads for each
   if (R > 1) bh /= R;
   const int32_t b = bh / a.H, h = bh % a.H;
@@ -487,20 +487,16 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a) {
 
 template <int D, int BLK, bool kExact>
 __global__ void __launch_bounds__(2 * BLK, 1) radial_bwd_dkdv_kernel(const BwdArgs a) {
-  dkdv_body<D, BLK, kExact, 1, 1, false>(a);
+  dkdv_body<D, BLK, kExact, 1, 1, false>(a, blockIdx.x);
 }
 template <int D, int BLK, bool kExact, int S, int R>
 __global__ void __launch_bounds__(2 * BLK / R * S, 1) radial_bwd_dkdv_split_kernel(const BwdArgs a) {
-  dkdv_body<D, BLK, kExact, S, R, false>(a);
-}
-template <int D, int BLK, bool kExact, int S, int R>
-__global__ void __launch_bounds__(2 * BLK / R * S, 1) radial_bwd_dkdv_single_kernel(const BwdArgs a) {  // one wave per group
-  dkdv_body<D, BLK, kExact, S, R, false>(a);
+  dkdv_body<D, BLK, kExact, S, R, false>(a, blockIdx.x);
 }
 
 template <int D, int BLK, bool kExact, int S, int R>
 __global__ void __launch_bounds__(2 * BLK / R * S, 2) radial_bwd_dkdv_two_kernel(const BwdArgs a) {  // two waves per SIMD
-  dkdv_body<D, BLK, kExact, S, R, true>(a);
+  dkdv_body<D, BLK, kExact, S, R, true>(a, blockIdx.x);
 }
 
 // dK/dV of head dimension 128, two waves per SIMD: a pair of waves shares 32 keys.  One wave of each kind has K, S, P and dV, the
@@ -895,7 +891,7 @@ struct DqTile {
 };
 
 template <int D, int BLK, bool kExact, int S, int R>
-__global__ void __launch_bounds__(2 * BLK / R * S, 2) radial_bwd_dq_kernel(const BwdArgs a) {
+__device__ __forceinline__ void dq_body(const BwdArgs& a, uint32_t id) {
   using T = DqTile<D, BLK, S, R>;
   using SW = SwzTile<D>;
   // [group][stage buffer][K, V][kStageKeys x D bf16]; one group's are a static array, as in the forward
@@ -917,7 +913,7 @@ __global__ void __launch_bounds__(2 * BLK / R * S, 2) radial_bwd_dq_kernel(const
   const int half16 = (lane >> 4) & 1;
 
   int32_t bh, qb;
-  if (!work_item(a.work, blockIdx.x, bh, qb)) return;
+  if (!work_item(a.work, id, bh, qb)) return;
   const int32_t part = R == 1 ? 0 : bh % R;
   if (R > 1) bh /= R;
   const int32_t b = bh / a.H, h = bh % a.H;
@@ -1129,14 +1125,25 @@ __global__ void __launch_bounds__(2 * BLK / R * S, 2) radial_bwd_dq_kernel(const
   }
 }
 
+template <int D, int BLK, bool kExact, int S, int R>
+__global__ void __launch_bounds__(2 * BLK / R * S, 2) radial_bwd_dq_kernel(const BwdArgs a) {
+  dq_body<D, BLK, kExact, S, R>(a, blockIdx.x);
+}
+
+// dK/dV and dQ in one launch (see both_groups): the first n_key workgroups take key blocks, the others query blocks.
+template <int D, int BLK, bool kExact, int S, int R>
+__global__ void __launch_bounds__(2 * BLK / R * S, 2) radial_bwd_both_kernel(const BwdArgs a, uint32_t n_key) {
+  if (blockIdx.x < n_key) dkdv_body<D, BLK, kExact, S, R, true>(a, blockIdx.x);
+  else dq_body<D, BLK, kExact, S, R>(a, blockIdx.x - n_key);
+}
+
 template <int D, int BLK, bool kExact, int S, int R, bool kTwoWaves = false>
 int launch_dkdv(BwdArgs a, hipStream_t stream) {
   using T = BwdTile<D, BLK, S, R>;
   void (*kernel)(BwdArgs);
   if constexpr (kTwoWaves) kernel = radial_bwd_dkdv_two_kernel<D, BLK, kExact, S, R>;
   else if constexpr (S == 1) kernel = radial_bwd_dkdv_kernel<D, BLK, kExact>;
-  else if constexpr (T::kWaves > 1) kernel = radial_bwd_dkdv_split_kernel<D, BLK, kExact, S, R>;
-  else kernel = radial_bwd_dkdv_single_kernel<D, BLK, kExact, S, R>;
+  else kernel = radial_bwd_dkdv_split_kernel<D, BLK, kExact, S, R>;
   static DeviceOnce configured;
   if (int rc = allow_dynamic_lds(configured, (const void*)kernel, T::kLdsBytes)) return rc;
   a.work_t.ordered *= R;  // R > 1 only up to kOneRound items, where all heads are taken by list length
@@ -1167,6 +1174,21 @@ int launch_dq(BwdArgs a, hipStream_t stream) {
   return RADIAL_OK;
 }
 
+template <int BLK, bool kExact, int S, int R>
+int launch_both(BwdArgs a, hipStream_t stream) {
+  constexpr int kKeyBytes = BwdTile<64, BLK, S, R>::kLdsBytes, kQueryBytes = DqTile<64, BLK, S, R>::kLdsBytes;
+  constexpr int kBytes = kKeyBytes > kQueryBytes ? kKeyBytes : kQueryBytes;
+  const auto kernel = radial_bwd_both_kernel<64, BLK, kExact, S, R>;
+  static DeviceOnce configured;
+  if (int rc = allow_dynamic_lds(configured, (const void*)kernel, kBytes)) return rc;
+  a.work.ordered *= R;  // at most kOneRound items, where all heads are taken by list length
+  a.work_t.ordered *= R;
+  const uint32_t n_key = (uint32_t)work_grid(a.work_t, a.n_blocks);
+  kernel<<<dim3(n_key + (unsigned)work_grid(a.work, a.n_blocks)), dim3(2 * BLK / R * S), kBytes, stream>>>(a, n_key);
+  RADIAL_HIP_TRY(hipGetLastError());
+  return RADIAL_OK;
+}
+
 template <int D, int BLK, bool kExact>
 int launch(const BwdArgs& a, hipStream_t stream) {
   const int64_t rows = (int64_t)a.B * a.H * a.N;
@@ -1176,16 +1198,26 @@ int launch(const BwdArgs& a, hipStream_t stream) {
     return fail(RADIAL_ESHAPE, "problem too large for one launch");
   bwd_prepare_kernel<D><<<dim3((unsigned)prep_grid), dim3(256), 0, stream>>>(a);
   const int64_t items = work_items(a.work, a.n_blocks);
-  const int two = key_groups_two_waves(BLK, a.work_t, items), kv = key_groups(BLK, a.work_t, items), q = query_groups(D, BLK, a.work, items, false);
+  if constexpr (D == 64) {
+    switch (both_groups(BLK, items)) {
+      case 4: return launch_both<BLK, kExact, 4, BLK / 32>(a, stream);
+      case 2: return launch_both<BLK, kExact, 2, BLK / 64>(a, stream);
+      case 1: return launch_both<BLK, kExact, 1, 1>(a, stream);
+    }
+    // two waves per SIMD; in blocks of 64 two groups take fewer walks at once, which pays on long lists (3200 items L 16 251 / 261, L 32
+    // 454 / 453; radial lists: 2136 items, mean 172, 1620 / 1563)
+    int rc = BLK == 64 && a.work_t.mean >= 32 ? launch_dkdv<64, 64, kExact, 2, 1, true>(a, stream) : launch_dkdv<64, BLK, kExact, 1, 1, true>(a, stream);
+    if (rc) return rc;
+    if ((rc = launch_dq<64, BLK, kExact, 1, 1>(a, stream))) return rc;
+    RADIAL_HIP_TRY(hipGetLastError());
+    return RADIAL_OK;
+  }
+  const int kv = key_groups(BLK, a.work_t, items), q = query_groups(D, BLK, a.work, items, false);
   int rc;
-  if (D == 64 && single_waves(BLK, a.work_t, items)) rc = launch_dkdv<64, BLK, kExact, 4, BLK / 32>(a, stream);
-  else if (D == 64 && two == 4) rc = launch_dkdv<64, BLK, kExact, 4, BLK / 64, true>(a, stream);
-  else if (D == 64 && two == 2) rc = launch_dkdv<64, BLK, kExact, 2, 1, true>(a, stream);
-  else if (D == 64 && two == 1) rc = launch_dkdv<64, BLK, kExact, 1, 1, true>(a, stream);
-  else if (D == 128 && BLK == 128 && kv == 1) rc = launch_dkdv_pairs<128, kExact>(a, stream);
+  if (D == 128 && BLK == 128 && kv == 1) rc = launch_dkdv_pairs<128, kExact>(a, stream);
   else rc = kv == 2 ? launch_dkdv<D, BLK, kExact, 2, BLK / 64>(a, stream) : launch_dkdv<D, BLK, kExact, 1, 1>(a, stream);
   if (rc) return rc;
-  if (single_waves(BLK, a.work, items)) rc = launch_dq<D, BLK, kExact, D == 64 ? 8 : 4, BLK / 32>(a, stream);
+  if (single_waves(BLK, a.work, items)) rc = launch_dq<D, BLK, kExact, 4, BLK / 32>(a, stream);
   else if (q == 4) rc = launch_dq<D, BLK, kExact, 4, BLK / 64>(a, stream);
   else rc = q == 2 ? launch_dq<D, BLK, kExact, 2, 1>(a, stream) : launch_dq<D, BLK, kExact, 1, 1>(a, stream);
   if (rc) return rc;

@@ -212,8 +212,8 @@ inline bool two_groups_pay_64(int D, const WorkMap& w, int64_t items) {
   return items <= 1536 && w.mean >= 12;
 }
 
-// Groups of a single wave, 32 rows per workgroup (in the forward and dQ 4 groups at D 128 and 8 at D 64, in dK/dV 4 at D 64;
-// dK/dV at D 128 has LDS for two waves only and keeps the forms below): while all parts of all blocks still get a compute
+// Groups of a single wave, 32 rows per workgroup (in the forward 4 groups at D 128 and 8 at D 64, in dQ 4 at D 128; the backward at
+// D 64 has both_groups, and dK/dV at D 128 has LDS for two waves only and keeps the forms below): while all parts of all blocks still get a compute
 // unit of their own.  Such a launch spreads over 2 (block 64) or 4 (block 128) times the compute units of a workgroup per
 // block, and a wave that shares its stage buffers with nobody needs no barrier: in the forms above it waited there for 29 %
 // of its loop (64 items of D 64, block 64).  Best of the forms above / single waves, forward then backward, us: block 64, D 64, 64
@@ -254,23 +254,24 @@ inline int key_groups(int block, const WorkMap& w, int64_t items) {
   return items <= 1200 && w.mean >= (items <= 768 ? 24 : 32) && ((items - 1) / 256 % 2 == 0 || w.longest >= 2LL * w.mean) ? 2 : 1;
 }
 
-// dK/dV at D 64 with two waves per SIMD (see dkdv_body): groups of waves; 0: the forms of key_groups with one wave.
-// Whole backward pass, us, key_groups / one / two / four groups (four: half blocks at block 128).
-//   block 128: 128 items L 2 19.2 / 22.1 / 21.7 / 19.5, L 4 22.5 / 28.0 / 26.2 / 22.1, L 16 49.7 / 69.1 / 57.8 / 45.6; 256 items L 2
-//   24.7 / 25.1 / 24.6 / 28.5, L 4 33.5 / 33.5 / 32.1 / 35.3, L 16 83.8 / 84.2 / 76.0 / 80.0; 384 items L 1 30.3 / 26.5 / 31.8, L 32 276 /
-//   229 / 236; radial lists: 522 items (mean 57) 660 / 595 / 579, 714 (112) 1417 / 1305 / 1275, 996 (83) 1434 / 1284 / 1275, 2478 (165)
-//   6914 / 6272 / 6255, 7414 (250) 31.7 / 28.0 / 28.5 ms.
-//   block 64: 192 items L 6 19.9 / 22.9 / 20.1 / 20.4, L 16 30.4 / 40.4 / 30.7 / 29.0, L 32 47.2 / 67.7 / 47.1 / 42.7; 384 items L 2
-//   19.0 / 19.2 / 19.1 / 23.7, L 4 23.3 / 24.5 / 22.6 / 27.6, L 32 83.7 / 92.4 / 70.4 / 76.6; 768 items L 8 53.4 / 43.4 / 45.2, L 32 132 / 122 /
-//   119; 3200 items L 16 296 / 251 / 261, L 32 528 / 454 / 453; radial lists: 2136 items (172) 1800 / 1620 / 1563.
-inline int key_groups_two_waves(int block, const WorkMap& w, int64_t items) {
-  if (block == 128) {
-    if (items <= kOneRound) return w.longest < 4 ? 0 : items <= 128 ? 4 : 2;
-    return items > 512 && items <= 1024 && w.mean >= 48 ? 2 : 1;
-  }
-  if (items <= kOneRound) return w.longest >= 8 ? 4 : 0;
-  if (items <= 512) return w.longest >= 4 ? 2 : 0;
-  return w.mean >= (items <= 1536 ? 16 : 32) ? 2 : 1;
+// D 64, dK/dV and dQ in one launch: groups of waves per workgroup; 0: two launches, one after the other.
+// Each alone leaves compute units idle, a small one because it has too few workgroups or waves, a larger one where it ends.
+// Neither needs the other's results, both fit two waves per SIMD, and a workgroup of two groups is half a compute unit's LDS.  Up to 128 parts
+// of 32 rows, where each of the 256 workgroups has a compute unit: groups of one wave; up to kOneRound blocks two groups of 64 rows, so that
+// two workgroups share a compute unit; above, two groups of a block of 64, or one of a block of 128.
+// Backward pass, us, the best forms of two launches / one, (items, list length):
+//   one wave, block 64: (64; 32) 30.6 / 20.0, (4; 1) 15.6 / 13.2 (the host takes 13); block 128: (32; 8) 22.2 / 13.6, (32; 32) 48.4 / 29.5, (16; 16)
+//     30.1 / 18.2.  At 128 to 256 parts: block 64 (128; 32) 33.0 / 31.5, two groups 28.6; block 128 (64; 16) 33.0 / 31.4, two groups 27.9.
+//   two groups, block 64: (192; 4) 17.4 / 13.1, (256; 32) 46.1 / 39.7, (288; 8) 28.4 / 23.1, (384; 32) 71.9 / 59.5, (512; 32) 80.3 / 75.1, (768; 16)
+//     74.7 / 65.7, (1024; 32) 152 / 149, (1536; 16) 132 / 124, radial lists (1100; mean 57) 847 / 769.
+//   half blocks of two groups, block 128: (128; 2) 18.4 / 13.5, (128; 16) 46.1 / 39.7, (256; 16) 76.9 / 73.6, radial lists (250; 29) 228 / 206.
+//   one group, block 128: (288; 4) 43.7 / 36.4, (288; 24) 168 / 144, (512; 16) 143 / 137, (768; 16) 213 / 197, radial lists (550; 57) 939 / 836,
+//     (1330; 112) 2085 / 2038.
+//   above: radial lists, block 64 (2560) 2996 / 3015, block 128 (2580) 6284 / 6420.
+inline int both_groups(int block, int64_t items) {
+  if (items * (block / 32) <= kOneRound / 2) return 4;
+  if (items > 6 * kOneRound) return 0;
+  return block == 128 && items > kOneRound ? 1 : 2;
 }
 
 // Blocks of 128 above one round, whole blocks by one group: the launch takes ceil(items / 256) rounds of a workgroup per compute
