@@ -534,7 +534,7 @@ struct PairTile {
 };
 
 template <int D, int BLK, bool kExact>
-__global__ void __launch_bounds__(4 * BLK, 2) radial_bwd_dkdv_pairs_kernel(const BwdArgs a) {
+__device__ __forceinline__ void pairs_body(const BwdArgs& a, uint32_t id) {
   using T = PairTile<D, BLK>;
   using QT = SwzTile<D>;
   extern __shared__ __attribute__((aligned(1024))) char lds_all[];
@@ -550,7 +550,7 @@ __global__ void __launch_bounds__(4 * BLK, 2) radial_bwd_dkdv_pairs_kernel(const
   const int half16 = (lane >> 4) & 1;
 
   int32_t bh, kb;
-  if (!work_item(a.work_t, blockIdx.x, bh, kb)) return;
+  if (!work_item(a.work_t, id, bh, kb)) return;
   const int32_t b = bh / a.H, h = bh % a.H;
   const __bf16* qp = (const __bf16*)a.q.ptr + (int64_t)b * a.q.sb + (int64_t)h * a.q.sh;
   const __bf16* gp = (const __bf16*)a.dout.ptr + (int64_t)b * a.dout.sb + (int64_t)h * a.dout.sh;
@@ -1137,6 +1137,23 @@ __global__ void __launch_bounds__(2 * BLK / R * S, 2) radial_bwd_both_kernel(con
   else dq_body<D, BLK, kExact, S, R>(a, blockIdx.x - n_key);
 }
 
+template <int D, int BLK, bool kExact>
+__global__ void __launch_bounds__(4 * BLK, 2) radial_bwd_dkdv_pairs_kernel(const BwdArgs a) {
+  pairs_body<D, BLK, kExact>(a, blockIdx.x);
+}
+// The same at head dimension 128, blocks of 128: dK/dV in pairs of waves, dQ by two groups.
+template <int D, int BLK, bool kExact>
+__global__ void __launch_bounds__(4 * BLK, 2) radial_bwd_both_pairs_kernel(const BwdArgs a, uint32_t n_key) {
+  if (blockIdx.x < n_key) pairs_body<D, BLK, kExact>(a, blockIdx.x);
+  else dq_body<D, BLK, kExact, 2, 1>(a, blockIdx.x - n_key);
+}
+// With the hand-made schedule, one wave per SIMD: two groups of 64 rows each.
+template <int D, int BLK, bool kExact>
+__global__ void __launch_bounds__(256, 1) radial_bwd_both_hand_kernel(const BwdArgs a, uint32_t n_key) {
+  if (blockIdx.x < n_key) dkdv_body<D, BLK, kExact, 2, BLK / 64, false>(a, blockIdx.x);
+  else dq_body<D, BLK, kExact, 2, BLK / 64>(a, blockIdx.x - n_key);
+}
+
 template <int D, int BLK, bool kExact, int S, int R, bool kTwoWaves = false>
 int launch_dkdv(BwdArgs a, hipStream_t stream) {
   using T = BwdTile<D, BLK, S, R>;
@@ -1189,6 +1206,33 @@ int launch_both(BwdArgs a, hipStream_t stream) {
   return RADIAL_OK;
 }
 
+template <bool kExact>
+int launch_both_pairs(const BwdArgs& a, hipStream_t stream) {
+  constexpr int kKeyBytes = PairTile<128, 128>::kLdsBytes, kQueryBytes = DqTile<128, 128, 2, 1>::kLdsBytes;
+  constexpr int kBytes = kKeyBytes > kQueryBytes ? kKeyBytes : kQueryBytes;
+  const auto kernel = radial_bwd_both_pairs_kernel<128, 128, kExact>;
+  static DeviceOnce configured;
+  if (int rc = allow_dynamic_lds(configured, (const void*)kernel, kBytes)) return rc;
+  const uint32_t n_key = (uint32_t)work_grid(a.work_t, a.n_blocks);
+  kernel<<<dim3(n_key + (unsigned)work_grid(a.work, a.n_blocks)), dim3(512), kBytes, stream>>>(a, n_key);
+  RADIAL_HIP_TRY(hipGetLastError());
+  return RADIAL_OK;
+}
+template <int BLK, bool kExact>
+int launch_both_hand(BwdArgs a, hipStream_t stream) {
+  constexpr int kKeyBytes = BwdTile<128, BLK, 2, BLK / 64>::kLdsBytes, kQueryBytes = DqTile<128, BLK, 2, BLK / 64>::kLdsBytes;
+  constexpr int kBytes = kKeyBytes > kQueryBytes ? kKeyBytes : kQueryBytes;
+  const auto kernel = radial_bwd_both_hand_kernel<128, BLK, kExact>;
+  static DeviceOnce configured;
+  if (int rc = allow_dynamic_lds(configured, (const void*)kernel, kBytes)) return rc;
+  a.work.ordered *= BLK / 64;  // at most kOneRound items, where all heads are taken by list length
+  a.work_t.ordered *= BLK / 64;
+  const uint32_t n_key = (uint32_t)work_grid(a.work_t, a.n_blocks);
+  kernel<<<dim3(n_key + (unsigned)work_grid(a.work, a.n_blocks)), dim3(256), kBytes, stream>>>(a, n_key);
+  RADIAL_HIP_TRY(hipGetLastError());
+  return RADIAL_OK;
+}
+
 template <int D, int BLK, bool kExact>
 int launch(const BwdArgs& a, hipStream_t stream) {
   const int64_t rows = (int64_t)a.B * a.H * a.N;
@@ -1212,14 +1256,15 @@ int launch(const BwdArgs& a, hipStream_t stream) {
     RADIAL_HIP_TRY(hipGetLastError());
     return RADIAL_OK;
   }
+  if (both_by_hand(BLK, items)) return launch_both_hand<BLK, kExact>(a, stream);
+  if (BLK == 128 && both_in_pairs(items)) return launch_both_pairs<kExact>(a, stream);
   const int kv = key_groups(BLK, a.work_t, items), q = query_groups(D, BLK, a.work, items, false);
   int rc;
-  if (D == 128 && BLK == 128 && kv == 1) rc = launch_dkdv_pairs<128, kExact>(a, stream);
+  if (D == 128 && BLK == 128) rc = launch_dkdv_pairs<128, kExact>(a, stream);
   else rc = kv == 2 ? launch_dkdv<D, BLK, kExact, 2, BLK / 64>(a, stream) : launch_dkdv<D, BLK, kExact, 1, 1>(a, stream);
   if (rc) return rc;
-  if (single_waves(BLK, a.work, items)) rc = launch_dq<D, BLK, kExact, 4, BLK / 32>(a, stream);
-  else if (q == 4) rc = launch_dq<D, BLK, kExact, 4, BLK / 64>(a, stream);
-  else rc = q == 2 ? launch_dq<D, BLK, kExact, 2, 1>(a, stream) : launch_dq<D, BLK, kExact, 1, 1>(a, stream);
+  if (BLK == 64 && q == 4) rc = launch_dq<D, 64, kExact, 4, 1>(a, stream);
+  else rc = BLK == 64 && q == 2 ? launch_dq<D, 64, kExact, 2, 1>(a, stream) : launch_dq<D, BLK, kExact, 1, 1>(a, stream);
   if (rc) return rc;
   RADIAL_HIP_TRY(hipGetLastError());
   return RADIAL_OK;

@@ -274,6 +274,17 @@ inline int both_groups(int block, int64_t items) {
   return block == 128 && items > kOneRound ? 1 : 2;
 }
 
+// The same at D 128.  By hand, 4 waves with a compute unit each for either half of the work: while all workgroups of both, of 64 rows,
+// have one.  In pairs of waves, blocks of 128 (8 waves for either): up to 6 rounds.  In blocks of 64 the hand-made schedule, one wave per
+// SIMD, would hold dQ to one as well.  Backward pass, us, two launches / one, (items, list length):
+//   by hand, block 128: (8; 2) 22.1 / 13.5, (40; 8) 37.4 / 25.8, (60; 4) 27.4 / 18.6, (64; 32) 104 / 79.5, above (100; 16) 71.5 / 79.5; block 64: (16; 4) 20.9
+//     / 13.3, (64; 16) 37.3 / 25.5, (128; 8) 27.2 / 18.4, (128; 32) 59.4 / 43.9, above (192; 8) 31.5 / 31.3, (256; 32) 77.3 / 76.6.
+//   in pairs: (64; 32) 104 / 109, (100; 16) 71.5 / 65.3, (128; 1) 24.7 / 16.3, (128; 32) 135 / 129, (256; 32) 248 / 237, (288; 16) 209 / 164, (384; 32)
+//     405 / 355, (512; 16) 252 / 250, (640; 16) 347 / 310, radial lists (550; 57) 1697 / 1452, (1280) 5802 / 5760;
+//     above (2070) 8078 / 7960, (2560) 11510 / 11690, (2787) 33460 / 33330, (3000; 16) 1510 / 1553.
+inline bool both_by_hand(int block, int64_t items) { return items * (block / 64) <= kOneRound / 2; }
+inline bool both_in_pairs(int64_t items) { return items <= 6 * kOneRound; }
+
 // Blocks of 128 above one round, whole blocks by one group: the launch takes ceil(items / 256) rounds of a workgroup per compute
 // unit (two share one), so the items % 256 last ones keep most of the chip waiting for a whole list.  Up to half a
 // round of them are taken in two halves each, of 64 rows and two groups that walk half the list: the

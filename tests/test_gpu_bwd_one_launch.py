@@ -1,5 +1,6 @@
-"""Backward at head dimension 64, where dK/dV and dQ are one launch up to 1536 blocks: the sizes where its form changes (128
-parts of 32 rows, 256 blocks, 1536 blocks), ragged ends, empty and short lists and the token rule, against float64."""
+"""Backward where dK/dV and dQ are one launch: the sizes where its form changes (D 64: 128 parts of 32 rows, 256 blocks, 1536
+blocks; D 128: 128 parts of 64 rows, 1536 blocks of 128), ragged ends, empty and short lists and the token rule, against
+float64."""
 import numpy as np
 import pytest
 
@@ -8,16 +9,17 @@ from test_gpu_list_split import reference
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("block, H, N, most", [
+@pytest.mark.parametrize("D, block, H, N, most", [(64, *c) for c in [
     (64, 1, 40, 1), (64, 2, 32 * 64 - 1, 32), (64, 5, 13 * 64 - 33, 13), (64, 8, 32 * 64, 7), (64, 13, 20 * 64 + 31, 12), (64, 48, 32 * 64, 5),
     (64, 53, 29 * 64 - 63, 29), (128, 1, 100, 1), (128, 4, 8 * 128 - 95, 8), (128, 3, 11 * 128, 5), (128, 16, 16 * 128 - 1, 9),
-    (128, 17, 15 * 128 + 65, 15), (128, 96, 16 * 128, 4), (128, 53, 29 * 128 - 33, 11)])
+    (128, 17, 15 * 128 + 65, 15), (128, 96, 16 * 128, 4), (128, 53, 29 * 128 - 33, 11)]] + [(128, *c) for c in [
+    (64, 1, 40, 1), (64, 4, 32 * 64 - 33, 32), (64, 3, 43 * 64 + 1, 9), (128, 1, 100, 1), (128, 4, 16 * 128 - 95, 16), (128, 5, 13 * 128, 3),
+    (128, 16, 16 * 128 - 1, 9), (128, 17, 15 * 128 + 65, 15), (128, 48, 32 * 128 - 31, 4), (128, 53, 29 * 128 - 33, 11)]])
 @pytest.mark.parametrize("rule", [False, True])
-def test_gradients_match_float64(block, H, N, most, rule):
+def test_gradients_match_float64(D, block, H, N, most, rule):
     import torch
     from paper_2506_19852_amd import binding as rb
-    print(f"block={block} H={H} N={N} most={most} rule={rule}", flush=True)
-    D = 64
+    print(f"D={D} block={block} H={H} N={N} most={most} rule={rule}", flush=True)
     g = torch.Generator(device="cuda").manual_seed(N + H)
     q, k, v, do = (torch.randn((1, N, H, D), device="cuda", generator=g).bfloat16().transpose(1, 2) for _ in range(4))
     nb, scale = -(-N // block), D ** -0.5
