@@ -1233,6 +1233,14 @@ int launch_both_hand(BwdArgs a, hipStream_t stream) {
   return RADIAL_OK;
 }
 
+// Whether two tensors of a call may share memory (by their extents).
+bool may_overlap(const BwdArgs& a, int D, const TensorArg& x, const TensorArg& y) {
+  const auto end = [&](const TensorArg& t) {
+    return (uintptr_t)t.ptr + 2 * (uintptr_t)((int64_t)(a.B - 1) * t.sb + (int64_t)(a.H - 1) * t.sh + (int64_t)(a.N - 1) * t.sn + D);
+  };
+  return (uintptr_t)x.ptr < end(y) && (uintptr_t)y.ptr < end(x);
+}
+
 template <int D, int BLK, bool kExact>
 int launch(const BwdArgs& a, hipStream_t stream) {
   const int64_t rows = (int64_t)a.B * a.H * a.N;
@@ -1242,8 +1250,10 @@ int launch(const BwdArgs& a, hipStream_t stream) {
     return fail(RADIAL_ESHAPE, "problem too large for one launch");
   bwd_prepare_kernel<D><<<dim3((unsigned)prep_grid), dim3(256), 0, stream>>>(a);
   const int64_t items = work_items(a.work, a.n_blocks);
+  // dQ reads no rows of Q and dO but those it replaces, so dq may be either's memory; dK/dV has to be finished with them then.
+  const bool apart = !may_overlap(a, D, a.dq, a.q) && !may_overlap(a, D, a.dq, a.dout);
   if constexpr (D == 64) {
-    switch (both_groups(BLK, items)) {
+    switch (apart ? both_groups(BLK, items) : 0) {
       case 4: return launch_both<BLK, kExact, 4, BLK / 32>(a, stream);
       case 2: return launch_both<BLK, kExact, 2, BLK / 64>(a, stream);
       case 1: return launch_both<BLK, kExact, 1, 1>(a, stream);
@@ -1256,8 +1266,8 @@ int launch(const BwdArgs& a, hipStream_t stream) {
     RADIAL_HIP_TRY(hipGetLastError());
     return RADIAL_OK;
   }
-  if (both_by_hand(BLK, items)) return launch_both_hand<BLK, kExact>(a, stream);
-  if (BLK == 128 && both_in_pairs(items)) return launch_both_pairs<kExact>(a, stream);
+  if (apart && both_by_hand(BLK, items)) return launch_both_hand<BLK, kExact>(a, stream);
+  if (apart && BLK == 128 && both_in_pairs(items)) return launch_both_pairs<kExact>(a, stream);
   const int kv = key_groups(BLK, a.work_t, items), q = query_groups(D, BLK, a.work, items, false);
   int rc;
   if (D == 128 && BLK == 128) rc = launch_dkdv_pairs<128, kExact>(a, stream);

@@ -54,3 +54,31 @@ def test_gradients_match_float64(D, block, H, N, most, rule):
             assert torch.isfinite(x).all(), (name, h)
             assert (x.double() - r).norm() <= 8e-3 * r.norm() + 1e-6, (name, h, (x.double() - r).norm() / r.norm())
     m.free()
+
+
+@pytest.mark.parametrize("D, block, H, nb", [(64, 64, 2, 9), (64, 64, 16, 30), (64, 128, 16, 16), (64, 128, 17, 30), (128, 64, 4, 32), (128, 128, 4, 9),
+                                             (128, 128, 17, 30)])
+@pytest.mark.parametrize("shared", ["q", "dout", "packed"])
+def test_dq_in_the_memory_of_q_or_dout(D, block, H, nb, shared):
+    """dK/dV reads all rows of Q and dO, so dQ must not replace them while it runs."""
+    import torch
+    from paper_2506_19852_amd import binding as rb
+    print(f"D={D} block={block} H={H} nb={nb} shared={shared}", flush=True)
+    N, scale = nb * block - 17, D ** -0.5
+    g = torch.Generator(device="cuda").manual_seed(N)
+    packed = torch.randn((1, N, 4, H, D), device="cuda", generator=g).bfloat16()  # q, k, v, dout side by side
+    q, k, v, do = (packed[:, :, i].transpose(1, 2) for i in range(4))
+    if shared != "packed":
+        q, do = q.contiguous(), do.contiguous()
+    m = rb.radial_mask_build_dense(N, block, rb.RADIAL_MASK_TRANSPOSE)
+    out, dq, dk, dv, dk2, dv2 = (torch.empty((1, H, N, D), dtype=torch.bfloat16, device="cuda") for _ in range(6))
+    lse = torch.empty((1, H, N), dtype=torch.float32, device="cuda")
+    ws = torch.empty(rb.radial_attn_bwd_workspace(1, H, N, D, m), dtype=torch.uint8, device="cuda")
+    rb.radial_attn_fwd(q, k, v, out, lse, m, scale)
+    rb.radial_attn_bwd(q, k, v, out, do, lse, dq, dk, dv, m, scale, ws)
+    into = do if shared == "dout" else q
+    rb.radial_attn_bwd(q, k, v, out, do, lse, into, dk2, dv2, m, scale, ws)
+    # sums in another order, then one bf16 rounding (2^-9) of dS and one of the result
+    for name, x, y in (("dq", into, dq), ("dk", dk2, dk), ("dv", dv2, dv)):
+        assert (x.double() - y.double()).norm() <= 8e-3 * y.double().norm(), name
+    m.free()
