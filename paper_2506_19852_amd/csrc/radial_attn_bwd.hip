@@ -1252,29 +1252,27 @@ int launch(const BwdArgs& a, hipStream_t stream) {
   const int64_t items = work_items(a.work, a.n_blocks);
   // dQ reads no rows of Q and dO but those it replaces, so dq may be either's memory; dK/dV has to be finished with them then.
   const bool apart = !may_overlap(a, D, a.dq, a.q) && !may_overlap(a, D, a.dq, a.dout);
+  const BackwardForm form = backward_form(D, BLK, a.work, a.work_t, items, apart);
+  int rc;
   if constexpr (D == 64) {
-    switch (apart ? both_groups(BLK, items) : 0) {
+    if (form.kind == BackwardForm::kTogether) switch (form.key) {
       case 4: return launch_both<BLK, kExact, 4, BLK / 32>(a, stream);
       case 2: return launch_both<BLK, kExact, 2, BLK / 64>(a, stream);
-      case 1: return launch_both<BLK, kExact, 1, 1>(a, stream);
+      default: return launch_both<BLK, kExact, 1, 1>(a, stream);
     }
-    // two waves per SIMD; in blocks of 64 two groups take fewer walks at once, which pays on long lists (3200 items L 16 251 / 261, L 32
-    // 454 / 453; radial lists: 2136 items, mean 172, 1620 / 1563)
-    int rc = BLK == 64 && a.work_t.mean >= 32 ? launch_dkdv<64, 64, kExact, 2, 1, true>(a, stream) : launch_dkdv<64, BLK, kExact, 1, 1, true>(a, stream);
-    if (rc) return rc;
-    if ((rc = launch_dq<64, BLK, kExact, 1, 1>(a, stream))) return rc;
-    RADIAL_HIP_TRY(hipGetLastError());
-    return RADIAL_OK;
+    rc = form.key == 2 ? launch_dkdv<64, BLK, kExact, 2, BLK / 64, true>(a, stream) : launch_dkdv<64, BLK, kExact, 1, 1, true>(a, stream);
+  } else {
+    if (form.kind == BackwardForm::kTogetherByHand) return launch_both_hand<BLK, kExact>(a, stream);
+    if constexpr (BLK == 128) {
+      if (form.kind == BackwardForm::kTogetherInPairs) return launch_both_pairs<kExact>(a, stream);
+      rc = form.key == 2 ? launch_dkdv<D, BLK, kExact, 2, 2>(a, stream) : launch_dkdv_pairs<128, kExact>(a, stream);
+    } else {
+      rc = form.key == 2 ? launch_dkdv<D, BLK, kExact, 2, 1>(a, stream) : launch_dkdv<D, BLK, kExact, 1, 1>(a, stream);
+    }
   }
-  if (apart && both_by_hand(BLK, items)) return launch_both_hand<BLK, kExact>(a, stream);
-  if (apart && BLK == 128 && both_in_pairs(items)) return launch_both_pairs<kExact>(a, stream);
-  const int kv = key_groups(BLK, a.work_t, items), q = query_groups(D, BLK, a.work, items, false);
-  int rc;
-  if (D == 128 && BLK == 128) rc = launch_dkdv_pairs<128, kExact>(a, stream);
-  else rc = kv == 2 ? launch_dkdv<D, BLK, kExact, 2, BLK / 64>(a, stream) : launch_dkdv<D, BLK, kExact, 1, 1>(a, stream);
   if (rc) return rc;
-  if (BLK == 64 && q == 4) rc = launch_dq<D, 64, kExact, 4, 1>(a, stream);
-  else rc = BLK == 64 && q == 2 ? launch_dq<D, 64, kExact, 2, 1>(a, stream) : launch_dq<D, BLK, kExact, 1, 1>(a, stream);
+  rc = form.query == 4 ? launch_dq<D, BLK, kExact, 4, BLK / 64>(a, stream)
+                       : form.query == 2 ? launch_dq<D, BLK, kExact, 2, 1>(a, stream) : launch_dq<D, BLK, kExact, 1, 1>(a, stream);
   if (rc) return rc;
   RADIAL_HIP_TRY(hipGetLastError());
   return RADIAL_OK;

@@ -243,13 +243,14 @@ inline int query_groups(int D, int block, const WorkMap& w, int64_t items, bool 
 // dK/dV holds one wave per SIMD: a compute unit takes one workgroup of 128 keys, one of two groups of 64, or two of
 // one group of 64, so that at block 64 two groups take ceil(items / 256) / 2 walks where one takes ceil(items / 512).
 //   block 128, half blocks, 64 items: L 1 0, L 2 -3, L 16 -27; 256 items, L 32: +13.
+//   block 64, D 64, where two workgroups of either form fit a compute unit: 288 items L 3 +1, L 4 -1, L 8 -5.5, L 16 -10, 512 items L 3 0, L 8 -5.4.
 //   block 64, D 128: 256 items L 2 +1, L 3 0, L 8 -7, L 32 -22; 300 items L 8 +2, L 16 -6, L 48 -40; 500 items L 48 +7;
 //   572 items L 26 -26 (with dQ); 600 items L 8 +2, L 16 -1, L 48 -34; 700 items L 16 +9, L 48 -33; 1000 items L 48 +18; 1200 items L 16 +23, L 48 -25,
 //   radial lists (mean 51, 1140 items) -9; 1300 items, L 48: +5.  One list far longer than the others (text, the sink's
 //   columns) makes up for a round: 891 items (mean 418, longest 891) -153 of 3219.
-inline int key_groups(int block, const WorkMap& w, int64_t items) {
+inline int key_groups(int D, int block, const WorkMap& w, int64_t items) {
   if (block == 128) return items <= 128 && w.longest >= 2 ? 2 : 1;
-  if (items <= kOneRound) return w.longest >= 3 ? 2 : 1;
+  if (items <= (D == 64 ? 2 * kOneRound : kOneRound)) return w.longest >= 3 ? 2 : 1;
   if (items <= 384) return w.longest >= 16 ? 2 : 1;
   return items <= 1200 && w.mean >= (items <= 768 ? 24 : 32) && ((items - 1) / 256 % 2 == 0 || w.longest >= 2LL * w.mean) ? 2 : 1;
 }
@@ -284,6 +285,29 @@ inline int both_groups(int block, int64_t items) {
 //     above (2070) 8078 / 7960, (2560) 11510 / 11690, (2787) 33460 / 33330, (3000; 16) 1510 / 1553.
 inline bool both_by_hand(int block, int64_t items) { return items * (block / 64) <= kOneRound / 2; }
 inline bool both_in_pairs(int64_t items) { return items <= 6 * kOneRound; }
+
+// What a backward call launches, the groups of waves per list in dK/dV and dQ.  apart: dq shares no memory with q and dout, so that dQ may run
+// beside dK/dV.  Where it may not, the kernels alone are best in the forms that either has by itself, not in those of a common launch, which
+// leave it half of each compute unit.  Backward pass into the memory of dout, us, equal lists of L, the forms of a common launch one after the
+// other / every list whole in one group / these: D 128, block 128, 64 items L 32 142 / 210 / 112, 128 items L 8 64.0 / 68.5 / 45.7, L 32 188 / 213 /
+// 116, 1536 items L 3 229 / 199 / 199; D 64, block 128, 64 items L 32 85.4 / 157 / 77.9, block 64, 128 items L 32 49.0 / 64.4 / 46.0, 1024 items
+// L 3 41.4 / 33.3 / 33.1; D 128, block 64, 128 items L 32 79.5 / - / 66.4.
+struct BackwardForm {
+  enum Kind { kOneAfterTheOther, kTogether, kTogetherByHand, kTogetherInPairs } kind;
+  int key, query;
+};
+inline BackwardForm backward_form(int D, int block, const WorkMap& w, const WorkMap& wt, int64_t items, bool apart) {
+  if (apart && D == 64) {
+    if (const int groups = both_groups(block, items)) return {BackwardForm::kTogether, groups, groups};
+  } else if (apart) {
+    if (both_by_hand(block, items)) return {BackwardForm::kTogetherByHand, 2, 2};
+    if (block == 128 && both_in_pairs(items)) return {BackwardForm::kTogetherInPairs, 1, 2};
+  }
+  // D 64 has two waves per SIMD in dK/dV; in blocks of 64 two groups take fewer walks at once, which pays on long lists (3200 items L 16
+  // 251 / 261, L 32 454 / 453; radial lists: 2136 items, mean 172, 1620 / 1563)
+  const int key = D == 64 && block == 64 && wt.mean >= 32 ? 2 : key_groups(D, block, wt, items);
+  return {BackwardForm::kOneAfterTheOther, key, query_groups(D, block, w, items, false)};
+}
 
 // Blocks of 128 above one round, whole blocks by one group: the launch takes ceil(items / 256) rounds of a workgroup per compute
 // unit (two share one), so the items % 256 last ones keep most of the chip waiting for a whole list.  Up to half a

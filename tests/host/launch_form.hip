@@ -1,14 +1,15 @@
 // The launch rules (radial_internal.h) on the host: for each input line
 //   head_dim block heads n_blocks nnz longest longest_t
 // one line "forward dq dkdv fp8 ordered ordered_q ordered_k": groups of waves per list in each kernel, and the heads that
-// go by list length in the forward, dQ and dK/dV kernels.
+// go by list length in the forward, dQ and dK/dV kernels.  Run with the word "backward": one line "kind key query kind key query", the
+// form of a backward call whose dq has memory of its own, and of one whose dq is the memory of q or dout.
 #include <stdio.h>
 
 #include "radial_internal.h"
 
 using namespace radial;
 
-int main() {
+int main(int argc, char**) {
   int D, block, heads, nb, longest, longest_t;
   long long nnz;
   int32_t order = 0;  // only looked at for being there
@@ -25,8 +26,13 @@ int main() {
     const WorkMap w = make_work_map(&m, Walk::kForward, heads, D), wq = make_work_map(&m, Walk::kQueryGrad, heads, D),
                   wt = make_work_map(&m, Walk::kKeyGrad, heads, D);
     const int64_t items = work_items(w, nb);
+    if (argc > 1) {
+      const BackwardForm apart = backward_form(D, block, wq, wt, items, true), after = backward_form(D, block, wq, wt, items, false);
+      printf("%d %d %d %d %d %d\n", apart.kind, apart.key, apart.query, after.kind, after.key, after.query);
+      continue;
+    }
     printf("%d %d %d %d %d %d %d\n", query_groups(D, block, w, items, true), query_groups(D, block, wq, items, false),
-           key_groups(block, wt, items), fp8_groups(w, items), w.ordered, wq.ordered, wt.ordered);
+           key_groups(D, block, wt, items), fp8_groups(w, items), w.ordered, wq.ordered, wt.ordered);
   }
   return 0;
 }

@@ -82,3 +82,34 @@ def test_dq_in_the_memory_of_q_or_dout(D, block, H, nb, shared):
     for name, x, y in (("dq", into, dq), ("dk", dk2, dk), ("dv", dv2, dv)):
         assert (x.double() - y.double()).norm() <= 8e-3 * y.double().norm(), name
     m.free()
+
+
+@pytest.mark.parametrize("D, block, H, nb, cut", [(64, 64, 2, 30, 33), (64, 64, 9, 32, 1), (64, 64, 24, 32, 0), (64, 128, 4, 13, 65), (64, 128, 8, 16, 0), (64, 128, 8, 17, 100),
+                                                  (128, 64, 9, 13, 31), (128, 64, 3, 100, 5), (128, 128, 4, 13, 65), (128, 128, 8, 16, 0), (128, 128, 8, 17, 100), (128, 128, 9, 32, 1)])
+@pytest.mark.parametrize("rule", [False, True])
+def test_dq_in_the_memory_of_dout_on_ragged_lists(D, block, H, nb, cut, rule):
+    """Every form that the kernels take one after the other in small launches: lists of no entry, of one, of a few and of all
+    blocks, rows that end in either half of a block, and the token rule."""
+    import torch
+    from paper_2506_19852_amd import binding as rb
+    print(f"D={D} block={block} H={H} nb={nb} cut={cut} rule={rule}", flush=True)
+    N, scale = nb * block - cut, D ** -0.5
+    g = torch.Generator(device="cuda").manual_seed(N)
+    q, k, v, do = (torch.randn((1, N, H, D), device="cuda", generator=g).bfloat16().transpose(1, 2) for _ in range(4))
+    if rule:
+        m = rb.radial_mask_build(N // 90, 90, block, 1, rb.RADIAL_MASK_TRANSPOSE | rb.RADIAL_MASK_TOKEN_EXACT, extra_tokens=N % 90)
+    else:
+        rng = np.random.default_rng(N)
+        rows = [np.sort(rng.choice(nb, size=(nb, 0, 1, 5, 12)[r % 5], replace=False)) for r in range(nb)]
+        row_ptr = np.concatenate([[0], np.cumsum([len(r) for r in rows])]).astype(np.int32)
+        m = rb.radial_mask_from_csr(N, block, row_ptr, np.concatenate(rows).astype(np.int32), rb.RADIAL_MASK_TRANSPOSE)
+    out, dq, dk, dv, dk2, dv2 = (torch.full_like(q, float("nan")) for _ in range(6))
+    lse = torch.empty((1, H, N), dtype=torch.float32, device="cuda")
+    ws = torch.empty(rb.radial_attn_bwd_workspace(1, H, N, D, m), dtype=torch.uint8, device="cuda")
+    rb.radial_attn_fwd(q, k, v, out, lse, m, scale)
+    rb.radial_attn_bwd(q, k, v, out, do, lse, dq, dk, dv, m, scale, ws)
+    rb.radial_attn_bwd(q, k, v, out, do, lse, do, dk2, dv2, m, scale, ws)
+    # sums in another order, then one bf16 rounding (2^-9) of dS and one of the result
+    for name, x, y in (("dq", do, dq), ("dk", dk2, dk), ("dv", dv2, dv)):
+        assert torch.isfinite(x).all() and (x.double() - y.double()).norm() <= 8e-3 * y.double().norm(), name
+    m.free()

@@ -21,13 +21,13 @@ def forms(tmp_path_factory):
                        stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     assert r.returncode == 0, r.stdout[-3000:]
 
-    def run(cases):
+    def run(cases, *words):
         """(D, block, heads, n_blocks, entries per list or (total, longest)) -> (forward, dq, dkdv, fp8, heads by length in forward, dq, dkdv)"""
         lines = []
         for D, block, heads, nb, per in cases:
             nnz, longest = (nb * per, per) if isinstance(per, int) else per
             lines.append(f"{D} {block} {heads} {nb} {nnz} {longest} {longest}")
-        r = subprocess.run([str(exe)], input="\n".join(lines), stdout=subprocess.PIPE, text=True, timeout=60)
+        r = subprocess.run([str(exe), *words], input="\n".join(lines), stdout=subprocess.PIPE, text=True, timeout=60)
         assert r.returncode == 0
         out = [tuple(map(int, line.split())) for line in r.stdout.split("\n") if line]
         assert len(out) == len(cases)
@@ -83,3 +83,20 @@ def test_long_heads_in_blocks_of_64_stay_with_slices(forms):
     assert [f[4:] for f in forms(cases)] == [
         (4, 4, 4), (0, 4, 4), (4, 4, 4), (0, 4, 4), (1, 1, 1), (0, 4, 4), (5, 5, 5), (0, 5, 5), (0, 6, 6), (3, 3, 3), (0, 3, 3),
         (7, 7, 7), (0, 7, 7), (8, 8, 8), (0, 8, 8), (0, 2, 2), (0, 0, 2), (4, 4, 4), (1, 1, 1)]
+
+
+def test_backward_into_the_memory_of_q_or_dout_keeps_its_groups(forms):
+    """Such a call runs dK/dV and dQ one after the other, each in the form that is best by itself: small launches are split
+    as dense in groups as where dq has memory of its own."""
+    after = 0
+    cases = [(64, 64, 2, 32, 32), (64, 64, 9, 32, 8), (64, 64, 16, 32, 2), (64, 64, 24, 32, 16), (64, 64, 60, 32, 32), (64, 128, 2, 32, 32), (64, 128, 8, 32, 8),
+             (128, 64, 2, 32, 32), (128, 64, 9, 32, 8), (128, 64, 12, 32, 16), (128, 128, 4, 32, 32), (128, 128, 8, 32, 8), (128, 128, 9, 32, 8)]
+    assert [f[3:] for f in forms(cases, "backward")] == [
+        (after, 2, 4), (after, 2, 2), (after, 1, 1), (after, 1, 1), (after, 2, 1), (after, 2, 4), (after, 1, 2),
+        (after, 2, 4), (after, 1, 2), (after, 2, 2), (after, 2, 4), (after, 1, 2), (after, 1, 1)]
+    # with memory of its own: one launch in groups (1), by hand (2) or in pairs (3) up to these sizes
+    cases = [(64, 64, 2, 32, 1), (64, 64, 2, 33, 1), (64, 64, 48, 32, 1), (64, 64, 49, 32, 1), (64, 128, 1, 32, 1), (64, 128, 8, 32, 1), (64, 128, 8, 33, 1), (64, 128, 48, 33, 1),
+             (128, 64, 4, 32, 1), (128, 64, 4, 33, 1), (128, 128, 2, 32, 1), (128, 128, 2, 33, 1), (128, 128, 48, 32, 1), (128, 128, 48, 33, 1)]
+    assert [f[:3] for f in forms(cases, "backward")] == [
+        (1, 4, 4), (1, 2, 2), (1, 2, 2), (0, 1, 1), (1, 4, 4), (1, 2, 2), (1, 1, 1), (0, 1, 1),
+        (2, 2, 2), (0, 1, 1), (2, 2, 2), (3, 1, 2), (3, 1, 2), (0, 1, 1)]
