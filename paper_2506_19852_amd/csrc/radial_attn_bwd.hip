@@ -109,6 +109,7 @@ template <int D, int BLK, bool kExact, int S, int R, bool kTwoWaves>
 __device__ __forceinline__ void dkdv_body(const BwdArgs& a, uint32_t id) {
   using T = BwdTile<D, BLK, S, R>;
   using QT = SwzTile<D>;  // Q, dO tiles: rows of D elements
+  static_assert(kTwoWaves == (D == 64), "the hand-made schedule deals the 8 softmax pairs of a half over the 8 k-steps of head dimension 128");
   extern __shared__ __attribute__((aligned(1024))) char lds_all[];
 
   const int lane = threadIdx.x & 63;
@@ -417,8 +418,7 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a, uint32_t id) {
         mfma32_vgpr(s[1], qfr[T::kSteps + t], kf[t]);
         mfma32_vgpr(dp[1], gfr[T::kSteps + t], vf[t]);
       }
-      if (t * 8 / T::kSteps != (t + 1) * 8 / T::kSteps) softmax_pair(0, t * 8 / T::kSteps);
-      if (T::kSteps == 4) softmax_pair(0, 2 * t + 1);
+      softmax_pair(0, t);
       __builtin_amdgcn_sched_barrier(0);
     }
     mfma_results_settle(s[1], dp[1]);
@@ -1258,7 +1258,8 @@ int launch(const BwdArgs& a, hipStream_t stream) {
     if (form.kind == BackwardForm::kTogether) switch (form.key) {
       case 4: return launch_both<BLK, kExact, 4, BLK / 32>(a, stream);
       case 2: return launch_both<BLK, kExact, 2, BLK / 64>(a, stream);
-      default: return launch_both<BLK, kExact, 1, 1>(a, stream);
+      default:  // blocks of 128 only
+        if constexpr (BLK == 128) return launch_both<BLK, kExact, 1, 1>(a, stream);
     }
     rc = form.key == 2 ? launch_dkdv<64, BLK, kExact, 2, BLK / 64, true>(a, stream) : launch_dkdv<64, BLK, kExact, 1, 1, true>(a, stream);
   } else {
