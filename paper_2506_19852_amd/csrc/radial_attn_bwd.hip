@@ -1233,14 +1233,6 @@ int launch_both_hand(BwdArgs a, hipStream_t stream) {
   return RADIAL_OK;
 }
 
-// Whether two tensors of a call may share memory (by their extents).
-bool may_overlap(const BwdArgs& a, int D, const TensorArg& x, const TensorArg& y) {
-  const auto end = [&](const TensorArg& t) {
-    return (uintptr_t)t.ptr + 2 * (uintptr_t)((int64_t)(a.B - 1) * t.sb + (int64_t)(a.H - 1) * t.sh + (int64_t)(a.N - 1) * t.sn + D);
-  };
-  return (uintptr_t)x.ptr < end(y) && (uintptr_t)y.ptr < end(x);
-}
-
 template <int D, int BLK, bool kExact>
 int launch(const BwdArgs& a, hipStream_t stream) {
   const int64_t rows = (int64_t)a.B * a.H * a.N;
@@ -1251,7 +1243,7 @@ int launch(const BwdArgs& a, hipStream_t stream) {
   bwd_prepare_kernel<D><<<dim3((unsigned)prep_grid), dim3(256), 0, stream>>>(a);
   const int64_t items = work_items(a.work, a.n_blocks);
   // dQ reads no rows of Q and dO but those it replaces, so dq may be either's memory; dK/dV has to be finished with them then.
-  const bool apart = !may_overlap(a, D, a.dq, a.q) && !may_overlap(a, D, a.dq, a.dout);
+  const bool apart = !may_overlap(a.B, a.H, a.N, D, a.dq, a.q) && !may_overlap(a.B, a.H, a.N, D, a.dq, a.dout);
   const BackwardForm form = backward_form(D, BLK, a.work, a.work_t, items, apart);
   int rc;
   if constexpr (D == 64) {

@@ -339,6 +339,34 @@ struct TensorArg {
   int64_t sb, sh, sn;  // element strides
 };
 
+// Whether two bf16 tensors of a call, [B, H, N, D] each, may share memory.  They do not if their extents are apart, or if both stay
+// in parts of one period of memory that are apart, as slices of a packed [B, N, 4, H, D] or [B, H, N, 2, D] do.
+inline bool may_overlap(int32_t B, int32_t H, int32_t N, int D, const TensorArg& x, const TensorArg& y) {
+  const int32_t sizes[] = {B, H, N};
+  const auto extent = [&](const TensorArg& t) { return (B - 1) * t.sb + (H - 1) * t.sh + (N - 1) * t.sn + D; };
+  const int64_t apart = ((int64_t)(uintptr_t)y.ptr - (int64_t)(uintptr_t)x.ptr) / 2;  // elements; tensors are 16-byte aligned
+  if (apart >= extent(x) || -apart >= extent(y)) return false;
+  // Elements of one period that the tensor touches, from its first one on; 0: it does not repeat with this period.
+  const auto touched = [&](const TensorArg& t, int64_t period) -> int64_t {
+    const int64_t strides[] = {t.sb, t.sh, t.sn};
+    int64_t n = D;
+    for (int i = 0; i < 3; ++i) {
+      if (sizes[i] == 1 || strides[i] % period == 0) continue;
+      if (strides[i] > period) return 0;
+      n += (sizes[i] - 1) * strides[i];
+    }
+    return n <= period ? n : 0;
+  };
+  const int64_t periods[] = {x.sb, x.sh, x.sn};
+  for (int i = 0; i < 3; ++i) {
+    if (sizes[i] == 1 || periods[i] == 0) continue;
+    const int64_t of_x = touched(x, periods[i]), of_y = touched(y, periods[i]);
+    const int64_t at = (apart % periods[i] + periods[i]) % periods[i];
+    if (of_x && of_y && at >= of_x && at + of_y <= periods[i]) return false;
+  }
+  return true;
+}
+
 struct FwdArgs {
   TensorArg q, k, v, o;
   float* lse;  // may be null

@@ -113,3 +113,29 @@ def test_dq_in_the_memory_of_dout_on_ragged_lists(D, block, H, nb, cut, rule):
     for name, x, y in (("dq", do, dq), ("dk", dk2, dk), ("dv", dv2, dv)):
         assert torch.isfinite(x).all() and (x.double() - y.double()).norm() <= 8e-3 * y.double().norm(), name
     m.free()
+
+
+@pytest.mark.parametrize("D, block, H, nb", [(64, 64, 2, 9), (64, 128, 17, 30), (128, 64, 4, 32), (128, 128, 4, 9), (128, 128, 17, 30)])
+@pytest.mark.parametrize("beside", ["q", "dout"])
+def test_dq_beside_q_or_dout_in_one_buffer(D, block, H, nb, beside):
+    """A slice of a packed buffer that shares no element with q and dout: same kernels, same bits, and the other slices stay."""
+    import torch
+    from paper_2506_19852_amd import binding as rb
+    print(f"D={D} block={block} H={H} nb={nb} beside={beside}", flush=True)
+    N, scale = nb * block - 17, D ** -0.5
+    g = torch.Generator(device="cuda").manual_seed(N)
+    packed = torch.randn((1, N, 4, H, D), device="cuda", generator=g).bfloat16()
+    slices = [packed[:, :, i].transpose(1, 2) for i in range(4)]
+    k, v, other = (torch.randn((1, H, N, D), device="cuda", generator=g).bfloat16() for _ in range(3))
+    q, do = (slices[1], other) if beside == "q" else (other, slices[1])
+    m = rb.radial_mask_build_dense(N, block, rb.RADIAL_MASK_TRANSPOSE)
+    out, dq, dk, dv, dk2, dv2 = (torch.empty((1, H, N, D), dtype=torch.bfloat16, device="cuda") for _ in range(6))
+    lse = torch.empty((1, H, N), dtype=torch.float32, device="cuda")
+    ws = torch.empty(rb.radial_attn_bwd_workspace(1, H, N, D, m), dtype=torch.uint8, device="cuda")
+    rb.radial_attn_fwd(q, k, v, out, lse, m, scale)
+    rb.radial_attn_bwd(q, k, v, out, do, lse, dq, dk, dv, m, scale, ws)
+    before = packed.clone()
+    rb.radial_attn_bwd(q, k, v, out, do, lse, slices[2], dk2, dv2, m, scale, ws)
+    for name, x, y in (("dq", slices[2], dq), ("dk", dk2, dk), ("dv", dv2, dv), *((f"slice {i}", packed[:, :, i], before[:, :, i]) for i in (0, 1, 3))):
+        assert torch.equal(x, y), name
+    m.free()
