@@ -117,7 +117,11 @@ __device__ __forceinline__ void fwd_body(const FwdArgs& a, int32_t bh, int32_t q
   const int g = lane >> 5;    // which half of the 16-wide MFMA k-slice this lane feeds
 
   const uint64_t t_begin = kTrace ? __builtin_amdgcn_s_memrealtime() : 0;
-  const int32_t b = bh / a.H, h = bh % a.H;
+  // The division by the number of heads waits for that argument; the tensors' arguments are asked for before it (left to itself
+  // the compiler loads them after it, another 0.1 to 0.2 us: D 64, block 128, 288 items L 3 12.3 / 12.1 us, 640 items L 1 11.1 / 10.9).
+  int32_t heads = a.H;
+  asm("" : "+s"(heads) : "s"(a.q.ptr), "s"(a.k.ptr), "s"(a.row_ptr));
+  const int32_t b = bh / heads, h = bh % heads;
 
   const __bf16* qp = (const __bf16*)a.q.ptr + (int64_t)b * a.q.sb + (int64_t)h * a.q.sh;
   const __bf16* kp = (const __bf16*)a.k.ptr + (int64_t)b * a.k.sb + (int64_t)h * a.k.sh;

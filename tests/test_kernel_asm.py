@@ -150,3 +150,28 @@ def test_stage_buffers_of_unsplit_kernels_have_a_constant_address(source, kernel
     assert sizes
     for name, size in sizes:
         assert int(size) >= 32768, name
+
+
+def test_unsplit_forward_asks_for_its_arguments_before_it_divides(tmp_path):
+    """The pointers and strides of Q and K (the first 64 bytes of the arguments) are on their way while the workgroup divides
+    its index by the number of heads: loaded after that, they hold up every launch."""
+    if not os.path.exists(HIPCC) and shutil.which(HIPCC) is None:
+        pytest.skip("hipcc not available")
+    import sys
+    sys.path.insert(0, ROOT)
+    from paper_2506_19852_amd import build as hip_build
+    out = tmp_path / "kernels.s"
+    cmd = [HIPCC, *hip_build.FLAGS, "--cuda-device-only", "-S", os.path.join(hip_build.CSRC, "radial_attn_fwd.hip"), "-o", str(out)]
+    r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    assert r.returncode == 0, r.stdout[-3000:]
+    found = 0
+    for name, body in kernels(out.read_text().split("\n"), "radial_fwd_kernel"):
+        if "ELi1ELi1EEE" not in name:
+            continue
+        found += 1
+        code = list(instructions(body))
+        q_load = next(i for i, ins in enumerate(code) if ins.startswith("global_load_dwordx4"))
+        divide = max(i for i, ins in enumerate(code[:q_load]) if ins.startswith("v_rcp_iflag_f32"))
+        ask = next(i for i, ins in enumerate(code) if re.match(r"s_load_dwordx16 s\[\d+:\d+\], s\[0:1\], 0x0$", ins))
+        assert ask < divide, (name, ask, divide)
+    assert found == 8, found   # D in {64, 128} x block in {64, 128} x token rule on / off
