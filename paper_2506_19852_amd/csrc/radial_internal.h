@@ -269,9 +269,10 @@ inline int key_groups(int D, int block, const WorkMap& w, int64_t items) {
 //   one group, block 128: (288; 4) 43.7 / 36.4, (288; 24) 168 / 144, (512; 16) 143 / 137, (768; 16) 213 / 197, radial lists (550; 57) 939 / 836,
 //     (1330; 112) 2085 / 2038.
 //   above: radial lists, block 64 (2560) 2996 / 3015, block 128 (2580) 6284 / 6420.
-inline int both_groups(int block, int64_t items) {
+//   lists of one entry in blocks of 64, where two groups share nothing: 512 items 17.1 / 16.5, above 768 22.1 / 23.8, 1024 27.8 / 30.8, 1536 42.2 / 44.1.
+inline int both_groups(int block, const WorkMap& w, int64_t items) {
   if (items * (block / 32) <= kOneRound / 2) return 4;
-  if (items > 6 * kOneRound) return 0;
+  if (items > 6 * kOneRound || (block == 64 && items > 640 && w.mean < 2)) return 0;
   return block == 128 && items > kOneRound ? 1 : 2;
 }
 
@@ -283,8 +284,16 @@ inline int both_groups(int block, int64_t items) {
 //   in pairs: (64; 32) 104 / 109, (100; 16) 71.5 / 65.3, (128; 1) 24.7 / 16.3, (128; 32) 135 / 129, (256; 32) 248 / 237, (288; 16) 209 / 164, (384; 32)
 //     405 / 355, (512; 16) 252 / 250, (640; 16) 347 / 310, radial lists (550; 57) 1697 / 1452, (1280) 5802 / 5760;
 //     above (2070) 8078 / 7960, (2560) 11510 / 11690, (2787) 33460 / 33330, (3000; 16) 1510 / 1553.
+//   Either kind of workgroup fills a compute unit, so one launch of equal lists saves a round where the last one would be at most half full;
+//   elsewhere it saves only what unequal lists leave over, and lists of a few entries do not pay for dQ in two groups: (384; 1) 48.7 / 46.1, above
+//     (512; 1) 56.0 / 60.1, (768; 1) 80.4 / 86.8, (1280; 1) 127.5 / 138.7, (1024; 3) 151 / 162, (1280; 3) 185 / 198, (1536; 3) 225 / 242, (1024; 8) 270 / 275;
+//     by hand before the pairs / one (two launches in between): (448; 1) 51.1 / 55.8, (576; 1) 71.0 / 69.8, (640; 2) 89.6 / 84.1, (896; 1) 95.8 / 98.0, (896; 2) 118 / 114,
+//     (1408; 1) 144 / 152, (1408; 3) 213 / 209, (448; 4) 84.6 / 84.9.
 inline bool both_by_hand(int block, int64_t items) { return items * (block / 64) <= kOneRound / 2; }
-inline bool both_in_pairs(int64_t items) { return items <= 6 * kOneRound; }
+inline bool both_in_pairs(const WorkMap& w, int64_t items) {
+  if (items > 6 * kOneRound) return false;
+  return items <= kOneRound * 3 / 2 || w.mean >= 4 || (w.mean >= 2 && (items - 1) % kOneRound < kOneRound / 2);
+}
 
 // What a backward call launches, the groups of waves per list in dK/dV and dQ.  apart: dq shares no memory with q and dout, so that dQ may run
 // beside dK/dV.  Where it may not, the kernels alone are best in the forms that either has by itself, not in those of a common launch, which
@@ -298,10 +307,10 @@ struct BackwardForm {
 };
 inline BackwardForm backward_form(int D, int block, const WorkMap& w, const WorkMap& wt, int64_t items, bool apart) {
   if (apart && D == 64) {
-    if (const int groups = both_groups(block, items)) return {BackwardForm::kTogether, groups, groups};
+    if (const int groups = both_groups(block, w, items)) return {BackwardForm::kTogether, groups, groups};
   } else if (apart) {
     if (both_by_hand(block, items)) return {BackwardForm::kTogetherByHand, 2, 2};
-    if (block == 128 && both_in_pairs(items)) return {BackwardForm::kTogetherInPairs, 1, 2};
+    if (block == 128 && both_in_pairs(w, items)) return {BackwardForm::kTogetherInPairs, 1, 2};
   }
   // D 64 has two waves per SIMD in dK/dV; in blocks of 64 two groups take fewer walks at once, which pays on long lists (3200 items L 16
   // 251 / 261, L 32 454 / 453; radial lists: 2136 items, mean 172, 1620 / 1563)

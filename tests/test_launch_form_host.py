@@ -95,8 +95,16 @@ def test_backward_into_the_memory_of_q_or_dout_keeps_its_groups(forms):
         (after, 2, 4), (after, 2, 2), (after, 1, 1), (after, 1, 1), (after, 2, 1), (after, 2, 4), (after, 1, 2),
         (after, 2, 4), (after, 1, 2), (after, 2, 2), (after, 2, 4), (after, 1, 2), (after, 1, 1)]
     # with memory of its own: one launch in groups (1), by hand (2) or in pairs (3) up to these sizes
-    cases = [(64, 64, 2, 32, 1), (64, 64, 2, 33, 1), (64, 64, 48, 32, 1), (64, 64, 49, 32, 1), (64, 128, 1, 32, 1), (64, 128, 8, 32, 1), (64, 128, 8, 33, 1), (64, 128, 48, 33, 1),
-             (128, 64, 4, 32, 1), (128, 64, 4, 33, 1), (128, 128, 2, 32, 1), (128, 128, 2, 33, 1), (128, 128, 48, 32, 1), (128, 128, 48, 33, 1)]
+    cases = [(64, 64, 2, 32, 1), (64, 64, 2, 33, 1), (64, 64, 48, 32, 4), (64, 64, 49, 32, 4), (64, 128, 1, 32, 1), (64, 128, 8, 32, 1), (64, 128, 8, 33, 1), (64, 128, 48, 33, 1),
+             (128, 64, 4, 32, 1), (128, 64, 4, 33, 1), (128, 128, 2, 32, 1), (128, 128, 2, 33, 1), (128, 128, 48, 32, 4), (128, 128, 48, 33, 4)]
     assert [f[:3] for f in forms(cases, "backward")] == [
         (1, 4, 4), (1, 2, 2), (1, 2, 2), (0, 1, 1), (1, 4, 4), (1, 2, 2), (1, 1, 1), (0, 1, 1),
         (2, 2, 2), (0, 1, 1), (2, 2, 2), (3, 1, 2), (3, 1, 2), (0, 1, 1)]
+
+
+def test_backward_of_very_short_lists_is_one_launch_only_where_that_saves_a_round(forms):
+    """D 128 in blocks of 128: lists of one entry up to 384 blocks, of two and three also where the last round of 256 is at most
+    half full.  D 64 in blocks of 64: lists of one entry up to 640 blocks."""
+    cases = [(128, 128, *c) for c in ((12, 32, 1), (35, 11, 1), (16, 32, 1), (16, 32, 3), (20, 32, 1), (20, 32, 2), (20, 32, 3), (641, 1, 2), (13, 59, 2), (48, 32, 3), (16, 32, 4), (48, 32, 4))]
+    assert [f[0] for f in forms(cases, "backward")] == [3, 0, 0, 0, 0, 3, 3, 0, 0, 0, 3, 3]
+    assert [f[0] for f in forms([(64, 64, 20, 32, 1), (64, 64, 641, 1, 1), (64, 64, 48, 32, 1), (64, 64, 48, 32, 2), (64, 128, 48, 32, 1)], "backward")] == [1, 0, 0, 1, 1]
