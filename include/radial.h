@@ -175,7 +175,9 @@ RADIAL_API size_t radial_attn_bwd_workspace(int32_t B, int32_t H, int32_t N, int
  *   P = exp(scale*Q K^T - lse) on listed blocks,  dV = P^T dO,  dP = dO V^T,
  *   delta = rowsum(dO * O),  dS = P * (dP - delta),  dQ = scale * dS K,  dK = scale * dS^T Q.
  *   out, lse : as produced by radial_attn_fwd with the same q, k, v, mask, scale;
- *   dq, dk, dv : outputs, bf16, fully overwritten;
+ *   dq, dk, dv : outputs, bf16, fully overwritten.  dq may be the memory of q or of dout if it has the same
+ *               strides (small problems then run longer: dK/dV has to finish before dQ starts), and any of them the
+ *               memory of out; apart from that they may not share elements with the inputs or with each other;
  *   workspace : device memory of at least radial_attn_bwd_workspace(...) bytes, 256-byte
  *               aligned, contents ignored on entry and undefined on return.
  * The mask must carry RADIAL_MASK_TRANSPOSE (ESHAPE otherwise).  Allocates nothing. */

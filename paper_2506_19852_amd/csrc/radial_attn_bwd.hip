@@ -1194,7 +1194,9 @@ int launch_dq(BwdArgs a, hipStream_t stream) {
 template <int BLK, bool kExact, int S, int R>
 int launch_both(BwdArgs a, hipStream_t stream) {
   constexpr int kKeyBytes = BwdTile<64, BLK, S, R>::kLdsBytes, kQueryBytes = DqTile<64, BLK, S, R>::kLdsBytes;
-  constexpr int kBytes = kKeyBytes > kQueryBytes ? kKeyBytes : kQueryBytes;
+  constexpr int kStatic = S == 1 ? kQueryBytes : 0;  // one group's stage buffers in dQ
+  constexpr int kBytes = S == 1 || kKeyBytes > kQueryBytes ? kKeyBytes : kQueryBytes;
+  static_assert((S == 4 ? 1 : 2) * (kStatic + kBytes) <= 160 * 1024, "two workgroups per compute unit; groups of one wave have it to themselves");
   const auto kernel = radial_bwd_both_kernel<64, BLK, kExact, S, R>;
   static DeviceOnce configured;
   if (int rc = allow_dynamic_lds(configured, (const void*)kernel, kBytes)) return rc;
