@@ -3,7 +3,8 @@
 //     P = exp(scale*Q K^T - LSE),  dV = P^T dO,  dP = dO V^T,  delta = rowsum(dO * O),
 //     dS = P * (dP - delta),       dQ = scale * dS K,          dK = scale * dS^T Q.
 //
-// Three kernels, no atomics (results are reproducible run to run):
+// Three parts, no atomics (results are reproducible run to run); dkdv and dq are workgroups of one launch where either alone
+// would leave the chip idle (backward_form), else kernels of their own:
 //   prepare : delta[b,h,q] = sum_d dO*O;
 //   dkdv    : one workgroup per (batch, head, key block) walks the transposed list (the query
 //             blocks that list this key block) in stages of 64 query rows.  Wave w owns 32
@@ -104,7 +105,7 @@ __device__ __forceinline__ void mfma_results_settle(f32x16& acc0, f32x16& acc1) 
 // 64 a stage has 32 MFMAs (1024 cycles) to 178 plain vector instructions and 32 exponentials (1220 cycles), so the vector
 // unit is what bounds it and one wave cannot keep it busy: 2478 items of block 128 (10 x 17 000 tokens) 4.75 -> 4.1 ms, the
 // step 9.34 -> 8.21 ms.  196 to 214 registers; held to 168 for a third wave it spills 23 (block 128) to 45: 1-2 % slower, in
-// blocks of 64 25 %.  Head dimension 128 needs 422 registers and has one wave.
+// blocks of 64 25 %.  Head dimension 128 needs 376 to 384 registers and has one wave.
 template <int D, int BLK, bool kExact, int S, int R, bool kTwoWaves>
 __device__ __forceinline__ void dkdv_body(const BwdArgs& a, uint32_t id) {
   using T = BwdTile<D, BLK, S, R>;
@@ -500,15 +501,15 @@ __global__ void __launch_bounds__(2 * BLK / R * S, 2) radial_bwd_dkdv_two_kernel
 }
 
 // dK/dV of head dimension 128, two waves per SIMD: a pair of waves shares 32 keys.  One wave of each kind has K, S, P and dV, the
-// other V, dP, dS and dK, so that either needs half the registers of a wave that does all four products (422).  The
-// second wave needs P: the first leaves it in LDS in float32, lane by lane (both products come out in the same
+// other V, dP, dS and dK, so that either needs little more than half the registers of a wave that does all four products (376 to 384).
+// The second wave needs P: the first leaves it in LDS in float32, lane by lane (both products come out in the same
 // layout), and the second takes it a stage later, when every P of that stage is behind the barrier anyway:
 //   stage u:  first wave   S(u), P(u) -> LDS, dV += P(u)^T dO(u)
 //             second wave  dS(u - 1) = P(u - 1) * (dP(u - 1) - delta), dP(u), dK += dS(u - 1)^T Q(u - 1)
 // so Q has three stage buffers and dO two, and the vector part of one wave falls on the matrix part of the other.
-// Wave w and wave w + kPairs share keys: they are on one SIMD.  212 registers (235 under the token rule), and a pair that
-// sees nothing of a stage skips it, which one wave with four products had no registers for.
-// The chip lowers its clock for the busier matrix pipes (8 x 126 360 tokens, radial lists: 46 % at 2.06 GHz -> 52 % at 1.9), so the large
+// Wave w and wave w + kPairs share keys: they are on one SIMD.  206 registers (235 under the token rule; beside dQ in one launch 250
+// and 256), and a pair that sees nothing of a stage skips it, which one wave with four products had no registers for.
+// The chip lowers its clock for the busier matrix pipes (8 x 126 360 tokens, radial lists: 46 % busy at 2.05 GHz -> 54 % at 1.87), so the large
 // launches gain least.  Backward pass, one wave with four products / pairs: 8 x 126 360 tokens 82.5 / 80.3 ms, 5 x 14 040 1728 / 1653 us,
 // 5 x 32 760 with the token rule 6284 / 5897, 12 x 3500 398 / 363; equal lists, 4096 blocks L 1 417 / 404, 256 L 32 254 / 242, 320 L 8
 // 129 / 119, 1680 L 12 679 / 633, 8 L 1 23.9 / 22.9.  What bounds it is LDS traffic: without the exchange of P (16 of 81 KiB per stage

@@ -131,10 +131,10 @@ constexpr int32_t kMaxOrdered = 16384;  // blocks up to which a mask carries the
 // workgroups for 480 items; D 128, lists of 12, forward 37.3 -> 23.4 us, forward and backward 140 -> 91).
 // Blocks of 128 go by length with all their heads, however many, while K and V of all of them are well within the last-level
 // cache (160 MB): the grid of slices starts 8 times the longest slice per head, the more of them without work the fewer
-// blocks a head has, and ends on whole heads.  By slices but for the last 8 heads / all by length, forward, us: 74 heads x 9 blocks 90.7 /
-// 64.4, 28 x 18 (D 64) 64.7 / 51.4, 26 x 17 (D 64) 60.6 / 46.3, 15 x 49 322 / 300, 33 x 38 433 / 399, 42 x 26 278 / 259, 27 x 140 (D 64) 2569 /
-// 2413, 36 x 47 646 / 654, 10 x 146 1447 / 1447, 10 x 110 844 / 854 (the runs of one side differ by 1.5 %); forward and backward 36 x 20 (D 64) 386 / 325, 12 x 64
-// (D 64) 1016 / 936, 12 x 69 2262 / 2283.
+// blocks a head has, and ends on whole heads.  By slices but for the last 8 heads / all by length, radial lists, heads x blocks, forward, us: 74 x 9
+// 87.9 / 64.1, 42 x 26 273 / 244, 33 x 38 403 / 382, 36 x 47 636 / 609, 15 x 49 303 / 283, 12 x 69 444 / 410, 10 x 110 838 / 812, 10 x 147 1303 / 1304, 20 x 20 79.9 / 79.7;
+// D 64 28 x 18 64.6 / 51.4, 26 x 17 60.0 / 46.5, 27 x 140 1892 / 1833; backward 74 x 9 290 / 212, 42 x 26 868 / 783, 12 x 69 1348 / 1354, 10 x 110 2602 / 2618, 10 x 147
+// 4430 / 4452 (the runs of one side differ by 1.5 %), D 64 36 x 20 245 / 226, 12 x 64 612 / 579.
 constexpr int64_t kOrderedWholeBytes = 256 << 20, kOrderedTailBytes = 160 << 20;
 constexpr int64_t kOneRound = 256;
 // Blocks of 64 tokens move twice the K and V per product, and by length the blocks that an XCD works on at one time
@@ -190,7 +190,8 @@ inline int64_t work_grid(const WorkMap& w, int32_t n_blocks) {
 // other at the same barriers.  All figures are kernel times in microseconds, one group / the form named,
 // on lists of equal length L unless said otherwise.
 // `groups` = 4 at block 128 and 2 in the dK/dV kernel at block 128 mean half blocks: two workgroups per block, of 64 rows each.
-// (The figures of query_groups and key_groups up to 128 items are from before single_waves, which comes first.)
+// The forward asks single_waves first (query_groups' forward figures at 64 items are from before it), the backward
+// backward_form: it comes to query_groups and key_groups above the sizes of a common launch and where dq is the memory of q or dout.
 
 // Two groups for 64-token blocks above kOneRound items: four workgroups of one group fit a compute unit, or two of two, so that
 // two groups take ceil(items / 512) / 2 walks where one takes ceil(items / 1024).
@@ -212,14 +213,13 @@ inline bool two_groups_pay_64(int D, const WorkMap& w, int64_t items) {
   return items <= 1536 && w.mean >= 12;
 }
 
-// Groups of a single wave, 32 rows per workgroup (in the forward 4 groups at D 128 and 8 at D 64, in dQ 4 at D 128; the backward at
-// D 64 has both_groups, and dK/dV at D 128 has LDS for two waves only and keeps the forms below): while all parts of all blocks still get a compute
-// unit of their own.  Such a launch spreads over 2 (block 64) or 4 (block 128) times the compute units of a workgroup per
-// block, and a wave that shares its stage buffers with nobody needs no barrier: in the forms above it waited there for 29 %
-// of its loop (64 items of D 64, block 64).  Best of the forms above / single waves, forward then backward, us: block 64, D 64, 64
-// items L 28 15.3 / 11.1; 99 items L 99 36.6 / 23.0; D 128, 22 items L 11 15.2 / 11.0; 128 items L 3 8.9 / 7.4 and 25.3 / 21.7,
-// L 1 7.5 / 7.7 and 17.3 / 18.4; block 128, D 128, 64 items L 1 7.8 / 8.3 and 24.7 / 24.1, L 2 10.0 / 8.6 and 26.8 / 23.5, L 8
-// 16.6 / 13.5 and 44.2 / 39.2; D 64 L 8 10.2 / 8.2 and 30.2 / 23.9.  (A forward call takes the host 7.4 us.)
+// Forward: groups of a single wave, 32 rows per workgroup, 4 groups at D 128 and 8 at D 64, while all parts of all blocks still get a compute
+// unit of their own (the backward at D 64 has the like in both_groups; dK/dV at D 128 has LDS for two such waves only).  The launch
+// spreads over 2 (block 64) or 4 (block 128) times the compute units of a workgroup per block, and a wave that shares its
+// stage buffers with nobody needs no barrier: in the forms below it waited there for 29 % of its loop (64 items of D 64, block 64).
+// Best of the forms below / single waves, us: block 64, D 64, 64 items L 28 15.3 / 11.1; 99 items L 99 36.6 / 23.0; D 128, 22 items
+// L 11 15.2 / 11.0; 128 items L 3 8.9 / 7.4, L 1 7.5 / 7.7; block 128, D 128, 64 items L 1 7.8 / 8.3, L 2 10.0 / 8.6, L 8 16.6 /
+// 13.5; D 64 L 8 10.2 / 8.2.  (A forward call takes the host 7.4 us.)
 inline bool single_waves(int block, const WorkMap& w, int64_t items) { return items * (block / 32) <= kOneRound && w.longest >= 2; }
 
 // Block 128, up to 256 items.  Forward, D 128: half blocks at 64 items L 2 10.5 / 11.0, L 3 12.6 / 12.2, L 16 41.3 / 25.8, at
@@ -240,7 +240,7 @@ inline int query_groups(int D, int block, const WorkMap& w, int64_t items, bool 
   return forward && D == 64 && items > 1536 && w.mean >= 32 ? 2 : 1;
 }
 
-// dK/dV holds one wave per SIMD: a compute unit takes one workgroup of 128 keys, one of two groups of 64, or two of
+// dK/dV at D 128 by hand holds one wave per SIMD: a compute unit takes one workgroup of 128 keys, one of two groups of 64, or two of
 // one group of 64, so that at block 64 two groups take ceil(items / 256) / 2 walks where one takes ceil(items / 512).
 //   block 128, half blocks, 64 items: L 1 0, L 2 -3, L 16 -27; 256 items, L 32: +13.
 //   block 64, D 64, where two workgroups of either form fit a compute unit: 288 items L 3 +1, L 4 -1, L 8 -5.5, L 16 -10, 512 items L 3 0, L 8 -5.4.
