@@ -2,14 +2,16 @@
 //   head_dim block heads n_blocks nnz longest longest_t
 // one line "forward dq dkdv fp8 ordered ordered_q ordered_k": groups of waves per list in each kernel, and the heads that
 // go by list length in the forward, dQ and dK/dV kernels.  Run with the word "backward": one line "kind key query kind key query", the
-// form of a backward call whose dq has memory of its own, and of one whose dq is the memory of q or dout.
+// form of a backward call whose dq has memory of its own, and of one whose dq is the memory of q or dout.  With "forward": one line
+// "single halved parts", whether a forward goes in groups of one wave, how many of its last blocks go in halves, and the workgroups
+// per block of the 8-bit forward.
 #include <stdio.h>
 
 #include "radial_internal.h"
 
 using namespace radial;
 
-int main(int argc, char**) {
+int main(int argc, char** argv) {
   int D, block, heads, nb, longest, longest_t;
   long long nnz;
   int32_t order = 0;  // only looked at for being there
@@ -26,6 +28,10 @@ int main(int argc, char**) {
     const WorkMap w = make_work_map(&m, Walk::kForward, heads, D), wq = make_work_map(&m, Walk::kQueryGrad, heads, D),
                   wt = make_work_map(&m, Walk::kKeyGrad, heads, D);
     const int64_t items = work_items(w, nb);
+    if (argc > 1 && argv[1][0] == 'f') {
+      printf("%d %d %d\n", single_waves(block, w, items), halved_items(w, items), fp8_parts(w, items));
+      continue;
+    }
     if (argc > 1) {
       const BackwardForm apart = backward_form(D, block, wq, wt, items, true), after = backward_form(D, block, wq, wt, items, false);
       printf("%d %d %d %d %d %d\n", apart.kind, apart.key, apart.query, after.kind, after.key, after.query);

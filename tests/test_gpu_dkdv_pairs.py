@@ -1,5 +1,5 @@
-"""The dK/dV kernel of head dimension 128 and blocks of 128, where two waves share 32 keys: launches just above the half
-blocks of smaller ones, lists of no entry, of one and of two (its second wave is a stage behind), of 64, 65 and 130 (the chunks in which a
+"""dK/dV of head dimension 128 and blocks of 128, where two waves share 32 keys, beside dQ in one launch (65 to 1536 blocks) and
+alone (above): lists of no entry, of one and of two (its second wave is a stage behind), of 64, 65 and 130 (the chunks in which a
 wave reads its list), ragged ends that leave waves without keys, and the token rule, where whole pairs skip stages,
 against float64."""
 import numpy as np
@@ -11,7 +11,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("H, N, most", [(9, 15 * 128 - 31, 15), (3, 43 * 128 - 97, 1), (9, 16 * 128, 2), (2, 65 * 128 + 1, 64), (2, 65 * 128, 65),
-                                        (1, 130 * 128 - 64, 130), (7, 19 * 128 + 33, 3)])
+                                        (1, 130 * 128 - 64, 130), (7, 19 * 128 + 33, 3),
+                                        (110, 14 * 128 - 31, 14), (110, 14 * 128 + 33, 1), (24, 65 * 128, 65), (24, 65 * 128 + 1, 64)])  # alone
 @pytest.mark.parametrize("rule", [0, 90, 700])
 def test_gradients_match_float64(H, N, most, rule):
     import torch

@@ -1,5 +1,5 @@
-"""The dK/dV kernel of head dimension 64 with two waves per SIMD: every number of groups at both block sizes, the sizes
-where it changes, ragged ends, empty and short lists and the token rule, against float64."""
+"""dK/dV of head dimension 64 with two waves per SIMD: beside dQ in one launch with every number of groups at both block sizes, and alone
+above 1536 blocks, ragged ends, empty and short lists and the token rule, against float64."""
 import numpy as np
 import pytest
 
@@ -8,12 +8,14 @@ from test_gpu_list_split import reference
 pytestmark = pytest.mark.gpu
 
 
-# items = heads * blocks; block 128: four groups to 128, two to 256, one, two from 513 to 1024 on long lists; block 64: four to
-# 256, two to 512, one or two above
+# items = heads * blocks.  One launch, block 128: groups of one wave to 32 items, two groups to 256, one to 1536; block 64: groups of one
+# wave to 64 items, two groups to 1536.  Above: alone, by one group or (block 64, long lists) two
 @pytest.mark.parametrize("block, H, N, most", [
     (128, 5, 16 * 128 - 31, 16), (128, 8, 16 * 128, 4), (128, 8, 16 * 128 + 1, 9), (128, 16, 16 * 128, 3), (128, 17, 15 * 128 + 65, 15),
     (128, 40, 15 * 128 - 95, 1), (128, 11, 50 * 128 - 1, 50), (64, 9, 28 * 64 - 33, 28), (64, 9, 28 * 64, 7), (64, 13, 33 * 64 + 31, 12),
-    (64, 18, 33 * 64, 3), (64, 30, 33 * 64 - 1, 33), (64, 60, 33 * 64 + 5, 5)])
+    (64, 18, 33 * 64, 3), (64, 30, 33 * 64 - 1, 33), (64, 60, 33 * 64 + 5, 5),
+    (128, 100, 16 * 128 - 33, 16), (128, 110, 14 * 128 + 1, 1), (64, 18, 90 * 64 - 31, 90), (64, 50, 33 * 64, 33), (64, 100, 16 * 64 + 33, 2),
+    (128, 2, 16 * 128 - 65, 9), (64, 2, 30 * 64 + 1, 30)])
 @pytest.mark.parametrize("rule", [False, True])
 def test_gradients_match_float64(block, H, N, most, rule):
     import torch

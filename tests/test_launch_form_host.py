@@ -40,7 +40,7 @@ def test_short_lists_are_not_split(forms):
              for heads, nb in ((1, 1), (4, 16), (8, 32), (20, 12), (5, 60), (16, 60), (24, 50), (24, 200), (24, 800))]
     for case, form in zip(cases, forms(cases)):
         assert form[:4] == (1, 1, 1, 1), case
-    # two entries pay for half blocks in the backward only; three entries for nothing above one round
+    # two entries pay for half blocks in the backward only (dK/dV and dQ one after the other); three entries for nothing above one round
     assert [f[:4] for f in forms([(128, 128, 4, 16, 2), (128, 128, 4, 16, 3), (128, 128, 8, 32, 3), (64, 64, 16, 60, 3), (64, 64, 24, 200, 6)])] == [
         (1, 4, 2, 1), (4, 4, 2, 1), (1, 1, 1, 1), (1, 1, 1, 1), (1, 1, 1, 1)]
 
@@ -108,3 +108,34 @@ def test_backward_of_very_short_lists_is_one_launch_only_where_that_saves_a_roun
     cases = [(128, 128, *c) for c in ((12, 32, 1), (35, 11, 1), (16, 32, 1), (16, 32, 3), (20, 32, 1), (20, 32, 2), (20, 32, 3), (641, 1, 2), (13, 59, 2), (48, 32, 3), (16, 32, 4), (48, 32, 4))]
     assert [f[0] for f in forms(cases, "backward")] == [3, 0, 0, 0, 0, 3, 3, 0, 0, 0, 3, 3]
     assert [f[0] for f in forms([(64, 64, 20, 32, 1), (64, 64, 641, 1, 1), (64, 64, 48, 32, 1), (64, 64, 48, 32, 2), (64, 128, 48, 32, 1)], "backward")] == [1, 0, 0, 1, 1]
+
+
+def test_forward_forms_ahead_of_the_groups(forms):
+    """Groups of one wave while 32-row parts have a compute unit each; halves of the last blocks of 128 up to half a round of 256,
+    where all heads go by length; parts of the 8-bit forward to 64 and to 128 blocks.  Lists of one entry in none of them."""
+    single = [(64, 64, 4, 32, 2), (128, 64, 129, 1, 2), (64, 64, 4, 32, 1), (128, 128, 2, 32, 2), (64, 128, 65, 1, 2), (128, 128, 2, 32, 1)]
+    assert [f[0] for f in forms(single, "forward")] == [1, 0, 0, 1, 0, 0]
+    halved = [(128, 128, 8, 32, 16), (128, 128, 1, 257, 16), (128, 128, 12, 32, 16), (64, 128, 5, 77, 16), (128, 128, 16, 32, 16), (128, 128, 20, 32, 4), (128, 128, 20, 32, 3),
+              (128, 128, 10, 110, 90), (128, 128, 24, 929, 100)]
+    assert [f[1] for f in forms(halved, "forward")] == [0, 1, 128, 0, 0, 128, 0, 76, 0]
+    parts = [(128, 128, 2, 32, 2), (128, 128, 5, 13, 2), (128, 128, 4, 32, 2), (128, 128, 3, 43, 2), (128, 128, 2, 32, 1)]
+    assert [f[2] for f in forms(parts, "forward")] == [4, 2, 2, 1, 1]
+
+
+def test_parts_of_blocks_only_where_all_heads_go_by_length(forms):
+    """Several workgroups per block are laid over the heads that go by length: every head has to."""
+    cases = [(D, block, heads, nb, per) for D in (64, 128) for block in (64, 128) for per in (1, 2, 4, 12, 40)
+             for heads, nb in ((1, 1), (1, 64), (1, 128), (3, 43), (16, 8), (64, 2), (65, 2), (128, 1), (128, 2), (9, 28), (20, 12), (256, 1), (300, 1), (17, 33), (2, 900))]
+    groups, ahead, back = forms(cases), forms(cases, "forward"), forms(cases, "backward")
+    for (D, block, heads, nb, per), g, f, b in zip(cases, groups, ahead, back):
+        forward, dq, dkdv = g[4:]
+        half = block == 128
+        if f[0] or f[1] or f[2] > 1 or (half and g[0] == 4):
+            assert forward == heads, (D, block, heads, nb, per)
+        # one launch in groups of 32 or 64 rows (D 64), by hand in 64 rows; one after the other in half blocks
+        if b[0] == 1 and (b[1] == 4 or (half and b[1] == 2)) or (b[0] == 2 and half):
+            assert dq == dkdv == heads, (D, block, heads, nb, per)
+        if half and b[4] == 2:
+            assert dkdv == heads, (D, block, heads, nb, per)
+        if half and b[5] == 4:
+            assert dq == heads, (D, block, heads, nb, per)
