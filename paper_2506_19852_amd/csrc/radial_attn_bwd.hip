@@ -40,7 +40,6 @@ struct BwdTile {
   static constexpr int kWaves = kRows / 32;  // one wave per 32 keys
   static constexpr int kThreads = 64 * kWaves * S;
   static constexpr int kSubs = BLK / kStageQ;  // stages per listed query block
-  static constexpr int kLastOffset = BLK - kStageQ;
   static constexpr int kSteps = D / 16;
   static constexpr int kDTiles = D / 32;
   static constexpr int kQBytes = kStageQ * D * 2;        // Q or dO stage tile
@@ -162,12 +161,8 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a, uint32_t id) {
   const int32_t* rows_list = a.row_idx + list_lo + group;
   int32_t cvec = lane < n_list ? rows_list[S * lane] : 0;
   int32_t nvec = 64 + lane < n_list ? rows_list[S * (64 + lane)] : 0;
-  // token rule: (frame, position) of this lane's key and of every listed query block's first row
-  StagePos key_at = {0, 0}, cvec_at = {0, 0};
-  if (kExact) {
-    key_at = block_pos(key_ok ? key_row : a.N - 1, a.rule.s);
-    cvec_at = block_pos(cvec * BLK, a.rule.s);
-  }
+  ListRule<kStageQ, BLK> token;
+  if (kExact) token.init(a.rule, kb * BLK + part * T::kRows + wave * 32, a.N, lane);
 
   int32_t srow[T::kQLoadsPerWave], scol[T::kQLoadsPerWave];
 #pragma unroll
@@ -208,15 +203,15 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a, uint32_t id) {
   const float c = a.scale * kLog2e;
 
   int32_t q0 = 0;
-  StagePos q_at = {0, 0}, q_at_next = {0, 0};
   if (n_stage > 0) {
     q0 = __builtin_amdgcn_readlane(cvec, 0) * BLK;
-    if (kExact) q_at = stage_pos<0>(cvec_at, 0, 0, a.rule.s);
     issue_stage(q0, 0);
   }
 
   for (int32_t u = 0; u < n_stage; ++u) {
     const int buf = u & 1;
+    if (kExact && (u & 63) == 0) token.look(a.rule, cvec, u / T::kSubs & 63, lane, false);
+    const bool partial = kExact && !token.sees_all(u);
     int32_t q0_next = 0;
     const bool has_next = u + 1 < n_stage;
     if (has_next) {
@@ -224,10 +219,8 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a, uint32_t id) {
       if ((u + 1) % T::kSubs == 0 && (e1 & 63) == 0) {
         cvec = nvec;
         nvec = e1 + 64 + lane < n_list ? rows_list[S * (e1 + 64 + lane)] : 0;
-        if (kExact) cvec_at = block_pos(cvec * BLK, a.rule.s);
       }
       q0_next = __builtin_amdgcn_readlane(cvec, e1 & 63) * BLK + ((u + 1) % T::kSubs) * kStageQ;
-      if (kExact) q_at_next = stage_pos<T::kLastOffset>(cvec_at, e1 & 63, ((u + 1) % T::kSubs) * kStageQ, a.rule.s);
     }
 
     if (T::kWaves == 1) {  // nobody else reads or writes this group's stage buffers
@@ -238,17 +231,14 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a, uint32_t id) {
     }
     // The copies of a full next stage are spread over the first MFMAs of this one (see below);
     // a ragged one is issued at once.
-    StageRule vis = {};
-    if (kExact) vis = stage_rule(a.rule, key_at, q_at, false);  // which of the stage's queries see this lane's key
     // A wave that sees nothing of the stage skips it.  Backward pass, us: D 64, block 128, 10 x 17 000 tokens 2150 / 2045, 4 x 30 000
     // 2754 / 2607, blocks of 64 (fewer such stages) 910 / 911.  Not with the hand-made schedule: the second way round its
     // loop cost 15 to 18 % (D 128, block 64, 8 x 14 040 2502 / 2953).
-    const bool skip = kExact && kTwoWaves && vis.none;
+    const bool skip = kExact && kTwoWaves && token.sees_none(u);
     const bool spread_next = has_next && !skip && q0_next + kStageQ <= a.N;
     if (has_next && !spread_next) issue_stage(q0_next, buf ^ 1);
     if (skip) {
       q0 = q0_next;
-      q_at = q_at_next;
       continue;
     }
 
@@ -257,10 +247,9 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a, uint32_t id) {
     const char* st = sg + T::kQBytes;  // 64 x LSE then 64 x delta
     const bool ragged_q = q0 + kStageQ > a.N;
     uint32_t hidden = 0u;
-    if (ragged_q || (kExact && vis.partial)) {  // query rows past N, rows the token rule hides from this key
-      uint64_t seen = stage_prefix(a.N - q0);
-      if (kExact) seen &= vis.visible_mask();
-      hidden = ~lane_element_bits(seen, g);
+    if (ragged_q || partial) {  // query rows past N, rows the token rule hides from this key
+      if (!kExact || ragged_q) hidden = ~lane_element_bits(stage_prefix(a.N - q0), g);
+      if (kExact && partial) hidden |= token.hidden(u, a.rule.s, g, lane);
     }
     const bool any_hidden = __builtin_amdgcn_ballot_w64(hidden != 0u) != 0;
     // this wave's copies of the next stage, one or two per k-step of phase A
@@ -348,7 +337,6 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a, uint32_t id) {
         }
       }
       q0 = q0_next;
-      q_at = q_at_next;
       continue;
     }
 
@@ -457,7 +445,6 @@ __device__ __forceinline__ void dkdv_body(const BwdArgs& a, uint32_t id) {
       __builtin_amdgcn_sched_barrier(0);
     }
     q0 = q0_next;
-    q_at = q_at_next;
   }
 
   // ---- epilogue: dK = scale * dK^T, dV -----------------------------------------------------
@@ -520,7 +507,6 @@ struct PairTile {
   static constexpr int kPairs = BLK / 32;
   static constexpr int kThreads = 128 * kPairs;
   static constexpr int kSubs = BLK / kStageQ;
-  static constexpr int kLastOffset = BLK - kStageQ;
   static constexpr int kSteps = D / 16;
   static constexpr int kDTiles = D / 32;
   static constexpr int kTileBytes = kStageQ * D * 2;  // Q or dO of a stage
@@ -578,11 +564,8 @@ __device__ __forceinline__ void pairs_body(const BwdArgs& a, uint32_t id) {
   const int32_t* rows_list = a.row_idx + list_lo;
   int32_t cvec = lane < n_list ? rows_list[lane] : 0;
   int32_t nvec = 64 + lane < n_list ? rows_list[64 + lane] : 0;
-  StagePos key_at = {0, 0}, cvec_at = {0, 0};
-  if (kExact) {
-    key_at = block_pos(key_ok ? key_row : a.N - 1, a.rule.s);
-    cvec_at = block_pos(cvec * BLK, a.rule.s);
-  }
+  ListRule<kStageQ, BLK> token;
+  if (kExact) token.init(a.rule, kb * BLK + pair * 32, a.N, lane);
 
   int32_t srow[T::kLoadsPerWave], scol[T::kLoadsPerWave];
   uint32_t qoff[T::kLoadsPerWave], goff[T::kLoadsPerWave];  // byte offsets from the stage's first row
@@ -625,11 +608,9 @@ __device__ __forceinline__ void pairs_body(const BwdArgs& a, uint32_t id) {
   const float c = a.scale * kLog2e;
 
   int32_t q0 = 0, q0_next = 0;
-  StagePos q_at = {0, 0}, q_at_next = {0, 0};
   Bufs at = {0, T::kGradAt, T::kStatAt, T::kPAt};
   if (n_stage > 0) {
     q0 = __builtin_amdgcn_readlane(cvec, 0) * BLK;
-    if (kExact) q_at = stage_pos<0>(cvec_at, 0, 0, a.rule.s);
     issue_stage(q0, at);
   }
 
@@ -638,27 +619,25 @@ __device__ __forceinline__ void pairs_body(const BwdArgs& a, uint32_t id) {
   bool spread = false;
   uint64_t copy_lanes = 0;
   const __bf16 *qbase = qp, *gbase = gp;
-  StageRule vis = {};
-  bool skip = false;  // token rule: no row of the stage sees a key of this pair
+  bool partial = false, skip = false;  // token rule: some row, or all rows, of the stage see some key, or no key, of this pair
   auto open_stage = [&](int32_t u) __attribute__((always_inline)) {
     const bool has_next = u + 1 < n_stage;
+    if (kExact) {
+      if ((u & 63) == 0) token.look(a.rule, cvec, u / T::kSubs & 63, lane, false);
+      skip = token.sees_none(u);
+      partial = !token.sees_all(u);
+    }
     to = next_bufs(at);
     if (has_next) {
       const int32_t e1 = (u + 1) / T::kSubs;
       if ((u + 1) % T::kSubs == 0 && (e1 & 63) == 0) {
         cvec = nvec;
         nvec = e1 + 64 + lane < n_list ? rows_list[e1 + 64 + lane] : 0;
-        if (kExact) cvec_at = block_pos(cvec * BLK, a.rule.s);
       }
       q0_next = __builtin_amdgcn_readlane(cvec, e1 & 63) * BLK + ((u + 1) % T::kSubs) * kStageQ;
-      if (kExact) q_at_next = stage_pos<T::kLastOffset>(cvec_at, e1 & 63, ((u + 1) % T::kSubs) * kStageQ, a.rule.s);
     }
     wait_all_copies();  // stage u has landed
     __syncthreads();    // for every wave; stage u-1 is finished and its P written
-    if (kExact) {
-      vis = stage_rule(a.rule, key_at, q_at, false);  // which of the stage's queries see this lane's key
-      skip = vis.none;
-    }
     spread = has_next && !skip && q0_next + kStageQ <= a.N;
     if (has_next && !spread) issue_stage(q0_next, to);
     const uint32_t on = __builtin_amdgcn_readfirstlane(spread ? ~0u : 0u);
@@ -669,7 +648,6 @@ __device__ __forceinline__ void pairs_body(const BwdArgs& a, uint32_t id) {
   };
   auto close_stage = [&]() __attribute__((always_inline)) {
     q0 = q0_next;
-    q_at = q_at_next;
     at = to;
   };
   auto spread_copy = [&](int j) __attribute__((always_inline)) {
@@ -728,10 +706,9 @@ __device__ __forceinline__ void pairs_body(const BwdArgs& a, uint32_t id) {
       if (!skip) {
         const int32_t tq = at.q, tg = at.grad;
         uint32_t hidden = 0u;
-        if (q0 + kStageQ > a.N || (kExact && vis.partial)) {  // query rows past N, rows the token rule hides from this key
-          uint64_t seen = stage_prefix(a.N - q0);
-          if (kExact) seen &= vis.visible_mask();
-          hidden = ~lane_element_bits(seen, g);
+        if (q0 + kStageQ > a.N || partial) {  // query rows past N, rows the token rule hides from this key
+          if (!kExact || q0 + kStageQ > a.N) hidden = ~lane_element_bits(stage_prefix(a.N - q0), g);
+          if (kExact && partial) hidden |= token.hidden(u, a.rule.s, g, lane);
         }
         const bool any_hidden = __builtin_amdgcn_ballot_w64(hidden != 0u) != 0;
         f32x16 s[2];
@@ -881,7 +858,6 @@ struct DqTile {
   static constexpr int kWaves = kRows / 32;  // one wave per 32 query rows
   static constexpr int kThreads = 64 * kWaves * S;
   static constexpr int kSubs = BLK / kStageKeys;
-  static constexpr int kLastOffset = BLK - kStageKeys;
   static constexpr int kSteps = D / 16;
   static constexpr int kDTiles = D / 32;
   static constexpr int kTileBytes = kStageKeys * D * 2;  // one K (or V) stage tile
@@ -949,12 +925,8 @@ __device__ __forceinline__ void dq_body(const BwdArgs& a, uint32_t id) {
   const int32_t* cols = a.col_idx + list_lo + group;
   int32_t cvec = lane < n_list ? cols[S * lane] : 0;
   int32_t nvec = 64 + lane < n_list ? cols[S * (64 + lane)] : 0;
-  // token rule: (frame, position) of this lane's query and of every listed key block's first key
-  StagePos q_at = {0, 0}, cvec_at = {0, 0};
-  if (kExact) {
-    q_at = block_pos((int32_t)q_clamped, a.rule.s);
-    cvec_at = block_pos(cvec * BLK, a.rule.s);
-  }
+  ListRule<T::kStageKeys, BLK> token;
+  if (kExact) token.init(a.rule, qb * BLK + part * T::kRows + wave * 32, a.N, lane);
 
   uint32_t koff[T::kLoadsPerWave], voff[T::kLoadsPerWave];
 #pragma unroll
@@ -997,14 +969,15 @@ __device__ __forceinline__ void dq_body(const BwdArgs& a, uint32_t id) {
   const float c = a.scale * kLog2e;
 
   int32_t key0 = 0;
-  StagePos k_at = {0, 0}, k_at_next = {0, 0};
   if (n_stage > 0) {
     key0 = __builtin_amdgcn_readlane(cvec, 0) * BLK;
-    if (kExact) k_at = stage_pos<0>(cvec_at, 0, 0, a.rule.s);
     issue_stage(key0, 0);
   }
   for (int32_t u = 0; u < n_stage; ++u) {
     const int buf = u & 1;
+    if (kExact && (u & 63) == 0) token.look(a.rule, cvec, u / T::kSubs & 63, lane, true);
+    const bool skip = kExact && token.sees_none(u);  // no pair of this wave's queries with the stage's keys
+    const bool partial = kExact && !token.sees_all(u);
     int32_t key0_next = 0;
     const bool has_next = u + 1 < n_stage;
     if (has_next) {
@@ -1012,10 +985,8 @@ __device__ __forceinline__ void dq_body(const BwdArgs& a, uint32_t id) {
       if ((u + 1) % T::kSubs == 0 && (e1 & 63) == 0) {
         cvec = nvec;
         nvec = e1 + 64 + lane < n_list ? cols[S * (e1 + 64 + lane)] : 0;
-        if (kExact) cvec_at = block_pos(cvec * BLK, a.rule.s);
       }
       key0_next = __builtin_amdgcn_readlane(cvec, e1 & 63) * BLK + ((u + 1) % T::kSubs) * T::kStageKeys;
-      if (kExact) k_at_next = stage_pos<T::kLastOffset>(cvec_at, e1 & 63, ((u + 1) % T::kSubs) * T::kStageKeys, a.rule.s);
     }
     if (T::kWaves == 1) {  // nobody else reads or writes this group's stage buffers
       asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
@@ -1027,27 +998,19 @@ __device__ __forceinline__ void dq_body(const BwdArgs& a, uint32_t id) {
     const char* lds_k = lds_at(buf * 2 * T::kTileBytes);
     const char* lds_v = lds_k + T::kTileBytes;
     const bool ragged = key0 + T::kStageKeys > a.N;
-    StageRule vis = {};
-    bool skip = false;
-    if (kExact) {
-      vis = stage_rule<T::kStageKeys>(a.rule, q_at, k_at, true);  // which of the stage's keys this lane's query sees
-      skip = vis.none;                             // no pair of this wave's queries with the stage's keys
-    }
     // The copies of a full next stage are spread over the MFMAs of the first key tile (a burst
     // would hold the wave at the memory pipeline); a ragged next stage, or a stage this wave
     // skips, issues them at once.
     uint32_t hidden = 0u;  // bit 16kt + e: element e of key tile kt is past N or hidden by the token rule
-    if (ragged || (kExact && vis.partial)) {
-      uint64_t seen = stage_prefix(a.N - key0);
-      if (kExact) seen &= vis.visible_mask();
-      hidden = ~lane_element_bits(seen, g);
+    if (ragged || partial) {
+      if (!kExact || ragged) hidden = ~lane_element_bits(stage_prefix(a.N - key0), g);
+      if (kExact && partial) hidden |= token.hidden(u, a.rule.s, g, lane);
     }
     const bool any_hidden = __builtin_amdgcn_ballot_w64(hidden != 0u) != 0;
     const bool spread = has_next && !skip && key0_next + T::kStageKeys <= a.N;
     if (has_next && !spread) issue_stage(key0_next, buf ^ 1);
     if (skip) {
       key0 = key0_next;
-      k_at = k_at_next;
       continue;
     }
     const uint32_t on = __builtin_amdgcn_readfirstlane(spread ? ~0u : 0u);
@@ -1105,7 +1068,6 @@ __device__ __forceinline__ void dq_body(const BwdArgs& a, uint32_t id) {
       }
     }
     key0 = key0_next;
-    k_at = k_at_next;
   }
 
   __bf16* dst = (__bf16*)a.dq.ptr + (int64_t)b * a.dq.sb + (int64_t)h * a.dq.sh + (int64_t)q_row * a.dq.sn;

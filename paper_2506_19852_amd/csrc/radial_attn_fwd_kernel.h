@@ -44,7 +44,6 @@ struct Tile {
   static constexpr int kThreads = 64 * kWaves * S;
   static constexpr int kPiecesPerRow = D / 8;      // 16-byte pieces per K/V row
   static constexpr int kSubs = BLK / kStageKeys;   // stages per listed key block
-  static constexpr int kLastOffset = BLK - kStageKeys;
   static constexpr int kStageBytes = kStageKeys * D * 2;            // one K (or V) stage tile
   static constexpr int kLoadsPerWave = kStageBytes / 1024 / kWaves; // 1 KiB copies per wave per tile
   static constexpr int kSteps = D / 16;            // MFMA k-steps of the S product
@@ -152,13 +151,8 @@ __device__ __forceinline__ void fwd_body(const FwdArgs& a, int32_t bh, int32_t q
   const int32_t* cols = a.col_idx + list_lo + group;
   int32_t cvec = lane < n_list ? cols[S * lane] : 0;
   int32_t nvec = 64 + lane < n_list ? cols[S * (64 + lane)] : 0;
-  // token rule: this lane's query as (frame, position), and the same for the first token of
-  // every listed key block (one division per lane per 64 entries)
-  StagePos q_at = {0, 0}, cvec_at = {0, 0};
-  if (kExact) {
-    q_at = block_pos(q_ok ? q_row : a.N - 1, a.rule.s);
-    cvec_at = block_pos(cvec * BLK, a.rule.s);
-  }
+  ListRule<T::kStageKeys, BLK> token;
+  if (kExact) token.init(a.rule, qb * BLK + part * T::kRows + wave * 32, a.N, lane);
 
   // Which piece of a stage tile each of this lane's copies fetches (fixed for the kernel),
   // as a byte offset from the first row of the tile.
@@ -214,16 +208,14 @@ __device__ __forceinline__ void fwd_body(const FwdArgs& a, int32_t bh, int32_t q
   const float c = a.scale * 1.4426950408889634f;  // exp(scale*x) = exp2(c*x)
 
   int32_t key0 = 0;  // first key of the stage about to be computed
-  StagePos k_at = {0, 0}, k_at_next = {0, 0};  // its (frame, position), and the next stage's
   if (n_stage > 0) {
     key0 = __builtin_amdgcn_readlane(cvec, 0) * BLK;
-    if (kExact) k_at = stage_pos<0>(cvec_at, 0, 0, a.rule.s);
     issue_stage(key0, 0);
   }
 
-  // One stage: scores of 64 keys, online softmax, O update.  spread_lanes (all or none): also issue this
+  // One stage: scores of 64 keys, online softmax, O update.  partial: the token rule hides some pair of stage u.  spread_lanes (all or none): also issue this
   // wave's copies of the next stage between the MFMAs of the first product.
-  auto stage_body = [&](int buf, int32_t key0, int32_t key0_next, const StageRule& vis, uint64_t spread_lanes) __attribute__((always_inline)) {
+  auto stage_body = [&](int buf, int32_t u, int32_t key0, int32_t key0_next, bool partial, uint64_t spread_lanes) __attribute__((always_inline)) {
     const uint32_t kdst_next = lds_base + (buf ^ 1) * 2 * T::kStageBytes + wave * T::kLoadsPerWave * 1024;
     const uint32_t vdst_next = kdst_next + T::kStageBytes;
     const __bf16* kbase_next = kp + (int64_t)key0_next * a.k.sn;  // wave-uniform
@@ -253,17 +245,20 @@ __device__ __forceinline__ void fwd_body(const FwdArgs& a, int32_t bh, int32_t q
     // ---- online softmax ------------------------------------------------------------------
     // s[kt][e] belongs to key key0 + 32kt + 8(e/4) + 4g + e%4 and query q_row.  Keys >= N do not
     // exist; under the token rule some keys are hidden from this lane's query.
-    if (key0 + T::kStageKeys > a.N || (kExact && vis.partial)) {
-      uint64_t seen = stage_prefix(a.N - key0);
-      if (kExact) seen &= vis.visible_mask();
-      const uint32_t hidden = ~lane_element_bits(seen, g);
-      if (__builtin_amdgcn_ballot_w64(hidden != 0u) != 0) {
+    if (key0 + T::kStageKeys > a.N || (kExact && partial)) {
+      uint32_t hidden = 0u;
+      if (!kExact || key0 + T::kStageKeys > a.N) hidden = ~lane_element_bits(stage_prefix(a.N - key0), g);
+      if (kExact && partial) hidden |= token.hidden(u, a.rule.s, g, lane);
+      constexpr int kTogether = kExact ? 1 : T::kKeyTiles;  // key tiles looked at together: the edge of a diagonal is often in one
 #pragma unroll
-        for (int kt = 0; kt < T::kKeyTiles; ++kt)
+      for (int k0 = 0; k0 < T::kKeyTiles; k0 += kTogether)
+        if (__builtin_amdgcn_ballot_w64((kTogether == 2 ? hidden : hidden >> (16 * k0) & 0xffffu) != 0u) != 0) {
 #pragma unroll
-          for (int e = 0; e < 16; ++e)
-            if ((hidden >> (16 * kt + e)) & 1u) s[kt][e] = -INFINITY;
-      }
+          for (int kt = k0; kt < k0 + kTogether; ++kt)
+#pragma unroll
+            for (int e = 0; e < 16; ++e)
+              if ((hidden >> (16 * kt + e)) & 1u) s[kt][e] = -INFINITY;
+        }
     }
     float mx = s[0][0];
 #pragma unroll
@@ -325,6 +320,9 @@ __device__ __forceinline__ void fwd_body(const FwdArgs& a, int32_t bh, int32_t q
   // LDS addresses of its reads are immediates.
   auto one_stage = [&](int32_t u, auto buf_c) __attribute__((always_inline)) {
     constexpr int buf = decltype(buf_c)::value;
+    if (kExact && buf == 0 && (u & 63) == 0) token.look(a.rule, cvec, u / T::kSubs & 63, lane, true);
+    const bool skip = kExact && token.sees_none(u);  // nothing in this stage for any row of this wave
+    const bool partial = kExact && !token.sees_all(u);
     // First key of stage u+1.
     int32_t key0_next = 0;
     const bool has_next = u + 1 < n_stage;
@@ -333,10 +331,8 @@ __device__ __forceinline__ void fwd_body(const FwdArgs& a, int32_t bh, int32_t q
       if ((u + 1) % T::kSubs == 0 && (e1 & 63) == 0) {  // entering the next chunk of the list
         cvec = nvec;
         nvec = e1 + 64 + lane < n_list ? cols[S * (e1 + 64 + lane)] : 0;
-        if (kExact) cvec_at = block_pos(cvec * BLK, a.rule.s);
       }
       key0_next = __builtin_amdgcn_readlane(cvec, e1 & 63) * BLK + ((u + 1) % T::kSubs) * T::kStageKeys;
-      if (kExact) k_at_next = stage_pos<T::kLastOffset>(cvec_at, e1 & 63, ((u + 1) % T::kSubs) * T::kStageKeys, a.rule.s);
     }
 
     if (T::kWaves == 1) {  // nobody else reads or writes this group's stage buffers
@@ -346,12 +342,6 @@ __device__ __forceinline__ void fwd_body(const FwdArgs& a, int32_t bh, int32_t q
       __syncthreads();                                  // ... and everyone's; stage u-1 is fully consumed
     }
 
-    StageRule vis = {};
-    bool skip = false;
-    if (kExact) {
-      vis = stage_rule<T::kStageKeys>(a.rule, q_at, k_at, true);
-      skip = vis.none;  // nothing in this stage for any row of this wave
-    }
     // The copies of stage u+1 are spread over the first product of stage u (a burst of copies
     // would hold the wave at the memory pipeline before it reaches its first MFMA); only a
     // ragged next stage, or a stage this wave skips, issues them in one go.
@@ -359,10 +349,9 @@ __device__ __forceinline__ void fwd_body(const FwdArgs& a, int32_t bh, int32_t q
     if (has_next && !spread) issue_stage(key0_next, buf ^ 1);
     if (!skip) {
       const uint32_t on = __builtin_amdgcn_readfirstlane(spread ? ~0u : 0u);  // wave-uniform by construction
-      stage_body(buf, key0, spread ? key0_next : key0, vis, ((uint64_t)on << 32) | on);
+      stage_body(buf, u, key0, spread ? key0_next : key0, partial, ((uint64_t)on << 32) | on);
     }
     key0 = key0_next;
-    k_at = k_at_next;
   };
   for (int32_t u = 0; u < n_stage; u += 2) {
     one_stage(u, std::integral_constant<int, 0>{});

@@ -573,7 +573,8 @@ extern "C" int radial_mask_build_banded(int32_t frames, int32_t tokens_per_frame
   // device table with one extra entry: the kernels also look up the distance to the frame after
   // the last one (a stage of keys may run past the end of the sequence)
   std::vector<int32_t> table((size_t)frames + 1, -1);
-  for (int32_t d = 0; d < frames; ++d) table[d] = half_width[d] < -1 ? -1 : half_width[d];
+  // (half widths beyond a frame mean the whole frame; as tokens_per_frame the kernels' sums of positions stay within 32 bits)
+  for (int32_t d = 0; d < frames; ++d) table[d] = half_width[d] < -1 ? -1 : half_width[d] < tokens_per_frame ? half_width[d] : tokens_per_frame;
   const hipStream_t st = (hipStream_t)hip_stream;
   int rc = RADIAL_OK;
   if (hipMalloc(&m->d_half_width, sizeof(int32_t) * table.size()) != hipSuccess ||

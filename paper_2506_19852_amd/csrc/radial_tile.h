@@ -360,21 +360,12 @@ __host__ __device__ __forceinline__ StagePos advance(StagePos at, int32_t offset
   return at;
 }
 
-// Entry `idx` of the per-lane positions, advanced by `offset` tokens; wave-uniform.
-template <int kMaxOffset>
-__device__ __forceinline__ StagePos stage_pos(StagePos per_lane, int idx, int32_t offset, int32_t s) {
-  const StagePos at = {__builtin_amdgcn_readlane(per_lane.frame, idx), __builtin_amdgcn_readlane(per_lane.pos, idx)};
-  return advance<kMaxOffset>(at, offset, s);
-}
-
 // What one lane's token (its own frame/position, a query or a key) sees of a stage: tokens
 // [lo0, lo0 + n0) of the stage's first frame and [lo1, lo1 + n1) of its second, as offsets
 // 0..63 into the stage.
 struct StageRule {
   int32_t lo0, lo1;
   uint32_t n0, n1;
-  bool partial;  // wave-uniform: some lane of the wave has a hidden pair in this stage
-  bool none;     // wave-uniform: no lane of the wave has a visible pair in this stage
 
   // token `x` (0..63) of the stage
   __host__ __device__ __forceinline__ bool visible(int x) const {
@@ -407,36 +398,139 @@ __device__ __forceinline__ uint32_t lane_element_bits(uint64_t token_mask, int g
   return (uint32_t)v;
 }
 
-// The lane's own part of a StageRule (lo0, n0, lo1, n1).
-// own_is_query: the lane holds a query and the stage holds keys; otherwise the reverse.
+// The same bits for the tokens from x + 4g on (all of them up to x = 0, none from 64 on), with fewer instructions.  Not for the end of the
+// sequence where listed blocks are dense: the compiler takes the parts of it that do not change out of that rare branch, 4 to 10 registers
+// of every stage (D 64, block 64, 64 items L 28: 10.60 / 10.69 us).
+__host__ __device__ __forceinline__ uint32_t elements_from(int32_t x) {
+  x = max(min(x, 64), -4);
+  return (uint32_t)(~0ull << (4 * (x >> 3) + min(x & 7, 4)));
+}
+
+// The StageRule of a lane's own token at position own of its frame, for a stage that starts at `pos` of a frame: hw0 and hw1 are the half
+// widths of the pairs (own frame, stage's first frame) and (own frame, the next).
 // kWidth: tokens in the stage (64, or 32 for the kernels that walk half-size stages).
 template <int kWidth>
-__host__ __device__ __forceinline__ StageRule stage_intervals(const TokenRule& rule, StagePos own, StagePos stage, bool own_is_query) {
-  const int32_t s = rule.s;
-  const int32_t hw0 = own_is_query ? radial_half_width(rule, own.frame, stage.frame)
-                                   : radial_half_width(rule, stage.frame, own.frame);
-  const int32_t hw1 = own_is_query ? radial_half_width(rule, own.frame, stage.frame + 1)
-                                   : radial_half_width(rule, stage.frame + 1, own.frame);
-  const int32_t split = s - stage.pos;  // stage offset at which the second frame starts
+__host__ __device__ __forceinline__ StageRule visible_intervals(int32_t own, int32_t pos, int32_t hw0, int32_t hw1, int32_t s) {
+  const int32_t split = s - pos;  // stage offset at which the second frame starts
   StageRule r;
-  // first frame: positions stage.pos + x, x in [0, min(split, kWidth)), within hw0 of own.pos
-  const int32_t a0 = max(own.pos - hw0 - stage.pos, 0), b0 = min(own.pos + hw0 - stage.pos, min(split, kWidth) - 1);
+  // first frame: positions pos + x, x in [0, min(split, kWidth)), within hw0 of own
+  const int32_t a0 = max(own - hw0 - pos, 0), b0 = min(own + hw0 - pos, min(split, kWidth) - 1);
   r.lo0 = a0;
   r.n0 = b0 >= a0 ? (uint32_t)(b0 - a0 + 1) : 0u;
-  // second frame: positions x - split, x in [split, kWidth), within hw1 of own.pos
-  const int32_t a1 = max(own.pos - hw1 + split, split), b1 = min(own.pos + hw1 + split, kWidth - 1);
+  // second frame: positions x - split, x in [split, kWidth), within hw1 of own
+  const int32_t a1 = max(own - hw1 + split, split), b1 = min(own + hw1 + split, kWidth - 1);
   r.lo1 = a1;
   r.n1 = b1 >= a1 ? (uint32_t)(b1 - a1 + 1) : 0u;
   return r;
 }
 
-template <int kWidth = 64>
-__device__ __forceinline__ StageRule stage_rule(const TokenRule& rule, StagePos own, StagePos stage, bool own_is_query) {
-  StageRule r = stage_intervals<kWidth>(rule, own, stage, own_is_query);
-  const bool all_visible = r.n0 + r.n1 == (uint32_t)kWidth;
-  r.partial = __builtin_amdgcn_ballot_w64(!all_visible) != 0;
-  r.none = __builtin_amdgcn_ballot_w64(r.n0 + r.n1 != 0u) == 0;
+// The elements that the token does not see, in lane group g.
+template <int kWidth>
+__host__ __device__ __forceinline__ uint32_t hidden_elements(int32_t own, int32_t pos, int32_t hw0, int32_t hw1, int32_t s, int g) {
+  const int32_t split = s - pos, own_g = own - 4 * g;
+  uint32_t seen = elements_from(own_g - hw0 - pos) & ~elements_from(min(own_g + hw0 - pos + 1, min(split, kWidth) - 4 * g));
+  if (split < kWidth) seen |= elements_from(max(own_g - hw1, -4 * g) + split) & ~elements_from(min(own_g + hw1 + split + 1, kWidth - 4 * g));
+  return ~seen;
+}
+
+// own_is_query: the lane holds a query and the stage holds keys; otherwise the reverse.
+__host__ __device__ __forceinline__ int32_t pair_half_width(const TokenRule& rule, int32_t own, int32_t other, bool own_is_query) {
+  return own_is_query ? radial_half_width(rule, own, other) : radial_half_width(rule, other, own);
+}
+template <int kWidth>
+__host__ __device__ __forceinline__ StageRule stage_intervals(const TokenRule& rule, StagePos own, StagePos stage, bool own_is_query) {
+  return visible_intervals<kWidth>(own.pos, stage.pos, pair_half_width(rule, own.frame, stage.frame, own_is_query),
+                                   pair_half_width(rule, own.frame, stage.frame + 1, own_is_query), rule.s);
+}
+
+// What a wave's 32 consecutive tokens cover: positions lo .. hi of a frame and, with s >= 64, at most 0 .. hi2 of the next (hi2 < 0: none).
+struct WaveSpan {
+  int32_t frame, lo, hi, hi2;
+};
+// The 32 tokens from `first` on; those past N - 1 stand for token N - 1, as in the lanes.
+__host__ __device__ __forceinline__ WaveSpan wave_span(int32_t first, int32_t N, int32_t s) {
+  const StagePos at = block_pos(first < N ? first : N - 1, s);
+  const int32_t last = at.pos + (first + 31 < N ? 31 : first < N ? N - 1 - first : 0);
+  return WaveSpan{at.frame, at.pos, last < s ? last : s - 1, last - s};
+}
+
+// The rule between a span and one stage of kWidth tokens: whether all tokens of the span see all of the stage, whether none sees any, and the
+// half widths of the pairs of frames, [of the span][of the stage].
+struct SpanRule {
+  bool all, none;
+  int32_t hw[2][2];
+};
+template <int kWidth>
+__host__ __device__ __forceinline__ SpanRule span_rule(const TokenRule& rule, const WaveSpan& span, StagePos stage, bool own_is_query) {
+  SpanRule r = {true, true, {{0, 0}, {0, 0}}};
+  const int32_t end = stage.pos + kWidth - 1;  // last token of the stage, as a position of its first frame
+#pragma unroll 1  // one copy of the half width's arithmetic
+  for (int k = 0; k < 4; ++k) {
+    const int i = k >> 1, j = k & 1;
+    const int32_t lo = i ? 0 : span.lo, hi = i ? span.hi2 : span.hi;
+    const int32_t from = j ? 0 : stage.pos, to = j ? end - rule.s : min(end, rule.s - 1);
+    const int32_t hw = pair_half_width(rule, span.frame + i, stage.frame + j, own_is_query);
+    if (hi >= lo && to >= from) {
+      r.all = r.all && hi - from <= hw && to - lo <= hw;
+      r.none = r.none && (hw < 0 || lo - to > hw || from - hi > hw);
+    }
+    if (k == 0) r.hw[0][0] = hw;
+    if (k == 1) r.hw[0][1] = hw;
+    if (k == 2) r.hw[1][0] = hw;
+    if (k == 3) r.hw[1][1] = hw;
+  }
   return r;
 }
+
+// The token rule in a wave that walks a list.  Lane l looks at every 64th stage, l of each 64, so that a stage which the wave sees wholly or not at
+// all costs a bit test, and one that it sees in part some thirty vector instructions for the mask of its elements.  Left to itself
+// at every stage a lane needs two half widths, 64-bit masks and a change of order, 180 instructions, 100 of them in every stage, beside the 170 of
+// the forward's softmax; at 21 x 1560 tokens 72 % of a wave's stages are seen wholly, 15 % in part, and 30 % of a workgroup's in part by some wave.
+// Each lane for itself in every stage / so, us: forward, D 128, block 128, 5 heads x 21 x 1560 tokens 1830 / 1661, 3 x 33 x 3600 10107 / 9297, block 64, 4 x 21 x
+// 1183 946 / 826, D 64, block 64, 30 x 24 x 316 601 / 525; backward 5727 / 5509, 8 x 30 x 900 6113 / 5586, D 64 1 x 108 x 1010 4725 / 4209, block 64,
+// 4 x 16 x 400 169 / 163.
+template <int kWidth, int kBlock>
+struct ListRule {
+  static constexpr int kSubs = kBlock / kWidth;
+  WaveSpan span;
+  int32_t own;       // position of this lane's token in its frame
+  uint64_t seconds;  // lanes whose token is in the span's second frame
+  uint64_t all, none;  // stages of the 64 around the current one
+  int32_t pos, hw[2][2];  // of this lane's stage of them: position in its first frame, half widths
+
+  // first, N: as for wave_span.
+  __device__ __forceinline__ void init(const TokenRule& rule, int32_t first, int32_t N, int lane) {
+    span = wave_span(first, N, rule.s);
+    const int32_t token = first + (lane & 31);
+    const StagePos at = block_pos(token < N ? token : N - 1, rule.s);
+    own = at.pos;
+    seconds = __builtin_amdgcn_ballot_w64(at.frame != span.frame);
+  }
+  // The 64 stages from the first one of entry `entry` of the chunk of 64 list entries on; vec: this lane's entry of the chunk.
+  __device__ __forceinline__ void look(const TokenRule& rule, int32_t vec, int32_t entry, int lane, bool own_is_query) {
+    const int32_t block = __shfl(vec, entry + lane / kSubs);
+    const StagePos stage = advance<kBlock - kWidth>(block_pos(block * kBlock, rule.s), lane % kSubs * kWidth, rule.s);
+    const SpanRule r = span_rule<kWidth>(rule, span, stage, own_is_query);
+    all = __builtin_amdgcn_ballot_w64(r.all);
+    none = __builtin_amdgcn_ballot_w64(r.none);
+    pos = stage.pos;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) hw[k >> 1][k & 1] = r.hw[k >> 1][k & 1];
+  }
+  __device__ __forceinline__ bool sees_all(int32_t u) const { return all >> (u & 63) & 1; }
+  __device__ __forceinline__ bool sees_none(int32_t u) const { return none >> (u & 63) & 1; }
+  // The elements of stage u that this lane's token does not see.
+  __device__ __forceinline__ uint32_t hidden(int32_t u, int32_t s, int g, int lane) const {
+    const int32_t at = __builtin_amdgcn_readlane(pos, u & 63);
+    int32_t hw0 = __builtin_amdgcn_readlane(hw[0][0], u & 63), hw1 = __builtin_amdgcn_readlane(hw[0][1], u & 63);
+    if (span.hi2 >= 0) {
+      const bool second = seconds >> lane & 1;
+      const int32_t b0 = __builtin_amdgcn_readlane(hw[1][0], u & 63), b1 = __builtin_amdgcn_readlane(hw[1][1], u & 63);
+      hw0 = second ? b0 : hw0;
+      hw1 = second ? b1 : hw1;
+    }
+    return hidden_elements<kWidth>(own, at, hw0, hw1, s, g);
+  }
+};
 
 }  // namespace radial

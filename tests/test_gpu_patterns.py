@@ -53,6 +53,19 @@ def test_banded_radial_table_reproduces_the_radial_builder(f, s, block, sink):
     b.free()
 
 
+def test_half_widths_beyond_a_frame_are_the_whole_frame():
+    f, s, D = 3, 150, 64
+    x = [torch.randn(1, 1, f * s, D, generator=torch.Generator().manual_seed(i)).to(DEV, torch.bfloat16) for i in range(3)]
+    outs = []
+    for widest in (s - 1, s, 2**31 - 1):
+        m = rb.radial_mask_build_banded(f, s, 64, 0, [widest, 20, widest], rb.RADIAL_MASK_TOKEN_EXACT)
+        outs.append(torch.empty_like(x[0]))
+        rb.radial_attn_fwd(*x, outs[-1], None, m, D**-0.5)
+        torch.cuda.synchronize()
+        m.free()
+    assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
+
+
 def test_argument_errors():
     with pytest.raises(ValueError):
         rb.radial_mask_build_banded(4, 64, 64, 1, [1, 2, 3])
