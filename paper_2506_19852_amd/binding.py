@@ -102,13 +102,23 @@ def _check(rc: int):
         raise RadialError(rc, radial_last_error())
 
 
+_torch = None
 _current_stream = None
+
+
+def _load_torch():
+    """torch, imported by the first call that takes tensors (an import statement in every function of a call costs it 1 us of 8)."""
+    global _torch
+    if _torch is None:
+        import torch
+        _torch = torch
+    return _torch
 
 
 def _find_current_stream():
     """A function that gives the current stream of the current device as an integer: without a Stream object
     around it where this torch build can say it so."""
-    import torch
+    torch = _load_torch()
     raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
     if raw is None:
         return lambda: torch.cuda.current_stream().cuda_stream
@@ -206,16 +216,14 @@ def radial_mask_copy_transpose_to_host(mask: RadialMask):
 
 
 def _tensor(t, name) -> radial_tensor:
-    import torch
     stride = t.stride()
-    if t.dtype is not torch.bfloat16 or not t.is_cuda or len(stride) != 4 or stride[3] != 1:
+    if t.dtype is not (_torch or _load_torch()).bfloat16 or not t.is_cuda or len(stride) != 4 or stride[3] != 1:
         raise ValueError(f"{name} must be a CUDA bf16 tensor [B, H, N, D] with unit stride in D")
     return radial_tensor(t.data_ptr(), stride[0], stride[1], stride[2])
 
 
 def radial_attn_fwd(q, k, v, out, lse, mask: RadialMask, scale: float, stream=None):
     """out[B,H,N,D] (bf16) and lse[B,H,N] (fp32, or None) <- block-sparse attention of q, k, v."""
-    import torch
     shape = q.shape
     B, H, N, D = shape
     for t, nm in ((k, "k"), (v, "v"), (out, "out")):
@@ -223,11 +231,11 @@ def radial_attn_fwd(q, k, v, out, lse, mask: RadialMask, scale: float, stream=No
             raise ValueError(f"{nm} has shape {tuple(t.shape)}, expected {(B, H, N, D)}")
     lse_ptr = None
     if lse is not None:
-        if lse.dtype is not torch.float32 or not lse.is_cuda or not lse.is_contiguous() or lse.shape != shape[:3]:
+        if lse.dtype is not (_torch or _load_torch()).float32 or not lse.is_cuda or not lse.is_contiguous() or lse.shape != shape[:3]:
             raise ValueError("lse must be a contiguous CUDA float32 tensor [B, H, N]")
-        lse_ptr = c_void_p(lse.data_ptr())
+        lse_ptr = lse.data_ptr()
     _check(load().radial_attn_fwd(B, H, N, D, _tensor(q, "q"), _tensor(k, "k"), _tensor(v, "v"), _tensor(out, "out"),
-                                  lse_ptr, mask.handle, c_float(scale), _stream_ptr(stream)))
+                                  lse_ptr, mask.handle, scale, _stream_ptr(stream)))
 
 
 def radial_attn_fwd_trace_records(B: int, H: int, mask: RadialMask) -> int:
@@ -236,14 +244,14 @@ def radial_attn_fwd_trace_records(B: int, H: int, mask: RadialMask) -> int:
 
 def radial_attn_fwd_trace(q, k, v, out, lse, mask: RadialMask, scale: float, trace, stream=None):
     """radial_attn_fwd plus one {begin, end, where} record per workgroup in trace (zeroed CUDA int64 [records, 3])."""
-    import torch
+    torch = _torch or _load_torch()
     B, H, N, D = q.shape
     if trace.dtype != torch.int64 or not trace.is_cuda or not trace.is_contiguous() or trace.dim() != 2 or trace.shape[1] != 3:
         raise ValueError("trace must be a contiguous CUDA int64 tensor [records, 3]")
-    lse_ptr = c_void_p(lse.data_ptr()) if lse is not None else None
+    lse_ptr = lse.data_ptr() if lse is not None else None
     _check(load().radial_attn_fwd_trace(B, H, N, D, _tensor(q, "q"), _tensor(k, "k"), _tensor(v, "v"), _tensor(out, "out"),
-                                        lse_ptr, mask.handle, c_float(scale), _stream_ptr(stream),
-                                        c_void_p(trace.data_ptr()), trace.shape[0]))
+                                        lse_ptr, mask.handle, scale, _stream_ptr(stream),
+                                        trace.data_ptr(), trace.shape[0]))
 
 
 def radial_probe_mfma_bf16(iterations: int, stream=None) -> float:
@@ -255,40 +263,41 @@ def radial_probe_mfma_bf16(iterations: int, stream=None) -> float:
 
 def radial_quantize_fp8(x, block: int, codes, scales, stream=None):
     """codes (uint8 [B,H,N,D]) and scales (float32 [B,H,ceil(N/block)]) <- per-block E4M3 quantisation of x (bf16)."""
-    import torch
+    torch = _torch or _load_torch()
     B, H, N, D = x.shape
     nb = (N + block - 1) // block
-    if codes.dtype != torch.uint8 or not codes.is_cuda or not codes.is_contiguous() or tuple(codes.shape) != (B, H, N, D):
+    if codes.dtype is not torch.uint8 or not codes.is_cuda or not codes.is_contiguous() or codes.shape != x.shape:
         raise ValueError("codes must be a contiguous CUDA uint8 tensor [B, H, N, D]")
-    if scales.dtype != torch.float32 or not scales.is_cuda or not scales.is_contiguous() or tuple(scales.shape) != (B, H, nb):
+    if scales.dtype is not torch.float32 or not scales.is_cuda or not scales.is_contiguous() or scales.shape != (B, H, nb):
         raise ValueError("scales must be a contiguous CUDA float32 tensor [B, H, ceil(N/block)]")
-    _check(load().radial_quantize_fp8(B, H, N, D, _tensor(x, "x"), block, c_void_p(codes.data_ptr()),
-                                      c_void_p(scales.data_ptr()), _stream_ptr(stream)))
+    _check(load().radial_quantize_fp8(B, H, N, D, _tensor(x, "x"), block, codes.data_ptr(),
+                                      scales.data_ptr(), _stream_ptr(stream)))
 
 
 def radial_attn_fwd_fp8(q_codes, q_scales, k_codes, k_scales, v, out, lse, mask: RadialMask, scale: float, stream=None,
                         code_block: int = 128):
     """radial_attn_fwd with the scores computed from E4M3 codes of q and k made by radial_quantize_fp8
     with block = code_block."""
-    import torch
-    B, H, N, D = v.shape
+    torch = _torch or _load_torch()
+    shape = v.shape
+    B, H, N, D = shape
     nb = (N + code_block - 1) // code_block
     for t, nm in ((q_codes, "q_codes"), (k_codes, "k_codes")):
-        if t.dtype != torch.uint8 or not t.is_cuda or not t.is_contiguous() or tuple(t.shape) != (B, H, N, D):
+        if t.dtype is not torch.uint8 or not t.is_cuda or not t.is_contiguous() or t.shape != shape:
             raise ValueError(f"{nm} must be a contiguous CUDA uint8 tensor [B, H, N, D]")
     for t, nm in ((q_scales, "q_scales"), (k_scales, "k_scales")):
-        if t.dtype != torch.float32 or not t.is_cuda or not t.is_contiguous() or tuple(t.shape) != (B, H, nb):
+        if t.dtype is not torch.float32 or not t.is_cuda or not t.is_contiguous() or t.shape != (B, H, nb):
             raise ValueError(f"{nm} must be a contiguous CUDA float32 tensor [B, H, ceil(N/code_block)]")
-    if tuple(out.shape) != (B, H, N, D):
+    if out.shape != shape:
         raise ValueError("out has the wrong shape")
     lse_ptr = None
     if lse is not None:
-        if lse.dtype != torch.float32 or not lse.is_cuda or not lse.is_contiguous() or tuple(lse.shape) != (B, H, N):
+        if lse.dtype is not torch.float32 or not lse.is_cuda or not lse.is_contiguous() or lse.shape != (B, H, N):
             raise ValueError("lse must be a contiguous CUDA float32 tensor [B, H, N]")
-        lse_ptr = c_void_p(lse.data_ptr())
-    _check(load().radial_attn_fwd_fp8(B, H, N, D, code_block, c_void_p(q_codes.data_ptr()), c_void_p(q_scales.data_ptr()),
-                                      c_void_p(k_codes.data_ptr()), c_void_p(k_scales.data_ptr()), _tensor(v, "v"),
-                                      _tensor(out, "out"), lse_ptr, mask.handle, c_float(scale), _stream_ptr(stream)))
+        lse_ptr = lse.data_ptr()
+    _check(load().radial_attn_fwd_fp8(B, H, N, D, code_block, q_codes.data_ptr(), q_scales.data_ptr(),
+                                      k_codes.data_ptr(), k_scales.data_ptr(), _tensor(v, "v"),
+                                      _tensor(out, "out"), lse_ptr, mask.handle, scale, _stream_ptr(stream)))
 
 
 def radial_attn_bwd_workspace(B: int, H: int, N: int, D: int, mask: RadialMask) -> int:
@@ -300,8 +309,8 @@ def radial_attn_bwd(q, k, v, out, dout, lse, dq, dk, dv, mask: RadialMask, scale
     B, H, N, D = q.shape
     ts = [_tensor(t, nm) for t, nm in ((q, "q"), (k, "k"), (v, "v"), (out, "out"), (dout, "dout"))]
     gs = [_tensor(t, nm) for t, nm in ((dq, "dq"), (dk, "dk"), (dv, "dv"))]
-    _check(load().radial_attn_bwd(B, H, N, D, *ts, c_void_p(lse.data_ptr()), *gs, mask.handle, c_float(scale),
-                                  c_void_p(workspace.data_ptr()), workspace.numel() * workspace.element_size(),
+    _check(load().radial_attn_bwd(B, H, N, D, *ts, lse.data_ptr(), *gs, mask.handle, scale,
+                                  workspace.data_ptr(), workspace.numel() * workspace.element_size(),
                                   _stream_ptr(stream)))
 
 
@@ -310,5 +319,5 @@ def radial_attn_bwd_static(q, k, v, out, dout, lse, dq, dk, dv, mask: RadialMask
     B, H, N, D = q.shape
     ts = [_tensor(t, nm) for t, nm in ((q, "q"), (k, "k"), (v, "v"), (out, "out"), (dout, "dout"))]
     gs = [_tensor(t, nm) for t, nm in ((dq, "dq"), (dk, "dk"), (dv, "dv"))]
-    _check(load().radial_attn_bwd_static(B, H, N, D, *ts, c_void_p(lse.data_ptr()), *gs, mask.handle, c_float(scale),
+    _check(load().radial_attn_bwd_static(B, H, N, D, *ts, lse.data_ptr(), *gs, mask.handle, scale,
                                          _stream_ptr(stream)))
