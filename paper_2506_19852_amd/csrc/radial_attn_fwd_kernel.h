@@ -252,7 +252,7 @@ __device__ __forceinline__ void fwd_body(const FwdArgs& a, int32_t bh, int32_t q
       constexpr int kTogether = kExact ? 1 : T::kKeyTiles;  // key tiles looked at together: the edge of a diagonal is often in one
 #pragma unroll
       for (int k0 = 0; k0 < T::kKeyTiles; k0 += kTogether)
-        if (__builtin_amdgcn_ballot_w64((kTogether == 2 ? hidden : hidden >> (16 * k0) & 0xffffu) != 0u) != 0) {
+        if (__builtin_amdgcn_ballot_w64((kTogether == T::kKeyTiles ? hidden : hidden >> (16 * k0) & 0xffffu) != 0u) != 0) {
 #pragma unroll
           for (int kt = k0; kt < k0 + kTogether; ++kt)
 #pragma unroll
