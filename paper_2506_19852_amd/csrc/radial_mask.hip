@@ -15,6 +15,7 @@
 #include <string.h>
 
 #include <memory>
+#include <mutex>
 #include <new>
 #include <vector>
 
@@ -37,7 +38,7 @@ namespace {
 constexpr int kThreads = 256;
 // Blocks up to which a radial mask's lists get room for every pair, so that nothing has to be known before
 // they are written (up to 2 MiB per list; hipMalloc becomes slow from there on, and counting first is then cheaper).
-// radial_mask_build and free, four kernels and two waits / two kernels and one wait: 110 blocks 61 / 34 us, 720 blocks
+// radial_mask_build and free, four kernels and two waits / two kernels and one wait (then with a copy, see Meta): 110 blocks 61 / 34 us, 720 blocks
 // 62 / 35; 929 blocks 65 / 73.  With the transposed lists both come from one hipMalloc, of 2 MiB and more from 512 blocks
 // on, which takes most of the gain: 244 blocks 77 / 45, 512 blocks 94 / 90, 720 blocks 149 / 107.
 constexpr int32_t kMaxUncounted = 720;
@@ -257,11 +258,30 @@ __device__ inline long long slice_target(long long total, int32_t nb, int k) {
   return ((total + (long long)kItemCost * nb) * k + 7) / 8;
 }
 
+// What a build finds out about its lists, for the launches (device) and for the host: the kernels write both, so that the host
+// has it when it has waited for the stream.  A copy of these 128 bytes to pageable memory behind the kernels costs 10 us of that wait (kernel, copy and wait
+// 22.5 us, kernel writing mapped memory and wait 12.0); radial_mask_build and free, 110 blocks, 32.4 / 23.2 us.
+// [0..1] total of rows, [2..3] total of columns, [4] longest row, [5] longest column, [8..16] slice, [20..28] slice_t
+constexpr int kMetaInts = 32, kTotal = 0, kTotalT = 2, kLongest = 4, kLongestT = 5, kSlice = 8, kSliceT = 20;
+struct Meta {
+  int32_t* device;
+  int32_t* host;  // mapped host memory, or null
+  __device__ void put(int at, int32_t value) const {
+    device[at] = value;
+    if (host) host[at] = value;
+  }
+  __device__ void put_total(int at, long long value) const {
+    put(at, (int32_t)(uint32_t)(unsigned long long)value);
+    put(at + 1, (int32_t)(value >> 32));
+  }
+};
+
 // What workgroup r needs to know of all lists to write its own: where it starts.  On the way it writes
 // ptr[r], the launch partitions, the longest list and the totals, so that neither a scan nor a partition pass is needed: every
 // workgroup reads all counts (nb / 256 rounds), which up to kMaxOrdered blocks costs less than the launches.
-__device__ int32_t place_list(const int32_t* counts, int32_t nb, int32_t r, int32_t* ptr, int32_t* slice, int32_t* order,
-                              int32_t* longest, long long* total64) {
+// columns: of the transposed lists.
+__device__ int32_t place_list(const int32_t* counts, int32_t nb, int32_t r, int32_t* ptr, int32_t* order, const Meta& meta, bool columns) {
+  const int slice = columns ? kSliceT : kSlice;
   const int32_t len = counts[r];
   long long before = 0, total = 0;
   int32_t ahead = 0;
@@ -275,32 +295,31 @@ __device__ int32_t place_list(const int32_t* counts, int32_t nb, int32_t r, int3
   if (threadIdx.x == 0) {
     ptr[r] = (int32_t)before;
     order[ahead] = r;
-    if (ahead == 0) *longest = len;
+    if (ahead == 0) meta.put(columns ? kLongestT : kLongest, len);
     if (r == nb - 1) {
       ptr[nb] = (int32_t)total;
-      *total64 = total;
+      meta.put_total(columns ? kTotalT : kTotal, total);
     }
   }
   if (threadIdx.x <= 8) {
     const int k = threadIdx.x;
     const long long w = before + (long long)kItemCost * r, target = slice_target(total, nb, k);
     if (k == 0 || k == 8) {
-      if (r == 0) slice[k] = k == 0 ? 0 : nb;
+      if (r == 0) meta.put(slice + k, k == 0 ? 0 : nb);
     } else if (w >= target && (r == 0 || w - counts[r - 1] - kItemCost < target)) {
-      slice[k] = r;
+      meta.put(slice + k, r);
     } else if (r == nb - 1 && w < target) {
-      slice[k] = nb;
+      meta.put(slice + k, nb);
     }
   }
   return (int32_t)before;
 }
 
 __global__ void __launch_bounds__(kThreads) mask_lists_kernel(MaskGeom g, int32_t nwords, const int32_t* counts, int32_t* row_ptr,
-                                                             int32_t* slice, int32_t* order, int32_t* longest, long long* total64,
-                                                             int32_t* col_idx) {
+                                                             int32_t* order, Meta meta, int32_t* col_idx) {
   extern __shared__ uint32_t words[];
   row_bitmap(g, blockIdx.x, words, nwords);
-  const int32_t start = place_list(counts, g.nb, blockIdx.x, row_ptr, slice, order, longest, total64);
+  const int32_t start = place_list(counts, g.nb, blockIdx.x, row_ptr, order, meta, false);
   write_row(words, nwords, col_idx + start);
 }
 
@@ -333,16 +352,15 @@ __global__ void __launch_bounds__(kThreads) transpose_fill_kernel(const int32_t*
 }
 
 __global__ void __launch_bounds__(kThreads) transpose_lists_kernel(const int32_t* row_ptr, const int32_t* col_idx, int32_t nb,
-                                                                  const int32_t* counts, int32_t* col_ptr, int32_t* slice,
-                                                                  int32_t* order, int32_t* longest, long long* total64, int32_t* row_idx) {
-  const int32_t start = place_list(counts, nb, blockIdx.x, col_ptr, slice, order, longest, total64);
+                                                                  const int32_t* counts, int32_t* col_ptr, int32_t* order, Meta meta,
+                                                                  int32_t* row_idx) {
+  const int32_t start = place_list(counts, nb, blockIdx.x, col_ptr, order, meta, true);
   write_column(row_ptr, col_idx, nb, blockIdx.x, start, row_idx);
 }
 
 // Workgroup 0 cuts the slices; the others, a wave per block, place the block at its rank by falling
 // list length (equal lengths: by index) if there is an order to fill, and the first writes its length.
-__global__ void __launch_bounds__(kThreads) partition_kernel(const int32_t* ptr, int32_t nb, int32_t* slice, int32_t* order,
-                                                            int32_t* longest) {
+__global__ void __launch_bounds__(kThreads) partition_kernel(const int32_t* ptr, int32_t nb, int32_t* order, Meta meta, bool columns) {
   if (blockIdx.x > 0) {
     const int32_t b = (blockIdx.x - 1) * (kThreads / 64) + (threadIdx.x >> 6);
     if (b >= nb) return;
@@ -355,7 +373,7 @@ __global__ void __launch_bounds__(kThreads) partition_kernel(const int32_t* ptr,
     for (int off = 32; off > 0; off >>= 1) ahead += __shfl_xor(ahead, off);
     if ((threadIdx.x & 63) == 0) {
       order[ahead] = b;
-      if (ahead == 0) *longest = len;
+      if (ahead == 0) meta.put(columns ? kLongestT : kLongest, len);
     }
     return;
   }
@@ -367,7 +385,7 @@ __global__ void __launch_bounds__(kThreads) partition_kernel(const int32_t* ptr,
     const int32_t mid = lo + ((hi - lo) >> 1);
     if ((long long)ptr[mid] + (long long)kItemCost * mid >= target) hi = mid; else lo = mid + 1;
   }
-  slice[k] = k == 8 ? nb : (k == 0 ? 0 : lo);
+  meta.put((columns ? kSliceT : kSlice) + k, k == 8 ? nb : (k == 0 ? 0 : lo));
 }
 
 int check_common(int64_t n_tokens, int32_t block, uint32_t flags) {
@@ -383,12 +401,62 @@ int check_common(int64_t n_tokens, int32_t block, uint32_t flags) {
 // Device storage of a mask is three allocations: `meta` (two 64-bit totals and the two launch
 // partitions), `ptrs` (row_ptr and its order and, with the transposed lists, col_ptr and its order) and `idx` (col_idx and
 // row_idx).  The views d_row_ptr, d_col_ptr, ... point into them at 256-byte aligned offsets.
-// [0..1] total of rows, [2..3] total of columns, [4] longest row, [5] longest column, [8..16] slice, [20..28] slice_t
-constexpr int kMetaInts = 32, kLongest = 4, kLongestT = 5;
-void launch_partition(const int32_t* ptr, int32_t nb, int32_t* slice, int32_t* order, int32_t* longest, hipStream_t st) {
+void launch_partition(const int32_t* ptr, int32_t nb, int32_t* order, const Meta& meta, bool columns, hipStream_t st) {
   const int32_t per = kThreads / 64;
-  partition_kernel<<<1 + (order ? (nb + per - 1) / per : 0), kThreads, 0, st>>>(ptr, nb, slice, order, longest);
+  partition_kernel<<<1 + (order ? (nb + per - 1) / per : 0), kThreads, 0, st>>>(ptr, nb, order, meta, columns);
 }
+
+// A Meta's host side for the time of one build: a slot of one page of mapped host memory that the process keeps (mapping it anew would
+// cost more than it saves).  A build that finds no slot free, or no page, copies instead.
+class HostMeta {
+ public:
+  HostMeta() {
+    const std::lock_guard<std::mutex> lock(mutex());
+    static int32_t* const page = [] {
+      void* p = nullptr;
+      if (hipHostMalloc(&p, kSlots * kMetaInts * sizeof(int32_t), hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
+        (void)hipGetLastError();  // the build goes on without
+        p = nullptr;
+      }
+      return (int32_t*)p;
+    }();
+    for (int i = 0; page && i < kSlots && slot_ < 0; ++i)
+      if (!(used() >> i & 1u)) slot_ = i;
+    if (slot_ < 0) return;
+    void* device = nullptr;
+    if (hipHostGetDevicePointer(&device, page + slot_ * kMetaInts, 0) != hipSuccess) {
+      (void)hipGetLastError();
+      slot_ = -1;
+      return;
+    }
+    used() |= 1u << slot_;
+    host_ = page + slot_ * kMetaInts;
+    device_ = (int32_t*)device;
+  }
+  // Once the kernels of the build have ended.
+  void release() {
+    if (slot_ < 0) return;
+    const std::lock_guard<std::mutex> lock(mutex());
+    used() &= ~(1u << slot_);
+    slot_ = -1;
+  }
+  const int32_t* host() const { return host_; }  // null: none
+  int32_t* device() const { return device_; }
+
+ private:
+  static constexpr int kSlots = 32;
+  static std::mutex& mutex() {
+    static std::mutex m;
+    return m;
+  }
+  static uint32_t& used() {
+    static uint32_t bits = 0;
+    return bits;
+  }
+  int slot_ = -1;
+  int32_t* host_ = nullptr;
+  int32_t* device_ = nullptr;
+};
 
 inline int64_t aligned_ints(int64_t n) { return (n + 63) & ~(int64_t)63; }
 
@@ -401,11 +469,11 @@ int alloc_meta_and_ptrs(radial_mask* m) {
   if (no) m->d_counts = m->d_ptrs + (np + no) * lists;
   m->d_row_ptr = m->d_ptrs;
   if (no) m->d_order = m->d_ptrs + np;
-  m->d_slice = m->d_meta + 8;
+  m->d_slice = m->d_meta + kSlice;
   if (m->flags & RADIAL_MASK_TRANSPOSE) {
     m->d_col_ptr = m->d_ptrs + np + no;
     if (no) m->d_order_t = m->d_col_ptr + np;
-    m->d_slice_t = m->d_meta + 20;
+    m->d_slice_t = m->d_meta + kSliceT;
   }
   return RADIAL_OK;
 }
@@ -421,33 +489,35 @@ int alloc_idx(radial_mask* m) {
 
 // Shared tail of the constructors: transposed lists (optional) and launch partitions, then the one
 // wait of the call for everything queued on the stream (the partitions come back to the host).
-// rows_placed: the rows' launch partitions and their total are on the device already.
-int finish_mask(radial_mask* m, bool rows_placed, hipStream_t st) {
+// rows_placed: the rows' launch partitions and their total are written already.
+int finish_mask(radial_mask* m, HostMeta& shared, bool rows_placed, hipStream_t st) {
   const int32_t nb = m->n_blocks;
+  const Meta meta = {m->d_meta, shared.device()};
   alignas(8) int32_t h_meta[kMetaInts];
-  if (!rows_placed) launch_partition(m->d_row_ptr, nb, m->d_slice, m->d_order, m->d_meta + kLongest, st);
+  if (!rows_placed) launch_partition(m->d_row_ptr, nb, m->d_order, meta, false, st);
   if ((m->flags & RADIAL_MASK_TRANSPOSE) && m->d_counts) {
     transpose_count_kernel<<<nb, kThreads, 0, st>>>(m->d_row_ptr, m->d_col_idx, nb, m->d_counts);
-    transpose_lists_kernel<<<nb, kThreads, 0, st>>>(m->d_row_ptr, m->d_col_idx, nb, m->d_counts, m->d_col_ptr, m->d_slice_t, m->d_order_t,
-                                                    m->d_meta + kLongestT, (long long*)(m->d_meta + 2), m->d_row_idx);
+    transpose_lists_kernel<<<nb, kThreads, 0, st>>>(m->d_row_ptr, m->d_col_idx, nb, m->d_counts, m->d_col_ptr, m->d_order_t, meta, m->d_row_idx);
   } else if (m->flags & RADIAL_MASK_TRANSPOSE) {
     transpose_count_kernel<<<nb, kThreads, 0, st>>>(m->d_row_ptr, m->d_col_idx, nb, m->d_col_ptr);
-    scan_kernel<<<1, kThreads, 0, st>>>(m->d_col_ptr, nb, (long long*)(m->d_meta + 2));
+    scan_kernel<<<1, kThreads, 0, st>>>(m->d_col_ptr, nb, (long long*)(m->d_meta + kTotalT));
     transpose_fill_kernel<<<nb, kThreads, 0, st>>>(m->d_row_ptr, m->d_col_idx, nb, m->d_col_ptr, m->d_row_idx);
-    launch_partition(m->d_col_ptr, nb, m->d_slice_t, m->d_order_t, m->d_meta + kLongestT, st);
+    launch_partition(m->d_col_ptr, nb, m->d_order_t, meta, true, st);
   }
   hipError_t e = hipGetLastError();
-  if (e == hipSuccess) e = hipMemcpyAsync(h_meta, m->d_meta, sizeof h_meta, hipMemcpyDeviceToHost, st);
+  if (e == hipSuccess && !shared.host()) e = hipMemcpyAsync(h_meta, m->d_meta, sizeof h_meta, hipMemcpyDeviceToHost, st);
   if (e == hipSuccess) e = hipStreamSynchronize(st);
-  if (e != hipSuccess) return fail(RADIAL_EHIP, "mask kernels failed: %s", hipGetErrorString(e));
-  if (rows_placed) m->nnz = *(const long long*)h_meta;
+  if (e != hipSuccess) return fail(RADIAL_EHIP, "mask kernels failed: %s", hipGetErrorString(e));  // (the slot stays taken: they may write it yet)
+  if (shared.host()) memcpy(h_meta, shared.host(), sizeof h_meta);
+  shared.release();
+  if (rows_placed) memcpy(&m->nnz, h_meta + kTotal, sizeof m->nnz);
   m->longest = m->d_order ? h_meta[kLongest] : nb;
   if (m->flags & RADIAL_MASK_TRANSPOSE) m->longest_t = m->d_order_t ? h_meta[kLongestT] : nb;
   for (int k = 0; k < 8; ++k) {
-    const int32_t len = h_meta[8 + k + 1] - h_meta[8 + k];
+    const int32_t len = h_meta[kSlice + k + 1] - h_meta[kSlice + k];
     m->max_slice = len > m->max_slice ? len : m->max_slice;
     if (m->flags & RADIAL_MASK_TRANSPOSE) {
-      const int32_t len_t = h_meta[20 + k + 1] - h_meta[20 + k];
+      const int32_t len_t = h_meta[kSliceT + k + 1] - h_meta[kSliceT + k];
       m->max_slice_t = len_t > m->max_slice_t ? len_t : m->max_slice_t;
     }
   }
@@ -512,10 +582,10 @@ static int build_radial(radial_mask* m, const radial_mask_params* p, hipStream_t
       for (int32_t r = 0; r < nb; ++r) m->nnz += counts[r];  // at most kMaxOrdered^2 = 2^28
     }
     if (int rc = alloc_idx(m)) return rc;
-    mask_lists_kernel<<<nb, kThreads, nwords * sizeof(uint32_t), st>>>(g, nwords, m->d_counts, m->d_row_ptr, m->d_slice, m->d_order,
-                                                                       m->d_meta + kLongest, (long long*)m->d_meta, m->d_col_idx);
-    RADIAL_HIP_TRY(hipGetLastError());
-    return finish_mask(m, true, st);
+    HostMeta shared;
+    mask_lists_kernel<<<nb, kThreads, nwords * sizeof(uint32_t), st>>>(g, nwords, m->d_counts, m->d_row_ptr, m->d_order,
+                                                                       Meta{m->d_meta, shared.device()}, m->d_col_idx);
+    return finish_mask(m, shared, true, st);
   }
   mask_count_kernel<<<nb, kThreads, nwords * sizeof(uint32_t), st>>>(g, nwords, m->d_row_ptr);
   scan_kernel<<<1, kThreads, 0, st>>>(m->d_row_ptr, nb, (long long*)m->d_meta);
@@ -528,7 +598,8 @@ static int build_radial(radial_mask* m, const radial_mask_params* p, hipStream_t
   if (int rc = alloc_idx(m)) return rc;
   mask_fill_kernel<<<nb, kThreads, nwords * sizeof(uint32_t), st>>>(g, nwords, m->d_row_ptr, m->d_col_idx);
   RADIAL_HIP_TRY(hipGetLastError());
-  return finish_mask(m, false, st);
+  HostMeta shared;
+  return finish_mask(m, shared, false, st);
 }
 
 extern "C" int radial_mask_build(const radial_mask_params* p, void* hip_stream, radial_mask** out) {
@@ -600,7 +671,8 @@ static int build_dense(radial_mask* m, hipStream_t st) {
   if (int rc = alloc_idx(m)) return rc;
   dense_fill_kernel<<<1024, kThreads, 0, st>>>((int32_t)nb, m->d_row_ptr, m->d_col_idx);
   RADIAL_HIP_TRY(hipGetLastError());
-  return finish_mask(m, false, st);
+  HostMeta shared;
+  return finish_mask(m, shared, false, st);
 }
 
 extern "C" int radial_mask_build_dense(int32_t n_tokens, int32_t block, uint32_t flags, void* hip_stream,
@@ -634,7 +706,8 @@ static int build_from_csr(radial_mask* m, const int32_t* row_ptr, const int32_t*
   RADIAL_HIP_TRY(hipMemcpyAsync(m->d_row_ptr, row_ptr, sizeof(int32_t) * (nb + 1), hipMemcpyHostToDevice, st));
   if (m->nnz > 0)
     RADIAL_HIP_TRY(hipMemcpyAsync(m->d_col_idx, col_idx, sizeof(int32_t) * m->nnz, hipMemcpyHostToDevice, st));
-  return finish_mask(m, false, st);
+  HostMeta shared;
+  return finish_mask(m, shared, false, st);
 }
 
 extern "C" int radial_mask_from_csr(int32_t n_tokens, int32_t block, uint32_t flags, const int32_t* row_ptr,
