@@ -867,8 +867,9 @@ struct DqTile {
   static constexpr int kLdsBytes = S * kGroupBytes > Join::kLdsBytes ? S * kGroupBytes : Join::kLdsBytes;
 };
 
+// Part `part` of the R of query block qb.
 template <int D, int BLK, bool kExact, int S, int R>
-__device__ __forceinline__ void dq_body(const BwdArgs& a, uint32_t id) {
+__device__ __forceinline__ void dq_body(const BwdArgs& a, int32_t bh, int32_t qb, int32_t part) {
   using T = DqTile<D, BLK, S, R>;
   using SW = SwzTile<D>;
   // [group][stage buffer][K, V][kStageKeys x D bf16]; one group's are a static array, as in the forward
@@ -889,10 +890,6 @@ __device__ __forceinline__ void dq_body(const BwdArgs& a, uint32_t id) {
   const int i16 = lane & 15;
   const int half16 = (lane >> 4) & 1;
 
-  int32_t bh, qb;
-  if (!work_item(a.work, id, bh, qb)) return;
-  const int32_t part = R == 1 ? 0 : bh % R;
-  if (R > 1) bh /= R;
   const int32_t b = bh / a.H, h = bh % a.H;
 
   const __bf16* qp = (const __bf16*)a.q.ptr + (int64_t)b * a.q.sb + (int64_t)h * a.q.sh;
@@ -1088,33 +1085,55 @@ __device__ __forceinline__ void dq_body(const BwdArgs& a, uint32_t id) {
   }
 }
 
+// Work item `id`; with R > 1 the work map counts R heads for each.
+template <int D, int BLK, bool kExact, int S, int R>
+__device__ __forceinline__ void dq_item(const BwdArgs& a, uint32_t id) {
+  int32_t bh, qb;
+  if (!work_item(a.work, id, bh, qb)) return;
+  const int32_t part = R == 1 ? 0 : bh % R;
+  if (R > 1) bh /= R;
+  dq_body<D, BLK, kExact, S, R>(a, bh, qb, part);
+}
 template <int D, int BLK, bool kExact, int S, int R>
 __global__ void __launch_bounds__(2 * BLK / R * S, 2) radial_bwd_dq_kernel(const BwdArgs a) {
-  dq_body<D, BLK, kExact, S, R>(a, blockIdx.x);
+  dq_item<D, BLK, kExact, S, R>(a, blockIdx.x);
 }
 
 // dK/dV and dQ in one launch (see both_groups): the first n_key workgroups take key blocks, the others query blocks.
 template <int D, int BLK, bool kExact, int S, int R>
 __global__ void __launch_bounds__(2 * BLK / R * S, 2) radial_bwd_both_kernel(const BwdArgs a, uint32_t n_key) {
   if (blockIdx.x < n_key) dkdv_body<D, BLK, kExact, S, R, true>(a, blockIdx.x);
-  else dq_body<D, BLK, kExact, S, R>(a, blockIdx.x - n_key);
+  else dq_item<D, BLK, kExact, S, R>(a, blockIdx.x - n_key);
 }
 
 template <int D, int BLK, bool kExact>
 __global__ void __launch_bounds__(4 * BLK, 2) radial_bwd_dkdv_pairs_kernel(const BwdArgs a) {
   pairs_body<D, BLK, kExact>(a, blockIdx.x);
 }
-// The same at head dimension 128, blocks of 128: dK/dV in pairs of waves, dQ by two groups.
-template <int D, int BLK, bool kExact>
+// The same at head dimension 128, blocks of 128: dK/dV in pairs of waves, dQ by two groups; kHalves: the last a.work.halved query blocks in
+// two halves, of 64 rows and four groups each (an instance of its own: with both in one, 3 scalar registers of the loops go to memory).
+template <int D, int BLK, bool kExact, bool kHalves>
 __global__ void __launch_bounds__(4 * BLK, 2) radial_bwd_both_pairs_kernel(const BwdArgs a, uint32_t n_key) {
-  if (blockIdx.x < n_key) pairs_body<D, BLK, kExact>(a, blockIdx.x);
-  else dq_body<D, BLK, kExact, 2, 1>(a, blockIdx.x - n_key);
+  if (blockIdx.x < n_key) {
+    pairs_body<D, BLK, kExact>(a, blockIdx.x);
+    return;
+  }
+  const uint32_t id = blockIdx.x - n_key;
+  if constexpr (kHalves) {
+    const uint32_t whole = gridDim.x - n_key - 2u * (uint32_t)a.work.halved;
+    if (id >= whole) {
+      int32_t bh, qb, part = 0;
+      if (work_item(a.work, halved_item(id, whole, (uint32_t)a.work.halved, part), bh, qb)) dq_body<D, BLK, kExact, 4, 2>(a, bh, qb, part);
+      return;
+    }
+  }
+  dq_item<D, BLK, kExact, 2, 1>(a, id);
 }
 // With the hand-made schedule, one wave per SIMD: two groups of 64 rows each.
 template <int D, int BLK, bool kExact>
 __global__ void __launch_bounds__(256, 1) radial_bwd_both_hand_kernel(const BwdArgs a, uint32_t n_key) {
   if (blockIdx.x < n_key) dkdv_body<D, BLK, kExact, 2, BLK / 64, false>(a, blockIdx.x);
-  else dq_body<D, BLK, kExact, 2, BLK / 64>(a, blockIdx.x - n_key);
+  else dq_item<D, BLK, kExact, 2, BLK / 64>(a, blockIdx.x - n_key);
 }
 
 template <int D, int BLK, bool kExact, int S, int R, bool kTwoWaves = false>
@@ -1171,15 +1190,16 @@ int launch_both(BwdArgs a, hipStream_t stream) {
   return RADIAL_OK;
 }
 
-template <bool kExact>
+template <bool kExact, bool kHalves>
 int launch_both_pairs(const BwdArgs& a, hipStream_t stream) {
   constexpr int kKeyBytes = PairTile<128, 128>::kLdsBytes, kQueryBytes = DqTile<128, 128, 2, 1>::kLdsBytes;
   constexpr int kBytes = kKeyBytes > kQueryBytes ? kKeyBytes : kQueryBytes;
-  const auto kernel = radial_bwd_both_pairs_kernel<128, 128, kExact>;
+  static_assert(!kHalves || DqTile<128, 128, 4, 2>::kLdsBytes <= kBytes);
+  const auto kernel = radial_bwd_both_pairs_kernel<128, 128, kExact, kHalves>;
   static DeviceOnce configured;
   if (int rc = allow_dynamic_lds(configured, (const void*)kernel, kBytes)) return rc;
   const uint32_t n_key = (uint32_t)work_grid(a.work_t, a.n_blocks);
-  kernel<<<dim3(n_key + (unsigned)work_grid(a.work, a.n_blocks)), dim3(512), kBytes, stream>>>(a, n_key);
+  kernel<<<dim3(n_key + (unsigned)(work_grid(a.work, a.n_blocks) + a.work.halved)), dim3(512), kBytes, stream>>>(a, n_key);
   RADIAL_HIP_TRY(hipGetLastError());
   return RADIAL_OK;
 }
@@ -1222,7 +1242,11 @@ int launch(const BwdArgs& a, hipStream_t stream) {
   } else {
     if (form.kind == BackwardForm::kTogetherByHand) return launch_both_hand<BLK, kExact>(a, stream);
     if constexpr (BLK == 128) {
-      if (form.kind == BackwardForm::kTogetherInPairs) return launch_both_pairs<kExact>(a, stream);
+      if (form.kind == BackwardForm::kTogetherInPairs) {
+        BwdArgs both = a;
+        both.work.halved = halved_query_items(a.work, items);
+        return both.work.halved ? launch_both_pairs<kExact, true>(both, stream) : launch_both_pairs<kExact, false>(both, stream);
+      }
       rc = form.key == 2 ? launch_dkdv<D, BLK, kExact, 2, 2>(a, stream) : launch_dkdv_pairs<128, kExact>(a, stream);
     } else {
       rc = form.key == 2 ? launch_dkdv<D, BLK, kExact, 2, 1>(a, stream) : launch_dkdv<D, BLK, kExact, 1, 1>(a, stream);

@@ -422,7 +422,7 @@ __global__ void __launch_bounds__(2 * BLK, 2) radial_fwd_halves_kernel(const Fwd
     if (!work_item(a.work, blockIdx.x, bh, qb)) return;
     fwd_body<D, BLK, kExact, kTrace, 1, 1, true>(a, bh, qb, 0, (int64_t)blockIdx.x);
   } else {
-    const uint32_t id = halved_item(whole, (uint32_t)a.work.halved, part);
+    const uint32_t id = halved_item(blockIdx.x, whole, (uint32_t)a.work.halved, part);
     if (!work_item(a.work, id, bh, qb)) return;
     fwd_body<D, BLK, kExact, kTrace, 2, 2, true>(a, bh, qb, part, (int64_t)id);
   }

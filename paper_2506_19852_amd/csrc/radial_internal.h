@@ -332,6 +332,41 @@ inline int32_t halved_items(const WorkMap& w, int64_t items) {
   return items > kOneRound && rest <= kOneRound / 2 && w.sliced == 0 && w.longest >= 4 ? (int32_t)rest : 0;
 }
 
+// The common backward launch in pairs (D 128, blocks of 128): a compute unit holds one workgroup, dK/dV's go first and dQ's last, so the end of the
+// launch waits for a whole dQ list on however few units.  In two halves, of 64 rows and four groups that walk a quarter of the list each, the last
+// lists end sooner, at more copies per product (1.16 of the time, as much as 8 % of a launch that ends evenly as it is).  Which it is
+// depends on where the rounds fall: the launch is laid out as if lists were equal, a unit at a time to the workgroup that is next, at the
+// measured 40 : 31 : 18 of a dK/dV, a dQ and half a dQ list, and halves are taken where that ends 4 % earlier.
+// Backward, us, whole lists / (64 or 128 halved), predicted in brackets, radial lists unless said: 129 items 204 / (64) 180 [0.79], 170 194 / (128) 178
+// [0.94], 306 305 / (128) 292 [0.92], 294 375 / (128) 366 [0.87], 400 557 / (64) 520 [0.90], 513 equal lists 324 / (128) 306 [0.93], 812 1277 / (128)
+// 1245 [0.95]; not taken: 216 218 / (128) 237 [1.07], 238 219 / (128) 237 [1.07], 330 470 / (128) 490 [1.05], 372 795 / (128) 827 [1.05], 450 2812 / (128) 2872
+// [0.97], 506 335 / (128) 343 [1.04], 1280 5649 / (128) 5703 [1.01], 1455 3025 / (128) 2964 [0.97].
+inline int32_t common_launch_end(int64_t items, int64_t halved) {
+  constexpr int32_t kKey = 40, kQuery = 31, kHalf = 18;
+  int16_t free_at[640] = {(int16_t)kOneRound};  // units by the time they are free; items <= 6 * kOneRound end before 6 * (kKey + 2 * kHalf) + kKey
+  int32_t now = 0, end = 0;
+  const auto run = [&](int64_t workgroups, int32_t time) {
+    while (workgroups > 0) {
+      while (free_at[now] == 0) ++now;
+      const int64_t n = workgroups < free_at[now] ? workgroups : free_at[now];
+      free_at[now] -= (int16_t)n;
+      free_at[now + time] += (int16_t)n;
+      end = now + time > end ? now + time : end;
+      workgroups -= n;
+    }
+  };
+  run(items, kKey);
+  run(items - halved, kQuery);
+  run(2 * halved, kHalf);
+  return end;
+}
+inline int32_t halved_query_items(const WorkMap& w, int64_t items) {
+  if (w.sliced != 0 || items <= kOneRound / 2 || items > 6 * kOneRound || w.mean < 4) return 0;
+  const int32_t whole = common_launch_end(items, 0), some = common_launch_end(items, 64), more = common_launch_end(items, 128);
+  const int32_t best = more < some ? more : some;
+  return 25 * best > 24 * whole ? 0 : more < some ? 128 : 64;
+}
+
 // 8-bit scores: three groups of 4 waves (12 waves are what a compute unit holds of this kernel) while every item can
 // have a compute unit of its own.  64 items: L 4 16.9 / 17.7, L 6 22.3 / 19.8; 105 items L 5 (with the quantisation) 40.4 / 37.5; 256 items: L 6 24.0 / 22.7, L 32 93.5 / 69.0;
 // 288 items (with the quantisation) 127 / 133.

@@ -299,10 +299,10 @@ __device__ __forceinline__ bool work_item(const WorkMap& w, uint32_t id, int32_t
   return pos < w.slice[sl + 1] - s0;
 }
 
-// Where the last `halved` items of a launch are taken in two halves: item and half of this workgroup.  Both halves of an item
+// Where the last `halved` items of a launch are taken in two halves: item and half of workgroup `id`.  Both halves of an item
 // are on one XCD (8 workgroups apart) while 8 items are left.
-__device__ __forceinline__ uint32_t halved_item(uint32_t first, uint32_t halved, int32_t& part) {
-  const uint32_t j = blockIdx.x - first, by8 = halved >> 3;
+__device__ __forceinline__ uint32_t halved_item(uint32_t id, uint32_t first, uint32_t halved, int32_t& part) {
+  const uint32_t j = id - first, by8 = halved >> 3;
   if (j < 16u * by8) {
     part = (int32_t)(j >> 3) & 1;
     return first + (j >> 4) * 8u + (j & 7u);

@@ -1,0 +1,51 @@
+"""The rule for halves at the end of a common backward launch, as the library compiles it, against the same lists laid out on 256
+units one by one, up to the largest common launch."""
+import heapq
+import os
+import shutil
+import subprocess
+
+import pytest
+
+from paper_2506_19852_amd import build as hip_build
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+SOURCE = os.path.join(ROOT, "tests", "host", "halved_queries.hip")
+
+
+@pytest.fixture(scope="module")
+def rule(tmp_path_factory):
+    if not os.path.exists(hip_build.HIPCC) and shutil.which(hip_build.HIPCC) is None:
+        pytest.skip("hipcc not available")
+    exe = tmp_path_factory.mktemp("host") / "halved_queries"
+    r = subprocess.run([hip_build.HIPCC, *hip_build.FLAGS, "--cuda-host-only", SOURCE, "-o", str(exe)],
+                       stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    assert r.returncode == 0, r.stdout[-3000:]
+
+    def run(cases):
+        r = subprocess.run([str(exe)], input="\n".join("%d %d %d" % c for c in cases), stdout=subprocess.PIPE, text=True, timeout=60)
+        assert r.returncode == 0
+        return [tuple(map(int, line.split())) for line in r.stdout.split("\n") if line]
+    return run
+
+
+def laid_out(items, halved):
+    units = [0] * 256
+    for n, time in ((items, 40), (items - halved, 31), (2 * halved, 18)):
+        for _ in range(n):
+            heapq.heapreplace(units, units[0] + time)
+    return max(units)
+
+
+def test_rule_matches_lists_laid_out_one_by_one(rule):
+    sizes = sorted({129, 130, 192, 193, 255, 256, 257, 512, 513, 768, 769, 1024, 1535, 1536, *range(128, 1537, 37)})
+    for items, got in zip(sizes, rule([(n, 0, 30) for n in sizes])):
+        ends = [laid_out(items, h) for h in (0, 64, 128)]
+        best = min(ends[1:])
+        want = 0 if items <= 128 or 25 * best > 24 * ends[0] else (128 if ends[2] < ends[1] else 64)
+        assert got == (want, *ends), items
+
+
+def test_no_halves_in_other_launches(rule):
+    """Among slices, on lists of a few entries, where every workgroup has a unit, above the sizes of a common launch."""
+    assert [r[0] for r in rule([(400, 0, 4), (400, 1, 30), (400, 0, 3), (128, 0, 30), (1, 0, 30), (1537, 0, 30), (100000, 0, 30)])] == [64, 0, 0, 0, 0, 0, 0]
