@@ -849,12 +849,13 @@ __device__ __forceinline__ void pairs_body(const BwdArgs& a, uint32_t id) {
   }
 }
 
-template <int D, int BLK, int S, int R>
+// kBeside: in a launch with whole blocks of one group at head dimension 64, whose LDS two groups share on half-size stages.
+template <int D, int BLK, int S, int R, bool kBeside = false>
 struct DqTile {
   static constexpr int kRows = BLK / R;
   // Keys per stage of the dQ kernel.  Head dimension 128 with 64 rows walks half-size stages:
   // two 64-key stage buffers (64 KiB) per 2 waves would leave a compute unit with 4 waves.
-  static constexpr int kStageKeys = (D == 128 && kRows == 64) || kRows == 32 ? 32 : 64;
+  static constexpr int kStageKeys = (D == 128 && kRows == 64) || kRows == 32 || kBeside ? 32 : 64;
   static constexpr int kWaves = kRows / 32;  // one wave per 32 query rows
   static constexpr int kThreads = 64 * kWaves * S;
   static constexpr int kSubs = BLK / kStageKeys;
@@ -863,14 +864,14 @@ struct DqTile {
   static constexpr int kTileBytes = kStageKeys * D * 2;  // one K (or V) stage tile
   static constexpr int kLoadsPerWave = kTileBytes / 1024 / kWaves;
   static constexpr int kGroupBytes = 4 * kTileBytes;     // [stage buffer][K, V]
-  using Join = Merge<S, kWaves, kDTiles>;
+  using Join = Merge<S, kWaves, kDTiles, kBeside ? S * kGroupBytes : 160 * 1024>;
   static constexpr int kLdsBytes = S * kGroupBytes > Join::kLdsBytes ? S * kGroupBytes : Join::kLdsBytes;
 };
 
 // Part `part` of the R of query block qb.
-template <int D, int BLK, bool kExact, int S, int R>
+template <int D, int BLK, bool kExact, int S, int R, bool kBeside = false>
 __device__ __forceinline__ void dq_body(const BwdArgs& a, int32_t bh, int32_t qb, int32_t part) {
-  using T = DqTile<D, BLK, S, R>;
+  using T = DqTile<D, BLK, S, R, kBeside>;
   using SW = SwzTile<D>;
   // [group][stage buffer][K, V][kStageKeys x D bf16]; one group's are a static array, as in the forward
   __shared__ __attribute__((aligned(1024))) char lds_one[S == 1 ? T::kLdsBytes : 16];
@@ -1099,10 +1100,27 @@ __global__ void __launch_bounds__(2 * BLK / R * S, 2) radial_bwd_dq_kernel(const
   dq_item<D, BLK, kExact, S, R>(a, blockIdx.x);
 }
 
-// dK/dV and dQ in one launch (see both_groups): the first n_key workgroups take key blocks, the others query blocks.
+// The query blocks of a common launch, workgroup `id` of n: by S groups of waves in R parts each; the last a.work.halved of those parts in
+// two halves, of half the rows and twice the groups.
 template <int D, int BLK, bool kExact, int S, int R>
+__device__ __forceinline__ void dq_item_or_half(const BwdArgs& a, uint32_t id, uint32_t n) {
+  const uint32_t whole = n - 2u * (uint32_t)a.work.halved;
+  if (id < whole) {
+    dq_item<D, BLK, kExact, S, R>(a, id);
+    return;
+  }
+  int32_t bh, qb, half = 0;
+  if (!work_item(a.work, halved_item(id, whole, (uint32_t)a.work.halved, half), bh, qb)) return;
+  const int32_t part = R == 1 ? half : 2 * (bh % R) + half;
+  dq_body<D, BLK, kExact, 2 * S, 2 * R, S == 1>(a, R == 1 ? bh : bh / R, qb, part);
+}
+
+// dK/dV and dQ in one launch (see both_groups): the first n_key workgroups take key blocks, the others query blocks; kHalves: the last
+// of them in halves.
+template <int D, int BLK, bool kExact, int S, int R, bool kHalves>
 __global__ void __launch_bounds__(2 * BLK / R * S, 2) radial_bwd_both_kernel(const BwdArgs a, uint32_t n_key) {
   if (blockIdx.x < n_key) dkdv_body<D, BLK, kExact, S, R, true>(a, blockIdx.x);
+  else if constexpr (kHalves) dq_item_or_half<D, BLK, kExact, S, R>(a, blockIdx.x - n_key, gridDim.x - n_key);
   else dq_item<D, BLK, kExact, S, R>(a, blockIdx.x - n_key);
 }
 
@@ -1118,16 +1136,8 @@ __global__ void __launch_bounds__(4 * BLK, 2) radial_bwd_both_pairs_kernel(const
     pairs_body<D, BLK, kExact>(a, blockIdx.x);
     return;
   }
-  const uint32_t id = blockIdx.x - n_key;
-  if constexpr (kHalves) {
-    const uint32_t whole = gridDim.x - n_key - 2u * (uint32_t)a.work.halved;
-    if (id >= whole) {
-      int32_t bh, qb, part = 0;
-      if (work_item(a.work, halved_item(id, whole, (uint32_t)a.work.halved, part), bh, qb)) dq_body<D, BLK, kExact, 4, 2>(a, bh, qb, part);
-      return;
-    }
-  }
-  dq_item<D, BLK, kExact, 2, 1>(a, id);
+  if constexpr (kHalves) dq_item_or_half<D, BLK, kExact, 2, 1>(a, blockIdx.x - n_key, gridDim.x - n_key);
+  else dq_item<D, BLK, kExact, 2, 1>(a, blockIdx.x - n_key);
 }
 // With the hand-made schedule, one wave per SIMD: two groups of 64 rows each.
 template <int D, int BLK, bool kExact>
@@ -1173,19 +1183,23 @@ int launch_dq(BwdArgs a, hipStream_t stream) {
   return RADIAL_OK;
 }
 
-template <int BLK, bool kExact, int S, int R>
+template <int BLK, bool kExact, int S, int R, bool kHalves = false>
 int launch_both(BwdArgs a, hipStream_t stream) {
   constexpr int kKeyBytes = BwdTile<64, BLK, S, R>::kLdsBytes, kQueryBytes = DqTile<64, BLK, S, R>::kLdsBytes;
   constexpr int kStatic = S == 1 ? kQueryBytes : 0;  // one group's stage buffers in dQ
   constexpr int kBytes = S == 1 || kKeyBytes > kQueryBytes ? kKeyBytes : kQueryBytes;
   static_assert((S == 4 ? 1 : 2) * (kStatic + kBytes) <= 160 * 1024, "two workgroups per compute unit; groups of one wave have it to themselves");
-  const auto kernel = radial_bwd_both_kernel<64, BLK, kExact, S, R>;
+  if constexpr (kHalves) {
+    constexpr int kHalfBytes = DqTile<64, BLK, 2 * S, 2 * R, S == 1>::kLdsBytes;
+    static_assert(kHalfBytes <= kBytes);
+  }
+  const auto kernel = radial_bwd_both_kernel<64, BLK, kExact, S, R, kHalves>;
   static DeviceOnce configured;
   if (int rc = allow_dynamic_lds(configured, (const void*)kernel, kBytes)) return rc;
   a.work.ordered *= R;  // at most kOneRound items, where all heads are taken by list length
   a.work_t.ordered *= R;
   const uint32_t n_key = (uint32_t)work_grid(a.work_t, a.n_blocks);
-  kernel<<<dim3(n_key + (unsigned)work_grid(a.work, a.n_blocks)), dim3(2 * BLK / R * S), kBytes, stream>>>(a, n_key);
+  kernel<<<dim3(n_key + (unsigned)(work_grid(a.work, a.n_blocks) + a.work.halved)), dim3(2 * BLK / R * S), kBytes, stream>>>(a, n_key);
   RADIAL_HIP_TRY(hipGetLastError());
   return RADIAL_OK;
 }
@@ -1232,11 +1246,13 @@ int launch(const BwdArgs& a, hipStream_t stream) {
   const BackwardForm form = backward_form(D, BLK, a.work, a.work_t, items, apart);
   int rc;
   if constexpr (D == 64) {
-    if (form.kind == BackwardForm::kTogether) switch (form.key) {
-      case 4: return launch_both<BLK, kExact, 4, BLK / 32>(a, stream);
-      case 2: return launch_both<BLK, kExact, 2, BLK / 64>(a, stream);
-      default:  // blocks of 128 only
-        if constexpr (BLK == 128) return launch_both<BLK, kExact, 1, 1>(a, stream);
+    if (form.kind == BackwardForm::kTogether) {
+      BwdArgs both = a;
+      both.work.halved = form.key == 4 ? 0 : halved_query_items_64(BLK, a.work, items);
+      if (form.key == 4) return launch_both<BLK, kExact, 4, BLK / 32>(both, stream);
+      if (form.key == 2) return both.work.halved ? launch_both<BLK, kExact, 2, BLK / 64, true>(both, stream) : launch_both<BLK, kExact, 2, BLK / 64>(both, stream);
+      if constexpr (BLK == 128)  // the only ones of one group
+        return both.work.halved ? launch_both<BLK, kExact, 1, 1, true>(both, stream) : launch_both<BLK, kExact, 1, 1>(both, stream);
     }
     rc = form.key == 2 ? launch_dkdv<64, BLK, kExact, 2, BLK / 64, true>(a, stream) : launch_dkdv<64, BLK, kExact, 1, 1, true>(a, stream);
   } else {

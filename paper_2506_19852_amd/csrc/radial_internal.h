@@ -367,6 +367,20 @@ inline int32_t halved_query_items(const WorkMap& w, int64_t items) {
   return 25 * best > 24 * whole ? 0 : more < some ? 128 : 64;
 }
 
+// The same at D 64, where two workgroups share a compute unit.  dQ's parts are laid over what dK/dV, as many workgroups, leave of the units: halves pay
+// where that is a little more than half of them (129 to 176 parts), and where the last round of 256 has few parts (1 to 72).
+// Backward, us, whole parts / with halves.  Block 64, items: 132 33.9 / 31.3, 168 40.5 / 39.0, 175 36.9 / 35.5 (184 with 96 halved 0.98, 200 1.00, 210 1.05), 260 84.9 / 75.1,
+// 304 64.8 / 59.6, 328 71.7 / 68.2 (360 with 192 1.02, 378 1.02), 528 167 / 156, 792 348 / 328, 1032 569 / 549; equal lists 136 L 8 14.9 / 14.5, 272 L 4 17.9 / 16.9, 272 L 8 22.5 / 20.8;
+// token rule 294 80.8 / 71.0.  Block 128 (two parts a block up to 256): 66 60.2 / 54.1, 80 71.6 / 66.1 (96 with 96 1.03, 114 1.05, 126 1.05), 132 106 / 94, 148 118 / 110, 164 130 /
+// 127 (175 with 192 0.98, 225 1.07), 264 252 / 221, 320 232 / 216 (360 with 192 1.01, 410 1.00, 450 1.04), 528 441 / 406, 816 634 / 603, 784 2541 / 2333 (600 0.99, 1000 1.00, 1104
+// 1.00); equal lists 136 L 4 23.8 / 21.8, 280 L 4 46.8 / 46.9; token rule 320 236 / 218.
+inline int32_t halved_query_items_64(int block, const WorkMap& w, int64_t items) {
+  const int64_t parts = block == 128 && items <= kOneRound ? 2 * items : items, rest = parts % kOneRound;
+  if (w.sliced != 0 || w.mean < 4 || parts <= kOneRound / 2) return 0;
+  if (parts <= kOneRound) return parts <= 176 ? 96 : 0;
+  return rest >= 1 && rest <= 72 ? 192 : 0;
+}
+
 // 8-bit scores: three groups of 4 waves (12 waves are what a compute unit holds of this kernel) while every item can
 // have a compute unit of its own.  64 items: L 4 16.9 / 17.7, L 6 22.3 / 19.8; 105 items L 5 (with the quantisation) 40.4 / 37.5; 256 items: L 6 24.0 / 22.7, L 32 93.5 / 69.0;
 // 288 items (with the quantisation) 127 / 133.

@@ -1,9 +1,10 @@
-"""Backward of head dimension 128 in blocks of 128 whose last query blocks are taken in halves (the numbers of blocks at which the rule
-takes 64 and 128 of them, and neighbours at which it takes none), ragged ends in either half, lists of 0 entries, of one (groups
-without any), of a few and of all blocks, the token rule, against float64."""
+"""Backward in one launch whose last query blocks are taken in halves (the numbers of blocks at which the rules take some, and
+neighbours at which they take none), ragged ends in either half, lists of 0 entries, of one (groups without any), of a few and of
+all blocks, the token rule, against float64."""
 import pytest
 
 import test_gpu_halved_blocks as halved_blocks
+import test_gpu_list_split as list_split
 
 pytestmark = pytest.mark.gpu
 
@@ -12,3 +13,11 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("rule", [False, True])
 def test_backward_matches_float64(H, nb, cut, rule):
     halved_blocks.test_forward_and_backward_match_float64(128, H, nb, cut, rule)
+
+
+@pytest.mark.parametrize("block, H, N", [
+    (64, 3, 43 * 64 - 1), (64, 4, 44 * 64), (64, 3, 59 * 64 - 63), (64, 5, 52 * 64 - 31), (64, 8, 41 * 64 - 32), (64, 7, 47 * 64),
+    (128, 5, 13 * 128 - 64), (128, 4, 22 * 128 - 127), (128, 4, 33 * 128 - 1), (128, 4, 41 * 128 - 32), (128, 8, 33 * 128 - 65), (128, 8, 41 * 128 - 96), (128, 7, 47 * 128)])
+@pytest.mark.parametrize("rule", [False, True])
+def test_head_dimension_64_matches_float64(block, H, N, rule):
+    list_split.test_forward_and_backward_match_float64(64, block, H, N, rule)
