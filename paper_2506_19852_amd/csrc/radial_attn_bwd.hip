@@ -494,7 +494,7 @@ __global__ void __launch_bounds__(2 * BLK / R * S, 2) radial_bwd_dkdv_two_kernel
 //   stage u:  first wave   S(u), P(u) -> LDS, dV += P(u)^T dO(u)
 //             second wave  dS(u - 1) = P(u - 1) * (dP(u - 1) - delta), dP(u), dK += dS(u - 1)^T Q(u - 1)
 // so Q has three stage buffers and dO two, and the vector part of one wave falls on the matrix part of the other.
-// Wave w and wave w + kPairs share keys: they are on one SIMD.  206 registers (235 under the token rule; beside dQ in one launch 250
+// Wave w and wave w + kPairs share keys: they are on one SIMD.  206 registers (233 under the token rule; beside dQ in one launch 250
 // and 256), and a pair that sees nothing of a stage skips it, which one wave with four products had no registers for.
 // The chip lowers its clock for the busier matrix pipes (8 x 126 360 tokens, radial lists: 46 % busy at 2.05 GHz -> 54 % at 1.87), so the large
 // launches gain least.  Backward pass, one wave with four products / pairs: 8 x 126 360 tokens 82.5 / 80.3 ms, 5 x 14 040 1728 / 1653 us,

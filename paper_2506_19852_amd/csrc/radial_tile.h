@@ -406,25 +406,10 @@ __host__ __device__ __forceinline__ uint32_t elements_from(int32_t x) {
   return (uint32_t)(~0ull << (4 * (x >> 3) + min(x & 7, 4)));
 }
 
-// The StageRule of a lane's own token at position own of its frame, for a stage that starts at `pos` of a frame: hw0 and hw1 are the half
-// widths of the pairs (own frame, stage's first frame) and (own frame, the next).
+// The elements of a stage that starts at position pos of a frame which a token at position own of its frame does not see, in lane group g: hw0 and hw1
+// are the half widths of the pairs (own frame, stage's first frame) and (own frame, the next).  The bounds of stage_intervals straight
+// as elements: by way of its intervals the forward of 30 heads x 24 x 316 tokens takes 533 us instead of 526, 1 x 108 x 1010 backward 4333 instead of 4209.
 // kWidth: tokens in the stage (64, or 32 for the kernels that walk half-size stages).
-template <int kWidth>
-__host__ __device__ __forceinline__ StageRule visible_intervals(int32_t own, int32_t pos, int32_t hw0, int32_t hw1, int32_t s) {
-  const int32_t split = s - pos;  // stage offset at which the second frame starts
-  StageRule r;
-  // first frame: positions pos + x, x in [0, min(split, kWidth)), within hw0 of own
-  const int32_t a0 = max(own - hw0 - pos, 0), b0 = min(own + hw0 - pos, min(split, kWidth) - 1);
-  r.lo0 = a0;
-  r.n0 = b0 >= a0 ? (uint32_t)(b0 - a0 + 1) : 0u;
-  // second frame: positions x - split, x in [split, kWidth), within hw1 of own
-  const int32_t a1 = max(own - hw1 + split, split), b1 = min(own + hw1 + split, kWidth - 1);
-  r.lo1 = a1;
-  r.n1 = b1 >= a1 ? (uint32_t)(b1 - a1 + 1) : 0u;
-  return r;
-}
-
-// The elements that the token does not see, in lane group g.
 template <int kWidth>
 __host__ __device__ __forceinline__ uint32_t hidden_elements(int32_t own, int32_t pos, int32_t hw0, int32_t hw1, int32_t s, int g) {
   const int32_t split = s - pos, own_g = own - 4 * g;
@@ -437,10 +422,21 @@ __host__ __device__ __forceinline__ uint32_t hidden_elements(int32_t own, int32_
 __host__ __device__ __forceinline__ int32_t pair_half_width(const TokenRule& rule, int32_t own, int32_t other, bool own_is_query) {
   return own_is_query ? radial_half_width(rule, own, other) : radial_half_width(rule, other, own);
 }
+// The StageRule of a lane's own token: the rule as intervals, which the element masks are held against on the host.
 template <int kWidth>
 __host__ __device__ __forceinline__ StageRule stage_intervals(const TokenRule& rule, StagePos own, StagePos stage, bool own_is_query) {
-  return visible_intervals<kWidth>(own.pos, stage.pos, pair_half_width(rule, own.frame, stage.frame, own_is_query),
-                                   pair_half_width(rule, own.frame, stage.frame + 1, own_is_query), rule.s);
+  const int32_t hw0 = pair_half_width(rule, own.frame, stage.frame, own_is_query), hw1 = pair_half_width(rule, own.frame, stage.frame + 1, own_is_query);
+  const int32_t split = rule.s - stage.pos;  // stage offset at which the second frame starts
+  StageRule r;
+  // first frame: positions stage.pos + x, x in [0, min(split, kWidth)), within hw0 of own.pos
+  const int32_t a0 = max(own.pos - hw0 - stage.pos, 0), b0 = min(own.pos + hw0 - stage.pos, min(split, kWidth) - 1);
+  r.lo0 = a0;
+  r.n0 = b0 >= a0 ? (uint32_t)(b0 - a0 + 1) : 0u;
+  // second frame: positions x - split, x in [split, kWidth), within hw1 of own.pos
+  const int32_t a1 = max(own.pos - hw1 + split, split), b1 = min(own.pos + hw1 + split, kWidth - 1);
+  r.lo1 = a1;
+  r.n1 = b1 >= a1 ? (uint32_t)(b1 - a1 + 1) : 0u;
+  return r;
 }
 
 // What a wave's 32 consecutive tokens cover: positions lo .. hi of a frame and, with s >= 64, at most 0 .. hi2 of the next (hi2 < 0: none).
