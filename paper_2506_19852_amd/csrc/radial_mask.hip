@@ -585,6 +585,10 @@ static int build_radial(radial_mask* m, const radial_mask_params* p, hipStream_t
     HostMeta shared;
     mask_lists_kernel<<<nb, kThreads, nwords * sizeof(uint32_t), st>>>(g, nwords, m->d_counts, m->d_row_ptr, m->d_order,
                                                                        Meta{m->d_meta, shared.device()}, m->d_col_idx);
+    if (const hipError_t e = hipGetLastError(); e != hipSuccess) {  // the transposed lists would be made of what was not written
+      shared.release();
+      return fail(RADIAL_EHIP, "mask lists failed: %s", hipGetErrorString(e));
+    }
     return finish_mask(m, shared, true, st);
   }
   mask_count_kernel<<<nb, kThreads, nwords * sizeof(uint32_t), st>>>(g, nwords, m->d_row_ptr);

@@ -1,0 +1,150 @@
+// The host side of the mask builds (radial_mask.hip) on a runtime that is written here: it hands out host memory, notes launches, copies and
+// waits, runs no kernel and refuses the launch it is told to.
+//   refuse : for each way to build a mask and each of its launches, that launch is refused; one line
+//     "way launch kernel status launches-after allocations-left"
+#include <stdio.h>
+#include <stdlib.h>
+#include <string.h>
+
+#include <atomic>
+#include <map>
+#include <string>
+
+#include "radial_mask.hip"
+
+namespace {
+
+std::map<const void*, std::string> kernel_names;
+std::atomic<int> launches{0}, refused{-1}, allocations{0}, copies_back{0};
+thread_local hipError_t last_error = hipSuccess;
+
+hipError_t noted(hipError_t e) {
+  if (e != hipSuccess) last_error = e;
+  return e;
+}
+
+}  // namespace
+
+extern "C" {
+// what the compiler calls around a kernel and its launch
+char __hip_fatbin[64];
+void** __hipRegisterFatBinary(const void*) {
+  static void* handle = nullptr;
+  return &handle;
+}
+void __hipUnregisterFatBinary(void**) {}
+void __hipRegisterFunction(void**, const void* host, char*, const char* name, unsigned, void*, void*, void*, void*, int*) { kernel_names[host] = name; }
+void __hipRegisterVar(void**, void*, char*, char*, int, size_t, int, int) {}
+static thread_local struct { dim3 grid, block; size_t lds; hipStream_t stream; } call;
+hipError_t __hipPushCallConfiguration(dim3 grid, dim3 block, size_t lds, hipStream_t stream) {
+  call = {grid, block, lds, stream};
+  return hipSuccess;
+}
+hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* lds, hipStream_t* stream) {
+  *grid = call.grid;
+  *block = call.block;
+  *lds = call.lds;
+  *stream = call.stream;
+  return hipSuccess;
+}
+hipError_t hipLaunchKernel(const void* kernel, dim3, dim3, void**, size_t, hipStream_t) {
+  if (launches++ != refused) return hipSuccess;
+  fputs(kernel_names[kernel].c_str(), stdout);
+  return noted(hipErrorLaunchFailure);
+}
+
+hipError_t hipGetLastError() {
+  const hipError_t e = last_error;
+  last_error = hipSuccess;
+  return e;
+}
+const char* hipGetErrorString(hipError_t) { return "refused"; }
+hipError_t hipGetDevice(int* device) {
+  *device = 0;
+  return hipSuccess;
+}
+hipError_t hipMalloc(void** p, size_t bytes) {
+  ++allocations;
+  *p = calloc(1, bytes);
+  return hipSuccess;
+}
+hipError_t hipFree(void* p) {
+  allocations -= p != nullptr;
+  free(p);
+  return hipSuccess;
+}
+hipError_t hipHostMalloc(void** p, size_t bytes, unsigned) {
+  *p = calloc(1, bytes);
+  return hipSuccess;
+}
+hipError_t hipHostGetDevicePointer(void** device, void* host, unsigned) {
+  *device = host;
+  return hipSuccess;
+}
+hipError_t hipMemcpy(void* to, const void* from, size_t bytes, hipMemcpyKind) {
+  memcpy(to, from, bytes);
+  return hipSuccess;
+}
+hipError_t hipMemcpyAsync(void* to, const void* from, size_t bytes, hipMemcpyKind kind, hipStream_t) {
+  copies_back += kind == hipMemcpyDeviceToHost;
+  memcpy(to, from, bytes);
+  return hipSuccess;
+}
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+}
+
+namespace {
+
+constexpr uint32_t kBoth = RADIAL_MASK_TRANSPOSE;
+struct Way {
+  const char* name;
+  int frames, tokens;  // of a radial or banded mask; tokens alone of the others
+  uint32_t flags;
+};
+// by the size of the lists: room for every pair, counted on the host, and too many blocks for an order
+const Way kWays[] = {{"radial", 4, 500, 0},       {"radial", 4, 500, kBoth},       {"radial", 4, 15000, 0},          {"radial", 4, 15000, kBoth},
+                     {"radial", 1100, 1000, 0},   {"radial", 1100, 1000, kBoth},   {"banded", 4, 500, kBoth},        {"banded", 1100, 1000, kBoth},
+                     {"dense", 0, 2000, 0},       {"dense", 0, 2000, kBoth},       {"dense", 0, 1100000, kBoth},     {"lists", 0, 2000, 0},
+                     {"lists", 0, 2000, kBoth},   {"lists", 0, 1100000, kBoth}};
+
+int build(const Way& way, radial_mask** m) {
+  static int32_t nothing[1 << 15];
+  switch (way.name[0]) {
+    case 'r': {
+      const radial_mask_params p = {way.frames, way.tokens, 64, 1, way.flags, 1, 1, 0};
+      return radial_mask_build(&p, nullptr, m);
+    }
+    case 'b': return radial_mask_build_banded(way.frames, way.tokens, 64, 1, nothing, way.flags, nullptr, m);
+    case 'd': return radial_mask_build_dense(way.tokens, 64, way.flags, nullptr, m);
+    default: return radial_mask_from_csr(way.tokens, 64, way.flags, nothing, nothing, nullptr, m);
+  }
+}
+
+int refuse() {
+  for (const Way& way : kWays) {
+    radial_mask* m = nullptr;
+    launches = 0;
+    if (build(way, &m) != RADIAL_OK) return 1;
+    radial_mask_free(m);
+    const int n = launches;
+    for (int k = 0; k < n; ++k) {
+      printf("%s-%d-%d-%u %d ", way.name, way.frames, way.tokens, way.flags, k);
+      launches = 0;
+      refused = k;
+      const int rc = build(way, &m);
+      refused = -1;
+      printf(" %d %d %d\n", rc, launches - k - 1, (int)allocations);
+      if ((rc == RADIAL_OK) != (m != nullptr)) return 1;
+      radial_mask_free(m);
+    }
+  }
+  return 0;
+}
+
+}  // namespace
+
+int main(int argc, char** argv) {
+  const std::string mode = argc > 1 ? argv[1] : "";
+  if (mode == "refuse") return refuse();
+  return 1;
+}

@@ -1,0 +1,39 @@
+"""The host side of the mask builds on a runtime written for the test (tests/host/mask_runtime.hip): no GPU, no kernel runs."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+from paper_2506_19852_amd import build as hip_build
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+SOURCE = os.path.join(ROOT, "tests", "host", "mask_runtime.hip")
+RADIAL_EHIP = -3
+
+
+@pytest.fixture(scope="module")
+def program(tmp_path_factory):
+    if not os.path.exists(hip_build.HIPCC) and shutil.which(hip_build.HIPCC) is None:
+        pytest.skip("hipcc not available")
+    exe = tmp_path_factory.mktemp("host") / "mask_runtime"
+    r = subprocess.run([hip_build.HIPCC, *hip_build.FLAGS, "--cuda-host-only", SOURCE, "-o", str(exe)],
+                       stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    assert r.returncode == 0, r.stdout[-3000:]
+
+    def run(mode):
+        r = subprocess.run([str(exe), mode], stdout=subprocess.PIPE, text=True, timeout=60)
+        assert r.returncode == 0, r.stdout[-3000:]
+        return [line.split() for line in r.stdout.splitlines()]
+    return run
+
+
+def test_nothing_follows_a_refused_launch_of_the_lists(program):
+    """The transposed lists are made of what that kernel writes: without it they would search uninitialised memory."""
+    found = 0
+    for way, launch, kernel, status, after, left in program("refuse"):
+        if "mask_lists_kernel" not in kernel:
+            continue
+        found += 1
+        assert (int(status), int(after), int(left)) == (RADIAL_EHIP, 0, 0), (way, launch, kernel)
+    assert found == 5, found
