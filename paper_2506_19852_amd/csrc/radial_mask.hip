@@ -407,10 +407,11 @@ void launch_partition(const int32_t* ptr, int32_t nb, int32_t* order, const Meta
 }
 
 // A Meta's host side for the time of one build: a slot of one page of mapped host memory that the process keeps (mapping it anew would
-// cost more than it saves).  A build that finds no slot free, or no page, copies instead.
+// cost more than it saves).  A build that finds no slot free, or no page, copies instead.  One that ends early waits for what it has
+// queued on its stream before the slot goes to another; where the stream cannot be waited for, the slot is not used again.
 class HostMeta {
  public:
-  HostMeta() {
+  explicit HostMeta(hipStream_t stream) : stream_(stream) {
     const std::lock_guard<std::mutex> lock(mutex());
     static int32_t* const page = [] {
       void* p = nullptr;
@@ -433,6 +434,10 @@ class HostMeta {
     host_ = page + slot_ * kMetaInts;
     device_ = (int32_t*)device;
   }
+  HostMeta(const HostMeta&) = delete;
+  ~HostMeta() {
+    if (slot_ >= 0 && hipStreamSynchronize(stream_) == hipSuccess) release();
+  }
   // Once the kernels of the build have ended.
   void release() {
     if (slot_ < 0) return;
@@ -453,6 +458,7 @@ class HostMeta {
     static uint32_t bits = 0;
     return bits;
   }
+  hipStream_t stream_;
   int slot_ = -1;
   int32_t* host_ = nullptr;
   int32_t* device_ = nullptr;
@@ -507,7 +513,7 @@ int finish_mask(radial_mask* m, HostMeta& shared, bool rows_placed, hipStream_t 
   hipError_t e = hipGetLastError();
   if (e == hipSuccess && !shared.host()) e = hipMemcpyAsync(h_meta, m->d_meta, sizeof h_meta, hipMemcpyDeviceToHost, st);
   if (e == hipSuccess) e = hipStreamSynchronize(st);
-  if (e != hipSuccess) return fail(RADIAL_EHIP, "mask kernels failed: %s", hipGetErrorString(e));  // (the slot stays taken: they may write it yet)
+  if (e != hipSuccess) return fail(RADIAL_EHIP, "mask kernels failed: %s", hipGetErrorString(e));
   if (shared.host()) memcpy(h_meta, shared.host(), sizeof h_meta);
   shared.release();
   if (rows_placed) memcpy(&m->nnz, h_meta + kTotal, sizeof m->nnz);
@@ -582,13 +588,10 @@ static int build_radial(radial_mask* m, const radial_mask_params* p, hipStream_t
       for (int32_t r = 0; r < nb; ++r) m->nnz += counts[r];  // at most kMaxOrdered^2 = 2^28
     }
     if (int rc = alloc_idx(m)) return rc;
-    HostMeta shared;
+    HostMeta shared(st);
     mask_lists_kernel<<<nb, kThreads, nwords * sizeof(uint32_t), st>>>(g, nwords, m->d_counts, m->d_row_ptr, m->d_order,
                                                                        Meta{m->d_meta, shared.device()}, m->d_col_idx);
-    if (const hipError_t e = hipGetLastError(); e != hipSuccess) {  // the transposed lists would be made of what was not written
-      shared.release();
-      return fail(RADIAL_EHIP, "mask lists failed: %s", hipGetErrorString(e));
-    }
+    RADIAL_HIP_TRY(hipGetLastError());  // the transposed lists would be made of what was not written
     return finish_mask(m, shared, true, st);
   }
   mask_count_kernel<<<nb, kThreads, nwords * sizeof(uint32_t), st>>>(g, nwords, m->d_row_ptr);
@@ -602,7 +605,7 @@ static int build_radial(radial_mask* m, const radial_mask_params* p, hipStream_t
   if (int rc = alloc_idx(m)) return rc;
   mask_fill_kernel<<<nb, kThreads, nwords * sizeof(uint32_t), st>>>(g, nwords, m->d_row_ptr, m->d_col_idx);
   RADIAL_HIP_TRY(hipGetLastError());
-  HostMeta shared;
+  HostMeta shared(st);
   return finish_mask(m, shared, false, st);
 }
 
@@ -675,7 +678,7 @@ static int build_dense(radial_mask* m, hipStream_t st) {
   if (int rc = alloc_idx(m)) return rc;
   dense_fill_kernel<<<1024, kThreads, 0, st>>>((int32_t)nb, m->d_row_ptr, m->d_col_idx);
   RADIAL_HIP_TRY(hipGetLastError());
-  HostMeta shared;
+  HostMeta shared(st);
   return finish_mask(m, shared, false, st);
 }
 
@@ -710,7 +713,7 @@ static int build_from_csr(radial_mask* m, const int32_t* row_ptr, const int32_t*
   RADIAL_HIP_TRY(hipMemcpyAsync(m->d_row_ptr, row_ptr, sizeof(int32_t) * (nb + 1), hipMemcpyHostToDevice, st));
   if (m->nnz > 0)
     RADIAL_HIP_TRY(hipMemcpyAsync(m->d_col_idx, col_idx, sizeof(int32_t) * m->nnz, hipMemcpyHostToDevice, st));
-  HostMeta shared;
+  HostMeta shared(st);
   return finish_mask(m, shared, false, st);
 }
 

@@ -2,6 +2,7 @@
 // waits, runs no kernel and refuses the launch it is told to.
 //   refuse : for each way to build a mask and each of its launches, that launch is refused; one line
 //     "way launch kernel status launches-after allocations-left"
+//   ended : after 40 builds with each launch refused, one line "way copies" with the copies to the host of a build that succeeds
 #include <stdio.h>
 #include <stdlib.h>
 #include <string.h>
@@ -16,6 +17,7 @@ namespace {
 
 std::map<const void*, std::string> kernel_names;
 std::atomic<int> launches{0}, refused{-1}, allocations{0}, copies_back{0};
+std::atomic<const void*> refused_kernel{nullptr};
 thread_local hipError_t last_error = hipSuccess;
 
 hipError_t noted(hipError_t e) {
@@ -49,7 +51,7 @@ hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* lds, hipSt
 }
 hipError_t hipLaunchKernel(const void* kernel, dim3, dim3, void**, size_t, hipStream_t) {
   if (launches++ != refused) return hipSuccess;
-  fputs(kernel_names[kernel].c_str(), stdout);
+  refused_kernel = kernel;
   return noted(hipErrorLaunchFailure);
 }
 
@@ -128,15 +130,34 @@ int refuse() {
     radial_mask_free(m);
     const int n = launches;
     for (int k = 0; k < n; ++k) {
-      printf("%s-%d-%d-%u %d ", way.name, way.frames, way.tokens, way.flags, k);
       launches = 0;
       refused = k;
       const int rc = build(way, &m);
       refused = -1;
-      printf(" %d %d %d\n", rc, launches - k - 1, (int)allocations);
+      printf("%s-%d-%d-%u %d %s %d %d %d\n", way.name, way.frames, way.tokens, way.flags, k, kernel_names[refused_kernel].c_str(), rc, launches - k - 1, (int)allocations);
       if ((rc == RADIAL_OK) != (m != nullptr)) return 1;
       radial_mask_free(m);
     }
+  }
+  return 0;
+}
+
+int ended() {
+  for (const Way& way : kWays) {
+    radial_mask* m = nullptr;
+    for (int k = 0, n = 1; k < n; ++k)
+      for (int i = 0; i < 40; ++i) {
+        launches = 0;
+        refused = i < 39 ? k : -1;
+        const int rc = build(way, &m);
+        if ((rc == RADIAL_OK) != (i == 39)) return 1;
+        if (!rc) n = launches;
+        radial_mask_free(m);
+      }
+    copies_back = 0;
+    if (build(way, &m) != RADIAL_OK) return 1;
+    radial_mask_free(m);
+    printf("%s-%d-%d-%u %d\n", way.name, way.frames, way.tokens, way.flags, (int)copies_back);
   }
   return 0;
 }
@@ -146,5 +167,6 @@ int refuse() {
 int main(int argc, char** argv) {
   const std::string mode = argc > 1 ? argv[1] : "";
   if (mode == "refuse") return refuse();
+  if (mode == "ended") return ended();
   return 1;
 }

@@ -37,3 +37,10 @@ def test_nothing_follows_a_refused_launch_of_the_lists(program):
         found += 1
         assert (int(status), int(after), int(left)) == (RADIAL_EHIP, 0, 0), (way, launch, kernel)
     assert found == 5, found
+
+
+def test_builds_that_end_early_give_their_host_memory_back(program):
+    """Whatever was refused before: a build copies nothing back but the counts (one copy, where the host sizes the lists by them)."""
+    for way, copies in program("ended"):
+        counted = way.split("-")[0] in ("radial", "banded") and "-500-" not in way
+        assert int(copies) == int(counted), way
