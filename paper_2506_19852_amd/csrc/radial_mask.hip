@@ -401,9 +401,11 @@ int check_common(int64_t n_tokens, int32_t block, uint32_t flags) {
 // Device storage of a mask is three allocations: `meta` (two 64-bit totals and the two launch
 // partitions), `ptrs` (row_ptr and its order and, with the transposed lists, col_ptr and its order) and `idx` (col_idx and
 // row_idx).  The views d_row_ptr, d_col_ptr, ... point into them at 256-byte aligned offsets.
-void launch_partition(const int32_t* ptr, int32_t nb, int32_t* order, const Meta& meta, bool columns, hipStream_t st) {
+int launch_partition(const int32_t* ptr, int32_t nb, int32_t* order, const Meta& meta, bool columns, hipStream_t st) {
   const int32_t per = kThreads / 64;
   partition_kernel<<<1 + (order ? (nb + per - 1) / per : 0), kThreads, 0, st>>>(ptr, nb, order, meta, columns);
+  RADIAL_HIP_TRY(hipGetLastError());
+  return RADIAL_OK;
 }
 
 // A Meta's host side for the time of one build: a slot of one page of mapped host memory that the process keeps (mapping it anew would
@@ -495,23 +497,30 @@ int alloc_idx(radial_mask* m) {
 
 // Shared tail of the constructors: transposed lists (optional) and launch partitions, then the one
 // wait of the call for everything queued on the stream (the partitions come back to the host).
-// rows_placed: the rows' launch partitions and their total are written already.
+// rows_placed: the rows' launch partitions and their total are written already.  Here and above, every launch is checked before the
+// next: a kernel that finds what an earlier one should have written uninitialised reads and writes anywhere.
 int finish_mask(radial_mask* m, HostMeta& shared, bool rows_placed, hipStream_t st) {
   const int32_t nb = m->n_blocks;
   const Meta meta = {m->d_meta, shared.device()};
   alignas(8) int32_t h_meta[kMetaInts];
-  if (!rows_placed) launch_partition(m->d_row_ptr, nb, m->d_order, meta, false, st);
+  if (!rows_placed)
+    if (int rc = launch_partition(m->d_row_ptr, nb, m->d_order, meta, false, st)) return rc;
   if ((m->flags & RADIAL_MASK_TRANSPOSE) && m->d_counts) {
     transpose_count_kernel<<<nb, kThreads, 0, st>>>(m->d_row_ptr, m->d_col_idx, nb, m->d_counts);
+    RADIAL_HIP_TRY(hipGetLastError());
     transpose_lists_kernel<<<nb, kThreads, 0, st>>>(m->d_row_ptr, m->d_col_idx, nb, m->d_counts, m->d_col_ptr, m->d_order_t, meta, m->d_row_idx);
+    RADIAL_HIP_TRY(hipGetLastError());
   } else if (m->flags & RADIAL_MASK_TRANSPOSE) {
     transpose_count_kernel<<<nb, kThreads, 0, st>>>(m->d_row_ptr, m->d_col_idx, nb, m->d_col_ptr);
+    RADIAL_HIP_TRY(hipGetLastError());
     scan_kernel<<<1, kThreads, 0, st>>>(m->d_col_ptr, nb, (long long*)(m->d_meta + kTotalT));
+    RADIAL_HIP_TRY(hipGetLastError());
     transpose_fill_kernel<<<nb, kThreads, 0, st>>>(m->d_row_ptr, m->d_col_idx, nb, m->d_col_ptr, m->d_row_idx);
-    launch_partition(m->d_col_ptr, nb, m->d_order_t, meta, true, st);
+    RADIAL_HIP_TRY(hipGetLastError());
+    if (int rc = launch_partition(m->d_col_ptr, nb, m->d_order_t, meta, true, st)) return rc;
   }
-  hipError_t e = hipGetLastError();
-  if (e == hipSuccess && !shared.host()) e = hipMemcpyAsync(h_meta, m->d_meta, sizeof h_meta, hipMemcpyDeviceToHost, st);
+  hipError_t e = hipSuccess;
+  if (!shared.host()) e = hipMemcpyAsync(h_meta, m->d_meta, sizeof h_meta, hipMemcpyDeviceToHost, st);
   if (e == hipSuccess) e = hipStreamSynchronize(st);
   if (e != hipSuccess) return fail(RADIAL_EHIP, "mask kernels failed: %s", hipGetErrorString(e));
   if (shared.host()) memcpy(h_meta, shared.host(), sizeof h_meta);
@@ -591,10 +600,11 @@ static int build_radial(radial_mask* m, const radial_mask_params* p, hipStream_t
     HostMeta shared(st);
     mask_lists_kernel<<<nb, kThreads, nwords * sizeof(uint32_t), st>>>(g, nwords, m->d_counts, m->d_row_ptr, m->d_order,
                                                                        Meta{m->d_meta, shared.device()}, m->d_col_idx);
-    RADIAL_HIP_TRY(hipGetLastError());  // the transposed lists would be made of what was not written
+    RADIAL_HIP_TRY(hipGetLastError());
     return finish_mask(m, shared, true, st);
   }
   mask_count_kernel<<<nb, kThreads, nwords * sizeof(uint32_t), st>>>(g, nwords, m->d_row_ptr);
+  RADIAL_HIP_TRY(hipGetLastError());
   scan_kernel<<<1, kThreads, 0, st>>>(m->d_row_ptr, nb, (long long*)m->d_meta);
   hipError_t e = hipGetLastError();
   if (e == hipSuccess) e = hipMemcpyAsync(&total, m->d_meta, sizeof total, hipMemcpyDeviceToHost, st);

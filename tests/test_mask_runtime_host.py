@@ -10,6 +10,8 @@ from paper_2506_19852_amd import build as hip_build
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 SOURCE = os.path.join(ROOT, "tests", "host", "mask_runtime.hip")
 RADIAL_EHIP = -3
+KERNELS = ("mask_count_kernel", "mask_lists_kernel", "mask_fill_kernel", "dense_fill_kernel", "transpose_count_kernel", "transpose_lists_kernel",
+           "transpose_fill_kernel", "scan_kernel", "partition_kernel")
 
 
 @pytest.fixture(scope="module")
@@ -28,15 +30,13 @@ def program(tmp_path_factory):
     return run
 
 
-def test_nothing_follows_a_refused_launch_of_the_lists(program):
-    """The transposed lists are made of what that kernel writes: without it they would search uninitialised memory."""
-    found = 0
+def test_nothing_follows_a_refused_launch(program):
+    """Each kernel of a build reads what the ones before it write: without those it would search and write by uninitialised memory."""
+    kernels = set()
     for way, launch, kernel, status, after, left in program("refuse"):
-        if "mask_lists_kernel" not in kernel:
-            continue
-        found += 1
+        kernels.add(next(k for k in KERNELS if k in kernel))
         assert (int(status), int(after), int(left)) == (RADIAL_EHIP, 0, 0), (way, launch, kernel)
-    assert found == 5, found
+    assert kernels == set(KERNELS)
 
 
 def test_builds_that_end_early_give_their_host_memory_back(program):
