@@ -235,7 +235,7 @@ def radial_attn_fwd(q, k, v, out, lse, mask: RadialMask, scale: float, stream=No
             raise ValueError("lse must be a contiguous CUDA float32 tensor [B, H, N]")
         lse_ptr = lse.data_ptr()
     _check(load().radial_attn_fwd(B, H, N, D, _tensor(q, "q"), _tensor(k, "k"), _tensor(v, "v"), _tensor(out, "out"),
-                                  lse_ptr, mask.handle, scale, _stream_ptr(stream)))
+                                  lse_ptr, mask.handle, c_float(scale), _stream_ptr(stream)))
 
 
 def radial_attn_fwd_trace_records(B: int, H: int, mask: RadialMask) -> int:
@@ -250,7 +250,7 @@ def radial_attn_fwd_trace(q, k, v, out, lse, mask: RadialMask, scale: float, tra
         raise ValueError("trace must be a contiguous CUDA int64 tensor [records, 3]")
     lse_ptr = lse.data_ptr() if lse is not None else None
     _check(load().radial_attn_fwd_trace(B, H, N, D, _tensor(q, "q"), _tensor(k, "k"), _tensor(v, "v"), _tensor(out, "out"),
-                                        lse_ptr, mask.handle, scale, _stream_ptr(stream),
+                                        lse_ptr, mask.handle, c_float(scale), _stream_ptr(stream),
                                         trace.data_ptr(), trace.shape[0]))
 
 
@@ -297,7 +297,7 @@ def radial_attn_fwd_fp8(q_codes, q_scales, k_codes, k_scales, v, out, lse, mask:
         lse_ptr = lse.data_ptr()
     _check(load().radial_attn_fwd_fp8(B, H, N, D, code_block, q_codes.data_ptr(), q_scales.data_ptr(),
                                       k_codes.data_ptr(), k_scales.data_ptr(), _tensor(v, "v"),
-                                      _tensor(out, "out"), lse_ptr, mask.handle, scale, _stream_ptr(stream)))
+                                      _tensor(out, "out"), lse_ptr, mask.handle, c_float(scale), _stream_ptr(stream)))
 
 
 def radial_attn_bwd_workspace(B: int, H: int, N: int, D: int, mask: RadialMask) -> int:
@@ -309,7 +309,7 @@ def radial_attn_bwd(q, k, v, out, dout, lse, dq, dk, dv, mask: RadialMask, scale
     B, H, N, D = q.shape
     ts = [_tensor(t, nm) for t, nm in ((q, "q"), (k, "k"), (v, "v"), (out, "out"), (dout, "dout"))]
     gs = [_tensor(t, nm) for t, nm in ((dq, "dq"), (dk, "dk"), (dv, "dv"))]
-    _check(load().radial_attn_bwd(B, H, N, D, *ts, lse.data_ptr(), *gs, mask.handle, scale,
+    _check(load().radial_attn_bwd(B, H, N, D, *ts, lse.data_ptr(), *gs, mask.handle, c_float(scale),
                                   workspace.data_ptr(), workspace.numel() * workspace.element_size(),
                                   _stream_ptr(stream)))
 
@@ -319,5 +319,5 @@ def radial_attn_bwd_static(q, k, v, out, dout, lse, dq, dk, dv, mask: RadialMask
     B, H, N, D = q.shape
     ts = [_tensor(t, nm) for t, nm in ((q, "q"), (k, "k"), (v, "v"), (out, "out"), (dout, "dout"))]
     gs = [_tensor(t, nm) for t, nm in ((dq, "dq"), (dk, "dk"), (dv, "dv"))]
-    _check(load().radial_attn_bwd_static(B, H, N, D, *ts, lse.data_ptr(), *gs, mask.handle, scale,
+    _check(load().radial_attn_bwd_static(B, H, N, D, *ts, lse.data_ptr(), *gs, mask.handle, c_float(scale),
                                          _stream_ptr(stream)))
