@@ -1100,19 +1100,31 @@ __global__ void __launch_bounds__(2 * BLK / R * S, 2) radial_bwd_dq_kernel(const
   dq_item<D, BLK, kExact, S, R>(a, blockIdx.x);
 }
 
+// The kernel's BwdArgs (its first parameter), for one part of a kernel that has several.  Through one name the compiler loads what the parts have in
+// common before they branch, and keeps all of it: up to 100 scalars in vector lanes under the token rule, a part of them reloaded in every stage, and
+// 68 bytes of private memory per lane that nothing used in two of the kernels with halves.  Asked for part by part there are none (7 in
+// pairs of waves under the token rule, as where dK/dV is a launch of its own).
+__device__ __forceinline__ const BwdArgs& own_args() {
+  using Args = const BwdArgs __attribute__((address_space(4)));
+  Args* args = (Args*)__builtin_amdgcn_kernarg_segment_ptr();
+  asm("" : "+s"(args));  // not known to be the same memory
+  return *(const BwdArgs*)args;
+}
+
 // The query blocks of a common launch, workgroup `id` of n: by S groups of waves in R parts each; the last a.work.halved of those parts in
 // two halves, of half the rows and twice the groups.
 template <int D, int BLK, bool kExact, int S, int R>
 __device__ __forceinline__ void dq_item_or_half(const BwdArgs& a, uint32_t id, uint32_t n) {
   const uint32_t whole = n - 2u * (uint32_t)a.work.halved;
   if (id < whole) {
-    dq_item<D, BLK, kExact, S, R>(a, id);
+    dq_item<D, BLK, kExact, S, R>(own_args(), id);
     return;
   }
+  const BwdArgs& b = own_args();
   int32_t bh, qb, half = 0;
-  if (!work_item(a.work, halved_item(id, whole, (uint32_t)a.work.halved, half), bh, qb)) return;
+  if (!work_item(b.work, halved_item(id, whole, (uint32_t)b.work.halved, half), bh, qb)) return;
   const int32_t part = R == 1 ? half : 2 * (bh % R) + half;
-  dq_body<D, BLK, kExact, 2 * S, 2 * R, S == 1>(a, R == 1 ? bh : bh / R, qb, part);
+  dq_body<D, BLK, kExact, 2 * S, 2 * R, S == 1>(b, R == 1 ? bh : bh / R, qb, part);
 }
 
 // dK/dV and dQ in one launch (see both_groups): the first n_key workgroups take key blocks, the others query blocks; kHalves: the last
@@ -1121,7 +1133,7 @@ template <int D, int BLK, bool kExact, int S, int R, bool kHalves>
 __global__ void __launch_bounds__(2 * BLK / R * S, 2) radial_bwd_both_kernel(const BwdArgs a, uint32_t n_key) {
   if (blockIdx.x < n_key) dkdv_body<D, BLK, kExact, S, R, true>(a, blockIdx.x);
   else if constexpr (kHalves) dq_item_or_half<D, BLK, kExact, S, R>(a, blockIdx.x - n_key, gridDim.x - n_key);
-  else dq_item<D, BLK, kExact, S, R>(a, blockIdx.x - n_key);
+  else dq_item<D, BLK, kExact, S, R>(own_args(), blockIdx.x - n_key);
 }
 
 template <int D, int BLK, bool kExact>
@@ -1129,7 +1141,7 @@ __global__ void __launch_bounds__(4 * BLK, 2) radial_bwd_dkdv_pairs_kernel(const
   pairs_body<D, BLK, kExact>(a, blockIdx.x);
 }
 // The same at head dimension 128, blocks of 128: dK/dV in pairs of waves, dQ by two groups; kHalves: the last a.work.halved query blocks in
-// two halves, of 64 rows and four groups each (an instance of its own: with both in one, 3 scalar registers of the loops go to memory).
+// two halves, of 64 rows and four groups each.
 template <int D, int BLK, bool kExact, bool kHalves>
 __global__ void __launch_bounds__(4 * BLK, 2) radial_bwd_both_pairs_kernel(const BwdArgs a, uint32_t n_key) {
   if (blockIdx.x < n_key) {
@@ -1137,13 +1149,13 @@ __global__ void __launch_bounds__(4 * BLK, 2) radial_bwd_both_pairs_kernel(const
     return;
   }
   if constexpr (kHalves) dq_item_or_half<D, BLK, kExact, 2, 1>(a, blockIdx.x - n_key, gridDim.x - n_key);
-  else dq_item<D, BLK, kExact, 2, 1>(a, blockIdx.x - n_key);
+  else dq_item<D, BLK, kExact, 2, 1>(own_args(), blockIdx.x - n_key);
 }
 // With the hand-made schedule, one wave per SIMD: two groups of 64 rows each.
 template <int D, int BLK, bool kExact>
 __global__ void __launch_bounds__(256, 1) radial_bwd_both_hand_kernel(const BwdArgs a, uint32_t n_key) {
   if (blockIdx.x < n_key) dkdv_body<D, BLK, kExact, 2, BLK / 64, false>(a, blockIdx.x);
-  else dq_item<D, BLK, kExact, 2, BLK / 64>(a, blockIdx.x - n_key);
+  else dq_item<D, BLK, kExact, 2, BLK / 64>(own_args(), blockIdx.x - n_key);
 }
 
 template <int D, int BLK, bool kExact, int S, int R, bool kTwoWaves = false>
