@@ -1101,10 +1101,16 @@ __global__ void __launch_bounds__(2 * BLK / R * S, 2) radial_bwd_dq_kernel(const
 }
 
 // The kernel's BwdArgs (its first parameter), for one part of a kernel that has several.  Through one name the compiler loads what the parts have in
-// common before they branch, and keeps all of it: up to 100 scalars in vector lanes under the token rule, a part of them reloaded in every stage, and
-// 68 bytes of private memory per lane that nothing used in two of the kernels with halves.  Asked for part by part there are none (7 in
-// pairs of waves under the token rule, as where dK/dV is a launch of its own).
-__device__ __forceinline__ const BwdArgs& own_args() {
+// common before they branch and keeps it: under the token rule up to 100 scalars in vector lanes, a part of them reloaded in every stage, and
+// with halves of whole blocks on two groups 68 bytes of private memory per lane that nothing uses.  kOwn: asked for part by part, there are none of
+// either (7 scalars in pairs of waves under the token rule, as where dK/dV is a launch of its own).  Elsewhere loads before the branch are the better
+// ones.  Training step, us, shared / own: token rule, D 64, block 64, 8 frames of 333 tokens, 4 heads 71.3 / 69.2, 24 x 316, 8 heads 538 / 520, block
+// 128, 9 x 310, 3 heads 76.5 / 72.8, 40 x 800, 4 heads 2757 / 2725, D 128, 6 x 427, 2 heads 110.8 / 109.1, 21 x 620, 3 heads 904 / 877; block-dense, halves of
+// whole blocks on two groups, 8 x 333, 4 heads 57.7 / 57.6, D 128, 9 x 613, 3 heads 251.5 / 250.8.  Not taken: groups of one wave, 5 x 256, 1 head, token rule
+// 26.36 / 26.55, block-dense 22.67 / 22.88; halves of half blocks, 9 x 310 57.7 / 58.1; one group, 20 x 410, 5 heads 446 / 451.
+template <bool kOwn>
+__device__ __forceinline__ const BwdArgs& part_args(const BwdArgs& a) {
+  if constexpr (!kOwn) return a;
   using Args = const BwdArgs __attribute__((address_space(4)));
   Args* args = (Args*)__builtin_amdgcn_kernarg_segment_ptr();
   asm("" : "+s"(args));  // not known to be the same memory
@@ -1117,10 +1123,10 @@ template <int D, int BLK, bool kExact, int S, int R>
 __device__ __forceinline__ void dq_item_or_half(const BwdArgs& a, uint32_t id, uint32_t n) {
   const uint32_t whole = n - 2u * (uint32_t)a.work.halved;
   if (id < whole) {
-    dq_item<D, BLK, kExact, S, R>(own_args(), id);
+    dq_item<D, BLK, kExact, S, R>(part_args<kExact || S * R == 2>(a), id);
     return;
   }
-  const BwdArgs& b = own_args();
+  const BwdArgs& b = part_args<kExact || S * R == 2>(a);
   int32_t bh, qb, half = 0;
   if (!work_item(b.work, halved_item(id, whole, (uint32_t)b.work.halved, half), bh, qb)) return;
   const int32_t part = R == 1 ? half : 2 * (bh % R) + half;
@@ -1133,7 +1139,7 @@ template <int D, int BLK, bool kExact, int S, int R, bool kHalves>
 __global__ void __launch_bounds__(2 * BLK / R * S, 2) radial_bwd_both_kernel(const BwdArgs a, uint32_t n_key) {
   if (blockIdx.x < n_key) dkdv_body<D, BLK, kExact, S, R, true>(a, blockIdx.x);
   else if constexpr (kHalves) dq_item_or_half<D, BLK, kExact, S, R>(a, blockIdx.x - n_key, gridDim.x - n_key);
-  else dq_item<D, BLK, kExact, S, R>(own_args(), blockIdx.x - n_key);
+  else dq_item<D, BLK, kExact, S, R>(part_args<kExact && S < 4>(a), blockIdx.x - n_key);
 }
 
 template <int D, int BLK, bool kExact>
@@ -1149,13 +1155,13 @@ __global__ void __launch_bounds__(4 * BLK, 2) radial_bwd_both_pairs_kernel(const
     return;
   }
   if constexpr (kHalves) dq_item_or_half<D, BLK, kExact, 2, 1>(a, blockIdx.x - n_key, gridDim.x - n_key);
-  else dq_item<D, BLK, kExact, 2, 1>(own_args(), blockIdx.x - n_key);
+  else dq_item<D, BLK, kExact, 2, 1>(part_args<kExact>(a), blockIdx.x - n_key);
 }
 // With the hand-made schedule, one wave per SIMD: two groups of 64 rows each.
 template <int D, int BLK, bool kExact>
 __global__ void __launch_bounds__(256, 1) radial_bwd_both_hand_kernel(const BwdArgs a, uint32_t n_key) {
   if (blockIdx.x < n_key) dkdv_body<D, BLK, kExact, 2, BLK / 64, false>(a, blockIdx.x);
-  else dq_item<D, BLK, kExact, 2, BLK / 64>(own_args(), blockIdx.x - n_key);
+  else dq_item<D, BLK, kExact, 2, BLK / 64>(part_args<kExact>(a), blockIdx.x - n_key);
 }
 
 template <int D, int BLK, bool kExact, int S, int R, bool kTwoWaves = false>
