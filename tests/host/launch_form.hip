@@ -4,7 +4,7 @@
 // go by list length in the forward, dQ and dK/dV kernels.  Run with the word "backward": one line "kind key query kind key query", the
 // form of a backward call whose dq has memory of its own, and of one whose dq is the memory of q or dout.  With "forward": one line
 // "single halved parts", whether a forward goes in groups of one wave, how many of its last blocks go in halves, and the workgroups
-// per block of the 8-bit forward.
+// per block of the 8-bit forward.  With "halves": one line "halved", how many of a backward call's last query blocks (or parts) go in halves.
 #include <stdio.h>
 
 #include "radial_internal.h"
@@ -30,6 +30,12 @@ int main(int argc, char** argv) {
     const int64_t items = work_items(w, nb);
     if (argc > 1 && argv[1][0] == 'f') {
       printf("%d %d %d\n", single_waves(block, w, items), halved_items(w, items), fp8_parts(w, items));
+      continue;
+    }
+    if (argc > 1 && argv[1][0] == 'h') {
+      const BackwardForm form = backward_form(D, block, wq, wt, items, true);
+      printf("%d\n", form.kind == BackwardForm::kTogether && form.key != 4 ? halved_query_items_64(block, wq, items)
+                     : form.kind == BackwardForm::kTogetherInPairs ? halved_query_items(wq, items) : 0);
       continue;
     }
     if (argc > 1) {

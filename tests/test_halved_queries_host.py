@@ -7,7 +7,10 @@ import subprocess
 
 import pytest
 
+from oracle import build as obuild
 from paper_2506_19852_amd import build as hip_build
+from test_gpu_halved_queries import CASES, CASES_64
+from test_launch_form_host import forms  # noqa: F401  (a fixture)
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 SOURCE = os.path.join(ROOT, "tests", "host", "halved_queries.hip")
@@ -58,3 +61,23 @@ def test_halves_at_head_dimension_64(rule):
     sizes = [64, 65, 88, 89, 128, 129, 164, 165, 256, 257, 328, 329, 513]
     assert [r[5] for r in rule([(n, 0, 30) for n in sizes])] == [0, 96, 96, 0, 0, 192, 192, 0, 0, 192, 192, 0, 192]
     assert [r[4:] for r in rule([(257, 1, 30), (257, 0, 3), (257, 0, 4)])] == [(0, 0), (0, 0), (192, 192)]
+
+
+def test_gpu_cases_take_the_halves_they_are_meant_to(forms):  # noqa: F811
+    """The launches of tests/test_gpu_halved_queries.py, with the lengths of the lists and the frames that its two tests make."""
+    def by_rule(frames, s, block, N):
+        bitmap, _ = obuild.mask_scan(frames, s, block, 1, 0, -(-N // block), 1, 1, N - frames * s)
+        return int(bitmap.sum()), int(bitmap.sum(1).max())
+    launches, want = [], []
+    for (H, nb, cut), halved in CASES.items():
+        N = 128 * nb - cut
+        lists = [nb if r == 3 else (9, 0, 1, 4, 5)[r % 5] for r in range(nb)]
+        launches += [(128, 128, H, nb, (sum(lists), max(lists))), (128, 128, H, nb, by_rule(N // 150, 150, 128, N))]
+        want += halved
+    for (block, H, N), halved in CASES_64.items():
+        nb = -(-N // block)
+        lists = [(0, 1, 2, 3, 5, nb)[r % 6] for r in range(nb)]
+        launches += [(64, block, H, nb, (sum(lists), max(lists))), (64, block, H, nb, by_rule(N // 128, N // (N // 128), block, N))]
+        want += halved
+    for launch, got, halved in zip(launches, forms(launches, "halves"), want):
+        assert got == (halved,), launch
