@@ -1,15 +1,24 @@
 // The host side of the mask builds (radial_mask.hip) on a runtime that is written here: it hands out host memory, notes launches, copies and
-// waits, runs no kernel and refuses the launch it is told to.
+// waits and refuses the launch it is told to.  Of the kernels it runs nothing but the total of mask_lists_kernel, for which it puts the number of tokens.
 //   refuse : for each way to build a mask and each of its launches, that launch is refused; one line
 //     "way launch kernel status launches-after allocations-left"
+//   unmapped : no host memory can be mapped; per way "way status copies total-is-right"
+//   together : 40 threads build at a time, each its own size, and wait for each other before any reads what came back; one line
+//     "threads copies wrong" and one of a build after them
+//   unwaited : the stream of three builds cannot be waited for; one line "wrong slots", those of later builds that were these three's
 //   ended : after 40 builds with each launch refused, one line "way copies" with the copies to the host of a build that succeeds
 #include <stdio.h>
 #include <stdlib.h>
 #include <string.h>
 
 #include <atomic>
+#include <condition_variable>
 #include <map>
+#include <mutex>
+#include <set>
 #include <string>
+#include <thread>
+#include <vector>
 
 #include "radial_mask.hip"
 
@@ -18,6 +27,11 @@ namespace {
 std::map<const void*, std::string> kernel_names;
 std::atomic<int> launches{0}, refused{-1}, allocations{0}, copies_back{0};
 std::atomic<const void*> refused_kernel{nullptr};
+std::atomic<bool> can_map{true}, can_wait{true};
+std::atomic<void*> last_slot{nullptr};
+std::mutex gate_mutex;
+std::condition_variable gate;
+int expected = 0, arrived = 0;  // threads that wait for each other in hipStreamSynchronize
 thread_local hipError_t last_error = hipSuccess;
 
 hipError_t noted(hipError_t e) {
@@ -49,8 +63,16 @@ hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* lds, hipSt
   *stream = call.stream;
   return hipSuccess;
 }
-hipError_t hipLaunchKernel(const void* kernel, dim3, dim3, void**, size_t, hipStream_t) {
-  if (launches++ != refused) return hipSuccess;
+hipError_t hipLaunchKernel(const void* kernel, dim3, dim3, void** args, size_t, hipStream_t) {
+  if (launches++ != refused) {
+    if (kernel_names.at(kernel).find("mask_lists_kernel") != std::string::npos) {
+      const radial::MaskGeom& g = *(const radial::MaskGeom*)args[0];
+      const radial::Meta& meta = *(const radial::Meta*)args[5];
+      meta.device[radial::kTotal] = g.n;
+      if (meta.host) meta.host[radial::kTotal] = g.n;
+    }
+    return hipSuccess;
+  }
   refused_kernel = kernel;
   return noted(hipErrorLaunchFailure);
 }
@@ -76,11 +98,13 @@ hipError_t hipFree(void* p) {
   return hipSuccess;
 }
 hipError_t hipHostMalloc(void** p, size_t bytes, unsigned) {
+  if (!can_map) return noted(hipErrorOutOfMemory);
   *p = calloc(1, bytes);
   return hipSuccess;
 }
 hipError_t hipHostGetDevicePointer(void** device, void* host, unsigned) {
   *device = host;
+  last_slot = host;
   return hipSuccess;
 }
 hipError_t hipMemcpy(void* to, const void* from, size_t bytes, hipMemcpyKind) {
@@ -92,7 +116,13 @@ hipError_t hipMemcpyAsync(void* to, const void* from, size_t bytes, hipMemcpyKin
   memcpy(to, from, bytes);
   return hipSuccess;
 }
-hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) {
+  if (!can_wait) return noted(hipErrorUnknown);
+  std::unique_lock<std::mutex> lock(gate_mutex);
+  if (arrived < expected && ++arrived == expected) gate.notify_all();
+  gate.wait(lock, [] { return arrived >= expected; });
+  return hipSuccess;
+}
 }
 
 namespace {
@@ -142,6 +172,64 @@ int refuse() {
   return 0;
 }
 
+int unmapped() {
+  can_map = false;
+  for (const Way& way : kWays) {
+    radial_mask* m = nullptr;
+    copies_back = 0;
+    const int rc = build(way, &m);
+    const bool placed = (way.name[0] == 'r' || way.name[0] == 'b') && way.frames * way.tokens <= 64 * radial::kMaxOrdered;
+    printf("%s-%d-%d-%u %d %d %d\n", way.name, way.frames, way.tokens, way.flags, rc, (int)copies_back, m && (!placed || m->nnz == way.frames * way.tokens));
+    radial_mask_free(m);
+  }
+  return 0;
+}
+
+int together() {
+  std::atomic<int> wrong{0};
+  const auto one = [&](int size) {
+    radial_mask* m = nullptr;
+    const Way way = {"radial", 3, size, 0};
+    wrong += build(way, &m) != RADIAL_OK || m->nnz != 3 * size;
+    radial_mask_free(m);
+  };
+  for (int round = 0; round < 20; ++round) {
+    copies_back = 0;
+    expected = 40;
+    arrived = 0;
+    std::vector<std::thread> threads;
+    for (int i = 0; i < 40; ++i) threads.emplace_back(one, 100 + i);
+    for (std::thread& t : threads) t.join();
+    printf("40 %d %d\n", (int)copies_back, (int)wrong);
+    expected = 0;
+    copies_back = 0;
+    one(99);
+    printf("1 %d %d\n", (int)copies_back, (int)wrong);
+  }
+  return 0;
+}
+
+int unwaited() {
+  const Way way = {"radial", 3, 100, 0};
+  radial_mask* m = nullptr;
+  std::set<void*> lost;
+  can_wait = false;
+  for (int i = 0; i < 3; ++i) {
+    if (build(way, &m) != RADIAL_EHIP) return 1;
+    lost.insert(last_slot);
+    (void)hipGetLastError();
+  }
+  can_wait = true;
+  int again = 0;
+  for (int i = 0; i < 5; ++i) {
+    if (build(way, &m) != RADIAL_OK) return 1;
+    radial_mask_free(m);
+    again += (int)lost.count(last_slot);
+  }
+  printf("%d %d\n", again, (int)lost.size());
+  return 0;
+}
+
 int ended() {
   for (const Way& way : kWays) {
     radial_mask* m = nullptr;
@@ -168,5 +256,8 @@ int main(int argc, char** argv) {
   const std::string mode = argc > 1 ? argv[1] : "";
   if (mode == "refuse") return refuse();
   if (mode == "ended") return ended();
+  if (mode == "unmapped") return unmapped();
+  if (mode == "together") return together();
+  if (mode == "unwaited") return unwaited();
   return 1;
 }

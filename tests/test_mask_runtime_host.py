@@ -19,7 +19,7 @@ def program(tmp_path_factory):
     if not os.path.exists(hip_build.HIPCC) and shutil.which(hip_build.HIPCC) is None:
         pytest.skip("hipcc not available")
     exe = tmp_path_factory.mktemp("host") / "mask_runtime"
-    r = subprocess.run([hip_build.HIPCC, *hip_build.FLAGS, "--cuda-host-only", SOURCE, "-o", str(exe)],
+    r = subprocess.run([hip_build.HIPCC, *hip_build.FLAGS, "--cuda-host-only", SOURCE, "-pthread", "-o", str(exe)],
                        stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     assert r.returncode == 0, r.stdout[-3000:]
 
@@ -44,3 +44,21 @@ def test_builds_that_end_early_give_their_host_memory_back(program):
     for way, copies in program("ended"):
         counted = way.split("-")[0] in ("radial", "banded") and "-500-" not in way
         assert int(copies) == int(counted), way
+
+
+def test_builds_without_mapped_memory_copy(program):
+    lines = program("unmapped")
+    assert len(lines) == 14
+    for way, status, copies, right in lines:
+        counted = way.split("-")[0] in ("radial", "banded") and "-500-" not in way
+        assert (int(status), int(copies), int(right)) == (0, 1 + counted, 1), way
+
+
+def test_builds_at_a_time_have_a_slot_each_or_copy(program):
+    """32 slots for 40 threads: 8 copy, each finds its own total, and the slots are free again afterwards."""
+    lines = program("together")
+    assert lines == [["40", "8", "0"], ["1", "0", "0"]] * 20
+
+
+def test_a_slot_that_may_still_be_written_is_not_used_again(program):
+    assert program("unwaited") == [["0", "3"]]
