@@ -360,27 +360,6 @@ __host__ __device__ __forceinline__ StagePos advance(StagePos at, int32_t offset
   return at;
 }
 
-// What one lane's token (its own frame/position, a query or a key) sees of a stage: tokens
-// [lo0, lo0 + n0) of the stage's first frame and [lo1, lo1 + n1) of its second, as offsets
-// 0..63 into the stage.
-struct StageRule {
-  int32_t lo0, lo1;
-  uint32_t n0, n1;
-
-  // token `x` (0..63) of the stage
-  __host__ __device__ __forceinline__ bool visible(int x) const {
-    return ((uint32_t)(x - lo0) < n0) | ((uint32_t)(x - lo1) < n1);  // n1 = 0 without a second frame
-  }
-  // bit x set iff token x of the stage is visible
-  __host__ __device__ __forceinline__ uint64_t visible_mask() const { return stage_interval(lo0, n0) | stage_interval(lo1, n1); }
-  // bits [lo, lo + n) of a 64-token stage (n = 0: none; lo + n <= 64 otherwise)
-  __host__ __device__ static __forceinline__ uint64_t stage_interval(int32_t lo, uint32_t n) {
-    if (n == 0u) return 0ull;
-    const uint64_t ones = n >= 64u ? ~0ull : ((1ull << n) - 1ull);
-    return ones << lo;
-  }
-};
-
 // The first `count` tokens of a stage (count >= 64: all of them): those that exist before N.
 __device__ __forceinline__ uint64_t stage_prefix(int32_t count) {
   return count >= 64 ? ~0ull : (count <= 0 ? 0ull : ((1ull << count) - 1ull));
@@ -407,8 +386,9 @@ __host__ __device__ __forceinline__ uint32_t elements_from(int32_t x) {
 }
 
 // The elements of a stage that starts at position pos of a frame which a token at position own of its frame does not see, in lane group g: hw0 and hw1
-// are the half widths of the pairs (own frame, stage's first frame) and (own frame, the next).  The bounds of stage_intervals straight
-// as elements: by way of its intervals the forward of 30 heads x 24 x 316 tokens takes 533 us instead of 526, 1 x 108 x 1010 backward 4333 instead of 4209.
+// are the half widths of the pairs (own frame, stage's first frame) and (own frame, the next).  Of the first frame it sees the positions pos + x, x
+// in [0, min(split, kWidth)), within hw0 of its own, of the second x - split, x in [split, kWidth), within hw1.  The bounds straight as elements: by
+// way of the two intervals the forward of 30 heads x 24 x 316 tokens takes 533 us instead of 526, 1 x 108 x 1010 backward 4333 instead of 4209.
 // kWidth: tokens in the stage (64, or 32 for the kernels that walk half-size stages).
 template <int kWidth>
 __host__ __device__ __forceinline__ uint32_t hidden_elements(int32_t own, int32_t pos, int32_t hw0, int32_t hw1, int32_t s, int g) {
@@ -421,22 +401,6 @@ __host__ __device__ __forceinline__ uint32_t hidden_elements(int32_t own, int32_
 // own_is_query: the lane holds a query and the stage holds keys; otherwise the reverse.
 __host__ __device__ __forceinline__ int32_t pair_half_width(const TokenRule& rule, int32_t own, int32_t other, bool own_is_query) {
   return own_is_query ? radial_half_width(rule, own, other) : radial_half_width(rule, other, own);
-}
-// The StageRule of a lane's own token: the rule as intervals, which the element masks are held against on the host.
-template <int kWidth>
-__host__ __device__ __forceinline__ StageRule stage_intervals(const TokenRule& rule, StagePos own, StagePos stage, bool own_is_query) {
-  const int32_t hw0 = pair_half_width(rule, own.frame, stage.frame, own_is_query), hw1 = pair_half_width(rule, own.frame, stage.frame + 1, own_is_query);
-  const int32_t split = rule.s - stage.pos;  // stage offset at which the second frame starts
-  StageRule r;
-  // first frame: positions stage.pos + x, x in [0, min(split, kWidth)), within hw0 of own.pos
-  const int32_t a0 = max(own.pos - hw0 - stage.pos, 0), b0 = min(own.pos + hw0 - stage.pos, min(split, kWidth) - 1);
-  r.lo0 = a0;
-  r.n0 = b0 >= a0 ? (uint32_t)(b0 - a0 + 1) : 0u;
-  // second frame: positions x - split, x in [split, kWidth), within hw1 of own.pos
-  const int32_t a1 = max(own.pos - hw1 + split, split), b1 = min(own.pos + hw1 + split, kWidth - 1);
-  r.lo1 = a1;
-  r.n1 = b1 >= a1 ? (uint32_t)(b1 - a1 + 1) : 0u;
-  return r;
 }
 
 // What a wave's 32 consecutive tokens cover: positions lo .. hi of a frame and, with s >= 64, at most 0 .. hi2 of the next (hi2 < 0: none).

@@ -1,6 +1,6 @@
 // What the kernels make of the token rule for a wave of 32 tokens that walks a list (span_rule, hidden_elements in radial_tile.h), on
-// the host: for each input line, as in stage_rule.hip,
-//   frames tokens_per_frame extra sink width_num width_den block stage own_is_query
+// the host: for each input line
+//   frames tokens_per_frame extra sink width_num width_den block stage own_is_query table..., a count and as many half widths (0: the radial rule)
 // the N x N visibility that the element masks give, one byte a pair, to stdout (row = the wave's token, column = the stage's).  Exit
 // status 2: a stage is said to be seen wholly, or not at all, and its masks say otherwise.
 #include <stdio.h>
@@ -44,8 +44,11 @@ static int run(const TokenRule& rule, int32_t n, bool own_is_query) {
 }
 
 int main() {
-  int frames, s, extra, sink, num, den, block, stage, own_is_query;
-  while (scanf("%d %d %d %d %d %d %d %d %d", &frames, &s, &extra, &sink, &num, &den, &block, &stage, &own_is_query) == 9) {
+  int frames, s, extra, sink, num, den, block, stage, own_is_query, count;
+  while (scanf("%d %d %d %d %d %d %d %d %d %d", &frames, &s, &extra, &sink, &num, &den, &block, &stage, &own_is_query, &count) == 10) {
+    std::vector<int32_t> table(count);
+    for (int32_t& width : table)
+      if (scanf("%d", &width) != 1) return 1;
     radial_mask m;
     m.flags = RADIAL_MASK_TOKEN_EXACT;
     m.frames = frames;
@@ -53,6 +56,7 @@ int main() {
     m.sink_frames = sink;
     m.width_num = num;
     m.width_den = den;
+    m.d_half_width = count ? table.data() : nullptr;  // (host memory: so are these functions here)
     const TokenRule rule = make_token_rule(&m);
     const int32_t n = frames * s + extra;
     const int rc = block == 128 ? (stage == 64 ? run<128, 64>(rule, n, own_is_query) : run<128, 32>(rule, n, own_is_query))

@@ -14,17 +14,21 @@ using namespace radial;
 template <int kBlock, int kStage>
 static bool run(const TokenRule& rule, int32_t n, bool own_is_query) {
   std::vector<unsigned char> vis((size_t)n * n, 0);
-  for (int32_t own = 0; own < n; ++own)
+  for (int32_t token = 0; token < n; ++token) {
+    const StagePos own = block_pos(token, rule.s);
     for (int32_t block = 0; block < n; block += kBlock)
       for (int32_t offset = 0; offset < kBlock; offset += kStage) {
         const StagePos at = advance<kBlock - kStage>(block_pos(block, rule.s), offset, rule.s);
-        const StageRule r = stage_intervals<kStage>(rule, block_pos(own, rule.s), at, own_is_query);
-        const uint64_t mask = r.visible_mask();
-        for (int x = 0; x < kStage && block + offset + x < n; ++x) {
-          if (r.visible(x) != (((mask >> x) & 1u) != 0)) return false;
-          vis[(size_t)own * n + block + offset + x] = r.visible(x);
+        const int32_t hw0 = pair_half_width(rule, own.frame, at.frame, own_is_query), hw1 = pair_half_width(rule, own.frame, at.frame + 1, own_is_query);
+        for (int g = 0; g < 2; ++g) {
+          const uint32_t hidden = hidden_elements<kStage>(own.pos, at.pos, hw0, hw1, rule.s, g);
+          for (int e = 0; e < kStage / 2; ++e) {
+            const int32_t other = block + offset + 32 * (e >> 4) + 8 * ((e & 15) >> 2) + 4 * g + (e & 3);
+            if (other < n) vis[(size_t)token * n + other] = !(hidden >> e & 1u);
+          }
         }
       }
+  }
   return fwrite(vis.data(), 1, vis.size(), stdout) == vis.size();
 }
 
