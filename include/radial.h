@@ -18,7 +18,8 @@
  *     calls are asynchronous on that stream; mask construction returns after the lists are
  *     complete on the device.
  *   - Between calls the library keeps only what a radial_mask owns, a per-device note that a
- *     kernel attribute has been set, and the device array of radial_attn_bwd_static.
+ *     kernel attribute has been set, the device array of radial_attn_bwd_static, and 4 KiB of mapped
+ *     host memory that mask construction shares out among the builds under way.
  */
 #ifndef RADIAL_H_
 #define RADIAL_H_

@@ -103,7 +103,7 @@ __device__ __forceinline__ void mfma_results_settle(f32x16& acc0, f32x16& acc1) 
 // kTwoWaves: two waves per SIMD and the compiler's schedule instead of one wave and the hand-made one.  At head dimension
 // 64 a stage has 32 MFMAs (1024 cycles) to 178 plain vector instructions and 32 exponentials (1220 cycles), so the vector
 // unit is what bounds it and one wave cannot keep it busy: 2478 items of block 128 (10 x 17 000 tokens) 4.75 -> 4.1 ms, the
-// step 9.34 -> 8.21 ms.  196 to 214 registers; held to 168 for a third wave it spills 23 (block 128) to 45: 1-2 % slower, in
+// step 9.34 -> 8.21 ms.  192 to 216 registers (222 to 235 in groups of one wave beside dQ); held to 168 for a third wave it spills 23 (block 128) to 45: 1-2 % slower, in
 // blocks of 64 25 %.  Head dimension 128 needs 376 to 384 registers and has one wave.
 template <int D, int BLK, bool kExact, int S, int R, bool kTwoWaves>
 __device__ __forceinline__ void dkdv_body(const BwdArgs& a, uint32_t id) {
@@ -619,7 +619,7 @@ __device__ __forceinline__ void pairs_body(const BwdArgs& a, uint32_t id) {
   bool spread = false;
   uint64_t copy_lanes = 0;
   const __bf16 *qbase = qp, *gbase = gp;
-  bool partial = false, skip = false;  // token rule: some row, or all rows, of the stage see some key, or no key, of this pair
+  bool partial = false, skip = false;  // token rule: some row of the stage does not see some key of this pair; no row sees any
   auto open_stage = [&](int32_t u) __attribute__((always_inline)) {
     const bool has_next = u + 1 < n_stage;
     if (kExact) {

@@ -447,8 +447,9 @@ __host__ __device__ __forceinline__ SpanRule span_rule(const TokenRule& rule, co
 // at every stage a lane needs two half widths, 64-bit masks and a change of order, 180 instructions, 100 of them in every stage, beside the 170 of
 // the forward's softmax; at 21 x 1560 tokens 72 % of a wave's stages are seen wholly, 15 % in part, and 30 % of a workgroup's in part by some wave.
 // Each lane for itself in every stage / so, us: forward, D 128, block 128, 5 heads x 21 x 1560 tokens 1830 / 1661, 3 x 33 x 3600 10107 / 9297, block 64, 4 x 21 x
-// 1183 946 / 826, D 64, block 64, 30 x 24 x 316 601 / 525; backward 5727 / 5509, 8 x 30 x 900 6113 / 5586, D 64 1 x 108 x 1010 4725 / 4209, block 64,
-// 4 x 16 x 400 169 / 163.
+// 1183 946 / 826, D 64, block 64, 30 x 24 x 316 601 / 525; backward (a common launch's with arguments shared by its parts) 5727 / 5509, 8 x 30 x 900 6113 / 5586, D 64 1 x 108 x 1010 4725 / 4209, block 64,
+// 4 x 16 x 400 169 / 163.  The price is scalars (masks, span, the half widths' arithmetic): the forward's kernels hold 3 to 33 in vector lanes, those with
+// halves 69 to 90, where they held 0 to 20 and 26 to 35.
 template <int kWidth, int kBlock>
 struct ListRule {
   static constexpr int kSubs = kBlock / kWidth;
