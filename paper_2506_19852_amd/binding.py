@@ -107,7 +107,8 @@ _current_stream = None
 
 
 def _load_torch():
-    """torch, imported by the first call that takes tensors (an import statement in every function of a call costs it 1 us of 8)."""
+    """torch, imported by the first call that takes tensors (a forward took the host 7.97 us instead of 7.60 with an import statement in
+    every function, a wrapper object around every pointer and a tuple for every shape)."""
     global _torch
     if _torch is None:
         import torch

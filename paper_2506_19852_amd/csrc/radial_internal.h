@@ -219,7 +219,7 @@ inline bool two_groups_pay_64(int D, const WorkMap& w, int64_t items) {
 // stage buffers with nobody needs no barrier: in the forms below it waited there for 29 % of its loop (64 items of D 64, block 64).
 // Best of the forms below / single waves, us: block 64, D 64, 64 items L 28 15.3 / 11.1; 99 items L 99 36.6 / 23.0; D 128, 22 items
 // L 11 15.2 / 11.0; 128 items L 3 8.9 / 7.4, L 1 7.5 / 7.7; block 128, D 128, 64 items L 1 7.8 / 8.3, L 2 10.0 / 8.6, L 8 16.6 /
-// 13.5; D 64 L 8 10.2 / 8.2.  (A forward call takes the host 7.4 us.)
+// 13.5; D 64 L 8 10.2 / 8.2.  (A forward call takes the host 7.7 us.)
 inline bool single_waves(int block, const WorkMap& w, int64_t items) { return items * (block / 32) <= kOneRound && w.longest >= 2; }
 
 // Block 128, up to 256 items.  Forward, D 128: half blocks at 64 items L 2 10.5 / 11.0, L 3 12.6 / 12.2, L 16 41.3 / 25.8, at
