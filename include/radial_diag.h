@@ -12,8 +12,8 @@ extern "C" {
 
 /* radial_attn_fwd_trace is radial_attn_fwd plus one record per workgroup of the launch (in no
  * particular order; where a launch gives a query block to several workgroups, all blocks of a small one
- * or the last ones of a larger one, one record per block, of the workgroup with its first rows), for
- * load-balance figures: trace (device memory, trace_records x 3 uint64, zero-filled by the caller;
+ * or the last ones of a larger one, one record per block, of the workgroup with its first rows; where a
+ * workgroup takes two blocks, one record for both), for load-balance figures: trace (device memory, trace_records x 3 uint64, zero-filled by the caller;
  * trace_records >= radial_attn_fwd_trace_records(B, H, mask), else RADIAL_ESHAPE) receives, for
  * every workgroup that had work, {begin, end, where}: begin and end in ticks of the device's
  * constant 100 MHz clock, where = (XCC_ID register << 32) | HW_ID register of the wave that wrote

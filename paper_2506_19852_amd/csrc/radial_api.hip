@@ -52,6 +52,7 @@ int radial::make_fwd_args(int32_t B, int32_t H, int32_t N, int32_t D, radial_ten
   a->scale = scale;
   a->rule = make_token_rule(mask);
   a->wg_trace = nullptr;
+  a->pair_order = mask->d_pair_order;
   return RADIAL_OK;
 }
 

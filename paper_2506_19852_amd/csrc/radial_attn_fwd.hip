@@ -1,5 +1,6 @@
 // Forward entry of the library: the kernel template of radial_attn_fwd_kernel.h without trace records.
 #include "radial_attn_fwd_kernel.h"
+#include "radial_attn_fwd_two.h"
 
 namespace radial {
 

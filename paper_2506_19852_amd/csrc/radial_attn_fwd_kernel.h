@@ -80,21 +80,32 @@ __device__ __forceinline__ char* static_lds() {
   __shared__ __attribute__((aligned(1024))) char lds[kBytes];
   return lds;
 }
-template <int D, int BLK, bool kExact, bool kTrace, bool kHalves>
+template <int D, int BLK, bool kExact, bool kTrace, int kShared>
 struct FwdKey {};
+
+// One record per (head, query block), by the first thread of its first workgroup: begin, end, where it ran.
+__device__ __forceinline__ void write_trace(const FwdArgs& a, uint64_t begin, int64_t record) {
+  // hardware id registers: which XCD, shader engine and compute unit this workgroup ran on
+  constexpr int kHwId = 4, kXccId = 20, kAllBits = 31 << 11;
+  const uint64_t where = ((uint64_t)__builtin_amdgcn_s_getreg(kXccId | kAllBits) << 32) | (uint32_t)__builtin_amdgcn_s_getreg(kHwId | kAllBits);
+  uint64_t* rec = a.wg_trace + 3 * record;
+  rec[0] = begin;
+  rec[1] = __builtin_amdgcn_s_memrealtime();
+  rec[2] = where;
+}
 
 // One block of query rows, or part `part` of the R of one.
 // kExact: apply the token-level rule of the radial mask inside the listed blocks.
 // kTrace: also record begin, end and hardware ids of the workgroup (diagnostics build of the kernel;
 // the library's radial_attn_fwd launches kTrace = false, which carries none of it).
-// kHalves: in the kernel that takes its last blocks in halves.
-template <int D, int BLK, bool kExact, bool kTrace, int S, int R, bool kHalves>
+// kShared: bytes of the static stage buffers of a kernel that has several forms, 0: this is its only one.
+template <int D, int BLK, bool kExact, bool kTrace, int S, int R, int kShared>
 __device__ __forceinline__ void fwd_body(const FwdArgs& a, int32_t bh, int32_t qb, int32_t part, int64_t record) {
   using T = Tile<D, BLK, S, R>;
-  using Key = FwdKey<D, BLK, kExact, kTrace, kHalves>;
-  constexpr bool kStatic = S == 1 || kHalves;
-  constexpr int kStaticBytes = Tile<D, BLK, 1, 1>::kLdsBytes;
-  static_assert(!kHalves || T::kLdsBytes <= kStaticBytes, "halves use the stage buffers of whole blocks");
+  using Key = FwdKey<D, BLK, kExact, kTrace, kShared>;
+  constexpr bool kStatic = S == 1 || kShared;
+  constexpr int kStaticBytes = kShared ? kShared : T::kLdsBytes;
+  static_assert(T::kLdsBytes <= kStaticBytes, "every form uses the stage buffers of the largest");
   // [group][stage buffer][K, V][T::kStageKeys x D bf16]
   extern __shared__ __attribute__((aligned(1024))) char lds_all[];
 
@@ -391,15 +402,7 @@ __device__ __forceinline__ void fwd_body(const FwdArgs& a, int32_t bh, int32_t q
       if (a.lse && g == 0) store_lse(m_run, l_tot);
     }
   }
-  if (kTrace && a.wg_trace != nullptr && threadIdx.x == 0 && part == 0) {  // one record per (head, query block)
-    // hardware id registers: which XCD, shader engine and compute unit this workgroup ran on
-    constexpr int kHwId = 4, kXccId = 20, kAllBits = 31 << 11;
-    const uint64_t where = ((uint64_t)__builtin_amdgcn_s_getreg(kXccId | kAllBits) << 32) | (uint32_t)__builtin_amdgcn_s_getreg(kHwId | kAllBits);
-    uint64_t* rec = a.wg_trace + 3 * record;
-    rec[0] = t_begin;
-    rec[1] = __builtin_amdgcn_s_memrealtime();
-    rec[2] = where;
-  }
+  if (kTrace && a.wg_trace != nullptr && threadIdx.x == 0 && part == 0) write_trace(a, t_begin, record);
 }
 
 template <int D, int BLK, bool kExact, bool kTrace, int S, int R>
@@ -410,7 +413,7 @@ __global__ void __launch_bounds__(2 * BLK / R * S, 2) radial_fwd_kernel(const Fw
   if (!work_item(a.work, blockIdx.x, bh, qb)) return;
   const int32_t part = R == 1 ? 0 : bh % R;  // with R > 1 the work map counts R heads for each
   if (R > 1) bh /= R;
-  fwd_body<D, BLK, kExact, kTrace, S, R, false>(a, bh, qb, part, R == 1 ? (int64_t)blockIdx.x : (int64_t)bh * a.n_blocks + qb);
+  fwd_body<D, BLK, kExact, kTrace, S, R, 0>(a, bh, qb, part, R == 1 ? (int64_t)blockIdx.x : (int64_t)bh * a.n_blocks + qb);
 }
 
 // Whole blocks, and the last a.work.halved of the launch in halves of two groups.
@@ -418,13 +421,14 @@ template <int D, int BLK, bool kExact, bool kTrace>
 __global__ void __launch_bounds__(2 * BLK, 2) radial_fwd_halves_kernel(const FwdArgs a) {
   int32_t bh, qb, part = 0;
   const uint32_t whole = gridDim.x - 2u * (uint32_t)a.work.halved;
+  constexpr int kBytes = Tile<D, BLK, 1, 1>::kLdsBytes;
   if (blockIdx.x < whole) {
     if (!work_item(a.work, blockIdx.x, bh, qb)) return;
-    fwd_body<D, BLK, kExact, kTrace, 1, 1, true>(a, bh, qb, 0, (int64_t)blockIdx.x);
+    fwd_body<D, BLK, kExact, kTrace, 1, 1, kBytes>(a, bh, qb, 0, (int64_t)blockIdx.x);
   } else {
     const uint32_t id = halved_item(blockIdx.x, whole, (uint32_t)a.work.halved, part);
     if (!work_item(a.work, id, bh, qb)) return;
-    fwd_body<D, BLK, kExact, kTrace, 2, 2, true>(a, bh, qb, part, (int64_t)id);
+    fwd_body<D, BLK, kExact, kTrace, 2, 2, kBytes>(a, bh, qb, part, (int64_t)id);
   }
 }
 
@@ -449,6 +453,9 @@ int launch_halves(const FwdArgs& a, hipStream_t stream) {
   return RADIAL_OK;
 }
 
+template <bool kTrace>
+int launch_two(const FwdArgs& a, hipStream_t stream);  // radial_attn_fwd_two.h
+
 template <int D, int BLK, bool kExact, bool kTrace>
 int launch(const FwdArgs& a, hipStream_t stream) {
   if (work_grid_bound(a.work) > 0x7fffffffLL) return fail(RADIAL_ESHAPE, "B*H*n_blocks is too large for one launch");
@@ -458,6 +465,8 @@ int launch(const FwdArgs& a, hipStream_t stream) {
   if (single_waves(BLK, a.work, items)) return launch_split<D, BLK, kExact, kTrace, D == 64 ? 8 : 4, BLK / 32>(a, stream);
   if (groups == 4) return launch_split<D, BLK, kExact, kTrace, 4, BLK / 64>(a, stream);
   if (groups == 2) return launch_split<D, BLK, kExact, kTrace, 2, 1>(a, stream);
+  if constexpr (D == 128 && BLK == 128 && !kExact)
+    if (takes_pairs(a.work)) return launch_two<kTrace>(a, stream);
   if constexpr (BLK == 128)
     if (const int32_t halved = halved_items(a.work, items)) {
       FwdArgs h = a;

@@ -1,0 +1,403 @@
+// The forward of radial_attn_fwd_kernel.h for two neighbouring query blocks at a time: head dimension 128, blocks of 128, listed blocks
+// dense, launches that fill the chip several times over.
+//
+// One workgroup of four waves takes the query blocks 2p and 2p + 1, and wave w of it owns 32 rows of either, so that a key block which both
+// lists name is copied into LDS once for 256 query rows and every K and V fragment read from LDS feeds two MFMAs.  These kernels run at the
+// chip's power cap, and both are energy that is no arithmetic: with the copies and the LDS reads halved the clock rises from 1.60 to
+// 1.73 GHz at the same 62 % of matrix-pipe cycles (24 heads x 118 800 tokens, radial lists).  Two workgroups share a compute unit, the two waves of
+// a SIMD belong to different ones and so drift into each other's gaps: as one workgroup of eight waves of 32 rows, tied by its barrier, the same
+// sharing gained nothing, and so did 64 rows of one block per wave in workgroups of two waves (half the LDS reads, the same copies: 0.99).
+//
+// The union of two neighbouring lists is 5 to 20 % longer than either.  The softmax does not mind the order, so a pair is walked in three
+// passes, the entries of both lists, then those of the first alone and those of the second alone: three loops of their own, of which the
+// last two are one piece of code (the second set of rows moves into the registers of the first).  With one loop that branches at every
+// entry the compiler moves accumulators between the branches and spills 800 bytes a lane.  A pass over one list alone works like the
+// kernel for single blocks, so lists that have nothing in common are no slower (random lists of 10 to 90 % of the blocks: 0.97-1.00).
+//
+// Registers are what limits it: 128 of O, 64 of Q, 32 of scores, 12 of fragments in flight, and 14 for all the rest.  So
+// - K and V lie in LDS four rows at a time, rows in turn every 64 bytes, with 16 bytes between one four and the next: both kinds of reads are free of
+//   bank conflicts, as with the swizzle, but all pieces of a tile are at constant distances from one address per lane;
+// - values of rare use (the lane's number, addresses of a ragged stage, the store) are worked out again where they are needed;
+// - sums and packed P are pinned where they are written, or the compiler keeps the 32 values of P until it needs their sum.
+// Forward, us, single blocks / this: 24 heads x 118 800 tokens 77.0 / 68.7 ms, x 464 400 618 / 551, 40 x 32 760 13.38 / 12.35, all-ones list 19.9 /
+// 18.0, 12 x 64 500 16.0 / 15.0, 400 x 1536 613 / 535, 600 x 1152 643 / 480.
+#pragma once
+
+#include "radial_attn_fwd_kernel.h"
+
+namespace radial {
+namespace fwd {
+
+struct TwoTile {
+  static constexpr int kD = 128, kBlk = 128, kStageKeys = 64, kWaves = 4;
+  static constexpr int kFourRows = 1024 + 16;  // bytes of four rows and the gap behind them
+  static constexpr int kTileBytes = kStageKeys / 4 * kFourRows, kStageBytes = 2 * kTileBytes;  // K or V of a stage, both
+  static constexpr int kLoads = kStageKeys / 4 / kWaves;  // copies of four rows per wave and tile
+  static constexpr int kSteps = kD / 16, kDTiles = kD / 32;
+  static constexpr int kNamedAt = 2 * kStageBytes, kNamedWords = kMaxOrdered / 32;  // which blocks either list names, a bit each
+  static constexpr int kLdsBytes = kNamedAt + 2 * kNamedWords * 4;
+  static_assert(2 * kLdsBytes <= 160 * 1024, "two workgroups per compute unit");
+  static_assert(2 * kLoads == kSteps, "a copy after every other MFMA of the first product");
+};
+
+// The lane's number again, so that nothing derived from it is held in a register meanwhile.
+__device__ __forceinline__ int lane_again() {
+  int lane;
+  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(lane));
+  return lane;
+}
+
+// Query blocks qb and qb + 1 (which may not exist).
+template <bool kTrace>
+__device__ __forceinline__ void two_body(const FwdArgs& a, int32_t bh, int32_t qb, int64_t record, char* lds_all) {
+  using T = TwoTile;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lq = lane & 31, g = lane >> 5;
+  const uint64_t t_begin = kTrace ? __builtin_amdgcn_s_memrealtime() : 0;
+  int32_t heads = a.H;
+  asm("" : "+s"(heads) : "s"(a.q.ptr), "s"(a.k.ptr), "s"(a.row_ptr));
+  const int32_t b = bh / heads, h = bh % heads;
+  const __bf16* qp = (const __bf16*)a.q.ptr + (int64_t)b * a.q.sb + (int64_t)h * a.q.sh;
+  const __bf16* kp = (const __bf16*)a.k.ptr + (int64_t)b * a.k.sb + (int64_t)h * a.k.sh;
+  const __bf16* vp = (const __bf16*)a.v.ptr + (int64_t)b * a.v.sb + (int64_t)h * a.v.sh;
+
+  const int32_t lo0 = __builtin_amdgcn_readfirstlane(a.row_ptr[qb]), lo1 = __builtin_amdgcn_readfirstlane(a.row_ptr[qb + 1]);
+  const int32_t hi1 = qb + 2 <= a.n_blocks ? __builtin_amdgcn_readfirstlane(a.row_ptr[qb + 2]) : lo1;
+  const auto named = lds_cast<uint32_t>(lds_all + T::kNamedAt);  // by the first list, by the second
+  {
+    const int32_t words = (a.n_blocks + 31) >> 5;
+    for (int32_t i = threadIdx.x; i < words; i += 256) named[i] = named[T::kNamedWords + i] = 0u;
+    __syncthreads();
+    for (int32_t i = threadIdx.x; i < hi1 - lo0; i += 256) {
+      const int32_t e = a.col_idx[lo0 + i];
+      __hip_atomic_fetch_or(&named[(i < lo1 - lo0 ? 0 : T::kNamedWords) + (e >> 5)], 1u << (e & 31), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+    __syncthreads();
+  }
+  // A walk over the entries of list `w` that the other list names too (shared) or does not.
+  int32_t entry = 0;       // this lane's of 64
+  uint64_t left = 0;       // which of them are to be visited
+  int32_t chunk = 0, w = 0;
+  bool shared = true;
+  auto take = [&]() __attribute__((always_inline)) -> int32_t {  // the next block, -1: none
+    const int32_t list = w ? lo1 : lo0, size = w ? hi1 - lo1 : lo1 - lo0;
+    while (left == 0) {
+      if (chunk >= size) return -1;
+      const int i = chunk + lane_again();
+      entry = i < size ? a.col_idx[list + i] : 0;
+      const bool in = named[(w ^ 1) * T::kNamedWords + (entry >> 5)] >> (entry & 31) & 1u;
+      left = __builtin_amdgcn_ballot_w64(i < size && in == shared);
+      chunk += 64;
+    }
+    const int i = __builtin_ctzll(left);
+    left &= left - 1;
+    return __builtin_amdgcn_readlane(entry, i);
+  };
+
+  const int32_t q_first = qb * T::kBlk + wave * 32 + lq;
+  bf16x8 qf[2][T::kSteps];
+#pragma unroll
+  for (int set = 0; set < 2; ++set) {
+    const int32_t q_row = q_first + T::kBlk * set;
+    const bool q_ok = q_row < a.N;
+    const __bf16* src = qp + (int64_t)(q_ok ? q_row : a.N - 1) * a.q.sn + 8 * g;
+#pragma unroll
+    for (int t = 0; t < T::kSteps; ++t) {
+      u32x4 raw = *(const u32x4*)(src + 16 * t);
+      if (!q_ok) raw = u32x4{0u, 0u, 0u, 0u};
+      qf[set][t] = __builtin_bit_cast(bf16x8, raw);
+    }
+  }
+
+  // A copy takes four rows: lanes 4j .. 4j + 3 of every 16 fetch 64 bytes of row j, so that the rows lie in turn every 64 bytes.
+  const uint32_t koff = (uint32_t)((lane >> 2 & 3) * (int32_t)a.k.sn) * 2u + (lane >> 4) * 64 + (lane & 3) * 16;
+  const uint32_t voff = (uint32_t)((lane >> 2 & 3) * (int32_t)a.v.sn) * 2u + (lane >> 4) * 64 + (lane & 3) * 16;
+  const uint32_t lds0 = lds_address(lds_all);
+  const int i16 = lane & 15, half16 = (lane >> 4) & 1;
+  // K row lq, piece g, and the V rows and columns of a transposing read; the first stage goes to the other buffer.
+  uint32_t rows_at = lds0 + T::kStageBytes + (lq >> 2) * T::kFourRows + (lq & 3) * 64 + g * 16;
+  uint32_t cols_at = lds0 + T::kStageBytes + T::kTileBytes + g * T::kFourRows + (i16 >> 2) * 64 + half16 * 32 + (i16 & 3) * 8;
+  uint32_t copy_at = lds0 + wave * T::kLoads * T::kFourRows;  // where this wave's copies of the next stage go
+
+  // All of this wave's copies of a stage at once (first stage, ragged stages: rows past N-1 are clamped to N-1).
+  auto issue_stage = [&](int32_t key0) __attribute__((always_inline)) {
+    const int32_t last = a.N - 1 - key0;
+    const int lane = lane_again();
+#pragma unroll 1
+    for (int i = 0; i < T::kLoads; ++i) {
+      int32_t r = (wave * T::kLoads + i) * 4 + (lane >> 2 & 3);
+      r = r < last ? r : last;
+      const int col = (lane >> 4) * 32 + (lane & 3) * 8;
+      copy16_to_lds(kp + ((int64_t)key0 + r) * a.k.sn + col, copy_at + i * T::kFourRows);
+      copy16_to_lds(vp + ((int64_t)key0 + r) * a.v.sn + col, copy_at + T::kTileBytes + i * T::kFourRows);
+    }
+  };
+
+  f32x16 o[2][T::kDTiles];
+#pragma unroll
+  for (int set = 0; set < 2; ++set)
+#pragma unroll
+    for (int i = 0; i < T::kDTiles; ++i)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) o[set][i][e] = 0.f;
+  float m_run[2] = {-INFINITY, -INFINITY}, l_run[2] = {0.f, 0.f}, mc[2] = {0.f, 0.f};  // mc: maximum times c, 0 while there is none
+  const float c = a.scale * 1.4426950408889634f;
+  constexpr int kAhead = 2;  // LDS fragments are read this many MFMAs (of one set) before their use; the fences keep the written order
+  const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+
+  const char *kbase = (const char*)kp, *vbase = (const char*)vp;  // this wave's first rows of the next stage
+  uint64_t copy_lanes = 0;
+  const int64_t kstep = 8 * a.k.sn, vstep = 8 * a.v.sn;  // bytes of 4 rows
+  auto spread_copy = [&](int j) __attribute__((always_inline)) {  // of 2 * kLoads
+    const int i = j >> 1;
+    if ((j & 1) == 0) copy16_to_lds_sv_masked(kbase + i * kstep, koff, copy_at + i * T::kFourRows, copy_lanes);
+    else copy16_to_lds_sv_masked(vbase + i * vstep, voff, copy_at + T::kTileBytes + i * T::kFourRows, copy_lanes);
+  };
+  auto read_k = [&](int kt, int t) __attribute__((always_inline)) {
+    return *lds_pointer<const bf16x8>(rows_at + (kt * 8 * T::kFourRows + t / 2 * 256 + t % 2 * 32));
+  };
+  auto read_v = [&](int kt, int j) __attribute__((always_inline)) {  // j = 4 * 16-key step + d tile
+    const uint32_t at = cols_at + (j % 4 * 256 + (kt * 8 + j / 4 * 4) * T::kFourRows);
+    const s16x4 v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16(lds_pointer<s16x4>(at));
+    const s16x4 v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16(lds_pointer<s16x4>(at + 2 * T::kFourRows));
+    const u32x2 a0 = __builtin_bit_cast(u32x2, v0), a1 = __builtin_bit_cast(u32x2, v1);
+    return as_bf16x8(a0[0], a0[1], a1[0], a1[1]);
+  };
+  // New running maximum of set `set`.
+  auto raise = [&](int set, float mx) __attribute__((always_inline)) {
+    mx = max_with_other_half(mx);
+    if (__builtin_amdgcn_ballot_w64(mx > m_run[set]) != 0) {
+      const float alpha = mx > m_run[set] ? __builtin_amdgcn_exp2f((m_run[set] - mx) * c) : 1.f;
+      l_run[set] *= alpha;
+#pragma unroll
+      for (int i = 0; i < T::kDTiles; ++i)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) o[set][i][e] *= alpha;
+      m_run[set] = mx;
+      mc[set] = mx * c;
+    }
+  };
+  // Scores of keys past N - 1.
+  auto hide = [&](f32x16 (&s)[2], int32_t left0, int32_t left1) __attribute__((always_inline)) {  // keys that exist of either's 32
+    const int g = lane_again() >> 5;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const uint32_t hidden = elements_from((i ? left1 : left0) - 4 * g);
+#pragma unroll
+      for (int e = 0; e < 16; ++e)
+        if ((hidden >> e) & 1u) s[i][e] = -INFINITY;
+    }
+  };
+
+  // Half kt of a stage, 32 keys, for both sets of rows.  The first 16 keys' P are ready before the second product begins, the others follow between
+  // its MFMAs (all of them before it: 1 % slower).
+  bf16x8 ahead[kAhead];  // the first of the second half
+  auto both = [&](int32_t key0, int kt) __attribute__((always_inline)) {
+    f32x16 s[2];
+    bf16x8 kf[T::kSteps], vf[8];
+#pragma unroll
+    for (int t = 0; t < kAhead; ++t) kf[t] = kt == 0 ? read_k(0, t) : ahead[t];
+    __builtin_amdgcn_s_setprio(1);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int t = 0; t < T::kSteps; ++t) {
+      if (t + kAhead < T::kSteps) kf[t + kAhead] = read_k(kt, t + kAhead);
+      s[0] = mfma32(kf[t], qf[0][t], t == 0 ? zero : s[0]);
+      if (kt == 0) spread_copy(t);
+      s[1] = mfma32(kf[t], qf[1][t], t == 0 ? zero : s[1]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    __builtin_amdgcn_s_setprio(0);
+    if (key0 + 32 * kt + 32 > a.N) hide(s, a.N - key0 - 32 * kt, a.N - key0 - 32 * kt);
+    uint32_t pk[2][8];
+#pragma unroll
+    for (int set = 0; set < 2; ++set) {
+      float mx = m_run[set];
+#pragma unroll
+      for (int e = 0; e < 16; ++e) mx = fmaxf(mx, s[set][e]);
+      raise(set, mx);
+    }
+    float psum[2] = {0.f, 0.f};
+    auto softmax_pair = [&](int set, int pair) __attribute__((always_inline)) {
+      const int e = 2 * pair;
+      const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[set][e], c, -mc[set]));
+      const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[set][e + 1], c, -mc[set]));
+      psum[set] += p0 + p1;
+      pk[set][pair] = pack_bf16(p0, p1);
+      asm volatile("" : "+v"(pk[set][pair]), "+v"(psum[set]));
+    };
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int pair = 0; pair < 4; ++pair) {
+      softmax_pair(0, pair);
+      softmax_pair(1, pair);
+      if (pair >= 2) vf[pair - 2] = read_v(kt, pair - 2);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      if (j + kAhead < 8) vf[j + kAhead] = read_v(kt, j + kAhead);
+      else if (kt == 0) ahead[j + kAhead - 8] = read_k(1, j + kAhead - 8);
+      const int t = j / 4, dt = j % 4;
+#pragma unroll
+      for (int set = 0; set < 2; ++set) {
+        o[set][dt] = mfma32(vf[j], as_bf16x8(pk[set][4 * t], pk[set][4 * t + 1], pk[set][4 * t + 2], pk[set][4 * t + 3]), o[set][dt]);
+        if (j < 4) softmax_pair(set, 4 + j);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    l_run[0] += psum[0];
+    l_run[1] += psum[1];
+    asm volatile("" : "+v"(l_run[0]), "+v"(l_run[1]));
+  };
+
+  // A stage of 64 keys for set `set`.
+  auto one = [&](int32_t key0, auto set_c) __attribute__((always_inline)) {
+    constexpr int set = decltype(set_c)::value;
+    f32x16 s[2];
+    bf16x8 kf[2 * T::kSteps], vf[16];
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) kf[i] = read_k(i % 2, i / 2);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < 2 * T::kSteps; ++i) {
+      if (i + kAhead < 2 * T::kSteps) kf[i + kAhead] = read_k((i + kAhead) % 2, (i + kAhead) / 2);
+      const int kt = i % 2, t = i / 2;
+      s[kt] = mfma32(kf[i], qf[set][t], t == 0 ? zero : s[kt]);
+      if (kt == 0) spread_copy(t);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if (key0 + T::kStageKeys > a.N) hide(s, a.N - key0, a.N - key0 - 32);
+    uint32_t pk[2][8];
+    float mx = m_run[set];
+#pragma unroll
+    for (int e = 0; e < 16; ++e) mx = fmaxf(mx, s[0][e]);
+#pragma unroll
+    for (int e = 0; e < 16; ++e) mx = fmaxf(mx, s[1][e]);
+    raise(set, mx);
+    float psum = 0.f;
+    auto softmax_pair = [&](int pair) __attribute__((always_inline)) {
+      const int kt = pair / 8, e = 2 * (pair % 8);
+      const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[kt][e], c, -mc[set]));
+      const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[kt][e + 1], c, -mc[set]));
+      psum += p0 + p1;
+      pk[kt][pair % 8] = pack_bf16(p0, p1);
+      asm volatile("" : "+v"(pk[kt][pair % 8]), "+v"(psum));
+    };
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int pair = 0; pair < 4; ++pair) {
+      softmax_pair(pair);
+      if (pair >= 2) vf[pair - 2] = read_v(0, pair - 2);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+      if (j + kAhead < 16) vf[j + kAhead] = read_v((j + kAhead) / 8, (j + kAhead) % 8);
+      const int kt = j / 8, t = j / 4 % 2, dt = j % 4;
+      o[set][dt] = mfma32(vf[j], as_bf16x8(pk[kt][4 * t], pk[kt][4 * t + 1], pk[kt][4 * t + 2], pk[kt][4 * t + 3]), o[set][dt]);
+      if (j < 12) softmax_pair(4 + j);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    l_run[set] += psum;
+    asm volatile("" : "+v"(l_run[set]));
+  };
+
+  // A stage opens with one barrier: its copies have landed for every wave, and the buffer that the next one's go to is consumed.
+  int32_t towards = -T::kStageBytes;  // from the buffer that is read to the other one
+  auto swap_buffers = [&]() __attribute__((always_inline)) {
+    rows_at += towards;
+    cols_at += towards;
+    copy_at -= towards;
+    towards = -towards;
+  };
+  auto walk = [&](auto stage) __attribute__((always_inline)) {
+    left = 0;
+    chunk = 0;
+    int32_t block = take();
+    if (block < 0) return;
+    int32_t key0 = block * T::kBlk;
+    issue_stage(key0);
+    for (int32_t u = 0;; u ^= 1) {
+      swap_buffers();
+      int32_t key0_next = key0 + T::kStageKeys;
+      bool has_next = true;
+      if (u) {
+        block = take();
+        has_next = block >= 0;
+        key0_next = block * T::kBlk;
+      }
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      __syncthreads();
+      const bool spread = has_next && key0_next + T::kStageKeys <= a.N;
+      if (has_next && !spread) issue_stage(key0_next);
+      const uint32_t on = __builtin_amdgcn_readfirstlane(spread ? ~0u : 0u);
+      copy_lanes = ((uint64_t)on << 32) | on;
+      const int64_t from = (spread ? key0_next : key0) + wave * 4 * T::kLoads;
+      kbase = (const char*)(kp + from * a.k.sn);
+      vbase = (const char*)(vp + from * a.v.sn);
+      stage(key0);
+      if (!has_next) break;
+      key0 = key0_next;
+    }
+  };
+  walk([&](int32_t key0) __attribute__((always_inline)) {
+    both(key0, 0);
+    both(key0, 1);
+  });
+  shared = false;
+#pragma unroll 1
+  for (int set = 0; set < 2; ++set) {
+    w = set;
+    walk([&](int32_t key0) __attribute__((always_inline)) { one(key0, std::integral_constant<int, 0>{}); });
+    const int lane2 = lane_again(), g2 = lane2 >> 5;
+    __bf16* op = (__bf16*)a.o.ptr + (int64_t)b * a.o.sb + (int64_t)h * a.o.sh;
+    const int32_t q_row = (qb + set) * T::kBlk + wave * 32 + (lane2 & 31);
+    const float l_tot = l_run[0] + __shfl_xor(l_run[0], 32);
+    const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
+    if (q_row < a.N) {
+      __bf16* const dst = op + (int64_t)q_row * a.o.sn;
+#pragma unroll
+      for (int dt = 0; dt < T::kDTiles; ++dt)
+#pragma unroll
+        for (int e4 = 0; e4 < 4; ++e4) {
+          u32x2 x;
+          x[0] = pack_bf16(o[0][dt][4 * e4] * inv, o[0][dt][4 * e4 + 1] * inv);
+          x[1] = pack_bf16(o[0][dt][4 * e4 + 2] * inv, o[0][dt][4 * e4 + 3] * inv);
+          *(u32x2*)(dst + 32 * dt + 8 * e4 + 4 * g2) = x;
+        }
+      if (a.lse && g2 == 0) a.lse[((int64_t)b * a.H + h) * a.N + q_row] = l_tot > 0.f ? m_run[0] * a.scale + __logf(l_tot) : -INFINITY;
+    }
+#pragma unroll
+    for (int dt = 0; dt < T::kDTiles; ++dt) o[0][dt] = o[1][dt];
+#pragma unroll
+    for (int t = 0; t < T::kSteps; ++t) qf[0][t] = qf[1][t];
+    m_run[0] = m_run[1];
+    l_run[0] = l_run[1];
+    mc[0] = mc[1];
+  }
+  if (kTrace && a.wg_trace != nullptr && threadIdx.x == 0) write_trace(a, t_begin, record);
+}
+
+template <bool kTrace>
+__global__ void __launch_bounds__(256, 2) radial_fwd_two_kernel(const FwdArgs a, const TwoMap m) {
+  constexpr int kBytes = TwoTile::kLdsBytes;
+  TwoItem item;
+  if (!two_item(a.work, m, blockIdx.x, item)) return;
+  const int32_t qb = 2 * item.pair + item.block;
+  if (item.form == TwoItem::kPair) two_body<kTrace>(a, item.bh, qb, item.record, static_lds<FwdKey<128, 128, false, kTrace, kBytes>, kBytes>());
+  else if (item.form == TwoItem::kBlock) fwd_body<128, 128, false, kTrace, 1, 1, kBytes>(a, item.bh, qb, 0, item.record);
+  else fwd_body<128, 128, false, kTrace, 2, 2, kBytes>(a, item.bh, qb, item.half, item.record);
+}
+
+template <bool kTrace>
+int launch_two(const FwdArgs& a, hipStream_t stream) {
+  const TwoMap m = make_two_map(a.work, a.pair_order);
+  radial_fwd_two_kernel<kTrace><<<dim3(m.n_two + 2 * m.n_one + 4 * m.n_half), dim3(256), 0, stream>>>(a, m);
+  RADIAL_HIP_TRY(hipGetLastError());
+  return RADIAL_OK;
+}
+
+}  // namespace fwd
+}  // namespace radial

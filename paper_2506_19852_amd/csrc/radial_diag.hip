@@ -1,6 +1,7 @@
 // Measurement aids (declared in include/radial_diag.h; no part of the method): the forward kernel
 // built with per-workgroup trace records, and a kernel that only issues MFMAs.
 #include "radial_attn_fwd_kernel.h"
+#include "radial_attn_fwd_two.h"
 #include "radial_diag.h"
 
 namespace radial {

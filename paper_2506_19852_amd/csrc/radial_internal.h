@@ -18,7 +18,7 @@ struct radial_mask {
   int device = 0;
   // owners of the device storage; the pointers below are views into them
   int32_t* d_meta = nullptr;     // totals and launch partitions
-  int32_t* d_ptrs = nullptr;     // row_ptr, order (+ col_ptr, order), counts
+  int32_t* d_ptrs = nullptr;     // row_ptr, order (+ col_ptr, order), counts, order of pairs
   int32_t* d_idx = nullptr;      // col_idx (+ row_idx)
   int32_t* d_counts = nullptr;   // [n_blocks] scratch of the build; null above kMaxOrdered blocks
   int32_t* d_row_ptr = nullptr;  // [n_blocks + 1]
@@ -33,6 +33,7 @@ struct radial_mask {
   // Blocks by falling list length (null above kMaxOrdered blocks): the work order of short launches.
   int32_t* d_order = nullptr;    // [n_blocks]
   int32_t* d_order_t = nullptr;  // [n_blocks]
+  int32_t* d_pair_order = nullptr;  // [(n_blocks + 1) / 2]  pairs of query blocks 2p, 2p + 1 by falling length of both lists
   int32_t max_slice = 0;         // longest slice, in blocks (host copy, sizes the grid)
   int32_t max_slice_t = 0;
   int32_t longest = 0, longest_t = 0;  // entries of the longest list (n_blocks, a bound, where there is no order)
@@ -182,6 +183,46 @@ inline int64_t work_grid_bound(const WorkMap& w) { return 8LL * (w.sliced + w.or
 inline int64_t work_items(const WorkMap& w, int32_t n_blocks) { return (int64_t)(w.sliced + w.ordered) * n_blocks; }
 inline int64_t work_grid(const WorkMap& w, int32_t n_blocks) {
   return 8LL * w.sliced * w.max_slice + (int64_t)w.ordered * n_blocks;
+}
+
+// ---- Two query blocks per workgroup (forward, head dimension 128, blocks of 128) ------------------
+// Pairs are numbered: those of the sliced heads (n_sliced workgroups), then those of the ordered heads by falling length.  A workgroup each takes
+// the first n_two, two workgroups the next n_one, a block each, and four the last n_half, half a block each.
+struct TwoMap {
+  WorkMap pairs;  // the ordered heads alone, with pairs for blocks
+  uint32_t n_sliced, n_two, n_one, n_half;
+};
+constexpr uint32_t kTwoRound = 512;  // workgroups that the chip holds
+
+// A pair takes 1.75 times as long as a block, so a launch ends as evenly only if its last, shortest lists are taken singly, and the very
+// last in halves: whole rounds of pairs, what is left over singly (with slices before them, at least half a round), 64 pairs of that in halves.
+// Forward, us, single blocks / 512 pairs, 76 blocks / 512, the last 38 in halves / 448, 38 / 256, 38: 10 heads x 14 040 tokens 829 / 794 / 769 / 776 / 820.
+// 3 heads x 119 026 (1395 pairs) 8080 / 1024 pairs 7750, the last 80 in halves 7570, 192 7830, 256 8000; 1136 pairs, 64 in halves 7570, 1280 8060.  With
+// slices 40 heads x 32 760 (1024 ordered pairs), none / 512 / 768 of them as pairs 13010 / 12980 / 12960, 24 x 118 800 70.2 / 69.9 / 69.8 ms.
+inline TwoMap make_two_map(const WorkMap& w, const int32_t* pair_order) {
+  TwoMap m;
+  m.pairs = w;
+  m.pairs.order = pair_order;
+  m.pairs.sliced = 0;
+  m.pairs.n_blocks = (w.n_blocks + 1) / 2;
+  const uint32_t per_head = (uint32_t)m.pairs.n_blocks, most = ((uint32_t)w.max_slice + 1) / 2;  // pairs of a head; of it to an XCD
+  const uint32_t last = (uint32_t)w.sliced % 8u * most;                                       // of the heads that are no full eight to an XCD
+  m.n_sliced = 8u * ((uint32_t)w.sliced / 8u * per_head + (last < per_head ? last : per_head));
+  const uint32_t ordered = (uint32_t)w.ordered * per_head;
+  uint32_t rest = ordered % kTwoRound;
+  if (w.sliced > 0 && rest < kTwoRound / 2 && ordered >= kTwoRound) rest += kTwoRound;
+  m.n_half = rest < 64u ? rest : 64u;
+  m.n_one = rest - m.n_half;
+  m.n_two = m.n_sliced + ordered - rest;
+  return m;
+}
+// Wherever heads are taken by slices: there are thousands of lists.  By length alone from a whole round of pairs on, if the lists are long enough
+// to make up for the pair's longer beginning.  Single blocks / pairs, us: 10 heads x 104 blocks 777 / 712, 10 x 120 898 / 869, 8 x 200 1788 / 1716, 10 x 180
+// 1790 / 1778, 14 x 88 759 / 755, 8 x 256 2610 / 2535, 5 x 500 4925 / 4710, 4 x 929 13415 / 12250; lists of 20: 60 x 20 207 / 211, of 40: 32 x 40 422 / 429; below a
+// round: 5 x 110 480 / 487.
+inline bool takes_pairs(const WorkMap& w) {
+  if (w.n_blocks > kMaxOrdered) return false;
+  return w.sliced > 0 || (w.mean >= 64 && (int64_t)w.ordered * ((w.n_blocks + 1) / 2) >= kTwoRound);
 }
 
 // ---- How many groups of waves share a list ------------------------------------------------------
@@ -435,6 +476,7 @@ struct FwdArgs {
   float scale;
   TokenRule rule;
   uint64_t* wg_trace;  // null, or [grid][3]: begin, end (100 MHz clock), where the workgroup ran
+  const int32_t* pair_order;  // pairs of query blocks by falling length; null only if work.ordered == 0
 };
 
 int launch_fwd(int D, int block, const FwdArgs& a, hipStream_t stream);

@@ -276,25 +276,38 @@ struct Meta {
   }
 };
 
+// Entries of the lists of blocks r and r + 1.
+__device__ inline int32_t pair_length(const int32_t* counts, int32_t nb, int32_t r) { return counts[r] + (r + 1 < nb ? counts[r + 1] : 0); }
+
 // What workgroup r needs to know of all lists to write its own: where it starts.  On the way it writes
 // ptr[r], the launch partitions, the longest list and the totals, so that neither a scan nor a partition pass is needed: every
 // workgroup reads all counts (nb / 256 rounds), which up to kMaxOrdered blocks costs less than the launches.
-// columns: of the transposed lists.
-__device__ int32_t place_list(const int32_t* counts, int32_t nb, int32_t r, int32_t* ptr, int32_t* order, const Meta& meta, bool columns) {
+// columns: of the transposed lists.  pair_order: of the pairs of neighbouring blocks, or null.
+__device__ int32_t place_list(const int32_t* counts, int32_t nb, int32_t r, int32_t* ptr, int32_t* order, int32_t* pair_order, const Meta& meta,
+                              bool columns) {
   const int slice = columns ? kSliceT : kSlice;
   const int32_t len = counts[r];
+  const bool places_pair = pair_order && r % 2 == 0;
+  const int32_t pair_len = places_pair ? pair_length(counts, nb, r) : 0;
   long long before = 0, total = 0;
-  int32_t ahead = 0;
+  int32_t ahead = 0;  // blocks with longer lists, and pairs above bit 16: at most 2^14 and 2^13
   for (int32_t j = threadIdx.x; j < nb; j += kThreads) {
     const int32_t other = counts[j];
     total += other;
     before += j < r ? other : 0;
     ahead += (other > len || (other == len && j < r)) ? 1 : 0;
+    if (places_pair && j % 2 == 0) {
+      const int32_t other_pair = pair_length(counts, nb, j);
+      ahead += (other_pair > pair_len || (other_pair == pair_len && j < r)) ? 1 << 16 : 0;
+    }
   }
   block_sum3(before, total, ahead);
+  const int32_t pairs_ahead = ahead >> 16;
+  ahead &= 0xffff;
   if (threadIdx.x == 0) {
     ptr[r] = (int32_t)before;
     order[ahead] = r;
+    if (places_pair) pair_order[pairs_ahead] = r / 2;
     if (ahead == 0) meta.put(columns ? kLongestT : kLongest, len);
     if (r == nb - 1) {
       ptr[nb] = (int32_t)total;
@@ -316,10 +329,10 @@ __device__ int32_t place_list(const int32_t* counts, int32_t nb, int32_t r, int3
 }
 
 __global__ void __launch_bounds__(kThreads) mask_lists_kernel(MaskGeom g, int32_t nwords, const int32_t* counts, int32_t* row_ptr,
-                                                             int32_t* order, Meta meta, int32_t* col_idx) {
+                                                             int32_t* order, Meta meta, int32_t* col_idx, int32_t* pair_order) {
   extern __shared__ uint32_t words[];
   row_bitmap(g, blockIdx.x, words, nwords);
-  const int32_t start = place_list(counts, g.nb, blockIdx.x, row_ptr, order, meta, false);
+  const int32_t start = place_list(counts, g.nb, blockIdx.x, row_ptr, order, pair_order, meta, false);
   write_row(words, nwords, col_idx + start);
 }
 
@@ -354,13 +367,13 @@ __global__ void __launch_bounds__(kThreads) transpose_fill_kernel(const int32_t*
 __global__ void __launch_bounds__(kThreads) transpose_lists_kernel(const int32_t* row_ptr, const int32_t* col_idx, int32_t nb,
                                                                   const int32_t* counts, int32_t* col_ptr, int32_t* order, Meta meta,
                                                                   int32_t* row_idx) {
-  const int32_t start = place_list(counts, nb, blockIdx.x, col_ptr, order, meta, true);
+  const int32_t start = place_list(counts, nb, blockIdx.x, col_ptr, order, nullptr, meta, true);
   write_column(row_ptr, col_idx, nb, blockIdx.x, start, row_idx);
 }
 
-// Workgroup 0 cuts the slices; the others, a wave per block, place the block at its rank by falling
+// Workgroup 0 cuts the slices; the others, a wave per block, place the block (and its pair) at its rank by falling
 // list length (equal lengths: by index) if there is an order to fill, and the first writes its length.
-__global__ void __launch_bounds__(kThreads) partition_kernel(const int32_t* ptr, int32_t nb, int32_t* order, Meta meta, bool columns) {
+__global__ void __launch_bounds__(kThreads) partition_kernel(const int32_t* ptr, int32_t nb, int32_t* order, int32_t* pair_order, Meta meta, bool columns) {
   if (blockIdx.x > 0) {
     const int32_t b = (blockIdx.x - 1) * (kThreads / 64) + (threadIdx.x >> 6);
     if (b >= nb) return;
@@ -370,9 +383,21 @@ __global__ void __launch_bounds__(kThreads) partition_kernel(const int32_t* ptr,
       const int32_t other = ptr[j + 1] - ptr[j];
       ahead += (other > len || (other == len && j < b)) ? 1 : 0;
     }
-    for (int off = 32; off > 0; off >>= 1) ahead += __shfl_xor(ahead, off);
+    const bool places_pair = pair_order && b % 2 == 0;
+    if (places_pair) {
+      const auto pair_end = [&](int32_t r) { return ptr[r + 2 <= nb ? r + 2 : nb]; };
+      const int32_t pair_len = pair_end(b) - ptr[b];
+      for (int32_t j = 2 * (threadIdx.x & 63); j < nb; j += 128) {
+        const int32_t other = pair_end(j) - ptr[j];
+        ahead += (other > pair_len || (other == pair_len && j < b)) ? 1 << 16 : 0;
+      }
+    }
+    for (int off = 32; off > 0; off >>= 1) ahead += __shfl_xor(ahead, off);  // at most 2^14 blocks, 2^13 pairs
+    const int32_t pairs_ahead = ahead >> 16;
+    ahead &= 0xffff;
     if ((threadIdx.x & 63) == 0) {
       order[ahead] = b;
+      if (places_pair) pair_order[pairs_ahead] = b / 2;
       if (ahead == 0) meta.put(columns ? kLongestT : kLongest, len);
     }
     return;
@@ -399,11 +424,11 @@ int check_common(int64_t n_tokens, int32_t block, uint32_t flags) {
 }
 
 // Device storage of a mask is three allocations: `meta` (two 64-bit totals and the two launch
-// partitions), `ptrs` (row_ptr and its order and, with the transposed lists, col_ptr and its order) and `idx` (col_idx and
+// partitions), `ptrs` (row_ptr, its order and that of its pairs and, with the transposed lists, col_ptr and its order) and `idx` (col_idx and
 // row_idx).  The views d_row_ptr, d_col_ptr, ... point into them at 256-byte aligned offsets.
-int launch_partition(const int32_t* ptr, int32_t nb, int32_t* order, const Meta& meta, bool columns, hipStream_t st) {
+int launch_partition(const int32_t* ptr, int32_t nb, int32_t* order, int32_t* pair_order, const Meta& meta, bool columns, hipStream_t st) {
   const int32_t per = kThreads / 64;
-  partition_kernel<<<1 + (order ? (nb + per - 1) / per : 0), kThreads, 0, st>>>(ptr, nb, order, meta, columns);
+  partition_kernel<<<1 + (order ? (nb + per - 1) / per : 0), kThreads, 0, st>>>(ptr, nb, order, pair_order, meta, columns);
   RADIAL_HIP_TRY(hipGetLastError());
   return RADIAL_OK;
 }
@@ -473,8 +498,10 @@ int alloc_meta_and_ptrs(radial_mask* m) {
   RADIAL_HIP_TRY(hipMalloc(&m->d_meta, sizeof(int32_t) * kMetaInts));
   const int64_t no = m->n_blocks <= kMaxOrdered ? aligned_ints(m->n_blocks) : 0;
   const int64_t lists = (m->flags & RADIAL_MASK_TRANSPOSE) ? 2 : 1;
-  RADIAL_HIP_TRY(hipMalloc(&m->d_ptrs, sizeof(int32_t) * ((np + no) * lists + no)));
+  const int64_t pairs = no ? aligned_ints((m->n_blocks + 1) / 2) : 0;
+  RADIAL_HIP_TRY(hipMalloc(&m->d_ptrs, sizeof(int32_t) * ((np + no) * lists + no + pairs)));
   if (no) m->d_counts = m->d_ptrs + (np + no) * lists;
+  if (no) m->d_pair_order = m->d_counts + no;
   m->d_row_ptr = m->d_ptrs;
   if (no) m->d_order = m->d_ptrs + np;
   m->d_slice = m->d_meta + kSlice;
@@ -504,7 +531,7 @@ int finish_mask(radial_mask* m, HostMeta& shared, bool rows_placed, hipStream_t 
   const Meta meta = {m->d_meta, shared.device()};
   alignas(8) int32_t h_meta[kMetaInts];
   if (!rows_placed)
-    if (int rc = launch_partition(m->d_row_ptr, nb, m->d_order, meta, false, st)) return rc;
+    if (int rc = launch_partition(m->d_row_ptr, nb, m->d_order, m->d_pair_order, meta, false, st)) return rc;
   if ((m->flags & RADIAL_MASK_TRANSPOSE) && m->d_counts) {
     transpose_count_kernel<<<nb, kThreads, 0, st>>>(m->d_row_ptr, m->d_col_idx, nb, m->d_counts);
     RADIAL_HIP_TRY(hipGetLastError());
@@ -517,7 +544,7 @@ int finish_mask(radial_mask* m, HostMeta& shared, bool rows_placed, hipStream_t 
     RADIAL_HIP_TRY(hipGetLastError());
     transpose_fill_kernel<<<nb, kThreads, 0, st>>>(m->d_row_ptr, m->d_col_idx, nb, m->d_col_ptr, m->d_row_idx);
     RADIAL_HIP_TRY(hipGetLastError());
-    if (int rc = launch_partition(m->d_col_ptr, nb, m->d_order_t, meta, true, st)) return rc;
+    if (int rc = launch_partition(m->d_col_ptr, nb, m->d_order_t, nullptr, meta, true, st)) return rc;
   }
   hipError_t e = hipSuccess;
   if (!shared.host()) e = hipMemcpyAsync(h_meta, m->d_meta, sizeof h_meta, hipMemcpyDeviceToHost, st);
@@ -599,7 +626,7 @@ static int build_radial(radial_mask* m, const radial_mask_params* p, hipStream_t
     if (int rc = alloc_idx(m)) return rc;
     HostMeta shared(st);
     mask_lists_kernel<<<nb, kThreads, nwords * sizeof(uint32_t), st>>>(g, nwords, m->d_counts, m->d_row_ptr, m->d_order,
-                                                                       Meta{m->d_meta, shared.device()}, m->d_col_idx);
+                                                                       Meta{m->d_meta, shared.device()}, m->d_col_idx, m->d_pair_order);
     RADIAL_HIP_TRY(hipGetLastError());
     return finish_mask(m, shared, true, st);
   }

@@ -268,7 +268,7 @@ struct Merge {
 // at the same time (its K/V stay in the shared last-level cache), neighbouring workgroups of an XCD
 // share K/V tiles in that XCD's L2, and every XCD gets every slice equally often (slices of equal
 // weight do not take exactly equal time).
-__device__ __forceinline__ bool work_item(const WorkMap& w, uint32_t id, int32_t& bh, int32_t& block) {
+__host__ __device__ __forceinline__ bool work_item(const WorkMap& w, uint32_t id, int32_t& bh, int32_t& block) {
   const uint32_t n_sliced = 8u * (uint32_t)w.sliced * (uint32_t)w.max_slice;
   if (id >= n_sliced) {
     // By falling list length.  A window of 8 ranks of every head goes to the 8 XCDs at once; inside it an
@@ -310,6 +310,73 @@ __device__ __forceinline__ uint32_t halved_item(uint32_t id, uint32_t first, uin
   const uint32_t rest = halved & 7u, k = j - 16u * by8;
   part = k >= rest ? 1 : 0;
   return first + 8u * by8 + (k >= rest ? k - rest : k);
+}
+
+// What workgroup `id` of a launch over pairs of query blocks takes (see TwoMap): both blocks of a pair, block `block` of it, or half of that.
+struct TwoItem {
+  enum Form { kPair, kBlock, kHalf } form;
+  int32_t bh, pair, block, half;
+  int64_t record;  // of a trace: its own for every workgroup, the same for both halves of a block
+};
+
+// Workgroup `id` of those that share `count` items, 1 << kLog of them each: item and part.  All parts of an item are on one XCD while 8
+// items are left.
+template <int kLog>
+__host__ __device__ __forceinline__ uint32_t split_item(uint32_t id, uint32_t count, int32_t& part) {
+  const uint32_t whole = count & ~7u;
+  if (id < whole << kLog) {
+    part = (int32_t)(id >> 3) & ((1 << kLog) - 1);
+    return (id >> (3 + kLog)) * 8u + (id & 7u);
+  }
+  const uint32_t rest = count - whole, k = id - (whole << kLog);
+  part = (int32_t)(k / rest);
+  return whole + k % rest;
+}
+
+__host__ __device__ __forceinline__ bool two_item(const WorkMap& w, const TwoMap& m, uint32_t id, TwoItem& item) {
+  item.form = TwoItem::kPair;
+  item.block = item.half = 0;
+  item.record = id;
+  uint32_t pair_id = id;
+  if (id >= m.n_two) {
+    const uint32_t single = id - m.n_two;
+    int32_t part;
+    uint32_t k;
+    if (single < 2u * m.n_one) {
+      item.form = TwoItem::kBlock;
+      k = split_item<1>(single, m.n_one, part);
+      item.block = part;
+    } else {
+      item.form = TwoItem::kHalf;
+      k = m.n_one + split_item<2>(single - 2u * m.n_one, m.n_half, part);
+      item.block = part >> 1;
+      item.half = part & 1;
+    }
+    pair_id = m.n_two + k;
+    const uint32_t count = m.n_one + m.n_half, eights = k & ~7u;  // both blocks of a pair 8 records apart, as the workgroups' XCDs go round
+    item.record = m.n_two + 2u * eights + (uint32_t)item.block * (count - eights < 8u ? count - eights : 8u) + (k & 7u);
+  }
+  if (pair_id >= m.n_sliced) {
+    if (!work_item(m.pairs, pair_id - m.n_sliced, item.bh, item.pair)) return false;
+    item.bh += w.sliced;
+  } else {
+    // As in work_item, XCD x takes the pairs that start in slice (x + bh) mod 8 of head bh, but one head after the other without gaps: a head
+    // whose slices differ in length would leave workgroups without work among the others (heads of 8 blocks: 1.39 of the time).  Over 8 heads
+    // every XCD has each slice once.
+    const uint32_t xcd = id & 7u, per_head = (uint32_t)m.pairs.n_blocks, eight = (id >> 3) / per_head;
+    int32_t left = (int32_t)((id >> 3) - eight * per_head), first = 0;
+    item.bh = (int32_t)(8u * eight);
+    for (int t = 0;; ++t, ++item.bh) {
+      if (t == 8 || item.bh >= w.sliced) return false;
+      const int32_t sl = (int32_t)(xcd + t) & 7;
+      first = (w.slice[sl] + 1) / 2;
+      const int32_t n = (w.slice[sl + 1] + 1) / 2 - first;
+      if (left < n) break;
+      left -= n;
+    }
+    item.pair = first + left;
+  }
+  return 2 * item.pair + item.block < w.n_blocks;
 }
 
 // ---- token-level rule of the radial mask inside listed blocks ---------------------------------
