@@ -195,5 +195,6 @@ extern "C" int radial_attn_fwd_fp8(int32_t B, int32_t H, int32_t N, int32_t D, i
   a.work = make_work_map(mask, Walk::kForward, B * H, D);
   a.B = B; a.H = H; a.N = N; a.n_blocks = mask->n_blocks;
   a.scale = scale;
+  a.pair_order = mask->d_pair_order;
   return launch_fwd_fp8(a, (hipStream_t)hip_stream);
 }

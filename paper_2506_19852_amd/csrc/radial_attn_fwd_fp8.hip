@@ -12,6 +12,7 @@
 // product (P in bf16, V in bf16) and the epilogue are unchanged.  The two scales are positive and
 // constant over a stage, so they are folded into the exponent's multiplier and applied to the row
 // maximum once per stage instead of to every score.
+#include "radial_attn_fwd_two.h"
 #include "radial_internal.h"
 #include "radial_tile.h"
 
@@ -21,24 +22,6 @@ namespace {
 constexpr int D = 128, BLK = 128;
 constexpr int kDTiles = D / 32;
 using VT = SwzTile<D>;
-
-typedef int i32x8 __attribute__((ext_vector_type(8)));
-
-// K8 tile: rows of 128 bytes = 8 pieces of 16 bytes, two rows per 256-byte line; pieces are
-// XOR-swizzled inside their line so that the 128-bit reads of one piece column over 16
-// consecutive rows touch 16 different 16-byte bank groups.
-__device__ __forceinline__ int k8_piece(int r, int p) {
-  const int lin = r * 8 + p;
-  const int line = lin >> 4, slot = lin & 15;
-  return (line << 8) + ((slot ^ (line & 7)) << 4);
-}
-// (row, piece) of the source that belongs at linear LDS piece index `lin`
-__device__ __forceinline__ void k8_source_of(int lin, int& r, int& p) {
-  const int line = lin >> 4, slot = lin & 15;
-  const int src = (line << 4) + (slot ^ (line & 7));
-  r = src >> 3;
-  p = src & 7;
-}
 
 // One workgroup per (batch*head, block of tokens): amax, scale, codes.  Every thread loads its pieces of the block at once
 // and keeps them for the codes.  As a loop over pieces that read the block twice and waited for each, a launch of 16 to 82 blocks
@@ -153,13 +136,17 @@ struct Fp8Tile {
   static constexpr int kLdsBytes = S * 2 * kBufBytes > Join::kLdsBytes ? S * 2 * kBufBytes : Join::kLdsBytes;
 };
 
-template <int S, int R>
-__device__ __forceinline__ void fp8_body(const Fp8FwdArgs& a) {
+struct Fp8Key {};
+
+// Part `part` of the R of query block qb.  kShared: bytes of the static stage buffers of a kernel that has several forms, 0: this is its only one.
+template <int S, int R, int kShared = 0>
+__device__ __forceinline__ void fp8_body(const Fp8FwdArgs& a, int32_t bh, int32_t qb, int32_t part) {
   using T = Fp8Tile<S, R>;
   constexpr int kWaves = T::kWaves, kStageKeys = T::kStageKeys, kSubs = T::kSubs, kK8Bytes = T::kK8Bytes, kBufBytes = T::kBufBytes;
   constexpr int kKLoads = T::kKLoads, kVLoads = T::kVLoads, kKeyTiles = T::kKeyTiles;
   // [group][stage buffer][K8 tile, V tile]; one group's are a static array, as in the bf16 kernel
-  __shared__ __attribute__((aligned(1024))) char lds_one[S == 1 ? 2 * kBufBytes : 16];
+  static_assert(S == 1 || kShared == 0, "groups have theirs in dynamic LDS");
+  constexpr int kStaticBytes = kShared ? kShared : S == 1 ? 2 * kBufBytes : 16;
   extern __shared__ __attribute__((aligned(1024))) char lds_all[];
 
   const int lane = threadIdx.x & 63;
@@ -167,17 +154,13 @@ __device__ __forceinline__ void fp8_body(const Fp8FwdArgs& a) {
   const int group = S == 1 ? 0 : wave_all / kWaves;
   const int wave = S == 1 ? wave_all : wave_all % kWaves;
   const auto lds_at = [&](int32_t offset) __attribute__((always_inline)) -> const char* {
-    if constexpr (S == 1) return lds_one + offset;
+    if constexpr (S == 1) return fwd::static_lds<Fp8Key, kStaticBytes>() + offset;
     else return lds_all + group * 2 * kBufBytes + offset;
   };
   const uint32_t lds_base = lds_address(lds_at(0));
   const int lq = lane & 31;
   const int g = lane >> 5;
 
-  int32_t bh, qb;
-  if (!work_item(a.work, blockIdx.x, bh, qb)) return;
-  const int32_t part = R == 1 ? 0 : bh % R;  // with R > 1 the work map counts R heads for each
-  if (R > 1) bh /= R;
   const int32_t b = bh / a.H, h = bh % a.H;
 
   const uint8_t* qp = a.q8 + (int64_t)bh * a.N * D;
@@ -433,13 +416,33 @@ __device__ __forceinline__ void fp8_body(const Fp8FwdArgs& a) {
   }
 }
 
+// Work item of this workgroup; with R > 1 the work map counts R heads for each.
+template <int S, int R>
+__device__ __forceinline__ void fp8_item(const Fp8FwdArgs& a) {
+  int32_t bh, qb;
+  if (!work_item(a.work, blockIdx.x, bh, qb)) return;
+  fp8_body<S, R>(a, R == 1 ? bh : bh / R, qb, R == 1 ? 0 : bh % R);
+}
 template <int S>
 __global__ void __launch_bounds__(2 * BLK * S, 3) radial_fwd_fp8_kernel(const Fp8FwdArgs a) {
-  fp8_body<S, 1>(a);
+  fp8_item<S, 1>(a);
 }
 template <int S, int R>
 __global__ void __launch_bounds__(2 * BLK / R * S, (BLK / R / 32 * S + 3) / 4) radial_fwd_fp8_part_kernel(const Fp8FwdArgs a) {
-  fp8_body<S, R>(a);
+  fp8_item<S, R>(a);
+}
+
+// Pairs of query blocks (the header of radial_attn_fwd_two.h has the reasons), single ones at the end.  Here the vector unit is the bound rather
+// than the matrix pipes, and two waves per SIMD whose softmax is dealt among the matrix instructions keep it as busy as the three of the
+// kernel for single blocks, with half the copies and LDS reads.  Forward with the quantisation, ms, single blocks / pairs: 24 x 118 800 tokens 63.6 / 55.6, 40 x 32 760
+// 11.7 / 10.5, 3 x 118 800 8.19 / 7.30, 10 x 14 040 0.763 / 0.703, 400 x 2048 0.921 / 0.892.
+__global__ void __launch_bounds__(2 * BLK, 2) radial_fwd_fp8_two_kernel(const Fp8FwdArgs a, const TwoMap m) {
+  constexpr int kBytes = fwd::TwoTile<true>::kLdsBytes;
+  TwoItem item;
+  if (!two_item(a.work, m, blockIdx.x, item)) return;
+  const int32_t qb = 2 * item.pair + item.block;
+  if (item.form == TwoItem::kPair) fwd::two_body<false>(a, item.bh, qb, m.c, 0, fwd::static_lds<Fp8Key, kBytes>());
+  else fp8_body<1, 1, kBytes>(fwd::own_args<Fp8FwdArgs>(), item.bh, qb, 0);
 }
 
 }  // namespace
@@ -477,6 +480,12 @@ int launch_fwd_fp8(const Fp8FwdArgs& a, hipStream_t stream) {
   if (work_grid_bound(a.work) > 0x7fffffffLL) return fail(RADIAL_ESHAPE, "B*H*n_blocks is too large for one launch");
   const int64_t items = work_items(a.work, a.n_blocks);
   if (items == 0) return RADIAL_OK;
+  if (takes_pairs(a.work)) {
+    const TwoMap m = make_two_map(a.work, a.pair_order, a.scale, true);
+    radial_fwd_fp8_two_kernel<<<dim3(m.n_two + 2 * m.n_one), dim3(2 * BLK), 0, stream>>>(a, m);
+    RADIAL_HIP_TRY(hipGetLastError());
+    return RADIAL_OK;
+  }
   const int parts = fp8_parts(a.work, items);
   if (parts == 4) return launch_split<4, 4>(a, stream);
   if (parts == 2) return launch_split<4, 2>(a, stream);

@@ -191,6 +191,7 @@ inline int64_t work_grid(const WorkMap& w, int32_t n_blocks) {
 struct TwoMap {
   WorkMap pairs;  // the ordered heads alone, with pairs for blocks
   uint32_t n_sliced, n_two, n_one, n_half;
+  float c;  // exp(scale * x) = exp2(c * x); worked out here it is a scalar in the kernel
 };
 constexpr uint32_t kTwoRound = 512;  // workgroups that the chip holds
 
@@ -199,8 +200,13 @@ constexpr uint32_t kTwoRound = 512;  // workgroups that the chip holds
 // Forward, us, single blocks / 512 pairs, 76 blocks / 512, the last 38 in halves / 448, 38 / 256, 38: 10 heads x 14 040 tokens 829 / 794 / 769 / 776 / 820.
 // 3 heads x 119 026 (1395 pairs) 8080 / 1024 pairs 7750, the last 80 in halves 7570, 192 7830, 256 8000; 1136 pairs, 64 in halves 7570, 1280 8060.  With
 // slices 40 heads x 32 760 (1024 ordered pairs), none / 512 / 768 of them as pairs 13010 / 12980 / 12960, 24 x 118 800 70.2 / 69.9 / 69.8 ms.
-inline TwoMap make_two_map(const WorkMap& w, const int32_t* pair_order) {
+// 8-bit scores, which have no halves here: what is left over goes singly up to 192 pairs, and beyond 256, a pair for each compute unit, what is
+// above them up to 384; with slices 128 pairs.  Single blocks / the best of 0, 64 .. 256 pairs taken singly / this rule, us (pairs in order of length, left over above rounds): 550 (38)
+// 763 / 706 / 703, 600 (88) 769 / 727 / 721, 660 (148) 930 / 891 / 891, 700 (188) 990 / 932 / 932, 740 (228) 1146 / 1073 / 1076, 800 (288) 1638 / 1387 / 1390, 832 (320) 1762 / 1530 /
+// 1535, 900 (388) 1645 / 1487 / 1471, 1024 (0) 2265 / 2115 / 2098, 1395 (371) 8190 / 7353 / 7297; none singly: 550 800, 800 1525, 1395 8010.
+inline TwoMap make_two_map(const WorkMap& w, const int32_t* pair_order, float scale, bool codes) {
   TwoMap m;
+  m.c = scale * 1.4426950408889634f;
   m.pairs = w;
   m.pairs.order = pair_order;
   m.pairs.sliced = 0;
@@ -210,8 +216,13 @@ inline TwoMap make_two_map(const WorkMap& w, const int32_t* pair_order) {
   m.n_sliced = 8u * ((uint32_t)w.sliced / 8u * per_head + (last < per_head ? last : per_head));
   const uint32_t ordered = (uint32_t)w.ordered * per_head;
   uint32_t rest = ordered % kTwoRound;
-  if (w.sliced > 0 && rest < kTwoRound / 2 && ordered >= kTwoRound) rest += kTwoRound;
-  m.n_half = rest < 64u ? rest : 64u;
+  if (codes) {
+    if (w.sliced > 0) rest = ordered < 128u ? ordered : 128u;
+    else if (rest > 192u) rest = rest <= 256u || rest > 384u ? 0u : rest < 320u ? 64u : rest - 256u;
+  } else if (w.sliced > 0 && rest < kTwoRound / 2 && ordered >= kTwoRound) {
+    rest += kTwoRound;
+  }
+  m.n_half = codes ? 0u : rest < 64u ? rest : 64u;
   m.n_one = rest - m.n_half;
   m.n_two = m.n_sliced + ordered - rest;
   return m;
@@ -501,6 +512,7 @@ struct Fp8FwdArgs {
   WorkMap work;
   int32_t B, H, N, n_blocks;
   float scale;
+  const int32_t* pair_order;  // as in FwdArgs
 };
 int launch_fwd_fp8(const Fp8FwdArgs& a, hipStream_t stream);
 int launch_quantize_fp8(int32_t B, int32_t H, int32_t N, int32_t D, const TensorArg& x, int32_t block, uint8_t* codes,

@@ -17,6 +17,7 @@ typedef __attribute__((ext_vector_type(2))) float f32x2;
 typedef __attribute__((ext_vector_type(4))) short s16x4;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
+typedef __attribute__((ext_vector_type(8))) int i32x8;
 
 // Generic pointer into a __shared__ array -> LDS (address space 3) pointer.
 template <class T>
@@ -112,6 +113,22 @@ struct SwzTile {
     c = (src % kPieces) * 8;
   }
 };
+
+// K8 tile: rows of 128 bytes = 8 pieces of 16 bytes, two rows per 256-byte line; pieces are
+// XOR-swizzled inside their line so that the 128-bit reads of one piece column over 16
+// consecutive rows touch 16 different 16-byte bank groups.
+__device__ __forceinline__ int k8_piece(int r, int p) {
+  const int lin = r * 8 + p;
+  const int line = lin >> 4, slot = lin & 15;
+  return (line << 8) + ((slot ^ (line & 7)) << 4);
+}
+// (row, piece) of the source that belongs at linear LDS piece index `lin`
+__device__ __forceinline__ void k8_source_of(int lin, int& r, int& p) {
+  const int line = lin >> 4, slot = lin & 15;
+  const int src = (line << 4) + (slot ^ (line & 7));
+  r = src >> 3;
+  p = src & 7;
+}
 
 // Transposing LDS read: within each group of 16 lanes, lane i supplies the address of 4
 // consecutive bf16 of row i/4 (columns 4*(i%4)..) and receives, for column i of that 16-wide

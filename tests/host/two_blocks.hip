@@ -1,5 +1,5 @@
 // Which workgroup of a forward over pairs of query blocks takes what (radial_tile.h, radial_internal.h) on the host: for each input line
-//   n_blocks sliced ordered mean slice[0] .. slice[8]
+//   n_blocks sliced ordered mean codes slice[0] .. slice[8]
 // (the order of the pairs is their index, reversed) "takes_pairs grid records", then a line "bh block half form record" for every workgroup that
 // has work (form 0: block and block + 1, 1: a block, 2: half of one) and a line "end".
 #include <stdio.h>
@@ -14,8 +14,9 @@ using namespace radial;
 int main() {
   int32_t slice[9];
   WorkMap w = {};
+  int codes;
   w.slice = slice;
-  while (scanf("%d %d %d %d", &w.n_blocks, &w.sliced, &w.ordered, &w.mean) == 4) {
+  while (scanf("%d %d %d %d %d", &w.n_blocks, &w.sliced, &w.ordered, &w.mean, &codes) == 5) {
     w.max_slice = 0;
     for (int i = 0; i < 9; ++i) {
       if (scanf("%d", slice + i) != 1) return 1;
@@ -23,7 +24,7 @@ int main() {
     }
     std::vector<int32_t> order((w.n_blocks + 1) / 2);
     for (size_t i = 0; i < order.size(); ++i) order[i] = (int32_t)(order.size() - 1 - i);
-    const TwoMap m = make_two_map(w, order.data());
+    const TwoMap m = make_two_map(w, order.data(), 1.f, codes != 0);
     const uint32_t grid = m.n_two + 2 * m.n_one + 4 * m.n_half;
     printf("%d %u %lld\n", takes_pairs(w) ? 1 : 0, grid, 8LL * (w.sliced + w.ordered) * w.max_slice);
     for (uint32_t id = 0; id < grid; ++id) {

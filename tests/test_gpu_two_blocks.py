@@ -85,6 +85,45 @@ def test_long_lists(H, nb, cut, kind, gain):
     check(rb, 1, H, 128 * nb - cut, lists, "bnhd", gain, H + nb)
 
 
+@pytest.mark.parametrize("H, nb, cut, kind, gain", [(300, 1, 60, "mixed", 1.0), (120, 3, 127, "mixed", 4.0), (61, 7, 33, "all", 1.0), (20, 131, 97, "mixed", 4.0), (8, 130, 1, "mixed", 1.0), (14, 101, 0, "all", 2.0)])
+def test_8_bit_scores(H, nb, cut, kind, gain):
+    """The same launches on codes of Q and K with a scale per block, against float64 on the codes."""
+    import torch
+    from paper_2506_19852_amd import binding as rb
+    print(f"8 bits H={H} nb={nb} cut={cut} {kind} gain={gain}", flush=True)
+    D, N = 128, 128 * nb - cut
+    g = torch.Generator(device="cuda").manual_seed(N + H)
+    q, k, v = (torch.randn((1, H, N, D), device="cuda", generator=g) for _ in range(3))
+    # blocks far apart in scale: either block of a pair and every key block has its own
+    spread = (2.0 ** torch.randint(-2, 3, (1, H, nb, 1), device="cuda", generator=g)).repeat_interleave(128, 2)[:, :, :N]
+    q, k, v = (q * gain).bfloat16(), (k * spread).bfloat16(), v.bfloat16()
+    codes = [torch.empty((1, H, N, D), dtype=torch.uint8, device="cuda") for _ in range(2)]
+    scales = [torch.empty((1, H, nb), dtype=torch.float32, device="cuda") for _ in range(2)]
+    for x, c, s in zip((q, k), codes, scales):
+        rb.radial_quantize_fp8(x, 128, c, s)
+    lists = make_lists(nb, kind, nb + H)
+    row_ptr = np.concatenate([[0], np.cumsum([len(r) for r in lists])]).astype(np.int32)
+    m = rb.radial_mask_from_csr(N, 128, row_ptr, np.concatenate(lists).astype(np.int32))
+    out = torch.full((1, H, N, D), float("nan"), dtype=torch.bfloat16, device="cuda")
+    lse = torch.full((1, H, N), float("nan"), dtype=torch.float32, device="cuda")
+    rb.radial_attn_fwd_fp8(codes[0], scales[0], codes[1], scales[1], v, out, lse, m, D ** -0.5)
+    bm = torch.zeros((nb, nb), dtype=torch.bool)
+    for r, c in enumerate(lists):
+        bm[r, torch.from_numpy(c.astype(np.int64))] = True
+    vis = bm.cuda().repeat_interleave(128, 0).repeat_interleave(128, 1)[:N, :N]
+    some = vis.any(1)
+    for h in sorted({0, 1, H // 2, H - 2, H - 1}):
+        qd, kd = (c[0, h].view(torch.float8_e4m3fn).double() * s[0, h].double().repeat_interleave(128)[:N, None] for c, s in zip(codes, scales))
+        ref, ref_lse = reference(qd, kd, v[0, h], torch.zeros_like(qd), vis, D ** -0.5)[:2]
+        assert (lse[0, h][~some] == float("-inf")).all() and (out[0, h][~some] == 0).all()
+        if some.any():
+            # the 8-bit matrix instruction's sums: 1e-4 of the scores; P and out are rounded to bf16 (2^-9 each)
+            assert (lse[0, h][some].double() - ref_lse[some]).abs().max() <= 1e-4 * (1 + ref_lse[some].abs().max())
+            assert (out[0, h].double() - ref).norm() <= 8e-3 * ref.norm() + 1e-6
+    assert torch.isfinite(out).all() and torch.isfinite(lse[:, :, some]).all()
+    m.free()
+
+
 def test_trace_of_pairs():
     """One record for each workgroup that takes a pair and for each block that is taken alone or in halves; the same results."""
     import torch

@@ -23,7 +23,7 @@ def launches(tmp_path_factory):
     assert r.returncode == 0, r.stdout[-3000:]
 
     def run(cases):
-        text = "\n".join(" ".join(map(str, (*c[:4], *c[4]))) for c in cases)
+        text = "\n".join(" ".join(map(str, (*c[:4], int(len(c) > 5), *c[4]))) for c in cases)
         r = subprocess.run([str(exe)], input=text, stdout=subprocess.PIPE, text=True, timeout=120)
         assert r.returncode == 0
         parts = [p.strip().split("\n") for p in r.stdout.split("end\n") if p.strip()]
@@ -40,7 +40,7 @@ def uneven_slices(nb, seed):
     return [0, *sorted(rng.randint(0, nb) for _ in range(7)), nb]
 
 
-CASES = [(nb, sliced, ordered, 100, slices(nb)) for nb in (1, 2, 3, 7, 8, 9, 15, 16, 17, 64, 101, 110, 929)
+CASES = [(nb, sliced, ordered, 100, slices(nb), *codes) for codes in ((), (True,)) for nb in (1, 2, 3, 7, 8, 9, 15, 16, 17, 64, 101, 110, 929)
          for sliced, ordered in ((0, 10), (1, 8), (8, 0), (9, 8), (17, 2), (32, 8))
          for slices in (even_slices, lambda n: uneven_slices(n, 3 * n + 1))]
 
@@ -73,3 +73,11 @@ def test_whole_rounds_of_pairs_and_halves_at_the_end(launches):
     for _, items in launches([(110, 0, 10, 93, even_slices(110)), (930, 0, 3, 347, even_slices(930)), (256, 32, 8, 160, even_slices(256)), (930, 22, 2, 400, even_slices(930))]):
         forms.append([sum(1 for i in items if i[3] == form) for form in (0, 1, 2)])
     assert forms == [[512, 0, 4 * 38], [1024, 2 * (371 - 64), 4 * 64], [32 * 128 + 512, 2 * (512 - 64), 4 * 64], [22 * 465 + 512, 2 * (418 - 64), 4 * 64]]
+
+
+def test_single_blocks_with_8_bit_scores(launches):
+    """Left over above whole rounds of 512 pairs, in order of length: all up to 192 pairs, none to 256, what is above 256 (at least 64) to 384, none."""
+    pairs = {512: 0, 513: 1, 704: 192, 705: 0, 768: 0, 769: 64, 831: 64, 832: 64, 833: 65, 896: 128, 897: 0, 1023: 0, 1024: 0}
+    singles = [sum(1 for i in items if i[3] == 1) for _, items in launches([(2 * n, 0, 1, 93, even_slices(2 * n), True) for n in pairs])]
+    assert singles == [2 * n for n in pairs.values()]
+    assert [sum(1 for i in items if i[3]) for _, items in launches([(256, 32, 8, 160, even_slices(256), True), (16, 10, 2, 16, even_slices(16), True)])] == [256, 32]
