@@ -509,21 +509,22 @@ struct PairTile {
   static constexpr int kSubs = BLK / kStageQ;
   static constexpr int kSteps = D / 16;
   static constexpr int kDTiles = D / 32;
-  static constexpr int kTileBytes = kStageQ * D * 2;  // Q or dO of a stage
+  using Rows = RowsTile<D>;
+  static constexpr int kTileBytes = kStageQ / 4 * Rows::kFourRows;  // Q or dO of a stage
   static constexpr int kStatBytes = 2 * kStageQ * 4;  // LSE and delta of a stage
   static constexpr int kPBytes = kStageQ * 32 * 4;    // P of a stage and a pair
   static constexpr int kGradAt = 3 * kTileBytes;      // [Q x 3][dO x 2][LSE, delta x 3][P x 2 x pairs]
   static constexpr int kStatAt = kGradAt + 2 * kTileBytes;
   static constexpr int kPAt = kStatAt + 3 * kStatBytes;
   static constexpr int kLdsBytes = kPAt + 2 * kPairs * kPBytes;
-  static constexpr int kLoadsPerWave = kTileBytes / 1024 / (2 * kPairs);
+  static constexpr int kLoadsPerWave = kStageQ / 4 / (2 * kPairs);
   static constexpr int kCopies = 2 * kLoadsPerWave + 1;  // Q, dO, and LSE (wave 0) or delta (wave 1)
 };
 
 template <int D, int BLK, bool kExact>
 __device__ __forceinline__ void pairs_body(const BwdArgs& a, uint32_t id) {
   using T = PairTile<D, BLK>;
-  using QT = SwzTile<D>;
+  using Rows = typename T::Rows;
   extern __shared__ __attribute__((aligned(1024))) char lds_all[];
 
   const int lane = threadIdx.x & 63;
@@ -567,14 +568,8 @@ __device__ __forceinline__ void pairs_body(const BwdArgs& a, uint32_t id) {
   ListRule<kStageQ, BLK> token;
   if (kExact) token.init(a.rule, kb * BLK + pair * 32, a.N, lane);
 
-  int32_t srow[T::kLoadsPerWave], scol[T::kLoadsPerWave];
-  uint32_t qoff[T::kLoadsPerWave], goff[T::kLoadsPerWave];  // byte offsets from the stage's first row
-#pragma unroll
-  for (int i = 0; i < T::kLoadsPerWave; ++i) {
-    QT::source_of((wave * T::kLoadsPerWave + i) * 64 + lane, srow[i], scol[i]);
-    qoff[i] = (uint32_t)(srow[i] * (int32_t)a.q.sn + scol[i]) * 2u;
-    goff[i] = (uint32_t)(srow[i] * (int32_t)a.dout.sn + scol[i]) * 2u;
-  }
+  const uint32_t qoff = Rows::source_bytes(lane, a.q.sn), goff = Rows::source_bytes(lane, a.dout.sn);  // from a copy's first row
+  const int32_t first_row = wave * T::kLoadsPerWave * 4;                                                     // of this wave's copies
   // Stage buffers of stage u: Q and the row statistics go round three, dO and P round two.
   struct Bufs {
     int32_t q, grad, stat, p;  // byte offsets
@@ -585,13 +580,13 @@ __device__ __forceinline__ void pairs_body(const BwdArgs& a, uint32_t id) {
   };
   // All of this wave's copies of a stage at once (first stage, ragged stages: rows past N-1 are clamped to N-1).
   auto issue_stage = [&](int32_t q0, const Bufs& to) {
-    const uint32_t qdst = lds_base + to.q + wave * T::kLoadsPerWave * 1024, gdst = lds_base + to.grad + wave * T::kLoadsPerWave * 1024;
+    const uint32_t qdst = lds_base + to.q + first_row / 4 * Rows::kFourRows, gdst = lds_base + to.grad + first_row / 4 * Rows::kFourRows;
 #pragma unroll
     for (int i = 0; i < T::kLoadsPerWave; ++i) {
-      int32_t r = q0 + srow[i];
+      int32_t r = q0 + first_row + 4 * i + Rows::source_row(lane);
       r = r < a.N ? r : a.N - 1;
-      copy16_to_lds(qp + (int64_t)r * a.q.sn + scol[i], qdst + i * 1024);
-      copy16_to_lds(gp + (int64_t)r * a.dout.sn + scol[i], gdst + i * 1024);
+      copy16_to_lds(qp + (int64_t)r * a.q.sn + Rows::source_column(lane), qdst + i * Rows::kFourRows);
+      copy16_to_lds(gp + (int64_t)r * a.dout.sn + Rows::source_column(lane), gdst + i * Rows::kFourRows);
     }
     if (wave < 2) {
       int32_t r = q0 + lane;
@@ -642,7 +637,7 @@ __device__ __forceinline__ void pairs_body(const BwdArgs& a, uint32_t id) {
     if (has_next && !spread) issue_stage(q0_next, to);
     const uint32_t on = __builtin_amdgcn_readfirstlane(spread ? ~0u : 0u);
     copy_lanes = ((uint64_t)on << 32) | on;
-    const int32_t q_src = spread ? q0_next : q0;  // any valid row when the copies are switched off
+    const int32_t q_src = (spread ? q0_next : q0) + first_row;  // any row when the copies are switched off
     qbase = qp + (int64_t)q_src * a.q.sn;
     gbase = gp + (int64_t)q_src * a.dout.sn;
   };
@@ -652,28 +647,24 @@ __device__ __forceinline__ void pairs_body(const BwdArgs& a, uint32_t id) {
   };
   auto spread_copy = [&](int j) __attribute__((always_inline)) {
     if (j < T::kLoadsPerWave) {
-      copy16_to_lds_sv_masked(qbase, qoff[j], lds_base + to.q + (wave * T::kLoadsPerWave + j) * 1024, copy_lanes);
+      copy16_to_lds_sv_masked(qbase + j * 4 * a.q.sn, qoff, lds_base + to.q + (first_row / 4 + j) * Rows::kFourRows, copy_lanes);
     } else if (j < 2 * T::kLoadsPerWave) {
       const int i = j - T::kLoadsPerWave;
-      copy16_to_lds_sv_masked(gbase, goff[i], lds_base + to.grad + (wave * T::kLoadsPerWave + i) * 1024, copy_lanes);
+      copy16_to_lds_sv_masked(gbase + i * 4 * a.dout.sn, goff, lds_base + to.grad + (first_row / 4 + i) * Rows::kFourRows, copy_lanes);
     } else {
       copy4_to_lds_sv_masked(statp + (spread ? q0_next : q0), (uint32_t)lane * 4u, lds_base + to.stat + (wave & 1) * kStageQ * 4, wave < 2 ? copy_lanes : 0ull);
     }
   };
   // LDS fragments of both products: step i = 8 * half + k-step of the first, pair j = (2 * half + 16-row step) * kDTiles + d tile of
   // the second, whose A operand is read transposed.
-  // The swizzle exchanges pieces within a row by exclusive or, and tiles start at multiples of 1024 bytes: one address per lane
-  // and product, and the pieces by exclusive or with constants (8 offsets per product held in registers were spilled).
-  const uint32_t rows_at = lds_base + QT::piece(lq, g);
-  const uint32_t columns_at = lds_base + QT::elem(4 * g + (i16 >> 2), 16 * half16 + 4 * (i16 & 3));
+  const uint32_t rows_at = lds_base + Rows::row_at(lane), columns_at = lds_base + Rows::column_at(lane);
   auto read_rows = [&](int32_t tile, int i) __attribute__((always_inline)) -> bf16x8 {
-    return *lds_pointer<const bf16x8>(((rows_at + tile) ^ (i % T::kSteps * 32)) + i / T::kSteps * 32 * 2 * D);
+    return *lds_pointer<const bf16x8>(rows_at + tile + Rows::row_step(i / T::kSteps, i % T::kSteps));
   };
   auto read_columns = [&](int32_t tile, int j) __attribute__((always_inline)) -> bf16x8 {
-    const uint32_t at_row = (columns_at + tile) ^ (j % T::kDTiles * 64);
-    const uint32_t rows = j / T::kDTiles * 16 * 2 * D;
-    const s16x4 x0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16(lds_pointer<s16x4>(at_row + rows));
-    const s16x4 x1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16(lds_pointer<s16x4>((at_row ^ 32) + rows + 8 * 2 * D));
+    const uint32_t at = columns_at + tile + Rows::column_step(j / T::kDTiles, j % T::kDTiles);
+    const s16x4 x0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16(lds_pointer<s16x4>(at));
+    const s16x4 x1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16(lds_pointer<s16x4>(at + Rows::kEightRows));
     const u32x2 lo = __builtin_bit_cast(u32x2, x0), hi = __builtin_bit_cast(u32x2, x1);
     return as_bf16x8(lo[0], lo[1], hi[0], hi[1]);
   };

@@ -130,6 +130,29 @@ __device__ __forceinline__ void k8_source_of(int lin, int& r, int& p) {
   p = src & 7;
 }
 
+// Rows of 256 bytes in LDS, four at a time: a copy (1 KiB, 64 lanes x 16 bytes) fetches four rows, lanes 4j .. 4j + 3 of every 16 a 64-byte piece of
+// row j, so that the rows lie in turn every 64 bytes, and 16 bytes lie between one four and the next.  Both access patterns, 128-bit reads of one
+// 16-byte column over 16 consecutive rows and the transposing 64-bit reads of 4 consecutive rows x 64 bytes, are free of bank conflicts, as with the
+// swizzle, but the pieces of a tile are at constant distances from one address per lane, which go into the instructions: no address
+// arithmetic and no registers for addresses.
+template <int D>
+struct RowsTile {
+  static_assert(D == 128, "rows of 256 bytes");
+  static constexpr int kFourRows = 1024 + 16, kEightRows = 2 * kFourRows;
+  // What a lane of a copy fetches: row of the four, element of the row, and its byte offset from the first row (stride sn elements).
+  __device__ static __forceinline__ int source_row(int lane) { return lane >> 2 & 3; }
+  __device__ static __forceinline__ int source_column(int lane) { return (lane >> 4) * 32 + (lane & 3) * 8; }
+  __device__ static __forceinline__ uint32_t source_bytes(int lane, int64_t sn) { return (uint32_t)(source_row(lane) * (int32_t)sn + source_column(lane)) * 2u; }
+  // An MFMA operand of 32 rows: this lane's 16 bytes of k-step 0, and the distance to k-step t of the tile-th 32 rows.
+  __device__ static __forceinline__ uint32_t row_at(int lane) { return (lane >> 2 & 7) * kFourRows + (lane & 3) * 64 + (lane >> 5) * 16; }
+  __device__ static constexpr int row_step(int tile, int t) { return tile * 8 * kFourRows + t / 2 * 256 + t % 2 * 32; }
+  // One of 32 columns, by two transposing reads kEightRows apart: this lane's 8 bytes, and the distance to columns 32 * dt of rows 16 * step.
+  __device__ static __forceinline__ uint32_t column_at(int lane) {
+    return (lane >> 5) * kFourRows + (lane >> 2 & 3) * 64 + (lane >> 4 & 1) * 32 + (lane & 3) * 8;
+  }
+  __device__ static constexpr int column_step(int step, int dt) { return step * 4 * kFourRows + dt * 256; }
+};
+
 // Transposing LDS read: within each group of 16 lanes, lane i supplies the address of 4
 // consecutive bf16 of row i/4 (columns 4*(i%4)..) and receives, for column i of that 16-wide
 // patch, the values of the group's 4 rows.
