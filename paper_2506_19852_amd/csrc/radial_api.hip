@@ -92,6 +92,7 @@ static int bwd_call(int32_t B, int32_t H, int32_t N, int32_t D, radial_tensor q,
   a.B = B; a.H = H; a.N = N; a.n_blocks = mask->n_blocks;
   a.scale = scale;
   a.rule = make_token_rule(mask);
+  a.pair_order_t = mask->d_pair_order_t;
   return launch_bwd(D, mask->block, a, (hipStream_t)hip_stream);
 }
 

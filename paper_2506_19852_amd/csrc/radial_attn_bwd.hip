@@ -22,6 +22,8 @@
 //             here (7 products in total instead of 5), which is cheaper than pushing every
 //             listed pair's 64 KiB of dQ partial sums through memory atomics.
 // Stage tiles are copied HBM -> LDS by global_load_lds, double buffered, one stage ahead.
+#include <type_traits>
+
 #include "radial_internal.h"
 #include "radial_tile.h"
 
@@ -522,7 +524,7 @@ struct PairTile {
 };
 
 template <int D, int BLK, bool kExact>
-__device__ __forceinline__ void pairs_body(const BwdArgs& a, uint32_t id) {
+__device__ __forceinline__ void pairs_body(const BwdArgs& a, int32_t bh, int32_t kb) {
   using T = PairTile<D, BLK>;
   using Rows = typename T::Rows;
   extern __shared__ __attribute__((aligned(1024))) char lds_all[];
@@ -537,8 +539,6 @@ __device__ __forceinline__ void pairs_body(const BwdArgs& a, uint32_t id) {
   const int i16 = lane & 15;
   const int half16 = (lane >> 4) & 1;
 
-  int32_t bh, kb;
-  if (!work_item(a.work_t, id, bh, kb)) return;
   const int32_t b = bh / a.H, h = bh % a.H;
   const __bf16* qp = (const __bf16*)a.q.ptr + (int64_t)b * a.q.sb + (int64_t)h * a.q.sh;
   const __bf16* gp = (const __bf16*)a.dout.ptr + (int64_t)b * a.dout.sb + (int64_t)h * a.dout.sh;
@@ -840,6 +840,353 @@ __device__ __forceinline__ void pairs_body(const BwdArgs& a, uint32_t id) {
   }
 }
 
+template <int D, int BLK, bool kExact>
+__device__ __forceinline__ void pairs_item(const BwdArgs& a, uint32_t id) {
+  int32_t bh, kb;
+  if (work_item(a.work_t, id, bh, kb)) pairs_body<D, BLK, kExact>(a, bh, kb);
+}
+
+// Pairs of waves for two neighbouring key blocks: wave w and wave w + 4 share 32 keys of either.  A query block that both transposed lists name is
+// copied once for 256 keys, and every fragment of Q and dO read from LDS feeds two MFMAs: 48 KiB of LDS traffic per 64 MFMAs of a pair, with the
+// exchange of P, instead of 81, and half the copies.  Registers (128 of dV or dK, 64 of K or V) leave 32 of scores, so a stage is 32 query rows and
+// the second wave does all of its work a stage later:
+//   stage u:  first wave   S(u), P(u) -> LDS, dV += P(u)^T dO(u)
+//             second wave  dP(u - 1), dS(u - 1) = P(u - 1) * (dP(u - 1) - delta), dK += dS(u - 1)^T Q(u - 1)
+// and Q, dO and the row statistics go round three buffers.  The lists are walked in three passes, as in the forward over pairs of query blocks
+// (radial_attn_fwd_two.h): entries of both, of the first alone, of the second alone; lists with too little in common are walked one after the other, each
+// by the pairs of waves for one block, which also take the last blocks of a launch singly.  All loops are written out for either kind of wave and
+// either set of keys: with accumulators that pass a branch or move between registers the compiler spilled 36 to 580 bytes a lane.  252 registers.
+// 40 heads x 126 360 tokens, radial lists: 226.6 -> 207.9 ms, the matrix pipes 58 % busy at 1.91 GHz (one block 54 % at 1.87).  Training steps, one
+// block / two, us: 3 x 118 800 tokens 40 240 / 39 100, 20 x 32 760 all-ones list 41 600 / 39 900, 10 x 25 600 narrow bands 13 240 / 12 630, 16 x 12 800 4370 / 4212, 400 x 1024 1136 /
+// 1104, 800 x 512 997 / 808, 1000 x 256 742 / 463 (heads of few blocks: no workgroups without work); random lists of a quarter of the blocks 9085 / 9134.
+struct TwoKeysTile {
+  static constexpr int kD = 128, kBlk = 128, kPairs = 4, kStage = 32, kSubs = kBlk / kStage, kSteps = kD / 16, kDTiles = kD / 32;
+  using Rows = RowsTile<kD>;
+  static constexpr int kTileBytes = kStage / 4 * Rows::kFourRows, kGradAt = 3 * kTileBytes, kStatAt = 6 * kTileBytes;  // [Q x 3][dO x 3]
+  static constexpr int kStatBytes = 512;                      // LSE and delta of a stage, 64 floats each
+  static constexpr int kPAt = kStatAt + 3 * kStatBytes, kPBytes = 2 * kStage * 32 * 4;  // P of a stage and a pair, [set][4 x 1 KiB]
+  static constexpr int kNamedAt = kPAt + 2 * kPairs * kPBytes, kNamedWords = kMaxOrdered / 32;
+  static constexpr int kLdsBytes = kNamedAt + 2 * kNamedWords * 4;
+};
+
+// Key blocks kb and kb + 1 (which may not exist).  False: their lists have too little in common, and nothing is done.
+__device__ __forceinline__ bool two_keys_body(const BwdArgs& a, int32_t bh, int32_t kb, float c) {
+  using T = TwoKeysTile;
+  using Rows = T::Rows;
+  extern __shared__ __attribute__((aligned(1024))) char lds_all[];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const bool second = wave >= T::kPairs;
+  const int pair = second ? wave - T::kPairs : wave;
+  const uint32_t lds_base = lds_address(lds_all);
+  const int lq = lane & 31, g = lane >> 5;
+  const int32_t b = bh / a.H, h = bh % a.H;
+  const __bf16* qp = (const __bf16*)a.q.ptr + (int64_t)b * a.q.sb + (int64_t)h * a.q.sh;
+  const __bf16* gp = (const __bf16*)a.dout.ptr + (int64_t)b * a.dout.sb + (int64_t)h * a.dout.sh;
+  const float* statp = (wave == 0 ? a.lse : a.delta) + (int64_t)bh * a.N;  // what this wave copies of them
+
+  const int32_t lo0 = __builtin_amdgcn_readfirstlane(a.col_ptr[kb]), lo1 = __builtin_amdgcn_readfirstlane(a.col_ptr[kb + 1]);
+  const int32_t hi1 = kb + 2 <= a.n_blocks ? __builtin_amdgcn_readfirstlane(a.col_ptr[kb + 2]) : lo1;
+  const auto named = lds_cast<uint32_t>(lds_all + T::kNamedAt);  // by the first list, by the second
+  {
+    const int32_t words = (a.n_blocks + 31) >> 5;
+    for (int32_t i = threadIdx.x; i < words; i += 512) named[i] = named[T::kNamedWords + i] = 0u;
+    __syncthreads();
+    for (int32_t i = threadIdx.x; i < hi1 - lo0; i += 512) {
+      const int32_t e = a.row_idx[lo0 + i];
+      __hip_atomic_fetch_or(&named[(i < lo1 - lo0 ? 0 : T::kNamedWords) + (e >> 5)], 1u << (e & 31), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+    __syncthreads();
+    // A stage of one list's entry alone has half the MFMAs to a barrier (1.15 of the time that the pairs of waves for one block take for it, a common
+    // one 0.86 to 0.97).
+    int32_t common = 0;
+    for (int32_t i = lane; i < words; i += 64) common += __builtin_popcount(named[i] & named[T::kNamedWords + i]);
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) common += __shfl_xor(common, off);
+    if (20 * __builtin_amdgcn_readfirstlane(common) < 7 * (hi1 - lo0)) return false;
+  }
+  // A walk over the entries of list `w` that the other list names too (shared) or does not.
+  int32_t entry = 0;  // this lane's of 64
+  uint64_t left = 0;  // which of them are to be visited
+  int32_t chunk = 0, w = 0;
+  bool shared = true;
+  auto take = [&]() __attribute__((always_inline)) -> int32_t {  // the next block, -1: none
+    const int32_t list = w ? lo1 : lo0, size = w ? hi1 - lo1 : lo1 - lo0;
+    while (left == 0) {
+      if (chunk >= size) return -1;
+      const int i = chunk + lane_again();
+      entry = i < size ? a.row_idx[list + i] : 0;
+      const bool in = named[(w ^ 1) * T::kNamedWords + (entry >> 5)] >> (entry & 31) & 1u;
+      left = __builtin_amdgcn_ballot_w64(i < size && in == shared);
+      chunk += 64;
+    }
+    const int i = __builtin_ctzll(left);
+    left &= left - 1;
+    return __builtin_amdgcn_readlane(entry, i);
+  };
+
+  bf16x8 kv[2][T::kSteps];  // K (first wave) or V rows of this lane's keys: B operands of S = Q K^T or dP = dO V^T
+  {
+    const TensorArg& src = second ? a.v : a.k;
+#pragma unroll
+    for (int set = 0; set < 2; ++set) {
+      const int32_t key_row = (kb + set) * T::kBlk + pair * 32 + lq;
+      const bool key_ok = key_row < a.N;
+      const __bf16* row = (const __bf16*)src.ptr + (int64_t)b * src.sb + (int64_t)h * src.sh + (int64_t)(key_ok ? key_row : a.N - 1) * src.sn + 8 * g;
+#pragma unroll
+      for (int t = 0; t < T::kSteps; ++t) {
+        u32x4 raw = *(const u32x4*)(row + 16 * t);
+        if (!key_ok) raw = u32x4{0u, 0u, 0u, 0u};
+        kv[set][t] = __builtin_bit_cast(bf16x8, raw);
+      }
+    }
+  }
+  f32x16 acc[2][T::kDTiles];  // dV^T or dK^T: column = this lane's key, rows = d
+#pragma unroll
+  for (int set = 0; set < 2; ++set)
+#pragma unroll
+    for (int i = 0; i < T::kDTiles; ++i)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[set][i][e] = 0.f;
+
+  // A wave copies four rows of Q and of dO, waves 0 and 1 the row statistics as well.
+  const uint32_t qoff = Rows::source_bytes(lane, a.q.sn), goff = Rows::source_bytes(lane, a.dout.sn);
+  int32_t ring = 0, parity = 0;  // the buffer of three (of Q, dO and the statistics) and of two (of P) that the current stage reads
+  auto ring_after = [](int32_t r) { return r == 2 ? 0 : r + 1; };
+  auto issue_stage = [&](int32_t q0, int32_t to) __attribute__((always_inline)) {  // at once, rows past N-1 clamped to N-1
+    const int lane = lane_again();
+    int32_t r = q0 + wave * 4 + Rows::source_row(lane);
+    r = r < a.N ? r : a.N - 1;
+    const uint32_t dst = __builtin_amdgcn_readfirstlane(lds_base + to * T::kTileBytes + wave * Rows::kFourRows);
+    copy16_to_lds(qp + (int64_t)r * a.q.sn + Rows::source_column(lane), dst);
+    copy16_to_lds(gp + (int64_t)r * a.dout.sn + Rows::source_column(lane), dst + T::kGradAt);
+    if (wave < 2) {
+      int32_t s = q0 + (lane & 31);
+      s = s < a.N ? s : a.N - 1;
+      copy4_to_lds(statp + s, __builtin_amdgcn_readfirstlane(lds_base + T::kStatAt + to * T::kStatBytes + wave * 256));
+    }
+  };
+  int32_t next_row = 0;     // of the next stage, or any row
+  uint64_t copy_lanes = 0;  // all: its copies are spread over this stage's MFMAs
+  uint32_t copy_at = 0, stat_copy_at = 0;
+  auto spread_copy = [&](int j) __attribute__((always_inline)) {
+    if (j == 0) copy16_to_lds_sv_masked(qp + (int64_t)(next_row + wave * 4) * a.q.sn, qoff, copy_at, copy_lanes);
+    if (j == 2) copy16_to_lds_sv_masked(gp + (int64_t)(next_row + wave * 4) * a.dout.sn, goff, copy_at + T::kGradAt, copy_lanes);
+    if (j == 4) copy4_to_lds_sv_masked(statp + next_row, (uint32_t)(lane_again() & 31) * 4u, stat_copy_at, wave < 2 ? copy_lanes : 0ull);
+  };
+  const uint32_t rows_at = lds_base + Rows::row_at(lane), columns_at = lds_base + Rows::column_at(lane);
+  auto p_at = [&](int32_t p) __attribute__((always_inline)) -> uint32_t {
+    return lds_base + T::kPAt + (p * T::kPairs + pair) * T::kPBytes + (uint32_t)lane_again() * 16u;
+  };
+  auto read_rows = [&](uint32_t at, int t) __attribute__((always_inline)) -> bf16x8 { return *lds_pointer<const bf16x8>(at + Rows::row_step(0, t)); };
+  auto read_columns = [&](uint32_t at, int j) __attribute__((always_inline)) -> bf16x8 {  // j = 4 * 16-row step + d tile
+    const s16x4 x0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16(lds_pointer<s16x4>(at + Rows::column_step(j / 4, j % 4)));
+    const s16x4 x1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16(lds_pointer<s16x4>(at + Rows::column_step(j / 4, j % 4) + Rows::kEightRows));
+    const u32x2 lo = __builtin_bit_cast(u32x2, x0), hi = __builtin_bit_cast(u32x2, x1);
+    return as_bf16x8(lo[0], lo[1], hi[0], hi[1]);
+  };
+  constexpr int kAhead = 2;  // LDS fragments are read this many MFMAs (of one set) before their use; the fences keep the written order
+  const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+
+  // The first product of a stage, S or dP, for kSets sets of keys; the first fragments of the second product are read behind it.
+  auto first_product = [&](auto& s, uint32_t rows, bool copies, auto sets_c) __attribute__((always_inline)) {
+    constexpr int kSets = decltype(sets_c)::value;  // a bit each
+    bf16x8 f[T::kSteps];
+#pragma unroll
+    for (int t = 0; t < kAhead; ++t) f[t] = read_rows(rows, t);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int t = 0; t < T::kSteps; ++t) {
+      if (t + kAhead < T::kSteps) f[t + kAhead] = read_rows(rows, t + kAhead);
+#pragma unroll
+      for (int set = 0; set < 2; ++set) {
+        if (kSets >> set & 1) s[set] = mfma32(f[t], kv[set][t], t == 0 ? zero : s[set]);
+        if (set == 0 && copies) spread_copy(t);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  // The second product, whose B operands come from elements(set, pair of elements): those of the first 16 rows before it, the others between its MFMAs.
+  auto second_product = [&](uint32_t columns, auto sets_c, auto&& elements, uint32_t (&x)[2][8]) __attribute__((always_inline)) {
+    constexpr int kSets = decltype(sets_c)::value;  // a bit each
+    bf16x8 f[8];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+#pragma unroll
+      for (int set = 0; set < 2; ++set)
+        if (kSets >> set & 1) elements(set, k);
+      if (k >= 2) f[k - 2] = read_columns(columns, k - 2);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      if (j + kAhead < 8) f[j + kAhead] = read_columns(columns, j + kAhead);
+      const int t2 = j / 4, dt = j % 4;
+#pragma unroll
+      for (int set = 0; set < 2; ++set) {
+        if (!(kSets >> set & 1)) continue;
+        acc[set][dt] = mfma32(f[j], as_bf16x8(x[set][4 * t2], x[set][4 * t2 + 1], x[set][4 * t2 + 2], x[set][4 * t2 + 3]), acc[set][dt]);
+        if (j < 4) elements(set, 4 + j);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  // LSE (which = 0) or delta of the stage: element e is this value in lane e of this lane's row of 16.
+  auto stat = [&](int which, int32_t r) __attribute__((always_inline)) {
+    const int l = lane_again();
+    return *lds_pointer<const float>(lds_base + T::kStatAt + r * T::kStatBytes + which * 256 + (8 * (l >> 2 & 3) + 4 * (l >> 5) + (l & 3)) * 4);
+  };
+
+  // Stage with rows from q0 on in buffer `r`, P in buffer `p`.
+  auto do_first = [&](int32_t q0, int32_t r, int32_t p, auto sets_c) __attribute__((always_inline)) {
+    constexpr int kSets = decltype(sets_c)::value;  // a bit each
+    f32x16 s[2];
+    const float lse = stat(0, r) * kLog2e;
+    first_product(s, rows_at + r * T::kTileBytes, true, sets_c);
+    if (q0 + T::kStage > a.N) {  // query rows past N: P = exp(-inf) = 0
+      const uint32_t hidden = elements_from(a.N - q0 - 4 * (lane_again() >> 5));
+      float lowest;
+      asm volatile("v_mov_b32 %0, 0xff800000" : "=v"(lowest));
+#pragma unroll
+      for (int e = 0; e < 16; ++e)
+        if ((hidden >> e) & 1u) {
+#pragma unroll
+          for (int set = 0; set < 2; ++set)
+            if (kSets >> set & 1) s[set][e] = lowest;
+        }
+    }
+    const uint32_t to = p_at(p);
+    uint32_t pp[2][8];
+    f32x4 p4[2];
+    second_product(columns_at + T::kGradAt + r * T::kTileBytes, sets_c, [&](int set, int k) __attribute__((always_inline)) {
+      const int e = 2 * k;
+      const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[set][e], c, -row_lane(lse, e)));
+      const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[set][e + 1], c, -row_lane(lse, e + 1)));
+      p4[set][e & 3] = p0;
+      p4[set][(e & 3) + 1] = p1;
+      pp[set][k] = pack_bf16(p0, p1);
+      asm volatile("" : "+v"(pp[set][k]));  // stays between its MFMAs
+      if (k & 1) *lds_pointer<f32x4>(to + (set * 4 + k / 2) * 1024) = p4[set];
+    }, pp);
+  };
+  auto do_second = [&](int32_t r, int32_t p, bool copies, auto sets_c) __attribute__((always_inline)) {
+    constexpr int kSets = decltype(sets_c)::value;
+    f32x16 dp[2];
+    const float delta = stat(1, r);
+    first_product(dp, rows_at + T::kGradAt + r * T::kTileBytes, copies, sets_c);
+    const uint32_t from = p_at(p);
+    uint32_t ds[2][8];
+    f32x4 p4[2][2];  // of the current four elements and the next
+    auto read_p = [&](int set, int four) __attribute__((always_inline)) {
+      p4[set][four & 1] = *lds_pointer<const f32x4>(from + (set * 4 + four) * 1024);
+    };
+#pragma unroll
+    for (int set = 0; set < 2; ++set)
+      if (kSets >> set & 1) read_p(set, 0);
+    second_product(columns_at + r * T::kTileBytes, sets_c, [&](int set, int k) __attribute__((always_inline)) {
+      const int e = 2 * k;
+      if (k % 2 == 0 && k / 2 + 1 < 4) read_p(set, k / 2 + 1);
+      const f32x4 p = p4[set][k / 2 & 1];
+      ds[set][k] = pack_bf16(p[e & 3] * (dp[set][e] - row_lane(delta, e)), p[(e & 3) + 1] * (dp[set][e + 1] - row_lane(delta, e + 1)));
+      asm volatile("" : "+v"(ds[set][k]));
+    }, ds);
+  };
+
+  // One pass over the lists, of either kind of wave: loops of their own, which branch nowhere that the accumulators pass.
+  auto walk = [&](auto second_c, auto sets_c) __attribute__((always_inline)) {
+    constexpr bool kSecond = decltype(second_c)::value;
+    left = 0;
+    chunk = 0;
+    int32_t block = take();
+    if (block < 0) return;
+    int32_t q0 = block * T::kBlk, q0_next = 0, last_ring = 0, to = 0, u = 0;
+    bool has_next = true;
+    issue_stage(q0, ring);
+    auto open_stage = [&]() __attribute__((always_inline)) {
+      q0_next = q0 + T::kStage;
+      if (u == T::kSubs - 1) {
+        block = take();
+        has_next = block >= 0;
+        q0_next = block * T::kBlk;
+      }
+      to = ring_after(ring);
+      wait_all_copies();
+      __syncthreads();  // this stage's copies have landed for every wave, the last one's P is written and the one before it is consumed
+      const bool spread = has_next && q0_next + T::kStage <= a.N;
+      if (has_next && !spread) issue_stage(q0_next, to);
+      const uint32_t on = __builtin_amdgcn_readfirstlane(spread ? ~0u : 0u);
+      copy_lanes = ((uint64_t)on << 32) | on;
+      next_row = spread ? q0_next : q0;
+      copy_at = __builtin_amdgcn_readfirstlane(lds_base + to * T::kTileBytes + wave * Rows::kFourRows);
+      stat_copy_at = __builtin_amdgcn_readfirstlane(lds_base + T::kStatAt + to * T::kStatBytes + (wave & 1) * 256);
+    };
+    auto close_stage = [&]() __attribute__((always_inline)) {
+      last_ring = ring;
+      ring = to;
+      parity ^= 1;
+      q0 = q0_next;
+      u = (u + 1) & (T::kSubs - 1);
+    };
+    if constexpr (kSecond) {  // nothing to do yet but its copies
+      open_stage();
+#pragma unroll
+      for (int j = 0; j < 8; ++j) spread_copy(j);
+      close_stage();
+    }
+    while (has_next) {
+      open_stage();
+      if constexpr (kSecond) do_second(last_ring, parity ^ 1, true, sets_c);
+      else do_first(q0, ring, parity, sets_c);
+      close_stage();
+    }
+    __syncthreads();
+    if constexpr (kSecond) do_second(last_ring, parity ^ 1, false, sets_c);
+  };
+  auto run = [&](auto second_c) __attribute__((always_inline)) {
+    constexpr bool kSecond = decltype(second_c)::value;
+    walk(second_c, std::integral_constant<int, 3>{});
+    shared = false;
+    auto finish = [&](auto set_c) __attribute__((always_inline)) {
+      constexpr int set = decltype(set_c)::value;
+      w = set;
+      walk(second_c, std::integral_constant<int, 1 << set>{});
+      const int lane2 = lane_again(), g2 = lane2 >> 5;
+      const int32_t key_row = (kb + set) * T::kBlk + pair * 32 + (lane2 & 31);
+      if (key_row < a.N) {  // dK = scale * dK^T, dV
+        const TensorArg& to_tensor = kSecond ? a.dk : a.dv;
+        const float f = kSecond ? a.scale : 1.f;
+        __bf16* dst = (__bf16*)to_tensor.ptr + (int64_t)b * to_tensor.sb + (int64_t)h * to_tensor.sh + (int64_t)key_row * to_tensor.sn + 4 * g2;
+#pragma unroll
+        for (int dt = 0; dt < T::kDTiles; ++dt)
+#pragma unroll
+          for (int e4 = 0; e4 < 4; ++e4)
+            *(u32x2*)(dst + 32 * dt + 8 * e4) = u32x2{pack_bf16(acc[set][dt][4 * e4] * f, acc[set][dt][4 * e4 + 1] * f),
+                                                      pack_bf16(acc[set][dt][4 * e4 + 2] * f, acc[set][dt][4 * e4 + 3] * f)};
+      }
+    };
+    finish(std::integral_constant<int, 0>{});
+    finish(std::integral_constant<int, 1>{});
+  };
+  if (second) run(std::true_type{});
+  else run(std::false_type{});
+  return true;
+}
+
+__global__ void __launch_bounds__(512, 2) radial_bwd_two_keys_kernel(const BwdArgs a, const TwoMap m) {
+  TwoItem item;
+  if (!two_item(a.work_t, m, blockIdx.x, item)) return;
+  int32_t kb = 2 * item.pair + item.block, n = 1;
+  if (item.form == TwoItem::kPair) {
+    if (two_keys_body(own_args<BwdArgs>(), item.bh, kb, m.c)) return;
+    n = kb + 1 < a.n_blocks ? 2 : 1;
+  }
+#pragma unroll 1
+  for (; n > 0; --n, ++kb) {
+    if (item.form == TwoItem::kPair) __syncthreads();  // the LDS is consumed
+    pairs_body<128, 128, false>(own_args<BwdArgs>(), item.bh, kb);
+  }
+}
+
 // kBeside: in a launch with whole blocks of one group at head dimension 64, whose LDS two groups share on half-size stages.
 template <int D, int BLK, int S, int R, bool kBeside = false>
 struct DqTile {
@@ -1135,14 +1482,14 @@ __global__ void __launch_bounds__(2 * BLK / R * S, 2) radial_bwd_both_kernel(con
 
 template <int D, int BLK, bool kExact>
 __global__ void __launch_bounds__(4 * BLK, 2) radial_bwd_dkdv_pairs_kernel(const BwdArgs a) {
-  pairs_body<D, BLK, kExact>(a, blockIdx.x);
+  pairs_item<D, BLK, kExact>(a, blockIdx.x);
 }
 // The same at head dimension 128, blocks of 128: dK/dV in pairs of waves, dQ by two groups; kHalves: the last a.work.halved query blocks in
 // two halves, of 64 rows and four groups each.
 template <int D, int BLK, bool kExact, bool kHalves>
 __global__ void __launch_bounds__(4 * BLK, 2) radial_bwd_both_pairs_kernel(const BwdArgs a, uint32_t n_key) {
   if (blockIdx.x < n_key) {
-    pairs_body<D, BLK, kExact>(a, blockIdx.x);
+    pairs_item<D, BLK, kExact>(a, blockIdx.x);
     return;
   }
   if constexpr (kHalves) dq_item_or_half<D, BLK, kExact, 2, 1>(a, blockIdx.x - n_key, gridDim.x - n_key);
@@ -1169,8 +1516,20 @@ int launch_dkdv(BwdArgs a, hipStream_t stream) {
   return RADIAL_OK;
 }
 
+int launch_dkdv_two(const BwdArgs& a, hipStream_t stream) {
+  const TwoMap m = make_two_map(a.work_t, a.pair_order_t, a.scale, TwoWalk::kKeyGrad);
+  constexpr int kBytes = TwoKeysTile::kLdsBytes > PairTile<128, 128>::kLdsBytes ? TwoKeysTile::kLdsBytes : PairTile<128, 128>::kLdsBytes;
+  static DeviceOnce configured;
+  if (int rc = allow_dynamic_lds(configured, (const void*)radial_bwd_two_keys_kernel, kBytes)) return rc;
+  radial_bwd_two_keys_kernel<<<dim3(m.n_two + 2 * m.n_one), dim3(512), kBytes, stream>>>(a, m);
+  return RADIAL_OK;
+}
+
 template <int BLK, bool kExact>
 int launch_dkdv_pairs(const BwdArgs& a, hipStream_t stream) {
+  // Two key blocks at a time above the sizes of a common launch.
+  if constexpr (BLK == 128 && !kExact)
+    if (a.n_blocks <= kMaxOrdered && work_items(a.work_t, a.n_blocks) > 6 * kOneRound) return launch_dkdv_two(a, stream);
   using T = PairTile<128, BLK>;
   const auto kernel = radial_bwd_dkdv_pairs_kernel<128, BLK, kExact>;
   static DeviceOnce configured;

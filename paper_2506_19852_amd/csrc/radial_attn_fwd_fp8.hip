@@ -442,7 +442,7 @@ __global__ void __launch_bounds__(2 * BLK, 2) radial_fwd_fp8_two_kernel(const Fp
   if (!two_item(a.work, m, blockIdx.x, item)) return;
   const int32_t qb = 2 * item.pair + item.block;
   if (item.form == TwoItem::kPair) fwd::two_body<false>(a, item.bh, qb, m.c, 0, fwd::static_lds<Fp8Key, kBytes>());
-  else fp8_body<1, 1, kBytes>(fwd::own_args<Fp8FwdArgs>(), item.bh, qb, 0);
+  else fp8_body<1, 1, kBytes>(own_args<Fp8FwdArgs>(), item.bh, qb, 0);
 }
 
 }  // namespace
@@ -481,7 +481,7 @@ int launch_fwd_fp8(const Fp8FwdArgs& a, hipStream_t stream) {
   const int64_t items = work_items(a.work, a.n_blocks);
   if (items == 0) return RADIAL_OK;
   if (takes_pairs(a.work)) {
-    const TwoMap m = make_two_map(a.work, a.pair_order, a.scale, true);
+    const TwoMap m = make_two_map(a.work, a.pair_order, a.scale, TwoWalk::kCodes);
     radial_fwd_fp8_two_kernel<<<dim3(m.n_two + 2 * m.n_one), dim3(2 * BLK), 0, stream>>>(a, m);
     RADIAL_HIP_TRY(hipGetLastError());
     return RADIAL_OK;

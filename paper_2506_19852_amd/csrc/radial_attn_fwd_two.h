@@ -41,22 +41,6 @@ struct TwoTile {
   static_assert(2 * kLdsBytes <= 160 * 1024, "two workgroups per compute unit");
 };
 
-// The lane's number again, so that nothing derived from it is held in a register meanwhile.
-__device__ __forceinline__ int lane_again() {
-  int lane;
-  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(lane));
-  return lane;
-}
-
-// The kernel's first parameter, asked for here and not before.
-template <class Args>
-__device__ __forceinline__ const Args& own_args() {
-  using Own = const Args __attribute__((address_space(4)));
-  Own* args = (Own*)__builtin_amdgcn_kernarg_segment_ptr();
-  asm volatile("" : "+s"(args));  // not known to be the same memory
-  return *(const Args*)args;
-}
-
 // Query blocks qb and qb + 1 (which may not exist).
 template <bool kTrace, class Args>
 __device__ __forceinline__ void two_body(const Args& a, int32_t bh, int32_t qb, float c, int64_t record, char* lds_all) {
@@ -501,7 +485,7 @@ __global__ void __launch_bounds__(256, 2) radial_fwd_two_kernel(const FwdArgs a,
 
 template <bool kTrace>
 int launch_two(const FwdArgs& a, hipStream_t stream) {
-  const TwoMap m = make_two_map(a.work, a.pair_order, a.scale, false);
+  const TwoMap m = make_two_map(a.work, a.pair_order, a.scale, TwoWalk::kForward);
   radial_fwd_two_kernel<kTrace><<<dim3(m.n_two + 2 * m.n_one + 4 * m.n_half), dim3(256), 0, stream>>>(a, m);
   RADIAL_HIP_TRY(hipGetLastError());
   return RADIAL_OK;

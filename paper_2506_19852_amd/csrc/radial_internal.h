@@ -34,6 +34,7 @@ struct radial_mask {
   int32_t* d_order = nullptr;    // [n_blocks]
   int32_t* d_order_t = nullptr;  // [n_blocks]
   int32_t* d_pair_order = nullptr;  // [(n_blocks + 1) / 2]  pairs of query blocks 2p, 2p + 1 by falling length of both lists
+  int32_t* d_pair_order_t = nullptr;  // the same of key blocks
   int32_t max_slice = 0;         // longest slice, in blocks (host copy, sizes the grid)
   int32_t max_slice_t = 0;
   int32_t longest = 0, longest_t = 0;  // entries of the longest list (n_blocks, a bound, where there is no order)
@@ -204,7 +205,12 @@ constexpr uint32_t kTwoRound = 512;  // workgroups that the chip holds
 // above them up to 384; with slices 128 pairs.  Single blocks / the best of 0, 64 .. 256 pairs taken singly / this rule, us (pairs in order of length, left over above rounds): 550 (38)
 // 763 / 706 / 703, 600 (88) 769 / 727 / 721, 660 (148) 930 / 891 / 891, 700 (188) 990 / 932 / 932, 740 (228) 1146 / 1073 / 1076, 800 (288) 1638 / 1387 / 1390, 832 (320) 1762 / 1530 /
 // 1535, 900 (388) 1645 / 1487 / 1471, 1024 (0) 2265 / 2115 / 2098, 1395 (371) 8190 / 7353 / 7297; none singly: 550 800, 800 1525, 1395 8010.
-inline TwoMap make_two_map(const WorkMap& w, const int32_t* pair_order, float scale, bool codes) {
+//
+// dK/dV, a workgroup to a compute unit: what is left over above rounds of 256 goes singly up to 128 pairs, 64 up to 208, none above.  Single blocks / 0, 64, 128 pairs
+// singly, us, training steps: 800 pairs (32 left over) of lists of 20 1229 / 1238, 1188, 1186, radial 6127 / 6210, 5998, 6002, 4370 / 4356, 4212, 4221; 1212 (188) 10750 / 10640,
+// 10656, 10636, with text 15370 / 15820, 15490, 15500; 1000 (232) 13240 / 12625, 12780, 12788; 40 heads x 126 360 tokens 480 / 466, 467, 467 ms.
+enum class TwoWalk { kForward, kCodes, kKeyGrad };
+inline TwoMap make_two_map(const WorkMap& w, const int32_t* pair_order, float scale, TwoWalk walk) {
   TwoMap m;
   m.c = scale * 1.4426950408889634f;
   m.pairs = w;
@@ -215,14 +221,20 @@ inline TwoMap make_two_map(const WorkMap& w, const int32_t* pair_order, float sc
   const uint32_t last = (uint32_t)w.sliced % 8u * most;                                       // of the heads that are no full eight to an XCD
   m.n_sliced = 8u * ((uint32_t)w.sliced / 8u * per_head + (last < per_head ? last : per_head));
   const uint32_t ordered = (uint32_t)w.ordered * per_head;
-  uint32_t rest = ordered % kTwoRound;
-  if (codes) {
-    if (w.sliced > 0) rest = ordered < 128u ? ordered : 128u;
-    else if (rest > 192u) rest = rest <= 256u || rest > 384u ? 0u : rest < 320u ? 64u : rest - 256u;
-  } else if (w.sliced > 0 && rest < kTwoRound / 2 && ordered >= kTwoRound) {
-    rest += kTwoRound;
+  uint32_t rest;  // pairs at the end that are not taken by one workgroup
+  if (walk == TwoWalk::kForward) {
+    rest = ordered % kTwoRound;
+    if (w.sliced > 0 && rest < kTwoRound / 2 && ordered >= kTwoRound) rest += kTwoRound;
+  } else if (w.sliced > 0) {
+    rest = ordered < 128u ? ordered : 128u;
+  } else if (walk == TwoWalk::kCodes) {
+    rest = ordered % kTwoRound;
+    if (rest > 192u) rest = rest <= 256u || rest > 384u ? 0u : rest < 320u ? 64u : rest - 256u;
+  } else {
+    rest = ordered % (kTwoRound / 2);
+    if (rest > 128u) rest = rest <= 208u ? 64u : 0u;
   }
-  m.n_half = codes ? 0u : rest < 64u ? rest : 64u;
+  m.n_half = walk != TwoWalk::kForward ? 0u : rest < 64u ? rest : 64u;
   m.n_one = rest - m.n_half;
   m.n_two = m.n_sliced + ordered - rest;
   return m;
@@ -531,6 +543,7 @@ struct BwdArgs {
   int32_t B, H, N, n_blocks;
   float scale;
   TokenRule rule;
+  const int32_t* pair_order_t;  // pairs of key blocks by falling length; null only if work_t.ordered == 0
 };
 
 int launch_bwd(int D, int block, const BwdArgs& a, hipStream_t stream);

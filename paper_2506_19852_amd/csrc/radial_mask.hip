@@ -366,8 +366,8 @@ __global__ void __launch_bounds__(kThreads) transpose_fill_kernel(const int32_t*
 
 __global__ void __launch_bounds__(kThreads) transpose_lists_kernel(const int32_t* row_ptr, const int32_t* col_idx, int32_t nb,
                                                                   const int32_t* counts, int32_t* col_ptr, int32_t* order, Meta meta,
-                                                                  int32_t* row_idx) {
-  const int32_t start = place_list(counts, nb, blockIdx.x, col_ptr, order, nullptr, meta, true);
+                                                                  int32_t* row_idx, int32_t* pair_order) {
+  const int32_t start = place_list(counts, nb, blockIdx.x, col_ptr, order, pair_order, meta, true);
   write_column(row_ptr, col_idx, nb, blockIdx.x, start, row_idx);
 }
 
@@ -424,7 +424,7 @@ int check_common(int64_t n_tokens, int32_t block, uint32_t flags) {
 }
 
 // Device storage of a mask is three allocations: `meta` (two 64-bit totals and the two launch
-// partitions), `ptrs` (row_ptr, its order and that of its pairs and, with the transposed lists, col_ptr and its order) and `idx` (col_idx and
+// partitions), `ptrs` (row_ptr, its order and that of its pairs and, with the transposed lists, the same of col_ptr) and `idx` (col_idx and
 // row_idx).  The views d_row_ptr, d_col_ptr, ... point into them at 256-byte aligned offsets.
 int launch_partition(const int32_t* ptr, int32_t nb, int32_t* order, int32_t* pair_order, const Meta& meta, bool columns, hipStream_t st) {
   const int32_t per = kThreads / 64;
@@ -499,9 +499,10 @@ int alloc_meta_and_ptrs(radial_mask* m) {
   const int64_t no = m->n_blocks <= kMaxOrdered ? aligned_ints(m->n_blocks) : 0;
   const int64_t lists = (m->flags & RADIAL_MASK_TRANSPOSE) ? 2 : 1;
   const int64_t pairs = no ? aligned_ints((m->n_blocks + 1) / 2) : 0;
-  RADIAL_HIP_TRY(hipMalloc(&m->d_ptrs, sizeof(int32_t) * ((np + no) * lists + no + pairs)));
+  RADIAL_HIP_TRY(hipMalloc(&m->d_ptrs, sizeof(int32_t) * ((np + no + pairs) * lists + no)));
   if (no) m->d_counts = m->d_ptrs + (np + no) * lists;
   if (no) m->d_pair_order = m->d_counts + no;
+  if (no && lists == 2) m->d_pair_order_t = m->d_pair_order + pairs;
   m->d_row_ptr = m->d_ptrs;
   if (no) m->d_order = m->d_ptrs + np;
   m->d_slice = m->d_meta + kSlice;
@@ -535,7 +536,7 @@ int finish_mask(radial_mask* m, HostMeta& shared, bool rows_placed, hipStream_t 
   if ((m->flags & RADIAL_MASK_TRANSPOSE) && m->d_counts) {
     transpose_count_kernel<<<nb, kThreads, 0, st>>>(m->d_row_ptr, m->d_col_idx, nb, m->d_counts);
     RADIAL_HIP_TRY(hipGetLastError());
-    transpose_lists_kernel<<<nb, kThreads, 0, st>>>(m->d_row_ptr, m->d_col_idx, nb, m->d_counts, m->d_col_ptr, m->d_order_t, meta, m->d_row_idx);
+    transpose_lists_kernel<<<nb, kThreads, 0, st>>>(m->d_row_ptr, m->d_col_idx, nb, m->d_counts, m->d_col_ptr, m->d_order_t, meta, m->d_row_idx, m->d_pair_order_t);
     RADIAL_HIP_TRY(hipGetLastError());
   } else if (m->flags & RADIAL_MASK_TRANSPOSE) {
     transpose_count_kernel<<<nb, kThreads, 0, st>>>(m->d_row_ptr, m->d_col_idx, nb, m->d_col_ptr);
@@ -544,7 +545,7 @@ int finish_mask(radial_mask* m, HostMeta& shared, bool rows_placed, hipStream_t 
     RADIAL_HIP_TRY(hipGetLastError());
     transpose_fill_kernel<<<nb, kThreads, 0, st>>>(m->d_row_ptr, m->d_col_idx, nb, m->d_col_ptr, m->d_row_idx);
     RADIAL_HIP_TRY(hipGetLastError());
-    if (int rc = launch_partition(m->d_col_ptr, nb, m->d_order_t, nullptr, meta, true, st)) return rc;
+    if (int rc = launch_partition(m->d_col_ptr, nb, m->d_order_t, m->d_pair_order_t, meta, true, st)) return rc;
   }
   hipError_t e = hipSuccess;
   if (!shared.host()) e = hipMemcpyAsync(h_meta, m->d_meta, sizeof h_meta, hipMemcpyDeviceToHost, st);

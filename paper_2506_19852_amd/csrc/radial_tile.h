@@ -52,6 +52,22 @@ __device__ __forceinline__ bf16x8 as_bf16x8(uint32_t a, uint32_t b, uint32_t c, 
   return __builtin_bit_cast(bf16x8, raw);
 }
 
+// The lane's number again, so that nothing derived from it is held in a register meanwhile.
+__device__ __forceinline__ int lane_again() {
+  int lane;
+  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(lane));
+  return lane;
+}
+
+// The kernel's first parameter, asked for here and not before.
+template <class Args>
+__device__ __forceinline__ const Args& own_args() {
+  using Own = const Args __attribute__((address_space(4)));
+  Own* args = (Own*)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(args));  // not known to be the same memory
+  return *(const Args*)args;
+}
+
 // One 1 KiB HBM -> LDS copy: lane i's 16 bytes land at LDS address lds_addr + 16*i.  Issued
 // from assembly so that the compiler does not order later LDS reads after it; the caller
 // waits with wait_all_copies() and a barrier before anyone reads the destination.

@@ -1,4 +1,4 @@
-"""The forwards over pairs of query blocks hold 240 to 256 registers a lane: neither registers nor scalars may be spilled (36 bytes of private
+"""The kernels over pairs of query or key blocks hold 240 to 256 registers a lane: neither registers nor scalars may be spilled (36 bytes of private
 memory in the loop over the lists cost a tenth of the time)."""
 import os
 import re
@@ -11,7 +11,7 @@ from paper_2506_19852_amd import build as hip_build
 from test_kernel_asm import instructions, kernels
 
 
-@pytest.mark.parametrize("source, kernel", [("radial_attn_fwd.hip", "radial_fwd_two_kernel"), ("radial_attn_fwd_fp8.hip", "radial_fwd_fp8_two_kernel")])
+@pytest.mark.parametrize("source, kernel", [("radial_attn_fwd.hip", "radial_fwd_two_kernel"), ("radial_attn_fwd_fp8.hip", "radial_fwd_fp8_two_kernel"), ("radial_attn_bwd.hip", "radial_bwd_two_keys_kernel")])
 def test_nothing_is_spilled(source, kernel, tmp_path):
     if not os.path.exists(hip_build.HIPCC) and shutil.which(hip_build.HIPCC) is None:
         pytest.skip("hipcc not available")

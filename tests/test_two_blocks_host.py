@@ -1,4 +1,4 @@
-"""Every query block is taken once by a forward over pairs of query blocks: whole pairs, single blocks and halves of blocks, by slices and
+"""Every block is taken once by a launch over pairs of query (or key) blocks: whole pairs, single blocks and halves of blocks, by slices and
 by length, for even and odd numbers of blocks and slices of any length, and every workgroup has a trace record of its own."""
 import os
 import random
@@ -23,7 +23,7 @@ def launches(tmp_path_factory):
     assert r.returncode == 0, r.stdout[-3000:]
 
     def run(cases):
-        text = "\n".join(" ".join(map(str, (*c[:4], int(len(c) > 5), *c[4]))) for c in cases)
+        text = "\n".join(" ".join(map(str, (*c[:4], c[5] if len(c) > 5 else 0, *c[4]))) for c in cases)
         r = subprocess.run([str(exe)], input=text, stdout=subprocess.PIPE, text=True, timeout=120)
         assert r.returncode == 0
         parts = [p.strip().split("\n") for p in r.stdout.split("end\n") if p.strip()]
@@ -40,7 +40,7 @@ def uneven_slices(nb, seed):
     return [0, *sorted(rng.randint(0, nb) for _ in range(7)), nb]
 
 
-CASES = [(nb, sliced, ordered, 100, slices(nb), *codes) for codes in ((), (True,)) for nb in (1, 2, 3, 7, 8, 9, 15, 16, 17, 64, 101, 110, 929)
+CASES = [(nb, sliced, ordered, 100, slices(nb), *codes) for codes in ((), (1,), (2,)) for nb in (1, 2, 3, 7, 8, 9, 15, 16, 17, 64, 101, 110, 929)
          for sliced, ordered in ((0, 10), (1, 8), (8, 0), (9, 8), (17, 2), (32, 8))
          for slices in (even_slices, lambda n: uneven_slices(n, 3 * n + 1))]
 
@@ -78,6 +78,14 @@ def test_whole_rounds_of_pairs_and_halves_at_the_end(launches):
 def test_single_blocks_with_8_bit_scores(launches):
     """Left over above whole rounds of 512 pairs, in order of length: all up to 192 pairs, none to 256, what is above 256 (at least 64) to 384, none."""
     pairs = {512: 0, 513: 1, 704: 192, 705: 0, 768: 0, 769: 64, 831: 64, 832: 64, 833: 65, 896: 128, 897: 0, 1023: 0, 1024: 0}
-    singles = [sum(1 for i in items if i[3] == 1) for _, items in launches([(2 * n, 0, 1, 93, even_slices(2 * n), True) for n in pairs])]
+    singles = [sum(1 for i in items if i[3] == 1) for _, items in launches([(2 * n, 0, 1, 93, even_slices(2 * n), 1) for n in pairs])]
     assert singles == [2 * n for n in pairs.values()]
-    assert [sum(1 for i in items if i[3]) for _, items in launches([(256, 32, 8, 160, even_slices(256), True), (16, 10, 2, 16, even_slices(16), True)])] == [256, 32]
+    assert [sum(1 for i in items if i[3]) for _, items in launches([(256, 32, 8, 160, even_slices(256), 1), (16, 10, 2, 16, even_slices(16), 1)])] == [256, 32]
+
+
+def test_single_key_blocks(launches):
+    """Left over above whole rounds of 256 pairs: all up to 128 pairs, 64 to 208, none; 128 with slices; never halves."""
+    pairs = {256: 0, 257: 1, 384: 128, 385: 64, 464: 64, 465: 0, 511: 0, 1024: 0}
+    items = [i for _, i in launches([(2 * n, 0, 1, 93, even_slices(2 * n), 2) for n in pairs])]
+    assert [sum(1 for i in x if i[3] == 1) for x in items] == [2 * n for n in pairs.values()] and not any(i[3] == 2 for x in items for i in x)
+    assert [sum(1 for i in x if i[3]) for _, x in launches([(256, 32, 8, 160, even_slices(256), 2), (16, 10, 2, 16, even_slices(16), 2)])] == [256, 32]
