@@ -568,8 +568,12 @@ __device__ __forceinline__ void pairs_body(const BwdArgs& a, int32_t bh, int32_t
   ListRule<kStageQ, BLK> token;
   if (kExact) token.init(a.rule, kb * BLK + pair * 32, a.N, lane);
 
-  const uint32_t qoff = Rows::source_bytes(lane, a.q.sn), goff = Rows::source_bytes(lane, a.dout.sn);  // from a copy's first row
-  const int32_t first_row = wave * T::kLoadsPerWave * 4;                                                     // of this wave's copies
+  uint32_t qoff[T::kLoadsPerWave], goff[T::kLoadsPerWave];  // byte offsets from the stage's first row
+#pragma unroll
+  for (int i = 0; i < T::kLoadsPerWave; ++i) {
+    qoff[i] = (uint32_t)(((wave * T::kLoadsPerWave + i) * 4) * (int32_t)a.q.sn) * 2u + Rows::source_bytes(lane, a.q.sn);
+    goff[i] = (uint32_t)(((wave * T::kLoadsPerWave + i) * 4) * (int32_t)a.dout.sn) * 2u + Rows::source_bytes(lane, a.dout.sn);
+  }
   // Stage buffers of stage u: Q and the row statistics go round three, dO and P round two.
   struct Bufs {
     int32_t q, grad, stat, p;  // byte offsets
@@ -580,10 +584,10 @@ __device__ __forceinline__ void pairs_body(const BwdArgs& a, int32_t bh, int32_t
   };
   // All of this wave's copies of a stage at once (first stage, ragged stages: rows past N-1 are clamped to N-1).
   auto issue_stage = [&](int32_t q0, const Bufs& to) {
-    const uint32_t qdst = lds_base + to.q + first_row / 4 * Rows::kFourRows, gdst = lds_base + to.grad + first_row / 4 * Rows::kFourRows;
+    const uint32_t qdst = lds_base + to.q + wave * T::kLoadsPerWave * Rows::kFourRows, gdst = lds_base + to.grad + wave * T::kLoadsPerWave * Rows::kFourRows;
 #pragma unroll
     for (int i = 0; i < T::kLoadsPerWave; ++i) {
-      int32_t r = q0 + first_row + 4 * i + Rows::source_row(lane);
+      int32_t r = q0 + (wave * T::kLoadsPerWave + i) * 4 + Rows::source_row(lane);
       r = r < a.N ? r : a.N - 1;
       copy16_to_lds(qp + (int64_t)r * a.q.sn + Rows::source_column(lane), qdst + i * Rows::kFourRows);
       copy16_to_lds(gp + (int64_t)r * a.dout.sn + Rows::source_column(lane), gdst + i * Rows::kFourRows);
@@ -637,7 +641,7 @@ __device__ __forceinline__ void pairs_body(const BwdArgs& a, int32_t bh, int32_t
     if (has_next && !spread) issue_stage(q0_next, to);
     const uint32_t on = __builtin_amdgcn_readfirstlane(spread ? ~0u : 0u);
     copy_lanes = ((uint64_t)on << 32) | on;
-    const int32_t q_src = (spread ? q0_next : q0) + first_row;  // any row when the copies are switched off
+    const int32_t q_src = spread ? q0_next : q0;  // any valid row when the copies are switched off
     qbase = qp + (int64_t)q_src * a.q.sn;
     gbase = gp + (int64_t)q_src * a.dout.sn;
   };
@@ -646,11 +650,13 @@ __device__ __forceinline__ void pairs_body(const BwdArgs& a, int32_t bh, int32_t
     at = to;
   };
   auto spread_copy = [&](int j) __attribute__((always_inline)) {
+    int32_t wave_at = wave;
+    asm volatile("" : "+s"(wave_at));  // worked out here, not held: scalars are what the common launches are short of
     if (j < T::kLoadsPerWave) {
-      copy16_to_lds_sv_masked(qbase + j * 4 * a.q.sn, qoff, lds_base + to.q + (first_row / 4 + j) * Rows::kFourRows, copy_lanes);
+      copy16_to_lds_sv_masked(qbase, qoff[j], lds_base + to.q + (wave_at * T::kLoadsPerWave + j) * Rows::kFourRows, copy_lanes);
     } else if (j < 2 * T::kLoadsPerWave) {
       const int i = j - T::kLoadsPerWave;
-      copy16_to_lds_sv_masked(gbase + i * 4 * a.dout.sn, goff, lds_base + to.grad + (first_row / 4 + i) * Rows::kFourRows, copy_lanes);
+      copy16_to_lds_sv_masked(gbase, goff[i], lds_base + to.grad + (wave_at * T::kLoadsPerWave + i) * Rows::kFourRows, copy_lanes);
     } else {
       copy4_to_lds_sv_masked(statp + (spread ? q0_next : q0), (uint32_t)lane * 4u, lds_base + to.stat + (wave & 1) * kStageQ * 4, wave < 2 ? copy_lanes : 0ull);
     }
