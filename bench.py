@@ -25,7 +25,7 @@ PROFILES = os.path.join(ROOT, "profiles")
 # Sources of the attention kernels: a counter summary under profiles/ names the files it depends on
 # and their digest, so that a summary taken on other kernel code is recognised whatever the speed
 # of the box it was taken on.
-FWD_KERNEL_SOURCES = ("radial_attn_fwd.hip", "radial_attn_fwd_kernel.h", "radial_tile.h", "radial_internal.h")
+FWD_KERNEL_SOURCES = ("radial_attn_fwd.hip", "radial_attn_fwd_kernel.h", "radial_attn_fwd_two.h", "radial_tile.h", "radial_internal.h")
 BWD_KERNEL_SOURCES = FWD_KERNEL_SOURCES + ("radial_attn_bwd.hip",)
 
 
@@ -521,7 +521,7 @@ def main():
         "roofline": {"bound": "mfma", "achieved": round(achieved, 2), "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
                      "frac": round(achieved / MFMA_BF16_PEAK_TFLOPS, 4), "frac_of_mfma_probe": round(achieved / probe_tflops, 4),
                      "traffic": traffic, "traffic_source": traffic_source,
-                     "kernel": "radial_fwd_kernel", "flops_per_launch": fwd_flops},
+                     "kernel": "radial_fwd*_kernel", "flops_per_launch": fwd_flops},
     }
     if quant is not None:
         result["quantize_q_and_k_ms"] = round(quant["ms"], 3)
