@@ -248,7 +248,7 @@ __device__ __forceinline__ void two_body(const Args& a, int32_t bh, int32_t qb, 
 #pragma unroll
         for (int e = 0; e < 16; ++e) o[set][i][e] *= alpha;
       m_run[set] = mx;
-      mc[set] = mx * c;
+      mc[set] = mx > -INFINITY ? mx * c : 0.f;  // a row may still have no score above -inf when another row of the wave has
     }
   };
   // Scores of keys past N - 1: `exist` of a tile's 32 do.
