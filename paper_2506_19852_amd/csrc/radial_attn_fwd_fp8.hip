@@ -480,7 +480,7 @@ int launch_fwd_fp8(const Fp8FwdArgs& a, hipStream_t stream) {
   if (work_grid_bound(a.work) > 0x7fffffffLL) return fail(RADIAL_ESHAPE, "B*H*n_blocks is too large for one launch");
   const int64_t items = work_items(a.work, a.n_blocks);
   if (items == 0) return RADIAL_OK;
-  if (takes_pairs(a.work)) {
+  if (takes_pairs(a.work, true)) {
     const TwoMap m = make_two_map(a.work, a.pair_order, a.scale, TwoWalk::kCodes);
     radial_fwd_fp8_two_kernel<<<dim3(m.n_two + 2 * m.n_one), dim3(2 * BLK), 0, stream>>>(a, m);
     RADIAL_HIP_TRY(hipGetLastError());

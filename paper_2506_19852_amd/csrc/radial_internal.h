@@ -239,13 +239,27 @@ inline TwoMap make_two_map(const WorkMap& w, const int32_t* pair_order, float sc
   m.n_two = m.n_sliced + ordered - rest;
   return m;
 }
-// Wherever heads are taken by slices: there are thousands of lists.  By length alone from a whole round of pairs on, if the lists are long enough
-// to make up for the pair's longer beginning.  Single blocks / pairs, us: 10 heads x 104 blocks 777 / 712, 10 x 120 898 / 869, 8 x 200 1788 / 1716, 10 x 180
-// 1790 / 1778, 14 x 88 759 / 755, 8 x 256 2610 / 2535, 5 x 500 4925 / 4710, 4 x 929 13415 / 12250; lists of 20: 60 x 20 207 / 211, of 40: 32 x 40 422 / 429; below a
-// round: 5 x 110 480 / 487.
-inline bool takes_pairs(const WorkMap& w) {
+// A head of n blocks by slices starts at least 8 workgroups, 8 * max_slice, of which those beyond n have no work; pairs leave none out.  At least an eighth of them:
+inline bool slices_leave_gaps(const WorkMap& w) { return w.sliced > 0 && 64LL * w.max_slice >= 9LL * (w.n_blocks + w.n_blocks % 2); }
+// A pair begins later than a block (which entries both lists name, and up to three first stages to wait for) and lasts 1.75 times as long, so it takes lists of
+// some length, the workgroups without work that slices start, or 8-bit scores, whose kernel for single blocks is slower to begin as well.
+// Forward, single blocks / pairs, us, lists of L neighbouring entries unless said.
+//   by length, from a whole round of pairs on: 10 heads x 104 blocks 777 / 712, 10 x 120 898 / 869, 8 x 200 1788 / 1716, 10 x 180 1790 / 1778, 14 x 88 759 / 755, 8 x 256
+//     2610 / 2535, 5 x 500 4925 / 4710, 4 x 929 13415 / 12250; L 20: 60 x 20 207 / 211, L 40: 32 x 40 422 / 429; below a round: 5 x 110 480 / 487.
+//   by slices, hardly a gap: 40 x 128 L 2 168 / 182, 10 477 / 486, 20 865 / 875, 28 1173 / 1169, 40 1632 / 1609; 24 x 256 L 2 201 / 216, 20 1021 / 1049, 40 1935 / 1927;
+//     16 x 929 L 2 472 / 504, 10 1382 / 1401, 28 3409 / 3380; 113 x 24 L 3 114 / 119, 12 308 / 314, 24 566 / 563.  With gaps: 290 x 9 L 2 124 / 94, 9 321 / 244, 240 x 11 L 3 129 /
+//     117, 190 x 14 L 2 97.5 / 97.1, 149 x 18 L 2 104 / 97, 134 x 20 L 2 99.6 / 97.3, 105 x 25 L 25 617 / 558.  8-bit scores: 40 x 128 L 2 160 / 160, 10 429 / 422, 24 x 256 L 3 232 / 220,
+//     20 922 / 883, 16 x 929 L 2 444 / 441.
+//   fewer than 8 blocks, where pairs are half of the workgroups with work but a launch of a round or two lasts as long as one of them, and an odd last block is a pair of its
+//     own: 1 block 280 heads 25.6 / 15.1, 1200 87 / 39; 2 blocks 140 heads 32.6 / 21.7, 1000 L 1 137 / 55; 3 blocks 96 heads 19.2 / 26.3, 400 60 / 67, 800 L 1 80 / 88, L 3 114 / 115;
+//     4 blocks 65 heads 21.9 / 30.4, 100 L 1 18.4 / 20.3, 128 L 1 23.1 / 19.7, L 4 40.0 / 32.8, 600 177 / 120; 5 blocks 53 heads 25.6 / 34.9, 120 47 / 51, 200 L 2 45.1 / 41.0, 400 141 / 121;
+//     6 blocks 64 heads 32.6 / 40.0, 120 L 2 32.1 / 34.2, 180 85 / 88, 200 95.6 / 89.8, 400 183 / 151; 7 blocks 40 heads 32.5 / 43.3, 160 93 / 102, 350 L 2 89 / 96, L 7 200 / 203.
+inline bool takes_pairs(const WorkMap& w, bool codes = false) {
   if (w.n_blocks > kMaxOrdered) return false;
-  return w.sliced > 0 || (w.mean >= 64 && (int64_t)w.ordered * ((w.n_blocks + 1) / 2) >= kTwoRound);
+  const int64_t pairs = (int64_t)(w.sliced + w.ordered) * ((w.n_blocks + 1) / 2);
+  if (w.sliced == 0) return w.mean >= 64 && pairs >= kTwoRound;
+  if (w.n_blocks >= 8) return codes || w.mean >= 28 || slices_leave_gaps(w);
+  return w.n_blocks <= 2 || (w.n_blocks == 4 && pairs >= 256) || ((w.n_blocks == 5 || w.n_blocks == 6) && pairs >= 600);
 }
 
 // ---- How many groups of waves share a list ------------------------------------------------------

@@ -1,0 +1,16 @@
+// Which launches go over pairs of neighbouring blocks (radial_internal.h): for each input line
+//   n_blocks sliced ordered mean max_slice codes
+// a line with 1 where a forward takes pairs, else 0.
+#include <stdio.h>
+
+#include "radial_internal.h"
+
+using namespace radial;
+
+int main() {
+  WorkMap w = {};
+  int codes;
+  while (scanf("%d %d %d %d %d %d", &w.n_blocks, &w.sliced, &w.ordered, &w.mean, &w.max_slice, &codes) == 6)
+    printf("%d\n", takes_pairs(w, codes != 0) ? 1 : 0);
+  return 0;
+}

@@ -1,0 +1,59 @@
+"""Forward at the edges of the rules that choose between single query blocks and pairs of them, bf16 and 8-bit scores: few blocks and short lists
+by slices, against float64."""
+import numpy as np
+import pytest
+
+from test_gpu_list_split import reference
+from test_gpu_two_blocks import check
+
+pytestmark = pytest.mark.gpu
+
+
+def band(nb, width):
+    """`width` neighbouring blocks a row."""
+    first = np.minimum(np.maximum(np.arange(nb) - width // 2, 0), nb - width)
+    return [np.arange(f, f + width) for f in first]
+
+
+# fewer than 8 blocks on either side of a rule; 40 heads of 128 blocks are by slices, of 18 slices start workgroups without work
+EDGES = [(127, 4, 3, 7), (128, 4, 4, 90), (199, 5, 2, 64), (200, 5, 5, 1), (199, 6, 6, 33), (200, 6, 2, 0), (300, 3, 3, 127), (140, 7, 7, 5), (140, 2, 1, 3),
+         (40, 128, 27, 31), (40, 128, 28, 97), (149, 18, 2, 65)]
+
+
+@pytest.mark.parametrize("H, nb, width, cut", EDGES)
+def test_bf16(H, nb, width, cut):
+    from paper_2506_19852_amd import binding as rb
+    print(f"H={H} nb={nb} width={width} cut={cut}", flush=True)
+    check(rb, 1, H, 128 * nb - cut, band(nb, width), "bnhd" if H % 2 else "bhnd", 2.0, H + nb)
+
+
+@pytest.mark.parametrize("H, nb, width, cut", [e for e in EDGES if e[1] < 8] + [(40, 128, 2, 31), (149, 18, 2, 65)])
+def test_8_bit_scores(H, nb, width, cut):
+    import torch
+    from paper_2506_19852_amd import binding as rb
+    print(f"8 bits H={H} nb={nb} width={width} cut={cut}", flush=True)
+    D, N = 128, 128 * nb - cut
+    g = torch.Generator(device="cuda").manual_seed(N + H)
+    q, k, v = (torch.randn((1, H, N, D), device="cuda", generator=g).bfloat16() for _ in range(3))
+    codes = [torch.empty((1, H, N, D), dtype=torch.uint8, device="cuda") for _ in range(2)]
+    scales = [torch.empty((1, H, nb), dtype=torch.float32, device="cuda") for _ in range(2)]
+    for x, c, s in zip((q, k), codes, scales):
+        rb.radial_quantize_fp8(x, 128, c, s)
+    lists = band(nb, width)
+    bm = torch.zeros((nb, nb), dtype=torch.bool)
+    for r, c in enumerate(lists):
+        bm[r, torch.from_numpy(c)] = True
+    m = rb.radial_mask_from_csr(N, 128, np.arange(nb + 1, dtype=np.int32) * width, np.concatenate(lists).astype(np.int32))
+    out = torch.full((1, H, N, D), float("nan"), dtype=torch.bfloat16, device="cuda")
+    lse = torch.full((1, H, N), float("nan"), dtype=torch.float32, device="cuda")
+    rb.radial_attn_fwd_fp8(codes[0], scales[0], codes[1], scales[1], v, out, lse, m, D ** -0.5)
+    vis = bm.cuda().repeat_interleave(128, 0).repeat_interleave(128, 1)[:N, :N]
+    for h in sorted({0, 1, H // 2, H - 9, H - 8, H - 1}):
+        qd, kd = (c[0, h].view(torch.float8_e4m3fn).double() * s[0, h].double().repeat_interleave(128)[:N, None] for c, s in zip(codes, scales))
+        ref, ref_lse = reference(qd, kd, v[0, h], torch.zeros_like(qd), vis, D ** -0.5)[:2]
+        # the 8-bit matrix instruction's sums: 1e-4 of the scores; P and out are rounded to bf16 (2^-9 each)
+        assert (lse[0, h].double() - ref_lse).abs().max() <= 1e-4 * (1 + ref_lse.abs().max())
+        for r in range(0, N, 128):
+            assert (out[0, h, r:r + 128].double() - ref[r:r + 128]).norm() <= 8e-3 * ref[r:r + 128].norm() + 1e-6, (h, r // 128)
+    assert torch.isfinite(out).all() and torch.isfinite(lse).all()
+    m.free()

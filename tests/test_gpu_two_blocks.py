@@ -128,7 +128,7 @@ def test_trace_of_pairs():
     """One record for each workgroup that takes a pair and for each block that is taken alone or in halves; the same results."""
     import torch
     from paper_2506_19852_amd import binding as rb
-    H, nb, D = 120, 3, 128
+    H, nb, D = 136, 4, 128
     N = 128 * nb - 5
     m = rb.radial_mask_build_dense(N, 128, 0)
     q, k, v = (torch.randn((1, H, N, D), device="cuda").bfloat16() for _ in range(3))
@@ -141,6 +141,6 @@ def test_trace_of_pairs():
     assert torch.equal(outs[0].view(torch.int16), outs[1].view(torch.int16)) and torch.equal(*lses)
     t = trace.cpu().numpy()
     used = t[:, 1] != 0
-    assert int(used.sum()) == 112 * 2 + 8 * 3   # heads by slices: two pairs each; the last 8 by length: less than a round, a block at a time
+    assert int(used.sum()) == 128 * 2 + 8 * 4   # heads by slices: two pairs each; the last 8 by length: less than a round, a block at a time
     assert np.all(t[used, 1] >= t[used, 0]) and np.all(t[~used] == 0)
     m.free()

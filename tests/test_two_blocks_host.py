@@ -62,9 +62,9 @@ def test_every_block_is_taken_once(launches):
 
 
 def test_rule(launches):
-    """By slices always; by length from a round of pairs and lists of 64 blocks on; not without the order of the pairs."""
-    cases = [(110, 0, 10, 93, even_slices(110)), (110, 0, 9, 93, even_slices(110)), (110, 0, 10, 63, even_slices(110)), (110, 1, 8, 5, even_slices(110)),
-             (16384, 1, 0, 5, even_slices(16384)), (16385, 1, 0, 5, even_slices(16385))]
+    """By slices from lists of 28 blocks on; by length from a round of pairs and lists of 64 on; not without the order of the pairs."""
+    cases = [(110, 0, 10, 93, even_slices(110)), (110, 0, 9, 93, even_slices(110)), (110, 0, 10, 63, even_slices(110)), (110, 1, 8, 28, even_slices(110)),
+             (16384, 1, 0, 28, even_slices(16384)), (16385, 1, 0, 28, even_slices(16385))]
     assert [head[0] for head, _ in launches(cases)] == [1, 0, 0, 1, 1, 0]
 
 
