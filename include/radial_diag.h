@@ -10,14 +10,15 @@
 extern "C" {
 #endif
 
-/* radial_attn_fwd_trace is radial_attn_fwd plus one record per workgroup of the launch (in no
- * particular order; where a launch gives a query block to several workgroups, all blocks of a small one
- * or the last ones of a larger one, one record per block, of the workgroup with its first rows; where a
- * workgroup takes two blocks, one record for both), for load-balance figures: trace (device memory, trace_records x 3 uint64, zero-filled by the caller;
- * trace_records >= radial_attn_fwd_trace_records(B, H, mask), else RADIAL_ESHAPE) receives, for
- * every workgroup that had work, {begin, end, where}: begin and end in ticks of the device's
+/* radial_attn_fwd_trace is radial_attn_fwd plus one record per (head, query block), in no particular
+ * order, for load-balance figures: trace (device memory, trace_records x 3 uint64, zero-filled by the
+ * caller; trace_records >= radial_attn_fwd_trace_records(B, H, mask), else RADIAL_ESHAPE) receives
+ * {begin, end, where} of the workgroup that took the block: begin and end in ticks of the device's
  * constant 100 MHz clock, where = (XCC_ID register << 32) | HW_ID register of the wave that wrote
- * it.  Workgroups without work leave their record untouched.  Same errors as radial_attn_fwd;
+ * it.  Where a launch gives a block to several workgroups, all blocks of a small one or the last ones of
+ * a larger one, it is the workgroup with the block's first rows; where a workgroup takes two blocks, the
+ * second's record begins when the first's ends, which is when its rows are stored.  The other records
+ * are left untouched.  Same errors as radial_attn_fwd;
  * RADIAL_EINVAL if trace is NULL.  radial_attn_fwd_trace_records returns 0 on bad arguments. */
 RADIAL_API int64_t radial_attn_fwd_trace_records(int32_t B, int32_t H, const radial_mask* mask);
 RADIAL_API int radial_attn_fwd_trace(int32_t B, int32_t H, int32_t N, int32_t D, radial_tensor q, radial_tensor k,

@@ -244,7 +244,7 @@ def radial_attn_fwd_trace_records(B: int, H: int, mask: RadialMask) -> int:
 
 
 def radial_attn_fwd_trace(q, k, v, out, lse, mask: RadialMask, scale: float, trace, stream=None):
-    """radial_attn_fwd plus one {begin, end, where} record per workgroup in trace (zeroed CUDA int64 [records, 3])."""
+    """radial_attn_fwd plus one {begin, end, where} record per (head, query block) in trace (zeroed CUDA int64 [records, 3])."""
     torch = _torch or _load_torch()
     B, H, N, D = q.shape
     if trace.dtype != torch.int64 or not trace.is_cuda or not trace.is_contiguous() or trace.dim() != 2 or trace.shape[1] != 3:

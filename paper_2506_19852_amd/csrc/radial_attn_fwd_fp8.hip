@@ -441,7 +441,7 @@ __global__ void __launch_bounds__(2 * BLK, 2) radial_fwd_fp8_two_kernel(const Fp
   TwoItem item;
   if (!two_item(a.work, m, blockIdx.x, item)) return;
   const int32_t qb = 2 * item.pair + item.block;
-  if (item.form == TwoItem::kPair) fwd::two_body<false>(a, item.bh, qb, m.c, 0, fwd::static_lds<Fp8Key, kBytes>());
+  if (item.form == TwoItem::kPair) fwd::two_body<false>(a, item.bh, qb, m.c, fwd::static_lds<Fp8Key, kBytes>());
   else fp8_body<1, 1, kBytes>(own_args<Fp8FwdArgs>(), item.bh, qb, 0);
 }
 

@@ -43,13 +43,13 @@ struct TwoTile {
 
 // Query blocks qb and qb + 1 (which may not exist).
 template <bool kTrace, class Args>
-__device__ __forceinline__ void two_body(const Args& a, int32_t bh, int32_t qb, float c, int64_t record, char* lds_all) {
+__device__ __forceinline__ void two_body(const Args& a, int32_t bh, int32_t qb, float c, char* lds_all) {
   constexpr bool kFp8 = std::is_same_v<Args, Fp8FwdArgs>;
   using T = TwoTile<kFp8>;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lq = lane & 31, g = lane >> 5;
-  const uint64_t t_begin = kTrace ? __builtin_amdgcn_s_memrealtime() : 0;
+  uint64_t t_begin = kTrace ? __builtin_amdgcn_s_memrealtime() : 0;
   int32_t heads = a.H;
   if constexpr (!kFp8) asm("" : "+s"(heads) : "s"(a.q.ptr), "s"(a.k.ptr), "s"(a.row_ptr));
   const int32_t b = bh / heads, h = bh % heads;
@@ -459,6 +459,8 @@ __device__ __forceinline__ void two_body(const Args& a, int32_t bh, int32_t qb, 
         }
       if (late.lse && g2 == 0) late.lse[(int64_t)bh * late.N + q_row] = l_tot > 0.f ? m_run[0] * late.scale + __logf(l_tot) : -INFINITY;
     }
+    if constexpr (kTrace)
+      if (a.wg_trace != nullptr && threadIdx.x == 0 && qb + set < a.n_blocks) t_begin = write_trace(a, t_begin, bh, qb + set);
 #pragma unroll
     for (int dt = 0; dt < T::kDTiles; ++dt) o[0][dt] = o[1][dt];
 #pragma unroll
@@ -468,8 +470,6 @@ __device__ __forceinline__ void two_body(const Args& a, int32_t bh, int32_t qb, 
     mc[0] = mc[1];
     q_scale[0] = q_scale[1];
   }
-  if constexpr (kTrace)
-    if (a.wg_trace != nullptr && threadIdx.x == 0) write_trace(a, t_begin, record);
 }
 
 template <bool kTrace>
@@ -478,9 +478,9 @@ __global__ void __launch_bounds__(256, 2) radial_fwd_two_kernel(const FwdArgs a,
   TwoItem item;
   if (!two_item(a.work, m, blockIdx.x, item)) return;
   const int32_t qb = 2 * item.pair + item.block;
-  if (item.form == TwoItem::kPair) two_body<kTrace>(a, item.bh, qb, m.c, item.record, static_lds<FwdKey<128, 128, false, kTrace, kBytes>, kBytes>());
-  else if (item.form == TwoItem::kBlock) fwd_body<128, 128, false, kTrace, 1, 1, kBytes>(own_args<FwdArgs>(), item.bh, qb, 0, item.record);
-  else fwd_body<128, 128, false, kTrace, 2, 2, kBytes>(own_args<FwdArgs>(), item.bh, qb, item.half, item.record);
+  if (item.form == TwoItem::kPair) two_body<kTrace>(a, item.bh, qb, m.c, static_lds<FwdKey<128, 128, false, kTrace, kBytes>, kBytes>());
+  else if (item.form == TwoItem::kBlock) fwd_body<128, 128, false, kTrace, 1, 1, kBytes>(own_args<FwdArgs>(), item.bh, qb, 0);
+  else fwd_body<128, 128, false, kTrace, 2, 2, kBytes>(own_args<FwdArgs>(), item.bh, qb, item.half);
 }
 
 template <bool kTrace>

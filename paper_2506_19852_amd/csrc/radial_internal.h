@@ -512,7 +512,7 @@ struct FwdArgs {
   int32_t B, H, N, n_blocks;
   float scale;
   TokenRule rule;
-  uint64_t* wg_trace;  // null, or [grid][3]: begin, end (100 MHz clock), where the workgroup ran
+  uint64_t* wg_trace;  // null, or [B * H * n_blocks][3]: begin, end (100 MHz clock), where the workgroup ran
   const int32_t* pair_order;  // pairs of query blocks by falling length; null only if work.ordered == 0
 };
 

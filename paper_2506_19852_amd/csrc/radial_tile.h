@@ -372,7 +372,6 @@ __device__ __forceinline__ uint32_t halved_item(uint32_t id, uint32_t first, uin
 struct TwoItem {
   enum Form { kPair, kBlock, kHalf } form;
   int32_t bh, pair, block, half;
-  int64_t record;  // of a trace: its own for every workgroup, the same for both halves of a block
 };
 
 // Workgroup `id` of those that share `count` items, 1 << kLog of them each: item and part.  All parts of an item are on one XCD while 8
@@ -392,7 +391,6 @@ __host__ __device__ __forceinline__ uint32_t split_item(uint32_t id, uint32_t co
 __host__ __device__ __forceinline__ bool two_item(const WorkMap& w, const TwoMap& m, uint32_t id, TwoItem& item) {
   item.form = TwoItem::kPair;
   item.block = item.half = 0;
-  item.record = id;
   uint32_t pair_id = id;
   if (id >= m.n_two) {
     const uint32_t single = id - m.n_two;
@@ -409,8 +407,6 @@ __host__ __device__ __forceinline__ bool two_item(const WorkMap& w, const TwoMap
       item.half = part & 1;
     }
     pair_id = m.n_two + k;
-    const uint32_t count = m.n_one + m.n_half, eights = k & ~7u;  // both blocks of a pair 8 records apart, as the workgroups' XCDs go round
-    item.record = m.n_two + 2u * eights + (uint32_t)item.block * (count - eights < 8u ? count - eights : 8u) + (k & 7u);
   }
   if (pair_id >= m.n_sliced) {
     if (!work_item(m.pairs, pair_id - m.n_sliced, item.bh, item.pair)) return false;
