@@ -38,6 +38,7 @@ struct radial_mask {
   int32_t max_slice = 0;         // longest slice, in blocks (host copy, sizes the grid)
   int32_t max_slice_t = 0;
   int32_t longest = 0, longest_t = 0;  // entries of the longest list (n_blocks, a bound, where there is no order)
+  int32_t longest_pair = 0;            // entries of the longest pair of lists 2p, 2p + 1, both together (0 where there is no order)
   int32_t tokens_per_frame = 0;  // geometry of a radial mask (0 for dense / caller-supplied lists)
   int32_t sink_frames = 0;
   int32_t width_num = 1, width_den = 1;  // sparsity knob of a radial mask
@@ -111,6 +112,7 @@ struct WorkMap {
   int32_t sliced, ordered;  // heads; sum B * H
   int32_t n_blocks;
   int32_t longest, mean;    // entries of the longest and of an average list
+  int32_t longest_pair = 0; // of query blocks' lists: entries of the longest two neighbours 2p, 2p + 1
   int32_t halved = 0;       // the last items of the launch, taken in two halves each (kernels that have such a form)
 };
 
@@ -166,6 +168,7 @@ inline WorkMap make_work_map(const radial_mask* m, Walk walk, int32_t heads, int
   w.order = transposed ? m->d_order_t : m->d_order;
   w.max_slice = transposed ? m->max_slice_t : m->max_slice;
   w.longest = transposed ? m->longest_t : m->longest;
+  w.longest_pair = transposed ? 0 : m->longest_pair;
   w.mean = (int32_t)(m->nnz / m->n_blocks);
   const int64_t per_head = 4LL * D * m->n_tokens;  // K and V of one head
   const int64_t fit = (heads <= 8 && per_head * heads <= kOrderedWholeBytes ? kOrderedWholeBytes : kOrderedTailBytes) / per_head;
@@ -254,8 +257,26 @@ inline bool slices_leave_gaps(const WorkMap& w) { return w.sliced > 0 && 64LL * 
 //     own: 1 block 280 heads 25.6 / 15.1, 1200 87 / 39; 2 blocks 140 heads 32.6 / 21.7, 1000 L 1 137 / 55; 3 blocks 96 heads 19.2 / 26.3, 400 60 / 67, 800 L 1 80 / 88, L 3 114 / 115;
 //     4 blocks 65 heads 21.9 / 30.4, 100 L 1 18.4 / 20.3, 128 L 1 23.1 / 19.7, L 4 40.0 / 32.8, 600 177 / 120; 5 blocks 53 heads 25.6 / 34.9, 120 47 / 51, 200 L 2 45.1 / 41.0, 400 141 / 121;
 //     6 blocks 64 heads 32.6 / 40.0, 120 L 2 32.1 / 34.2, 180 85 / 88, 200 95.6 / 89.8, 400 183 / 151; 7 blocks 40 heads 32.5 / 43.3, 160 93 / 102, 350 L 2 89 / 96, L 7 200 / 203.
+//
+// Two neighbouring lists both at least twice as long as the others (text tokens) are one workgroup's in pairs, and the launch ends no sooner than it does: 1.13 of the time that either
+// takes alone (beside a list of the usual length a long one takes no longer than alone).  They start where the heads by length do, so the shorter of them counts against what a
+// workgroup of a whole round has of those heads, or of the launch where all heads go by slices.  Single blocks / pairs, us, radial lists and 512 tokens of text unless said, that share in
+// brackets: by length 1 head x 1129 blocks [1.10] 4881 / 5537, 1 x 1690 (226 tokens) [0.91] 8090 / 8559, 1 x 1971 (226) [0.84] 9970 / 10177, 1 x 2252 (226) [0.79] 12418 / 12027, 2 x 565 (226) [0.78]
+// 3003 / 2982, 2 x 933 [0.60] 6538 / 6142, one long list of a pair 1 x 1127 (226) 4617 / 4052; the last heads by length: lists of 32 and two full ones 40 x 128 [1.9] 1503 / 1588, one 1480 /
+// 1444, lists of 40 and two 20 x 256 [1.5] 1854 / 2164; 4 x 1804 [0.88] 36.3 / 32.2 ms, 24 x 114 [0.66] 2218 / 2138; all by slices 2 x 3633 [0.31] 52.1 / 55.6 ms, 2 x 2817 [0.35] 37.9 / 40.4, 3 x 2817
+// [0.24] 55.9 / 56.1, 4 x 3633 [0.16] 101 / 98, without text 2 x 3629 [0.08] 49.8 / 46.2.  8-bit scores: 1 x 1129 4176 / 4616, 1 x 1409 (226) [0.99] 5521 / 5785, 1 x 1690 7175 / 6988, 40 x 128 1386 /
+// 1429, 20 x 256 1732 / 1832, 2 x 3633 48.2 / 46.8 ms.
+// One long list that the whole launch waits for is slower beside a usual one in bf16: lists of 64 and a full one by length 4 x 929 [1.9]
+// 2425 / 2719; the last heads by length 8 x 929 [3.9] 5013 / 5253, lists of 32 10 x 929 [7.5] 4035 / 4243, 40 x 128 [1.9] 1404 / 1376; 8-bit scores 4 x 929 2953 / 2730.
+inline bool long_lists_end_the_launch(const WorkMap& w, bool codes) {
+  const int64_t shorter = w.longest_pair - w.longest, entries = (int64_t)w.n_blocks * w.mean;  // of a head
+  if (!codes && w.ordered > 0 && w.longest >= 2LL * w.mean && 2LL * kTwoRound * w.longest > (w.sliced ? 6 : 3) * w.ordered * entries) return true;
+  if (shorter < 2LL * w.mean) return false;
+  if (w.ordered == 0) return !codes && 5 * kTwoRound * shorter > w.sliced * entries;
+  return 20 * kTwoRound * shorter > (codes ? 19 : w.sliced ? 20 : 16) * w.ordered * entries;
+}
 inline bool takes_pairs(const WorkMap& w, bool codes = false) {
-  if (w.n_blocks > kMaxOrdered) return false;
+  if (w.n_blocks > kMaxOrdered || (w.n_blocks >= 8 && long_lists_end_the_launch(w, codes))) return false;
   const int64_t pairs = (int64_t)(w.sliced + w.ordered) * ((w.n_blocks + 1) / 2);
   if (w.sliced == 0) return w.mean >= 64 && pairs >= kTwoRound;
   if (w.n_blocks >= 8) return codes || w.mean >= 28 || slices_leave_gaps(w);

@@ -261,8 +261,8 @@ __device__ inline long long slice_target(long long total, int32_t nb, int k) {
 // What a build finds out about its lists, for the launches (device) and for the host: the kernels write both, so that the host
 // has it when it has waited for the stream.  A copy of these 128 bytes to pageable memory behind the kernels costs 10 us of that wait (kernel, copy and wait
 // 22.5 us, kernel writing mapped memory and wait 12.0); radial_mask_build and free, 110 blocks, 32.4 / 23.2 us.
-// [0..1] total of rows, [2..3] total of columns, [4] longest row, [5] longest column, [8..16] slice, [20..28] slice_t
-constexpr int kMetaInts = 32, kTotal = 0, kTotalT = 2, kLongest = 4, kLongestT = 5, kSlice = 8, kSliceT = 20;
+// [0..1] total of rows, [2..3] total of columns, [4] longest row, [5] longest column, [6] both rows of the longest pair, [8..16] slice, [20..28] slice_t
+constexpr int kMetaInts = 32, kTotal = 0, kTotalT = 2, kLongest = 4, kLongestT = 5, kLongestPair = 6, kSlice = 8, kSliceT = 20;
 struct Meta {
   int32_t* device;
   int32_t* host;  // mapped host memory, or null
@@ -308,6 +308,7 @@ __device__ int32_t place_list(const int32_t* counts, int32_t nb, int32_t r, int3
     ptr[r] = (int32_t)before;
     order[ahead] = r;
     if (places_pair) pair_order[pairs_ahead] = r / 2;
+    if (places_pair && !columns && pairs_ahead == 0) meta.put(kLongestPair, pair_len);
     if (ahead == 0) meta.put(columns ? kLongestT : kLongest, len);
     if (r == nb - 1) {
       ptr[nb] = (int32_t)total;
@@ -384,9 +385,10 @@ __global__ void __launch_bounds__(kThreads) partition_kernel(const int32_t* ptr,
       ahead += (other > len || (other == len && j < b)) ? 1 : 0;
     }
     const bool places_pair = pair_order && b % 2 == 0;
+    int32_t pair_len = 0;
     if (places_pair) {
       const auto pair_end = [&](int32_t r) { return ptr[r + 2 <= nb ? r + 2 : nb]; };
-      const int32_t pair_len = pair_end(b) - ptr[b];
+      pair_len = pair_end(b) - ptr[b];
       for (int32_t j = 2 * (threadIdx.x & 63); j < nb; j += 128) {
         const int32_t other = pair_end(j) - ptr[j];
         ahead += (other > pair_len || (other == pair_len && j < b)) ? 1 << 16 : 0;
@@ -398,6 +400,7 @@ __global__ void __launch_bounds__(kThreads) partition_kernel(const int32_t* ptr,
     if ((threadIdx.x & 63) == 0) {
       order[ahead] = b;
       if (places_pair) pair_order[pairs_ahead] = b / 2;
+      if (places_pair && !columns && pairs_ahead == 0) meta.put(kLongestPair, pair_len);
       if (ahead == 0) meta.put(columns ? kLongestT : kLongest, len);
     }
     return;
@@ -555,6 +558,7 @@ int finish_mask(radial_mask* m, HostMeta& shared, bool rows_placed, hipStream_t 
   shared.release();
   if (rows_placed) memcpy(&m->nnz, h_meta + kTotal, sizeof m->nnz);
   m->longest = m->d_order ? h_meta[kLongest] : nb;
+  m->longest_pair = m->d_pair_order ? h_meta[kLongestPair] : 0;
   if (m->flags & RADIAL_MASK_TRANSPOSE) m->longest_t = m->d_order_t ? h_meta[kLongestT] : nb;
   for (int k = 0; k < 8; ++k) {
     const int32_t len = h_meta[kSlice + k + 1] - h_meta[kSlice + k];

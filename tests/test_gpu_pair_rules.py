@@ -57,3 +57,38 @@ def test_8_bit_scores(H, nb, width, cut):
             assert (out[0, h, r:r + 128].double() - ref[r:r + 128]).norm() <= 8e-3 * ref[r:r + 128].norm() + 1e-6, (h, r // 128)
     assert torch.isfinite(out).all() and torch.isfinite(lse).all()
     m.free()
+
+
+@pytest.mark.parametrize("how", ["csr", "radial"])
+@pytest.mark.parametrize("full", [1, 2])
+def test_two_long_neighbours(how, full):
+    """Text rows see every block: where two of them are neighbours, one workgroup would have both for longer than the rest of the launch takes.  In
+    pairs, and only there, a block begins when its neighbour ends."""
+    import torch
+    from paper_2506_19852_amd import binding as rb
+    H, D, nb = (40, 128, 128) if how == "csr" else (1, 128, 1126 + full)
+    N = 128 * nb
+    if how == "csr":
+        lists = band(nb, 32)
+        for r in range(nb - full, nb):
+            lists[r] = np.arange(nb)
+        m = rb.radial_mask_from_csr(N, 128, np.concatenate([[0], np.cumsum([len(x) for x in lists])]).astype(np.int32), np.concatenate(lists).astype(np.int32))
+    else:   # 1125 blocks of video; text in block 1125, which has a neighbour that is video, 1126 and 1127, which are neighbours
+        m = rb.radial_mask_build(40, 3600, 128, 1, 0, extra_tokens=N - 40 * 3600)
+    g = torch.Generator(device="cuda").manual_seed(H)
+    q, k, v = (torch.randn((1, H, N, D), device="cuda", generator=g).bfloat16() for _ in range(3))
+    out, traced = torch.empty_like(q), torch.empty_like(q)
+    rb.radial_attn_fwd(q, k, v, out, None, m, D ** -0.5)
+    trace = torch.zeros((rb.radial_attn_fwd_trace_records(1, H, m), 3), dtype=torch.int64, device="cuda")
+    rb.radial_attn_fwd_trace(q, k, v, traced, None, m, D ** -0.5, trace)
+    torch.cuda.synchronize()
+    assert torch.equal(out.view(torch.int16), traced.view(torch.int16))
+    t = trace.cpu().numpy()[:H * nb].reshape(H, nb, 3)
+    seconds = np.mean(t[:, 1::2, 0] == t[:, :nb // 2 * 2:2, 1])
+    assert seconds > 0.5 if full == 1 else seconds < 0.1, seconds
+    h, rows = H - 1, slice(N - 128, N)
+    s = (D ** -0.5 * (q[0, h, rows].double() @ k[0, h].double().T)).softmax(1)   # the last block's list is full
+    ref = s @ v[0, h].double()
+    # P and out are rounded to bf16 (2^-9 each)
+    assert (out[0, h, rows].double() - ref).norm() <= 8e-3 * ref.norm()
+    m.free()

@@ -26,8 +26,8 @@ def rules(tmp_path_factory):
     return run
 
 
-def case(n_blocks, sliced, ordered, mean, max_slice=0, codes=0):
-    return (n_blocks, sliced, ordered, mean, max_slice or (n_blocks + 7) // 8, codes)
+def case(n_blocks, sliced, ordered, mean, max_slice=0, codes=0, longest=0, shorter=0):
+    return (n_blocks, sliced, ordered, mean, max_slice or (n_blocks + 7) // 8, codes, longest or mean, (longest or mean) + (shorter or mean))
 
 
 def test_fewer_than_8_blocks(rules):
@@ -51,3 +51,23 @@ def test_short_lists_by_slices(rules):
 def test_by_length(rules):
     """A whole round of pairs, lists of 64."""
     assert rules([case(110, 0, 10, 93), case(110, 0, 9, 93), case(110, 0, 10, 63), case(16384, 0, 1, 64), case(16385, 0, 1, 64)]) == [1, 0, 0, 1, 0]
+
+
+def test_two_long_neighbours(rules):
+    """Not where the shorter list of the longest pair, at least twice the mean, is more than a workgroup of a whole round has: by length 0.8 of it, 0.95 with 8-bit scores; the last
+    heads by length all of it; a fifth where all heads go by slices, 8-bit scores whatever it is."""
+    def at(nb, sliced, ordered, mean, share, codes=0):
+        shorter = int(share * (ordered or sliced) * nb * mean / 512)
+        return case(nb, sliced, ordered, mean, 0, codes, max(nb, shorter), shorter)
+    assert rules([at(1971, 0, 1, 606, x) for x in (0.5, 0.79, 0.81, 1.1)]) == [1, 1, 0, 0]
+    assert rules([at(1971, 0, 1, 606, x, 1) for x in (0.81, 0.94, 0.96)]) == [1, 1, 0]
+    assert rules([at(1804, 3, 1, 582, x) for x in (0.88, 0.99, 1.01)]) == [1, 1, 0]
+    assert rules([at(128, 32, 8, 33, x) for x in (0.99, 1.9)] + [at(128, 32, 8, 33, x, 1) for x in (0.94, 1.9)]) == [1, 0, 1, 0]
+    assert rules([at(3633, 4, 0, 819, x) for x in (0.16, 0.19, 0.21)] + [at(3633, 2, 0, 819, 0.31, 1)]) == [1, 1, 0, 1]
+    # neighbours that are not twice as long as the others, however short the launch; one long list beside a usual one
+    assert rules([case(128, 32, 8, 33, longest=128, shorter=x) for x in (33, 65, 67, 128)] + [case(9, 282, 8, 2)]) == [1, 1, 0, 0, 1]
+    # one long list beside usual ones: more than 1.5 of a workgroup's share by length, 3 for the last heads by length; not with 8-bit scores
+    assert rules([case(929, 0, 4, 66, longest=x) for x in (718, 719)] + [case(929, 0, 4, 66, codes=1, longest=929)]) == [1, 0, 1]
+    assert rules([case(929, 6, 2, 66, longest=x) for x in (718, 719)] + [case(929, 6, 0, 66, longest=929)]) == [1, 0, 1]
+    # fewer than 8 blocks: one list can be no longer than the others by much
+    assert rules([case(2, 132, 8, 1, longest=2, shorter=2), case(4, 120, 8, 1, longest=4, shorter=4)]) == [1, 1]
