@@ -39,6 +39,7 @@ struct radial_mask {
   int32_t max_slice_t = 0;
   int32_t longest = 0, longest_t = 0;  // entries of the longest list (n_blocks, a bound, where there is no order)
   int32_t longest_pair = 0;            // entries of the longest pair of lists 2p, 2p + 1, both together (0 where there is no order)
+  bool alike = true;             // the lists of query blocks 2p and 2p + 1 name some of the same blocks (caller-supplied lists may not)
   int32_t tokens_per_frame = 0;  // geometry of a radial mask (0 for dense / caller-supplied lists)
   int32_t sink_frames = 0;
   int32_t width_num = 1, width_den = 1;  // sparsity knob of a radial mask
@@ -113,6 +114,7 @@ struct WorkMap {
   int32_t n_blocks;
   int32_t longest, mean;    // entries of the longest and of an average list
   int32_t longest_pair = 0; // of query blocks' lists: entries of the longest two neighbours 2p, 2p + 1
+  bool alike = true;        // of query blocks' lists: see radial_mask
   int32_t halved = 0;       // the last items of the launch, taken in two halves each (kernels that have such a form)
 };
 
@@ -169,6 +171,7 @@ inline WorkMap make_work_map(const radial_mask* m, Walk walk, int32_t heads, int
   w.max_slice = transposed ? m->max_slice_t : m->max_slice;
   w.longest = transposed ? m->longest_t : m->longest;
   w.longest_pair = transposed ? 0 : m->longest_pair;
+  w.alike = m->alike;
   w.mean = (int32_t)(m->nnz / m->n_blocks);
   const int64_t per_head = 4LL * D * m->n_tokens;  // K and V of one head
   const int64_t fit = (heads <= 8 && per_head * heads <= kOrderedWholeBytes ? kOrderedWholeBytes : kOrderedTailBytes) / per_head;
@@ -242,8 +245,9 @@ inline TwoMap make_two_map(const WorkMap& w, const int32_t* pair_order, float sc
   m.n_two = m.n_sliced + ordered - rest;
   return m;
 }
-// A head of n blocks by slices starts at least 8 workgroups, 8 * max_slice, of which those beyond n have no work; pairs leave none out.  At least an eighth of them:
-inline bool slices_leave_gaps(const WorkMap& w) { return w.sliced > 0 && 64LL * w.max_slice >= 9LL * (w.n_blocks + w.n_blocks % 2); }
+// A head of n blocks by slices starts at least 8 workgroups, 8 * max_slice, of which those beyond n have no work; pairs have no such gaps.  Whether there are
+// at least eighths / 8 workgroups to a block:
+inline bool slices_leave_gaps(const WorkMap& w, int eighths) { return w.sliced > 0 && 64LL * w.max_slice >= (int64_t)eighths * (w.n_blocks + w.n_blocks % 2); }
 // A pair begins later than a block (which entries both lists name, and up to three first stages to wait for) and lasts 1.75 times as long, so it takes lists of
 // some length, the workgroups without work that slices start, or 8-bit scores, whose kernel for single blocks is slower to begin as well.
 // Forward, single blocks / pairs, us, lists of L neighbouring entries unless said.
@@ -275,11 +279,15 @@ inline bool long_lists_end_the_launch(const WorkMap& w, bool codes) {
   if (w.ordered == 0) return !codes && 5 * kTwoRound * shorter > w.sliced * entries;
   return 20 * kTwoRound * shorter > (codes ? 19 : w.sliced ? 20 : 16) * w.ordered * entries;
 }
+// Lists that hardly share an entry gain nothing from being walked together and are slower at any length, above all with 8-bit scores, whose kernel for single blocks keeps three waves to a
+// SIMD: forward, single blocks / pairs, us, 40 x 128 L 40, nothing shared 1636 / 1668, 8 bits 1437 / 1497; 16 x 929 random lists of a tenth of the blocks 11805 / 11797, 8 bits 9949 / 10301; of a
+// quarter 29035 / 28175, 24384 / 24062; 40 x 128 of a quarter 1414 / 1424, 1231 / 1247, of a half 2694 / 2674, 2355 / 2297.  Gaps have to be wider then: 40 x 128 random lists of 2.5
+// entries, 9 workgroups to 8 blocks, 194 / 199, 8 bits 179 / 181.
 inline bool takes_pairs(const WorkMap& w, bool codes = false) {
   if (w.n_blocks > kMaxOrdered || (w.n_blocks >= 8 && long_lists_end_the_launch(w, codes))) return false;
   const int64_t pairs = (int64_t)(w.sliced + w.ordered) * ((w.n_blocks + 1) / 2);
-  if (w.sliced == 0) return w.mean >= 64 && pairs >= kTwoRound;
-  if (w.n_blocks >= 8) return codes || w.mean >= 28 || slices_leave_gaps(w);
+  if (w.sliced == 0) return w.alike && w.mean >= 64 && pairs >= kTwoRound;
+  if (w.n_blocks >= 8) return slices_leave_gaps(w, w.alike ? 9 : 12) || (w.alike && (codes || w.mean >= 28));
   return w.n_blocks <= 2 || (w.n_blocks == 4 && pairs >= 256) || ((w.n_blocks == 5 || w.n_blocks == 6) && pairs >= 600);
 }
 

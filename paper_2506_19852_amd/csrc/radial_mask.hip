@@ -738,6 +738,24 @@ extern "C" int radial_mask_build_dense(int32_t n_tokens, int32_t block, uint32_t
   return RADIAL_OK;
 }
 
+// Whether lists 2p and 2p + 1 have at least a fifth of their entries in common, from 64 to 127 pairs spread over all (all of fewer).
+static bool neighbours_alike(const int32_t* row_ptr, const int32_t* col_idx, int32_t nb) {
+  const int32_t pairs = nb / 2, step = pairs < 64 ? 1 : pairs / 64;
+  int64_t entries = 0, common = 0;
+  for (int32_t p = 0; p < pairs; p += step) {
+    int32_t i = row_ptr[2 * p], j = row_ptr[2 * p + 1];
+    const int32_t i_end = j, j_end = row_ptr[2 * p + 2];
+    entries += j_end - i;
+    while (i < i_end && j < j_end) {
+      const int32_t a = col_idx[i], b = col_idx[j];
+      common += a == b;
+      i += a <= b;
+      j += b <= a;
+    }
+  }
+  return 10 * common >= entries;
+}
+
 static int build_from_csr(radial_mask* m, const int32_t* row_ptr, const int32_t* col_idx, hipStream_t st) {
   const int32_t nb = m->n_blocks;
   if (row_ptr[0] != 0) return fail(RADIAL_EINVAL, "row_ptr[0] must be 0");
@@ -749,6 +767,7 @@ static int build_from_csr(radial_mask* m, const int32_t* row_ptr, const int32_t*
     }
   }
   m->nnz = row_ptr[nb];
+  m->alike = neighbours_alike(row_ptr, col_idx, nb);
   if (int rc = alloc_meta_and_ptrs(m)) return rc;
   if (int rc = alloc_idx(m)) return rc;
   // the caller's arrays are read until finish_mask has waited for the stream

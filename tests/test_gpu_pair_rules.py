@@ -59,6 +59,48 @@ def test_8_bit_scores(H, nb, width, cut):
     m.free()
 
 
+def pairs_of(rb, m, q, k, v, scale):
+    """The share of second blocks that began when their neighbour ended: all of those in pairs, hardly any other.  The traced launch gives the same output."""
+    import torch
+    _, H, N, _ = q.shape
+    nb = -(-N // 128)
+    out, traced = torch.empty_like(q), torch.empty_like(q)
+    rb.radial_attn_fwd(q, k, v, out, None, m, scale)
+    trace = torch.zeros((rb.radial_attn_fwd_trace_records(1, H, m), 3), dtype=torch.int64, device="cuda")
+    rb.radial_attn_fwd_trace(q, k, v, traced, None, m, scale, trace)
+    torch.cuda.synchronize()
+    assert torch.equal(out.view(torch.int16), traced.view(torch.int16))
+    t = trace.cpu().numpy()[:H * nb].reshape(H, nb, 3)
+    return out, np.mean(t[:, 1::2, 0] == t[:, :nb // 2 * 2:2, 1])
+
+
+# entries that neighbouring rows share: none, an eighth, a quarter of 32 of them, all
+@pytest.mark.parametrize("common", [0, 4, 8, 32])
+def test_lists_with_little_in_common(common):
+    import torch
+    from paper_2506_19852_amd import binding as rb
+    H, nb, D = 40, 128, 128
+    lists = []
+    for r in range(nb):
+        own = 64 * (r % 2) + (r // 2 + np.arange(32 - common)) % 64      # the two halves of the blocks in turn
+        both = (64 + r // 2 + np.arange(32 - common, 32)) % 64 if common else np.zeros(0, dtype=np.int64)
+        lists.append(np.unique(np.concatenate([own, both])))
+        assert len(lists[r]) >= 32 - common
+    m = rb.radial_mask_from_csr(128 * nb, 128, np.concatenate([[0], np.cumsum([len(x) for x in lists])]).astype(np.int32), np.concatenate(lists).astype(np.int32))
+    g = torch.Generator(device="cuda").manual_seed(common)
+    q, k, v = (torch.randn((1, H, 128 * nb, D), device="cuda", generator=g).bfloat16() for _ in range(3))
+    out, seconds = pairs_of(rb, m, q, k, v, D ** -0.5)
+    assert seconds > 0.5 if common >= 8 else seconds < 0.1, seconds
+    vis = torch.zeros((nb, nb), dtype=torch.bool)
+    for r, c in enumerate(lists):
+        vis[r, torch.from_numpy(c)] = True
+    vis = vis.cuda().repeat_interleave(128, 0).repeat_interleave(128, 1)
+    for h in (0, H - 1):
+        ref = reference(q[0, h], k[0, h], v[0, h], torch.zeros_like(q[0, h]), vis, D ** -0.5)[0]
+        assert (out[0, h].double() - ref).norm() <= 8e-3 * ref.norm()    # P and out are rounded to bf16 (2^-9 each)
+    m.free()
+
+
 @pytest.mark.parametrize("how", ["csr", "radial"])
 @pytest.mark.parametrize("full", [1, 2])
 def test_two_long_neighbours(how, full):
@@ -77,14 +119,7 @@ def test_two_long_neighbours(how, full):
         m = rb.radial_mask_build(40, 3600, 128, 1, 0, extra_tokens=N - 40 * 3600)
     g = torch.Generator(device="cuda").manual_seed(H)
     q, k, v = (torch.randn((1, H, N, D), device="cuda", generator=g).bfloat16() for _ in range(3))
-    out, traced = torch.empty_like(q), torch.empty_like(q)
-    rb.radial_attn_fwd(q, k, v, out, None, m, D ** -0.5)
-    trace = torch.zeros((rb.radial_attn_fwd_trace_records(1, H, m), 3), dtype=torch.int64, device="cuda")
-    rb.radial_attn_fwd_trace(q, k, v, traced, None, m, D ** -0.5, trace)
-    torch.cuda.synchronize()
-    assert torch.equal(out.view(torch.int16), traced.view(torch.int16))
-    t = trace.cpu().numpy()[:H * nb].reshape(H, nb, 3)
-    seconds = np.mean(t[:, 1::2, 0] == t[:, :nb // 2 * 2:2, 1])
+    out, seconds = pairs_of(rb, m, q, k, v, D ** -0.5)
     assert seconds > 0.5 if full == 1 else seconds < 0.1, seconds
     h, rows = H - 1, slice(N - 128, N)
     s = (D ** -0.5 * (q[0, h, rows].double() @ k[0, h].double().T)).softmax(1)   # the last block's list is full

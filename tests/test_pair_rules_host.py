@@ -26,8 +26,8 @@ def rules(tmp_path_factory):
     return run
 
 
-def case(n_blocks, sliced, ordered, mean, max_slice=0, codes=0, longest=0, shorter=0):
-    return (n_blocks, sliced, ordered, mean, max_slice or (n_blocks + 7) // 8, codes, longest or mean, (longest or mean) + (shorter or mean))
+def case(n_blocks, sliced, ordered, mean, max_slice=0, codes=0, longest=0, shorter=0, alike=1):
+    return (n_blocks, sliced, ordered, mean, max_slice or (n_blocks + 7) // 8, codes, longest or mean, (longest or mean) + (shorter or mean), alike)
 
 
 def test_fewer_than_8_blocks(rules):
@@ -51,6 +51,14 @@ def test_short_lists_by_slices(rules):
 def test_by_length(rules):
     """A whole round of pairs, lists of 64."""
     assert rules([case(110, 0, 10, 93), case(110, 0, 9, 93), case(110, 0, 10, 63), case(16384, 0, 1, 64), case(16385, 0, 1, 64)]) == [1, 0, 0, 1, 0]
+
+
+def test_lists_with_little_in_common(rules):
+    """Only where slices start half as many workgroups again as there are blocks, or heads have fewer than 8 blocks."""
+    cases = [(110, 0, 10, 93), (128, 32, 8, 40), (9, 282, 8, 2), (2, 132, 8, 1)]
+    assert [rules([case(*c, codes=codes, alike=0) for c in cases]) for codes in (0, 1)] == [[0, 0, 1, 1]] * 2
+    assert rules([case(*c) for c in cases]) == [1, 1, 1, 1]
+    assert rules([case(128, 32, 8, 5, s, alike=0) for s in (23, 24)]) == [0, 1]
 
 
 def test_two_long_neighbours(rules):
