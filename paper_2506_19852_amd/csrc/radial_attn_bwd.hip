@@ -1533,9 +1533,8 @@ int launch_dkdv_two(const BwdArgs& a, hipStream_t stream) {
 
 template <int BLK, bool kExact>
 int launch_dkdv_pairs(const BwdArgs& a, hipStream_t stream) {
-  // Two key blocks at a time above the sizes of a common launch.
   if constexpr (BLK == 128 && !kExact)
-    if (a.n_blocks <= kMaxOrdered && work_items(a.work_t, a.n_blocks) > 6 * kOneRound) return launch_dkdv_two(a, stream);
+    if (takes_key_pairs(a.work_t)) return launch_dkdv_two(a, stream);
   using T = PairTile<128, BLK>;
   const auto kernel = radial_bwd_dkdv_pairs_kernel<128, BLK, kExact>;
   static DeviceOnce configured;

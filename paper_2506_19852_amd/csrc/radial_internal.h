@@ -263,7 +263,7 @@ inline bool slices_leave_gaps(const WorkMap& w, int eighths) { return w.sliced >
 //     6 blocks 64 heads 32.6 / 40.0, 120 L 2 32.1 / 34.2, 180 85 / 88, 200 95.6 / 89.8, 400 183 / 151; 7 blocks 40 heads 32.5 / 43.3, 160 93 / 102, 350 L 2 89 / 96, L 7 200 / 203.
 //
 // Two neighbouring lists both at least twice as long as the others (text tokens) are one workgroup's in pairs, and the launch ends no sooner than it does: 1.13 of the time that either
-// takes alone (beside a list of the usual length a long one takes no longer than alone).  They start where the heads by length do, so the shorter of them counts against what a
+// takes alone.  They start where the heads by length do, so the shorter of them counts against what a
 // workgroup of a whole round has of those heads, or of the launch where all heads go by slices.  Single blocks / pairs, us, radial lists and 512 tokens of text unless said, that share in
 // brackets: by length 1 head x 1129 blocks [1.10] 4881 / 5537, 1 x 1690 (226 tokens) [0.91] 8090 / 8559, 1 x 1971 (226) [0.84] 9970 / 10177, 1 x 2252 (226) [0.79] 12418 / 12027, 2 x 565 (226) [0.78]
 // 3003 / 2982, 2 x 933 [0.60] 6538 / 6142, one long list of a pair 1 x 1127 (226) 4617 / 4052; the last heads by length: lists of 32 and two full ones 40 x 128 [1.9] 1503 / 1588, one 1480 /
@@ -289,6 +289,15 @@ inline bool takes_pairs(const WorkMap& w, bool codes = false) {
   if (w.sliced == 0) return w.alike && w.mean >= 64 && pairs >= kTwoRound;
   if (w.n_blocks >= 8) return slices_leave_gaps(w, w.alike ? 9 : 12) || (w.alike && (codes || w.mean >= 28));
   return w.n_blocks <= 2 || (w.n_blocks == 4 && pairs >= 256) || ((w.n_blocks == 5 || w.n_blocks == 6) && pairs >= 600);
+}
+
+// dK/dV, above the sizes of a common launch, whatever neighbouring lists share (the kernel sees that itself): lists of 7 entries, fewer than 8 blocks but for 3 and 7, whose last
+// pair is a block, or gaps among the slices.  Backward, one block / two, us, lists of L neighbouring entries: 40 heads x 128 blocks L 2 612 / 619, 3 717 / 731, 6 1091 / 1093, 8 1353 / 1336, 10 1596 /
+// 1581, 40 5462 / 5192; 16 x 929 L 2 1687 / 1728, 5 2774 / 2781, 10 4618 / 4542; 100 x 40 L 2 477 / 494, 5 770 / 771, 10 1314 / 1264; 200 x 16 L 2 401 / 408, 8 900 / 869; gaps: 400 x 9 L 2 599 / 494, 300 x 11 L 2 472 / 441,
+// 5 777 / 684, 220 x 15 (none) L 2 420 / 426; 1600 x 1 433 / 283, 800 x 2 532 / 332, 520 x 3 L 1 184 / 192, L 3 274 / 269, 400 x 4 L 1 240 / 212, 320 x 5 L 2 252 / 211, 260 x 6 L 2 226 / 201, 224 x 7 L 2 209 / 223, L 7 413 / 411.
+inline bool takes_key_pairs(const WorkMap& w) {
+  if (w.n_blocks > kMaxOrdered || work_items(w, w.n_blocks) <= 6 * kOneRound) return false;
+  return w.mean >= 7 || (w.n_blocks < 8 ? w.n_blocks != 3 && w.n_blocks != 7 : slices_leave_gaps(w, 9));
 }
 
 // ---- How many groups of waves share a list ------------------------------------------------------

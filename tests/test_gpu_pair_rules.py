@@ -1,5 +1,5 @@
-"""Forward at the edges of the rules that choose between single query blocks and pairs of them, bf16 and 8-bit scores: few blocks and short lists
-by slices, against float64."""
+"""At the edges of the rules that choose between single blocks and pairs of them, against float64: the forward, bf16 and 8-bit scores, and dK/dV; few blocks and
+short lists by slices, long neighbours, lists with little in common, batches, peaked rows, dq in the memory of q or dout."""
 import numpy as np
 import pytest
 
@@ -126,4 +126,43 @@ def test_two_long_neighbours(how, full):
     ref = s @ v[0, h].double()
     # P and out are rounded to bf16 (2^-9 each)
     assert (out[0, h, rows].double() - ref).norm() <= 8e-3 * ref.norm()
+    m.free()
+
+
+# dK/dV above 1536 blocks: lists of 6 and 7, 3 and 7 blocks, slices with gaps
+@pytest.mark.parametrize("B, H, nb, width, cut, gain, dq_in", [(2, 260, 3, 3, 127, 4.0, None), (1, 230, 7, 6, 33, 1.0, "dout"), (2, 115, 7, 7, 1, 4.0, "q"), (2, 20, 40, 6, 64, 4.0, "q"),
+                                                               (2, 20, 40, 7, 95, 4.0, "dout"), (1, 400, 4, 1, 3, 4.0, "q"), (2, 150, 9, 2, 65, 4.0, "dout"), (3, 8, 131, 40, 31, 4.0, "q")])
+def test_key_blocks(B, H, nb, width, cut, gain, dq_in):
+    import torch
+    from paper_2506_19852_amd import binding as rb
+    print(f"keys B={B} H={H} nb={nb} width={width} cut={cut} gain={gain} dq in {dq_in}", flush=True)
+    D, N = 128, 128 * nb - cut
+    g = torch.Generator(device="cuda").manual_seed(N + H)
+    q, k, v, do = (torch.randn((B, N, H, D), device="cuda", generator=g).transpose(1, 2) for _ in range(4))
+    q, k, v, do = (q * gain).bfloat16(), k.bfloat16(), v.bfloat16(), do.bfloat16()
+    lists = band(nb, width)
+    m = rb.radial_mask_from_csr(N, 128, np.arange(nb + 1, dtype=np.int32) * width, np.concatenate(lists).astype(np.int32), rb.RADIAL_MASK_TRANSPOSE)
+    out, dq, dk, dv = (torch.full_like(q, float("nan")) for _ in range(4))
+    lse = torch.full((B, H, N), float("nan"), dtype=torch.float32, device="cuda")
+    ws = torch.empty(rb.radial_attn_bwd_workspace(B, H, N, D, m), dtype=torch.uint8, device="cuda")
+    scale = D ** -0.5
+    rb.radial_attn_fwd(q, k, v, out, lse, m, scale)
+    rb.radial_attn_bwd(q, k, v, out, do, lse, dq, dk, dv, m, scale, ws)
+    if dq_in:
+        shared = {"q": q, "dout": do, dq_in: (q if dq_in == "q" else do).clone(memory_format=torch.preserve_format)}
+        again = [torch.full_like(q, float("nan")) for _ in range(2)]
+        rb.radial_attn_bwd(shared["q"], k, v, out, shared["dout"], lse, shared[dq_in], *again, m, scale, ws)
+        for x, y in zip((dq, dk, dv), (shared[dq_in], *again)):
+            assert torch.equal(x, y)
+    vis = torch.zeros((nb, nb), dtype=torch.bool)
+    for r, c in enumerate(lists):
+        vis[r, torch.from_numpy(c)] = True
+    vis = vis.cuda().repeat_interleave(128, 0).repeat_interleave(128, 1)[:N, :N]
+    for bh in sorted({0, H - 1, (B - 1) * H, B * H - 9, B * H - 8, B * H - 1}):
+        b, h = divmod(bh, H)
+        want = reference(q[b, h], k[b, h], v[b, h], do[b, h], vis, scale)[2:]
+        for name, x, ref in zip(("dq", "dk", "dv"), (dq, dk, dv), want):
+            # P and dS are rounded to bf16 between the products and the results once more, 2^-9 each; delta comes from the rounded output
+            assert (x[b, h].double() - ref).norm() <= 1.2e-2 * ref.norm() + 1e-6, (bh, name, float((x[b, h].double() - ref).norm() / ref.norm()))
+    assert all(torch.isfinite(x).all() for x in (dq, dk, dv))
     m.free()

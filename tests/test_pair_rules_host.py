@@ -79,3 +79,12 @@ def test_two_long_neighbours(rules):
     assert rules([case(929, 6, 2, 66, longest=x) for x in (718, 719)] + [case(929, 6, 0, 66, longest=929)]) == [1, 0, 1]
     # fewer than 8 blocks: one list can be no longer than the others by much
     assert rules([case(2, 132, 8, 1, longest=2, shorter=2), case(4, 120, 8, 1, longest=4, shorter=4)]) == [1, 1]
+
+
+def test_key_blocks(rules):
+    """Above 1536 blocks: lists of 7 entries, fewer than 8 blocks but for 3 and 7, slices that leave gaps."""
+    def keys(*c, s=0):
+        return case(*c, s, 2)
+    assert rules([keys(128, 4, 8, 7), keys(128, 5, 8, 6), keys(128, 5, 8, 7), keys(129, 0, 12, 7), keys(16384, 1, 0, 7), keys(16385, 1, 0, 7)]) == [0, 0, 1, 1, 1, 0]
+    assert rules([keys(nb, 1600, 8, 1) for nb in range(1, 8)] + [keys(7, 400, 8, 7)]) == [1, 1, 0, 1, 1, 1, 0, 1]
+    assert rules([keys(nb, 300, 8, 2) for nb in (8, 9, 14, 15, 16, 17)] + [keys(9, 0, 175, 2)]) == [0, 1, 1, 0, 0, 1, 0]
