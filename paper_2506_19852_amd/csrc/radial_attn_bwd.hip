@@ -496,7 +496,7 @@ __global__ void __launch_bounds__(2 * BLK / R * S, 2) radial_bwd_dkdv_two_kernel
 //   stage u:  first wave   S(u), P(u) -> LDS, dV += P(u)^T dO(u)
 //             second wave  dS(u - 1) = P(u - 1) * (dP(u - 1) - delta), dP(u), dK += dS(u - 1)^T Q(u - 1)
 // so Q has three stage buffers and dO two, and the vector part of one wave falls on the matrix part of the other.
-// Wave w and wave w + kPairs share keys: they are on one SIMD.  206 registers (233 under the token rule; beside dQ in one launch 250
+// Wave w and wave w + kPairs share keys: they are on one SIMD.  200 registers (228 under the token rule; beside dQ in one launch 250
 // and 256), and a pair that sees nothing of a stage skips it, which one wave with four products had no registers for.
 // The chip lowers its clock for the busier matrix pipes (8 x 126 360 tokens, radial lists: 46 % busy at 2.05 GHz -> 54 % at 1.87), so the large
 // launches gain least.  Backward pass, one wave with four products / pairs: 8 x 126 360 tokens 82.5 / 80.3 ms, 5 x 14 040 1728 / 1653 us,
@@ -537,7 +537,6 @@ __device__ __forceinline__ void pairs_body(const BwdArgs& a, int32_t bh, int32_t
   const int lq = lane & 31;
   const int g = lane >> 5;
   const int i16 = lane & 15;
-  const int half16 = (lane >> 4) & 1;
 
   const int32_t b = bh / a.H, h = bh % a.H;
   const __bf16* qp = (const __bf16*)a.q.ptr + (int64_t)b * a.q.sb + (int64_t)h * a.q.sh;
@@ -861,7 +860,7 @@ __device__ __forceinline__ void pairs_item(const BwdArgs& a, uint32_t id) {
 // and Q, dO and the row statistics go round three buffers.  The lists are walked in three passes, as in the forward over pairs of query blocks
 // (radial_attn_fwd_two.h): entries of both, of the first alone, of the second alone; lists with too little in common are walked one after the other, each
 // by the pairs of waves for one block, which also take the last blocks of a launch singly.  All loops are written out for either kind of wave and
-// either set of keys: with accumulators that pass a branch or move between registers the compiler spilled 36 to 580 bytes a lane.  252 registers.
+// either set of keys: with accumulators that pass a branch or move between registers the compiler spilled 36 to 580 bytes a lane.  255 registers.
 // 40 heads x 126 360 tokens, radial lists: 226.6 -> 207.9 ms, the matrix pipes 58 % busy at 1.91 GHz (one block 54 % at 1.87).  Training steps, one
 // block / two, us: 3 x 118 800 tokens 40 240 / 39 100, 20 x 32 760 all-ones list 41 600 / 39 900, 10 x 25 600 narrow bands 13 240 / 12 630, 16 x 12 800 4370 / 4212, 400 x 1024 1136 /
 // 1104, 800 x 512 997 / 808, 1000 x 256 742 / 463 (heads of few blocks: no workgroups without work); random lists of a quarter of the blocks 9085 / 9134.

@@ -432,16 +432,16 @@ __global__ void __launch_bounds__(2 * BLK / R * S, (BLK / R / 32 * S + 3) / 4) r
   fp8_item<S, R>(a);
 }
 
-// Pairs of query blocks (the header of radial_attn_fwd_two.h has the reasons), single ones at the end.  Here the vector unit is the bound rather
-// than the matrix pipes, and two waves per SIMD whose softmax is dealt among the matrix instructions keep it as busy as the three of the
-// kernel for single blocks, with half the copies and LDS reads.  Forward with the quantisation, ms, single blocks / pairs: 24 x 118 800 tokens 63.6 / 55.6, 40 x 32 760
+// Pairs of query blocks (the header of radial_attn_fwd_two.h has the reasons), single ones at the end.  Two waves per SIMD whose softmax is dealt among the matrix
+// instructions need a sixth fewer vector instructions than the three of the kernel for single blocks, and half the copies and LDS reads: 24 x 118 800 tokens, single blocks / pairs,
+// vector unit 75 / 67 % and matrix pipes 52 / 54 % busy at 1.72 / 1.86 GHz.  Forward with the quantisation, ms, single blocks / pairs: 24 x 118 800 tokens 63.6 / 55.6, 40 x 32 760
 // 11.7 / 10.5, 3 x 118 800 8.19 / 7.30, 10 x 14 040 0.763 / 0.703, 400 x 2048 0.921 / 0.892.
 __global__ void __launch_bounds__(2 * BLK, 2) radial_fwd_fp8_two_kernel(const Fp8FwdArgs a, const TwoMap m) {
   constexpr int kBytes = fwd::TwoTile<true>::kLdsBytes;
   TwoItem item;
   if (!two_item(a.work, m, blockIdx.x, item)) return;
   const int32_t qb = 2 * item.pair + item.block;
-  if (item.form == TwoItem::kPair) fwd::two_body<false>(a, item.bh, qb, m.c, fwd::static_lds<Fp8Key, kBytes>());
+  if (item.form == TwoItem::kPair) fwd::two_body<false>(a, item.bh, qb, m.c, 0, fwd::static_lds<Fp8Key, kBytes>());
   else fp8_body<1, 1, kBytes>(own_args<Fp8FwdArgs>(), item.bh, qb, 0);
 }
 

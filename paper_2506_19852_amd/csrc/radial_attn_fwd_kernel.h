@@ -84,11 +84,11 @@ template <int D, int BLK, bool kExact, bool kTrace, int kShared>
 struct FwdKey {};
 
 // One record per (head, query block), by the first thread of the workgroup with its first rows: begin, end, where it ran.  Returns the end.
-__device__ __forceinline__ uint64_t write_trace(const FwdArgs& a, uint64_t begin, int32_t bh, int32_t qb) {
+__device__ __forceinline__ uint64_t write_trace(const FwdArgs& a, uint64_t begin, int64_t record) {
   // hardware id registers: which XCD, shader engine and compute unit this workgroup ran on
   constexpr int kHwId = 4, kXccId = 20, kAllBits = 31 << 11;
   const uint64_t where = ((uint64_t)__builtin_amdgcn_s_getreg(kXccId | kAllBits) << 32) | (uint32_t)__builtin_amdgcn_s_getreg(kHwId | kAllBits);
-  uint64_t* rec = a.wg_trace + 3 * ((int64_t)bh * a.n_blocks + qb);
+  uint64_t* rec = a.wg_trace + 3 * record;
   const uint64_t end = __builtin_amdgcn_s_memrealtime();
   rec[0] = begin;
   rec[1] = end;
@@ -102,7 +102,7 @@ __device__ __forceinline__ uint64_t write_trace(const FwdArgs& a, uint64_t begin
 // the library's radial_attn_fwd launches kTrace = false, which carries none of it).
 // kShared: bytes of the static stage buffers of a kernel that has several forms, 0: this is its only one.
 template <int D, int BLK, bool kExact, bool kTrace, int S, int R, int kShared>
-__device__ __forceinline__ void fwd_body(const FwdArgs& a, int32_t bh, int32_t qb, int32_t part) {
+__device__ __forceinline__ void fwd_body(const FwdArgs& a, int32_t bh, int32_t qb, int32_t part, int64_t record) {
   using T = Tile<D, BLK, S, R>;
   using Key = FwdKey<D, BLK, kExact, kTrace, kShared>;
   constexpr bool kStatic = S == 1 || kShared;
@@ -404,7 +404,7 @@ __device__ __forceinline__ void fwd_body(const FwdArgs& a, int32_t bh, int32_t q
       if (a.lse && g == 0) store_lse(m_run, l_tot);
     }
   }
-  if (kTrace && a.wg_trace != nullptr && threadIdx.x == 0 && part == 0) write_trace(a, t_begin, bh, qb);
+  if (kTrace && a.wg_trace != nullptr && threadIdx.x == 0 && part == 0) write_trace(a, t_begin, record);
 }
 
 template <int D, int BLK, bool kExact, bool kTrace, int S, int R>
@@ -415,7 +415,7 @@ __global__ void __launch_bounds__(2 * BLK / R * S, 2) radial_fwd_kernel(const Fw
   if (!work_item(a.work, blockIdx.x, bh, qb)) return;
   const int32_t part = R == 1 ? 0 : bh % R;  // with R > 1 the work map counts R heads for each
   if (R > 1) bh /= R;
-  fwd_body<D, BLK, kExact, kTrace, S, R, 0>(a, bh, qb, part);
+  fwd_body<D, BLK, kExact, kTrace, S, R, 0>(a, bh, qb, part, R == 1 ? (int64_t)blockIdx.x : (int64_t)bh * a.n_blocks + qb);
 }
 
 // Whole blocks, and the last a.work.halved of the launch in halves of two groups.
@@ -426,11 +426,11 @@ __global__ void __launch_bounds__(2 * BLK, 2) radial_fwd_halves_kernel(const Fwd
   constexpr int kBytes = Tile<D, BLK, 1, 1>::kLdsBytes;
   if (blockIdx.x < whole) {
     if (!work_item(a.work, blockIdx.x, bh, qb)) return;
-    fwd_body<D, BLK, kExact, kTrace, 1, 1, kBytes>(a, bh, qb, 0);
+    fwd_body<D, BLK, kExact, kTrace, 1, 1, kBytes>(a, bh, qb, 0, (int64_t)blockIdx.x);
   } else {
     const uint32_t id = halved_item(blockIdx.x, whole, (uint32_t)a.work.halved, part);
     if (!work_item(a.work, id, bh, qb)) return;
-    fwd_body<D, BLK, kExact, kTrace, 2, 2, kBytes>(a, bh, qb, part);
+    fwd_body<D, BLK, kExact, kTrace, 2, 2, kBytes>(a, bh, qb, part, (int64_t)id);
   }
 }
 

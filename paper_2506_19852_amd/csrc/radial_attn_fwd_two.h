@@ -3,8 +3,9 @@
 //
 // One workgroup of four waves takes the query blocks 2p and 2p + 1, and wave w of it owns 32 rows of either, so that a key block which both
 // lists name is copied into LDS once for 256 query rows and every K and V fragment read from LDS feeds two MFMAs.  These kernels run at the
-// chip's power cap, and both are energy that is no arithmetic: with the copies and the LDS reads halved the clock rises from 1.60 to
-// 1.73 GHz at the same 62 % of matrix-pipe cycles (24 heads x 118 800 tokens, radial lists).  Two workgroups share a compute unit, the two waves of
+// chip's power cap, and both are energy that is no arithmetic, and cycles: with the copies and the LDS reads halved the clock rises and fewer cycles are
+// needed, by much the same share.  24 heads x 118 800 tokens, one block / two in turn on one box, by the counters: radial lists 74.2 / 65.8 ms, 1.64 / 1.75 GHz, the
+// matrix pipes 61.5 / 65.1 % busy; all-ones list 152.8 / 135.7 ms, 1.69 / 1.81 GHz, 64.0 / 67.4 %.  Two workgroups share a compute unit, the two waves of
 // a SIMD belong to different ones and so drift into each other's gaps: as one workgroup of eight waves of 32 rows, tied by its barrier, the same
 // sharing gained nothing, and so did 64 rows of one block per wave in workgroups of two waves (half the LDS reads, the same copies: 0.99).
 //
@@ -12,11 +13,12 @@
 // passes, the entries of both lists, then those of the first alone and those of the second alone: three loops of their own, of which the
 // last two are one piece of code (the second set of rows moves into the registers of the first).  With one loop that branches at every
 // entry the compiler moves accumulators between the branches and spills 800 bytes a lane.  A pass over one list alone works like the
-// kernel for single blocks, so lists that have nothing in common are no slower (random lists of 10 to 90 % of the blocks: 0.97-1.00).
+// kernel for single blocks; lists that have little in common gain nothing, and short ones lose (takes_pairs in radial_internal.h).
 //
-// Registers are what limits it: 128 of O, 64 of Q, 32 of scores, 12 of fragments in flight, and 11 for all the rest.  So
+// Registers are what limits it: 128 of O, 64 of Q, 32 of scores, 12 of fragments in flight, and 20 for all the rest.  So
 // - K and V lie in LDS four rows at a time, rows in turn every 64 bytes, with 16 bytes between one four and the next: both kinds of reads are free of
-//   bank conflicts, as with the swizzle, but all pieces of a tile are at constant distances from one address per lane;
+//   bank conflicts, as with the swizzle, but all pieces of a tile are at constant distances from one address per lane (the conflicts that the counters show, 0.2 % of the LDS
+//   instructions, are the bitmaps' atomics, up to 32 lanes to a word: four times as many on an all-ones list);
 // - values of rare use (the lane's number, addresses of a ragged stage, the store) are worked out again where they are needed;
 // - strides and pointers that only the store needs are loaded again there, and the three forms of the kernel load their arguments each for itself;
 // - sums and packed P are pinned where they are written, or the compiler keeps the 32 values of P until it needs their sum.
@@ -43,7 +45,7 @@ struct TwoTile {
 
 // Query blocks qb and qb + 1 (which may not exist).
 template <bool kTrace, class Args>
-__device__ __forceinline__ void two_body(const Args& a, int32_t bh, int32_t qb, float c, char* lds_all) {
+__device__ __forceinline__ void two_body(const Args& a, int32_t bh, int32_t qb, float c, int64_t record, char* lds_all) {
   constexpr bool kFp8 = std::is_same_v<Args, Fp8FwdArgs>;
   using T = TwoTile<kFp8>;
   const int lane = threadIdx.x & 63;
@@ -460,7 +462,7 @@ __device__ __forceinline__ void two_body(const Args& a, int32_t bh, int32_t qb, 
       if (late.lse && g2 == 0) late.lse[(int64_t)bh * late.N + q_row] = l_tot > 0.f ? m_run[0] * late.scale + __logf(l_tot) : -INFINITY;
     }
     if constexpr (kTrace)
-      if (a.wg_trace != nullptr && threadIdx.x == 0 && qb + set < a.n_blocks) t_begin = write_trace(a, t_begin, bh, qb + set);
+      if (a.wg_trace != nullptr && threadIdx.x == 0 && qb + set < a.n_blocks) t_begin = write_trace(a, t_begin, record + 8 * set);
 #pragma unroll
     for (int dt = 0; dt < T::kDTiles; ++dt) o[0][dt] = o[1][dt];
 #pragma unroll
@@ -478,9 +480,9 @@ __global__ void __launch_bounds__(256, 2) radial_fwd_two_kernel(const FwdArgs a,
   TwoItem item;
   if (!two_item(a.work, m, blockIdx.x, item)) return;
   const int32_t qb = 2 * item.pair + item.block;
-  if (item.form == TwoItem::kPair) two_body<kTrace>(a, item.bh, qb, m.c, static_lds<FwdKey<128, 128, false, kTrace, kBytes>, kBytes>());
-  else if (item.form == TwoItem::kBlock) fwd_body<128, 128, false, kTrace, 1, 1, kBytes>(own_args<FwdArgs>(), item.bh, qb, 0);
-  else fwd_body<128, 128, false, kTrace, 2, 2, kBytes>(own_args<FwdArgs>(), item.bh, qb, item.half);
+  if (item.form == TwoItem::kPair) two_body<kTrace>(a, item.bh, qb, m.c, item.record, static_lds<FwdKey<128, 128, false, kTrace, kBytes>, kBytes>());
+  else if (item.form == TwoItem::kBlock) fwd_body<128, 128, false, kTrace, 1, 1, kBytes>(own_args<FwdArgs>(), item.bh, qb, 0, item.record);
+  else fwd_body<128, 128, false, kTrace, 2, 2, kBytes>(own_args<FwdArgs>(), item.bh, qb, item.half, item.record);
 }
 
 template <bool kTrace>

@@ -57,7 +57,7 @@ using namespace radial;
 
 extern "C" int64_t radial_attn_fwd_trace_records(int32_t B, int32_t H, const radial_mask* mask) {
   if (!mask || B < 1 || H < 1) return 0;
-  return 8LL * B * H * mask->max_slice;  // as work_grid_bound, for any B and H
+  return trace_records((int64_t)B * H, mask->max_slice);
 }
 
 extern "C" int radial_attn_fwd_trace(int32_t B, int32_t H, int32_t N, int32_t D, radial_tensor q, radial_tensor k,

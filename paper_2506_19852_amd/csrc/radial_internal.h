@@ -185,6 +185,8 @@ inline WorkMap make_work_map(const radial_mask* m, Walk walk, int32_t heads, int
   w.n_blocks = m->n_blocks;
   return w;
 }
+// Records of a trace: one for every block of every head, by workgroup; pairs of blocks take an even number of every slice.
+inline int64_t trace_records(int64_t heads, int32_t max_slice) { return 8 * heads * (max_slice + (max_slice & 1)); }
 // (head, block) pairs of a launch, its workgroups, and the most workgroups that any division of the heads could start.
 inline int64_t work_grid_bound(const WorkMap& w) { return 8LL * (w.sliced + w.ordered) * w.max_slice; }
 inline int64_t work_items(const WorkMap& w, int32_t n_blocks) { return (int64_t)(w.sliced + w.ordered) * n_blocks; }
@@ -207,14 +209,19 @@ constexpr uint32_t kTwoRound = 512;  // workgroups that the chip holds
 // Forward, us, single blocks / 512 pairs, 76 blocks / 512, the last 38 in halves / 448, 38 / 256, 38: 10 heads x 14 040 tokens 829 / 794 / 769 / 776 / 820.
 // 3 heads x 119 026 (1395 pairs) 8080 / 1024 pairs 7750, the last 80 in halves 7570, 192 7830, 256 8000; 1136 pairs, 64 in halves 7570, 1280 8060.  With
 // slices 40 heads x 32 760 (1024 ordered pairs), none / 512 / 768 of them as pairs 13010 / 12980 / 12960, 24 x 118 800 70.2 / 69.9 / 69.8 ms.
-// 8-bit scores, which have no halves here: what is left over goes singly up to 192 pairs, and beyond 256, a pair for each compute unit, what is
-// above them up to 384; with slices 128 pairs.  Single blocks / the best of 0, 64 .. 256 pairs taken singly / this rule, us (pairs in order of length, left over above rounds): 550 (38)
+// Over 15 more launches without slices (540 to 1395 pairs) and 8 with them it is faster than single blocks and 0 to 4.5 % behind the best of none, 128 and 256 pairs singly and of 0, 32 and 128
+// of them in halves (836 pairs 2927 us, 128 singly 2794; 1000 pairs 6458, none singly 6249; 1140 pairs 11153, no halves 10813; single blocks 2979, 6625, 11790).
+// 8-bit scores, which have no halves here: what is left over above rounds of 512 goes singly up to 192 pairs, none up to 256, a pair for each compute unit, what is above those up to
+// 384 but at least 64, none beyond; with slices 128 pairs.  At either side of each step (1, 2 and 4 heads, 150 to 460 left over, 78 launches, and 34 others) that is within 2 % of the best of 0,
+// 64, 128, 192, all and all above 256, but for 240 to 250 at one head (3 %): 192 / 195 left over 5662 / 6143 us (none singly 5688 / 6084, all 5705 / 6025), 256 / 258 6306 / 6931 (6328 / 6970, 64 6595 /
+// 6910), 384 / 387 8292 / 9495 (8984 / 9556, 128 8328 / 9442); single blocks 6227 / 6464, 6900 / 7793, 9593 / 10095: it is the next round that makes the steps.  Single blocks / the best of 0, 64 .. 256 pairs taken singly / this rule, us (pairs in order of length, left over above rounds): 550 (38)
 // 763 / 706 / 703, 600 (88) 769 / 727 / 721, 660 (148) 930 / 891 / 891, 700 (188) 990 / 932 / 932, 740 (228) 1146 / 1073 / 1076, 800 (288) 1638 / 1387 / 1390, 832 (320) 1762 / 1530 /
 // 1535, 900 (388) 1645 / 1487 / 1471, 1024 (0) 2265 / 2115 / 2098, 1395 (371) 8190 / 7353 / 7297; none singly: 550 800, 800 1525, 1395 8010.
 //
 // dK/dV, a workgroup to a compute unit: what is left over above rounds of 256 goes singly up to 128 pairs, 64 up to 208, none above.  Single blocks / 0, 64, 128 pairs
 // singly, us, training steps: 800 pairs (32 left over) of lists of 20 1229 / 1238, 1188, 1186, radial 6127 / 6210, 5998, 6002, 4370 / 4356, 4212, 4221; 1212 (188) 10750 / 10640,
-// 10656, 10636, with text 15370 / 15820, 15490, 15500; 1000 (232) 13240 / 12625, 12780, 12788; 40 heads x 126 360 tokens 480 / 466, 467, 467 ms.
+// 10656, 10636, with text 15370 / 15820, 15490, 15500; 1000 (232) 13240 / 12625, 12780, 12788; 1290 (10) 18353 / 18016, 18096, 17510 (this rule 18140).  128 with slices is hardly better than
+// any other number: 40 heads x 126 360 tokens 480 / 466, 467, 467 ms, backward of 20 x 32 760 22.5 / 21.8, 21.6, 21.5, 40 x 14 040 11.3 / 10.8, 10.8, 10.75, 24 x 21 600 14.3 / 13.4, 13.5, 13.5.
 enum class TwoWalk { kForward, kCodes, kKeyGrad };
 inline TwoMap make_two_map(const WorkMap& w, const int32_t* pair_order, float scale, TwoWalk walk) {
   TwoMap m;
@@ -242,7 +249,7 @@ inline TwoMap make_two_map(const WorkMap& w, const int32_t* pair_order, float sc
   }
   m.n_half = walk != TwoWalk::kForward ? 0u : rest < 64u ? rest : 64u;
   m.n_one = rest - m.n_half;
-  m.n_two = m.n_sliced + ordered - rest;
+  m.n_two = m.n_sliced + ordered - rest;  // in the forward a multiple of 8
   return m;
 }
 // A head of n blocks by slices starts at least 8 workgroups, 8 * max_slice, of which those beyond n have no work; pairs have no such gaps.  Whether there are
@@ -550,7 +557,7 @@ struct FwdArgs {
   int32_t B, H, N, n_blocks;
   float scale;
   TokenRule rule;
-  uint64_t* wg_trace;  // null, or [B * H * n_blocks][3]: begin, end (100 MHz clock), where the workgroup ran
+  uint64_t* wg_trace;  // null, or [trace_records][3]: begin, end (100 MHz clock), where the workgroup ran
   const int32_t* pair_order;  // pairs of query blocks by falling length; null only if work.ordered == 0
 };
 

@@ -372,6 +372,8 @@ __device__ __forceinline__ uint32_t halved_item(uint32_t id, uint32_t first, uin
 struct TwoItem {
   enum Form { kPair, kBlock, kHalf } form;
   int32_t bh, pair, block, half;
+  int64_t record;  // of a trace: of the block, or of a pair's first, whose second has the one 8 further; its index and the workgroup's are the same modulo 8, but for the
+                   // last pairs in halves where their number is no multiple of 8
 };
 
 // Workgroup `id` of those that share `count` items, 1 << kLog of them each: item and part.  All parts of an item are on one XCD while 8
@@ -391,6 +393,7 @@ __host__ __device__ __forceinline__ uint32_t split_item(uint32_t id, uint32_t co
 __host__ __device__ __forceinline__ bool two_item(const WorkMap& w, const TwoMap& m, uint32_t id, TwoItem& item) {
   item.form = TwoItem::kPair;
   item.block = item.half = 0;
+  item.record = 16 * (int64_t)(id >> 3) + (id & 7u);
   uint32_t pair_id = id;
   if (id >= m.n_two) {
     const uint32_t single = id - m.n_two;
@@ -400,11 +403,14 @@ __host__ __device__ __forceinline__ bool two_item(const WorkMap& w, const TwoMap
       item.form = TwoItem::kBlock;
       k = split_item<1>(single, m.n_one, part);
       item.block = part;
+      item.record = 2 * (int64_t)m.n_two + single;
     } else {
       item.form = TwoItem::kHalf;
       k = m.n_one + split_item<2>(single - 2u * m.n_one, m.n_half, part);
       item.block = part >> 1;
       item.half = part & 1;
+      const uint32_t at = k - m.n_one, eights = at & ~7u;
+      item.record = 2 * (int64_t)(m.n_two + m.n_one + eights) + (uint32_t)item.block * (m.n_half - eights < 8u ? m.n_half - eights : 8u) + (at & 7u);
     }
     pair_id = m.n_two + k;
   }

@@ -1,7 +1,7 @@
 // Which workgroup of a forward over pairs of query blocks takes what (radial_tile.h, radial_internal.h) on the host: for each input line
 //   n_blocks sliced ordered mean walk slice[0] .. slice[8]   (walk 0: forward, 1: with 8-bit scores, 2: dK/dV)
-// (the order of the pairs is their index, reversed) "takes_pairs grid", then a line "bh block half form" for every workgroup that
-// has work (form 0: block and block + 1, 1: a block, 2: half of one) and a line "end".
+// (the order of the pairs is their index, reversed) "takes_pairs grid records", then a line "bh block half form record" for every workgroup that
+// has work (and its number; form 0: block and block + 1, 1: a block, 2: half of one) and a line "end".
 #include <stdio.h>
 
 #include <vector>
@@ -26,10 +26,10 @@ int main() {
     for (size_t i = 0; i < order.size(); ++i) order[i] = (int32_t)(order.size() - 1 - i);
     const TwoMap m = make_two_map(w, order.data(), 1.f, codes == 0 ? TwoWalk::kForward : codes == 1 ? TwoWalk::kCodes : TwoWalk::kKeyGrad);
     const uint32_t grid = m.n_two + 2 * m.n_one + 4 * m.n_half;
-    printf("%d %u\n", takes_pairs(w) ? 1 : 0, grid);
+    printf("%d %u %lld\n", takes_pairs(w) ? 1 : 0, grid, (long long)trace_records(w.sliced + w.ordered, w.max_slice));
     for (uint32_t id = 0; id < grid; ++id) {
       TwoItem item;
-      if (two_item(w, m, id, item)) printf("%d %d %d %d\n", item.bh, 2 * item.pair + item.block, item.half, (int)item.form);
+      if (two_item(w, m, id, item)) printf("%d %d %d %d %lld %u\n", item.bh, 2 * item.pair + item.block, item.half, (int)item.form, (long long)item.record, id);
     }
     printf("end\n");
   }

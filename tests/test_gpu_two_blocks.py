@@ -153,7 +153,8 @@ def test_trace_of_pairs(H, nb):
     used = t[:, 1] != 0
     assert int(used.sum()) == H * nb
     assert np.all(t[used, 1] >= t[used, 0]) and np.all(t[~used] == 0)
-    ends = set(t[used, 1].tolist())
-    in_pairs = sum(int(b) in ends for b in t[used, 0])   # a tick is 10 ns: others begin at another's end by chance only
-    assert in_pairs >= H * nb // 4 if nb != 3 else in_pairs < H
+    in_pairs = int(np.sum((t[8:, 0] == t[:-8, 1]) & (t[8:, 0] != 0)))   # a pair's records are 8 apart; a tick is 10 ns
+    assert in_pairs >= H * nb // 4 if nb != 3 else in_pairs < 8
+    # by the workgroup that wrote it, whose number modulo 8 is its XCD: but for the last pairs in halves where their number is no multiple of 8
+    assert np.mean((np.flatnonzero(used) & 7) == (t[used, 2] >> 32 & 0xf)) >= 0.95
     m.free()

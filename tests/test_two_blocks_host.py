@@ -1,5 +1,5 @@
 """Every block is taken once by a launch over pairs of query (or key) blocks: whole pairs, single blocks and halves of blocks, by slices and
-by length, for even and odd numbers of blocks and slices of any length."""
+by length, for even and odd numbers of blocks and slices of any length, and every block has a trace record of its own."""
 import os
 import random
 import shutil
@@ -46,16 +46,22 @@ CASES = [(nb, sliced, ordered, 100, slices(nb), *codes) for codes in ((), (1,), 
 
 
 def test_every_block_is_taken_once(launches):
-    for case, (_, items) in zip(CASES, launches(CASES)):
+    for case, ((_, _, records), items) in zip(CASES, launches(CASES)):
         nb, sliced, ordered = case[:3]
         taken = {}
-        for bh, block, half, form in items:
+        for bh, block, half, form, *_ in items:
             for part in [(bh, block, h) for h in (0, 1)] + [(bh, block + 1, h) for h in (0, 1)] if form == 0 else [(bh, block, 0), (bh, block, 1)] if form == 1 else [(bh, block, half)]:
                 assert part not in taken, (case, part)
                 taken[part] = form
         want = {(bh, block, half) for bh in range(sliced + ordered) for block in range(nb) for half in (0, 1)}
         assert want <= set(taken), (case, sorted(want - set(taken))[:5])
         assert all(block == nb and nb % 2 for _, block, _ in set(taken) - want), case    # the block after an odd last one is in no list
+        if len(case) > 5:     # only the bf16 forward is traced
+            continue
+        written = [r for _, block, half, form, record, _ in items if half == 0 for r in ([record, record + 8] if form == 0 and block + 1 < nb else [record])]
+        assert len(written) == len(set(written)) == (sliced + ordered) * nb and min(written) >= 0 and max(written) < records, case
+        same = [record % 8 == workgroup % 8 for _, _, _, form, record, workgroup in items if form != 2]
+        assert all(same), case
 
 
 def test_rule(launches):
