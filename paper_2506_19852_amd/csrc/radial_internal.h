@@ -33,7 +33,7 @@ struct radial_mask {
   // Blocks by falling list length (null above kMaxOrdered blocks): the work order of short launches.
   int32_t* d_order = nullptr;    // [n_blocks]
   int32_t* d_order_t = nullptr;  // [n_blocks]
-  int32_t* d_pair_order = nullptr;  // [(n_blocks + 1) / 2]  pairs of query blocks 2p, 2p + 1 by falling length of both lists
+  int32_t* d_pair_order = nullptr;  // [(n_blocks + 1) / 2]  pairs of query blocks 2p, 2p + 1 by falling length of both lists (blocks of 128, without the token rule)
   int32_t* d_pair_order_t = nullptr;  // the same of key blocks
   int32_t max_slice = 0;         // longest slice, in blocks (host copy, sizes the grid)
   int32_t max_slice_t = 0;
@@ -558,7 +558,7 @@ struct FwdArgs {
   float scale;
   TokenRule rule;
   uint64_t* wg_trace;  // null, or [trace_records][3]: begin, end (100 MHz clock), where the workgroup ran
-  const int32_t* pair_order;  // pairs of query blocks by falling length; null only if work.ordered == 0
+  const int32_t* pair_order;  // pairs of query blocks by falling length; null where no kernel takes pairs (blocks of 64, token rule, above kMaxOrdered blocks)
 };
 
 int launch_fwd(int D, int block, const FwdArgs& a, hipStream_t stream);
@@ -602,7 +602,7 @@ struct BwdArgs {
   int32_t B, H, N, n_blocks;
   float scale;
   TokenRule rule;
-  const int32_t* pair_order_t;  // pairs of key blocks by falling length; null only if work_t.ordered == 0
+  const int32_t* pair_order_t;  // pairs of key blocks by falling length; null as in FwdArgs
 };
 
 int launch_bwd(int D, int block, const BwdArgs& a, hipStream_t stream);
