@@ -269,12 +269,12 @@ inline bool slices_leave_gaps(const WorkMap& w, int eighths) { return w.sliced >
 //     4 blocks 65 heads 21.9 / 30.4, 100 L 1 18.4 / 20.3, 128 L 1 23.1 / 19.7, L 4 40.0 / 32.8, 600 177 / 120; 5 blocks 53 heads 25.6 / 34.9, 120 47 / 51, 200 L 2 45.1 / 41.0, 400 141 / 121;
 //     6 blocks 64 heads 32.6 / 40.0, 120 L 2 32.1 / 34.2, 180 85 / 88, 200 95.6 / 89.8, 400 183 / 151; 7 blocks 40 heads 32.5 / 43.3, 160 93 / 102, 350 L 2 89 / 96, L 7 200 / 203.
 //
-// Two neighbouring lists both at least twice as long as the others (text tokens) are one workgroup's in pairs, and the launch ends no sooner than it does: 1.13 of the time that either
+// Two neighbouring lists far longer than the others (text tokens) are one workgroup's in pairs, and the launch ends no sooner than it does: 1.13 of the time that either
 // takes alone.  They start where the heads by length do, so the shorter of them counts against what a
 // workgroup of a whole round has of those heads, or of the launch where all heads go by slices.  Single blocks / pairs, us, radial lists and 512 tokens of text unless said, that share in
 // brackets: by length 1 head x 1129 blocks [1.10] 4881 / 5537, 1 x 1690 (226 tokens) [0.91] 8090 / 8559, 1 x 1971 (226) [0.84] 9970 / 10177, 1 x 2252 (226) [0.79] 12418 / 12027, 2 x 565 (226) [0.78]
-// 3003 / 2982, 2 x 933 [0.60] 6538 / 6142, one long list of a pair 1 x 1127 (226) 4617 / 4052; the last heads by length: lists of 32 and two full ones 40 x 128 [1.9] 1503 / 1588, one 1480 /
-// 1444, lists of 40 and two 20 x 256 [1.5] 1854 / 2164; 4 x 1804 [0.88] 36.3 / 32.2 ms, 24 x 114 [0.66] 2218 / 2138; all by slices 2 x 3633 [0.31] 52.1 / 55.6 ms, 2 x 2817 [0.35] 37.9 / 40.4, 3 x 2817
+// 3003 / 2982, 2 x 933 [0.60] 6538 / 6142, 3 x 359 (226) [0.81] 1827 / 1909, 3 x 363 [0.85] 1772 / 1880, 2 x 531 [0.95] 2380 / 2506, 4 x 269 [0.75] 1481 / 1497, 4 x 268 [0.72] 1534 / 1491, one long list of a pair 1 x 1127 (226) 4617 / 4052; the last heads by length: lists of 32 and two full ones 40 x 128 [1.9] 1503 / 1588, one 1480 /
+// 1444, lists of 40 and two 20 x 256 [1.5] 1854 / 2164; 4 x 1804 [0.88] 36.3 / 32.2 ms, 24 x 114 [0.66] 2218 / 2138; (beside slices they have to be twice the mean: few heads by length are less than a round of their own) all by slices 2 x 3633 [0.31] 52.1 / 55.6 ms, 2 x 2817 [0.35] 37.9 / 40.4, 3 x 2817
 // [0.24] 55.9 / 56.1, 4 x 3633 [0.16] 101 / 98, without text 2 x 3629 [0.08] 49.8 / 46.2.  8-bit scores: 1 x 1129 4176 / 4616, 1 x 1409 (226) [0.99] 5521 / 5785, 1 x 1690 7175 / 6988, 40 x 128 1386 /
 // 1429, 20 x 256 1732 / 1832, 2 x 3633 48.2 / 46.8 ms.
 // One long list that the whole launch waits for is slower beside a usual one in bf16: lists of 64 and a full one by length 4 x 929 [1.9]
@@ -282,7 +282,7 @@ inline bool slices_leave_gaps(const WorkMap& w, int eighths) { return w.sliced >
 inline bool long_lists_end_the_launch(const WorkMap& w, bool codes) {
   const int64_t shorter = w.longest_pair - w.longest, entries = (int64_t)w.n_blocks * w.mean;  // of a head
   if (!codes && w.ordered > 0 && w.longest >= 2LL * w.mean && 2LL * kTwoRound * w.longest > (w.sliced ? 6 : 3) * w.ordered * entries) return true;
-  if (shorter < 2LL * w.mean) return false;
+  if (w.sliced > 0 && shorter < 2LL * w.mean) return false;
   if (w.ordered == 0) return !codes && 5 * kTwoRound * shorter > w.sliced * entries;
   return 20 * kTwoRound * shorter > (codes ? 19 : w.sliced ? 20 : 16) * w.ordered * entries;
 }

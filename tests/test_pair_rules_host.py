@@ -62,7 +62,7 @@ def test_lists_with_little_in_common(rules):
 
 
 def test_two_long_neighbours(rules):
-    """Not where the shorter list of the longest pair, at least twice the mean, is more than a workgroup of a whole round has: by length 0.8 of it, 0.95 with 8-bit scores; the last
+    """Not where the shorter list of the longest pair (beside slices: at least twice the mean) is more than a workgroup of a whole round has: by length 0.8 of it, 0.95 with 8-bit scores; the last
     heads by length all of it; a fifth where all heads go by slices, 8-bit scores whatever it is."""
     def at(nb, sliced, ordered, mean, share, codes=0):
         shorter = int(share * (ordered or sliced) * nb * mean / 512)
@@ -72,6 +72,7 @@ def test_two_long_neighbours(rules):
     assert rules([at(1804, 3, 1, 582, x) for x in (0.88, 0.99, 1.01)]) == [1, 1, 0]
     assert rules([at(128, 32, 8, 33, x) for x in (0.99, 1.9)] + [at(128, 32, 8, 33, x, 1) for x in (0.94, 1.9)]) == [1, 0, 1, 0]
     assert rules([at(3633, 4, 0, 819, x) for x in (0.16, 0.19, 0.21)] + [at(3633, 2, 0, 819, 0.31, 1)]) == [1, 1, 0, 1]
+    assert rules([case(531, 0, 2, 269, longest=531, shorter=531), case(361, 0, 3, 200, longest=361, shorter=361)]) == [0, 0]    # less than twice the mean
     # neighbours that are not twice as long as the others, however short the launch; one long list beside a usual one
     assert rules([case(128, 32, 8, 33, longest=128, shorter=x) for x in (33, 65, 67, 128)] + [case(9, 282, 8, 2)]) == [1, 1, 0, 0, 1]
     # one long list beside usual ones: more than 1.5 of a workgroup's share by length, 3 for the last heads by length; not with 8-bit scores
