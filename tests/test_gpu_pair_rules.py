@@ -130,6 +130,35 @@ def test_two_long_neighbours(how, full):
     m.free()
 
 
+@pytest.mark.parametrize("how", ["csr", "radial"])
+def test_long_list_of_an_odd_last_block_is_among_the_first(how):
+    """In order of length the workgroups of the last block, which has no neighbour, are among the first eight ranks where its list is full, though two of the others are longer.
+    They are the ones whose second record is missing."""
+    import torch
+    from paper_2506_19852_amd import binding as rb
+    H, D, nb = (9, 128, 131) if how == "csr" else (4, 128, 269)
+    N = 128 * nb if how == "csr" else 24 * 1420 + 226
+    if how == "csr":
+        lists = band(nb, 80)
+        lists[-1] = np.arange(nb)
+        m = rb.radial_mask_from_csr(N, 128, np.concatenate([[0], np.cumsum([len(x) for x in lists])]).astype(np.int32), np.concatenate(lists).astype(np.int32))
+    else:
+        m = rb.radial_mask_build(24, 1420, 128, 1, 0, extra_tokens=226)
+    row_ptr, _ = rb.radial_mask_copy_to_host(m)
+    n = np.diff(row_ptr)
+    assert len(n) == nb and n[-1] == nb and n[-1] < np.sort(n[0:-1:2] + n[1::2])[10]
+    g = torch.Generator(device="cuda").manual_seed(H)
+    q, k, v = (torch.randn((1, H, N, D), device="cuda", generator=g).bfloat16() for _ in range(3))
+    trace = torch.zeros((rb.radial_attn_fwd_trace_records(1, H, m), 3), dtype=torch.int64, device="cuda")
+    rb.radial_attn_fwd_trace(q, k, v, torch.empty_like(q), None, m, D ** -0.5, trace)
+    torch.cuda.synchronize()
+    used = (trace[:, 1] != 0).cpu().numpy()
+    assert used.sum() == H * nb
+    first = used[:16 * H].reshape(H, 2, 8)      # the first 8 * H workgroups, eight at a time
+    assert first[:, 0].all() and (~first[:, 1]).sum() == H
+    m.free()
+
+
 # dK/dV above 1536 blocks: lists of 6 and 7, 3 and 7 blocks, slices with gaps
 @pytest.mark.parametrize("B, H, nb, width, cut, gain, dq_in", [(2, 260, 3, 3, 127, 4.0, None), (1, 230, 7, 6, 33, 1.0, "dout"), (2, 115, 7, 7, 1, 4.0, "q"), (2, 20, 40, 6, 64, 4.0, "q"),
                                                                (2, 20, 40, 7, 95, 4.0, "dout"), (1, 400, 4, 1, 3, 4.0, "q"), (2, 150, 9, 2, 65, 4.0, "dout"), (3, 8, 131, 40, 31, 4.0, "q")])
