@@ -33,7 +33,7 @@ struct radial_mask {
   // Blocks by falling list length (null above kMaxOrdered blocks): the work order of short launches.
   int32_t* d_order = nullptr;    // [n_blocks]
   int32_t* d_order_t = nullptr;  // [n_blocks]
-  int32_t* d_pair_order = nullptr;  // [(n_blocks + 1) / 2]  pairs of query blocks 2p, 2p + 1 by falling length of both lists (blocks of 128, without the token rule)
+  int32_t* d_pair_order = nullptr;  // [(n_blocks + 1) / 2]  pairs of query blocks 2p, 2p + 1 by falling length of both lists, an odd last block's counted twice (blocks of 128, without the token rule)
   int32_t* d_pair_order_t = nullptr;  // the same of key blocks
   int32_t max_slice = 0;         // longest slice, in blocks (host copy, sizes the grid)
   int32_t max_slice_t = 0;
